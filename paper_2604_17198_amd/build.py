@@ -19,7 +19,9 @@ LIB = os.path.join(PKG, "libnacho.so")
 # the same sources with -DNACHO_INSTRUMENT: every executing wavefront logs what it did (benchmarks, balance tests)
 LIB_INSTR = os.path.join(PKG, "libnacho_instr.so")
 
-SOURCES = ["api.hip", "partition.hip", "spmv.hip", "spmm.hip", "spadd.hip", "remap.hip", "validate.hip", "probe.hip"]
+SOURCES = ["api.hip", "partition.hip", "spmv.hip", "spmm.hip", "spadd.hip", "merge_vector.hip",
+           "merge_csr.hip", "merge_csr_product.hip", "merge_csr_mapped.hip", "merge_dcsr.hip", "merge_coo.hip",
+           "merge_csf3.hip", "remap.hip", "validate.hip", "probe.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

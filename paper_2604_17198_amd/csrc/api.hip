@@ -1,5 +1,6 @@
 // C-ABI entry points: argument checks, workspace carving, kernel sequencing.
 // Nothing here computes; every step of the hot path runs in the kernels.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -194,6 +195,9 @@ int compute_units()
 }
 
 // Workspace of a DCSR product (recursive partitioning, Section 3.3)
+// Entries of a partition of the remapped nest, at most (its entries are asked for one by one, behind their rows:
+// smaller partitions than the merge kernel could hold keep more of those requests in flight).
+constexpr int64_t kMappedEntries = 4096;
 constexpr int64_t kRowGrain = 2048;     // level-0 coordinates of all operands per partition of the row loop
 struct RemapWs {
     int64_t P0, Pmax, Mmax, count0;
@@ -201,6 +205,7 @@ struct RemapWs {
     int32_t *flags, *qpos, *tsum;
     RemapArrays remap;
     int64_t *info;                   // {partitions, intersected rows, remapped total cost} of the last call
+    MergeFields fields;              // key layout of the remapped nest
     PartsWs parts;                   // partitions of the remapped nest
     unsigned long long *tile_state;
     int32_t *pos_full;
@@ -214,16 +219,28 @@ int spadd_fmt(Format f)
     return f == FMT_VECTOR ? SPADD_VECTOR : (f == FMT_CSR ? SPADD_CSR : (f == FMT_COO ? SPADD_COO : SPADD_DCSR));
 }
 
+MergeFields fields_of(Format fmt, int32_t dtype, const nacho_tensor *ops, int64_t total_nnz)
+{
+    return merge_fields(spadd_fmt(fmt), dtype, ops[0].lvl[0].extent, ops[0].nlevels > 1 ? ops[0].lvl[1].extent : 0,
+                        ops[0].nlevels > 2 ? ops[0].lvl[2].extent : 0, total_nnz, compute_units());
+}
+
 // Partitions a fused call uses: at least P, and enough that one partition's work
 // (ideal share + k - 1 by the tightness bound of Section 3.2.2) fits a wavefront.
-int64_t fused_partitions(int32_t op, Format fmt, int32_t dtype, int32_t k, int64_t total_nnz, int64_t P)
+int64_t fused_partitions(int32_t op, int32_t dtype, int64_t total_nnz, int64_t P)
 {
-    int64_t cap;
-    if (op == NACHO_OP_SPMV) cap = spmv_capacity(dtype);
-    else if (op == NACHO_OP_SPMM) cap = spmm_capacity(dtype);
-    else cap = spadd_capacity(spadd_fmt(fmt), dtype) - k;
+    const int64_t cap = op == NACHO_OP_SPMV ? spmv_capacity(dtype) : spmm_capacity(dtype);
+    const int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
+    return P > need ? P : need;
+}
+
+// The same for the merge kernel of sums and products; `fields` is its key layout for the operands.
+int64_t merge_partitions(int fmt, int32_t dtype, int32_t k, const MergeFields &fields, int64_t total_nnz, int64_t P,
+                         int64_t most = 1 << 30)
+{
+    const int64_t cap = std::min<int64_t>(spadd_capacity(fmt, dtype, fields), most) - k;
     int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
-    if (P == 0 && op != NACHO_OP_SPMV && op != NACHO_OP_SPMM) {
+    if (P == 0) {
         // The merge kernel keeps spadd_resident() workgroups per compute unit, and its partitions all
         // take about the same time: they run in rounds of that many workgroups per unit.  With the
         // partition count a whole number of rounds the last round is as full as the others.
@@ -246,7 +263,8 @@ RemapWs carve_remap(void *ws, const nacho_tensor *ops, int k, int32_t dtype, int
     }
     w.P0 = rows_total > 0 ? ceil_div(rows_total, kRowGrain) : 1;
     // the remapped cost never exceeds the stored non-zeros: enough partitions for any outcome
-    w.Pmax = fused_partitions(NACHO_OP_SPADD, FMT_CSR, dtype, k, total_nnz, P);
+    w.fields = merge_fields(SPADD_CSR, dtype, w.Mmax, ops[0].lvl[1].extent, 0, total_nnz, compute_units());
+    w.Pmax = merge_partitions(SPADD_CSR, dtype, k, w.fields, total_nnz, P, kMappedEntries);
     w.parts0 = carve_parts(c, w.P0, k, 1);
     w.flags = c.take<int32_t>((size_t)w.count0);
     w.qpos = c.take<int32_t>((size_t)w.count0 * (k - 1));
@@ -359,11 +377,11 @@ int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int
     case NACHO_OP_SPMV:
     case NACHO_OP_SPMM:
         if (k != 1 || fmt != FMT_CSR) return 0;
-        return fused_partitions(op, fmt, dtype, k, total, P);
+        return fused_partitions(op, dtype, total, P);
     case NACHO_OP_SPADD:
     case NACHO_OP_SPMUL:      // (a DCSR product: an upper bound, the count depends on the intersected rows)
         if (fmt == FMT_CSF3 && op == NACHO_OP_SPMUL) return 0;
-        return fused_partitions(NACHO_OP_SPADD, fmt, dtype, k, total, P);
+        return merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
     default: return 0;
     }
 }
@@ -383,7 +401,7 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
     case NACHO_OP_SPMV:
     case NACHO_OP_SPMM: {
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
-        const int64_t Pe = fused_partitions(op, fmt, dtype, k, total, P);
+        const int64_t Pe = fused_partitions(op, dtype, total, P);
         *bytes = carve_carry(nullptr, Pe, dtype, op == NACHO_OP_SPMM ? NACHO_WAVE : 1).bytes;
         return NACHO_OK;
     }
@@ -395,7 +413,7 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
         }
         /* fall through: the pipeline of the union */
     case NACHO_OP_SPADD: {
-        const int64_t Pe = fused_partitions(NACHO_OP_SPADD, fmt, dtype, k, total, P);
+        const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
         *bytes = carve_spadd(nullptr, Pe, k, dev.d).bytes;
         return NACHO_OK;
     }
@@ -422,7 +440,7 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
     case NACHO_OP_SPMM: {
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
         if (op == NACHO_OP_SPMM && n_dense < 1) return NACHO_ERR_INVALID_ARG;
-        Pe = fused_partitions(op, fmt, dtype, k, total, P);
+        Pe = fused_partitions(op, dtype, total, P);
         CarryWs c = carve_carry(ws, Pe, dtype, op == NACHO_OP_SPMM ? NACHO_WAVE : 1);
         w = c.parts;
         need = c.bytes;
@@ -447,7 +465,7 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
         }
         /* fall through */
     case NACHO_OP_SPADD: {
-        Pe = fused_partitions(NACHO_OP_SPADD, fmt, dtype, k, total, P);
+        Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
         SpaddWs c = carve_spadd(ws, Pe, k, dev.d);
         w = c.parts;
         need = c.bytes;
@@ -514,7 +532,7 @@ int32_t nacho_spmv(const nacho_tensor *A, const void *x, void *y, int32_t dtype,
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && (!A->val || !aligned16(A->val))) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, fmt, dtype, 1, nnz, P);
+    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, dtype, nnz, P);
     CarryWs w = carve_carry(ws, Pe, dtype, 1);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     return spmv_enqueue(A, dev, nnz, x, y, dtype, P, Pe, w, static_cast<hipStream_t>(hip_stream));
@@ -532,7 +550,7 @@ int32_t nacho_spmv_fused(const nacho_tensor *A, const void *x, void *y, int32_t 
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && (!A->val || !aligned16(A->val))) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, fmt, dtype, 1, nnz, 0);
+    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, dtype, nnz, 0);
     CarryWs w = carve_carry(ws, Pe, dtype, 1);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -563,7 +581,7 @@ int32_t nacho_spmv_static(const nacho_tensor *A, const void *x, void *y, int32_t
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && (!A->val || !aligned16(A->val))) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, fmt, dtype, 1, nnz, P);
+    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, dtype, nnz, P);
     // sizes first: nothing is touched when the call does not fit the built-in scratch memory
     if (carve_carry(nullptr, Pe, dtype, 1).bytes > kStaticScratchBytes) return NACHO_ERR_TOO_LARGE;
     void *base = nullptr;
@@ -650,7 +668,7 @@ int32_t nacho_spmm(const nacho_tensor *A, const void *B, int64_t n, int64_t ldb,
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && !A->val) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMM, fmt, dtype, 1, nnz, P);
+    const int64_t Pe = fused_partitions(NACHO_OP_SPMM, dtype, nnz, P);
     CarryWs w = carve_carry(ws, Pe, dtype, NACHO_WAVE);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -733,7 +751,7 @@ static int32_t dcsr_product(const nacho_tensor *ops, int32_t k, int32_t dtype, i
     // The size of the remapped space (rows all operands store, entries in them) stays on the device:
     // everything below is launched for the upper bounds the workspace was carved for, reads the real
     // sizes there, and lets the surplus workgroups leave at once.  The call never waits for the stream.
-    const int64_t capacity = spadd_capacity(SPADD_CSR, dtype) - k;
+    const int64_t capacity = std::min<int64_t>(spadd_capacity(SPADD_CSR, dtype, w.fields), kMappedEntries) - k;
     if (launch_remap_plan(k, w.remap, capacity, (int64_t)compute_units() * spadd_resident(), P, w.Pmax, w.info,
                           s) != hipSuccess)
         return NACHO_ERR_HIP;
@@ -765,7 +783,7 @@ static int32_t dcsr_product(const nacho_tensor *ops, int32_t k, int32_t dtype, i
         return NACHO_ERR_HIP;
     profile_mark("partition");
     if (launch_spadd(SPADD_CSR, dtype, true, mapped, vals, w.Pmax, w.parts.coord, w.parts.posn, w.tile_state, mo,
-                     s) != hipSuccess)
+                     w.fields, s) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("spmul_merge");
     if (launch_compact_rows(w.remap, w.pos_full, w.counts, o, w.tsum, s) != hipSuccess) return NACHO_ERR_HIP;
@@ -802,7 +820,8 @@ static int32_t sparse_combine(bool multiply, const nacho_tensor *ops, int32_t k,
     if (fmt == FMT_CSF3 && (!out->pos0 || !out->pos2 || out->cap_fibres < 0 || (out->cap_rows > 0 && !out->crd0) ||
                             (out->cap_fibres > 0 && !out->crd1) || (out->cap_nnz > 0 && !out->crd2)))
         return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPADD, fmt, dtype, k, total, P);
+    const MergeFields fields = fields_of(fmt, dtype, ops, total);
+    const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields, total, P);
     SpaddWs w = carve_spadd(ws, Pe, k, dev.d);
     const bool recursive = multiply && fmt == FMT_DCSR && k > 1;    // (its own workspace layout)
     if (!recursive && (!ws || ws_bytes < w.bytes)) return NACHO_ERR_WORKSPACE;
@@ -822,7 +841,7 @@ static int32_t sparse_combine(bool multiply, const nacho_tensor *ops, int32_t k,
                          w.tile_state, spadd_state_words(Pe), o.status) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("partition");
-    if (launch_spadd(f, dtype, multiply, dev, vals, Pe, w.parts.coord, w.parts.posn, w.tile_state, o, s) != hipSuccess)
+    if (launch_spadd(f, dtype, multiply, dev, vals, Pe, w.parts.coord, w.parts.posn, w.tile_state, o, fields, s) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark(multiply ? "spmul_merge" : "spadd_merge");
     return NACHO_OK;
@@ -853,7 +872,7 @@ int32_t nacho_spadd_fused(const nacho_tensor *ops, int32_t k, int32_t dtype, int
     }
     if (!out->counts || !out->status || !out->pos1 || out->cap_nnz < 0) return NACHO_ERR_INVALID_ARG;
     if (out->cap_nnz > 0 && (!out->crd1 || !out->val)) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPADD, fmt, dtype, k, total, P);
+    const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
     SpaddWs w = carve_spadd(ws, Pe, k, dev.d);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     SpaddOut o;

@@ -65,8 +65,17 @@ struct SpaddOut {
     int64_t *counts;
     int32_t *status;
 };
+// How the merge kernel packs the coordinates of a matrix or tensor entry into a key: row field << cb | column; for a
+// tensor the row field is (i - i0) << jb | j.  Rows (slices) count from the partition's first one and a key tells
+// `limit` of them apart.  `wide`: 64-bit keys.  `small`: short partitions, for calls that do not fill the chip.
+struct MergeFields {
+    int32_t cb, jb, wide, small;
+    uint32_t limit;
+};
+// `rows`, `cols`, `depth`: the extents of the levels; `total`: stored entries of all operands; `units`: compute units.
+MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units);
 // Entries of all operands one partition (workgroup) may hold.
-int spadd_capacity(int fmt, int dtype);
+int spadd_capacity(int fmt, int dtype, const MergeFields &fields);
 // Workgroups of the merge kernel that run on one compute unit at a time.
 int spadd_resident();
 // Wavefronts of one of its workgroups (the instrumented build logs one record per wavefront).
@@ -89,7 +98,28 @@ hipError_t launch_spadd_vector_search(int dtype, const DevOperands &ops, const S
 // intersection with products instead of the union with sums (vectors and CSR only).
 hipError_t launch_spadd(int fmt, int dtype, bool multiply, const DevOperands &ops, const SpaddValues &vals,
                         int64_t P, const int32_t *coord, const int32_t *posn, unsigned long long *tile_state,
-                        const SpaddOut &out, hipStream_t s);
+                        const SpaddOut &out, const MergeFields &fields, hipStream_t s);
+
+// The merge kernel's instantiations, one translation unit per format.
+struct MergeLaunch {
+    const DevOperands &ops;
+    const SpaddValues &vals;
+    int64_t P;
+    const int32_t *coord, *posn;
+    unsigned long long *tile_state;
+    const SpaddOut &out;
+    MergeFields fields;
+    SpaddSearch search;
+    hipStream_t s;
+};
+hipError_t merge_vector(int dtype, bool multiply, const MergeLaunch &a);
+hipError_t merge_vector_search(int dtype, const MergeLaunch &a);
+hipError_t merge_csr(int dtype, const MergeLaunch &a);
+hipError_t merge_csr_product(int dtype, const MergeLaunch &a);
+hipError_t merge_csr_mapped(int dtype, const MergeLaunch &a);
+hipError_t merge_dcsr(int dtype, const MergeLaunch &a);
+hipError_t merge_coo(int dtype, bool multiply, const MergeLaunch &a);
+hipError_t merge_csf3(int dtype, const MergeLaunch &a);
 
 // ---- recursive partitioning for an outer intersection (DCSR products) -----------
 // Memoised row loop of Section 3.3, all arrays on the device:
