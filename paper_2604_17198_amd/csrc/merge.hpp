@@ -173,6 +173,17 @@ __device__ inline int lanes_below(unsigned long long mask)     // set bits of th
 // This lane's bit of a mask every lane agrees on.
 __device__ inline bool my_bit(unsigned long long mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
+// The n lowest bits of a 64-bit word (n: this lane's; below 0: none, above 64: all), built from 32-bit shifts.
+// A 64-bit shift whose amount is in the LAST vector register a kernel was given takes the amount of another
+// wavefront now and then (measured: some rows' pos of a CSR product, another wavefront's every time); the kernels
+// here use all of their registers, so no lane shifts 64 bits by an amount of its own.
+__device__ inline unsigned long long low_bits(int n)
+{
+    const unsigned lo = n >= 32 ? ~0u : (n > 0 ? (1u << n) - 1u : 0u);
+    const unsigned hi = n >= 64 ? ~0u : (n > 32 ? (1u << (n - 32)) - 1u : 0u);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 // Barrier of the workgroup for what its wavefronts exchange through LDS.  (__syncthreads also waits for every
 // global load in flight; here those travel on.)
 __device__ inline void lds_barrier()
@@ -910,9 +921,9 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         auto put_bits = [&](unsigned long long *at, uint32_t m) {
             m = (__builtin_bitreverse32(m) >> (32 - R)) & in;
             uint32_t *a = reinterpret_cast<uint32_t *>(at) + (d0 >> 5);
-            const unsigned long long v = (unsigned long long)m << (d0 & 31);
-            atomicOr(a, (uint32_t)v);
-            if ((d0 & 31) + R > 32) atomicOr(a + 1, (uint32_t)(v >> 32));
+            const int shift = d0 & 31;
+            atomicOr(a, m << shift);
+            if (shift + R > 32) atomicOr(a + 1, m >> (32 - shift));
         };
         put_bits(w.heads, hm);
         if constexpr (kRowHeads) put_bits(w.row_heads, rm);
@@ -1089,8 +1100,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // ---- 3. assembly: which places are emitted, and how many before every block -----------
     // lane l: block block0 + l of the wavefront's own (and, l = R, the one behind them)
     auto valid_bits = [&](int b) -> unsigned long long {
-        const int left = n - b * NACHO_WAVE;
-        return left >= NACHO_WAVE ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
+        return low_bits(n - b * NACHO_WAVE);
     };
     auto shifted = [](unsigned long long own, unsigned long long next, int g) {
         return (own >> g) | (next << (64 - g));        // 1 <= g <= 7
@@ -1392,7 +1402,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             const int b = m / NACHO_WAVE;
             int before = own_nnz;
             if (b < NB) before = w.wave_before[b / R] + w.block_before[b] +
-                                 __popcll(w.emitted[b] & ((1ull << (m & (NACHO_WAVE - 1))) - 1ull));
+                                 __popcll(w.emitted[b] & low_bits(m & (NACHO_WAVE - 1)));
             pos_out[row] = at_nnz + before;
         }
     }
