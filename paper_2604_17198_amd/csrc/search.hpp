@@ -289,6 +289,37 @@ __device__ __forceinline__ LevelResult sampled_search(const DevOperands &ops, in
         // lower bound exceeds it a suffix: one ballot each finds the largest / smallest
         // such sample, no reduction over the wavefront.
         CoordT vminus = -1, vplus = Acc::kNone;
+        // Until the windows are small one operand's samples are bounded per round, those of the widest window:
+        // they are the ones that narrow the total, and K - 1 rank searches take a third of the instructions
+        // of K (K - 1) (three operands; the chain of them is what a boundary takes).  Its neighbours' windows shrink
+        // to what overlaps.
+        auto bounds_of_widest = [&]() {
+            int wide = 0, w_wide = w[0];
+#pragma unroll
+            for (int u = 1; u < K; ++u)
+                if (w[u] > w_wide) { wide = u; w_wide = w[u]; }
+            CoordT vp = v[0];
+            int cp = cb[0];
+#pragma unroll
+            for (int u = 1; u < K; ++u)
+                if (u == wide) { vp = v[u]; cp = cb[u]; }
+            int glo = cp, ghi = cp;
+#pragma unroll
+            for (int u = 0; u < K; ++u) {
+                if (u == wide || mt[u] == 0) {         // (uniform)
+                    if (u != wide) { glo += cl[u]; ghi += cl[u]; }
+                    continue;
+                }
+                const int c = rank_among<CoordT>(v[u], vp);
+                const int a = __shfl(ca[u], (c - 1) & (NACHO_WAVE - 1), NACHO_WAVE);
+                const int bq = __shfl(cb[u], c & (NACHO_WAVE - 1), NACHO_WAVE);
+                glo += c == 0 ? cl[u] : a;
+                ghi += c == mt[u] ? ch[u] : bq;
+            }
+            const int n_le = __popcll(__ballot(ghi <= R_lo)), n_in = __popcll(__ballot(glo <= R_hi));   // (64 samples)
+            if (n_le > 0) vminus = lane_value(vp, n_le - 1);
+            if (n_in < NACHO_WAVE) vplus = lane_value(vp, n_in);
+        };
         auto bounds_of = [&](int t, const int (&lo_t)[K]) {
             int glo = cb[t], ghi = cb[t];           // own operand: the sample's position is exact
 #pragma unroll
@@ -318,13 +349,15 @@ __device__ __forceinline__ LevelResult sampled_search(const DevOperands &ops, in
         };
         // rank of every sample of t among the samples of u (lanes past mt[u] hold kNone, which is
         // smaller than no key: a rank never exceeds mt[u]); one operand at a time, ranks and bounds
+        if (!all_small) bounds_of_widest();
+        else
 #pragma unroll
-        for (int t = 0; t < K; ++t) {
-            int lo_t[K];
+            for (int t = 0; t < K; ++t) {
+                int lo_t[K];
 #pragma unroll
-            for (int u = 0; u < K; ++u) lo_t[u] = u == t ? 0 : rank_among<CoordT>(v[u], v[t]);
-            bounds_of(t, lo_t);
-        }
+                for (int u = 0; u < K; ++u) lo_t[u] = u == t ? 0 : rank_among<CoordT>(v[u], v[t]);
+                bounds_of(t, lo_t);
+            }
 
 #pragma unroll
         for (int u = 0; u < K; ++u) {
@@ -379,11 +412,11 @@ __device__ __forceinline__ LevelResult sampled_search(const DevOperands &ops, in
 // of rank R of the two merged segments, so the search is for the split of the first R merged entries (the first
 // operand first on ties) -- i of them from the first operand for the largest i with A[i - 1] <= B[R - i] -- and every
 // lane tries one i per round.  Two loads and a ballot a round; the sampled search spends a few hundred
-// instructions on the ranks and bounds that more operands need (DCSR + DCSR, 8192 boundaries: 36 against 24 us).
+// instructions on the ranks and bounds that more operands need (DCSR + DCSR, 8192 boundaries: 36 against 28 us).
 // Requires both segments non-empty and 0 <= R < their total length.
 template <int K, class Acc>
 __device__ __forceinline__ LevelResult split_search(const DevOperands &ops, int m, int R, const int *seg_lo,
-                                                    const int *seg_hi, int *p, const int *sh)
+                                                    const int *seg_hi, int *p, const int *sh, int fan)
 {
     static_assert(K == 2, "two operands");
     typedef typename Acc::type CoordT;
@@ -391,8 +424,11 @@ __device__ __forceinline__ LevelResult split_search(const DevOperands &ops, int 
     const int a0 = seg_lo[0], b0 = seg_lo[1], na = seg_hi[0] - a0, nb = seg_hi[1] - b0;
     int lo = R > nb ? R - nb : 0, hi = R < na ? R : na;
     while (lo < hi) {
-        const int step = (hi - lo + NACHO_WAVE - 1) / NACHO_WAVE;
-        int i = lo + (lane + 1) * step;
+        // 64 >> fan candidates a round (lanes that share one read the same words), all 64 once they share cache lines
+        const int f = hi - lo > 256 ? fan : 0;
+        const int way = lane >> f, ways = NACHO_WAVE >> f;
+        const int step = (hi - lo + ways - 1) >> (6 - f);
+        int i = lo + (way + 1) * step;
         i = i < hi ? i : hi;
         const int j = R - i;                           // (i <= R, and i >= R - nb: 0 <= j <= nb)
         const CoordT av = Acc::load(ops, 0, m, a0 + i - 1 + sh[0]);
@@ -451,7 +487,7 @@ __device__ inline int row_starts(const DevOperands &ops, int hi, int64_t x)
 template <bool kLast, int K, class Acc = PlainCoords, bool kDeep = false>
 __device__ __forceinline__ LevelResult compressed_level(const DevOperands &ops, int m, int64_t R, int64_t total,
                                         const int *seg_lo, const int *seg_hi, Windows<K> &W, int *p,
-                                        const int *sh)
+                                        const int *sh, int fan = 0)
 {
     const int k = ops.k;
     LevelResult r;
@@ -485,7 +521,7 @@ __device__ __forceinline__ LevelResult compressed_level(const DevOperands &ops, 
         return r;
     }
     if constexpr (kLast && K == 2) {
-        if (nonempty == 2) return split_search<K, Acc>(ops, m, (int)R, seg_lo, seg_hi, p, sh);
+        if (nonempty == 2) return split_search<K, Acc>(ops, m, (int)R, seg_lo, seg_hi, p, sh, fan);
     }
     if constexpr (K > 4) {
         // many operands: the sampled search would carry K * K rank searches per round and a
@@ -526,6 +562,11 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
 #pragma unroll
     for (int t = 0; t < K; ++t) found[t] = 0;
     const int64_t total_scaled = total_unscaled * cost_scale;
+    // Two operands: candidates per round of the split search, 64 >> fan.  Every candidate is a cache line of its own
+    // that no other boundary asks for: with thousands of boundaries in flight the lines are what takes the time (10M
+    // + 10M entries, 8192 boundaries: 46 us with 64 candidates a round, 24 with 16, 19 with 8, 18 with 4), with
+    // few of them the rounds are (16 boundaries: 6.5 / 7.0 / 7.4 / 8.1 us).
+    const int fan = P > 1024 ? 3 : 2;
     const bool dense0 = ops.lvl[0][0].kind == NACHO_DENSE;
     constexpr bool pairs = kMode == 1;                              // coordinate lists (COO), d == 2
     constexpr bool csf3 = kMode == 2;                               // three compressed levels, d == 3
@@ -591,7 +632,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
             // that of its first entry in the boundary's row
             Windows<K> W = W0;
             LevelResult r = compressed_level<true, K, PairCoords>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi, W, p,
-                                                                  no_shift);
+                                                                  no_shift, fan);
             R -= r.c;
             const int x0 = (int)(r.x >> 32), x1 = (int)(r.x & 0xffffffffLL);
             constexpr int G = NACHO_WAVE / (K <= 2 ? 2 : (K <= 4 ? 4 : 8));    // lanes of an operand's group
@@ -653,7 +694,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
             }
             Windows<K> W2;
             windows_init<true, K>(ops, 2, seg_lo, seg_hi, W2);
-            LevelResult r2 = compressed_level<true, K>(ops, 2, R, tot2, seg_lo, seg_hi, W2, p, no_shift);
+            LevelResult r2 = compressed_level<true, K>(ops, 2, R, tot2, seg_lo, seg_hi, W2, p, no_shift, fan);
             R -= r2.c;
             if (lane == 0) {
                 cb[0] = (int32_t)r0.x;
@@ -669,7 +710,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
             }
         } else if (d == 1) {
             Windows<K> W = W0;
-            LevelResult r = compressed_level<true, K>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi, W, p, no_shift);
+            LevelResult r = compressed_level<true, K>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi, W, p, no_shift, fan);
             R -= r.c;
 #pragma unroll
             for (int t = 0; t < K; ++t)
@@ -710,7 +751,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
             Windows<K> W1;
             windows_init<true, K>(ops, 1, seg_lo, seg_hi, W1);
             const int64_t tot1 = level_total<true, K>(ops, 1, seg_lo, seg_hi);
-            LevelResult r1 = compressed_level<true, K>(ops, 1, R, tot1, seg_lo, seg_hi, W1, p, sh);
+            LevelResult r1 = compressed_level<true, K>(ops, 1, R, tot1, seg_lo, seg_hi, W1, p, sh, fan);
             R -= r1.c;
             if (lane == 0) {
                 cb[0] = (int32_t)r0.x;
