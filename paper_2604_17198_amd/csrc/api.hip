@@ -296,18 +296,22 @@ int32_t spmv_enqueue(const nacho_tensor *A, const DevOperands &dev, int64_t nnz,
     // kernel uses to deal them out; with a row cost the boundaries are no longer multiples of the grain
     // in pos, and the equally spaced queries are used)
     const int64_t grain = (P == 0 && row_cost == 0) ? spmv_capacity(dtype) : 0;
-    // (the partition kernel also writes the zeros of the rows A stores nothing in)
-    ZeroRows zero;
-    zero.base = y;
-    zero.ld = 1;
-    zero.width = 1;
-    zero.elem = (int32_t)dtype_size(dtype);
-    if (launch_partition(dev, 1, Pe, grain, nullptr, nnz, w.parts.coord, w.parts.posn, w.parts.cost, s, nullptr, 0,
-                         nullptr, &zero, row_cost) != hipSuccess)
-        return NACHO_ERR_HIP;
-    profile_mark("partition");
-    if (launch_spmv_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, x, y, n_rows, nnz,
-                         w.parts.coord, w.parts.posn, Pe, w.carry_val, w.carry_row, grain, s) != hipSuccess)
+    const bool whole = grain > 0 && spmv_whole(Pe, n_rows);
+    if (!whole) {
+        // (the partition kernel also writes the zeros of the rows A stores nothing in)
+        ZeroRows zero;
+        zero.base = y;
+        zero.ld = 1;
+        zero.width = 1;
+        zero.elem = (int32_t)dtype_size(dtype);
+        if (launch_partition(dev, 1, Pe, grain, nullptr, nnz, w.parts.coord, w.parts.posn, w.parts.cost, s, nullptr, 0,
+                             nullptr, &zero, row_cost) != hipSuccess)
+            return NACHO_ERR_HIP;
+        profile_mark("partition");
+    }
+    if (launch_spmv_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, x, y, n_rows, nnz, w.parts.coord, w.parts.posn,
+                         w.parts.cost, Pe, w.carry_val, w.carry_row, grain,
+                         whole ? SPMV_WHOLE : (grain > 0 ? SPMV_DEALT : SPMV_TABLE), s) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("spmv_exec");
     if (launch_spmv_fixup(dtype, y, Pe, w.carry_val, w.carry_row, A->lvl[1].pos, grain, s) != hipSuccess)
@@ -559,8 +563,8 @@ int32_t nacho_spmv_fused(const nacho_tensor *A, const void *x, void *y, int32_t 
     profile_begin(s);
     if (launch_zero_vector(dtype, y, n_rows, s) != hipSuccess) return NACHO_ERR_HIP;
     profile_mark("zero_y");
-    if (launch_spmv_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, x, y, n_rows, nnz, nullptr, nullptr, Pe,
-                         w.carry_val, w.carry_row, grain, s) != hipSuccess)
+    if (launch_spmv_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, x, y, n_rows, nnz, nullptr, nullptr, nullptr, Pe,
+                         w.carry_val, w.carry_row, grain, SPMV_SEARCH, s) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("spmv_exec_fused");
     if (launch_spmv_fixup(dtype, y, Pe, w.carry_val, w.carry_row, A->lvl[1].pos, grain, s) != hipSuccess)

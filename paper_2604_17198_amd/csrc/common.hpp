@@ -96,6 +96,38 @@ __device__ inline int wave_inclusive_scan(int v)
     return v;
 }
 
+// Sum over the lanes of a wavefront in a fixed order, in lane 63, by DPP moves (a butterfly of shuffles goes
+// through the LDS unit: six dependent round trips of over a hundred cycles).
+template <int kCtrl, int kRowMask> __device__ inline float dpp_moved(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRowMask, 0xf, false));
+}
+template <int kCtrl, int kRowMask> __device__ inline double dpp_moved(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, kCtrl, kRowMask, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, kRowMask, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <typename T> __device__ inline T dpp_wave_sum(T v)
+{
+    v += dpp_moved<0x111, 0xf>(v);                     // row_shr:1, 2, 4, 8: inside 16 lanes
+    v += dpp_moved<0x112, 0xf>(v);
+    v += dpp_moved<0x114, 0xf>(v);
+    v += dpp_moved<0x118, 0xf>(v);
+    v += dpp_moved<0x142, 0xa>(v);                     // row_bcast:15 into rows 1 and 3
+    v += dpp_moved<0x143, 0xc>(v);                     // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ inline float last_lane(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), NACHO_WAVE - 1)); }
+__device__ inline double last_lane(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(unsigned)b, NACHO_WAVE - 1);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), NACHO_WAVE - 1);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // Least position in [lo, hi) whose coordinate is >= x; hi if there is none.
 __device__ inline int lower_bound_global(const int32_t *__restrict__ crd, int lo, int hi, int64_t x)
 {
@@ -124,6 +156,30 @@ __device__ inline int first_row_past(const int32_t *__restrict__ pos, int lo, in
         hi = t_hit + 1;
     }
     return lo;
+}
+
+// The rows ra, rb with pos[r] <= q < pos[r + 1] for q = qa and qb (n_rows where pos[n_rows] <= q), both at once:
+// half of the wavefront searches each, 32 probes per round.
+__device__ inline void rows_holding(const int32_t *__restrict__ pos, int n_rows, int qa, int qb, int &ra, int &rb)
+{
+    constexpr int G = NACHO_WAVE / 2;
+    const int lane = lane_id(), sub = lane & (G - 1);
+    const int q = lane < G ? qa : qb;
+    int lo = 0, hi = n_rows;                           // the number of rows that end at or before q
+    while (__ballot(lo < hi) != 0ull) {
+        const int step = (hi - lo + G - 1) / G;
+        const int at = lo + (sub + 1) * step - 1;
+        const bool before = lo < hi && at < hi && pos[at + 1] <= q;        // (a prefix of the half)
+        const unsigned long long mask = __ballot(before);
+        const int n = __popc(lane < G ? (unsigned)mask : (unsigned)(mask >> 32));
+        if (lo < hi) {
+            const int lo_new = lo + n * step, at_next = lo + (n + 1) * step - 1;
+            hi = n < G && at_next < hi ? at_next : hi;
+            lo = lo_new < hi ? lo_new : hi;
+        }
+    }
+    ra = __builtin_amdgcn_readlane(lo, 0);
+    rb = __builtin_amdgcn_readlane(lo, G);
 }
 
 // ---- instrumented build (-DNACHO_INSTRUMENT): what every wavefront did, and when -----------

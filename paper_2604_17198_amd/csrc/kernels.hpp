@@ -31,13 +31,16 @@ hipError_t launch_partition_csr64(const int64_t *pos, const int32_t *crd, int64_
 
 // Items one wavefront can stage for SpMV (partition work must not exceed it).
 int spmv_capacity(int dtype);
-// `grain` > 0: the partitions come from the fixed-grain queries Q_p = min(p * grain, nnz)
-// (the kernel then deals the partitions of long rows out by XCD); 0: any partitions.
+// SPMV_TABLE: any partition table; SPMV_DEALT: the table of the fixed-grain queries Q_p = min(p * grain, nnz), dealt out by
+// XCD inside long rows; SPMV_SEARCH: no table, every wavefront searches its own boundaries (y has been cleared);
+// SPMV_WHOLE: the same, and the kernel writes the table and the zeros of empty rows itself.
+enum SpmvForm { SPMV_TABLE = 0, SPMV_DEALT = 1, SPMV_SEARCH = 2, SPMV_WHOLE = 3 };
+// Whether a fixed-grain call with P partitions takes the last form.
+bool spmv_whole(int64_t P, int64_t n_rows);
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *x, void *y, int64_t n_rows, int64_t nnz,
-                            const int32_t *coord, const int32_t *posn, int64_t P,
-                            void *carry_val, int32_t *carry_row, int64_t grain, hipStream_t stream);
-// (coord == nullptr with grain > 0: the fused form, every wavefront searches its own boundaries)
+                            int32_t *coord, int32_t *posn, int64_t *cost, int64_t P,
+                            void *carry_val, int32_t *carry_row, int64_t grain, SpmvForm form, hipStream_t stream);
 hipError_t launch_zero_vector(int dtype, void *y, int64_t n, hipStream_t stream);
 hipError_t launch_spmv_fixup(int dtype, void *y, int64_t P, const void *carry_val,
                              const int32_t *carry_row, const int32_t *pos, int64_t grain, hipStream_t stream);

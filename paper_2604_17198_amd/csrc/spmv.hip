@@ -23,18 +23,22 @@ namespace nacho {
 
 namespace {
 
-constexpr int kLongRow = 192;  // products per row above which the wavefront sums it together
+// Products per row from which the wavefront sums it together.  Below, the row's lane does, four products at a time:
+// the wavefront takes as long as its longest such row, a round trip to LDS per step (40,000 non-zeros, where nothing
+// else hides it: 13.5 us with one product at a time and rows of up to 191 of them, 5 us like this).
+constexpr int kLongRow = 48;
 
 // kDealt: the partitions come from fixed-grain queries (grain > 0) and are dealt out by XCD; the
 // instantiation without it serves arbitrary partition tables (caller's P, the row-aware cost).
 // kFused (with kDealt): there is no partition table; the wavefront finds its own two boundaries, the
 // search of Algorithm 1 for one CSR operand (Section 4.2.2: the row with pos[r] <= Q < pos[r + 1], at
 // position Q) with the fixed-grain queries Q_b = min(b * grain, nnz), as a 64-ary search over pos.
-template <typename T, int G, int RBLK, bool kDealt, bool kFused = false>
+// kTable (with kFused): the wavefront stores its boundary in the partition table and writes the zeros of its empty rows.
+template <typename T, int G, int RBLK, bool kDealt, bool kFused = false, bool kTable = false>
 __global__ void __launch_bounds__(NACHO_WAVE)
 spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
                  const T *__restrict__ val, const T *__restrict__ x, T *__restrict__ y,
-                 int nnz, const int32_t *__restrict__ coord, const int32_t *__restrict__ posn,
+                 int nnz, int32_t *__restrict__ coord, int32_t *__restrict__ posn, int64_t *__restrict__ cost,
                  T *__restrict__ carry_val, int32_t *__restrict__ carry_row, int n_rows, int grain, WaveLog wlog)
 {
     const WaveStamp stamp = wave_begin();
@@ -54,20 +58,21 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     // partitions (stretches as long as there are such workgroups): a
     // permutation of first .. end - 1; everything else keeps its index.
     int p = blockIdx.x;
-    // (fused search) boundary b: its row and its position
-    auto boundary = [&](int b, int from, int &r, int &n) {
-        const long long Q = (long long)b * grain;
-        if (b == 0) { r = 0; n = pos[0]; }
-        else if (Q >= nnz) { r = n_rows; n = pos[0] + nnz; }
-        else {
-            n = pos[0] + (int)Q;
-            r = pos[from + 1] > n ? from : first_row_past(pos, from, n_rows, n);
-        }
+    // (fused search) the rows and positions of the boundaries p and p + 1
+    int r0 = 0, r1 = 0, n0 = 0, n1 = 0;
+    auto boundaries = [&]() {
+        const int base = pos[0];
+        const long long Qa = (long long)p * grain, Qb = Qa + grain;
+        n0 = base + (int)(Qa < nnz ? Qa : nnz);
+        n1 = base + (int)(Qb < nnz ? Qb : nnz);
+        rows_holding(pos, n_rows, n0, n1, r0, r1);
+        if (p == 0) r0 = 0;
+        else if (Qa >= nnz) r0 = n_rows;
+        if (Qb >= nnz) r1 = n_rows;
     };
-    int r_own = 0, n_own = 0;
-    if (kFused) boundary(p, 0, r_own, n_own);
+    if (kFused) boundaries();
     if (kDealt) {
-        const int r = kFused ? r_own : coord[2 * p];
+        const int r = kFused ? r0 : coord[2 * p];
         if (r < n_rows) {
             const int base = pos[0];
             const int first = ((pos[r] - base) + grain - 1) / grain;
@@ -87,12 +92,23 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         }
     }
     // k = 1, d = 2: coord[b*2 + 0] = row, posn[b*2 + 1] = position in crd/val
-    int r0, r1, n0, n1;
     if (kFused) {
-        // (a dealt partition lies in the row of the one it was dealt for)
-        if (p == (int)blockIdx.x) { r0 = r_own; n0 = n_own; }
-        else boundary(p, r_own < n_rows ? r_own : 0, r0, n0);
-        boundary(p + 1, r0 < n_rows ? r0 : 0, r1, n1);
+        if (p != (int)blockIdx.x) boundaries();
+        if (kTable && lane == 0) {
+            // the partition table: this boundary, and the end
+            coord[2 * p] = r0;
+            coord[2 * p + 1] = r0 < n_rows ? (p == 0 ? 0 : crd[n0]) : 0;
+            posn[2 * p] = r0;
+            posn[2 * p + 1] = p == 0 ? 0 : (r0 < n_rows ? n0 : nnz);
+            cost[p] = n0 - pos[0];
+            if (p == (int)gridDim.x - 1) {
+                coord[2 * p + 2] = n_rows;
+                coord[2 * p + 3] = 0;
+                posn[2 * p + 2] = n_rows;
+                posn[2 * p + 3] = nnz;
+                cost[p + 1] = nnz;
+            }
+        }
     } else {
         r0 = coord[2 * p]; r1 = coord[2 * p + 2];
         n0 = posn[2 * p + 1]; n1 = posn[2 * p + 3];
@@ -148,8 +164,11 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             // kernel wrote them), so the wavefront steps over them, however many there are.
             const int q = spos[0];
             if (q == spos[nr]) {
+                const int next = q >= n1 ? nrows : first_row_past(pos, r0 + rb + nr, r0 + nrows, q) - r0;
+                if (kTable)
+                    for (int i = rb + lane; i < next; i += NACHO_WAVE) y[r0 + i] = T(0);
                 if (q >= n1) break;                     // every product of the partition is summed
-                rb = first_row_past(pos, r0 + rb + nr, r0 + nrows, q) - r0 - RBLK;
+                rb = next - RBLK;
                 continue;
             }
         }
@@ -163,15 +182,23 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             const int len = valid && hi > lo ? hi - lo : 0;
             T sum = T(0);
             if (len < kLongRow)
-                for (int i = lo; i < lo + len; ++i) sum += prod[i];
+                for (int i = lo; i < lo + len; i += 4) {
+                    T t[4];                            // (the words past the row are there: the slack of prod)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) t[u] = prod[i + u];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sum += i + u < lo + len ? t[u] : T(0);
+                }
             unsigned long long heavy = __ballot(len >= kLongRow);
             while (heavy) {
                 const int L = __ffsll((long long)heavy) - 1;
                 heavy &= heavy - 1;
-                const int llo = __shfl(lo, L, NACHO_WAVE), lhi = __shfl(hi, L, NACHO_WAVE);
+                const int llo = __builtin_amdgcn_readlane(lo, L), lhi = __builtin_amdgcn_readlane(hi, L);
                 T s = T(0);
+#pragma unroll 4
                 for (int i = llo + lane; i < lhi; i += NACHO_WAVE) s += prod[i];
-                s = wave_sum(s);
+                s = dpp_wave_sum(s);                   // (in lane 63)
+                s = last_lane(s);
                 if (lane == L) sum = s;
             }
             if (valid) {
@@ -282,25 +309,30 @@ constexpr int kGrainF32 = 1024, kRowsF32 = 1024;
 
 int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32; }
 
+// Small calls do without a partition kernel.  Its place in the stream (a launch and 3 us) is what the call is made
+// of, while a handful of wavefronts find their rows in two or three rounds of loads that hit the cache.  Not so many
+// rows that one wavefront could be left with zeroing tens of thousands of them.
+bool spmv_whole(int64_t P, int64_t n_rows) { return P <= 1024 && n_rows <= 32768; }
+
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *x, void *y, int64_t n_rows, int64_t nnz,
-                            const int32_t *coord, const int32_t *posn, int64_t P,
-                            void *carry_val, int32_t *carry_row, int64_t grain, hipStream_t stream)
+                            int32_t *coord, int32_t *posn, int64_t *cost, int64_t P,
+                            void *carry_val, int32_t *carry_row, int64_t grain, SpmvForm form, hipStream_t stream)
 {
-#define NACHO_SPMV_LAUNCH(T, G, R, DEALT, FUSED)                                                        \
-    hipLaunchKernelGGL((spmv_exec_kernel<T, G, R, DEALT, FUSED>), dim3((unsigned)P), dim3(NACHO_WAVE), 0, stream, \
-                       pos, crd, (const T *)val, (const T *)x, (T *)y, (int)nnz, coord, posn, (T *)carry_val,    \
+#define NACHO_SPMV_LAUNCH(T, G, R, DEALT, FUSED, TABLE)                                                        \
+    hipLaunchKernelGGL((spmv_exec_kernel<T, G, R, DEALT, FUSED, TABLE>), dim3((unsigned)P), dim3(NACHO_WAVE), 0, stream, \
+                       pos, crd, (const T *)val, (const T *)x, (T *)y, (int)nnz, coord, posn, cost, (T *)carry_val,    \
                        carry_row, (int)n_rows, (int)grain, nacho_host::wave_log())
-    const bool fused = grain > 0 && coord == nullptr;       // no table: the wavefronts search their boundaries
-    if (dtype == NACHO_F64) {
-        if (fused) NACHO_SPMV_LAUNCH(double, kGrainF64, kRowsF64, true, true);
-        else if (grain > 0) NACHO_SPMV_LAUNCH(double, kGrainF64, kRowsF64, true, false);
-        else NACHO_SPMV_LAUNCH(double, kGrainF64, kRowsF64, false, false);
-    } else {
-        if (fused) NACHO_SPMV_LAUNCH(float, kGrainF32, kRowsF32, true, true);
-        else if (grain > 0) NACHO_SPMV_LAUNCH(float, kGrainF32, kRowsF32, true, false);
-        else NACHO_SPMV_LAUNCH(float, kGrainF32, kRowsF32, false, false);
+#define NACHO_SPMV_FORM(T, G, R)                                                                \
+    switch (form) {                                                                             \
+    case SPMV_TABLE: NACHO_SPMV_LAUNCH(T, G, R, false, false, false); break;                    \
+    case SPMV_DEALT: NACHO_SPMV_LAUNCH(T, G, R, true, false, false); break;                     \
+    case SPMV_SEARCH: NACHO_SPMV_LAUNCH(T, G, R, true, true, false); break;                     \
+    case SPMV_WHOLE: NACHO_SPMV_LAUNCH(T, G, R, false, true, true); break;                      \
     }
+    if (dtype == NACHO_F64) { NACHO_SPMV_FORM(double, kGrainF64, kRowsF64) }
+    else { NACHO_SPMV_FORM(float, kGrainF32, kRowsF32) }
+#undef NACHO_SPMV_FORM
 #undef NACHO_SPMV_LAUNCH
     return hipGetLastError();
 }
