@@ -129,18 +129,21 @@ def _check(status: int, where: str):
         raise NachoError(status, where)
 
 
+# (A small call takes the GPU five to ten microseconds, so what Python spends per call counts: addresses and the
+# stream go through ctypes as plain integers, descriptors are passed by reference, and the current stream is asked
+# for without building a torch Stream object around it -- 13 us per call before, of which the stream was a third.)
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def dtype_code(dt) -> int:
-    if dt == torch.float32:
+    if dt is torch.float32:
         return F32
-    if dt == torch.float64:
+    if dt is torch.float64:
         return F64
     raise TypeError(f"unsupported value type {dt}")
 
@@ -215,11 +218,15 @@ def coo(rows, cols, n_rows, n_cols, val=None):
                     {"kind": "singleton", "extent": n_cols, "crd": cols}], val)
 
 
+_ARRAYS = [_Tensor * n for n in range(MAX_OPERANDS + 1)]
+
+
 def _pack(ops):
-    arr = (_Tensor * len(ops))()
-    for t, o in enumerate(ops):
-        arr[t] = o.c
-    return arr
+    """The operands' descriptors as one C array (one operand: its descriptor itself)."""
+    n = len(ops)
+    if n == 1:
+        return C.byref(ops[0].c)
+    return (_ARRAYS[n] if n <= MAX_OPERANDS else _Tensor * n)(*[o.c for o in ops])
 
 
 # --------------------------------------------------------------------------- #
@@ -231,13 +238,13 @@ def version() -> int:
 
 def num_partitions(op, ops, dtype, n_dense=0, P=0) -> int:
     arr = _pack(ops)
-    return int(lib().nacho_num_partitions(op, C.cast(arr, C.c_void_p), len(ops), dtype, n_dense, P))
+    return int(lib().nacho_num_partitions(op, arr, len(ops), dtype, n_dense, P))
 
 
 def workspace_bytes(op, ops, dtype, n_dense=0, P=0) -> int:
     n = C.c_size_t(0)
     arr = _pack(ops)
-    _check(lib().nacho_workspace_bytes(op, C.cast(arr, C.c_void_p), len(ops), dtype, n_dense, P,
+    _check(lib().nacho_workspace_bytes(op, arr, len(ops), dtype, n_dense, P,
                                        C.byref(n)), "nacho_workspace_bytes")
     return int(n.value)
 
@@ -258,7 +265,7 @@ def nacho_partition(ops, P, queries=None, cost_scale=1):
     arr = _pack(ops)
     if queries is not None:
         assert queries.dtype == torch.int64 and queries.numel() == P + 1
-    _check(lib().nacho_partition(C.cast(arr, C.c_void_p), k, cost_scale, P, _ptr(queries),
+    _check(lib().nacho_partition(arr, k, cost_scale, P, _ptr(queries),
                                  C.byref(parts), None, 0, _stream()), "nacho_partition")
     return {"coord": coord, "posn": posn, "cost": cost}
 
@@ -283,7 +290,7 @@ def workspace_parts(op, ops, dtype, ws, n_dense=0, P=0):
     parts = _Parts()
     grain = C.c_int64(0)
     arr = _pack(ops)
-    _check(lib().nacho_workspace_parts(op, C.cast(arr, C.c_void_p), len(ops), dtype, n_dense, P, _ptr(ws),
+    _check(lib().nacho_workspace_parts(op, arr, len(ops), dtype, n_dense, P, _ptr(ws),
                                        ws.numel(), C.byref(parts), C.byref(grain), _stream()),
            "nacho_workspace_parts")
     base = ws.data_ptr()
@@ -307,7 +314,7 @@ def nacho_spmv(A: Operand, x, y=None, P=0, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPMV, [A], dt, 0, P), x.device)
     arr = _pack([A])
-    _check(lib().nacho_spmv(C.cast(arr, C.c_void_p), _ptr(x), _ptr(y), dt, P, _ptr(ws),
+    _check(lib().nacho_spmv(arr, _ptr(x), _ptr(y), dt, P, _ptr(ws),
                             ws.numel(), _stream()), "nacho_spmv")
     return y
 
@@ -318,7 +325,7 @@ def nacho_spmv_fused(A: Operand, x, y, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPMV, [A], dt, 0, 0), x.device)
     arr = _pack([A])
-    _check(lib().nacho_spmv_fused(C.cast(arr, C.c_void_p), _ptr(x), _ptr(y), dt, _ptr(ws), ws.numel(), _stream()),
+    _check(lib().nacho_spmv_fused(arr, _ptr(x), _ptr(y), dt, _ptr(ws), ws.numel(), _stream()),
            "nacho_spmv_fused")
     return y
 
@@ -327,7 +334,7 @@ def nacho_spmv_static(A: Operand, x, y, P=0):
     """y = A x on the library's built-in scratch memory: no workspace, nothing allocated (y is the
     caller's)."""
     arr = _pack([A])
-    _check(lib().nacho_spmv_static(C.cast(arr, C.c_void_p), _ptr(x), _ptr(y), dtype_code(x.dtype), P,
+    _check(lib().nacho_spmv_static(arr, _ptr(x), _ptr(y), dtype_code(x.dtype), P,
                                    _stream()), "nacho_spmv_static")
     return y
 
@@ -338,7 +345,7 @@ def static_scratch_bytes() -> int:
 
 def rowcost_partitions(A: Operand, dtype, row_cost, P=0) -> int:
     arr = _pack([A])
-    return int(lib().nacho_rowcost_partitions(C.cast(arr, C.c_void_p), dtype, row_cost, P))
+    return int(lib().nacho_rowcost_partitions(arr, dtype, row_cost, P))
 
 
 def nacho_partition_rowcost(A: Operand, P, row_cost):
@@ -349,7 +356,7 @@ def nacho_partition_rowcost(A: Operand, P, row_cost):
     cost = torch.empty(P + 1, dtype=torch.int64, device=dev)
     parts = _Parts(1, 2, P, coord.data_ptr(), posn.data_ptr(), cost.data_ptr())
     arr = _pack([A])
-    _check(lib().nacho_partition_rowcost(C.cast(arr, C.c_void_p), row_cost, P, C.byref(parts), _stream()),
+    _check(lib().nacho_partition_rowcost(arr, row_cost, P, C.byref(parts), _stream()),
            "nacho_partition_rowcost")
     return {"coord": coord, "posn": posn, "cost": cost}
 
@@ -361,7 +368,7 @@ def nacho_spmv_rowcost(A: Operand, x, y, row_cost, P=0, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPMV, [A], dt, 0, Pe), x.device)
     arr = _pack([A])
-    _check(lib().nacho_spmv_rowcost(C.cast(arr, C.c_void_p), _ptr(x), _ptr(y), dt, row_cost, P, _ptr(ws),
+    _check(lib().nacho_spmv_rowcost(arr, _ptr(x), _ptr(y), dt, row_cost, P, _ptr(ws),
                                     ws.numel(), _stream()), "nacho_spmv_rowcost")
     return y
 
@@ -375,7 +382,7 @@ def nacho_spmm(A: Operand, B, Cout=None, P=0, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPMM, [A], dt, n, P), B.device)
     arr = _pack([A])
-    _check(lib().nacho_spmm(C.cast(arr, C.c_void_p), _ptr(B), n, int(B.stride(0)), _ptr(Cout),
+    _check(lib().nacho_spmm(arr, _ptr(B), n, int(B.stride(0)), _ptr(Cout),
                             int(Cout.stride(0)), dt, P, _ptr(ws), ws.numel(), _stream()), "nacho_spmm")
     return Cout
 
@@ -414,7 +421,7 @@ def nacho_spadd_k(ops, out: SparseOut, P=0, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPADD, ops, dt, 0, P), dev)
     arr = _pack(ops)
-    _check(lib().nacho_spadd_k(C.cast(arr, C.c_void_p), len(ops), dt, P, C.byref(out.c), _ptr(ws),
+    _check(lib().nacho_spadd_k(arr, len(ops), dt, P, C.byref(out.c), _ptr(ws),
                                ws.numel(), _stream()), "nacho_spadd_k")
     return out
 
@@ -427,7 +434,7 @@ def nacho_spadd_fused(ops, out: SparseOut, P=0, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPADD, ops, dt, 0, P), dev)
     arr = _pack(ops)
-    _check(lib().nacho_spadd_fused(C.cast(arr, C.c_void_p), len(ops), dt, P, C.byref(out.c), _ptr(ws),
+    _check(lib().nacho_spadd_fused(arr, len(ops), dt, P, C.byref(out.c), _ptr(ws),
                                    ws.numel(), _stream()), "nacho_spadd_fused")
     return out
 
@@ -440,7 +447,7 @@ def nacho_spmul_k(ops, out: SparseOut, P=0, ws=None):
     if ws is None:
         ws = _workspace(workspace_bytes(OP_SPMUL, ops, dt, 0, P), dev)
     arr = _pack(ops)
-    _check(lib().nacho_spmul_k(C.cast(arr, C.c_void_p), len(ops), dt, P, C.byref(out.c), _ptr(ws),
+    _check(lib().nacho_spmul_k(arr, len(ops), dt, P, C.byref(out.c), _ptr(ws),
                                ws.numel(), _stream()), "nacho_spmul_k")
     return out
 
@@ -452,7 +459,7 @@ def nacho_validate(ops):
     status = torch.zeros(1, dtype=torch.int32, device=dev)
     info = torch.zeros(3, dtype=torch.int64, device=dev)
     arr = _pack(ops)
-    _check(lib().nacho_validate(C.cast(arr, C.c_void_p), len(ops), _ptr(status), _ptr(info), _stream()),
+    _check(lib().nacho_validate(arr, len(ops), _ptr(status), _ptr(info), _stream()),
            "nacho_validate")
     torch.cuda.synchronize()
     return int(status.cpu()[0]), tuple(int(v) for v in info.cpu())
