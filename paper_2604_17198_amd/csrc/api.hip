@@ -149,7 +149,12 @@ struct CarryWs {
     size_t bytes;
 };
 
-// SpMV: one carry value per partition; SpMM: one 64-wide carry row per partition.
+// Columns SpMM works on at a time (wider operands: one pass after the other), and with them the width of its carry
+// rows: what one wavefront's lanes hold of a row of floats.  A workspace sized for 64 columns serves any operand.
+constexpr int64_t kSpmmPass = 256;
+int spmm_pass(int64_t n) { return (int)(n < NACHO_WAVE ? NACHO_WAVE : (n < kSpmmPass ? n : kSpmmPass)); }
+
+// SpMV: one carry value per partition; SpMM: one carry row per partition.
 CarryWs carve_carry(void *ws, int64_t P, int32_t dtype, int width)
 {
     Carver c(ws);
@@ -229,7 +234,8 @@ MergeFields fields_of(Format fmt, int32_t dtype, const nacho_tensor *ops, int64_
 // (ideal share + k - 1 by the tightness bound of Section 3.2.2) fits a wavefront.
 int64_t fused_partitions(int32_t op, int32_t dtype, int64_t total_nnz, int64_t P)
 {
-    const int64_t cap = op == NACHO_OP_SPMV ? spmv_capacity(dtype) : spmm_capacity(dtype);
+    const int64_t cap = op == NACHO_OP_SPMV ? spmv_capacity(dtype)
+                                            : (P == 0 ? spmm_grain(total_nnz, compute_units()) : spmm_capacity());
     const int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
     return P > need ? P : need;
 }
@@ -406,7 +412,7 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
     case NACHO_OP_SPMM: {
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
         const int64_t Pe = fused_partitions(op, dtype, total, P);
-        *bytes = carve_carry(nullptr, Pe, dtype, op == NACHO_OP_SPMM ? NACHO_WAVE : 1).bytes;
+        *bytes = carve_carry(nullptr, Pe, dtype, op == NACHO_OP_SPMM ? spmm_pass(n_dense) : 1).bytes;
         return NACHO_OK;
     }
     case NACHO_OP_SPMUL:
@@ -445,10 +451,10 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
         if (op == NACHO_OP_SPMM && n_dense < 1) return NACHO_ERR_INVALID_ARG;
         Pe = fused_partitions(op, dtype, total, P);
-        CarryWs c = carve_carry(ws, Pe, dtype, op == NACHO_OP_SPMM ? NACHO_WAVE : 1);
+        CarryWs c = carve_carry(ws, Pe, dtype, op == NACHO_OP_SPMM ? spmm_pass(n_dense) : 1);
         w = c.parts;
         need = c.bytes;
-        if (P == 0) g = op == NACHO_OP_SPMV ? (int64_t)spmv_capacity(dtype) : (int64_t)spmm_capacity(dtype) * n_dense;
+        if (P == 0) g = op == NACHO_OP_SPMV ? (int64_t)spmv_capacity(dtype) : spmm_grain(total, compute_units()) * n_dense;
         break;
     }
     case NACHO_OP_SPMUL:
@@ -673,36 +679,45 @@ int32_t nacho_spmm(const nacho_tensor *A, const void *B, int64_t n, int64_t ldb,
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && !A->val) return NACHO_ERR_INVALID_ARG;
     const int64_t Pe = fused_partitions(NACHO_OP_SPMM, dtype, nnz, P);
-    CarryWs w = carve_carry(ws, Pe, dtype, NACHO_WAVE);
+    int pass = spmm_pass(n);
+    CarryWs w = carve_carry(ws, Pe, dtype, pass);
+    if (ws && ws_bytes < w.bytes) {
+        pass = NACHO_WAVE;
+        w = carve_carry(ws, Pe, dtype, pass);
+    }
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    const int64_t n_rows = A->lvl[0].extent;
     profile_begin(s);
     // cost of a stored non-zero = n (broadcast over the dense loop); queries are multiples of n
-    const int64_t grain = (P == 0) ? (int64_t)spmm_capacity(dtype) * n : 0;
-    ZeroRows zero;                      // rows of C whose row of A is empty
-    zero.base = C;
-    zero.ld = ldc;
-    zero.width = (int32_t)n;
-    zero.elem = (int32_t)dtype_size(dtype);
-    if (launch_partition(dev, n, Pe, grain, nullptr, nnz, w.parts.coord, w.parts.posn, w.parts.cost, s, nullptr, 0,
-                         nullptr, &zero) != hipSuccess)
-        return NACHO_ERR_HIP;
-    profile_mark("partition");
-    // The executing kernel gives every lane of a wavefront one column of B: wider operands go through it
-    // in stretches of 64 columns.  The partitions are the same for every stretch (the queries are multiples
-    // of n, so no boundary falls inside the dense loop), and so are the carry buffers, which the stretches
-    // use one after the other on the stream.
+    const int64_t grain = P == 0 ? spmm_grain(nnz, compute_units()) : 0;
+    const bool whole = grain > 0 && nnz > 0 && spmm_whole(Pe, n_rows);
+    if (!whole) {
+        ZeroRows zero;                  // rows of C whose row of A is empty
+        zero.base = C;
+        zero.ld = ldc;
+        zero.width = (int32_t)n;
+        zero.elem = (int32_t)dtype_size(dtype);
+        if (launch_partition(dev, n, Pe, grain * n, nullptr, nnz, w.parts.coord, w.parts.posn, w.parts.cost, s, nullptr,
+                             0, nullptr, &zero) != hipSuccess)
+            return NACHO_ERR_HIP;
+        profile_mark("partition");
+    }
+    // Wide operands go through in passes.  The partitions are the same for every pass (the queries are multiples of n,
+    // so no boundary falls inside the dense loop), and so are the carry buffers, which the passes use one after the
+    // other on the stream.
     const size_t elem = dtype_size(dtype);
-    for (int64_t j0 = 0; j0 < n; j0 += NACHO_WAVE) {
-        const int width = (int)(n - j0 < NACHO_WAVE ? n - j0 : NACHO_WAVE);
+    for (int64_t j0 = 0; j0 < n; j0 += pass) {
+        const int width = (int)(n - j0 < pass ? n - j0 : pass);
         const void *Bj = static_cast<const char *>(B) + (size_t)j0 * elem;
         void *Cj = static_cast<char *>(C) + (size_t)j0 * elem;
-        if (launch_spmm_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, Bj, width, ldb, Cj, ldc,
-                             w.parts.coord, w.parts.posn, Pe, w.carry_val, w.carry_row, s) != hipSuccess)
+        if (launch_spmm_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, Bj, width, ldb, Cj, ldc, n_rows, nnz,
+                             w.parts.coord, w.parts.posn, w.parts.cost, Pe, w.carry_val, w.carry_row, grain, n, whole,
+                             s) != hipSuccess)
             return NACHO_ERR_HIP;
         profile_mark("spmm_exec");
-        if (launch_spmm_fixup(dtype, Cj, ldc, width, Pe, w.carry_val, w.carry_row, A->lvl[1].pos, grain / n, s) !=
-            hipSuccess)
+        if (launch_spmm_fixup(dtype, Cj, ldc, width, Pe, w.carry_val, w.carry_row, A->lvl[1].pos, w.parts.posn, grain,
+                              s) != hipSuccess)
             return NACHO_ERR_HIP;
         profile_mark("spmm_fixup");
     }

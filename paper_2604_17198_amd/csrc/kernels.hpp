@@ -45,15 +45,19 @@ hipError_t launch_zero_vector(int dtype, void *y, int64_t n, hipStream_t stream)
 hipError_t launch_spmv_fixup(int dtype, void *y, int64_t P, const void *carry_val,
                              const int32_t *carry_row, const int32_t *pos, int64_t grain, hipStream_t stream);
 
-// ---- SpMM (lane per column of B, n <= 64) -----------------------------------
-int spmm_capacity(int dtype);
+// ---- SpMM ------------------------------------------------------------------
+int spmm_capacity();                                // most non-zeros of a partition
+int spmm_grain(int64_t nnz, int units);             // non-zeros of a fixed-grain partition
+// Whether a fixed-grain call goes without a partition kernel (the executing kernel writes the table and the zeros).
+bool spmm_whole(int64_t P, int64_t n_rows);
+// carry_val: n values per partition.  `grain` (non-zeros) > 0: fixed-grain partitions.
 hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
-                            const void *B, int n, int64_t ldb, void *C, int64_t ldc,
-                            const int32_t *coord, const int32_t *posn, int64_t P, void *carry_val,
-                            int32_t *carry_row, hipStream_t stream);
-// `grain` > 0: fixed-grain partitions of `grain` non-zeros (run lengths then come from `pos`).
+                            const void *B, int n, int64_t ldb, void *C, int64_t ldc, int64_t n_rows, int64_t nnz,
+                            int32_t *coord, int32_t *posn, int64_t *cost, int64_t P, void *carry_val,
+                            int32_t *carry_row, int64_t grain, int64_t cost_scale, bool whole, hipStream_t stream);
 hipError_t launch_spmm_fixup(int dtype, void *C, int64_t ldc, int n, int64_t P, const void *carry_val,
-                             const int32_t *carry_row, const int32_t *pos, int64_t grain, hipStream_t stream);
+                             const int32_t *carry_row, const int32_t *pos, const int32_t *posn, int64_t grain,
+                             hipStream_t stream);
 
 // ---- k-way union addition ---------------------------------------------------
 enum { SPADD_VECTOR = 0, SPADD_CSR = 1, SPADD_DCSR = 2, SPADD_COO = 3, SPADD_CSF3 = 4 };

@@ -1,14 +1,23 @@
-// SpMM execution, C = A B with A in CSR and B, C dense row-major: one wavefront
-// per partition, one lane per column of B (n <= 64), loop order i -> j -> k with
-// the dense k innermost (the broadcast rule of Section 4.2.2 scales the cost of
-// every stored non-zero by n, so the partitions are those of SpMV).
+// SpMM execution, C = A B with A in CSR and B, C dense row-major: loop order i -> j -> k with the dense k
+// innermost (the broadcast rule of Section 4.2.2 scales the cost of every stored non-zero by n, so the
+// partitions are those of SpMV), one wavefront per partition.
 //
-// The wavefront stages its partition's crd/val and the pos entries of its rows
-// in LDS, then streams over the non-zeros sixteen at a time: sixteen rows of B are
-// requested (one 4n-byte coalesced load each) before the first is consumed.  A
-// row of C is stored by the partition in which the row starts; the partial row
-// of a partition that starts inside a row goes to the carry buffer and is added
-// by the fix-up pass in a fixed order.
+// What bounds it: large matrices the rows of B (30M non-zeros x 256 bytes: 6.6 TB/s out of the last-level cache and
+// memory), all others how many of those rows are on their way at a time.  So a row of B is not spread over the whole
+// wavefront: a lane takes 16 bytes of it, W = 4 to 16 lanes a row, and the 64 / W groups of lanes of a wavefront each
+// walk their own stretch of the partition's non-zeros.  One instruction then asks for up to 16 rows, and the chain of
+// dependent steps is that many times shorter (20,000 non-zeros, n = 4: 80 us with a lane per column and the wavefront
+// walking all 512 non-zeros of a partition, sixteen at a time).
+//
+// The wavefront stages crd and val of its partition in LDS and beside every non-zero the row that starts with it, so
+// that the walk needs neither pos nor searches and empty rows do not exist for it.  A group keeps the sum of the row
+// in hand in registers, stores rows that start and end in its stretch, and keeps the piece in front of its first row
+// start (head) and the one of its last row (tail) to the end, where a tail is joined with the heads behind it.  A row
+// of C is stored by the partition in which the row starts; the piece of a row that started in an earlier partition
+// goes to the carry buffer and is added by the fix-up pass in a fixed order.  No floating-point atomics: results
+// repeat bit for bit.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -16,187 +25,383 @@ namespace nacho {
 
 namespace {
 
-constexpr int kUnroll = 16;
+constexpr int kGrain = 512;                    // most non-zeros of a partition
 
-template <typename T, int G, int RBLK>
+// V elements of a row of B or C; in memory they are aligned as one element is (16-byte loads and stores need no more).
+template <typename T, int V> struct Piece {
+    typedef T type __attribute__((ext_vector_type(V)));
+    typedef type mem __attribute__((aligned(sizeof(T))));
+};
+
+// W lanes a row, CPL pieces of V elements a lane.  kWhole: there is no partition kernel; the wavefront searches its
+// rows, stores its part of the partition table and writes the zeros of its empty rows.
+template <typename T, int V, int W, int CPL, bool kWhole>
 __global__ void __launch_bounds__(NACHO_WAVE)
-spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
-                 const T *__restrict__ val, const T *__restrict__ B, int n, int64_t ldb,
-                 T *__restrict__ C, int64_t ldc, const int32_t *__restrict__ coord,
-                 const int32_t *__restrict__ posn, T *__restrict__ carry_val,
-                 int32_t *__restrict__ carry_row, WaveLog wlog)
+spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd, const T *__restrict__ val,
+                 const T *__restrict__ B, int n, int span, int64_t ldb, T *__restrict__ C, int64_t ldc,
+                 int32_t *__restrict__ coord, int32_t *__restrict__ posn, int64_t *__restrict__ cost,
+                 T *__restrict__ carry_val, int32_t *__restrict__ carry_row, int n_rows, int nnz, int grain,
+                 int64_t cost_scale, WaveLog wlog)
 {
+    typedef typename Piece<T, V>::type P;
+    typedef typename Piece<T, V>::mem PM;
+    constexpr int NG = NACHO_WAVE / W;         // groups
+    constexpr int kSlots = kGrain + 4 * NG;    // a group's stretch is followed by 4 words (banks of their own for every group)
+    constexpr int kIter = kGrain / NACHO_WAVE;
+    // non-zeros a group has in flight: 64 registers of B, 16 at most
+    constexpr int kRegs = CPL * V * (int)sizeof(T) / 4;
+    constexpr int U = kRegs <= 4 ? 16 : (kRegs <= 8 ? 8 : 4);
     const WaveStamp stamp = wave_begin();
-    __shared__ int32_t s_crd[G];
-    __shared__ T s_val[G];
-    __shared__ int32_t spos[RBLK + 1];
+    // crd and val; at the end, over them, the heads of the groups
+    constexpr int kStaged = kSlots * (4 + (int)sizeof(T)), kHeads = NACHO_WAVE * CPL * (int)sizeof(P);
+    __shared__ alignas(16) char smem[kStaged > kHeads ? kStaged : kHeads];
+    __shared__ alignas(16) int32_t s_row[kSlots];      // the row that starts with the non-zero, or -1
+    T *s_val = reinterpret_cast<T *>(smem);
+    int32_t *s_crd = reinterpret_cast<int32_t *>(smem + kSlots * sizeof(T));
 
-    const int p = blockIdx.x;
-    const int lane = threadIdx.x;
-    const bool col = lane < n;
-    const int r0 = coord[2 * p], r1 = coord[2 * p + 2];
-    const int n0 = posn[2 * p + 1], n1 = posn[2 * p + 3];
-    const int pr0 = pos[r0], pr1 = pos[r1];
-    const bool has_head = n0 > pr0;
-    const int next_first = (n1 > pr1) ? r1 + 1 : r1;
-    const int nrows = next_first - r0;
-
-    for (int i = lane; i < n1 - n0; i += NACHO_WAVE) {
-        s_crd[i] = crd[n0 + i];
-        s_val[i] = val[n0 + i];
+    const int p = blockIdx.x, lane = threadIdx.x, g = lane / W, gl = lane & (W - 1);
+    int r0, r1, n0, n1;
+    if (kWhole) {
+        const int base = pos[0];
+        const long long Qa = (long long)p * grain, Qb = Qa + grain;
+        n0 = base + (int)(Qa < nnz ? Qa : nnz);
+        n1 = base + (int)(Qb < nnz ? Qb : nnz);
+        rows_holding(pos, n_rows, n0, n1, r0, r1);
+        if (p == 0) r0 = 0;
+        else if (Qa >= nnz) r0 = n_rows;
+        if (Qb >= nnz) r1 = n_rows;
+    } else {
+        r0 = coord[2 * p]; r1 = coord[2 * p + 2];
+        n0 = posn[2 * p + 1]; n1 = posn[2 * p + 3];
     }
-    int blk0 = r0;                                     // spos[i] = pos[blk0 + i]
-    {
-        const int cnt = nrows < RBLK ? nrows : RBLK;
-        if (nrows > 0)
-            for (int i = lane; i <= cnt; i += NACHO_WAVE) spos[i] = pos[blk0 + i];
+    const int len = n1 - n0;
+    const int S = ((len + NG - 1) / NG + 3) & ~3;      // a group's stretch
+    const int left = len - g * S, items = left < 0 ? 0 : (left < S ? left : S);
+    const int base = g * (S + 4);                      // its first slot
+    // everything is asked for before the first wait: the stretch, the ends of the rows
+    int32_t c_in[kIter];
+    T v_in[kIter];
+#pragma unroll
+    for (int j = 0; j < kIter; ++j) {
+        const int i = gl + j * W;
+        c_in[j] = 0;
+        v_in[j] = T(0);
+        if (i < items) {
+            c_in[j] = __builtin_nontemporal_load(crd + (n0 + g * S + i));
+            v_in[j] = __builtin_nontemporal_load(val + (n0 + g * S + i));
+        }
+    }
+    const int pr0 = pos[r0], pr1 = pos[r1];
+    const bool has_head = n0 > pr0;                    // row r0 started in an earlier partition
+    const int next_first = n1 > pr1 ? r1 + 1 : r1;     // first row that starts after this partition
+    int row = r0 + lane, row_a = 0, row_b = 0;
+    if (row < next_first) { row_a = pos[row]; row_b = pos[row + 1]; }
+    if (kWhole && lane == 0 && blockIdx.y == 0) {
+        coord[2 * p] = r0;
+        coord[2 * p + 1] = r0 < n_rows ? (p == 0 ? 0 : crd[n0]) : 0;
+        posn[2 * p] = r0;
+        posn[2 * p + 1] = p == 0 ? 0 : (r0 < n_rows ? n0 : nnz);
+        cost[p] = (int64_t)(n0 - pos[0]) * cost_scale;
+        if (p == (int)gridDim.x - 1) {
+            coord[2 * p + 2] = n_rows;
+            coord[2 * p + 3] = 0;
+            posn[2 * p + 2] = n_rows;
+            posn[2 * p + 3] = nnz;
+            cost[p + 1] = (int64_t)nnz * cost_scale;
+        }
+    }
+
+    // this lane's columns: piece c is at col[c] (the last piece of a row moves back where it would stick out: it holds
+    // some columns of the one before it again, with the same sums)
+    const int j0 = blockIdx.y * span, width = n - j0 < span ? n - j0 : span;
+    const int pieces = (width + V - 1) / V;
+    int col[CPL];
+    bool mine[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+        const int i = c * W + gl;
+        mine[c] = i < pieces;
+        col[c] = j0 + i * V < n - V ? j0 + i * V : n - V;
+    }
+
+#pragma unroll
+    for (int j = 0; j < kIter; ++j) {
+        const int i = gl + j * W;
+        if (i < S) {
+            s_crd[base + i] = c_in[j];
+            s_val[base + i] = v_in[j];
+            s_row[base + i] = -1;
+        }
+    }
+    __syncthreads();
+    const float per_S = 1.0f / (float)S;
+    for (;;) {                                         // rows, 64 at a time
+        const bool is_row = row < next_first;
+        if (is_row && row_b > row_a && row_a >= n0) {
+            const int i = row_a - n0;                  // (< len: the row starts in this partition)
+            const int at = (int)(((float)i + 0.5f) * per_S);       // i / S
+            s_row[i + 4 * at] = row;
+        }
+        const int first = __builtin_amdgcn_readfirstlane(row), next = first + NACHO_WAVE;
+        if (kWhole) {
+            const unsigned long long empty = __ballot(is_row && row_b == row_a);
+            if (empty)
+                for (int i = g; i < NACHO_WAVE; i += NG) {
+                    if ((unsigned)((i < 32 ? (unsigned)empty : (unsigned)(empty >> 32)) >> (i & 31)) & 1u) {
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c)
+                            if (mine[c]) *reinterpret_cast<PM *>(C + (int64_t)(first + i) * ldc + col[c]) = P(T(0));
+                    }
+                }
+        }
+        if (next >= next_first) break;
+        int from = next;
+        if (!kWhole && __ballot(row_b > row_a) == 0ull) {
+            // 64 rows without an entry (the partition kernel wrote their zeros): however many there are, stepped over
+            const int q = __builtin_amdgcn_readfirstlane(row_b);
+            if (q >= n1) break;
+            from = first_row_past(pos, next, next_first, q);
+        }
+        row = from + lane;
+        row_a = row_b = 0;
+        if (row < next_first) { row_a = pos[row]; row_b = pos[row + 1]; }
     }
     __syncthreads();
 
-    T acc = T(0);
-    int cur = r0;                                      // row being accumulated
-    int cur_end = n1;                                  // its end inside the partition
-    if (nrows > 0) { const int e = spos[1]; cur_end = e < n1 ? e : n1; }
-
-    // store row `cur` (to C, or to the carry buffer when the row started in an earlier partition)
-    auto store = [&]() {
-        if (has_head && cur == r0) { if (col) carry_val[(int64_t)p * NACHO_WAVE + lane] = acc; }
-        else if (col) C[(int64_t)cur * ldc + lane] = acc;
-        acc = T(0);
+    P acc[CPL], head[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) acc[c] = head[c] = P(T(0));
+    int cur = -1;                                      // the row in hand; -1: one that started before the stretch
+    auto store_row = [&](int r, const P (&x)[CPL]) {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+            if (mine[c]) *reinterpret_cast<PM *>(C + (int64_t)r * ldc + col[c]) = x[c];
     };
-    // move on to the row that holds position q (cur_end <= q < n1).  The rows in between are
-    // empty: their rows of C are zero already (the partition kernel wrote them), so they are
-    // stepped over however many there are.
-    int win = nrows < RBLK ? nrows : RBLK;             // rows whose pos entries are staged: blk0 .. blk0 + win
-    auto advance = [&](int q) {
-        ++cur;
-        const int idx = cur + 1 - blk0;
-        if (idx <= win) {
-            const int e = spos[idx];
-            if (e > q) {                               // the next row holds q: the common case
-                cur_end = e < n1 ? e : n1;
-                return;
+    // N non-zeros from slot base + i0 on; kAll: all of them lie in the stretch
+    auto step = [&](int i0, auto count, auto all) {
+        constexpr int N = decltype(count)::value;
+        constexpr bool kAll = decltype(all)::value;
+        P b[N][CPL];
+        int r[N];
+        T v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int64_t at = (int64_t)s_crd[base + i0 + u] * ldb;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                b[u][c] = P(T(0));
+                if (mine[c] && (kAll || i0 + u < items)) b[u][c] = *reinterpret_cast<const PM *>(B + at + col[c]);
             }
         }
-        if (spos[win] > q) {
-            while (spos[cur + 1 - blk0] <= q) ++cur;   // inside the window: at most RBLK cheap steps
-        } else {                                       // beyond the staged window: search pos, restage
-            cur = first_row_past(pos, blk0 + win, next_first, q);
-            __syncthreads();
-            blk0 = cur;
-            const int left = next_first - blk0;
-            win = left < RBLK ? left : RBLK;
-            for (int i = lane; i <= win; i += NACHO_WAVE) spos[i] = pos[blk0 + i];
-            __syncthreads();
-        }
-        const int e = spos[cur + 1 - blk0];
-        cur_end = e < n1 ? e : n1;
-    };
-
-    for (int q0 = n0; q0 < n1; q0 += kUnroll) {
-        T b[kUnroll], v[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int q = q0 + u;
-            const bool in = q < n1;
-            const int c = in ? s_crd[q - n0] : 0;
-            v[u] = in ? s_val[q - n0] : T(0);
-            b[u] = (in && col) ? B[(int64_t)c * ldb + lane] : T(0);
+        for (int u = 0; u < N; ++u) {
+            r[u] = s_row[base + i0 + u];
+            v[u] = s_val[base + i0 + u];
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int q = q0 + u;
-            if (q < n1) {
-                if (q >= cur_end) { store(); advance(q); }
-                acc += v[u] * b[u];
+        for (int u = 0; u < N; ++u) {
+            if (r[u] >= 0) {
+                if (cur >= 0) store_row(cur, acc);
+                else {
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) head[c] = acc[c];
+                }
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) acc[c] = P(T(0));
+                cur = r[u];
             }
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) acc[c] += v[u] * b[u][c];
         }
+    };
+    int i0 = 0;
+    for (; i0 + U <= items; i0 += U) step(i0, std::integral_constant<int, U>(), std::true_type());
+    for (; i0 < items; i0 += 4) step(i0, std::integral_constant<int, 4>(), std::false_type());
+    if (cur < 0) {
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) head[c] = acc[c];
     }
-    // the row of the last non-zero (or, for a partition without work that starts inside a
-    // row, a zero carry); every row after it up to the next partition is empty
-    if (cur < next_first) store();
-    if (lane == 0) carry_row[p] = has_head ? r0 : -1;
-    wave_end(wlog, blockIdx.x, stamp, (uint32_t)(n1 - n0), (uint32_t)nrows);
+
+    // a group's last row goes on in the heads of the groups behind it, up to the first that starts a row of its own
+    const unsigned long long started = __ballot(cur >= 0);
+    __syncthreads();
+    P *s_head = reinterpret_cast<P *>(smem);
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) s_head[c * NACHO_WAVE + lane] = head[c];
+    __syncthreads();
+    auto starts = [&](int h) { return (((h * W) < 32 ? (unsigned)started : (unsigned)(started >> 32)) >> ((h * W) & 31) & 1u) != 0u; };
+    auto add_heads = [&](P (&x)[CPL]) {
+        for (int h = g + 1; h < NG; ++h) {
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) x[c] += s_head[c * NACHO_WAVE + h * W + gl];
+            if (starts(h)) break;
+        }
+    };
+    if (cur >= 0) {
+        add_heads(acc);
+        store_row(cur, acc);
+    }
+    if (has_head && g == 0) {                          // the piece of the row that started in an earlier partition
+        if (cur < 0) add_heads(head);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+            if (mine[c]) *reinterpret_cast<PM *>(carry_val + (int64_t)p * n + col[c]) = head[c];
+    }
+    if (lane == 0 && blockIdx.y == 0) carry_row[p] = has_head ? r0 : -1;
+    if (blockIdx.y == 0) wave_end(wlog, p, stamp, (uint32_t)len, (uint32_t)(next_first - r0));
 }
+
+// Carry fix-up: 16 lanes and up to 64 columns per partition, 16 partitions per workgroup.  The carries of a row lie in
+// consecutive partitions; the lanes of the first one add the run to the row of C.  A run of more than kShort carries
+// (there is at most one per workgroup: it is longer than the workgroup's partitions) is added by the whole workgroup,
+// every group a sixteenth of it: the largest row of 30M non-zeros has 488, which one wavefront, a row of carries at a
+// time, took 35 us for.  The order of the additions is fixed.
+constexpr int kFixLanes = 16, kFixCols = 4, kFixGroups = 256 / kFixLanes, kShort = 32;
 
 template <typename T>
 __global__ void __launch_bounds__(256)
 spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restrict__ carry_val,
-                  const int32_t *__restrict__ carry_row, const int32_t *__restrict__ pos, int grain)
+                  const int32_t *__restrict__ carry_row, const int32_t *__restrict__ pos,
+                  const int32_t *__restrict__ posn, int grain)
 {
-    const int p = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / NACHO_WAVE);
-    if (p >= P) return;
-    const int lane = lane_id();
-    const int r = carry_row[p];
-    if (r < 0) return;
-    if (p > 0 && carry_row[p - 1] == r) return;
+    static_assert(kShort >= kFixGroups, "one long run per workgroup");
+    __shared__ T part[kFixGroups][kFixLanes * kFixCols];
+    __shared__ int s_first, s_end, s_row;
+    const int g = threadIdx.x / kFixLanes, gl = threadIdx.x & (kFixLanes - 1);
+    const int p = blockIdx.x * kFixGroups + g;
+    const int j0 = blockIdx.y * (kFixLanes * kFixCols) + gl;
+    if (threadIdx.x == 0) s_first = -1;
+    __syncthreads();
+    const int r = p < P ? carry_row[p] : -1;
+    const bool first = r >= 0 && (p == 0 || carry_row[p - 1] != r);
     int e = p + 1;
-    if (grain > 0) {
-        // fixed-grain partitions: the carries of row r come from the partitions that start
-        // strictly inside it, the last one being ceil(pos[r+1] / grain) - 1
-        e = ((pos[r + 1] - pos[0]) + grain - 1) / grain;
-        if (e > P) e = P;
-    } else for (;;) {
-        const int q = e + lane;
-        const bool same = q < P && carry_row[q] == r;
-        const unsigned long long m = __ballot(same);
-        if (m == ~0ull) { e += NACHO_WAVE; continue; }
-        e += __ffsll((long long)~m) - 1;
-        break;
+    if (first) {
+        // the run ends with the last partition that starts inside the row
+        const int row_end = pos[r + 1];
+        if (grain > 0) e = (row_end - pos[0] + grain - 1) / grain;
+        else {
+            int lo = p + 1, hi = P;                    // the first partition that starts at or behind the row's end
+            while (lo < hi) {
+                const int mid = lo + ((hi - lo) >> 1);
+                if (posn[2 * mid + 1] < row_end) lo = mid + 1; else hi = mid;
+            }
+            e = lo;
+        }
+        e = e < P ? e : P;
     }
-    if (lane >= n) return;
-    // 32 independent partial sums keep 32 carry rows in flight (a row of hundreds of
-    // thousands of non-zeros has hundreds of carries); the order of the additions is
-    // fixed, so the result repeats bit for bit
-    constexpr int kAcc = 32;
-    T s[kAcc];
+    // carries q, q + step, ... below `to`, eight of them in flight
+    auto sum = [&](int q, int to, int step, T (&x)[kFixCols]) {
 #pragma unroll
-    for (int u = 0; u < kAcc; ++u) s[u] = T(0);
-    int q = p;
-    for (; q + kAcc <= e; q += kAcc) {
+        for (int c = 0; c < kFixCols; ++c) x[c] = T(0);
+        for (; q < to; q += 8 * step) {
+            T t[8][kFixCols];
 #pragma unroll
-        for (int u = 0; u < kAcc; ++u) s[u] += carry_val[(int64_t)(q + u) * NACHO_WAVE + lane];
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int c = 0; c < kFixCols; ++c) {
+                    t[u][c] = T(0);
+                    if (q + u * step < to && j0 + c * kFixLanes < n)
+                        t[u][c] = carry_val[(int64_t)(q + u * step) * n + j0 + c * kFixLanes];
+                }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int c = 0; c < kFixCols; ++c) x[c] += t[u][c];
+        }
+    };
+    T x[kFixCols];
+    if (first && e - p <= kShort) {
+        sum(p, e, 1, x);
+#pragma unroll
+        for (int c = 0; c < kFixCols; ++c)
+            if (j0 + c * kFixLanes < n) C[(int64_t)r * ldc + j0 + c * kFixLanes] += x[c];
+    } else if (first && gl == 0) {
+        s_first = p;
+        s_end = e;
+        s_row = r;
     }
-    for (; q < e; ++q) s[(q - p) & (kAcc - 1)] += carry_val[(int64_t)q * NACHO_WAVE + lane];
+    __syncthreads();
+    if (s_first < 0) return;                           // (the whole workgroup)
+    sum(s_first + g, s_end, kFixGroups, x);
 #pragma unroll
-    for (int w = kAcc / 2; w > 0; w >>= 1)
+    for (int c = 0; c < kFixCols; ++c) part[g][c * kFixLanes + gl] = x[c];
+    __syncthreads();
+    if (g < kFixCols && j0 + g * kFixLanes < n) {
+        T y = T(0);
 #pragma unroll
-        for (int u = 0; u < w; ++u) s[u] += s[u + w];
-    C[(int64_t)r * ldc + lane] += s[0];
+        for (int u = 0; u < kFixGroups; ++u) y += part[u][g * kFixLanes + gl];
+        C[(int64_t)s_row * ldc + j0 + g * kFixLanes] += y;
+    }
 }
-
-constexpr int kGrain = 512, kRows = 512;
 
 }  // namespace
 
-int spmm_capacity(int dtype) { (void)dtype; return kGrain; }
+int spmm_capacity() { return kGrain; }
+
+// Non-zeros per partition when the caller leaves the partitioning to the library: enough wavefronts for the chip.
+int spmm_grain(int64_t nnz, int units)
+{
+    const int64_t per = nnz / ((int64_t)units * 16);
+    return per >= kGrain ? kGrain : (per < 64 ? 64 : (int)((per + 63) / 64 * 64));
+}
+
+// Small calls do without a partition kernel (its place in the stream is half of what they take): a handful of
+// wavefronts find their rows in two or three rounds of loads that hit the cache.  Not so many rows that one wavefront
+// could be left with zeroing tens of thousands of them.
+bool spmm_whole(int64_t P, int64_t n_rows) { return P <= 1024 && n_rows <= 16384; }
 
 hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
-                            const void *B, int n, int64_t ldb, void *C, int64_t ldc,
-                            const int32_t *coord, const int32_t *posn, int64_t P, void *carry_val,
-                            int32_t *carry_row, hipStream_t stream)
+                            const void *B, int n, int64_t ldb, void *C, int64_t ldc, int64_t n_rows, int64_t nnz,
+                            int32_t *coord, int32_t *posn, int64_t *cost, int64_t P, void *carry_val,
+                            int32_t *carry_row, int64_t grain, int64_t cost_scale, bool whole,
+                            hipStream_t stream)
 {
-    if (dtype == NACHO_F64)
-        hipLaunchKernelGGL((spmm_exec_kernel<double, kGrain, kRows>), dim3((unsigned)P), dim3(NACHO_WAVE),
-                           0, stream, pos, crd, (const double *)val, (const double *)B, n, ldb,
-                           (double *)C, ldc, coord, posn, (double *)carry_val, carry_row, nacho_host::wave_log());
-    else
-        hipLaunchKernelGGL((spmm_exec_kernel<float, kGrain, kRows>), dim3((unsigned)P), dim3(NACHO_WAVE),
-                           0, stream, pos, crd, (const float *)val, (const float *)B, n, ldb,
-                           (float *)C, ldc, coord, posn, (float *)carry_val, carry_row, nacho_host::wave_log());
+    const int V = dtype == NACHO_F64 ? 2 : 4;
+    // stretches of up to 64 pieces of V columns, of about equal width
+    const int pieces = n < V ? n : (n + V - 1) / V, stretches = (pieces + NACHO_WAVE - 1) / NACHO_WAVE;
+    const int per = (pieces + stretches - 1) / stretches;
+    const int span = n < V ? n : per * V;
+#define NACHO_SPMM_LAUNCH(T, VV, W, CPL, WHOLE)                                                                         \
+    hipLaunchKernelGGL((spmm_exec_kernel<T, VV, W, CPL, WHOLE>), dim3((unsigned)P, (unsigned)stretches), dim3(NACHO_WAVE), 0,  \
+                       stream, pos, crd, (const T *)val, (const T *)B, n, span, ldb, (T *)C, ldc, coord, posn, cost,    \
+                       (T *)carry_val, carry_row, (int)n_rows, (int)nnz, (int)grain, cost_scale, \
+                       nacho_host::wave_log())
+#define NACHO_SPMM_SHAPE(T, VV, W, CPL)                                                                                 \
+    do {                                                                                                                \
+        if (whole) NACHO_SPMM_LAUNCH(T, VV, W, CPL, true);                                                              \
+        else NACHO_SPMM_LAUNCH(T, VV, W, CPL, false);                                                                   \
+    } while (0)
+    // the fewest lanes that hold a row: more rows in flight per instruction
+#define NACHO_SPMM_TYPE(T, VV)                                                                                          \
+    do {                                                                                                                \
+        if (n < VV) NACHO_SPMM_SHAPE(T, 1, 4, 1);                                                                       \
+        else if (per <= 4) NACHO_SPMM_SHAPE(T, VV, 4, 1);                                                               \
+        else if (per <= 8) NACHO_SPMM_SHAPE(T, VV, 8, 1);                                                               \
+        else if (per <= 16) NACHO_SPMM_SHAPE(T, VV, 16, 1);                                                             \
+        else if (per <= 32) NACHO_SPMM_SHAPE(T, VV, 16, 2);                                                             \
+        else if (per <= 48) NACHO_SPMM_SHAPE(T, VV, 16, 3);                                                             \
+        else NACHO_SPMM_SHAPE(T, VV, 16, 4);                                                                            \
+    } while (0)
+    if (dtype == NACHO_F64) NACHO_SPMM_TYPE(double, 2);
+    else NACHO_SPMM_TYPE(float, 4);
+#undef NACHO_SPMM_TYPE
+#undef NACHO_SPMM_SHAPE
+#undef NACHO_SPMM_LAUNCH
     return hipGetLastError();
 }
 
 hipError_t launch_spmm_fixup(int dtype, void *C, int64_t ldc, int n, int64_t P, const void *carry_val,
-                             const int32_t *carry_row, const int32_t *pos, int64_t grain, hipStream_t stream)
+                             const int32_t *carry_row, const int32_t *pos, const int32_t *posn, int64_t grain,
+                             hipStream_t stream)
 {
-    const unsigned grid = (unsigned)((P * NACHO_WAVE + 255) / 256);
+    constexpr int cols = kFixLanes * kFixCols;
+    const dim3 grid((unsigned)((P + kFixGroups - 1) / kFixGroups), (unsigned)((n + cols - 1) / cols));
     if (dtype == NACHO_F64)
-        hipLaunchKernelGGL((spmm_fixup_kernel<double>), dim3(grid), dim3(256), 0, stream, (double *)C, ldc,
-                           n, (int)P, (const double *)carry_val, carry_row, pos, (int)grain);
+        hipLaunchKernelGGL((spmm_fixup_kernel<double>), grid, dim3(256), 0, stream, (double *)C, ldc,
+                           n, (int)P, (const double *)carry_val, carry_row, pos, posn, (int)grain);
     else
-        hipLaunchKernelGGL((spmm_fixup_kernel<float>), dim3(grid), dim3(256), 0, stream, (float *)C, ldc,
-                           n, (int)P, (const float *)carry_val, carry_row, pos, (int)grain);
+        hipLaunchKernelGGL((spmm_fixup_kernel<float>), grid, dim3(256), 0, stream, (float *)C, ldc,
+                           n, (int)P, (const float *)carry_val, carry_row, pos, posn, (int)grain);
     return hipGetLastError();
 }
 
