@@ -134,6 +134,21 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         }
     }
     __syncthreads();
+    if (kWhole) {
+        // zeros of empty rows: every wavefront looks after an equal share of all rows, 64 of them at a time
+        const int z0 = (int)((int64_t)n_rows * p / gridDim.x), z1 = (int)((int64_t)n_rows * (p + 1) / gridDim.x);
+        for (int z = z0; z < z1; z += NACHO_WAVE) {
+            const bool is_empty = z + lane < z1 && pos[z + lane] == pos[z + lane + 1];
+            const unsigned long long empty = __ballot(is_empty);
+            if (empty == 0ull) continue;
+            for (int i = g; i < NACHO_WAVE; i += NG)
+                if ((i < 32 ? (unsigned)empty : (unsigned)(empty >> 32)) >> (i & 31) & 1u) {
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c)
+                        if (mine[c]) *reinterpret_cast<PM *>(C + (int64_t)(z + i) * ldc + col[c]) = P(T(0));
+                }
+        }
+    }
     const float per_S = 1.0f / (float)S;
     for (;;) {                                         // rows, 64 at a time
         const bool is_row = row < next_first;
@@ -142,22 +157,11 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             const int at = (int)(((float)i + 0.5f) * per_S);       // i / S
             s_row[i + 4 * at] = row;
         }
-        const int first = __builtin_amdgcn_readfirstlane(row), next = first + NACHO_WAVE;
-        if (kWhole) {
-            const unsigned long long empty = __ballot(is_row && row_b == row_a);
-            if (empty)
-                for (int i = g; i < NACHO_WAVE; i += NG) {
-                    if ((unsigned)((i < 32 ? (unsigned)empty : (unsigned)(empty >> 32)) >> (i & 31)) & 1u) {
-#pragma unroll
-                        for (int c = 0; c < CPL; ++c)
-                            if (mine[c]) *reinterpret_cast<PM *>(C + (int64_t)(first + i) * ldc + col[c]) = P(T(0));
-                    }
-                }
-        }
+        const int next = __builtin_amdgcn_readfirstlane(row) + NACHO_WAVE;
         if (next >= next_first) break;
         int from = next;
-        if (!kWhole && __ballot(row_b > row_a) == 0ull) {
-            // 64 rows without an entry (the partition kernel wrote their zeros): however many there are, stepped over
+        if (__ballot(row_b > row_a) == 0ull) {
+            // 64 rows without an entry: however many there are, stepped over
             const int q = __builtin_amdgcn_readfirstlane(row_b);
             if (q >= n1) break;
             from = first_row_past(pos, next, next_first, q);
@@ -345,10 +349,11 @@ int spmm_grain(int64_t nnz, int units)
     return per >= kGrain ? kGrain : (per < 64 ? 64 : (int)((per + 63) / 64 * 64));
 }
 
-// Small calls do without a partition kernel (its place in the stream is half of what they take): a handful of
-// wavefronts find their rows in two or three rounds of loads that hit the cache.  Not so many rows that one wavefront
-// could be left with zeroing tens of thousands of them.
-bool spmm_whole(int64_t P, int64_t n_rows) { return P <= 1024 && n_rows <= 16384; }
+// Fixed-grain calls do without a partition kernel: the wavefronts of the executing kernel find their rows in two to
+// four rounds of loads, which hide behind each other, and its place in the stream is saved (100k non-zeros, n = 16:
+// 13.4 to 11.2 us; 1.3M, n = 37: 75 to 72; 30M, n = 64: 1136 to 1125).  The zeros of empty rows are spread over the
+// wavefronts; where that would be thousands of rows each, the partition kernel writes them.
+bool spmm_whole(int64_t P, int64_t n_rows) { return n_rows <= P * 1024; }
 
 hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *B, int n, int64_t ldb, void *C, int64_t ldc, int64_t n_rows, int64_t nnz,

@@ -309,10 +309,15 @@ constexpr int kGrainF32 = 1024, kRowsF32 = 1024;
 
 int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32; }
 
-// Small calls do without a partition kernel.  Its place in the stream (a launch and 3 us) is what the call is made
-// of, while a handful of wavefronts find their rows in two or three rounds of loads that hit the cache.  Not so many
-// rows that one wavefront could be left with zeroing tens of thousands of them.
-bool spmv_whole(int64_t P, int64_t n_rows) { return P <= 1024 && n_rows <= 32768; }
+// Small calls do without a partition kernel.  Its place in the stream (a launch and 3 us) is a third of what such a
+// call takes, while the wavefronts find their rows in two or three rounds of loads that hit the cache (40,000
+// non-zeros: 9.3 us in all; 1M: 16.8 to 15.4; 5M: 33.2 to 32.4).  Past a thousand partitions only while x fits an L2:
+// partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 309 to 469 us without).  Not so
+// many rows that one wavefront could be left with zeroing more than some hundred thousand of them.
+bool spmv_whole(int64_t P, int64_t n_rows, int64_t x_bytes)
+{
+    return n_rows <= (1 << 17) && (P <= 1024 || (P <= 8192 && x_bytes <= (4 << 20)));
+}
 
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *x, void *y, int64_t n_rows, int64_t nnz,
