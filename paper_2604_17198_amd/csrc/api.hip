@@ -203,11 +203,11 @@ int compute_units()
 // Entries of a partition of the remapped nest, at most (its entries are asked for one by one, behind their rows:
 // smaller partitions than the merge kernel could hold keep more of those requests in flight).
 constexpr int64_t kMappedEntries = 4096;
-constexpr int64_t kRowGrain = 2048;     // level-0 coordinates of all operands per partition of the row loop
 struct RemapWs {
-    int64_t P0, Pmax, Mmax, count0;
+    int64_t P0, Pmax, Mmax;
     PartsWs parts0;                  // partitions of the row loop
-    int32_t *flags, *qpos, *tsum;
+    unsigned long long *rows_state, *compact_state;      // prefix-sum state, one after the other
+    int64_t state_words;
     RemapArrays remap;
     int64_t *info;                   // {partitions, intersected rows, remapped total cost} of the last call
     MergeFields fields;              // key layout of the remapped nest
@@ -261,22 +261,20 @@ RemapWs carve_remap(void *ws, const nacho_tensor *ops, int k, int32_t dtype, int
     Carver c(ws);
     RemapWs w;
     int64_t rows_total = 0;
-    w.count0 = ops[0].lvl[0].count;
-    w.Mmax = w.count0;
+    w.Mmax = ops[0].lvl[0].count;
     for (int t = 0; t < k; ++t) {
         rows_total += ops[t].lvl[0].count;
         if (ops[t].lvl[0].count < w.Mmax) w.Mmax = ops[t].lvl[0].count;
     }
-    w.P0 = rows_total > 0 ? ceil_div(rows_total, kRowGrain) : 1;
+    w.P0 = rows_total > 0 ? ceil_div(rows_total, kRemapGrain) : 1;
     // the remapped cost never exceeds the stored non-zeros: enough partitions for any outcome
     w.fields = merge_fields(SPADD_CSR, dtype, w.Mmax, ops[0].lvl[1].extent, 0, total_nnz, compute_units());
     w.Pmax = merge_partitions(SPADD_CSR, dtype, k, w.fields, total_nnz, P, kMappedEntries);
     w.parts0 = carve_parts(c, w.P0, k, 1);
-    w.flags = c.take<int32_t>((size_t)w.count0);
-    w.qpos = c.take<int32_t>((size_t)w.count0 * (k - 1));
-    int64_t sw = remap_scan_words(w.count0, 1);
-    if (remap_scan_words(w.Mmax + 1, k) > sw) sw = remap_scan_words(w.Mmax + 1, k);
-    w.tsum = c.take<int32_t>((size_t)sw);
+    const int64_t rows_words = remap_state_words(w.P0, k);
+    w.state_words = rows_words + compact_state_words(w.Mmax);
+    w.rows_state = c.take<unsigned long long>((size_t)w.state_words);
+    w.compact_state = w.rows_state + rows_words;
     w.remap.stride = w.Mmax;
     w.remap.rows = c.take<int32_t>((size_t)w.Mmax);
     w.remap.start = c.take<int32_t>((size_t)w.Mmax * k);
@@ -753,28 +751,19 @@ static int32_t dcsr_product(const nacho_tensor *ops, int32_t k, int32_t dtype, i
         rows.lvl[t][0] = dev.lvl[t][0];
         rows_total += dev.lvl[t][0].count;
     }
-    // (the partition kernel also zeroes the per-row counts; the array starts on a 256-byte
-    // boundary and so does whatever follows it, so whole 64-bit words may be cleared)
-    const int64_t cost_words = ((int64_t)(w.Mmax + 1) * k + 1) / 2;
     if (launch_partition(rows, 1, w.P0, 0, nullptr, rows_total, w.parts0.coord, w.parts0.posn, w.parts0.cost,
-                         s, reinterpret_cast<unsigned long long *>(w.remap.cost), cost_words) != hipSuccess)
+                         s, w.rows_state, w.state_words, o.status) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("rows_partition");
-    if (launch_rows_match(dev, w.P0, w.parts0.posn, w.flags, w.qpos, s) != hipSuccess) return NACHO_ERR_HIP;
-    profile_mark("rows_match");
-    // 2. T (per operand) and the rows' places, 3. its prefix sums: the remapped cost function
-    if (launch_remap_rows(dev, w.flags, w.qpos, w.remap, w.tsum, s) != hipSuccess) return NACHO_ERR_HIP;
-    profile_mark("remap_rows");
-    if (launch_remap_costs(k, w.remap, w.tsum, s) != hipSuccess) return NACHO_ERR_HIP;
-    profile_mark("remap_costs");
+    // 2. T (per operand) and the rows' places, 3. its prefix sums: the remapped cost function.
     // The size of the remapped space (rows all operands store, entries in them) stays on the device:
     // everything below is launched for the upper bounds the workspace was carved for, reads the real
     // sizes there, and lets the surplus workgroups leave at once.  The call never waits for the stream.
     const int64_t capacity = std::min<int64_t>(spadd_capacity(SPADD_CSR, dtype, w.fields), kMappedEntries) - k;
-    if (launch_remap_plan(k, w.remap, capacity, (int64_t)compute_units() * spadd_resident(), P, w.Pmax, w.info,
-                          s) != hipSuccess)
+    if (launch_remap_rows(dev, w.P0, w.parts0.posn, w.remap, w.rows_state, capacity,
+                          (int64_t)compute_units() * spadd_resident(), P, w.Pmax, w.info, o.status, s) != hipSuccess)
         return NACHO_ERR_HIP;
-    profile_mark("remap_plan");
+    profile_mark("remap_rows");
     DevOperands mapped;
     std::memset(&mapped, 0, sizeof(mapped));
     mapped.k = k;
@@ -798,14 +787,14 @@ static int32_t dcsr_product(const nacho_tensor *ops, int32_t k, int32_t dtype, i
     mo.cap_rows = w.Mmax;
     mo.counts = w.counts;
     if (launch_partition(mapped, 1, w.Pmax, 0, nullptr, total, w.parts.coord, w.parts.posn, w.parts.cost, s,
-                         w.tile_state, spadd_state_words(w.Pmax), o.status) != hipSuccess)
+                         w.tile_state, spadd_state_words(w.Pmax)) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("partition");
     if (launch_spadd(SPADD_CSR, dtype, true, mapped, vals, w.Pmax, w.parts.coord, w.parts.posn, w.tile_state, mo,
                      w.fields, s) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("spmul_merge");
-    if (launch_compact_rows(w.remap, w.pos_full, w.counts, o, w.tsum, s) != hipSuccess) return NACHO_ERR_HIP;
+    if (launch_compact_rows(w.remap, w.pos_full, w.counts, o, w.compact_state, s) != hipSuccess) return NACHO_ERR_HIP;
     profile_mark("rows_compact");
     return NACHO_OK;
 }

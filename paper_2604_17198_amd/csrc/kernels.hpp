@@ -132,33 +132,27 @@ hipError_t merge_csf3(int dtype, const MergeLaunch &a);
 // Memoised row loop of Section 3.3, all arrays on the device:
 //   rows[i']                    coordinate of the i'-th row all operands store
 //   start[t * stride + i']      position in operand t's crd / val of that row's first entry
-//   cost[t * (stride + 1) + x]  entries operand t stores in the intersected rows before row x
-//                               (x <= stride; rows past the last intersected one hold nothing)
-//   head[0] = number M of intersected rows, head[1 + t] = cost[t][stride]
+//   cost[t * (stride + 1) + x]  entries operand t stores in the intersected rows before row x (x <= M)
+//   head[0] = number M <= stride of intersected rows, head[1 + t] = cost[t][M]
 struct RemapArrays {
     int32_t *rows, *start, *cost, *head;
     int64_t stride;
 };
-// 32-bit words of scratch a prefix sum over `batch` arrays of n items uses.
-int64_t remap_scan_words(int64_t n, int batch);
-// flags[e] = all operands store row crd0_0[e]; qpos[(t-1) * count_0 + e] = its position in operand t.
-// posn0: boundaries of a P0-way partition of the operands' level-0 coordinate arrays.
-hipError_t launch_rows_match(const DevOperands &ops, int64_t P0, const int32_t *posn0, int32_t *flags,
-                             int32_t *qpos, hipStream_t s);
-// rows, start and the per-row entry counts (in r.cost, which must be zero beforehand), head[0]
-hipError_t launch_remap_rows(const DevOperands &ops, const int32_t *flags, const int32_t *qpos,
-                             const RemapArrays &r, int32_t *tsum, hipStream_t s);
-// r.cost: per-row counts -> exclusive prefix sums (in place), head[1 + t]
-hipError_t launch_remap_costs(int k, const RemapArrays &r, int32_t *tsum, hipStream_t s);
+constexpr int kRemapGrain = 1024;      // level-0 coordinates of all operands per partition of the row loop
+// 64-bit words of look-up state, zero when the kernel starts.
+int64_t remap_state_words(int64_t P0, int k);
+int64_t compact_state_words(int64_t rows);
+// The row loop.  posn0: boundaries of a P0-way partition of the operands' level-0 coordinate arrays.  Also
+// plan[0..2] = {partitions of the remapped nest, intersected rows, remapped total cost}: capacity = entries one
+// partition may hold, round = resident workgroups of the chip (the count is rounded up to whole rounds when
+// P_min == 0), P_max = what the launches are sized for.
+hipError_t launch_remap_rows(const DevOperands &ops, int64_t P0, const int32_t *posn0, const RemapArrays &r,
+                             unsigned long long *state, int64_t capacity, int64_t round, int64_t P_min, int64_t P_max,
+                             int64_t *plan, int32_t *status, hipStream_t s);
 // Result rows that hold an entry: pos_full[0 .. head[0]] over the intersected rows -> out.pos0 / crd0 /
 // pos1 / counts (counts_in = {rows, nnz} of the remapped result).
-hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full,
-                               const int64_t *counts_in, const SpaddOut &out, int32_t *tsum, hipStream_t s);
-// plan[0..2] = {partitions of the remapped nest, intersected rows, remapped total cost}, computed on the
-// device from r.head: capacity = entries one partition may hold, round = resident workgroups of the
-// chip (the count is rounded up to whole rounds when P_min == 0), P_max = what the launches are sized for.
-hipError_t launch_remap_plan(int k, const RemapArrays &r, int64_t capacity, int64_t round, int64_t P_min,
-                             int64_t P_max, int64_t *plan, hipStream_t s);
+hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full, const int64_t *counts_in,
+                               const SpaddOut &out, unsigned long long *state, hipStream_t s);
 hipError_t launch_empty_result(const SpaddOut &out, int64_t *info, hipStream_t s);
 
 // ---- measurement aids: kernels of known traffic (streaming read, copy, independent gathers) ----

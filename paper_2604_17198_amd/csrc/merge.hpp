@@ -442,7 +442,8 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         return arg_ptr->ops.dyn_head ? (int64_t)arg_ptr->ops.dyn_head[0] : arg_ptr->ops.lvl[0][0].extent;
     };
     auto level_count = [&](int t, int m) -> int {      // segments of level m
-        return FMT == SPADD_CSR && m == 0 ? (int)arg_ptr->ops.lvl[t][0].extent : (int)arg_ptr->ops.lvl[t][m].count;
+        if (FMT == SPADD_CSR && m == 0) return kMapped ? (int)row_extent() : (int)arg_ptr->ops.lvl[t][0].extent;
+        return (int)arg_ptr->ops.lvl[t][m].count;
     };
 
     // ---- the segments of this partition -------------------------------------

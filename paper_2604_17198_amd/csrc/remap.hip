@@ -19,9 +19,12 @@
 // array is S_t' and whose row i' starts at the stored position in crd/val.
 // Finally the rows of the result that received no entry are dropped.
 //
-// The prefix sums are the backend capability of Section 4.1: here two kernels,
-// per-tile sums, then every tile adds up the sums of the tiles before it and
-// scans its own items (no chain between workgroups).
+// What bounds it: the arrays are short (a few hundred thousand rows), so the stage is a chain of latencies and kernel
+// launches.  All of 1. to 3. is one kernel, one workgroup per partition of the level-0 arrays: their segments are
+// staged in LDS and searched there, and the prefix sums (number of rows, S_t per operand) run along the workgroups by
+// decoupled look-back.  As kernels of their own -- match, two scans of two kernels each, plan -- with 4096 items per
+// workgroup these took 56 of the 226 us of a product of two matrices of 20M entries in 100k rows.  The rows without
+// an entry are dropped by a scan of the same kind (one kernel instead of two, 18 us).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -29,203 +32,301 @@ namespace nacho {
 
 namespace {
 
-// ---- rows all operands store -----------------------------------------------
+constexpr int kScanThreads = 256, kScanWaves = kScanThreads / NACHO_WAVE;
+
+// ---- prefix sums along the workgroups of a launch (decoupled look-back) --------
+// Workgroup p publishes its own sum (an aggregate), reads back over the words of the workgroups before it until it
+// meets one that already knows the sum of everything up to and including itself (a prefix), and publishes its own
+// prefix.  Workgroups are handed out in index order and wait only for smaller indexes, so the waits end (they are
+// bounded all the same).
+constexpr unsigned long long kAggregate = 1ull << 62, kPrefix = 1ull << 63;
+constexpr int kSpinLimit = 1 << 14;
+
+__device__ inline void publish(unsigned long long *state, int64_t p, unsigned long long flag, int v)
+{
+    __hip_atomic_store(&state[p], flag | (unsigned)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// By a whole wavefront: the sum of the workgroups before p, whose own sum is `own`; publishes the prefix.
+__device__ inline bool look_back(unsigned long long *state, int64_t p, int own, int &before)
+{
+    const int lane = lane_id();
+    int sum = 0;
+    for (int64_t end = p; end > 0; end -= NACHO_WAVE) {        // words end - 1 - lane
+        const int64_t j = end - 1 - lane;
+        unsigned long long s = 0ull, prefixes = 0ull;
+        for (int spins = 0;; ++spins) {
+            if (s == 0ull) s = j < 0 ? kPrefix : __hip_atomic_load(&state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            prefixes = __ballot((s & kPrefix) != 0ull);
+            const unsigned long long missing = __ballot(s == 0ull);
+            // (lanes nearer than the nearest prefix count)
+            const unsigned long long nearer = prefixes ? (prefixes & (0ull - prefixes)) - 1ull : ~0ull;
+            if ((missing & nearer) == 0ull) break;
+            if (spins > kSpinLimit) return false;
+            __builtin_amdgcn_s_sleep(4);
+        }
+        const int nearest = prefixes ? __ffsll((long long)prefixes) - 1 : NACHO_WAVE - 1;
+        sum += __builtin_amdgcn_readlane(wave_inclusive_scan(lane <= nearest ? (int)(unsigned)s : 0), NACHO_WAVE - 1);
+        if (prefixes) break;
+    }
+    before = sum;
+    if (lane == 0) publish(state, p, kPrefix, sum + own);
+    return true;
+}
+
+// ---- the row loop -----------------------------------------------------------
 struct RowArrays {
     int32_t k;
-    const int32_t *crd0[NACHO_MAX_OPERANDS];
-};
-
-// One workgroup per partition of the level-0 coordinate arrays.  Equal
-// coordinates of different operands fall in one partition (Section 6), so every
-// row of operand 0 in the partition looks for itself in the partition's segment
-// of every other operand.  flags[e] = 1 when all operands store row crd0_0[e];
-// qpos[(t-1) * count0 + e] = position of that row in operand t >= 1.
-__global__ void __launch_bounds__(256)
-rows_match_kernel(RowArrays rows, const int32_t *__restrict__ posn0, int32_t *__restrict__ flags,
-                  int32_t *__restrict__ qpos, int64_t count0)
-{
-    const int64_t p = blockIdx.x;
-    const int k = rows.k;
-    const int a0 = posn0[p * k], b0 = posn0[(p + 1) * k];
-    for (int e = a0 + (int)threadIdx.x; e < b0; e += (int)blockDim.x) {
-        const int x = rows.crd0[0][e];
-        bool all = true;
-        for (int t = 1; t < k; ++t) {
-            const int lo = posn0[p * k + t], hi = posn0[(p + 1) * k + t];
-            const int q = lower_bound_global(rows.crd0[t], lo, hi, x);
-            const bool hit = q < hi && rows.crd0[t][q] == x;
-            all = all && hit;
-            qpos[(int64_t)(t - 1) * count0 + e] = q;
-        }
-        flags[e] = all ? 1 : 0;
-    }
-}
-
-// ---- exclusive prefix sums --------------------------------------------------
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;                        // consecutive items of a thread
-constexpr int kScanTile = kScanThreads * kScanItems;  // items of a workgroup
-
-__device__ inline int block_sum(int v, int *lds)
-{
-    v = wave_sum<int>(v);
-    __syncthreads();                                  // lds may still be read from an earlier call
-    if (lane_id() == 0) lds[threadIdx.x / NACHO_WAVE] = v;
-    __syncthreads();
-    int s = 0;
-#pragma unroll
-    for (int w = 0; w < kScanThreads / NACHO_WAVE; ++w) s += lds[w];
-    return s;
-}
-
-// tsum[b * n_tiles + tile] = sum of the items of the tile, for every array b of a batch
-template <class In>
-__global__ void __launch_bounds__(kScanThreads)
-scan_sums_kernel(In in, int64_t n, int64_t n_tiles, int32_t *__restrict__ tsum)
-{
-    __shared__ int lds[kScanThreads / NACHO_WAVE];
-    const int b = blockIdx.y;
-    const int64_t tile = blockIdx.x;
-    int s = 0;
-#pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        const int64_t i = tile * kScanTile + (int64_t)j * kScanThreads + threadIdx.x;
-        if (i < n) s += in.load(b, i);
-    }
-    s = block_sum(s, lds);
-    if (threadIdx.x == 0) tsum[(int64_t)b * n_tiles + tile] = s;
-}
-
-// Item i of array b receives out.store(b, i, sum of the items before it, item);
-// the last tile reports the total through out.finish.
-template <class In, class Out>
-__global__ void __launch_bounds__(kScanThreads)
-scan_apply_kernel(In in, Out out, int64_t n, int64_t n_tiles, const int32_t *__restrict__ tsum)
-{
-    __shared__ int lds[kScanThreads / NACHO_WAVE];
-    const int b = blockIdx.y;
-    const int64_t tile = blockIdx.x;
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE;
-    int part = 0;
-    for (int64_t j = tid; j < tile; j += kScanThreads) part += tsum[(int64_t)b * n_tiles + j];
-    const int offset = block_sum(part, lds);          // items of the tiles before this one
-    int v[kScanItems], sum = 0;
-    const int64_t first = tile * kScanTile + (int64_t)tid * kScanItems;
-#pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        v[j] = first + j < n ? in.load(b, first + j) : 0;
-        sum += v[j];
-    }
-    const int incl = wave_inclusive_scan(sum);
-    __syncthreads();
-    if (lane == NACHO_WAVE - 1) lds[wave] = incl;
-    __syncthreads();
-    int excl = offset + incl - sum;
-#pragma unroll
-    for (int w = 0; w < kScanThreads / NACHO_WAVE; ++w)
-        if (w < wave) excl += lds[w];
-#pragma unroll
-    for (int j = 0; j < kScanItems; ++j) {
-        if (first + j < n) out.store(b, first + j, excl, v[j]);
-        excl += v[j];
-    }
-    if (tile == n_tiles - 1 && tid == kScanThreads - 1) out.finish(b, excl);
-}
-
-struct ArrayIn {
-    const int32_t *base;
-    int64_t stride;
-    __device__ int load(int b, int64_t i) const { return base[(int64_t)b * stride + i]; }
-};
-
-// S_t: in place, n + 1 results per array (the last one is the total, also kept in head[1 + t])
-struct CostOut {
-    int32_t *base;
-    int64_t stride, n;
-    int32_t *head;
-    __device__ void store(int b, int64_t i, int before, int) const { base[(int64_t)b * stride + i] = before; }
-    __device__ void finish(int b, int total) const
-    {
-        base[(int64_t)b * stride + n] = total;
-        head[1 + b] = total;
-    }
-};
-
-// Second stage of the row loop: the i'-th intersected row (i' = number of
-// flagged rows before it) stores its coordinate, and per operand the position
-// of its first entry and its number of entries.
-struct RemapOut {
-    int32_t k;
-    const int32_t *crd0_0;
-    const int32_t *qpos;
-    int64_t count0;
-    const int32_t *pos1[NACHO_MAX_OPERANDS];
-    int32_t *rows;      // [M]
-    int32_t *start;     // [k][stride]
-    int32_t *len;       // [k][stride + 1]
-    int64_t stride;
-    int32_t *head;      // head[0] = M
-    __device__ void store(int, int64_t e, int before, int flag) const
-    {
-        if (!flag) return;
-        rows[before] = crd0_0[e];
-        for (int t = 0; t < k; ++t) {
-            const int q = t == 0 ? (int)e : qpos[(int64_t)(t - 1) * count0 + e];
-            const int a = pos1[t][q], z = pos1[t][q + 1];
-            start[(int64_t)t * stride + before] = a;
-            len[(int64_t)t * (stride + 1) + before] = z - a;
-        }
-    }
-    __device__ void finish(int, int total) const { head[0] = total; }
-};
-
-// Rows of the remapped result that hold an entry (the first head[0] rows exist)
-struct KeepIn {
-    const int32_t *pos_full;
-    const int32_t *head;
-    __device__ int load(int, int64_t i) const { return i < head[0] && pos_full[i + 1] > pos_full[i] ? 1 : 0; }
-};
-
-struct CompactOut {
-    const int32_t *rows, *pos_full;
-    const int64_t *counts_in;      // {rows, nnz} of the remapped result
-    SpaddOut out;
-    __device__ void store(int, int64_t i, int before, int keep) const
-    {
-        if (keep && before < out.cap_rows) {
-            out.crd0[before] = rows[i];
-            out.pos1[before] = pos_full[i];
-        }
-    }
-    __device__ void finish(int, int total) const
-    {
-        const int64_t nnz = counts_in[1];
-        out.pos0[0] = 0;
-        out.pos0[1] = total;
-        if (total <= out.cap_rows) out.pos1[total] = (int32_t)nnz;
-        else *out.status = NACHO_ERR_CAPACITY;
-        out.counts[0] = total;
-        out.counts[1] = nnz;
-    }
+    const int32_t *crd0[NACHO_MAX_OPERANDS], *pos1[NACHO_MAX_OPERANDS];
 };
 
 // What the kernels after the row loop need to know, left where they can read it: the number of
 // partitions of the remapped nest (the rule of the fused calls: enough partitions that one fits a
 // workgroup, a whole number of rounds of resident workgroups, at least what the caller asked for),
 // the number of intersected rows and the remapped total cost.
-__global__ void remap_plan_kernel(const int32_t *__restrict__ head, int k, int64_t capacity, int64_t round,
-                                  int64_t P_min, int64_t P_max, int64_t *__restrict__ plan)
+struct PlanRule {
+    int64_t capacity, round, P_min, P_max;
+    __device__ void write(int64_t rows, int64_t total, int64_t *plan) const
+    {
+        int64_t need = total > 0 ? (total + capacity - 1) / capacity : 1;
+        if (P_min == 0 && need > round) need = (need + round - 1) / round * round;
+        int64_t P = P_min > need ? P_min : need;
+        if (P > P_max) P = P_max;
+        plan[0] = P;
+        plan[1] = rows;
+        plan[2] = total;
+    }
+};
+
+// One workgroup per partition of the level-0 coordinate arrays (at most kRemapGrain + k - 1 coordinates).  Equal
+// coordinates of different operands fall in one partition (Section 6), so every row of operand 0 in the partition
+// looks for itself in the partition's segment of every other operand.
+__global__ void __launch_bounds__(kScanThreads)
+remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, RemapArrays r,
+                  unsigned long long *__restrict__ state, PlanRule rule, int64_t *__restrict__ plan,
+                  int32_t *__restrict__ status)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int64_t total = 0;
-    for (int t = 0; t < k; ++t) total += head[1 + t];
-    int64_t need = total > 0 ? (total + capacity - 1) / capacity : 1;
-    if (P_min == 0 && need > round) need = (need + round - 1) / round * round;
-    int64_t P = P_min > need ? P_min : need;
-    if (P > P_max) P = P_max;
-    plan[0] = P;
-    plan[1] = head[0];
-    plan[2] = total;
+    constexpr int kMost = kRemapGrain + NACHO_MAX_OPERANDS, kPairs = kMost / 2, kEach = (kPairs + kScanThreads - 1) / kScanThreads;
+    static_assert(kMost < (1 << 16), "places in a partition fit 16 bits");
+    __shared__ int s_crd[kMost];
+    __shared__ uint16_t s_q[NACHO_MAX_OPERANDS][kMost];        // place of operand 0's row in the other operands' segments
+    __shared__ uint16_t s_item[kPairs];                        // the intersected rows of the partition
+    __shared__ int s_count[kScanWaves], s_len[NACHO_MAX_OPERANDS][kScanWaves], s_base[NACHO_MAX_OPERANDS + 1];
+    __shared__ int s_fail;
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE, k = in.k;
+    const int64_t p = blockIdx.x;
+
+    int lo[NACHO_MAX_OPERANDS], off[NACHO_MAX_OPERANDS + 1];
+    off[0] = 0;
+    bool broken = false;
+#pragma unroll
+    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) {
+        lo[t] = 0;
+        off[t + 1] = off[t];
+        if (t < k) {
+            lo[t] = posn0[p * k + t];
+            const int len = posn0[(p + 1) * k + t] - lo[t];
+            broken = broken || len < 0 || len > kMost;
+            off[t + 1] = off[t] + len;
+        }
+    }
+    // (only operands that violate their preconditions can have more coordinates in a partition than its share)
+    broken = broken || off[NACHO_MAX_OPERANDS] > kRemapGrain + k - 1;
+    if (tid == 0) {
+        s_fail = 0;
+        if (broken) atomicMin(status, (int32_t)NACHO_ERR_INVALID_ARG);
+    }
+    const int n = broken ? 0 : off[1];
+    if (!broken) {
+#pragma unroll
+        for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+            if (t < k)
+                for (int i = tid; i < off[t + 1] - off[t]; i += kScanThreads) s_crd[off[t] + i] = in.crd0[t][lo[t] + i];
+    }
+    __syncthreads();
+    // consecutive rows of operand 0 per thread
+    const int each = (n + kScanThreads - 1) / kScanThreads, first = tid * each;
+    unsigned found = 0u;
+    for (int j = 0; j < each && first + j < n; ++j) {
+        const int x = s_crd[first + j];
+        bool all = true;
+#pragma unroll
+        for (int t = 1; t < NACHO_MAX_OPERANDS; ++t)
+            if (t < k && all) {
+                int a = off[t], z = off[t + 1];
+                while (a < z) {
+                    const int mid = (a + z) >> 1;
+                    if (s_crd[mid] < x) a = mid + 1; else z = mid;
+                }
+                all = a < off[t + 1] && s_crd[a] == x;
+                s_q[t][first + j] = (uint16_t)(a - off[t]);
+            }
+        found |= all ? 1u << j : 0u;
+    }
+    const int mine = __popc(found), incl = wave_inclusive_scan(mine);
+    if (lane == NACHO_WAVE - 1) s_count[wave] = incl;
+    __syncthreads();
+    int m = 0, at = incl - mine;                       // intersected rows of the partition; before this thread's
+#pragma unroll
+    for (int w = 0; w < kScanWaves; ++w) {
+        if (w < wave) at += s_count[w];
+        m += s_count[w];
+    }
+    for (; found; found &= found - 1u) s_item[at++] = (uint16_t)(first + __ffs(found) - 1);
+    __syncthreads();
+    // consecutive intersected rows per thread: where their entries start, how many there are
+    int start[NACHO_MAX_OPERANDS][kEach], len[NACHO_MAX_OPERANDS][kEach], before[NACHO_MAX_OPERANDS];
+#pragma unroll
+    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+        if (t < k)
+#pragma unroll
+            for (int u = 0; u < kEach; ++u) {
+                start[t][u] = len[t][u] = 0;
+                if (tid * kEach + u < m) {
+                    const int i = s_item[tid * kEach + u], q = lo[t] + (t == 0 ? i : (int)s_q[t][i]);
+                    start[t][u] = in.pos1[t][q];
+                    len[t][u] = in.pos1[t][q + 1] - start[t][u];
+                }
+            }
+#pragma unroll
+    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+        if (t < k) {
+            int sum = 0;
+#pragma unroll
+            for (int u = 0; u < kEach; ++u) sum += len[t][u];
+            const int to = wave_inclusive_scan(sum);
+            before[t] = to - sum;
+            if (lane == NACHO_WAVE - 1) s_len[t][wave] = to;
+        }
+    __syncthreads();
+    // sums along the workgroups: value 0 counts rows, value 1 + t entries of operand t
+    auto own = [&](int v) {
+        int x = m;
+        if (v > 0) {
+            x = 0;
+#pragma unroll
+            for (int w = 0; w < kScanWaves; ++w) x += s_len[v - 1][w];
+        }
+        return x;
+    };
+    if (tid <= k && p > 0) publish(state + (int64_t)tid * P0, p, kAggregate, own(tid));
+    for (int v = wave; v <= k; v += kScanWaves) {
+        int base = 0;
+        const bool ok = look_back(state + (int64_t)v * P0, p, own(v), base);
+        if (lane == 0) {
+            s_base[v] = base;
+            if (!ok) s_fail = 1;
+        }
+    }
+    __syncthreads();
+    if (s_fail) {                                      // (a workgroup before this one never published)
+        if (tid == 0) {
+            atomicMin(status, (int32_t)NACHO_ERR_HIP);
+            if (p == P0 - 1) {
+                for (int v = 0; v <= k; ++v) r.head[v] = 0;
+                for (int t = 0; t < k; ++t) r.cost[(int64_t)t * (r.stride + 1)] = 0;
+                rule.write(0, 0, plan);
+            }
+        }
+        return;
+    }
+    const int row0 = s_base[0];
+#pragma unroll
+    for (int u = 0; u < kEach; ++u)
+        if (tid * kEach + u < m) r.rows[row0 + tid * kEach + u] = s_crd[s_item[tid * kEach + u]];
+#pragma unroll
+    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+        if (t < k) {
+            int x = s_base[1 + t] + before[t];
+#pragma unroll
+            for (int w = 0; w < kScanWaves; ++w)
+                if (w < wave) x += s_len[t][w];
+#pragma unroll
+            for (int u = 0; u < kEach; ++u) {
+                const int i = row0 + tid * kEach + u;
+                if (tid * kEach + u < m) {
+                    r.start[(int64_t)t * r.stride + i] = start[t][u];
+                    r.cost[(int64_t)t * (r.stride + 1) + i] = x;
+                }
+                x += len[t][u];
+            }
+        }
+    if (p == P0 - 1 && tid == 0) {                     // the totals
+        int64_t total = 0;
+        const int rows = row0 + m;
+        r.head[0] = rows;
+        for (int t = 0; t < k; ++t) {
+            const int x = s_base[1 + t] + own(1 + t);
+            r.cost[(int64_t)t * (r.stride + 1) + rows] = x;
+            r.head[1 + t] = x;
+            total += x;
+        }
+        rule.write(rows, total, plan);
+    }
+}
+
+// ---- rows of the remapped result that hold an entry --------------------------
+constexpr int kKeepItems = 8, kKeepTile = kScanThreads * kKeepItems;
+
+__global__ void __launch_bounds__(kScanThreads)
+compact_rows_kernel(const int32_t *__restrict__ rows, const int32_t *__restrict__ pos_full, const int32_t *__restrict__ head,
+                    const int64_t *__restrict__ counts_in, SpaddOut out, unsigned long long *__restrict__ state)
+{
+    __shared__ int s_count[kScanWaves], s_base, s_fail;
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE;
+    const int64_t tile = blockIdx.x;
+    const int M = head[0];                             // (the launch is sized for an upper bound)
+    if (tile > 0 && tile * kKeepTile >= M) return;
+    const int first = (int)tile * kKeepTile + tid * kKeepItems;
+    int x[kKeepItems + 1];
+#pragma unroll
+    for (int u = 0; u <= kKeepItems; ++u) x[u] = pos_full[first + u < M ? first + u : M];
+    unsigned keep = 0u;
+#pragma unroll
+    for (int u = 0; u < kKeepItems; ++u) keep |= first + u < M && x[u + 1] > x[u] ? 1u << u : 0u;
+    const int mine = __popc(keep), incl = wave_inclusive_scan(mine);
+    if (lane == NACHO_WAVE - 1) s_count[wave] = incl;
+    __syncthreads();
+    int own = 0, at = incl - mine;
+#pragma unroll
+    for (int w = 0; w < kScanWaves; ++w) {
+        if (w < wave) at += s_count[w];
+        own += s_count[w];
+    }
+    if (wave == 0) {
+        if (lane == 0 && tile > 0) publish(state, tile, kAggregate, own);
+        int base = 0;
+        const bool ok = look_back(state, tile, own, base);
+        if (lane == 0) {
+            s_base = base;
+            s_fail = ok ? 0 : 1;
+        }
+    }
+    __syncthreads();
+    if (s_fail) {
+        if (tid == 0) atomicMin(out.status, (int32_t)NACHO_ERR_HIP);
+        return;
+    }
+    at += s_base;
+#pragma unroll
+    for (int u = 0; u < kKeepItems; ++u)
+        if (keep >> u & 1u) {
+            if (at < out.cap_rows) {
+                out.crd0[at] = rows[first + u];
+                out.pos1[at] = x[u];
+            }
+            ++at;
+        }
+    if (tid == 0 && (tile + 1) * kKeepTile >= M) {     // the last tile
+        const int total = s_base + own;
+        const int64_t nnz = counts_in[1];
+        out.pos0[0] = 0;
+        out.pos0[1] = total;
+        if (total <= out.cap_rows) out.pos1[total] = (int32_t)nnz;
+        else atomicMin(out.status, (int32_t)NACHO_ERR_CAPACITY);
+        out.counts[0] = total;
+        out.counts[1] = nnz;
+    }
 }
 
 __global__ void empty_result_kernel(SpaddOut out, int64_t *info)
@@ -241,84 +342,33 @@ __global__ void empty_result_kernel(SpaddOut out, int64_t *info)
     }
 }
 
-int64_t tiles_of(int64_t n) { return n > 0 ? (n + kScanTile - 1) / kScanTile : 1; }
-
-template <class In, class Out>
-hipError_t scan(const In &in, const Out &out, int64_t n, int batch, int32_t *tsum, hipStream_t s)
-{
-    const int64_t n_tiles = tiles_of(n);
-    const dim3 grid((unsigned)n_tiles, (unsigned)batch);
-    hipLaunchKernelGGL((scan_sums_kernel<In>), grid, dim3(kScanThreads), 0, s, in, n, n_tiles, tsum);
-    hipLaunchKernelGGL((scan_apply_kernel<In, Out>), grid, dim3(kScanThreads), 0, s, in, out, n, n_tiles, tsum);
-    return hipGetLastError();
-}
-
 }  // namespace
 
-int64_t remap_scan_words(int64_t n, int batch) { return tiles_of(n) * batch; }
+int64_t remap_state_words(int64_t P0, int k) { return P0 * (k + 1); }
+int64_t compact_state_words(int64_t rows) { return rows > 0 ? (rows + kKeepTile - 1) / kKeepTile : 1; }
 
-hipError_t launch_rows_match(const DevOperands &ops, int64_t P0, const int32_t *posn0, int32_t *flags,
-                             int32_t *qpos, hipStream_t s)
+hipError_t launch_remap_rows(const DevOperands &ops, int64_t P0, const int32_t *posn0, const RemapArrays &r,
+                             unsigned long long *state, int64_t capacity, int64_t round, int64_t P_min, int64_t P_max,
+                             int64_t *plan, int32_t *status, hipStream_t s)
 {
     RowArrays rows;
     rows.k = ops.k;
-    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) rows.crd0[t] = t < ops.k ? ops.lvl[t][0].crd : nullptr;
-    hipLaunchKernelGGL(rows_match_kernel, dim3((unsigned)P0), dim3(256), 0, s, rows, posn0, flags, qpos,
-                       ops.lvl[0][0].count);
+    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) {
+        rows.crd0[t] = t < ops.k ? ops.lvl[t][0].crd : nullptr;
+        rows.pos1[t] = t < ops.k ? ops.lvl[t][1].pos : nullptr;
+    }
+    const PlanRule rule = {capacity, round, P_min, P_max};
+    hipLaunchKernelGGL(remap_rows_kernel, dim3((unsigned)P0), dim3(kScanThreads), 0, s, rows, posn0, P0, r, state, rule,
+                       plan, status);
     return hipGetLastError();
 }
 
-hipError_t launch_remap_rows(const DevOperands &ops, const int32_t *flags, const int32_t *qpos,
-                             const RemapArrays &r, int32_t *tsum, hipStream_t s)
+hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full, const int64_t *counts_in,
+                               const SpaddOut &out, unsigned long long *state, hipStream_t s)
 {
-    ArrayIn in;
-    in.base = flags;
-    in.stride = 0;
-    RemapOut out;
-    out.k = ops.k;
-    out.crd0_0 = ops.lvl[0][0].crd;
-    out.qpos = qpos;
-    out.count0 = ops.lvl[0][0].count;
-    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) out.pos1[t] = t < ops.k ? ops.lvl[t][1].pos : nullptr;
-    out.rows = r.rows;
-    out.start = r.start;
-    out.len = r.cost;
-    out.stride = r.stride;
-    out.head = r.head;
-    return scan(in, out, ops.lvl[0][0].count, 1, tsum, s);
-}
-
-hipError_t launch_remap_costs(int k, const RemapArrays &r, int32_t *tsum, hipStream_t s)
-{
-    ArrayIn in;
-    in.base = r.cost;
-    in.stride = r.stride + 1;
-    CostOut out;
-    out.base = r.cost;
-    out.stride = r.stride + 1;
-    out.n = r.stride;
-    out.head = r.head;
-    return scan(in, out, r.stride, k, tsum, s);
-}
-
-hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full,
-                               const int64_t *counts_in, const SpaddOut &out, int32_t *tsum, hipStream_t s)
-{
-    KeepIn in;
-    in.pos_full = pos_full;
-    in.head = r.head;
-    CompactOut o;
-    o.rows = r.rows;
-    o.pos_full = pos_full;
-    o.counts_in = counts_in;
-    o.out = out;
-    return scan(in, o, r.stride, 1, tsum, s);       // (over the upper bound of the rows; those past head[0] count as empty)
-}
-
-hipError_t launch_remap_plan(int k, const RemapArrays &r, int64_t capacity, int64_t round, int64_t P_min,
-                             int64_t P_max, int64_t *plan, hipStream_t s)
-{
-    hipLaunchKernelGGL(remap_plan_kernel, dim3(1), dim3(64), 0, s, r.head, k, capacity, round, P_min, P_max, plan);
+    // (over the upper bound of the rows; tiles past head[0] leave at once)
+    hipLaunchKernelGGL(compact_rows_kernel, dim3((unsigned)compact_state_words(r.stride)), dim3(kScanThreads), 0, s, r.rows,
+                       pos_full, r.head, counts_in, out, state);
     return hipGetLastError();
 }
 

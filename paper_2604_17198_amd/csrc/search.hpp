@@ -71,7 +71,7 @@ __device__ __forceinline__ LevelResult dense_search(const DevOperands &ops, int 
 {
     const int lane = lane_id();
     const int k = ops.k;
-    const int64_t N = ops.lvl[0][m].extent;
+    const int64_t N = level0_extent(ops);
     int64_t low = 0, high = N, c_low = 0;
     while (low < high) {
         const int64_t span = high - low;
