@@ -1,0 +1,227 @@
+"""GPU parity at the edges of the kernels' tiles and of the rules that choose a kernel: column counts around the pieces
+and lanes of SpMM, row lengths around SpMV's long rows, calls just under and over the sizes at which a partition kernel
+or the long partitions of a merge come in, rows that do not fit a merge key's row field, and more workgroups than one
+look-back step reads.  Index arrays and boundaries bit-exact; values as the oracle has them, within the tolerances of
+the files whose checks are used here."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import test_gpu_coo as coo
+import test_gpu_csf3 as csf3
+import test_gpu_partition as part
+import test_gpu_spadd as add
+import test_gpu_spmm as spmm
+import test_gpu_spmul as mul
+import test_gpu_spmul_dcsr as mul_dcsr
+import test_gpu_spmv as spmv
+from paper_2604_17198_amd import binding as nb
+from gpu_util import csr_operand, dev, parts_to_numpy
+from util import to_csr
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = [np.float32, np.float64]
+UNITS = 256                                     # compute units; a merge keeps 4 workgroups on each
+
+
+def _matrix(rng, lens, n_cols, dtype):
+    """A CSR matrix with the given row lengths."""
+    lens = np.asarray(lens)
+    crd = np.concatenate([np.sort(rng.choice(n_cols, l, replace=False)) for l in lens] + [np.zeros(0, np.int64)])
+    pos = np.zeros(len(lens) + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    return {"n_rows": len(lens), "n_cols": n_cols, "pos": pos, "crd": crd.astype(np.int32),
+            "val": rng.uniform(-1, 1, len(crd)).astype(dtype)}
+
+
+# ---- SpMM -------------------------------------------------------------------
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_spmm_columns(dtype):
+    """One piece of a row (16 bytes), a lane group's width (4, 8, 16 lanes), 1 to 4 pieces a lane, two passes -- and one
+    column on either side of each; with a partition kernel and without one."""
+    rng = np.random.default_rng(1)
+    v = 16 // np.dtype(dtype).itemsize
+    A = _matrix(rng, [0, 300, 0, 0, 1, 900, 3, 5, 0, 64, 63, 65, 0], 1000, dtype)
+    edges = {1, 2, 3} | {v * lanes * pieces + d for lanes, pieces in ((1, 1), (4, 1), (8, 1), (16, 1), (16, 2), (16, 3), (16, 4))
+                         for d in (-1, 0, 1)} | {257, 300}
+    for n in sorted(e for e in edges if e > 0):
+        B = rng.uniform(-1, 1, (A["n_cols"], n)).astype(dtype)
+        for P in (0, 9):
+            spmm._check(A, B, P, "columns")
+
+
+@pytest.mark.parametrize("nnz", [1, 63, 64, 65, 262_144, 262_145, 2_097_151, 2_097_153])
+def test_spmm_grain(nnz):
+    """Partitions of 64 non-zeros up to 64 x 4096 of them, of 512 from 512 x 4096 on; rows of a few entries, one that
+    spans many partitions, and a run of carries either side of what one group adds by itself (32)."""
+    rng = np.random.default_rng(nnz)
+    n_rows, n_cols = max(1, nnz // 9), 40_000
+    lens = np.full(n_rows, nnz // n_rows)
+    lens[-1] += nnz - lens.sum()
+    if nnz > 60_000:
+        for r, l in ((n_rows // 2, 64 * 32), (n_rows // 3, 64 * 34), (7, 20_000)):
+            take = np.flatnonzero(lens > 1)[:l]
+            lens[take] -= 1
+            lens[r] += len(take)
+    starts = rng.integers(0, n_cols - int(lens.max()), n_rows)
+    pos = np.zeros(n_rows + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    crd = (np.repeat(starts, lens) + np.arange(nnz) - np.repeat(pos[:-1], lens)).astype(np.int32)
+    A = {"n_rows": n_rows, "n_cols": n_cols, "pos": pos, "crd": crd, "val": rng.uniform(-1, 1, nnz).astype(np.float32)}
+    spmm._check(A, rng.uniform(-1, 1, (n_cols, 5)).astype(np.float32), 0, "grain")
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+def test_spmm_rows_per_partition(extra):
+    """1024 rows a partition: with more the partition kernel writes the zeros of empty rows."""
+    rng = np.random.default_rng(5)
+    lens = np.zeros(2 * 1024 + extra, np.int64)         # two partitions of 64 non-zeros
+    lens[[3, 700, 1500]] = 50, 30, 20
+    A = _matrix(rng, lens, 500, np.float64)
+    spmm._check(A, rng.uniform(-1, 1, (500, 6)), 0, "rows per partition")
+
+
+# ---- SpMV -------------------------------------------------------------------
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_spmv_row_lengths(dtype):
+    """Rows around the four products a lane adds at a time, the 48 from which a wavefront adds them, and the partition."""
+    rng = np.random.default_rng(11)
+    grain = 512 if dtype == np.float64 else 1024
+    lens = [1, 2, 3, 4, 5, 7, 8, 9, 0, 46, 47, 48, 49, 50, 63, 64, 65, 0, 0, grain - 1, grain, grain + 1, 3 * grain]
+    A = _matrix(rng, lens * 3, 4000, dtype)
+    x = rng.uniform(-1, 1, 4000).astype(dtype)
+    for P in (0, 5):
+        spmv._check(A, x, P, "row lengths")
+
+
+@pytest.mark.parametrize("parts,rows,cols", [
+    (1024, 5000, 3000), (1025, 5000, 600_000), (1025, 5000, 524_288), (1025, 5000, 524_289),
+    (8192, 5000, 3000), (8193, 5000, 3000), (100, 1 << 17, 3000), (100, (1 << 17) + 1, 3000)])
+def test_spmv_calls_without_a_partition_kernel(parts, rows, cols):
+    """Partitions, the bytes of x and rows around the limits up to which the wavefronts search their own rows: the
+    stored table is Algorithm 1's either way."""
+    rng = np.random.default_rng(parts + rows + cols)
+    nnz = parts * 512 - 100
+    lens = np.zeros(rows, np.int64)
+    some = np.sort(rng.choice(rows, min(rows, 4000), replace=False))
+    lens[some] = nnz // len(some)
+    lens[some[:nnz % len(some)]] += 1
+    pos = np.zeros(rows + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    # (columns of a row: evenly spaced over the row of A)
+    at = np.arange(nnz) - np.repeat(pos[:-1].astype(np.int64), lens)
+    crd = (at * cols // np.repeat(np.maximum(lens, 1), lens)).astype(np.int32)
+    A = {"n_rows": rows, "n_cols": cols, "pos": pos, "crd": crd, "val": rng.uniform(-1, 1, nnz)}
+    x = rng.uniform(-1, 1, cols)
+    spmv._check(A, x, 0, "limits")
+    op = csr_operand(A)
+    ws = torch.empty(nb.workspace_bytes(nb.OP_SPMV, [op], nb.F64), dtype=torch.uint8, device="cuda")
+    nb.nacho_spmv(op, dev(x), ws=ws)
+    t = nb.workspace_parts(nb.OP_SPMV, [op], nb.F64, ws)
+    queries = np.minimum(np.arange(t["P"] + 1, dtype=np.int64) * 512, nnz)
+    ref = oracle.partition([oracle.csr(pos, crd, rows, cols)], t["P"], queries=queries)
+    got = {k: v.cpu().numpy() for k, v in t.items() if k in ("coord", "posn", "cost")}
+    part._compare(got, ref, "limits")
+
+
+# ---- partition search ---------------------------------------------------------
+def test_partition_two_vectors():
+    """Two operands are searched by splits of the merge path: lengths and spreads far apart, ties, nothing interleaved."""
+    rng = np.random.default_rng(21)
+    draw = lambda lo, hi, n: np.unique(rng.integers(lo, hi, n)).astype(np.int32)
+    tied = draw(0, 1 << 30, 200_000)
+    cases = {"equal": (draw(0, 1 << 30, 300_000), draw(0, 1 << 30, 300_000)), "tied": (tied, tied.copy()),
+             "one": (draw(0, 1 << 30, 300_000), np.array([1 << 29], np.int32)),
+             "apart": (draw(0, 1 << 20, 100_000), draw(1 << 20, 1 << 30, 100_000)),
+             "behind": (draw(1 << 29, 1 << 30, 70_000), draw(0, 1 << 29, 1000)),
+             "empty": (np.zeros(0, np.int32), draw(0, 1 << 30, 5000))}
+    for name, vs in cases.items():
+        for order in (vs, vs[::-1]):
+            g, o = part._vec_ops(order, (1 << 30) + 7)
+            for P in (3, 64, 3000):
+                print(f"partition two vectors {name} sizes={[len(v) for v in order]} P={P}", flush=True)
+                part._compare(parts_to_numpy(nb.nacho_partition(g, P)), oracle.partition(o, P), (name, P))
+
+
+# ---- merge --------------------------------------------------------------------
+def _short_limit(dtype):
+    """Most entries of a call with short partitions: all of them run at once (1512 places, less 64 words around runs)."""
+    return UNITS * 4 * (min(3 * 504, 3 * 512 - 64) - 8)
+
+
+@pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("over", [0, 1])
+def test_merge_short_and_long_partitions(k, over):
+    rng = np.random.default_rng(31)
+    for dtype in DTYPES:
+        total = _short_limit(dtype) + over
+        sizes = [total // k] * (k - 1)
+        sizes.append(total - sum(sizes))
+        vs = [np.sort(rng.choice(1 << 22, n, replace=False)).astype(np.int32) for n in sizes]
+        add.check_vec(vs, [rng.uniform(-1, 1, n).astype(dtype) for n in sizes], 1 << 22, 0, f"limit+{over}")
+
+
+def _banded(rng, n_rows, n_cols, dense, sparse):
+    """Many entries in a few rows and a few in rows far apart: partitions of the latter span more rows than the row
+    field of their keys holds."""
+    top = rng.integers(0, 60, dense) * n_cols + rng.integers(0, n_cols, dense)
+    rest = rng.integers(60, n_rows, sparse) * n_cols + rng.integers(0, n_cols, sparse)
+    return np.unique(np.concatenate([top, rest]))
+
+
+@pytest.mark.parametrize("k,total,dtype", [(2, 1_100_000, np.float32), (3, 1_100_000, np.float64),
+                                           (2, 3_300_000, np.float64), (3, 3_300_000, np.float32)])
+def test_merge_in_bands(k, total, dtype):
+    """Rows past the row field (12 bits beside 2^20 columns): the partition is taken in bands of rows, twice; in short
+    partitions and in long ones."""
+    rng = np.random.default_rng(41)
+    shape = (1 << 19, 1 << 20)
+    keys = [_banded(rng, *shape, int(total / (k + 0.33)), 9000) for _ in range(k)]
+    keys[1] = np.unique(np.concatenate([keys[1], keys[0][::3]]))
+    cs = [np.stack([x // shape[1], x % shape[1]], 1) for x in keys]
+    mats = [(c, rng.uniform(-1, 1, len(c)).astype(dtype)) for c in cs]
+    vals = [v for _, v in mats]
+    add.check_dcsr(mats, shape, 0, "bands")
+    add.check_csr(mats, shape, 0, "bands")
+    coo._check(nb.nacho_spadd_k, oracle.spadd_coo, cs, vals, shape, 0, "add bands")
+    coo._check(nb.nacho_spmul_k, oracle.spmul_coo, cs, vals, shape, 0, "mul bands")
+    prods = []
+    for c, v in mats:
+        pos, crd = to_csr(c, shape[0])
+        prods.append({"pos": pos, "crd": crd, "val": v})
+    mul.check_csr(prods, shape, 0, "bands")
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_merge_tensors_in_bands(dtype):
+    """Slices past the row field of a tensor's keys (16 bits hold slice and fibre)."""
+    rng = np.random.default_rng(51)
+    shape = (100_000, 64, 256)
+    tens = []
+    for _ in range(2):
+        top = rng.integers(0, 400, 1_500_000) * (64 * 256) + rng.integers(0, 64 * 256, 1_500_000)
+        rest = rng.integers(400, shape[0], 4000) * (64 * 256) + rng.integers(0, 64 * 256, 4000)
+        lin = np.unique(np.concatenate([top, rest]))
+        c = np.stack(np.unravel_index(lin, shape), axis=1)
+        tens.append(csf3._tensor(c, rng.uniform(-1, 1, len(c)).astype(dtype)))
+    csf3._check(tens, shape, 0, "bands")
+
+
+# ---- recursive partitioning -----------------------------------------------------
+@pytest.mark.parametrize("rows", [511, 512, 513, 2047, 2048, 2049, 40_000, 140_000])
+def test_product_row_loop(rows):
+    """Row-loop partitions of 1024 coordinates and result tiles of 2048 rows, one more and one less; more workgroups
+    than the 64 words a look-back step reads."""
+    rng = np.random.default_rng(rows)
+    shape = (3 * rows, 50)
+    mats = []
+    common = np.sort(rng.choice(shape[0], rows, replace=False))
+    for t in range(2):
+        own = rng.choice(shape[0], rows // 8, replace=False) if t and rows > 3000 else common[:0]
+        r = np.unique(np.concatenate([common, own]))
+        keys = np.unique(np.concatenate([r * 50 + rng.integers(0, 4, len(r)), r * 50 + rng.integers(0, 50, len(r))]))
+        c = np.stack([keys // 50, keys % 50], 1)
+        mats.append(mul_dcsr._mat(c, rng.uniform(0.5, 1, len(c)).astype(np.float32)))
+    mul_dcsr.check(mats, shape, 0, "row loop")
