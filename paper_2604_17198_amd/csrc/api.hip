@@ -449,7 +449,8 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
         if (op == NACHO_OP_SPMM && n_dense < 1) return NACHO_ERR_INVALID_ARG;
         Pe = fused_partitions(op, dtype, total, P);
-        CarryWs c = carve_carry(ws, Pe, dtype, op == NACHO_OP_SPMM ? spmm_pass(n_dense) : 1);
+        // (the table comes first; the call itself also takes a workspace sized for one pass of 64 columns)
+        CarryWs c = carve_carry(ws, Pe, dtype, op == NACHO_OP_SPMM ? NACHO_WAVE : 1);
         w = c.parts;
         need = c.bytes;
         if (P == 0) g = op == NACHO_OP_SPMV ? (int64_t)spmv_capacity(dtype) : spmm_grain(total, compute_units()) * n_dense;

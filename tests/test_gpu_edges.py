@@ -18,7 +18,7 @@ import test_gpu_spmul_dcsr as mul_dcsr
 import test_gpu_spmv as spmv
 from paper_2604_17198_amd import binding as nb
 from gpu_util import csr_operand, dev, parts_to_numpy
-from util import to_csr
+from util import to_csr, tol_ok
 
 pytestmark = pytest.mark.gpu
 
@@ -81,6 +81,21 @@ def test_spmm_rows_per_partition(extra):
     lens[[3, 700, 1500]] = 50, 30, 20
     A = _matrix(rng, lens, 500, np.float64)
     spmm._check(A, rng.uniform(-1, 1, (500, 6)), 0, "rows per partition")
+
+
+def test_spmm_workspace_for_fewer_columns():
+    """A workspace sized without a column count (64 of them) serves 200 columns, and its table can be read."""
+    rng = np.random.default_rng(6)
+    A = _matrix(rng, [0, 300, 0, 0, 1, 900, 3, 5, 0, 64], 1000, np.float32)
+    op = csr_operand(A)
+    B = rng.uniform(-1, 1, (1000, 200)).astype(np.float32)
+    ws = torch.empty(nb.workspace_bytes(nb.OP_SPMM, [op], nb.F32), dtype=torch.uint8, device="cuda")
+    assert ws.numel() < nb.workspace_bytes(nb.OP_SPMM, [op], nb.F32, 200)
+    C = nb.nacho_spmm(op, dev(B), ws=ws)
+    table = nb.workspace_parts(nb.OP_SPMM, [op], nb.F32, ws, 200)
+    ref, sabs = oracle.spmm(A["pos"], A["crd"], A["val"], B)
+    assert tol_ok(C.cpu().numpy(), ref, sabs, spmm.TOL[np.float32]).all()
+    assert int(table["posn"][-1, 0, 1]) == int(A["pos"][-1])
 
 
 # ---- SpMV -------------------------------------------------------------------
