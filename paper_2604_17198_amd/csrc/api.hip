@@ -246,13 +246,7 @@ int64_t merge_partitions(int fmt, int32_t dtype, int32_t k, const MergeFields &f
 {
     const int64_t cap = std::min<int64_t>(spadd_capacity(fmt, dtype, fields), most) - k;
     int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
-    if (P == 0) {
-        // The merge kernel keeps spadd_resident() workgroups per compute unit, and its partitions all
-        // take about the same time: they run in rounds of that many workgroups per unit.  With the
-        // partition count a whole number of rounds the last round is as full as the others.
-        const int64_t round = (int64_t)compute_units() * spadd_resident();
-        if (need > round) need = ceil_div(need, round) * round;
-    }
+    if (P == 0) need = whole_rounds(need, (int64_t)compute_units() * spadd_resident());
     return P > need ? P : need;
 }
 

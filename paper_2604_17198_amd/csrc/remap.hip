@@ -82,14 +82,14 @@ struct RowArrays {
 
 // What the kernels after the row loop need to know, left where they can read it: the number of
 // partitions of the remapped nest (the rule of the fused calls: enough partitions that one fits a
-// workgroup, a whole number of rounds of resident workgroups, at least what the caller asked for),
+// workgroup, a whole number of rounds of resident workgroups where that is near, at least what the caller asked for),
 // the number of intersected rows and the remapped total cost.
 struct PlanRule {
     int64_t capacity, round, P_min, P_max;
     __device__ void write(int64_t rows, int64_t total, int64_t *plan) const
     {
         int64_t need = total > 0 ? (total + capacity - 1) / capacity : 1;
-        if (P_min == 0 && need > round) need = (need + round - 1) / round * round;
+        if (P_min == 0) need = whole_rounds(need, round);
         int64_t P = P_min > need ? P_min : need;
         if (P > P_max) P = P_max;
         plan[0] = P;
