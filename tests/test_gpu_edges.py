@@ -240,3 +240,25 @@ def test_product_row_loop(rows):
         c = np.stack([keys // 50, keys % 50], 1)
         mats.append(mul_dcsr._mat(c, rng.uniform(0.5, 1, len(c)).astype(np.float32)))
     mul_dcsr.check(mats, shape, 0, "row loop")
+
+
+@pytest.mark.parametrize("need,partitions", [(945, 945), (946, 1024), (1025, 1025), (1890, 1890), (1891, 2048), (2049, 2049)])
+def test_merge_whole_rounds(need, partitions):
+    """Partitions are rounded up to a whole number of rounds of workgroups where that adds a twelfth at most; the sum is
+    that of the same call in other partitions, bit for bit."""
+    capacity = 11 * 504 - 2                             # 11 places for each of 504 threads; shares differ by k at most
+    total = need * capacity
+    gen = torch.Generator(device="cuda").manual_seed(need)
+    ops = []
+    for n in (total - total // 3, total // 3):
+        step = torch.randint(1, 90, (n,), device="cuda", generator=gen)
+        keys = torch.cumsum(step, 0).to(torch.int32)
+        ops.append(nb.vector(keys, (1 << 30) + 7, torch.rand(n, device="cuda", generator=gen)))
+    print(f"whole rounds {need}", flush=True)
+    if nb.num_partitions(nb.OP_SPADD, ops, nb.F32, 0, 1) != need:
+        pytest.fail("the capacity of a partition has changed")
+    assert nb.num_partitions(nb.OP_SPADD, ops, nb.F32) == partitions
+    a, b = (nb.nacho_spadd_k(ops, nb.SparseOut("vector", 0, total, torch.float32, "cuda"), P=P) for P in (0, 2500))
+    n = int(a.counts[1])
+    assert torch.equal(a.counts, b.counts) and int(a.status[0]) == 0 and int(b.status[0]) == 0
+    assert torch.equal(a.crd1[:n], b.crd1[:n]) and torch.equal(a.val[:n], b.val[:n])
