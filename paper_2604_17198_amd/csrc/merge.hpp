@@ -197,7 +197,7 @@ template <typename KeyT, typename S, bool kRows, bool kRowHeads, bool kCsr, bool
 struct Tile {
     // The staged words: run t's entries from word sb[t] on, its sentinel behind them.  64-bit keys: the
     // columns are staged in the first half, the row ids of the row starts in the second, and the keys are
-    // written over both.
+    // written over both.  (Tensors: the row field above its 32nd bit in `order`.)
     alignas(16) KeyT keys[S::kWords];
     // Order words by place: which staged word the place's entry is in (two operands: the byte offset of its
     // key; more: operand << 13 | word).  Before the keys are formed, with 32-bit keys: the row field of every
@@ -215,7 +215,6 @@ struct Tile {
     unsigned long long scol[kMaxRuns];    // the same for the columns (remapped operands)
     unsigned long long srow[kMaxRuns];    // coordinate lists: the same for the rows; remapped operands: start[t]
     unsigned long long spos[kMaxRuns];    // remapped operands: pos of run t
-    int32_t band_counts[3];               // partitions taken in bands: entries, rows, slices of the bands so far
     uint32_t cont, cont_next, cont_slice; // does the partition (the next one) start inside a row / slice
     uint32_t overflow;                    // the rows do not fit the key's row field
     int32_t base_nnz, base_rows, base_slices;      // output of the workgroups before this one in its chunk ...
@@ -388,11 +387,9 @@ typedef const __attribute__((address_space(4))) MergeArgs *ArgPtr;
 // kSearch (sparse vectors): there is no partition kernel before this one; wavefronts 0 and 1 of the
 // workgroup search its two boundaries themselves (Algorithm 1, equal-share queries) and store them in
 // the partition table on the way -- the search fused into the executing kernel.
-// kBands: the partition's rows do not fit the row field of its keys, so it is taken in bands of rows, twice:
-// all bands are counted, then the offset is looked up, then all are written.
-// Returns true (kBands = false) when the rows do not fit; nothing has been published or written then.
-template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch, bool kBands>
-__device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, KeyT, kSmall> &w, const DevOperands &search_ops,
+// A partition whose rows do not fit the row field of its keys is merged without keys (`far` below).
+template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch>
+__device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, KeyT, kSmall> &w, const DevOperands &search_ops,
                                                 const WaveStamp &stamp)
 {
     static_assert(!kSearch || (FMT == SPADD_VECTOR && !kMapped), "the fused search is built for sparse vectors");
@@ -404,7 +401,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         // the number of partitions is a result of earlier kernels of the call: the launch is sized for
         // an upper bound and the workgroups past the last partition have nothing to do
         P = arg_ptr->ops.dyn_plan[0];
-        if ((int64_t)blockIdx.x >= P) return false;
+        if ((int64_t)blockIdx.x >= P) return;
     }
     typedef Shape<KeyT, T, kSmall> S;
     constexpr int D = FMT == SPADD_VECTOR ? 1 : (FMT == SPADD_CSF3 ? 3 : 2);
@@ -508,91 +505,9 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     int n = dpp_sum(len_v);                    // <= kCapacity by the host's choice of the partition count
     bool broken = __ballot(len_v < 0 || len_v > S::kCapacity) != 0ull || n > S::kCapacity;
     if (broken) n = len_v = 0;
+    bool far = false;                          // (matrices and tensors) the rows do not fit the keys
     uint32_t logged_items = 0, logged_rows = 0;    // (instrumented build) places / row heads this wavefront walked
 
-    // (bands: the counts of the bands so far are in w.band_counts)
-    bool first_band = true, last_band = true;
-    int next_row = 0, next_q_v = 0, next_i_v = 0;  // where the next band starts: its row, and in operand `lane`
-    auto restart_bands = [&]() {
-        fresh();
-        next_row = table_coord(p, 0);
-        if (lane < k) {
-            next_q_v = table_pos(p, lane, D - 1);
-            if (kWindow) next_i_v = table_pos(p, lane, D >= 2 ? D - 2 : 0);
-        }
-        if (tid < 3) w.band_counts[tid] = 0;
-    };
-    // The next band: rows (slices) next_row .. next_row + limit - 1 of every operand (every wavefront works it out).
-    auto next_band = [&]() {
-        if constexpr (D >= 2) {
-            __syncthreads();                   // nobody reads the LDS of the band before any more
-            fresh();
-            const int64_t row_end = (int64_t)next_row + arg_ptr->fields.limit;
-            row0 = next_row;
-            q_v = next_q_v;
-            ilo_v = next_i_v;
-            len_v = 0;
-            int after = 0x7fffffff;            // the row of the operand's first entry behind the band
-            if (lane < k) {
-                const int t = lane;
-                const int32_t *crd0 = arg_ptr->ops.lvl[t][0].crd, *pos1 = arg_ptr->ops.lvl[t][1].pos;
-                const int32_t *pos = arg_ptr->ops.lvl[t][D - 1].pos;
-                const int q_end = table_pos(p + 1, t, D - 1);
-                int q, i = 0;                  // first entry at or after row_end, and its segment
-                if (kCoo) q = lower_bound_global(crd0, q_v, q_end, row_end);
-                else {
-                    if (FMT == SPADD_CSR) i = (int)(row_end < level_count(t, 0) ? row_end : level_count(t, 0));
-                    else i = lower_bound_global(crd0, 0, level_count(t, 0), row_end);
-                    if (kCsf) i = pos1[i];
-                    q = pos[i];
-                }
-                q = q < q_v ? q_v : (q > q_end ? q_end : q);
-                if (q < q_end) {
-                    if (kCoo) after = crd0[q];
-                    else {
-                        int lo = i, hi = level_count(t, D >= 2 ? D - 2 : 0) - 1;       // first segment that ends after q
-                        while (lo < hi) {
-                            const int mid = lo + ((hi - lo) >> 1);
-                            if (pos[mid + 1] > q) hi = mid; else lo = mid + 1;
-                        }
-                        if (kCsf) {
-                            int a = 0, z = level_count(t, 0) - 1;              // the last slice that starts at or before it
-                            while (a < z) {
-                                const int mid = a + ((z - a + 1) >> 1);
-                                if (pos1[mid] <= lo) a = mid; else z = mid - 1;
-                            }
-                            lo = a;
-                        }
-                        after = FMT == SPADD_CSR ? lo : crd0[lo];
-                    }
-                }
-                len_v = q - q_v;
-                next_q_v = q;
-                if (kWindow) {
-                    const int most = level_count(t, D >= 2 ? D - 2 : 0);
-                    next_i_v = i;
-                    ihi_v = i + 1 < most ? i + 1 : most;
-                }
-            }
-            next_row = 0x7fffffff;
-#pragma unroll
-            for (int t = 0; t < K; ++t) next_row = min(next_row, of(after, t));
-            last_band = next_row == 0x7fffffff;
-            n = dpp_sum(len_v);
-            if ((n == 0 && !last_band) || n > S::kCapacity) {      // (cannot happen while the preconditions hold)
-                broken = true;
-                last_band = true;
-                n = len_v = 0;
-            }
-        }
-    };
-    bool writing = !kBands;                    // bands: the second time round
-    if constexpr (kBands) {
-        __syncthreads();
-        restart_bands();
-        next_band();
-    }
-    for (;;) {
     // ---- 1. staging -----------------------------------------------------------
     // staged word of the operand's first entry (the copy of a run starts on a 16-byte boundary), words in all
     const int lead_v = kDirect ? (q_v & 3) : 0;
@@ -710,10 +625,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if (kDirect) cols[sb_v + len_v] = ~0u;
         }
         if (lane == 0) {
-            if (!kBands) {
-                w.cont = w.cont_next = w.cont_slice = 0u;
-                w.band_counts[0] = w.band_counts[1] = w.band_counts[2] = 0;
-            }
+            w.cont = w.cont_next = w.cont_slice = 0u;
             w.overflow = 0u;
             w.gave_up = 0;
         }
@@ -721,10 +633,11 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     __syncthreads();                           // vectors: the keys are there; others: bits and flags are cleared
     if constexpr (D >= 2) {
         if constexpr (kWindow) {
-            auto mark_start = [&](int s, uint32_t field) {
+            auto mark_start = [&](int s, KeyT field) {
                 atomicOr(reinterpret_cast<uint32_t *>(w.starts) + (s >> 5), 1u << (s & 31));
-                if (kWide) wide_rows[s] = field;
-                else w.order[s] = (uint16_t)field;
+                if (kWide) wide_rows[s] = (uint32_t)field;
+                if (!kWide) w.order[s] = (uint16_t)field;
+                else if (kCsf) w.order[s] = (uint16_t)(field >> (kWide ? 32 : 0));
             };
             const uint32_t limit = arg_ptr->fields.limit;
 #pragma unroll
@@ -743,7 +656,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                         if (up_hi == up_lo + 1) second_at = ((Table)(uintptr_t)arg_ptr->ops.lvl[t][1].pos)[up_hi];
                     }
                 }
-                if (!kBands && t < k) {
+                if (t < k) {
                     // Does this partition (the next one) start inside a row, i.e. does some operand hold an
                     // entry of the boundary's row before the boundary?  Then that row's first output entry
                     // belongs to an earlier partition.  The boundary's row is the first (last) segment.
@@ -772,7 +685,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     const int s = a > q ? a : q;
                     if (b <= s || s >= q + len) return;            // nothing of it lies in the partition
                     int up = FMT == SPADD_CSR ? i : id;            // row, or slice of the fibre
-                    uint32_t field;
+                    KeyT field;
                     if constexpr (kCsf) {
                         up = i < second_at ? up_first : up_last;
                         if (many) {                                // (uniform)
@@ -784,8 +697,8 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                             }
                             up = crd_of(t, 0)[lo];
                         }
-                        field = ((uint32_t)(up - row0) << jb) | (uint32_t)id;
-                    } else field = (uint32_t)(up - row0);
+                        field = ((KeyT)(uint32_t)(up - row0) << jb) | (KeyT)(uint32_t)id;
+                    } else field = (KeyT)(uint32_t)(up - row0);
                     if ((uint32_t)(up - row0) >= limit) w.overflow = 1u;
                     mark_start(sb + s - q, field);
                     // (remapped operands: how far the row is stored from where it is counted)
@@ -806,7 +719,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 }
             }
             // the sentinel of a run: a row start whose row field is all ones, as its column is
-            if (tid < K) mark_start(sb_v + len_v, ~0u);
+            if (tid < K) mark_start(sb_v + len_v, kSentinel);
             __syncthreads();
         }
         // Keys.  A wavefront takes R blocks of 64 words; the words' row starts are in its lanes, and where the
@@ -839,14 +752,17 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             }
             return e;
         };
-        auto field_at = [&](int e) -> uint32_t { return kWide ? wide_rows[e] : (uint32_t)w.order[e]; };
+        auto field_at = [&](int e) -> KeyT {
+            if (!kWide) return (KeyT)w.order[e];
+            return kCsf ? (KeyT)wide_rows[e] | (KeyT)w.order[e] << (kWide ? 32 : 0) : (KeyT)wide_rows[e];
+        };
         if constexpr (!kWide && kWindow && kDirect) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const int s = word0 + j * NACHO_WAVE + lane;
                 if (word0 + j * NACHO_WAVE >= words) break;        // (uniform)
-                const uint32_t f = field_at(start_of(j));
-                cols[s] = (uint32_t)(((KeyT)f << cb) | cols[s]);
+                const KeyT f = field_at(start_of(j));
+                cols[s] = (uint32_t)((f << cb) | cols[s]);
             }
         } else {
             KeyT key[R];
@@ -867,7 +783,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
                 for (int j = 0; j < R; ++j) e[j] = start_of(j);
 #pragma unroll
-                for (int j = 0; j < R; ++j) key[j] = (KeyT)field_at(e[j]) << cb;
+                for (int j = 0; j < R; ++j) key[j] = field_at(e[j]) << cb;
                 if constexpr (kMapped) {
                     // the words of the columns hold the rows' shifts so far
                     uint32_t c[R];
@@ -898,12 +814,128 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             }
         }
         __syncthreads();
-        if (w.overflow && !broken) {           // (uniform, rare)
-            if constexpr (!kBands) return true;
-            broken = true;                     // (a band is cut to fit: an operand violates its preconditions)
-            n = 0;
-        }
+        far = __builtin_amdgcn_readfirstlane((int)w.overflow) != 0 && !broken;
     }
+
+    // ---- 1b. rows too far apart for the keys ------------------------------------------
+    // The partition is merged without keys: every entry finds, in the other operands' segments, the entries before it
+    // by binary searches over the operands' own arrays, and with them its place and whether it is a head.  Works for
+    // rows, columns and slices of any extent, in one pass and without more LDS or registers than the merge by keys.
+    // It takes some thirty dependent loads (cache hits, most of them) per entry and operand; the layout of the keys is
+    // chosen so that few partitions come here (merge_fields).
+    auto lower = [](Ints a, int lo, int hi, int x) {           // the first position of [lo, hi) whose coordinate is >= x
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo) >> 1);
+            if (a[mid] < x) lo = mid + 1; else hi = mid;
+        }
+        return lo;
+    };
+    auto holder = [](Ints pos, int lo, int hi, int q) {        // the segment of [lo, hi) that position q lies in
+        --hi;
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo + 1) >> 1);
+            if (pos[mid] <= q) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    auto starts_of = [&](int t) { return ints(arg_ptr->ops.start[t]); };
+    auto rank_far = [&]() {
+        if constexpr (D >= 2) {
+#pragma unroll 1
+            for (int t = 0; t < k; ++t) {
+                const int q_t = of(q_v, t), len_t = of(len_v, t), sb_t = of(sb_v, t);
+                const int ilo_t = of(ilo_v, t), ihi_t = of(ihi_v, t);
+                const int up_lo_t = of(up_lo_v, t), up_hi_t = of(up_hi_v, t);
+#pragma unroll 1
+                for (int i = tid; i < len_t; i += kThreads) {
+                    const int q = q_t + i;
+                    // the entry's coordinates: row (slice), fibre of a tensor, column
+                    int seg = 0, up = 0, row, fibre = 0, shift = 0;
+                    if constexpr (kCoo) row = crd_of(t, 0)[q];
+                    else {
+                        seg = holder(pos_of(t, D - 1), ilo_t, ihi_t, q);
+                        row = seg;
+                        if (FMT != SPADD_CSR) row = crd_of(t, D - 2)[seg];
+                        if (kMapped) shift = starts_of(t)[seg] - pos_of(t, D - 1)[seg];
+                        if constexpr (kCsf) {
+                            fibre = row;
+                            up = holder(pos_of(t, 1), up_lo_t, up_hi_t + 1, seg);
+                            row = crd_of(t, 0)[up];
+                        }
+                    }
+                    const int col = crd_of(t, D - 1)[q + shift];
+                    int place = i;
+                    bool head = true, row_head = true, slice_head = true;
+#pragma unroll 1
+                    for (int u = 0; u < k; ++u) {
+                        const int q_u = of(q_v, u), end_u = q_u + of(len_v, u);
+                        if (q_u == end_u) continue;
+                        auto clamp = [&](int x) { return x < q_u ? q_u : (x > end_u ? end_u : x); };
+                        // [a, b): u's entries of the row (fibre), s0: where those of the slice start
+                        int a = q_u, b = end_u, s0 = q_u, at, shift_u = 0;
+                        if constexpr (kCoo) {
+                            while (a < b) {                    // (pairs)
+                                const int mid = a + ((b - a) >> 1), r = crd_of(u, 0)[mid];
+                                if (r < row || (r == row && crd_of(u, 1)[mid] < col)) a = mid + 1; else b = mid;
+                            }
+                            at = a;
+                            const bool same = u != t && at < end_u && crd_of(u, 0)[at] == row && crd_of(u, 1)[at] == col;
+                            if (u < t && same) { head = false; ++at; }
+                            place += u != t ? at - q_u : 0;
+                            continue;
+                        }
+                        const Ints pos = pos_of(u, D - 1);
+                        if (u == t) {
+                            a = clamp(pos[seg]);
+                            if constexpr (kCsf) s0 = clamp(pos[pos_of(t, 1)[up]]);
+                            row_head = row_head && a == q;
+                            slice_head = slice_head && s0 == q;
+                            continue;
+                        }
+                        int i_lo = of(ilo_v, u), i_hi = of(ihi_v, u), seg_u = row;
+                        bool stored = true;                    // does u store the row (fibre)
+                        if constexpr (kCsf) {
+                            const int up_hi = of(up_hi_v, u), up_u = lower(crd_of(u, 0), of(up_lo_v, u), up_hi + 1, row);
+                            stored = up_u <= up_hi && crd_of(u, 0)[up_u] == row;
+                            const int f_end = i_hi;
+                            if (up_u <= up_hi) {
+                                const int f = pos_of(u, 1)[up_u];
+                                s0 = clamp(pos[f]);
+                                i_lo = f > i_lo ? f : i_lo;
+                                if (stored) i_hi = pos_of(u, 1)[up_u + 1];
+                                i_hi = i_hi < f_end ? i_hi : f_end;
+                            } else {
+                                s0 = end_u;
+                                i_lo = i_hi;
+                            }
+                        }
+                        if constexpr (FMT != SPADD_CSR) {
+                            if (kCsf && !stored) seg_u = i_lo;
+                            else seg_u = lower(crd_of(u, D - 2), i_lo, i_hi, kCsf ? fibre : row);
+                            stored = stored && seg_u < i_hi && crd_of(u, D - 2)[seg_u] == (kCsf ? fibre : row);
+                        }
+                        a = clamp(pos[seg_u]);
+                        b = stored ? clamp(pos[seg_u + 1]) : a;
+                        if (kMapped) shift_u = starts_of(u)[seg_u] - pos[seg_u];
+                        at = lower(crd_of(u, D - 1) + shift_u, a, b, col);
+                        if (u < t && at < b && crd_of(u, D - 1)[at + shift_u] == col) { head = false; ++at; }
+                        row_head = row_head && at == a;
+                        slice_head = slice_head && at == s0;
+                        place += at - q_u;
+                    }
+                    w.order[place] = (uint16_t)(K <= 2 ? (sb_t + i) * (int)sizeof(KeyT) : (t << 13 | (sb_t + i)));
+                    keys[sb_t + i] = (KeyT)place;
+                    auto put_bit = [&](unsigned long long *at) {
+                        atomicOr(reinterpret_cast<uint32_t *>(at) + (place >> 5), 1u << (place & 31));
+                    };
+                    if (head) put_bit(w.heads);
+                    if (kRowHeads && head && row_head) put_bit(w.row_heads);
+                    if (kCsf && head && slice_head) put_bit(w.slice_heads);
+                }
+            }
+            __syncthreads();
+        }
+    };
 
     // ---- 2. merge: adjacent runs pairwise, in rounds ------------------------------
     // (all of this is uniform over the workgroup except the thread's own share)
@@ -939,7 +971,10 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if (kCsf) sm += sm + (diff > slice_mask ? 1u : 0u);
         }
     };
-    if constexpr (K <= 2) {
+    if (far) {
+        rank_far();
+        moved = marked = true;
+    } else if constexpr (K <= 2) {
         if (live == 2) {
             const int nx = of(len_v, 0), ny = of(len_v, K - 1);
             const int d0 = tid * R;
@@ -1085,7 +1120,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         if constexpr (K <= 2) return moved ? (int)w.order[m] : (mb + m) * KB;
         else return moved ? (int)w.order[mb + m] : (only << 13 | (mb + m));
     };
-    if (!kMul && writing && n > 0) {
+    if (!kMul && !far && n > 0) {
         int o[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -1123,18 +1158,19 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     } else if (!all_heads && lane < R) e = w.heads[block0 + lane] & in;
     if constexpr (kRowHeads) {
         if (lane < R) r = w.row_heads[block0 + lane] & in;
-        if (tid == 0 && first_band && w.cont) r &= ~1ull;          // the first row's head is elsewhere
+        if (tid == 0 && w.cont) r &= ~1ull;          // the first row's head is elsewhere
     }
     if constexpr (kCsf) {
         if (lane < R) sl = w.slice_heads[block0 + lane] & in;
-        if (tid == 0 && first_band && w.cont_slice) sl &= ~1ull;
+        if (tid == 0 && w.cont_slice) sl &= ~1ull;
     }
     const int block_counts = lane < R ? __popcll(e) | __popcll(r) << 16 : 0;
     const int wave_incl = dpp_scan_add(block_counts);
+    int slice_incl = 0;
     if (lane == NACHO_WAVE - 1) w.wave_counts[wave] = (uint32_t)wave_incl;
     if constexpr (kCsf) {
-        const int sc = dpp_sum(lane < R ? __popcll(sl) : 0);
-        if (lane == 0) w.wave_slices[wave] = (uint32_t)sc;
+        slice_incl = dpp_scan_add(lane < R ? __popcll(sl) : 0);
+        if (lane == NACHO_WAVE - 1) w.wave_slices[wave] = (uint32_t)slice_incl;
     }
     if (FMT == SPADD_CSR && lane < R) {        // (read by all wavefronts after the prefix sum)
         w.emitted[block0 + lane] = e;
@@ -1157,24 +1193,15 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
     const int own_nnz = own_counts & 0xffff, own_rows = own_counts >> 16;
 
-    // counts of the bands before this one (writing), of all of them (otherwise)
-    auto add_band = [&]() {
-        __syncthreads();
-        if (tid == 0) {
-            w.band_counts[0] += own_nnz;
-            w.band_counts[1] += own_rows;
-            w.band_counts[2] += own_slices;
-        }
-        __syncthreads();
-        first_band = false;
-    };
-    if constexpr (kBands)
-        if (!writing) {
-            add_band();
-            if (!last_band) {
-                next_band();
-                continue;
-            }
+    if constexpr (D >= 2)
+        if (far && lane < R) {
+            // every thread looks bits and counts up by place; a wavefront's are in its lanes
+            w.heads[block0 + lane] = e;
+            if constexpr (kRowHeads) w.row_heads[block0 + lane] = r;
+            if constexpr (kCsf) w.slice_heads[block0 + lane] = sl;
+            const int before = wave_before + wave_incl - block_counts;
+            w.starts[block0 + lane] = (unsigned)before;
+            if constexpr (kCsf) w.starts[block0 + lane] |= (unsigned long long)(slices_before + slice_incl - __popcll(sl)) << 32;
         }
 
     // ---- 4. prefix sum over the workgroups, first half: publish -------------------------
@@ -1187,16 +1214,13 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     unsigned long long *totals2 = totals + state_half;
     unsigned int *counts_of2 = reinterpret_cast<unsigned int *>(totals + state_half + n_chunks);
     const int64_t chunk = p / kChunk, chunk0 = chunk * kChunk;
-    const bool look_up = !kBands || !writing;
-    const int t_nnz = kBands ? w.band_counts[0] : own_nnz, t_rows = kBands ? w.band_counts[1] : own_rows;
-    const int t_slices = kBands ? w.band_counts[2] : own_slices;
     unsigned early[kWordLoads];
-    if (look_up && wave == 0) {
+    if (wave == 0) {
         if (lane == 0) {
-            __hip_atomic_store(&counts_of[p], kWordValid | ((unsigned)t_rows << 14) | (unsigned)t_nnz, __ATOMIC_RELAXED,
+            __hip_atomic_store(&counts_of[p], kWordValid | ((unsigned)own_rows << 14) | (unsigned)own_nnz, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
             if (kCsf)
-                __hip_atomic_store(&counts_of2[p], kWordValid | (unsigned)t_slices, __ATOMIC_RELAXED,
+                __hip_atomic_store(&counts_of2[p], kWordValid | (unsigned)own_slices, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
         const int m = (int)(p - chunk0);
@@ -1209,7 +1233,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
     }
 
-    // CSR: the rows whose pos this partition (band) writes, and the places before such a row
+    // CSR: the rows whose pos this partition writes, and the places before such a row
     int first_row = 0, end_row = 0, pos_at = 0;
     auto places_before = [&](int row) {
         int m = 0;
@@ -1221,15 +1245,15 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         return m;
     };
-    if (FMT == SPADD_CSR && writing) {
-        first_row = row0 + (first_band && w.cont ? 1 : 0);
-        end_row = last_band ? table_coord(p + 1, 0) + (int)w.cont_next : next_row;
+    if (FMT == SPADD_CSR) {
+        first_row = row0 + (w.cont ? 1 : 0);
+        end_row = table_coord(p + 1, 0) + (int)w.cont_next;
         if (first_row + tid < end_row) pos_at = places_before(first_row + tid);
     }
 
     // ---- the keys of the output entries, and what else the sums and products need ----------------
     KeyT key[R];
-    if (writing && n > 0) {
+    if (!far && n > 0) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int m = place0 + j * NACHO_WAVE + lane, mm = m < n ? m : n - 1;
@@ -1295,98 +1319,89 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 
     // ---- 4. prefix sum, second half: wavefront 0 reads the counts of the workgroups before this one in its
     // chunk, wavefront 1 those of the chunks before
-    if (look_up) {
-        if (wave == 0) {
-            int b_nnz = 0, b_rows = 0, b_slices = 0, unused = 0;
-            bool ok = sum_words<true, kWordLoads>(counts_of, chunk0, (int)(p - chunk0), early, lane, b_nnz, b_rows);
-            if (kCsf && ok) ok = sum_words<false, kWordLoads>(counts_of2, chunk0, (int)(p - chunk0), early, lane, b_slices, unused);
-            if (lane == 0) {
-                if (ok && (p == chunk0 + kChunk - 1 || p == P - 1)) {
-                    __hip_atomic_store(&totals[chunk], kTotalValid | pack_counts(b_rows + t_rows, b_nnz + t_nnz),
+    if (wave == 0) {
+        int b_nnz = 0, b_rows = 0, b_slices = 0, unused = 0;
+        bool ok = sum_words<true, kWordLoads>(counts_of, chunk0, (int)(p - chunk0), early, lane, b_nnz, b_rows);
+        if (kCsf && ok) ok = sum_words<false, kWordLoads>(counts_of2, chunk0, (int)(p - chunk0), early, lane, b_slices, unused);
+        if (lane == 0) {
+            if (ok && (p == chunk0 + kChunk - 1 || p == P - 1)) {
+                __hip_atomic_store(&totals[chunk], kTotalValid | pack_counts(b_rows + own_rows, b_nnz + own_nnz),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (kCsf)
+                    __hip_atomic_store(&totals2[chunk], kTotalValid | pack_counts(0, b_slices + own_slices),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (kCsf)
-                        __hip_atomic_store(&totals2[chunk], kTotalValid | pack_counts(0, b_slices + t_slices),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                w.base_nnz = b_nnz;
-                w.base_rows = b_rows;
-                w.base_slices = b_slices;
-                if (!ok) w.gave_up = 1;
             }
-        } else if (wave == 1) {
-            int c_nnz = 0, c_rows = 0, c_slices = 0, unused = 0;
-            bool ok = true;
-            if (chunk > 0) {
-                ok = sum_totals<kChunk>(totals, counts_of, chunk, lane, c_nnz, c_rows);
-                if (kCsf && ok) ok = sum_totals<kChunk>(totals2, counts_of2, chunk, lane, c_slices, unused);
-            }
-            if (lane == 0) {
-                w.more_nnz = c_nnz;
-                w.more_rows = c_rows;
-                w.more_slices = c_slices;
-                if (!ok) w.gave_up = 1;
-            }
+            w.base_nnz = b_nnz;
+            w.base_rows = b_rows;
+            w.base_slices = b_slices;
+            if (!ok) w.gave_up = 1;
         }
-        lds_barrier();
-        const bool gave_up = __builtin_amdgcn_readfirstlane(w.gave_up) != 0;
-        fresh();
-        if (tid == 0) {
-            const auto &out = arg_ptr->out;
-            const int base_nnz = w.base_nnz + w.more_nnz, base_rows = w.base_rows + w.more_rows;
-            const int base_slices = w.base_slices + w.more_slices;
-            // a status once set to an error stays: the errors are ordered, the gravest wins
-            if (gave_up) atomicMin(out.status, (int32_t)NACHO_ERR_HIP);
-            else if (broken) atomicMin(out.status, (int32_t)NACHO_ERR_INVALID_ARG);
-            if (p == P - 1 && !gave_up) {
-                // totals, tails and the capacity verdict (the only writer of these words)
-                const long long total_nnz = (long long)base_nnz + t_nnz;
-                const long long total_rows = kRowHeads ? (long long)base_rows + t_rows
-                                                       : (FMT == SPADD_CSR ? row_extent() : 1);
-                const long long total_slices = (long long)base_slices + t_slices;
-                bool fits = total_nnz <= out.cap_nnz && (FMT != SPADD_DCSR || total_rows <= out.cap_rows);
-                if (kCsf) {
-                    // third-order tensors: {slices, fibres, entries}; the tails of the three pos arrays
-                    out.counts[0] = total_slices;
-                    out.counts[1] = total_rows;
-                    out.counts[2] = total_nnz;
-                    fits = fits && total_slices <= out.cap_rows && total_rows <= out.cap_fibres;
-                    out.pos0[0] = 0;
-                    out.pos0[1] = (int32_t)total_slices;
-                    if (total_slices <= out.cap_rows) out.pos1[total_slices] = (int32_t)total_rows;
-                    if (total_rows <= out.cap_fibres) out.pos2[total_rows] = (int32_t)total_nnz;
-                } else {
-                    out.counts[0] = total_rows;
-                    out.counts[1] = total_nnz;
-                }
-                if (!fits) atomicMin(out.status, (int32_t)NACHO_ERR_CAPACITY);
-                if (FMT == SPADD_VECTOR || kCoo) { out.pos1[0] = 0; out.pos1[1] = (int32_t)total_nnz; }
-                if (FMT == SPADD_CSR) out.pos1[row_extent()] = (int32_t)total_nnz;
-                if (FMT == SPADD_DCSR) {
-                    out.pos0[0] = 0;
-                    out.pos0[1] = (int32_t)total_rows;
-                    if (total_rows <= out.cap_rows) out.pos1[total_rows] = (int32_t)total_nnz;
-                }
-            }
+    } else if (wave == 1) {
+        int c_nnz = 0, c_rows = 0, c_slices = 0, unused = 0;
+        bool ok = true;
+        if (chunk > 0) {
+            ok = sum_totals<kChunk>(totals, counts_of, chunk, lane, c_nnz, c_rows);
+            if (kCsf && ok) ok = sum_totals<kChunk>(totals2, counts_of2, chunk, lane, c_slices, unused);
         }
-        if (gave_up) break;                    // no offset: nothing of this partition may be written
-        if constexpr (kBands) {
-            if (broken) break;
-            writing = true;
-            first_band = true;
-            __syncthreads();
-            restart_bands();
-            next_band();
-            continue;
+        if (lane == 0) {
+            w.more_nnz = c_nnz;
+            w.more_rows = c_rows;
+            w.more_slices = c_slices;
+            if (!ok) w.gave_up = 1;
         }
     }
+    lds_barrier();
+    const bool gave_up = __builtin_amdgcn_readfirstlane(w.gave_up) != 0;
+    fresh();
+    if (tid == 0) {
+        const auto &out = arg_ptr->out;
+        const int base_nnz = w.base_nnz + w.more_nnz, base_rows = w.base_rows + w.more_rows;
+        const int base_slices = w.base_slices + w.more_slices;
+        // a status once set to an error stays: the errors are ordered, the gravest wins
+        if (gave_up) atomicMin(out.status, (int32_t)NACHO_ERR_HIP);
+        else if (broken) atomicMin(out.status, (int32_t)NACHO_ERR_INVALID_ARG);
+        if (p == P - 1 && !gave_up) {
+            // totals, tails and the capacity verdict (the only writer of these words)
+            const long long total_nnz = (long long)base_nnz + own_nnz;
+            const long long total_rows = kRowHeads ? (long long)base_rows + own_rows
+                                                   : (FMT == SPADD_CSR ? row_extent() : 1);
+            const long long total_slices = (long long)base_slices + own_slices;
+            bool fits = total_nnz <= out.cap_nnz && (FMT != SPADD_DCSR || total_rows <= out.cap_rows);
+            if (kCsf) {
+                // third-order tensors: {slices, fibres, entries}; the tails of the three pos arrays
+                out.counts[0] = total_slices;
+                out.counts[1] = total_rows;
+                out.counts[2] = total_nnz;
+                fits = fits && total_slices <= out.cap_rows && total_rows <= out.cap_fibres;
+                out.pos0[0] = 0;
+                out.pos0[1] = (int32_t)total_slices;
+                if (total_slices <= out.cap_rows) out.pos1[total_slices] = (int32_t)total_rows;
+                if (total_rows <= out.cap_fibres) out.pos2[total_rows] = (int32_t)total_nnz;
+            } else {
+                out.counts[0] = total_rows;
+                out.counts[1] = total_nnz;
+            }
+            if (!fits) atomicMin(out.status, (int32_t)NACHO_ERR_CAPACITY);
+            if (FMT == SPADD_VECTOR || kCoo) { out.pos1[0] = 0; out.pos1[1] = (int32_t)total_nnz; }
+            if (FMT == SPADD_CSR) out.pos1[row_extent()] = (int32_t)total_nnz;
+            if (FMT == SPADD_DCSR) {
+                out.pos0[0] = 0;
+                out.pos0[1] = (int32_t)total_rows;
+                if (total_rows <= out.cap_rows) out.pos1[total_rows] = (int32_t)total_nnz;
+            }
+        }
+    }
+    const WaveLog wlog = {arg_ptr->wlog.rec, arg_ptr->wlog.capacity};
+    auto log_end = [&]() { wave_end(wlog, (long long)p * kWaves + wave, stamp, logged_items, logged_rows); };
+    if (gave_up) return log_end();             // no offset: nothing of this partition may be written
 
     // ---- 5. compute: write the partition's output ------------------------------
     // (the partition's offsets are uniform: the stores address base + a small per-lane offset)
     fresh();
     const auto &out = arg_ptr->out;
-    const int at_nnz = __builtin_amdgcn_readfirstlane(w.base_nnz + w.more_nnz + w.band_counts[0]);
-    const int at_rows = __builtin_amdgcn_readfirstlane(w.base_rows + w.more_rows + w.band_counts[1]);
-    const int at_slices = __builtin_amdgcn_readfirstlane(w.base_slices + w.more_slices + w.band_counts[2]);
+    const int at_nnz = __builtin_amdgcn_readfirstlane(w.base_nnz + w.more_nnz);
+    const int at_rows = __builtin_amdgcn_readfirstlane(w.base_rows + w.more_rows);
+    const int at_slices = __builtin_amdgcn_readfirstlane(w.base_slices + w.more_slices);
     auto room_of = [](int64_t cap, int at) {
         const int64_t left = cap - at;
         return left < 0 ? 0 : (left > 0x7fffffffll ? 0x7fffffff : (int)left);
@@ -1420,6 +1435,60 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     const Out seg_pos_out = kRowHeads ? out_at(kCsf ? out.pos2 : out.pos1, at_rows) : nullptr;
     const Out top_crd = kCsf ? out_at(out.crd0, at_slices) : nullptr;
     const Out top_pos = kCsf ? out_at(out.pos1, at_slices) : nullptr;
+    if constexpr (D >= 2)
+        if (far) {                             // (uniform, rare) by entry, each at its place
+#pragma unroll 1
+            for (int t = 0; t < k; ++t) {
+                const int q_t = of(q_v, t), len_t = of(len_v, t), sb_t = of(sb_v, t);
+#pragma unroll 1
+                for (int i = tid; i < len_t; i += kThreads) {
+                    const int m = (int)keys[sb_t + i], blk = m / NACHO_WAVE, q = q_t + i;
+                    const unsigned long long below = low_bits(m & (NACHO_WAVE - 1)), upto = low_bits((m & (NACHO_WAVE - 1)) + 1);
+                    if ((w.heads[blk] & upto & ~below) == 0ull) continue;      // not emitted
+                    const unsigned long long before = w.starts[blk];
+                    const int loc = (int)(before & 0xffffu) + __popcll(w.heads[blk] & below);
+                    int seg = 0, shift = 0;
+                    const bool row_starts_here = kRowHeads && (w.row_heads[blk] & upto & ~below) != 0ull;
+                    if (kMapped || row_starts_here) seg = holder(pos_of(t, D - 1), of(ilo_v, t), of(ihi_v, t), q);
+                    if (kMapped) shift = starts_of(t)[seg] - pos_of(t, D - 1)[seg];
+                    T v = global_ptr<T>(w.sval[t])[sb_t + i + shift];
+                    for (int g = 1; g < k; ++g) {
+                        if constexpr (kMul) {
+                            // (emitted: the next k - 1 places are the other operands' entries, in order)
+                            int at = K <= 2 ? w.order[m + g] / KB : w.order[m + g] & 0x1fff;
+                            if (kMapped) at += starts_of(g)[seg] - pos_of(g, D - 1)[seg];
+                            v *= global_ptr<T>(w.sval[g])[at];
+                        } else {
+                            if (m + g >= n) break;
+                            const int at = (m + g) / NACHO_WAVE, bit = (m + g) & (NACHO_WAVE - 1);
+                            if ((w.heads[at] & low_bits(bit + 1) & ~low_bits(bit)) != 0ull) break;
+                            v += value_at((int)w.order[m + g]);
+                        }
+                    }
+                    if (loc < room) {
+                        store(crd_out, (unsigned)loc, (int32_t)crd_of(t, D - 1)[q + shift]);
+                        if (kCoo) store(row_out, (unsigned)loc, (int32_t)crd_of(t, 0)[q]);
+                        store(val_out, (unsigned)loc, v);
+                    }
+                    if constexpr (kRowHeads) {
+                        const int rloc = (int)((unsigned)before >> 16) + __popcll(w.row_heads[blk] & below);
+                        if (row_starts_here && rloc < room_rows) {
+                            store(seg_crd_out, (unsigned)rloc, (int32_t)crd_of(t, D - 2)[seg]);
+                            store(seg_pos_out, (unsigned)rloc, at_nnz + loc);
+                        }
+                        if constexpr (kCsf) {
+                            const int sloc = (int)(before >> 32) + __popcll(w.slice_heads[blk] & below);
+                            if ((w.slice_heads[blk] & upto & ~below) != 0ull && sloc < room_slices) {
+                                const int up = holder(pos_of(t, 1), of(up_lo_v, t), of(up_hi_v, t) + 1, seg);
+                                store(top_crd, (unsigned)sloc, (int32_t)crd_of(t, 0)[up]);
+                                store(top_pos, (unsigned)sloc, at_rows + rloc);
+                            }
+                        }
+                    }
+                }
+            }
+            return log_end();
+        }
     int at = wave_before & 0xffff, at_row = wave_before >> 16, at_slice = slices_before;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
@@ -1442,17 +1511,17 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             const unsigned long long rj = lane_word(r, j);
             if (rj != 0ull) {                  // (uniform)
                 const unsigned rloc = (unsigned)(at_row + lanes_below(rj));
-                const uint32_t field = (uint32_t)(key[j] >> cb);
+                const KeyT field = key[j] >> cb;
                 if (my_bit(rj) && (int)rloc < room_rows) {
                     // (a row's coordinate; a fibre's j) and where its entries start
-                    store(seg_crd_out, rloc, kCsf ? (int32_t)(field & (uint32_t)((1ull << jb) - 1ull)) : row0 + (int32_t)field);
+                    store(seg_crd_out, rloc, kCsf ? (int32_t)(uint32_t)(field & ((KeyT(1) << jb) - KeyT(1))) : row0 + (int32_t)(uint32_t)field);
                     store(seg_pos_out, rloc, at_nnz + (int)loc);
                 }
                 if constexpr (kCsf) {
                     const unsigned long long sj = lane_word(sl, j);
                     const unsigned sloc = (unsigned)(at_slice + lanes_below(sj));
                     if (my_bit(sj) && (int)sloc < room_slices) {
-                        store(top_crd, sloc, row0 + (int32_t)(uint32_t)((unsigned long long)field >> jb));
+                        store(top_crd, sloc, row0 + (int32_t)(uint32_t)(field >> jb));
                         store(top_pos, sloc, at_rows + (int)rloc);
                     }
                     at_slice += __popcll(sj);
@@ -1462,27 +1531,7 @@ __device__ __forceinline__ bool merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         at += __popcll(ej);
     }
-    if (!kBands || last_band) break;
-    add_band();
-    next_band();
-    }
-    const WaveLog wlog = {arg_ptr->wlog.rec, arg_ptr->wlog.capacity};
-    wave_end(wlog, (long long)p * kWaves + wave, stamp, logged_items, logged_rows);
-    return false;
-}
-
-// (a function of its own: what it needs of registers and loops costs the ordinary path nothing)
-template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped>
-__device__ __attribute__((noinline)) void merge_bands(unsigned long long args, TileOf<FMT, T, KeyT, kSmall> *w,
-                                                      unsigned long long t_begin, unsigned long long c_begin)
-{
-    const WaveStamp stamp = {t_begin, c_begin};
-    // (arguments of a function arrive in vector registers)
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)args);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(args >> 32));
-    const ArgPtr arg_ptr = (ArgPtr)(((unsigned long long)hi << 32) | lo);
-    const DevOperands *none = nullptr;
-    merge_partition<FMT, T, KeyT, kSmall, K, kMul, kMapped, false, true>(arg_ptr, *w, *none, stamp);
+    log_end();
 }
 
 template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch = false>
@@ -1492,9 +1541,7 @@ spadd_kernel(MergeArgs args)
     __shared__ TileOf<FMT, T, KeyT, kSmall> w;
     const WaveStamp stamp = wave_begin();
     const ArgPtr arg_ptr = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    const bool redo = merge_partition<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch, false>(arg_ptr, w, args.ops, stamp);
-    if constexpr (FMT != SPADD_VECTOR)
-        if (redo) merge_bands<FMT, T, KeyT, kSmall, K, kMul, kMapped>((unsigned long long)arg_ptr, &w, stamp.t, stamp.c);
+    merge_partition<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch>(arg_ptr, w, args.ops, stamp);
 }
 
 inline int64_t chunks_of(int64_t P, int chunk) { return (P + chunk - 1) / chunk; }

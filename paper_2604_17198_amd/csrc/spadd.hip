@@ -27,8 +27,8 @@ int spadd_resident() { return 32 / kWaves; }
 int spadd_wavefronts() { return kWaves; }
 
 // The key layout of a call: 32-bit keys when the rows (slices) that an average full partition spans take a
-// quarter of the row field or less, or the field holds any row (a partition that spans more than the field is taken in bands, twice), else
-// 64-bit keys.
+// quarter of the row field or less, or the field holds any row, else 64-bit keys.  A partition that spans more rows
+// than the field holds is merged without keys, by searches, at about a fifth of the speed.
 MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units)
 {
     MergeFields f;
@@ -55,9 +55,13 @@ MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t
     if (f.limit == 0 || (rows > (int64_t)f.limit && span > (int64_t)(f.limit / 4))) {
         f.wide = 1;
         f.small = 0;
-        f.cb = 32;
-        // (matrices: any row; tensors: the row field (i - i0) << jb | j has 32 bits)
-        f.limit = fmt == SPADD_CSF3 ? (uint32_t)(((uint64_t)1 << (32 - f.jb)) - 1u) : 0x80000000u;
+        f.limit = 0x80000000u;                 // matrices: any row
+        if (fmt != SPADD_CSF3) f.cb = 32;
+        else {
+            // tensors: the row field (i - i0) << jb | j has what is left of the key, kept in 48 bits before
+            const int room = (64 - f.cb < 48 ? 64 - f.cb : 48) - f.jb;         // (>= 2)
+            if (room < 32) f.limit = (uint32_t)(((uint64_t)1 << room) - 1u);
+        }
     }
     return f;
 }

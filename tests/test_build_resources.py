@@ -1,0 +1,55 @@
+"""What the kernels of the built library ask of the GPU beside registers and LDS, read from the metadata of the code
+objects compiled here (no GPU): a private segment is memory that the runtime sets aside for every wavefront the chip
+can hold, and the library allocates nothing."""
+import os
+
+import msgpack
+import pytest
+
+from paper_2604_17198_amd import build
+
+
+def _code_objects(blob):
+    """The gfx950 images (little-endian 64-bit ELF, machine 224) inside a host library."""
+    at = blob.find(b"\x7fELF\x02\x01\x01", 1)
+    while at >= 0:
+        if int.from_bytes(blob[at + 18:at + 20], "little") == 224:
+            yield at
+        at = blob.find(b"\x7fELF\x02\x01\x01", at + 4)
+
+
+def kernels(path):
+    """name -> metadata of every kernel of the library (the AMDGPU metadata note, type 32, is MessagePack)."""
+    blob = open(path, "rb").read()
+    word = lambda at, n: int.from_bytes(blob[at:at + n], "little")
+    found = {}
+    for elf in _code_objects(blob):
+        for h in range(word(elf + 56, 2)):
+            segment = elf + word(elf + 32, 8) + 56 * h
+            if word(segment, 4) != 4:                   # PT_NOTE
+                continue
+            note = elf + word(segment + 8, 8)
+            end = note + word(segment + 32, 8)
+            while note + 12 <= end:
+                name, size, kind = word(note, 4), word(note + 4, 4), word(note + 8, 4)
+                body = note + 12 + (name + 3 & ~3)
+                if kind == 32:
+                    for k in msgpack.unpackb(blob[body:body + size])["amdhsa.kernels"]:
+                        found[k[".name"]] = k
+                note = body + (size + 3 & ~3)
+    return found
+
+
+@pytest.fixture(scope="module")
+def built():
+    if not os.path.exists(build.LIB):
+        pytest.fail(f"{build.LIB} not built; run `python -m paper_2604_17198_amd.build`")
+    return kernels(build.LIB)
+
+
+def test_no_kernel_has_a_stack(built):
+    """No private segment but for spilled registers (no calls, no arrays outside registers)."""
+    assert sum("spadd_kernel" in name for name in built) > 100
+    stacks = {name: k[".private_segment_fixed_size"] for name, k in built.items()
+              if k[".private_segment_fixed_size"] > 0 and k[".vgpr_spill_count"] == 0}
+    assert not stacks

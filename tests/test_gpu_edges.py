@@ -179,8 +179,8 @@ def test_merge_short_and_long_partitions(k, over):
 
 
 def _banded(rng, n_rows, n_cols, dense, sparse):
-    """Many entries in a few rows and a few in rows far apart: partitions of the latter span more rows than the row
-    field of their keys holds."""
+    """Many entries in a band of a few rows and a few in rows far apart: partitions of the latter span more rows than the
+    row field of their keys holds."""
     top = rng.integers(0, 60, dense) * n_cols + rng.integers(0, n_cols, dense)
     rest = rng.integers(60, n_rows, sparse) * n_cols + rng.integers(0, n_cols, sparse)
     return np.unique(np.concatenate([top, rest]))
@@ -189,8 +189,8 @@ def _banded(rng, n_rows, n_cols, dense, sparse):
 @pytest.mark.parametrize("k,total,dtype", [(2, 1_100_000, np.float32), (3, 1_100_000, np.float64),
                                            (2, 3_300_000, np.float64), (3, 3_300_000, np.float32)])
 def test_merge_in_bands(k, total, dtype):
-    """Rows past the row field (12 bits beside 2^20 columns): the partition is taken in bands of rows, twice; in short
-    partitions and in long ones."""
+    """Rows past the row field (12 bits beside 2^20 columns): the partition is merged without keys; short partitions and
+    long ones."""
     rng = np.random.default_rng(41)
     shape = (1 << 19, 1 << 20)
     keys = [_banded(rng, *shape, int(total / (k + 0.33)), 9000) for _ in range(k)]
@@ -222,6 +222,87 @@ def test_merge_tensors_in_bands(dtype):
         c = np.stack(np.unravel_index(lin, shape), axis=1)
         tens.append(csf3._tensor(c, rng.uniform(-1, 1, len(c)).astype(dtype)))
     csf3._check(tens, shape, 0, "bands")
+
+
+@pytest.mark.parametrize("k,dtype", [(2, np.float32), (3, np.float64)])
+def test_merge_few_rows_per_key(k, dtype):
+    """Eight bits of row field beside 2^24 columns, thousands of rows in the first partitions; and a result that does not
+    fit: what is written is the start of the whole result, what lies behind it stays."""
+    rng = np.random.default_rng(61)
+    shape = (65_000, 1 << 24)
+    keys = []
+    for _ in range(k):
+        top = rng.integers(0, 60_000, 2500) * shape[1] + rng.integers(0, shape[1], 2500)
+        rest = rng.integers(60_000, shape[0], 6_200_000 // k) * shape[1] + rng.integers(0, shape[1], 6_200_000 // k)
+        keys.append(np.unique(np.concatenate([top, rest])))
+    keys[1] = np.unique(np.concatenate([keys[1], keys[0][:3000:2]]))
+    cs = [np.stack([x // shape[1], x % shape[1]], 1) for x in keys]
+    mats = [(c, rng.uniform(-1, 1, len(c)).astype(dtype)) for c in cs]
+    add.check_dcsr(mats, shape, 0, "few rows per key")
+    ds = [mul_dcsr._mat(c, v) for c, v in mats]
+    ops = [nb.dcsr(dev(m["pos0"]), dev(m["crd0"]), dev(m["pos1"]), dev(m["crd1"]), *shape, dev(m["val"])) for m in ds]
+    total = sum(len(c) for c in cs)
+    dt = torch.float32 if dtype == np.float32 else torch.float64
+    whole = nb.nacho_spadd_k(ops, nb.SparseOut("dcsr", total, total, dt, "cuda"))
+    for cap_rows, cap_nnz in ((total, 2999), (1777, total)):
+        part_of = nb.SparseOut("dcsr", total, total, dt, "cuda")
+        part_of.c.cap_rows, part_of.c.cap_nnz = cap_rows, cap_nnz
+        for a in (part_of.crd0, part_of.pos1, part_of.crd1, part_of.val):
+            a.fill_(-7)
+        nb.nacho_spadd_k(ops, part_of)
+        assert int(part_of.status[0]) == -4 and torch.equal(part_of.counts, whole.counts)
+        rows, nnz = min(cap_rows, int(whole.counts[0])), min(cap_nnz, int(whole.counts[1]))
+        for name, n in (("crd0", rows), ("pos1", rows), ("crd1", nnz), ("val", nnz)):
+            got, ref = getattr(part_of, name), getattr(whole, name)
+            assert torch.equal(got[:n], ref[:n]), name
+            behind = n + (1 if name == "pos1" else 0)
+            assert bool((got[behind:] == -7).all()), name
+
+
+def _triples(rng, shape, n):
+    c = np.stack([rng.integers(0, e, n) for e in shape], 1)
+    return np.unique(c, axis=0)
+
+
+@pytest.mark.parametrize("k,dtype", [(2, np.float64), (3, np.float32), (5, np.float32)])
+def test_merge_tensors_wide(k, dtype):
+    """64-bit keys: a second mode of 2^24 (any slice fits), modes with which 20, 17 and 2 bits are left for the slice, and
+    slices, fibres and entries that two operands share."""
+    rng = np.random.default_rng(71)
+    top = (1 << 31) - 1
+    for shape in ((1_000_000, 1 << 24, 16), (top, 1 << 24, 1 << 20), (top, top, 300), (top, top, top)):
+        tens, first = [], None
+        for t in range(k):
+            c = _triples(rng, shape, 40_000 // k)
+            if t == 0:
+                first = c
+            else:
+                same = first[rng.choice(len(first), 3000, replace=False)]
+                fibre, piece = same.copy(), same.copy()
+                fibre[:, 2] = rng.integers(0, shape[2], len(same))
+                piece[:, 1] = rng.integers(0, shape[1], len(same))
+                c = np.unique(np.concatenate([c, same[:1500], fibre, piece]), axis=0)
+            tens.append(csf3._tensor(c, rng.uniform(-1, 1, len(c)).astype(dtype)))
+        for P in (0, 1, 37):
+            csf3._check(tens, shape, P, "wide")
+
+
+@pytest.mark.parametrize("k,dtype", [(2, np.float32), (2, np.float64), (3, np.float64)])
+def test_product_rows_past_the_key(k, dtype):
+    """Remapped operands: eight bits of row field beside 2^24 columns, thousands of common rows of one or two entries."""
+    rng = np.random.default_rng(81)
+    shape = (1 << 20, 1 << 24)
+    thin = np.sort(rng.choice(np.arange(100, shape[0]), 4000, replace=False))
+    shared = np.unique(thin * shape[1] + rng.integers(0, shape[1], len(thin)))
+    wide = np.unique(rng.integers(0, 60, 30_000) * shape[1] + rng.integers(0, shape[1], 30_000))
+    mats = []
+    for _ in range(k):
+        own = thin[rng.choice(len(thin), 2500, replace=False)] * shape[1] + rng.integers(0, shape[1], 2500)
+        more = rng.integers(0, 60, 400_000) * shape[1] + rng.integers(0, shape[1], 400_000)
+        keys = np.unique(np.concatenate([shared, own, wide, more]))
+        c = np.stack([keys // shape[1], keys % shape[1]], 1)
+        mats.append(mul_dcsr._mat(c, rng.uniform(0.5, 1, len(c)).astype(dtype)))
+    mul_dcsr.check(mats, shape, 0, "rows past the key")
 
 
 # ---- recursive partitioning -----------------------------------------------------
