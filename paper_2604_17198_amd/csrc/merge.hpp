@@ -841,6 +841,11 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     auto starts_of = [&](int t) { return ints(arg_ptr->ops.start[t]); };
     auto rank_far = [&]() {
         if constexpr (D >= 2) {
+            // (unsorted or repeated coordinates can give two entries one place and another place none: every order
+            // word names an entry before the searches write theirs)
+            for (int m = tid; m < n; m += kThreads)
+                w.order[m] = (uint16_t)(K <= 2 ? first_word * (int)sizeof(KeyT) : (live_t << 13 | first_word));
+            __syncthreads();
 #pragma unroll 1
             for (int t = 0; t < k; ++t) {
                 const int q_t = of(q_v, t), len_t = of(len_v, t), sb_t = of(sb_v, t);
@@ -1454,10 +1459,20 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     T v = global_ptr<T>(w.sval[t])[sb_t + i + shift];
                     for (int g = 1; g < k; ++g) {
                         if constexpr (kMul) {
-                            // (emitted: the next k - 1 places are the other operands' entries, in order)
-                            int at = K <= 2 ? w.order[m + g] / KB : w.order[m + g] & 0x1fff;
-                            if (kMapped) at += starts_of(g)[seg] - pos_of(g, D - 1)[seg];
-                            v *= global_ptr<T>(w.sval[g])[at];
+                            // (emitted: the next k - 1 places are the other operands' entries)
+                            const int o = w.order[m + g], t_g = K <= 2 ? (K == 2 && o >= two_at ? 1 : 0) : o >> 13;
+                            int at = K <= 2 ? o / KB : o & 0x1fff;
+                            if constexpr (kMapped) {
+                                const int place_at = at;
+#pragma unroll 1
+                                for (int u = 0; u < k; ++u) {
+                                    if (u != t_g) continue;
+                                    const int q_u = of(q_v, u) + place_at - of(sb_v, u);
+                                    const int seg_u = holder(pos_of(u, D - 1), of(ilo_v, u), of(ihi_v, u), q_u);
+                                    at += starts_of(u)[seg_u] - pos_of(u, D - 1)[seg_u];
+                                }
+                            }
+                            v *= global_ptr<T>(w.sval[t_g])[at];
                         } else {
                             if (m + g >= n) break;
                             const int at = (m + g) / NACHO_WAVE, bit = (m + g) & (NACHO_WAVE - 1);
