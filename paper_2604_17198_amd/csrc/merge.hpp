@@ -1257,8 +1257,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
 
     // ---- the keys of the output entries, and what else the sums and products need ----------------
+    // (products: the keys after the values, whose requests need the registers)
     KeyT key[R];
-    if (!far && n > 0) {
+    auto load_keys = [&]() {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int m = place0 + j * NACHO_WAVE + lane, mm = m < n ? m : n - 1;
@@ -1266,6 +1267,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if (K <= 2 && moved) at = w.order[mm];
             key[j] = *reinterpret_cast<const KeyT *>(kb + at);
         }
+    };
+    if (!far && n > 0) {
+        if constexpr (!kMul) load_keys();
         if constexpr (kMul) {
             // products: few places are emitted; those ask for the values of all operands
             auto load_value = [&](int m) -> T {
@@ -1286,16 +1290,22 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 }
 #pragma unroll 1
                 for (int g = 1; g < k; ++g) {
-                    T more[R];
+                    // (as many at a time as there are registers for beside the products)
+                    constexpr int kBatch = sizeof(T) == 8 ? (R + 1) / 2 : R;
 #pragma unroll
-                    for (int j = 0; j < R; ++j) {
-                        more[j] = T(1);
-                        if (my_bit(lane_word(e, j))) more[j] = load_value(place0 + j * NACHO_WAVE + lane + g);
+                    for (int j0 = 0; j0 < R; j0 += kBatch) {
+                        T more[kBatch];
+#pragma unroll
+                        for (int j = j0; j < j0 + kBatch && j < R; ++j) {
+                            more[j - j0] = T(1);
+                            if (my_bit(lane_word(e, j))) more[j - j0] = load_value(place0 + j * NACHO_WAVE + lane + g);
+                        }
+#pragma unroll
+                        for (int j = j0; j < j0 + kBatch && j < R; ++j) val[j] *= more[j - j0];
                     }
-#pragma unroll
-                    for (int j = 0; j < R; ++j) val[j] *= more[j];
                 }
             }
+            load_keys();
         } else {
             // sums: the equal keys behind a head belong to the lanes after it, in operand order
             load_heads();

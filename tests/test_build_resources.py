@@ -53,3 +53,8 @@ def test_no_kernel_has_a_stack(built):
     stacks = {name: k[".private_segment_fixed_size"] for name, k in built.items()
               if k[".private_segment_fixed_size"] > 0 and k[".vgpr_spill_count"] == 0}
     assert not stacks
+
+
+def test_no_kernel_spills(built):
+    spills = {name: k[".vgpr_spill_count"] for name, k in built.items() if k[".vgpr_spill_count"] > 0}
+    assert not spills
