@@ -118,6 +118,7 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
 
     int lo[NACHO_MAX_OPERANDS], off[NACHO_MAX_OPERANDS + 1];
     off[0] = 0;
+    int least = kMost;                                 // coordinates of the operand with the fewest
     bool broken = false;
 #pragma unroll
     for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) {
@@ -127,6 +128,7 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
             lo[t] = posn0[p * k + t];
             const int len = posn0[(p + 1) * k + t] - lo[t];
             broken = broken || len < 0 || len > kMost;
+            least = len < least ? len : least;
             off[t + 1] = off[t] + len;
         }
     }
@@ -171,6 +173,14 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
     for (int w = 0; w < kScanWaves; ++w) {
         if (w < wave) at += s_count[w];
         m += s_count[w];
+    }
+    // Rows without repetitions: every intersected row takes one coordinate of each operand (so they fit s_item, and all
+    // partitions together fit the workspace).  Operand 0 repeating a row that the others store breaks that; such a
+    // partition contributes nothing.
+    if (m > least) {                                   // (uniform)
+        m = 0;
+        found = 0u;
+        if (tid == 0) atomicMin(status, (int32_t)NACHO_ERR_INVALID_ARG);
     }
     for (; found; found &= found - 1u) s_item[at++] = (uint16_t)(first + __ffs(found) - 1);
     __syncthreads();

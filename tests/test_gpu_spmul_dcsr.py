@@ -179,6 +179,27 @@ def test_capacity_overflow_is_reported():
     assert np.array_equal(out.crd0.cpu().numpy()[:nr - 3], ref["crd0"][:nr - 3])
 
 
+@pytest.mark.parametrize("copies", [2, 700, 5000])
+def test_repeated_rows_are_reported(copies):
+    """Operand 0 stores one row `copies` times (against the preconditions): more rows match than the row loop and the
+    workspace have room for.  The partitions that hold them contribute nothing, the others do, and the call says so."""
+    print(f"spmul dcsr repeated rows copies={copies}", flush=True)
+    arr = lambda a: dev(np.asarray(a, dtype=np.int32))
+    val = lambda n: torch.ones(n, dtype=torch.float32, device="cuda")
+    crd0 = [0] + [5] * copies + [9]
+    n = len(crd0)
+    a = nb.dcsr(arr([0, n]), arr(crd0), arr(range(n + 1)), arr([3] * n), 10, 10, val(n))
+    b = nb.dcsr(arr([0, 2]), arr([0, 5]), arr([0, 1, 2]), arr([3, 3]), 10, 10, val(2))
+    for ops in ([a, b], [b, a]):
+        out = nb.SparseOut("dcsr", 2, 2, torch.float32, "cuda")
+        nb.nacho_spmul_k(ops, out)
+        torch.cuda.synchronize()
+        rows, nnz = (int(v) for v in out.counts.cpu().numpy()[:2])
+        assert rows <= 2 and nnz <= 2
+        if ops[0] is a:
+            assert int(out.status[0]) == -1
+
+
 def test_workspace_too_small_and_reuse():
     rng = np.random.default_rng(12)
     shape = (100, 100)
