@@ -426,6 +426,9 @@ int32_t nacho_probe(int32_t kind, void *dst, const void *src, size_t bytes, int6
  */
 int32_t nacho_instrument(void *records /* device */, int64_t capacity);
 int32_t nacho_instrument_record_bytes(void);
+/* Instrumented build: from now on the wait of this workgroup of the row loop of a DCSR product counts as run out (-1:
+ * none), for tests of what such a call leaves. */
+int32_t nacho_instrument_wait(int64_t workgroup);
 /* Wavefronts per workgroup (= per partition) of the merge kernel of nacho_spadd_k / nacho_spmul_k. */
 int32_t nacho_merge_wavefronts(void);
 

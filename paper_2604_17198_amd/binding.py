@@ -26,7 +26,7 @@ EXPORTS = [
     "nacho_version", "nacho_status_string", "nacho_num_partitions", "nacho_workspace_bytes",
     "nacho_partition", "nacho_spmv", "nacho_spmm", "nacho_spadd_k", "nacho_spmul_k", "nacho_workspace_parts",
     "nacho_validate", "nacho_profile_enable", "nacho_profile_read", "nacho_spmv_static",
-    "nacho_static_scratch_bytes", "nacho_instrument", "nacho_instrument_record_bytes",
+    "nacho_static_scratch_bytes", "nacho_instrument", "nacho_instrument_record_bytes", "nacho_instrument_wait",
     "nacho_probe", "nacho_merge_wavefronts", "nacho_rowcost_partitions", "nacho_partition_rowcost",
     "nacho_spmv_rowcost", "nacho_partition_csr64", "nacho_spmv_fused", "nacho_spadd_fused",
 ]
@@ -105,6 +105,7 @@ def lib():
         L.nacho_profile_read.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]
         L.nacho_validate.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
         L.nacho_instrument.argtypes = [C.c_void_p, C.c_int64]
+        L.nacho_instrument_wait.argtypes = [C.c_int64]
         L.nacho_spmv_fused.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_size_t,
                                        C.c_void_p]
         L.nacho_partition_csr64.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_int64,
@@ -478,6 +479,11 @@ def instrument(records, capacity=None):
         return
     cap = records.numel() // rb if capacity is None else capacity
     _check(lib().nacho_instrument(_ptr(records), cap), "nacho_instrument")
+
+
+def instrument_wait(workgroup):
+    """Instrumented library only: the wait of this workgroup of the row loop of a DCSR product counts as run out (-1: none)."""
+    _check(lib().nacho_instrument_wait(workgroup), "nacho_instrument_wait")
 
 
 def merge_wavefronts() -> int:

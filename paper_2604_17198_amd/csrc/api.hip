@@ -21,6 +21,12 @@ nacho::WaveLog &wave_log()
     return log;
 }
 
+int64_t &wait_runs_out()
+{
+    static int64_t workgroup = -1;
+    return workgroup;
+}
+
 void profile_begin(hipStream_t s)
 {
     Profiler &p = profiler();
@@ -209,7 +215,7 @@ struct RemapWs {
     unsigned long long *rows_state, *compact_state;      // prefix-sum state, one after the other
     int64_t state_words;
     RemapArrays remap;
-    int64_t *info;                   // {partitions, intersected rows, remapped total cost} of the last call
+    int64_t *info;                   // {partitions, intersected rows, remapped total cost, abandoned} of the last call
     MergeFields fields;              // key layout of the remapped nest
     PartsWs parts;                   // partitions of the remapped nest
     unsigned long long *tile_state;
@@ -266,15 +272,16 @@ RemapWs carve_remap(void *ws, const nacho_tensor *ops, int k, int32_t dtype, int
     w.Pmax = merge_partitions(SPADD_CSR, dtype, k, w.fields, total_nnz, P, kMappedEntries);
     w.parts0 = carve_parts(c, w.P0, k, 1);
     const int64_t rows_words = remap_state_words(w.P0, k);
-    w.state_words = rows_words + compact_state_words(w.Mmax);
+    // (info is cleared with the state in front of it)
+    w.state_words = rows_words + compact_state_words(w.Mmax) + 4;
     w.rows_state = c.take<unsigned long long>((size_t)w.state_words);
     w.compact_state = w.rows_state + rows_words;
+    w.info = reinterpret_cast<int64_t *>(w.rows_state + w.state_words - 4);
     w.remap.stride = w.Mmax;
     w.remap.rows = c.take<int32_t>((size_t)w.Mmax);
     w.remap.start = c.take<int32_t>((size_t)w.Mmax * k);
     w.remap.cost = c.take<int32_t>((size_t)(w.Mmax + 1) * k);
     w.remap.head = c.take<int32_t>(1 + NACHO_MAX_OPERANDS);
-    w.info = c.take<int64_t>(4);
     w.parts = carve_parts(c, w.Pmax, k, 2);
     w.tile_state = c.take<unsigned long long>((size_t)spadd_state_words(w.Pmax));
     w.pos_full = c.take<int32_t>((size_t)w.Mmax + 1);
@@ -461,6 +468,7 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
                 hipStreamSynchronize(s) != hipSuccess)
                 return NACHO_ERR_HIP;
             if (info[0] < 0 || info[0] > c.Pmax) return NACHO_ERR_INVALID_ARG;   // no call has run on ws
+            if (info[3]) return NACHO_ERR_HIP;                                   // the last one came to nothing
             w = c.parts;
             Pe = info[0];
             need = c.bytes;
@@ -789,7 +797,8 @@ static int32_t dcsr_product(const nacho_tensor *ops, int32_t k, int32_t dtype, i
                      w.fields, s) != hipSuccess)
         return NACHO_ERR_HIP;
     profile_mark("spmul_merge");
-    if (launch_compact_rows(w.remap, w.pos_full, w.counts, o, w.compact_state, s) != hipSuccess) return NACHO_ERR_HIP;
+    if (launch_compact_rows(w.remap, w.pos_full, w.counts, w.info, o, w.compact_state, s) != hipSuccess)
+        return NACHO_ERR_HIP;
     profile_mark("rows_compact");
     return NACHO_OK;
 }
@@ -936,6 +945,13 @@ int32_t nacho_instrument(void *records, int64_t capacity)
     if (capacity < 0 || (capacity > 0 && !records)) return NACHO_ERR_INVALID_ARG;
     wave_log().rec = static_cast<WaveRecord *>(records);
     wave_log().capacity = records ? capacity : 0;
+    return NACHO_OK;
+}
+
+int32_t nacho_instrument_wait(int64_t workgroup)
+{
+    if (!kInstrument) return NACHO_ERR_UNSUPPORTED;
+    wait_runs_out() = workgroup;
     return NACHO_OK;
 }
 

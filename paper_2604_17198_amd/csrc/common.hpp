@@ -30,7 +30,8 @@ struct DevOperands {
     // Remapped operands only: their sizes are results of earlier kernels of the same call and are
     // read on the device.  dyn_head[0] = rows all operands store (the extent of the dense level),
     // dyn_head[1 + t] = entries operand t stores in them (the count of its compressed level);
-    // dyn_plan[0] = partitions of the remapped nest, dyn_plan[2] = its total cost.  The extents and
+    // dyn_plan[0] = partitions of the remapped nest, dyn_plan[2] = its total cost, dyn_plan[3] != 0: the row
+    // loop was abandoned (a wait ran out) and nothing of the remapped nest may be read.  The extents and
     // counts in lvl[][] are upper bounds then (what the launches are sized for).  NULL otherwise.
     const int32_t *dyn_head;
     const int64_t *dyn_plan;
@@ -254,5 +255,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Where the executing kernels of an instrumented build log their wavefronts (null otherwise).
 nacho::WaveLog &wave_log();
+// Instrumented build: the workgroup of the row loop of a DCSR product whose wait counts as run out (-1: none).
+int64_t &wait_runs_out();
 
 }  // namespace nacho_host

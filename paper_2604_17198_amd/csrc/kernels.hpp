@@ -156,14 +156,15 @@ int64_t compact_state_words(int64_t rows);
 // The row loop.  posn0: boundaries of a P0-way partition of the operands' level-0 coordinate arrays.  Also
 // plan[0..2] = {partitions of the remapped nest, intersected rows, remapped total cost}: capacity = entries one
 // partition may hold, round = resident workgroups of the chip (the count is rounded up to whole rounds when
-// P_min == 0), P_max = what the launches are sized for.
+// P_min == 0), P_max = what the launches are sized for.  plan[3], zero when the kernel starts, is set when a
+// workgroup's wait ran out: the kernels behind it then leave at once, *status is NACHO_ERR_HIP.
 hipError_t launch_remap_rows(const DevOperands &ops, int64_t P0, const int32_t *posn0, const RemapArrays &r,
                              unsigned long long *state, int64_t capacity, int64_t round, int64_t P_min, int64_t P_max,
                              int64_t *plan, int32_t *status, hipStream_t s);
 // Result rows that hold an entry: pos_full[0 .. head[0]] over the intersected rows -> out.pos0 / crd0 /
 // pos1 / counts (counts_in = {rows, nnz} of the remapped result).
 hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full, const int64_t *counts_in,
-                               const SpaddOut &out, unsigned long long *state, hipStream_t s);
+                               const int64_t *plan, const SpaddOut &out, unsigned long long *state, hipStream_t s);
 hipError_t launch_empty_result(const SpaddOut &out, int64_t *info, hipStream_t s);
 
 // ---- measurement aids: kernels of known traffic (streaming read, copy, independent gathers) ----

@@ -401,7 +401,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         // the number of partitions is a result of earlier kernels of the call: the launch is sized for
         // an upper bound and the workgroups past the last partition have nothing to do
         P = arg_ptr->ops.dyn_plan[0];
-        if ((int64_t)blockIdx.x >= P) return;
+        if ((int64_t)blockIdx.x >= P || arg_ptr->ops.dyn_plan[3]) return;      // (nor after an abandoned row loop)
     }
     typedef Shape<KeyT, T, kSmall> S;
     constexpr int D = FMT == SPADD_VECTOR ? 1 : (FMT == SPADD_CSF3 ? 3 : 2);

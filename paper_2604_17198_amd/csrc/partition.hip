@@ -76,6 +76,7 @@ partition_kernel(DevOperands ops, int64_t cost_scale, int64_t P, int64_t grain,
 {
     clear.run((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
     if (ops.dyn_plan) {                      // sizes left on the device by earlier kernels of the call
+        if (ops.dyn_plan[3]) return;         // (the row loop was abandoned)
         P = ops.dyn_plan[0];
         total_unscaled = ops.dyn_plan[2];
     }

@@ -78,6 +78,7 @@ __device__ inline bool look_back(unsigned long long *state, int64_t p, int own, 
 struct RowArrays {
     int32_t k;
     const int32_t *crd0[NACHO_MAX_OPERANDS], *pos1[NACHO_MAX_OPERANDS];
+    int64_t runs_out;                                  // (instrumented build) the workgroup whose wait counts as run out
 };
 
 // What the kernels after the row loop need to know, left where they can read it: the number of
@@ -225,22 +226,22 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
         const bool ok = look_back(state + (int64_t)v * P0, p, own(v), base);
         if (lane == 0) {
             s_base[v] = base;
-            if (!ok) s_fail = 1;
+            if (!ok || (kInstrument && p == in.runs_out)) s_fail = 1;
         }
     }
     __syncthreads();
-    if (s_fail) {                                      // (a workgroup before this one never published)
+    const int row0 = s_base[0];
+    // (rows past the workspace: only of operands whose rows are not sorted, where partitions can overlap)
+    if (s_fail || row0 + m > r.stride) {
+        // A workgroup before this one had not published in time.  This one's rows are missing then, whatever the others
+        // find (its own counts are published, and the one it waited for may still come), so the kernels after the row loop
+        // are told to leave: plan[3] was cleared at the start of the call.
         if (tid == 0) {
-            atomicMin(status, (int32_t)NACHO_ERR_HIP);
-            if (p == P0 - 1) {
-                for (int v = 0; v <= k; ++v) r.head[v] = 0;
-                for (int t = 0; t < k; ++t) r.cost[(int64_t)t * (r.stride + 1)] = 0;
-                rule.write(0, 0, plan);
-            }
+            atomicMin(status, (int32_t)(s_fail ? NACHO_ERR_HIP : NACHO_ERR_INVALID_ARG));
+            plan[3] = 1;
         }
         return;
     }
-    const int row0 = s_base[0];
 #pragma unroll
     for (int u = 0; u < kEach; ++u)
         if (tid * kEach + u < m) r.rows[row0 + tid * kEach + u] = s_crd[s_item[tid * kEach + u]];
@@ -280,11 +281,13 @@ constexpr int kKeepItems = 8, kKeepTile = kScanThreads * kKeepItems;
 
 __global__ void __launch_bounds__(kScanThreads)
 compact_rows_kernel(const int32_t *__restrict__ rows, const int32_t *__restrict__ pos_full, const int32_t *__restrict__ head,
-                    const int64_t *__restrict__ counts_in, SpaddOut out, unsigned long long *__restrict__ state)
+                    const int64_t *__restrict__ counts_in, const int64_t *__restrict__ plan, SpaddOut out,
+                    unsigned long long *__restrict__ state)
 {
     __shared__ int s_count[kScanWaves], s_base, s_fail;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE;
     const int64_t tile = blockIdx.x;
+    if (plan[3]) return;                               // (the row loop was abandoned)
     const int M = head[0];                             // (the launch is sized for an upper bound)
     if (tile > 0 && tile * kKeepTile >= M) return;
     const int first = (int)tile * kKeepTile + tid * kKeepItems;
@@ -348,7 +351,7 @@ __global__ void empty_result_kernel(SpaddOut out, int64_t *info)
         out.counts[0] = 0;
         out.counts[1] = 0;
         *out.status = NACHO_OK;
-        info[0] = info[1] = info[2] = 0;
+        info[0] = info[1] = info[2] = info[3] = 0;
     }
 }
 
@@ -363,6 +366,7 @@ hipError_t launch_remap_rows(const DevOperands &ops, int64_t P0, const int32_t *
 {
     RowArrays rows;
     rows.k = ops.k;
+    rows.runs_out = nacho_host::wait_runs_out();
     for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) {
         rows.crd0[t] = t < ops.k ? ops.lvl[t][0].crd : nullptr;
         rows.pos1[t] = t < ops.k ? ops.lvl[t][1].pos : nullptr;
@@ -374,11 +378,11 @@ hipError_t launch_remap_rows(const DevOperands &ops, int64_t P0, const int32_t *
 }
 
 hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full, const int64_t *counts_in,
-                               const SpaddOut &out, unsigned long long *state, hipStream_t s)
+                               const int64_t *plan, const SpaddOut &out, unsigned long long *state, hipStream_t s)
 {
     // (over the upper bound of the rows; tiles past head[0] leave at once)
     hipLaunchKernelGGL(compact_rows_kernel, dim3((unsigned)compact_state_words(r.stride)), dim3(kScanThreads), 0, s, r.rows,
-                       pos_full, r.head, counts_in, out, state);
+                       pos_full, r.head, counts_in, plan, out, state);
     return hipGetLastError();
 }
 

@@ -200,6 +200,48 @@ def test_repeated_rows_are_reported(copies):
             assert int(out.status[0]) == -1
 
 
+@pytest.mark.parametrize("workgroup", [0, 1, 4])
+def test_a_wait_that_runs_out_ends_the_call(workgroup):
+    """Instrumented library: one workgroup of the row loop (the first, one in the middle, the last) gives up although its
+    own counts are out.  No kernel behind it may use the row list it left unfinished; the next call is whole again."""
+    rng = np.random.default_rng(77)
+    shape = (20000, 500)
+    mats = []
+    for t in range(2):
+        rows = np.sort(rng.choice(shape[0], 2500, replace=False))          # 5 partitions of 1024 rows
+        rr = np.repeat(rows, 4)
+        cc = np.concatenate([np.sort(rng.choice(shape[1], 4, replace=False)) for _ in rows])
+        mats.append(_mat(np.stack([rr, cc], axis=1), rng.uniform(0.5, 1.5, rr.shape[0]).astype(np.float32)))
+    ref = oracle.spmul_dcsr(mats)
+    n = ref["crd1"].shape[0]
+    assert n > 0
+    nb.select_library(True)
+    try:
+        ops = [nb.dcsr(dev(m["pos0"]), dev(m["crd0"]), dev(m["pos1"]), dev(m["crd1"]), *shape, dev(m["val"])) for m in mats]
+        # (what an unwritten workspace holds: positions far outside of every array)
+        ws = torch.full((nb.workspace_bytes(nb.OP_SPMUL, ops, nb.F32),), 0x7f, dtype=torch.uint8, device="cuda")
+        print(f"spmul dcsr wait of workgroup {workgroup} runs out", flush=True)
+        for gives_up in (True, False, True):
+            out = nb.SparseOut("dcsr", 2500, 10000, torch.float32, "cuda")
+            for a in (out.crd0, out.pos1, out.crd1):
+                a.fill_(-9)
+            nb.instrument_wait(workgroup if gives_up else -1)
+            nb.nacho_spmul_k(ops, out, ws=ws)
+            torch.cuda.synchronize()
+            if gives_up:
+                assert int(out.status[0]) == -5
+                assert all(bool((a == -9).all()) for a in (out.crd0, out.pos1, out.crd1))
+                with pytest.raises(nb.NachoError):
+                    nb.workspace_parts(nb.OP_SPMUL, ops, nb.F32, ws)
+            else:
+                assert int(out.status[0]) == 0 and int(out.counts[1]) == n
+                assert np.array_equal(out.crd1.cpu().numpy()[:n], ref["crd1"])
+                assert tol_ok(out.val.cpu().numpy()[:n], ref["val"], ref["abs"], TOL[np.float32]).all()
+    finally:
+        nb.instrument_wait(-1)
+        nb.select_library(False)
+
+
 def test_workspace_too_small_and_reuse():
     rng = np.random.default_rng(12)
     shape = (100, 100)
