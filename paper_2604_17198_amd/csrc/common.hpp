@@ -55,6 +55,13 @@ __host__ __device__ inline int64_t equal_query(int64_t p, int64_t total, int64_t
     return p * q + (p * r) / P;
 }
 
+// Partitions of `grain` units that start before the place `at` of a row's (or the matrix's) non-zeros: at / grain
+// rounded up, 0 <= at < 2^31 (unsigned: at + grain may lie past 2^31).
+__host__ __device__ inline int shares_before(int at, int grain)
+{
+    return (int)(((unsigned)at + (unsigned)grain - 1u) / (unsigned)grain);
+}
+
 __device__ inline int lane_id() { return (int)(threadIdx.x & (NACHO_WAVE - 1)); }
 
 // Orders the LDS traffic of ONE wavefront: writes issued before it are visible

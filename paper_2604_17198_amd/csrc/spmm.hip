@@ -282,7 +282,7 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
     if (first) {
         // the run ends with the last partition that starts inside the row
         const int row_end = pos[r + 1];
-        if (grain > 0) e = (row_end - pos[0] + grain - 1) / grain;
+        if (grain > 0) e = shares_before(row_end - pos[0], grain);
         else {
             int lo = p + 1, hi = P;                    // the first partition that starts at or behind the row's end
             while (lo < hi) {

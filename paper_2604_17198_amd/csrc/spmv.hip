@@ -75,7 +75,7 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         const int r = kFused ? r0 : coord[2 * p];
         if (r < n_rows) {
             const int base = pos[0];
-            const int first = ((pos[r] - base) + grain - 1) / grain;
+            const int first = shares_before(pos[r] - base, grain);
             const int end = (pos[r + 1] - base) / grain;
             if (end - first >= 4 && p >= first && p < end) {
                 const int j = p & 7;
@@ -128,30 +128,27 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     // instruction fall into few cache lines of x (columns are sorted).  All
     // streamed loads are issued before the first gather, all gathers before the
     // first LDS store, so one wavefront keeps its whole window in flight.
+    // (places are compared, not positions: the last ones may lie past 2^31)
     constexpr int kIter = G / NACHO_WAVE;
+    const int left = n1 - n0 - lane;
     int c[kIter];
     T v[kIter];
 #pragma unroll
     for (int j = 0; j < kIter; ++j) {
-        const int idx = n0 + j * NACHO_WAVE + lane;
         c[j] = 0;
         v[j] = T(0);
-        if (idx < n1) {
+        if (j * NACHO_WAVE < left) {
+            const int idx = n0 + j * NACHO_WAVE + lane;
             c[j] = __builtin_nontemporal_load(crd + idx);
             v[j] = __builtin_nontemporal_load(val + idx);
         }
     }
     T xv[kIter];
 #pragma unroll
-    for (int j = 0; j < kIter; ++j) {
-        const int idx = n0 + j * NACHO_WAVE + lane;
-        xv[j] = idx < n1 ? x[c[j]] : T(0);
-    }
+    for (int j = 0; j < kIter; ++j) xv[j] = j * NACHO_WAVE < left ? x[c[j]] : T(0);
 #pragma unroll
-    for (int j = 0; j < kIter; ++j) {
-        const int idx = n0 + j * NACHO_WAVE + lane;
-        if (idx < n1) prod[idx - a0] = v[j] * xv[j];
-    }
+    for (int j = 0; j < kIter; ++j)
+        if (j * NACHO_WAVE < left) prod[j * NACHO_WAVE + lane] = v[j] * xv[j];
     __syncthreads();
 
     for (int rb = 0; rb < nrows; rb += RBLK) {
@@ -265,7 +262,7 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
         // (long runs: a row of a million non-zeros has 2000 carries) 32 chunks of 64 in
         // flight, added in a fixed order
         const int base = pos[0];
-        int last = ((pos[r_last + 1] - base) + grain - 1) / grain - 1;
+        int last = shares_before(pos[r_last + 1] - base, grain) - 1;
         if (last > P - 1) last = P - 1;
         T acc[8];
 #pragma unroll

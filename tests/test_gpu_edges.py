@@ -343,3 +343,21 @@ def test_merge_whole_rounds(need, partitions):
     n = int(a.counts[1])
     assert torch.equal(a.counts, b.counts) and int(a.status[0]) == 0 and int(b.status[0]) == 0
     assert torch.equal(a.crd1[:n], b.crd1[:n]) and torch.equal(a.val[:n], b.val[:n])
+
+
+def test_positions_up_to_the_last_one():
+    """2^31 - 1 stored non-zeros, the most a call takes: positions of the last partitions and ends of the last rows lie
+    less than a partition below 2^31.  Every sum is a whole number below 2^24: exact in any order."""
+    rows, cols = 2048, 1 << 20
+    nnz = rows * cols - 1
+    pos = torch.arange(rows + 1, dtype=torch.int64, device="cuda").mul_(cols).clamp_(max=nnz).to(torch.int32)
+    crd = torch.arange(cols, dtype=torch.int32, device="cuda").repeat(rows)[:nnz]
+    op = nb.csr(pos, crd, rows, cols, torch.ones(nnz, dtype=torch.float32, device="cuda"))
+    j = torch.arange(cols, device="cuda")
+    for n in (0, 4):                                       # SpMV, SpMM
+        B = ((j[:, None] + torch.arange(max(n, 1), device="cuda")) % 7).to(torch.float32)
+        want = B.double().sum(0).expand(rows, -1).clone()
+        want[-1] -= B[-1].double()                         # (the last row ends one column early)
+        print(f"positions to the last one n={n}", flush=True)
+        got = nb.nacho_spmm(op, B) if n else nb.nacho_spmv(op, B[:, 0].contiguous())[:, None]
+        assert torch.equal(got.double(), want)
