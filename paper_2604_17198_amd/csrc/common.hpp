@@ -136,6 +136,27 @@ __device__ inline double last_lane(double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// The n lowest bits of a 64-bit word (n: this lane's; below 0: none, above 64: all), built from 32-bit shifts.
+// A 64-bit shift whose amount is in the LAST vector register a kernel was given takes the amount of another
+// wavefront now and then (measured: some rows' pos of a CSR product, another wavefront's every time), and which
+// register that is hangs on the compiler, so no lane shifts 64 bits by an amount of its own.
+__device__ inline unsigned long long low_bits(int n)
+{
+    const unsigned lo = n >= 32 ? ~0u : (n > 0 ? (1u << n) - 1u : 0u);
+    const unsigned hi = n >= 64 ? ~0u : (n > 32 ? (1u << (n - 32)) - 1u : 0u);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Bit `at` (this lane's) of a mask every lane agrees on, without such a shift.  (The compiler would turn the choice
+// between the halves of one word into one; it does not know that these two belong together.)
+__device__ inline bool bit_at(unsigned long long mask, int at)
+{
+    const unsigned lo = (unsigned)mask;
+    unsigned hi = (unsigned)(mask >> 32);
+    asm("" : "+s"(hi));
+    return (((at < 32 ? lo : hi) >> (at & 31)) & 1u) != 0u;
+}
+
 // Least position in [lo, hi) whose coordinate is >= x; hi if there is none.
 __device__ inline int lower_bound_global(const int32_t *__restrict__ crd, int lo, int hi, int64_t x)
 {
@@ -173,13 +194,13 @@ __device__ inline void rows_holding(const int32_t *__restrict__ pos, int n_rows,
     constexpr int G = NACHO_WAVE / 2;
     const int lane = lane_id(), sub = lane & (G - 1);
     const int q = lane < G ? qa : qb;
+    const unsigned long long half = lane < G ? 0xffffffffull : 0xffffffff00000000ull;
     int lo = 0, hi = n_rows;                           // the number of rows that end at or before q
     while (__ballot(lo < hi) != 0ull) {
         const int step = (hi - lo + G - 1) / G;
         const int at = lo + (sub + 1) * step - 1;
         const bool before = lo < hi && at < hi && pos[at + 1] <= q;        // (a prefix of the half)
-        const unsigned long long mask = __ballot(before);
-        const int n = __popc(lane < G ? (unsigned)mask : (unsigned)(mask >> 32));
+        const int n = __popcll(__ballot(before) & half);
         if (lo < hi) {
             const int lo_new = lo + n * step, at_next = lo + (n + 1) * step - 1;
             hi = n < G && at_next < hi ? at_next : hi;

@@ -463,6 +463,7 @@ __device__ inline int row_starts(const DevOperands &ops, int hi, int64_t x)
 {
     constexpr int G = NACHO_WAVE / (K <= 2 ? 2 : (K <= 4 ? 4 : 8));
     const int lane = lane_id(), sub = lane & (G - 1), first = lane - sub, t = lane / G;
+    const unsigned long long group = low_bits(first + G) & ~low_bits(first);
     const int32_t *rows = ops.lvl[t < ops.k ? t : 0][0].crd;
     int lo = 0;
     while (__ballot(lo < hi) != 0ull) {
@@ -470,8 +471,7 @@ __device__ inline int row_starts(const DevOperands &ops, int hi, int64_t x)
         const int step = (hi - lo + G - 1) / G;
         const int at = lo + (sub + 1) * step - 1;
         const bool before = lo < hi && at < hi && (int64_t)rows[at] < x;
-        const unsigned long long mask = __ballot(before) >> first;
-        const int n = __popcll(mask & (G == 64 ? ~0ull : (1ull << G) - 1ull));
+        const int n = __popcll(__ballot(before) & group);
         if (lo < hi) {
             const int lo_new = lo + n * step, at_next = lo + (n + 1) * step - 1;
             hi = n < G && at_next < hi ? at_next : hi;

@@ -142,7 +142,7 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             const unsigned long long empty = __ballot(is_empty);
             if (empty == 0ull) continue;
             for (int i = g; i < NACHO_WAVE; i += NG)
-                if ((i < 32 ? (unsigned)empty : (unsigned)(empty >> 32)) >> (i & 31) & 1u) {
+                if (bit_at(empty, i)) {
 #pragma unroll
                     for (int c = 0; c < CPL; ++c)
                         if (mine[c]) *reinterpret_cast<PM *>(C + (int64_t)(z + i) * ldc + col[c]) = P(T(0));
@@ -233,7 +233,7 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
 #pragma unroll
     for (int c = 0; c < CPL; ++c) s_head[c * NACHO_WAVE + lane] = head[c];
     __syncthreads();
-    auto starts = [&](int h) { return (((h * W) < 32 ? (unsigned)started : (unsigned)(started >> 32)) >> ((h * W) & 31) & 1u) != 0u; };
+    auto starts = [&](int h) { return bit_at(started, h * W); };
     auto add_heads = [&](P (&x)[CPL]) {
         for (int h = g + 1; h < NG; ++h) {
 #pragma unroll

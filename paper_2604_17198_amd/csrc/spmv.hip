@@ -230,7 +230,7 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
     const bool head = r >= 0 && r != before;           // first carry of its row
     const bool first_here = r != before || lane == 0;  // first lane of its segment in this wavefront
     const unsigned long long starts = __ballot(first_here);
-    const unsigned long long upto = lane == NACHO_WAVE - 1 ? ~0ull : ((2ull << lane) - 1ull);
+    const unsigned long long upto = low_bits(lane + 1);
     const int start = 63 - __clzll((long long)(starts & upto));
     const unsigned long long after = starts & ~upto;
     const int end = after ? __ffsll((long long)after) - 2 : NACHO_WAVE - 1;   // last lane of the segment
@@ -244,9 +244,7 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
     add(dpp_moved<0x142, 0xa>(v), start < (lane & ~15));                   // row_bcast:15 into rows 1 and 3
     add(dpp_moved<0x143, 0xc>(v), start < NACHO_WAVE / 2);                 // row_bcast:31 into rows 2 and 3
     const unsigned long long heads = __ballot(head);
-    auto owned_from = [&](int first) {                 // the run that starts in lane `first` starts in this wavefront
-        return (((first < 32 ? (unsigned)heads : (unsigned)(heads >> 32)) >> (first & 31)) & 1u) != 0u;
-    };
+    auto owned_from = [&](int first) { return bit_at(heads, first); };     // the run from that lane on starts in this wavefront
     const bool owned = owned_from(start);
     // a run that reaches the last lane may go on in the next wavefronts
     const int r_last = __builtin_amdgcn_readlane(r, NACHO_WAVE - 1);
