@@ -28,12 +28,16 @@ namespace {
 // else hides it: 13.5 us with one product at a time and rows of up to 191 of them, 5 us like this).
 constexpr int kLongRow = 48;
 
+// Rows whose zeros one wavefront of a call without a partition kernel may have to write: one batch of loads.
+constexpr int kZeroRows = 256;
+
 // kDealt: the partitions come from fixed-grain queries (grain > 0) and are dealt out by XCD; the
 // instantiation without it serves arbitrary partition tables (caller's P, the row-aware cost).
 // kFused (with kDealt): there is no partition table; the wavefront finds its own two boundaries, the
 // search of Algorithm 1 for one CSR operand (Section 4.2.2: the row with pos[r] <= Q < pos[r + 1], at
 // position Q) with the fixed-grain queries Q_b = min(b * grain, nnz), as a 64-ary search over pos.
-// kTable (with kFused): the wavefront stores its boundary in the partition table and writes the zeros of its empty rows.
+// kTable (with kFused): the wavefront stores its boundary in the partition table, and the zeros of empty rows, wherever
+// they lie, are shared out evenly over the wavefronts (at most kZeroRows rows each).
 template <typename T, int G, int RBLK, bool kDealt, bool kFused = false, bool kTable = false>
 __global__ void __launch_bounds__(NACHO_WAVE)
 spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd,
@@ -146,6 +150,20 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     T xv[kIter];
 #pragma unroll
     for (int j = 0; j < kIter; ++j) xv[j] = j * NACHO_WAVE < left ? x[c[j]] : T(0);
+    if (kTable) {
+        const int share = (n_rows + (int)gridDim.x - 1) / (int)gridDim.x;
+        const int z = (int)blockIdx.x * share + lane, z_end = min((int)(blockIdx.x + 1) * share, n_rows);
+        int a[kZeroRows / NACHO_WAVE], b[kZeroRows / NACHO_WAVE];
+#pragma unroll
+        for (int u = 0; u < kZeroRows / NACHO_WAVE; ++u) {
+            a[u] = 0;
+            b[u] = 1;
+            if (z + u * NACHO_WAVE < z_end) { a[u] = pos[z + u * NACHO_WAVE]; b[u] = pos[z + u * NACHO_WAVE + 1]; }
+        }
+#pragma unroll
+        for (int u = 0; u < kZeroRows / NACHO_WAVE; ++u)
+            if (a[u] == b[u]) y[z + u * NACHO_WAVE] = T(0);
+    }
 #pragma unroll
     for (int j = 0; j < kIter; ++j)
         if (j * NACHO_WAVE < left) prod[j * NACHO_WAVE + lane] = v[j] * xv[j];
@@ -157,15 +175,12 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             __syncthreads();
             for (int i = lane; i <= nr; i += NACHO_WAVE) spos[i] = pos[r0 + rb + i];
             __syncthreads();
-            // A block of rows without entries: empty rows are zero already (the partition
-            // kernel wrote them), so the wavefront steps over them, however many there are.
+            // A block of rows without entries: their zeros are written elsewhere (by the partition
+            // kernel, or above), so the wavefront steps over them, however many there are.
             const int q = spos[0];
             if (q == spos[nr]) {
-                const int next = q >= n1 ? nrows : first_row_past(pos, r0 + rb + nr, r0 + nrows, q) - r0;
-                if (kTable)
-                    for (int i = rb + lane; i < next; i += NACHO_WAVE) y[r0 + i] = T(0);
                 if (q >= n1) break;                     // every product of the partition is summed
-                rb = next - RBLK;
+                rb = first_row_past(pos, r0 + rb + nr, r0 + nrows, q) - r0 - RBLK;
                 continue;
             }
         }
@@ -323,11 +338,12 @@ int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32
 // Small calls do without a partition kernel.  Its place in the stream (a launch and 3 us) is a third of what such a
 // call takes, while the wavefronts find their rows in two or three rounds of loads that hit the cache (40,000
 // non-zeros: 9.3 us in all; 1M: 16.8 to 15.4; 5M: 33.2 to 32.4).  Past a thousand partitions only while x fits an L2:
-// partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 309 to 469 us without).  Not so
-// many rows that one wavefront could be left with zeroing more than some hundred thousand of them.
+// partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 309 to 469 us without).  With more
+// rows than the wavefronts can look after in one batch of loads each the partition kernel writes the zeros, a row a
+// thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).
 bool spmv_whole(int64_t P, int64_t n_rows, int64_t x_bytes)
 {
-    return n_rows <= (1 << 17) && (P <= 1024 || (P <= 8192 && x_bytes <= (4 << 20)));
+    return n_rows <= (1 << 17) && n_rows <= P * kZeroRows && (P <= 1024 || (P <= 8192 && x_bytes <= (4 << 20)));
 }
 
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,

@@ -141,6 +141,28 @@ def test_spmv_calls_without_a_partition_kernel(parts, rows, cols):
     part._compare(got, ref, "limits")
 
 
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("parts,rows", [(1, 256), (1, 257), (3, 768), (3, 769), (1, 1 << 17), (512, 1 << 17), (512, (1 << 17) + 1)])
+@pytest.mark.parametrize("first", [0, 0.5, 1])
+def test_spmv_rows_per_partition(parts, rows, first, dtype):
+    """All non-zeros at the first, the middle or the last rows: no wavefront is left with the zeros of more than 256 of the
+    others, with more rows a partition kernel writes them."""
+    rng = np.random.default_rng(parts + rows)
+    grain = 512 if dtype == np.float64 else 1024
+    nnz, full = parts * grain - 7, max(1, parts // 4)
+    lens = np.full(full, nnz // full)
+    lens[0] += nnz - lens.sum()
+    r0 = int(first * (rows - full))
+    A = _matrix(rng, np.concatenate([np.zeros(r0, np.int64), lens, np.zeros(rows - full - r0, np.int64)]), 9000, dtype)
+    nb.profile_enable(True)
+    try:
+        spmv._check(A, rng.uniform(-1, 1, 9000).astype(dtype), 0, "rows per partition")
+        kernels = [name for name, _ in nb.profile_read()]
+    finally:
+        nb.profile_enable(False)
+    assert ("partition" in kernels) == (rows > min(256 * parts, 1 << 17))
+
+
 # ---- partition search ---------------------------------------------------------
 def test_partition_two_vectors():
     """Two operands are searched by splits of the merge path: lengths and spreads far apart, ties, nothing interleaved."""
