@@ -376,7 +376,7 @@ typedef const __attribute__((address_space(4))) MergeArgs *ArgPtr;
 // kSearch (sparse vectors): there is no partition kernel before this one; wavefronts 0 and 1 of the
 // workgroup search its two boundaries themselves (Algorithm 1, equal-share queries) and store them in
 // the partition table on the way -- the search fused into the executing kernel.
-// A partition whose rows do not fit the row field of its keys is merged without keys (`far` below).
+// A partition whose rows do not fit the row field of its keys is merged by searches (`far` below).
 template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch>
 __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, KeyT, kSmall> &w, const DevOperands &search_ops,
                                                 const WaveStamp &stamp)
@@ -404,6 +404,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     constexpr int R = S::kIpt, NB = S::kBlocks;
     constexpr int NR = K <= 2 ? 2 : (K <= 4 ? 4 : 8);     // runs of the merge tree (a power of two)
     constexpr KeyT kSentinel = ~KeyT(0);
+    constexpr uint16_t kPastKey = 0xffff;
 
     const int tid = threadIdx.x;
     const int lane = lane_id();
@@ -688,10 +689,17 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                         }
                         field = ((KeyT)(uint32_t)(up - row0) << jb) | (KeyT)(uint32_t)id;
                     } else field = (KeyT)(uint32_t)(up - row0);
-                    if ((uint32_t)(up - row0) >= limit) w.overflow = 1u;
-                    mark_start(sb + s - q, field);
+                    const int at = sb + s - q;
+                    mark_start(at, field);
                     // (remapped operands: how far the row is stored from where it is counted)
-                    if (kMapped) cols[sb + s - q] = (uint32_t)(id - a);
+                    if (kMapped) cols[at] = (uint32_t)(id - a);
+                    if ((uint32_t)(up - row0) >= limit) {
+                        // past the key: the whole field over the column, and a mark that no other field has
+                        w.overflow = 1u;
+                        if (!kWide || kCsf) w.order[at] = kPastKey;
+                        if (!kWide) cols[at] = (uint32_t)field;
+                        else if (kCsf) { cols[at] = (uint32_t)(up - row0); wide_rows[at] = (uint32_t)id; }
+                    }
                 };
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u)
@@ -710,6 +718,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             // the sentinel of a run: a row start whose row field is all ones, as its column is
             if (tid < K) mark_start(sb_v + len_v, kSentinel);
             __syncthreads();
+            far = __builtin_amdgcn_readfirstlane((int)w.overflow) != 0 && !broken;
         }
         // Keys.  A wavefront takes R blocks of 64 words; the words' row starts are in its lanes, and where the
         // latest start before a block lies goes from block to block in a scalar register.
@@ -745,7 +754,29 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if (!kWide) return (KeyT)w.order[e];
             return kCsf ? (KeyT)wide_rows[e] | (KeyT)w.order[e] << (kWide ? 32 : 0) : (KeyT)wide_rows[e];
         };
-        if constexpr (!kWide && kWindow && kDirect) {
+        if (kWindow && far) {
+            // (the keys are put together in rank_far)
+            if constexpr (!kWide) {
+#pragma unroll 1
+                for (int j = 0; j < R && word0 + j * NACHO_WAVE < words; ++j) {
+                    const int e = start_of(j);         // (a row start gets the field it holds)
+                    cols[word0 + j * NACHO_WAVE + lane] = w.order[e] == kPastKey ? cols[e] : w.order[e];
+                }
+            } else {
+                KeyT field[R];
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const int e = start_of(j);
+                    field[j] = kCsf && w.order[e] == kPastKey ? ((KeyT)cols[e] << jb) | (KeyT)wide_rows[e] : field_at(e);
+                }
+                lds_barrier();
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const int s = word0 + j * NACHO_WAVE + lane;
+                    if (s < words) keys[s] = field[j];
+                }
+            }
+        } else if constexpr (!kWide && kWindow && kDirect) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const int s = word0 + j * NACHO_WAVE + lane;
@@ -803,140 +834,142 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             }
         }
         __syncthreads();
-        far = __builtin_amdgcn_readfirstlane((int)w.overflow) != 0 && !broken;
+        if constexpr (kCoo) far = __builtin_amdgcn_readfirstlane((int)w.overflow) != 0 && !broken;
     }
 
     // ---- 1b. rows too far apart for the keys ------------------------------------------
-    // The partition is merged without keys: every entry finds, in the other operands' segments, the entries before it
-    // by binary searches over the operands' own arrays, and with them its place and whether it is a head.  Works for
-    // rows, columns and slices of any extent, in one pass and without more LDS or registers than the merge by keys.
-    // It takes some thirty dependent loads (cache hits, most of them) per entry and operand; the layout of the keys is
-    // chosen so that few partitions come here (merge_fields).
-    auto lower = [](Ints a, int lo, int hi, int x) {           // the first position of [lo, hi) whose coordinate is >= x
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo) >> 1);
-            if (a[mid] < x) lo = mid + 1; else hi = mid;
-        }
-        return lo;
+    // The keys of such a partition are its row fields, which one word holds for any rows, slices and fibres (merge_fields), and
+    // below them as many of the column's upper bits as there is room for.  Every entry searches its place in the other
+    // operands' runs: a binary search in LDS and, only among words that equal its own, one in the operand's columns.
+    // (Merging pairs of words would take a second word per entry, for which there is no LDS.  Searching rows and columns in
+    // the operands' own arrays was bound by the gathers a compute unit's L1 takes, searching the columns of a long row by
+    // their latency, unrolled searches by fetching their instructions, which no other partition of the XCD has run: two
+    // matrices of 2M entries, eight of their 718 partitions far: 130, 98, 85 and, like this, 67 us a call.)  Values and
+    // output go the way of every partition, but for the columns, which are stored once more in full.  The layout of the
+    // keys is chosen so that few partitions come here.
+    int row_at = cb;                           // the row field of a key starts at this bit
+    if (far) {
+        const int last = (int)row_extent() - 1, next = table_coord(p + 1, 0);
+        const uint32_t most = (uint32_t)((next < last ? next : last) - row0);
+        const int room = 8 * (int)sizeof(KeyT) - jb - (most > 0u ? 32 - __builtin_clz(most) : 0);
+        row_at = room < 0 ? 0 : (room < cb ? room : cb);
+    }
+    auto row_field = [&](KeyT key) -> KeyT { return key >> row_at; };
+    // (remapped operands) how far an entry of operand t is stored from where it is counted
+    auto shift_of = [&](int t, KeyT field) -> int {
+        if constexpr (!kMapped) return 0;
+        const int row = row0 + (int)(uint32_t)field;
+        return global_ptr<int32_t>(w.srow[t])[row] - global_ptr<int32_t>(w.spos[t])[row];
     };
-    auto holder = [](Ints pos, int lo, int hi, int q) {        // the segment of [lo, hi) that position q lies in
-        --hi;
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo + 1) >> 1);
-            if (pos[mid] <= q) lo = mid; else hi = mid - 1;
-        }
-        return lo;
+    auto column_at = [&](int t, int s, KeyT field) -> int {
+        if constexpr (kMapped) return global_ptr<int32_t>(w.scol[t])[s + shift_of(t, field)];
+        int c = 0;
+#pragma unroll 1
+        for (int u = 0; u < k; ++u)
+            if (t == u) c = crd_of(u, D - 1)[of(q_v, u) + (s - of(sb_v, u))];
+        return c;
     };
-    auto starts_of = [&](int t) { return ints(arg_ptr->ops.start[t]); };
+    constexpr int KB = (int)sizeof(KeyT);
+    const int place0 = wave * (R * NACHO_WAVE);    // a wavefront's places: place0 + j * 64 + lane, j < R
+    const int block0 = wave * R;
+    const int two_at = K <= 2 ? of(sb_v, K - 1) * KB : 0;      // two operands: the second one's words start here
+    auto word_of = [&](int o, int &t) -> int {     // the staged word an order word names, and its operand
+        t = K <= 2 ? (K == 2 && o >= two_at ? 1 : 0) : o >> 13;
+        return K <= 2 ? o / KB : o & 0x1fff;
+    };
     auto rank_far = [&]() {
         if constexpr (D >= 2) {
+#pragma unroll 1
+            for (int u = 0; u < k; ++u) {
+                const int q = of(q_v, u), sb = of(sb_v, u), len = of(len_v, u);
+#pragma unroll 4
+                for (int i = tid; i < len; i += kThreads) {
+                    KeyT field;
+                    if constexpr (kCoo) field = (KeyT)(uint32_t)(crd_of(u, 0)[q + i] - row0);
+                    else field = keys[sb + i];
+                    const uint32_t col = (uint32_t)crd_of(u, D - 1)[q + i + shift_of(u, field)];
+                    keys[sb + i] = (field << row_at) | (KeyT)(row_at > 0 ? col >> (cb - row_at) : 0u);
+                }
+            }
             // (unsorted or repeated coordinates can give two entries one place and another place none: every order
             // word names an entry before the searches write theirs)
             for (int m = tid; m < n; m += kThreads)
                 w.order[m] = (uint16_t)(K <= 2 ? first_word * (int)sizeof(KeyT) : (live_t << 13 | first_word));
             __syncthreads();
 #pragma unroll 1
-            for (int t = 0; t < k; ++t) {
-                const int q_t = of(q_v, t), len_t = of(len_v, t), sb_t = of(sb_v, t);
-                const int ilo_t = of(ilo_v, t), ihi_t = of(ihi_v, t);
-                const int up_lo_t = of(up_lo_v, t), up_hi_t = of(up_hi_v, t);
+            for (int j = 0; j < R && word0 + j * NACHO_WAVE < words; ++j) {
+                int s = word0 + j * NACHO_WAVE + lane;
+                bool valid;
+                const int t = run_of(s, valid);
+                const KeyT key = keys[s];
+                int place = 0;
+                bool head = true;
 #pragma unroll 1
-                for (int i = tid; i < len_t; i += kThreads) {
-                    const int q = q_t + i;
-                    // the entry's coordinates: row (slice), fibre of a tensor, column
-                    int seg = 0, up = 0, row, fibre = 0, shift = 0;
-                    if constexpr (kCoo) row = crd_of(t, 0)[q];
-                    else {
-                        seg = holder(pos_of(t, D - 1), ilo_t, ihi_t, q);
-                        row = seg;
-                        if (FMT != SPADD_CSR) row = crd_of(t, D - 2)[seg];
-                        if (kMapped) shift = starts_of(t)[seg] - pos_of(t, D - 1)[seg];
-                        if constexpr (kCsf) {
-                            fibre = row;
-                            up = holder(pos_of(t, 1), up_lo_t, up_hi_t + 1, seg);
-                            row = crd_of(t, 0)[up];
+                for (int u = 0; u < k; ++u) {
+                    const int first = of(sb_v, u), end = first + of(len_v, u);
+                    int at = s;                                    // the entries of u before this one: those in front of word `at`
+                    if (t != u && first < end) {
+                        at = first;
+                        // (four ways a step, as in merge_share)
+                        for (int step = 1 << ((31 - __builtin_clz((unsigned)(end - first))) & ~1); step > 0; step >>= 2) {
+                            KeyT x[3];
+                            int to[3];
+#pragma unroll
+                            for (int g = 0; g < 3; ++g) {
+                                to[g] = at + (g + 1) * step < end ? at + (g + 1) * step : end;
+                                x[g] = keys[to[g] - 1];
+                            }
+#pragma unroll
+                            for (int g = 0; g < 3; ++g) at = x[g] < key ? to[g] : at;
+                        }
+                        if (at < end && keys[at] == key) {
+                            // words that equal this one, as a rule one or two: steps that double, then halve
+                            const KeyT field = row_field(key);
+                            const int col = column_at(t, s, field);
+                            const Ints cols_u = crd_of(u, D - 1) + (of(q_v, u) - first + shift_of(u, field));
+                            bool up = true;
+                            for (int step = 1; step > 0;) {
+                                const int to = at + step;
+                                const bool before = to <= end && keys[to - 1] == key && cols_u[to - 1] < col;
+                                at = before ? to : at;
+                                up = up && before;
+                                step = up ? 2 * step : step >> 1;
+                            }
+                            if (u < t && at < end && keys[at] == key && cols_u[at] == col) { head = false; ++at; }
                         }
                     }
-                    const int col = crd_of(t, D - 1)[q + shift];
-                    int place = i;
-                    bool head = true, row_head = true, slice_head = true;
-#pragma unroll 1
-                    for (int u = 0; u < k; ++u) {
-                        const int q_u = of(q_v, u), end_u = q_u + of(len_v, u);
-                        if (q_u == end_u) continue;
-                        auto clamp = [&](int x) { return x < q_u ? q_u : (x > end_u ? end_u : x); };
-                        // [a, b): u's entries of the row (fibre), s0: where those of the slice start
-                        int a = q_u, b = end_u, s0 = q_u, at, shift_u = 0;
-                        if constexpr (kCoo) {
-                            while (a < b) {                    // (pairs)
-                                const int mid = a + ((b - a) >> 1), r = crd_of(u, 0)[mid];
-                                if (r < row || (r == row && crd_of(u, 1)[mid] < col)) a = mid + 1; else b = mid;
-                            }
-                            at = a;
-                            const bool same = u != t && at < end_u && crd_of(u, 0)[at] == row && crd_of(u, 1)[at] == col;
-                            if (u < t && same) { head = false; ++at; }
-                            place += u != t ? at - q_u : 0;
-                            continue;
-                        }
-                        const Ints pos = pos_of(u, D - 1);
-                        if (u == t) {
-                            a = clamp(pos[seg]);
-                            if constexpr (kCsf) s0 = clamp(pos[pos_of(t, 1)[up]]);
-                            row_head = row_head && a == q;
-                            slice_head = slice_head && s0 == q;
-                            continue;
-                        }
-                        int i_lo = of(ilo_v, u), i_hi = of(ihi_v, u), seg_u = row;
-                        bool stored = true;                    // does u store the row (fibre)
-                        if constexpr (kCsf) {
-                            const int up_hi = of(up_hi_v, u), up_u = lower(crd_of(u, 0), of(up_lo_v, u), up_hi + 1, row);
-                            stored = up_u <= up_hi && crd_of(u, 0)[up_u] == row;
-                            const int f_end = i_hi;
-                            if (up_u <= up_hi) {
-                                const int f = pos_of(u, 1)[up_u];
-                                s0 = clamp(pos[f]);
-                                i_lo = f > i_lo ? f : i_lo;
-                                if (stored) i_hi = pos_of(u, 1)[up_u + 1];
-                                i_hi = i_hi < f_end ? i_hi : f_end;
-                            } else {
-                                s0 = end_u;
-                                i_lo = i_hi;
-                            }
-                        }
-                        if constexpr (FMT != SPADD_CSR) {
-                            if (kCsf && !stored) seg_u = i_lo;
-                            else seg_u = lower(crd_of(u, D - 2), i_lo, i_hi, kCsf ? fibre : row);
-                            stored = stored && seg_u < i_hi && crd_of(u, D - 2)[seg_u] == (kCsf ? fibre : row);
-                        }
-                        a = clamp(pos[seg_u]);
-                        b = stored ? clamp(pos[seg_u + 1]) : a;
-                        if (kMapped) shift_u = starts_of(u)[seg_u] - pos[seg_u];
-                        at = lower(crd_of(u, D - 1) + shift_u, a, b, col);
-                        if (u < t && at < b && crd_of(u, D - 1)[at + shift_u] == col) { head = false; ++at; }
-                        row_head = row_head && at == a;
-                        slice_head = slice_head && at == s0;
-                        place += at - q_u;
-                    }
-                    w.order[place] = (uint16_t)(K <= 2 ? (sb_t + i) * (int)sizeof(KeyT) : (t << 13 | (sb_t + i)));
-                    keys[sb_t + i] = (KeyT)place;
-                    auto put_bit = [&](unsigned long long *at) {
-                        atomicOr(reinterpret_cast<uint32_t *>(at) + (place >> 5), 1u << (place & 31));
-                    };
-                    if (head) put_bit(w.heads);
-                    if (kRowHeads && head && row_head) put_bit(w.row_heads);
-                    if (kCsf && head && slice_head) put_bit(w.slice_heads);
+                    place += at - first;
+                }
+                if (valid) {
+                    w.order[place] = (uint16_t)(K <= 2 ? s * (int)sizeof(KeyT) : (t << 13 | s));
+                    // (few: the bits of the others are set below)
+                    if (!head) atomicOr(reinterpret_cast<uint32_t *>(w.heads) + (place >> 5), 1u << (place & 31));
                 }
             }
             __syncthreads();
+            if constexpr (kRowHeads) {
+                // rows and slices start where the fields of neighbours differ
+#pragma unroll 1
+                for (int j = 0; j < R && place0 + j * NACHO_WAVE < n; ++j) {
+                    const int m = place0 + j * NACHO_WAVE + lane, mm = m < n ? m : n - 1;
+                    int t;
+                    const KeyT field = row_field(keys[word_of(w.order[mm], t)]), before = row_field(keys[word_of(w.order[mm > 0 ? mm - 1 : 0], t)]);
+                    const unsigned long long in = low_bits(n - (place0 + j * NACHO_WAVE));
+                    const unsigned long long rm = __ballot(m == 0 || field != before) & in;
+                    const unsigned long long sm = __ballot(m == 0 || field >> jb != before >> jb) & in;
+                    if (lane == 0) {
+                        w.row_heads[block0 + j] = rm;
+                        if (kCsf) w.slice_heads[block0 + j] = sm;
+                    }
+                }
+            }
+            if (lane < R) w.heads[block0 + lane] = ~w.heads[block0 + lane];
         }
     };
 
     // ---- 2. merge: adjacent runs pairwise, in rounds ------------------------------
     // (all of this is uniform over the workgroup except the thread's own share)
     const char *kb = reinterpret_cast<const char *>(w.keys);
-    constexpr int KB = (int)sizeof(KeyT);
-    const int place0 = wave * (R * NACHO_WAVE);    // a wavefront's places: place0 + j * 64 + lane, j < R
-    const int block0 = wave * R;
     int mb = 0;                                // K > 2 or one run: the key of place m is keys[mb + m]
     bool moved = false;                        // the order words are in w.order (K > 2: from word mb on)
     bool marked = false;                       // the head bits are in place
@@ -1101,20 +1134,17 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // (64 places read one contiguous stretch per operand; the requests travel while the heads are counted and
     // the counts of the partitions before this one are looked up)
     T val[R], tail = T(0);
-    const int two_at = K <= 2 ? of(sb_v, K - 1) * KB : 0;      // two operands: the second one's words start here
     // address of the value of the entry an order word names
     auto value_at = [&](int o) -> T {
-        if constexpr (K <= 2) {
-            const int t = K == 2 && o >= two_at ? 1 : 0;
-            const int at = o / KB;
-            return global_ptr<T>(w.sval[t])[at];
-        } else return global_ptr<T>(w.sval[o >> 13])[o & 0x1fff];
+        int t;
+        const int at = word_of(o, t);
+        return global_ptr<T>(w.sval[t])[at];
     };
     auto order_of = [&](int m) -> int {
         if constexpr (K <= 2) return moved ? (int)w.order[m] : (mb + m) * KB;
         else return moved ? (int)w.order[mb + m] : (only << 13 | (mb + m));
     };
-    if (!kMul && !far && n > 0) {
+    if (!kMul && n > 0) {
         int o[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -1187,17 +1217,6 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
     const int own_nnz = own_counts & 0xffff, own_rows = own_counts >> 16;
 
-    if constexpr (D >= 2)
-        if (far && lane < R) {
-            // every thread looks bits and counts up by place; a wavefront's are in its lanes
-            w.heads[block0 + lane] = e;
-            if constexpr (kRowHeads) w.row_heads[block0 + lane] = r;
-            if constexpr (kCsf) w.slice_heads[block0 + lane] = sl;
-            const int before = wave_before + wave_incl - block_counts;
-            w.starts[block0 + lane] = (unsigned)before;
-            if constexpr (kCsf) w.starts[block0 + lane] |= (unsigned long long)(slices_before + slice_incl - __popcll(sl)) << 32;
-        }
-
     // ---- 4. prefix sum over the workgroups, first half: publish -------------------------
     // state of the call: one total per chunk, one 32-bit word per workgroup; third-order tensors keep
     // a second such pair behind the first for the slices
@@ -1249,6 +1268,14 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // (products: the keys after the values, whose requests need the registers)
     KeyT key[R];
     auto load_keys = [&]() {
+        if (K > 2 && far) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int m = place0 + j * NACHO_WAVE + lane;
+                key[j] = keys[w.order[m < n ? m : n - 1] & 0x1fff];
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int m = place0 + j * NACHO_WAVE + lane, mm = m < n ? m : n - 1;
@@ -1257,7 +1284,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             key[j] = *reinterpret_cast<const KeyT *>(kb + at);
         }
     };
-    if (!far && n > 0) {
+    if (n > 0) {
         if constexpr (!kMul) load_keys();
         if constexpr (kMul) {
             // products: few places are emitted; those ask for the values of all operands
@@ -1265,8 +1292,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 if constexpr (kMapped) {
                     const int o = order_of(m);
                     const int t = K <= 2 ? (o >= two_at ? 1 : 0) : o >> 13;
-                    const KeyT key = K <= 2 ? keys[o / KB] : keys[mb + m];
-                    const int row = row0 + (int)(uint32_t)(key >> cb);
+                    const KeyT key = keys[K <= 2 ? o / KB : (far ? o & 0x1fff : mb + m)];
+                    const int row = row0 + (int)(uint32_t)row_field(key);
                     const int sh = global_ptr<int32_t>(w.srow[t])[row] - global_ptr<int32_t>(w.spos[t])[row];
                     return global_ptr<T>(w.sval[t])[(K <= 2 ? o / KB : o & 0x1fff) + sh];
                 } else return value_at(order_of(m));
@@ -1294,7 +1321,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     }
                 }
             }
-            load_keys();
+            if constexpr (!kMapped) load_keys();
         } else {
             // sums: the equal keys behind a head belong to the lanes after it, in operand order
             load_heads();
@@ -1439,71 +1466,10 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     const Out seg_pos_out = kRowHeads ? out_at(kCsf ? out.pos2 : out.pos1, at_rows) : nullptr;
     const Out top_crd = kCsf ? out_at(out.crd0, at_slices) : nullptr;
     const Out top_pos = kCsf ? out_at(out.pos1, at_slices) : nullptr;
-    if constexpr (D >= 2)
-        if (far) {                             // (uniform, rare) by entry, each at its place
-#pragma unroll 1
-            for (int t = 0; t < k; ++t) {
-                const int q_t = of(q_v, t), len_t = of(len_v, t), sb_t = of(sb_v, t);
-#pragma unroll 1
-                for (int i = tid; i < len_t; i += kThreads) {
-                    const int m = (int)keys[sb_t + i], blk = m / NACHO_WAVE, q = q_t + i;
-                    const unsigned long long below = low_bits(m & (NACHO_WAVE - 1)), upto = low_bits((m & (NACHO_WAVE - 1)) + 1);
-                    if ((w.heads[blk] & upto & ~below) == 0ull) continue;      // not emitted
-                    const unsigned long long before = w.starts[blk];
-                    const int loc = (int)(before & 0xffffu) + __popcll(w.heads[blk] & below);
-                    int seg = 0, shift = 0;
-                    const bool row_starts_here = kRowHeads && (w.row_heads[blk] & upto & ~below) != 0ull;
-                    if (kMapped || row_starts_here) seg = holder(pos_of(t, D - 1), of(ilo_v, t), of(ihi_v, t), q);
-                    if (kMapped) shift = starts_of(t)[seg] - pos_of(t, D - 1)[seg];
-                    T v = global_ptr<T>(w.sval[t])[sb_t + i + shift];
-                    for (int g = 1; g < k; ++g) {
-                        if constexpr (kMul) {
-                            // (emitted: the next k - 1 places are the other operands' entries)
-                            const int o = w.order[m + g], t_g = K <= 2 ? (K == 2 && o >= two_at ? 1 : 0) : o >> 13;
-                            int at = K <= 2 ? o / KB : o & 0x1fff;
-                            if constexpr (kMapped) {
-                                const int place_at = at;
-#pragma unroll 1
-                                for (int u = 0; u < k; ++u) {
-                                    if (u != t_g) continue;
-                                    const int q_u = of(q_v, u) + place_at - of(sb_v, u);
-                                    const int seg_u = holder(pos_of(u, D - 1), of(ilo_v, u), of(ihi_v, u), q_u);
-                                    at += starts_of(u)[seg_u] - pos_of(u, D - 1)[seg_u];
-                                }
-                            }
-                            v *= global_ptr<T>(w.sval[t_g])[at];
-                        } else {
-                            if (m + g >= n) break;
-                            const int at = (m + g) / NACHO_WAVE, bit = (m + g) & (NACHO_WAVE - 1);
-                            if ((w.heads[at] & low_bits(bit + 1) & ~low_bits(bit)) != 0ull) break;
-                            v += value_at((int)w.order[m + g]);
-                        }
-                    }
-                    if (loc < room) {
-                        store(crd_out, (unsigned)loc, (int32_t)crd_of(t, D - 1)[q + shift]);
-                        if (kCoo) store(row_out, (unsigned)loc, (int32_t)crd_of(t, 0)[q]);
-                        store(val_out, (unsigned)loc, v);
-                    }
-                    if constexpr (kRowHeads) {
-                        const int rloc = (int)((unsigned)before >> 16) + __popcll(w.row_heads[blk] & below);
-                        if (row_starts_here && rloc < room_rows) {
-                            store(seg_crd_out, (unsigned)rloc, (int32_t)crd_of(t, D - 2)[seg]);
-                            store(seg_pos_out, (unsigned)rloc, at_nnz + loc);
-                        }
-                        if constexpr (kCsf) {
-                            const int sloc = (int)(before >> 32) + __popcll(w.slice_heads[blk] & below);
-                            if ((w.slice_heads[blk] & upto & ~below) != 0ull && sloc < room_slices) {
-                                const int up = holder(pos_of(t, 1), of(up_lo_v, t), of(up_hi_v, t) + 1, seg);
-                                store(top_crd, (unsigned)sloc, (int32_t)crd_of(t, 0)[up]);
-                                store(top_pos, (unsigned)sloc, at_rows + rloc);
-                            }
-                        }
-                    }
-                }
-            }
-            return log_end();
-        }
     int at = wave_before & 0xffff, at_row = wave_before >> 16, at_slice = slices_before;
+    // (remapped operands: no registers for the keys before this)
+    if constexpr (kMapped)
+        if (n > 0) load_keys();
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const unsigned long long ej = lane_word(e, j);
@@ -1518,14 +1484,14 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         if (tight) emit = emit && (int)loc < room;
         if (emit) {
             store(crd_out, loc, (int32_t)(D == 1 ? (uint32_t)key[j] : (uint32_t)(key[j] & col_mask)));
-            if (kCoo) store(row_out, loc, row0 + (int32_t)(uint32_t)(key[j] >> cb));
+            if (kCoo) store(row_out, loc, row0 + (int32_t)(uint32_t)row_field(key[j]));
             store(val_out, loc, val[j]);
         }
         if constexpr (kRowHeads) {
             const unsigned long long rj = lane_word(r, j);
             if (rj != 0ull) {                  // (uniform)
                 const unsigned rloc = (unsigned)(at_row + lanes_below(rj));
-                const KeyT field = key[j] >> cb;
+                const KeyT field = row_field(key[j]);
                 if (my_bit(rj) && (int)rloc < room_rows) {
                     // (a row's coordinate; a fibre's j) and where its entries start
                     store(seg_crd_out, rloc, kCsf ? (int32_t)(uint32_t)(field & ((KeyT(1) << jb) - KeyT(1))) : row0 + (int32_t)(uint32_t)field);
@@ -1545,6 +1511,29 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         at += __popcll(ej);
     }
+    if constexpr (D >= 2)
+        if (far) {
+            // (uniform, rare) the columns, whose lower bits the keys lack
+            at = wave_before & 0xffff;
+#pragma unroll 1
+            for (int j0 = 0; j0 < R && place0 + j0 * NACHO_WAVE < n; j0 += 4) {
+                int col[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int m = place0 + (j0 + i) * NACHO_WAVE + lane;
+                    int t;
+                    const int s = word_of((int)w.order[m < n ? m : n - 1], t);
+                    col[i] = column_at(t, s, row_field(keys[s]));
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned long long ej = j0 + i < R ? lane_word(e, j0 + i) : 0ull;
+                    const int loc = at + lanes_below(ej);
+                    if (my_bit(ej) && loc < room) store(crd_out, (unsigned)loc, (int32_t)col[i]);
+                    at += __popcll(ej);
+                }
+            }
+        }
     log_end();
 }
 

@@ -1,5 +1,7 @@
 // Host side of the k-way merge: capacities, key layout, and which instantiation of the kernel (merge.hpp) a
 // call runs.
+#include <algorithm>
+
 #include "merge.hpp"
 
 namespace nacho {
@@ -28,7 +30,7 @@ int spadd_wavefronts() { return kWaves; }
 
 // The key layout of a call: 32-bit keys when the rows (slices) that an average full partition spans take a
 // quarter of the row field or less, or the field holds any row, else 64-bit keys.  A partition that spans more rows
-// than the field holds is merged without keys, by searches, at about a fifth of the speed.
+// than the field holds is merged by searches (rank_far), for which a key's word has to hold any (slice, fibre) pair.
 MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units)
 {
     MergeFields f;
@@ -52,15 +54,18 @@ MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t
     }
     int64_t span = (int64_t)((double)rows * capacity_of(false, f.small != 0, dtype) / (double)per) + 2;
     if (span > rows) span = rows;
-    if (f.limit == 0 || (rows > (int64_t)f.limit && span > (int64_t)(f.limit / 4))) {
+    if (f.limit == 0 || (fmt == SPADD_CSF3 && rows > (int64_t)1 << (32 - f.jb)) ||
+        (rows > (int64_t)f.limit && span > (int64_t)(f.limit / 4))) {
         f.wide = 1;
         f.small = 0;
         f.limit = 0x80000000u;                 // matrices: any row
         if (fmt != SPADD_CSF3) f.cb = 32;
         else {
-            // tensors: the row field (i - i0) << jb | j has what is left of the key, kept in 48 bits before
+            // tensors: the row field (i - i0) << jb | j has what is left of the key, kept in 48 bits before (whose
+            // upper 16 are never all ones)
             const int room = (64 - f.cb < 48 ? 64 - f.cb : 48) - f.jb;         // (>= 2)
             if (room < 32) f.limit = (uint32_t)(((uint64_t)1 << room) - 1u);
+            if (f.jb > 16) f.limit = std::min(f.limit, 0xffffu << (32 - f.jb));
         }
     }
     return f;

@@ -211,7 +211,7 @@ def _banded(rng, n_rows, n_cols, dense, sparse):
 @pytest.mark.parametrize("k,total,dtype", [(2, 1_100_000, np.float32), (3, 1_100_000, np.float64),
                                            (2, 3_300_000, np.float64), (3, 3_300_000, np.float32)])
 def test_merge_in_bands(k, total, dtype):
-    """Rows past the row field (12 bits beside 2^20 columns): the partition is merged without keys; short partitions and
+    """Rows past the row field (12 bits beside 2^20 columns): the partition is merged by searches; short partitions and
     long ones."""
     rng = np.random.default_rng(41)
     shape = (1 << 19, 1 << 20)
@@ -325,6 +325,75 @@ def test_product_rows_past_the_key(k, dtype):
         c = np.stack([keys // shape[1], keys % shape[1]], 1)
         mats.append(mul_dcsr._mat(c, rng.uniform(0.5, 1, len(c)).astype(dtype)))
     mul_dcsr.check(mats, shape, 0, "rows past the key")
+
+
+@pytest.mark.parametrize("k", [2, 5, 8])
+@pytest.mark.parametrize("gap", [65533, 65534, 65535, 65536])
+def test_merge_rows_at_the_limit_of_the_key(gap, k):
+    """16 bits of row field beside 16 of column: the first partition holds two rows just within it, or just past it."""
+    rng = np.random.default_rng(gap + k)
+    shape = (200_000, 1 << 16)
+    row = lambda r, n: r * shape[1] + rng.choice(shape[1], n, replace=False)
+    both = np.concatenate([row(0, 100), row(gap, 400)])
+    cs, vals = [], []
+    for _ in range(k):
+        keys = [both, row(0, 1000 // k), row(gap, 4000 // k)] + [row(199_000 + i, 30_000 // k) for i in range(2)]
+        keys = np.unique(np.concatenate(keys))
+        cs.append(np.stack([keys // shape[1], keys % shape[1]], 1))
+        vals.append(rng.uniform(-1, 1, len(keys)).astype(np.float32))
+    mats = list(zip(cs, vals))
+    add.check_dcsr(mats, shape, 0, "limit")
+    add.check_csr(mats, shape, 0, "limit")
+    coo._check(nb.nacho_spadd_k, oracle.spadd_coo, cs, vals, shape, 0, "add limit")
+    coo._check(nb.nacho_spmul_k, oracle.spmul_coo, cs, vals, shape, 0, "mul limit")
+    mul.check_csr([dict(zip(("pos", "crd"), to_csr(c, shape[0])), val=v) for c, v in mats], shape, 0, "limit")
+
+
+@pytest.mark.parametrize("k", [2, 3, 8])
+@pytest.mark.parametrize("shape,gap", [((100_000, 64, 256), g) for g in (1021, 1022, 1023, 1024)] +
+                         [((1 << 25, 1 << 24, 16), g) for g in (16_776_958, 16_776_959, 16_776_960, 16_777_216)])
+def test_merge_slices_at_the_limit_of_the_key(shape, gap, k):
+    """The same for the slices of tensors: ten bits beside six of the fibre (32-bit keys), 24 beside 24 (64-bit keys)."""
+    rng = np.random.default_rng(gap + k)
+
+    def slice_(i, n):
+        c = np.stack([np.full(n, i), rng.integers(0, shape[1], n), rng.integers(0, shape[2], n)], 1)
+        c[::3, 1] = shape[1] - 1
+        return c
+
+    both = np.concatenate([slice_(0, 100), slice_(gap, 400)])
+    tens = []
+    for _ in range(k):
+        c = [both, slice_(0, 1000 // k), slice_(gap, 4000 // k)] + [slice_(shape[0] - 2 - i, 60_000 // k) for i in range(2)]
+        c = np.unique(np.concatenate(c), axis=0)
+        tens.append(csf3._tensor(c, rng.uniform(-1, 1, len(c)).astype(np.float32)))
+    csf3._check(tens, shape, 0, "limit")
+
+
+@pytest.mark.parametrize("k,dtype", [(2, np.float32), (3, np.float64), (8, np.float32)])
+def test_merge_far_rows_beside_long_ones(k, dtype):
+    """Eight bits of row field beside 2^24 columns; in one partition rows of one entry and rows of hundreds, which some
+    or all of the operands store, with entries that some or all of them share."""
+    rng = np.random.default_rng(91 + k)
+    shape = (60_000, 1 << 24)
+    long_rows = np.repeat(np.arange(40, 5000, 700), 300)
+    common = np.unique(np.concatenate([long_rows * shape[1] + rng.integers(0, shape[1], len(long_rows)),
+                                       rng.integers(0, 5000, 300) * shape[1] + rng.integers(0, 9, 300)]))
+    cs, vals = [], []
+    for t in range(k):
+        own = np.repeat(np.arange(40 + 700 * (t % 3), 5000, 1400), 200)
+        keys = np.unique(np.concatenate([common if t < 2 else common[rng.random(len(common)) < 0.7],
+                                         own * shape[1] + rng.integers(0, shape[1], len(own)),
+                                         rng.integers(0, 5000, 500) * shape[1] + rng.integers(0, 9, 500),
+                                         59_990 * shape[1] + rng.integers(0, 10 * shape[1], 6_200_000 // k)]))
+        cs.append(np.stack([keys // shape[1], keys % shape[1]], 1))
+        vals.append(rng.uniform(-1, 1, len(keys)).astype(dtype))
+    mats = list(zip(cs, vals))
+    add.check_dcsr(mats, shape, 0, "far and long")
+    add.check_csr(mats, shape, 0, "far and long")
+    coo._check(nb.nacho_spadd_k, oracle.spadd_coo, cs, vals, shape, 0, "add far and long")
+    coo._check(nb.nacho_spmul_k, oracle.spmul_coo, cs, vals, shape, 0, "mul far and long")
+    mul_dcsr.check([mul_dcsr._mat(c, v) for c, v in mats], shape, 0, "far and long")
 
 
 # ---- recursive partitioning -----------------------------------------------------
