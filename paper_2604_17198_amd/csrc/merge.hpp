@@ -681,9 +681,18 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                         if (many) {                                // (uniform)
                             const Ints pos1 = pos_of(t, 1);
                             int lo = up_lo, hi = of(up_hi_v, t);
-                            while (lo < hi) {                      // the last slice that starts at or before fibre i
-                                const int mid = (lo + hi + 1) >> 1;
-                                if (pos1[mid] <= i) lo = mid; else hi = mid - 1;
+                            while (lo < hi) {                      // the last slice that starts at or before fibre i,
+                                const int step = (hi - lo + 3) >> 2;       // four ways: half the dependent loads
+                                int at[3], first[3];
+#pragma unroll
+                                for (int g = 0; g < 3; ++g) {
+                                    at[g] = lo + (g + 1) * step < hi ? lo + (g + 1) * step : hi;
+                                    first[g] = pos1[at[g]];
+                                }
+#pragma unroll
+                                for (int g = 2; g >= 0; --g) hi = first[g] > i ? at[g] - 1 : hi;
+#pragma unroll
+                                for (int g = 0; g < 3; ++g) lo = first[g] <= i ? at[g] : lo;
                             }
                             up = crd_of(t, 0)[lo];
                         }
