@@ -671,6 +671,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     }
                 }
                 if (len == 0) continue;
+                constexpr int kMore = !kCsf && K <= 4 ? 8 : 4;         // segments a thread has in flight (registers)
                 auto mark_segment = [&](int i, int a, int b, int id) {
                     const int s = a > q ? a : q;
                     if (b <= s || s >= q + len) return;            // nothing of it lies in the partition
@@ -713,15 +714,15 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u)
                     mark_segment(i_lo + u * kThreads + tid, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
-                for (int i = i_lo + tid + kAhead * kThreads; i < i_hi; i += kThreads * 4) {
-                    int a[4], b[4], id[4];
+                for (int i = i_lo + tid + kAhead * kThreads; i < i_hi; i += kThreads * kMore) {
+                    int a[kMore], b[kMore], id[kMore];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < kMore; ++u) {
                         a[u] = b[u] = id[u] = 0;
                         if (i + u * kThreads < i_hi) load_segment(t, i + u * kThreads, a[u], b[u], id[u]);
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) mark_segment(i + u * kThreads, a[u], b[u], id[u]);
+                    for (int u = 0; u < kMore; ++u) mark_segment(i + u * kThreads, a[u], b[u], id[u]);
                 }
             }
             // the sentinel of a run: a row start whose row field is all ones, as its column is
