@@ -137,8 +137,16 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-def _stream():
+def _public_stream():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _raw_stream():
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+# (torch's raw getters are private names: without them the public call)
+_stream = _raw_stream if all(hasattr(torch._C, n) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice")) else _public_stream
 
 
 def dtype_code(dt) -> int:

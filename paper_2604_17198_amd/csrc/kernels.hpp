@@ -113,7 +113,8 @@ hipError_t launch_spadd_vector_search(int dtype, const DevOperands &ops, const S
                                       const SpaddSearch &search, unsigned long long *tile_state, const SpaddOut &out,
                                       hipStream_t s);
 // Count, prefix sum and fill in one kernel, one workgroup per partition.  `multiply`: the k-way
-// intersection with products instead of the union with sums (vectors and CSR only).
+// intersection with products instead of the union with sums (vectors, CSR and coordinate lists; DCSR operands come
+// here remapped, as CSR; no tensors).
 hipError_t launch_spadd(int fmt, int dtype, bool multiply, const DevOperands &ops, const SpaddValues &vals,
                         int64_t P, const int32_t *coord, const int32_t *posn, unsigned long long *tile_state,
                         const SpaddOut &out, const MergeFields &fields, hipStream_t s);

@@ -452,3 +452,10 @@ def test_positions_up_to_the_last_one():
         print(f"positions to the last one n={n}", flush=True)
         got = nb.nacho_spmm(op, B) if n else nb.nacho_spmv(op, B[:, 0].contiguous())[:, None]
         assert torch.equal(got.double(), want)
+
+
+def test_the_stream_of_a_call_is_torchs_current_one():
+    """The private getter and the public call it stands for name the same stream, on torch's default stream and on others."""
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            assert nb._stream() == nb._public_stream() == stream.cuda_stream
