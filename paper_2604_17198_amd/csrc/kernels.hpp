@@ -73,10 +73,12 @@ struct SpaddOut {
     int32_t *status;
 };
 // Partitions of a merge that needs `need` of them, on a chip that holds `round` of its workgroups at a time: a whole
-// number of rounds where that adds a twelfth at most (three CSR matrices, 948 to 1024 partitions: 44.6 to 43.4 us; two
-// tensors, 2887 to 3072: 125.5 to 124.3), else as few as will do.  Workgroups come and go one by one, so a last round
-// need not be full; shorter partitions only pay a partition's fixed time more often (coordinate lists, 1047 partitions
-// or 2048: 44 or 57 us; vectors, 1102 or 2048: 52 or 58; DCSR matrices, 40M entries, 7195 or 8192: 194 or 206).
+// number of rounds where that adds a twelfth at most, else as few as will do.  Workgroups come and go one by one, so a last
+// round need not be full; shorter partitions pay a partition's fixed time more often.  Measured on sums of vectors, CSR
+// matrices, coordinate lists, DCSR matrices and tensors with 3 to 16 % more partitions than needed (whole rounds against
+// as few as will do): one and two rounds of matrices and tensors -5 to +1 % up to 13 % more, -5 to +4 % at 16 %; four
+// rounds -2 to 0 % at 3 and 6 %, -1 to +2 % at 8 %, +0 to +4 % at 10 to 16 %.  Vectors: 0 to +3 % at one and two
+// rounds, +3 to +5 % at four.  So the line is a mean: the gains of a few rounds end where the losses of many begin.
 __host__ __device__ inline int64_t whole_rounds(int64_t need, int64_t round)
 {
     const int64_t up = (need + round - 1) / round * round;
