@@ -621,6 +621,23 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
     }
     __syncthreads();                           // vectors: the keys are there; others: bits and flags are cleared
+    unsigned long long st = 0ull;              // lane l: the starts of block wave * R + l
+    int latest = 0;                            // latest row start before the block in hand (0: none yet)
+    const uint32_t upto_lo = lane >= 31 ? ~0u : (2u << lane) - 1u;
+    const uint32_t upto_hi = lane == 63 ? ~0u : (lane >= 32 ? (2u << (lane - 32)) - 1u : 0u);
+    // the row start at or before word word0 + j * 64 + lane (called for j = 0, 1, ...)
+    auto start_of = [&](int j) -> int {
+        const unsigned long long x = lane_word(st, j);
+        int e = latest;
+        if (x) {                           // (uniform) some row starts in the block
+            const uint32_t lo = (uint32_t)x & upto_lo, hi = (uint32_t)(x >> 32) & upto_hi;
+            const int at = word0 + j * NACHO_WAVE;
+            e = lo ? at + 31 - __builtin_clz(lo) : e;
+            e = hi ? at + 63 - __builtin_clz(hi) : e;
+            latest = at + 63 - __clzll((long long)x);
+        }
+        return e;
+    };
     if constexpr (D >= 2) {
         if constexpr (kWindow) {
             auto mark_start = [&](int s, KeyT field) {
@@ -671,7 +688,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     }
                 }
                 if (len == 0) continue;
-                constexpr int kMore = !kCsf && K <= 4 ? 8 : 4;         // segments a thread has in flight (registers)
+                constexpr int kMore = !kCsf && !kSmall && K <= 4 ? 8 : 4;      // segments a thread has in flight (registers)
                 auto mark_segment = [&](int i, int a, int b, int id) {
                     const int s = a > q ? a : q;
                     if (b <= s || s >= q + len) return;            // nothing of it lies in the partition
@@ -732,8 +749,6 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         // Keys.  A wavefront takes R blocks of 64 words; the words' row starts are in its lanes, and where the
         // latest start before a block lies goes from block to block in a scalar register.
-        unsigned long long st = 0ull;          // lane l: the starts of block wave * R + l
-        int latest = 0;                        // latest row start before the block in hand (0: none yet)
         if constexpr (kWindow) {
             if (lane < R) st = w.starts[wave * R + lane];
             int last = 0;
@@ -745,47 +760,14 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             }
             latest = __builtin_amdgcn_readlane(dpp_scan_max(last, 0), NACHO_WAVE - 1);
         }
-        const uint32_t upto_lo = lane >= 31 ? ~0u : (2u << lane) - 1u;
-        const uint32_t upto_hi = lane == 63 ? ~0u : (lane >= 32 ? (2u << (lane - 32)) - 1u : 0u);
-        // the row start at or before word word0 + j * 64 + lane (called for j = 0, 1, ...)
-        auto start_of = [&](int j) -> int {
-            const unsigned long long x = lane_word(st, j);
-            int e = latest;
-            if (x) {                           // (uniform) some row starts in the block
-                const uint32_t lo = (uint32_t)x & upto_lo, hi = (uint32_t)(x >> 32) & upto_hi;
-                const int at = word0 + j * NACHO_WAVE;
-                e = lo ? at + 31 - __builtin_clz(lo) : e;
-                e = hi ? at + 63 - __builtin_clz(hi) : e;
-                latest = at + 63 - __clzll((long long)x);
-            }
-            return e;
-        };
         auto field_at = [&](int e) -> KeyT {
             if (!kWide) return (KeyT)w.order[e];
             return kCsf ? (KeyT)wide_rows[e] | (KeyT)w.order[e] << (kWide ? 32 : 0) : (KeyT)wide_rows[e];
         };
         if (kWindow && far) {
-            // (the keys are put together in rank_far)
-            if constexpr (!kWide) {
-#pragma unroll 1
-                for (int j = 0; j < R && word0 + j * NACHO_WAVE < words; ++j) {
-                    const int e = start_of(j);         // (a row start gets the field it holds)
-                    cols[word0 + j * NACHO_WAVE + lane] = w.order[e] == kPastKey ? cols[e] : w.order[e];
-                }
-            } else {
-                KeyT field[R];
-#pragma unroll
-                for (int j = 0; j < R; ++j) {
-                    const int e = start_of(j);
-                    field[j] = kCsf && w.order[e] == kPastKey ? ((KeyT)cols[e] << jb) | (KeyT)wide_rows[e] : field_at(e);
-                }
-                lds_barrier();
-#pragma unroll
-                for (int j = 0; j < R; ++j) {
-                    const int s = word0 + j * NACHO_WAVE + lane;
-                    if (s < words) keys[s] = field[j];
-                }
-            }
+            // (the keys are put together in rank_far, where the code of such partitions lies together, out of the way of
+            // the others': a small call waits for its instructions; the product of four CSR matrices of 10k entries 23.9 us with
+            // it here, 23.1 there)
         } else if constexpr (!kWide && kWindow && kDirect) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
@@ -858,7 +840,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // output go the way of every partition, but for the columns, which are stored once more in full.  The layout of the
     // keys is chosen so that few partitions come here.
     int row_at = cb;                           // the row field of a key starts at this bit
-    if (far) {
+    if (__builtin_expect(far, 0)) {
         const int last = (int)row_extent() - 1, next = table_coord(p + 1, 0);
         const uint32_t most = (uint32_t)((next < last ? next : last) - row0);
         const int room = 8 * (int)sizeof(KeyT) - jb - (most > 0u ? 32 - __builtin_clz(most) : 0);
@@ -889,6 +871,31 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     };
     auto rank_far = [&]() {
         if constexpr (D >= 2) {
+            if constexpr (kWindow) {
+                // the row fields
+                if constexpr (!kWide) {
+#pragma unroll 1
+                    for (int j = 0; j < R && word0 + j * NACHO_WAVE < words; ++j) {
+                        const int e = start_of(j);         // (a row start gets the field it holds)
+                        cols[word0 + j * NACHO_WAVE + lane] = w.order[e] == kPastKey ? cols[e] : w.order[e];
+                    }
+                } else {
+                    KeyT field[R];
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        const int e = start_of(j);
+                        field[j] = (KeyT)wide_rows[e];
+                        if (kCsf) field[j] |= w.order[e] == kPastKey ? (KeyT)cols[e] << jb : (KeyT)w.order[e] << (kWide ? 32 : 0);
+                    }
+                    lds_barrier();
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        const int s = word0 + j * NACHO_WAVE + lane;
+                        if (s < words) keys[s] = field[j];
+                    }
+                }
+                __syncthreads();
+            }
 #pragma unroll 1
             for (int u = 0; u < k; ++u) {
                 const int q = of(q_v, u), sb = of(sb_v, u), len = of(len_v, u);
@@ -1008,7 +1015,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if (kCsf) sm += sm + (diff > slice_mask ? 1u : 0u);
         }
     };
-    if (far) {
+    if (__builtin_expect(far, 0)) {
         rank_far();
         moved = marked = true;
     } else if constexpr (K <= 2) {
@@ -1278,7 +1285,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // (products: the keys after the values, whose requests need the registers)
     KeyT key[R];
     auto load_keys = [&]() {
-        if (K > 2 && far) {
+        if (K > 2 && __builtin_expect(far, 0)) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const int m = place0 + j * NACHO_WAVE + lane;
@@ -1522,7 +1529,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         at += __popcll(ej);
     }
     if constexpr (D >= 2)
-        if (far) {
+        if (__builtin_expect(far, 0)) {
             // (uniform, rare) the columns, whose lower bits the keys lack
             at = wave_before & 0xffff;
 #pragma unroll 1
