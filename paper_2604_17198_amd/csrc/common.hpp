@@ -55,11 +55,37 @@ __host__ __device__ inline int64_t equal_query(int64_t p, int64_t total, int64_t
     return p * q + (p * r) / P;
 }
 
+// The same where everything fits 31 bits, without divisions of 64 bits (some 400 instructions before the first load
+// of a boundary search).
+__device__ inline int64_t equal_query_short(unsigned p, unsigned total, unsigned P)
+{
+    const unsigned q = total / P, r = total - q * P;
+    const uint64_t product = (uint64_t)p * r;              // < 2^62; the quotient by P is below 2^31, so the estimate is off by 1 at most
+    unsigned x = (unsigned)((double)product / (double)P);
+    const int64_t left = (int64_t)(product - (uint64_t)x * P);
+    x += left < 0 ? ~0u : (left >= (int64_t)P ? 1u : 0u);
+    return (int64_t)p * q + x;
+}
+
 // Partitions of `grain` units that start before the place `at` of a row's (or the matrix's) non-zeros: at / grain
 // rounded up, 0 <= at < 2^31 (unsigned: at + grain may lie past 2^31).
 __host__ __device__ inline int shares_before(int at, int grain)
 {
     return (int)(((unsigned)at + (unsigned)grain - 1u) / (unsigned)grain);
+}
+
+// Asks for the first kBytes of the kernel's arguments at once.  They lie in memory that no cache holds at a kernel's
+// start; left to the places where they are used, every line of them is a round trip of its own.
+template <int kBytes> __device__ inline void touch_arguments()
+{
+    typedef const __attribute__((address_space(4))) unsigned *Words;
+    const Words words = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+    auto line = [&](int i) { return words[i * 64 < kBytes ? i * 16 : 0]; };
+    static_assert(kBytes <= 22 * 64, "twenty-two lines");
+    // (one statement: the compiler waits for what it names in one go)
+    asm volatile("" ::"s"(line(0)), "s"(line(1)), "s"(line(2)), "s"(line(3)), "s"(line(4)), "s"(line(5)), "s"(line(6)),
+                 "s"(line(7)), "s"(line(8)), "s"(line(9)), "s"(line(10)), "s"(line(11)), "s"(line(12)), "s"(line(13)),
+                 "s"(line(14)), "s"(line(15)), "s"(line(16)), "s"(line(17)), "s"(line(18)), "s"(line(19)), "s"(line(20)), "s"(line(21)));
 }
 
 __device__ inline int lane_id() { return (int)(threadIdx.x & (NACHO_WAVE - 1)); }
@@ -82,13 +108,6 @@ __device__ inline T wave_sum(T v)
 {
 #pragma unroll
     for (int off = NACHO_WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, NACHO_WAVE);
-    return v;
-}
-
-__device__ inline int wave_max(int v)
-{
-#pragma unroll
-    for (int off = NACHO_WAVE / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, NACHO_WAVE));
     return v;
 }
 
@@ -155,16 +174,6 @@ __device__ inline bool bit_at(unsigned long long mask, int at)
     unsigned hi = (unsigned)(mask >> 32);
     asm("" : "+s"(hi));
     return (((at < 32 ? lo : hi) >> (at & 31)) & 1u) != 0u;
-}
-
-// Least position in [lo, hi) whose coordinate is >= x; hi if there is none.
-__device__ inline int lower_bound_global(const int32_t *__restrict__ crd, int lo, int hi, int64_t x)
-{
-    while (lo < hi) {
-        int mid = lo + ((hi - lo) >> 1);
-        if ((int64_t)crd[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
 }
 
 // First row t in [lo, hi) with pos[t + 1] > q, found by the whole wavefront (64 probes

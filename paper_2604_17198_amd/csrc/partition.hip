@@ -8,21 +8,21 @@
 // 64 lanes of a wavefront shorten it.
 //   * Dense level (rows of CSR): a 64-ary search, 64 candidate coordinates per
 //     round, ceil(log64(N+1)) rounds, one pos load per operand and round.
-//   * Compressed level: every round each operand's current window is sampled at
-//     64 evenly spaced positions (one load per lane and operand).  A sample's
-//     own position is its exact lower bound in its operand; in the other
+//   * Compressed level: the lanes are shared out over the operands, and every
+//     round a lane looks at one sample of its operand's current window.  A
+//     sample's own position is its exact lower bound in its operand; in the other
 //     operands its lower bound is bracketed by the two neighbouring samples.
 //     That gives a lower and an upper bound of the cost of every sampled
 //     coordinate; samples whose upper bound is <= the residual query are not
 //     after the boundary, samples whose lower bound exceeds it are after it, and
 //     every window shrinks to the bracket of the largest / smallest such sample.
-//     Once every window holds <= 64 entries the bounds are exact and the round
-//     returns the boundary.  A boundary over 10M + 1M + 100k entries takes about
-//     seven rounds, i.e. seven dependent loads instead of several hundred.
-//     (With five to eight operands the K * K rank searches per round outgrow the
-//     registers and the instruction cache; those calls use the 64-ary search over
-//     coordinates with one lower-bound search per operand and probe, inside
-//     tracked windows, throughout.)
+//     The samples lie around the place where the boundary is expected, further
+//     apart with the distance from it: operands whose entries are spread alike
+//     take three or four rounds for ten million entries, any others some more.
+//     Once every window has no more entries than its operand has lanes the
+//     bounds are exact and the round returns the boundary.
+//   * Two operands on the last level: the split of their merged segments, which
+//     takes two loads and one comparison a round.
 //   * Coordinate lists (COO): both levels are searched as one level of (row,
 //     column) pairs with 64-bit coordinates.
 //   * One CSR operand (SpMV, SpMM): no search at all, see partition_csr1_kernel.
@@ -74,13 +74,14 @@ partition_kernel(DevOperands ops, int64_t cost_scale, int64_t P, int64_t grain,
                  int32_t *__restrict__ coord, int32_t *__restrict__ posn, int64_t *__restrict__ cost,
                  ClearWords clear)
 {
-    clear.run((int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+    touch_arguments<sizeof(DevOperands) + 80>();
+    clear.run((int64_t)blockIdx.x * 256 + threadIdx.x);
     if (ops.dyn_plan) {                      // sizes left on the device by earlier kernels of the call
         if (ops.dyn_plan[3]) return;         // (the row loop was abandoned)
         P = ops.dyn_plan[0];
         total_unscaled = ops.dyn_plan[2];
     }
-    const int64_t b = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / NACHO_WAVE;
+    const int64_t b = (int64_t)blockIdx.x * (256 / NACHO_WAVE) + threadIdx.x / NACHO_WAVE;
     if (b > P) return;                       // whole wavefront leaves together
     int found[K];
     search_boundary<K, kMode>(ops, cost_scale, P, grain, queries, total_unscaled, coord, posn, cost, b, found);
@@ -280,46 +281,23 @@ hipError_t launch_partition(const DevOperands &ops, int64_t cost_scale, int64_t 
     if (clear.n > waves * NACHO_WAVE) waves = (clear.n + NACHO_WAVE - 1) / NACHO_WAVE;
     const int waves_per_block = 256 / NACHO_WAVE;
     const unsigned grid = (unsigned)((waves + waves_per_block - 1) / waves_per_block);
-    // instantiated for 1, 2, 3, 4 and 8 operands so that small calls keep their state in registers
-    if (ops.d == 3) {
-        if (ops.k <= 2)
-            hipLaunchKernelGGL((partition_kernel<2, 2>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                               queries, total_unscaled, coord, posn, cost, clear);
-        else if (ops.k <= 4)
-            hipLaunchKernelGGL((partition_kernel<4, 2>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                               queries, total_unscaled, coord, posn, cost, clear);
-        else
-            hipLaunchKernelGGL((partition_kernel<8, 2>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                               queries, total_unscaled, coord, posn, cost, clear);
-        return hipGetLastError();
-    }
-    if (ops.lvl[0][0].kind == NACHO_NONUNIQUE) {
-        if (ops.k <= 2)
-            hipLaunchKernelGGL((partition_kernel<2, 1>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                               queries, total_unscaled, coord, posn, cost, clear);
-        else if (ops.k <= 4)
-            hipLaunchKernelGGL((partition_kernel<4, 1>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                               queries, total_unscaled, coord, posn, cost, clear);
-        else
-            hipLaunchKernelGGL((partition_kernel<8, 1>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                               queries, total_unscaled, coord, posn, cost, clear);
-        return hipGetLastError();
-    }
-    if (ops.k <= 1)
-        hipLaunchKernelGGL((partition_kernel<1, 0>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                           queries, total_unscaled, coord, posn, cost, clear);
-    else if (ops.k <= 2)
-        hipLaunchKernelGGL((partition_kernel<2, 0>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                           queries, total_unscaled, coord, posn, cost, clear);
-    else if (ops.k <= 3)
-        hipLaunchKernelGGL((partition_kernel<3, 0>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                           queries, total_unscaled, coord, posn, cost, clear);
-    else if (ops.k <= 4)
-        hipLaunchKernelGGL((partition_kernel<4, 0>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                           queries, total_unscaled, coord, posn, cost, clear);
-    else
-        hipLaunchKernelGGL((partition_kernel<8, 0>), dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain,
-                           queries, total_unscaled, coord, posn, cost, clear);
+    // instantiated for up to 1, 2, 3, 4, 6 and 8 operands: the searches in the other operands' samples are unrolled
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, ops, cost_scale, P, grain, queries, total_unscaled, coord,
+                           posn, cost, clear);
+    };
+    auto launch_mode = [&](auto mode) {
+        constexpr int kMode = decltype(mode)::value;
+        if (kMode == 0 && ops.k <= 1) launch(partition_kernel<1, 0>);
+        else if (ops.k <= 2) launch(partition_kernel<2, kMode>);
+        else if (ops.k <= 3) launch(partition_kernel<3, kMode>);
+        else if (ops.k <= 4) launch(partition_kernel<4, kMode>);
+        else if (ops.k <= 6) launch(partition_kernel<6, kMode>);
+        else launch(partition_kernel<8, kMode>);
+    };
+    if (ops.d == 3) launch_mode(std::integral_constant<int, 2>());
+    else if (ops.lvl[0][0].kind == NACHO_NONUNIQUE) launch_mode(std::integral_constant<int, 1>());
+    else launch_mode(std::integral_constant<int, 0>());
     return hipGetLastError();
 }
 

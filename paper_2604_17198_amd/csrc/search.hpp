@@ -1,6 +1,8 @@
 // The boundary search of Algorithm 1 (Section 3.2) as one wavefront runs it, for the partition
 // kernel and for kernels that search their own boundaries: see partition.hip for the method.
 #pragma once
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -8,28 +10,38 @@ namespace nacho {
 
 namespace {
 
-struct LevelResult {
-    int64_t x;  // chosen coordinate
-    int64_t c;  // C_m(x | prefix), unscaled
-};
-
 // How a compressed level's coordinates are read.  Plain: one int32 array.  Pairs: the level is
 // the list of (row, column) pairs of a coordinate-list (COO) operand, i.e. both of its levels
 // taken together as one sorted, duplicate-free level with the 64-bit coordinate row << 32 | column
 // (Algorithm 1 on the two levels and on this one level find the same boundary: the highest row
 // whose cost fits, then the highest column inside it, is the highest pair whose cost fits).
+typedef const __attribute__((address_space(1))) int32_t *Ints32;
+__device__ inline Ints32 as_global(const int32_t *a) { return (Ints32)(unsigned long long)(uintptr_t)a; }
+
 struct PlainCoords {
     typedef int type;
+    static constexpr bool kPairs = false;
     static constexpr type kNone = INT32_MAX;            // no coordinate
-    __device__ static type load(const DevOperands &ops, int t, int m, int at) { return ops.lvl[t][m].crd[at]; }
+    Ints32 crd;
+    __device__ type load(int at) const { return crd[at]; }
+    __device__ static float apart(type a, type b) { return (float)(b - a); }
+    __device__ static PlainCoords of(const DevOperands &ops, int t, int m) { return PlainCoords{as_global(ops.lvl[t][m].crd)}; }
     __device__ static int64_t extent(const DevOperands &ops, int m) { return ops.lvl[0][m].extent; }
 };
 struct PairCoords {
     typedef long long type;
+    static constexpr bool kPairs = true;
     static constexpr type kNone = INT64_MAX;
-    __device__ static type load(const DevOperands &ops, int t, int, int at)
+    Ints32 row, col;
+    __device__ type load(int at) const { return ((long long)row[at] << 32) | (long long)(unsigned)col[at]; }
+    // (in halves: the conversion of 64 bits shifts by an amount of the lane's own)
+    __device__ static float apart(type a, type b)
     {
-        return ((long long)ops.lvl[t][0].crd[at] << 32) | (long long)(unsigned)ops.lvl[t][1].crd[at];
+        return (float)(int)((b - a) >> 32) * 4294967296.0f + (float)(unsigned)(b - a);
+    }
+    __device__ static PairCoords of(const DevOperands &ops, int t, int)
+    {
+        return PairCoords{as_global(ops.lvl[t][0].crd), as_global(ops.lvl[t][1].crd)};
     }
     __device__ static int64_t extent(const DevOperands &ops, int) { return ops.lvl[0][0].extent << 32; }
 };
@@ -42,37 +54,58 @@ __device__ inline long long lane_value(long long x, int from)
     const int hi = __builtin_amdgcn_readlane((int)(x >> 32), from);
     return ((long long)hi << 32) | (long long)lo;
 }
-
-// Least position in [lo, hi) of operand t whose coordinate is >= x; hi if there is none.
-template <class Acc>
-__device__ inline int lower_bound_level(const DevOperands &ops, int t, int m, int shift, int lo, int hi, int64_t x)
+// The value lane `from` holds, `from` this lane's own choice.
+__device__ inline int value_from(int x, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, x); }
+__device__ inline long long value_from(long long x, int from)
 {
-    while (lo < hi) {
-        const int mid = lo + ((hi - lo) >> 1);
-        if ((int64_t)Acc::load(ops, t, m, mid + shift) < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
+    const unsigned lo = (unsigned)value_from((int)(unsigned)(unsigned long long)x, from);
+    return ((long long)value_from((int)(x >> 32), from) << 32) | (long long)lo;
 }
 
-// Cost of the entries before position q of a level that is not the last one: the start of
-// q's segment one level down -- or, kDeep (level 0 of a three-level operand), the start two
-// levels down, where the non-zeros are.
-template <bool kDeep>
-__device__ inline int cost_at(const DevOperands &ops, int t, int m, int q)
+__device__ inline int lane_left(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false); }     // wave_shr:1
+
+// Sum, maximum and minimum over the wavefront by DPP moves (in every lane).
+__device__ inline int sum_of_lanes(int v)
 {
-    const int v = ops.lvl[t][m + 1].pos[q];
-    return kDeep ? ops.lvl[t][m + 2].pos[v] : v;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);    // row_shr:1, 2, 4, 8: inside 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);    // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);    // row_bcast:31 into rows 2 and 3
+    return lane_value(v, NACHO_WAVE - 1);
+}
+template <int kCtrl, int kRowMask> __device__ inline int moved(int none, int v)
+{
+    return __builtin_amdgcn_update_dpp(none, v, kCtrl, kRowMask, 0xf, false);
+}
+template <int kCtrl, int kRowMask> __device__ inline long long moved(long long none, long long v)
+{
+    const unsigned lo = (unsigned)moved<kCtrl, kRowMask>((int)(unsigned)none, (int)(unsigned)v);
+    return ((long long)moved<kCtrl, kRowMask>((int)(none >> 32), (int)(v >> 32)) << 32) | (long long)lo;
+}
+// `none`: no lane's value comes after it (max) / before it (min).
+template <bool kMax, typename C> __device__ inline C extreme_of_lanes(C v, C none)
+{
+    auto fold = [&](C o) { v = (kMax ? o > v : o < v) ? o : v; };
+    fold(moved<0x111, 0xf>(none, v));
+    fold(moved<0x112, 0xf>(none, v));
+    fold(moved<0x114, 0xf>(none, v));
+    fold(moved<0x118, 0xf>(none, v));
+    fold(moved<0x142, 0xa>(none, v));
+    fold(moved<0x143, 0xc>(none, v));
+    return lane_value(v, NACHO_WAVE - 1);
 }
 
 // Dense level (level 0 of CSR operands): position == coordinate, cost through
-// the next level's pos array.  64-ary search over [0, N].
+// the next level's pos array.  64-ary search over [0, N].  Returns the row, and its cost in c_low.
 template <int K>
-__device__ __forceinline__ LevelResult dense_search(const DevOperands &ops, int m, int64_t R, int *p)
+__device__ __forceinline__ int64_t dense_search(const DevOperands &ops, int64_t R, int64_t &c_low)
 {
     const int lane = lane_id();
     const int k = ops.k;
-    const int64_t N = level0_extent(ops);
-    int64_t low = 0, high = N, c_low = 0;
+    int64_t low = 0, high = level0_extent(ops);
+    c_low = 0;
     while (low < high) {
         const int64_t span = high - low;
         const int64_t step = (span + NACHO_WAVE - 1) / NACHO_WAVE;
@@ -82,7 +115,7 @@ __device__ __forceinline__ LevelResult dense_search(const DevOperands &ops, int 
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             if (t >= k) break;
-            const int32_t *pos = ops.lvl[t][m + 1].pos;
+            const int32_t *pos = ops.lvl[t][1].pos;
             c += (int64_t)(pos[x] - pos[0]);
         }
         const unsigned long long ok = __ballot(c <= R);   // a prefix of the lanes (monotone cost)
@@ -93,459 +126,399 @@ __device__ __forceinline__ LevelResult dense_search(const DevOperands &ops, int 
         }
         if (n < NACHO_WAVE) high = lane_value((long long)x, n) - 1;
     }
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        if (t >= k) break;
-        p[t] = (int)low;
-    }
-    LevelResult r;
-    r.x = low;
-    r.c = c_low;
-    return r;
+    return low;
 }
 
-// (In all searches of a compressed level, sh[t] is added to operand t's positions
-// where its coordinates are read: the offset between the positions the cost is
-// counted in and the storage of a remapped operand's row, 0 otherwise.)
-//
-// 64-ary search over coordinates with one lower-bound search per operand and
-// probe inside tracked windows [wl, wh] (the specialised search of Section
-// 4.2.3, 64 probes per round).  Lower bounds are clamped to the windows, which
-// is exact as long as the windows bracket the boundary's positions.  c_low is
-// the cost at coordinate 0 under that clamping.  Used when the sampled search
-// below stops making progress.
-template <bool kLast, int K, class Acc = PlainCoords, bool kDeep = false>
-__device__ __forceinline__ LevelResult tracked_search(const DevOperands &ops, int m, int64_t R, const int *base,
-                                      int *wl, int *wh, int64_t c_low, int *p, const int *sh)
-{
-    const int lane = lane_id();
-    const int k = ops.k;
-    int64_t low = 0, high = Acc::extent(ops, m);
-    while (low < high) {
-        const int64_t span = high - low;
-        const int64_t step = (span + NACHO_WAVE - 1) / NACHO_WAVE;
-        int64_t x = low + (int64_t)(lane + 1) * step;
-        if (x > high) x = high;
-        int ip[K];
-        int64_t c = 0;
+// ---- compressed levels ---------------------------------------------------------
+// The lanes of a wavefront are split into k groups of 64 / k, one operand each: lane i of a group holds that operand's
+// window, and its i-th sample of it.  What bounds a search is the chain of rounds -- a load each, and some 300 instructions
+// -- and, with thousands of boundaries in flight, the cache lines it asks for.  (A lane for one of 64 samples of EVERY
+// operand asks for k times the lines, keeps k times the state, and has k (k - 1) ranks to find instead of k - 1: three
+// operands of 10M, 1M and 100k entries 19.2 us, like this 12.8; with that many operands that it searched coordinates instead, with
+// binary searches inside: five vectors of 2.5M 119 and 21.7, eight coordinate lists of 1.4M 256 and 65, eight tensors
+// of 1M 100 and 30.)
+template <int K> struct Group {
+    int k, size;               // groups, lanes of one
+    int t, i, first;           // this lane's group, its place in it, the group's first lane (a lane left over: i >= size)
+    unsigned long long lanes;  // of the group
+    __device__ explicit Group(int k_) : k(k_)
+    {
+        const int lane = lane_id();
+        size = NACHO_WAVE;                     // (64 / k without a division)
+        if (K > 1) size = k == 1 ? 64 : (k == 2 ? 32 : (k == 3 ? 21 : 16));
+        if (K > 4 && k > 4) size = k == 5 ? 12 : (k == 6 ? 10 : (k == 7 ? 9 : 8));
+        t = 0;
 #pragma unroll
-        for (int t = 0; t < K; ++t) {
-            if (t >= k) break;
-            const int q = lower_bound_level<Acc>(ops, t, m, sh[t], wl[t], wh[t], x);
-            ip[t] = q;
-            c += kLast ? (int64_t)(q - base[t]) : (int64_t)(cost_at<kDeep>(ops, t, m, q) - base[t]);
-        }
-        const unsigned long long ok = __ballot(c <= R);
-        const int n = __popcll(ok);
-        if (n > 0) {
-            low = lane_value((long long)x, n - 1);
-            c_low = lane_value((long long)c, n - 1);
-        }
-        if (n < NACHO_WAVE) high = lane_value((long long)x, n) - 1;
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
-            if (t >= k) break;
-            const int lo_new = lane_value(ip[t], n > 0 ? n - 1 : 0);
-            const int hi_new = lane_value(ip[t], n < NACHO_WAVE ? n : NACHO_WAVE - 1);
-            if (n > 0) wl[t] = lo_new;
-            if (n < NACHO_WAVE) wh[t] = hi_new;
-        }
+        for (int u = 1; u < K; ++u) t += (u < k ? 1 : 0) & (lane >= u * size ? 1 : 0);
+        first = t * size;
+        i = lane - first;
+        lanes = low_bits(first + size) & ~low_bits(first);
     }
+    // the value the group's lane `at` holds
+    template <typename C> __device__ C from(C v, int at) const { return value_from(v, first + at); }
+    __device__ int count(unsigned long long mask) const { return __popcll(mask & lanes); }
+    __device__ bool any(unsigned long long mask) const { return (mask & lanes) != 0ull; }
+    // sum of the groups' values (the same in all lanes of a group)
+    __device__ int sum(int v) const
+    {
+        if (K > 4) return sum_of_lanes(i == 0 ? v : 0);
+        int x = lane_value(v, 0);
 #pragma unroll
-    for (int t = 0; t < K; ++t) {
-        if (t >= k) break;
-        p[t] = wl[t];
+        for (int u = 1; u < K; ++u)
+            if (u < k) x += lane_value(v, u * size);
+        return x;
     }
-    LevelResult r;
-    r.x = low;
-    r.c = c_low;
-    return r;
-}
-
-// How many of the wavefront's 64 values xs -- ascending with the lane, lanes past the valid ones hold
-// the largest value there is -- are smaller than this lane's key.  Three levels of a 4-ary search: the
-// values of lanes 15, 31, 47 (through scalar registers) pick sixteen lanes, three shuffles their
-// quarter, three more count inside it; the last lane of a quarter is a pivot that was compared
-// before, but for lane 63.  (A binary search is a chain of seven dependent shuffles and twice the
-// instructions; these rank searches were half of a round's time, and the kernel is bound by the
-// instructions its wavefronts issue.)
-template <typename CoordT>
-__device__ inline int rank_among(CoordT xs, CoordT key)
-{
-    int sixteen = 0;
-#pragma unroll
-    for (int g = 0; g < 3; ++g) sixteen += lane_value(xs, 16 * g + 15) < key ? 1 : 0;
-    const int b1 = sixteen * 16;
-    int quarter = 0;
-#pragma unroll
-    for (int g = 0; g < 3; ++g) quarter += __shfl(xs, b1 + 4 * g + 3, NACHO_WAVE) < key ? 1 : 0;
-    const int b2 = b1 + quarter * 4;
-    int n = b2 + (lane_value(xs, NACHO_WAVE - 1) < key ? 1 : 0);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) n += __shfl(xs, b2 + i, NACHO_WAVE) < key ? 1 : 0;
-    return n;
-}
-
-// Search windows of one compressed level: for operand t the boundary's position
-// lies in [l, h]; cl/ch are the costs of the entries before l / before h,
-// relative to the segment start (base = cost offset of the segment start).
-template <int K>
-struct Windows {
-    int base[K], l[K], h[K], cl[K], ch[K];
 };
 
-template <bool kLast, int K, bool kDeep = false>
-__device__ inline void windows_init(const DevOperands &ops, int m, const int *seg_lo, const int *seg_hi,
-                                    Windows<K> &W)
+// How many of the `size` values of the group that starts at lane b -- ascending, the ones past the valid ones hold the
+// largest value there is -- are smaller than this lane's key.  Four ways a step: two or three dependent shuffles.
+template <int K, typename C> __device__ inline int rank_in(C v, int b, int size, C key)
 {
+    int c = 0;
+    auto step = [&](auto ways_tag, auto stride_tag) {
+        constexpr int kWays = decltype(ways_tag)::value, kStride = decltype(stride_tag)::value;
+        C x[kWays];
 #pragma unroll
-    for (int t = 0; t < K; ++t) {
-        W.l[t] = W.h[t] = W.cl[t] = W.ch[t] = W.base[t] = 0;   // operands beyond k: empty, no cost
-        if (t < ops.k) {
-            W.l[t] = seg_lo[t];
-            W.h[t] = seg_hi[t];
-            if (kLast) {
-                W.base[t] = seg_lo[t];
-                W.ch[t] = seg_hi[t] - seg_lo[t];
-            } else {
-                W.base[t] = cost_at<kDeep>(ops, t, m, seg_lo[t]);
-                W.ch[t] = cost_at<kDeep>(ops, t, m, seg_hi[t]) - W.base[t];
-            }
+        for (int g = 0; g < kWays; ++g) {
+            const int at = c + (g + 1) * kStride;
+            x[g] = value_from(v, b + (at < size ? at : size) - 1);
         }
+        int more = 0;
+#pragma unroll
+        for (int g = 0; g < kWays; ++g) more += c + (g + 1) * kStride <= size && x[g] < key ? 1 : 0;
+        c += more * kStride;
+    };
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    typedef std::integral_constant<int, 3> Three;
+    if constexpr (K <= 2) {                    // up to 32
+        step(Two(), std::integral_constant<int, 16>());
+        step(Three(), std::integral_constant<int, 4>());
+        step(Three(), One());
+    } else if constexpr (K <= 4) {             // up to 21
+        step(Two(), std::integral_constant<int, 8>());
+        step(Three(), Two());
+        step(One(), One());
+    } else {                                   // up to 12; two ways a step: the other groups' searches hide each other
+        step(One(), std::integral_constant<int, 8>());
+        step(One(), std::integral_constant<int, 4>());
+        step(One(), Two());
+        step(One(), One());
     }
+    return c;
 }
 
-// Compressed level.  Requires 0 <= R_lo <= R_hi < total cost of the segments
-// (interior queries), so the boundaries are stored coordinates.  Invariant of
-// the windows [l, h]: for every query R in [R_lo, R_hi] the position of its
-// boundary coordinate x in operand t lies in [l_t, h_t], and so does the
-// position of x + 1.  With that, clamping any coordinate's lower bounds into
-// the windows preserves "cost <= R  <=>  coordinate <= x".
-// Runs until the boundary of query R is found.
-template <bool kLast, int K, class Acc = PlainCoords, bool kDeep = false>
-__device__ __forceinline__ LevelResult sampled_search(const DevOperands &ops, int m, int64_t R64, Windows<K> &W,
-                                                      int *p, const int *sh)
+// Where sample i of `size` lies in a window of w > size entries when the coordinate is expected `at` entries in: the
+// window's ends are samples, the others lie at distances from `at` that grow geometrically, from half the deviation that
+// positions have when the operands' entries are spread alike (at most sqrt(w) / 4) to the window's ends.  An
+// expectation that is off by e leaves a window of about e; entries that are spread alike (the columns of a row, the
+// coordinates of a vector) go from ten million to a few thousand to under a hundred.  `even`: evenly spaced.
+__device__ inline int aimed_sample(int i, int size, int w, float at, bool even)
 {
-    typedef typename Acc::type CoordT;
-    // costs, positions and coordinates all fit 32 bits (the operands hold fewer than
-    // 2^31 entries together; INT32_MAX is no coordinate)
-    const int R_lo = (int)R64, R_hi = (int)R64;      // (the bounds below are written for a range of queries)
-    const int lane = lane_id();
-    const int k = ops.k;
-    int base[K], l[K], h[K], cl[K], ch[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        base[t] = W.base[t]; l[t] = W.l[t]; h[t] = W.h[t]; cl[t] = W.cl[t]; ch[t] = W.ch[t];
+    // (the reciprocals need not be exact: any place in the window will do)
+    const float inv = 2.0f * __builtin_amdgcn_rcpf((float)(size - 1)), all = (float)w;
+    const float e = (float)i * inv - 1.0f;             // -1 .. 1
+    float x = 0.5f * (all + all * e);
+    if (!even) {
+        const float left = fmaxf(at, 1.0f), right = fmaxf(all - at, 1.0f);
+        const float near = fmaxf(0.5f * __builtin_amdgcn_sqrtf(left * right * __builtin_amdgcn_rcpf(left + right)), 0.5f);
+        const float side = fmaxf(e < 0.0f ? left : right, near);
+        const float off = near * __builtin_amdgcn_exp2f(fabsf(e) * __builtin_amdgcn_logf(side * __builtin_amdgcn_rcpf(near)));
+        x = fabsf(e) * (float)size < 0.5f ? at : at + copysignf(off, e);
     }
-    LevelResult r;
-    r.x = 0;
-    r.c = 0;
-    // position of sample j of a window (l, w): every entry when w <= 64, else 64 evenly spaced ones
-    // (j * w / 64 with w = 128 q + r is 2 j q + j r / 64: two 24-bit products, no 64-bit one)
-    auto sample_pos = [](int lo, int w, int j) -> int {
-        const int spread = 2 * __mul24(j, w >> 7) + (__mul24(j, w & 127) >> 6);
-        return lo + (w <= NACHO_WAVE ? j : spread);
+    int s = (int)fminf(fmaxf(x, 0.0f), fminf(all, 2147483520.0f));
+    s = s < w - 1 ? s : w - 1;
+    return i == 0 ? 0 : (i == size - 1 ? w - 1 : s);
+}
+
+// The first position in [a, z) of the group's operand that is not `before` what is looked for, z if all are: the probes of
+// a round are spread evenly over the group's lanes, those before it are a prefix of them.
+template <int K, class Before> __device__ inline int group_lower_bound(const Group<K> &g, int a, int z, Before &&before)
+{
+    while (__ballot(a < z) != 0ull) {
+        // (unsigned: probes behind z may lie past 2^31)
+        const unsigned stride = (unsigned)(z - a + g.size - 1) / (unsigned)g.size, from = (unsigned)a;
+        const unsigned probe = from + (unsigned)(g.i + 1) * stride - 1u;
+        const bool yes = g.i < g.size && a < z && probe < (unsigned)z && before((int)probe);
+        const unsigned m = (unsigned)g.count(__ballot(yes));
+        if (a < z) {
+            const unsigned a_new = from + m * stride, z_new = from + (m + 1u) * stride - 1u;
+            z = m < (unsigned)g.size && z_new < (unsigned)z ? (int)z_new : z;
+            a = a_new < (unsigned)z ? (int)a_new : z;
+        }
+    }
+    return a;
+}
+
+// What a level's search finds.
+template <class Acc> struct LevelFound {
+    typename Acc::type x;      // the boundary's coordinate
+    int c;                     // cost of the level's entries before it
+    // in the lanes of every group:
+    int p;                     // the operand's first entry that is not before x
+    bool present;              // ... is at x
+    int lo, hi;                // (not on the last level) the entry's segment one level down, empty if it is not at x
+    int deep_lo, deep_hi;      // (kDepth 2) its segment two levels down
+    int row_from;              // (pairs) no entry of x's row lies before this position
+};
+
+// A compressed level.  kDepth: 0 on the last level, where an entry costs 1; 1 where it costs the entries of its segment one
+// level down (pos_1); 2 those two levels down (pos_1, then pos_2).  [l, h): the operand's entries of the level, in
+// the lanes of its group; `total` their cost, all operands together; 0 <= R < total, so the boundary is a
+// stored coordinate.  sh: what is added to positions where coordinates are read (a remapped operand's row).
+//
+// Invariant: the boundary coordinate x and x + 1 have their positions in [l, h] in every operand.  A round looks at the
+// samples of every window.  A sample's position is exact in its own operand; in the others it lies between the two samples
+// around it, which bounds its cost from both sides.  The largest sample whose cost is at most R for sure, and the smallest
+// whose cost is above it for sure, cut every window.  Once a window has no more entries than its group has lanes every entry is
+// a sample; when that holds for all, the costs are exact and the round returns the boundary.
+// A round that does not narrow the windows to a half (data that is nothing like evenly spread) is followed by
+// one with evenly spaced samples, and if that does not narrow them to three quarters, by one that looks up the exact
+// cost of the middle entry of the largest window and so halves that one: the search ends for any operands.
+// (Three rounds take a sixteenth off all windows together in the worst case: 2^31 entries in 8 operands take a thousand.)
+constexpr int kMostRounds = 1100;
+
+template <int K, class Acc, int kDepth>
+__device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const Acc &crd, Ints32 pos_1, Ints32 pos_2, int l,
+                                                        int h, int R, int total, int sh)
+{
+    typedef typename Acc::type C;
+    constexpr bool kLast = kDepth == 0;
+    LevelFound<Acc> found;
+    // what an entry's position stands for: the cost before it, not yet relative to the segment's start
+    auto cost_from = [&](int q, int &below) -> int {
+        if (kLast) return below = q;
+        below = pos_1[q];
+        return kDepth == 2 ? pos_2[below] : below;
     };
-    int prev_total = INT32_MAX;
-    for (;;) {
-        CoordT v[K];
-        int ca[K], cb[K], w[K], mt[K];
-        bool all_small = true;
-        int total = 0;
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
-            w[t] = h[t] - l[t];
-            mt[t] = w[t] < NACHO_WAVE ? w[t] : NACHO_WAVE;
-            total += w[t];
-            if (w[t] > NACHO_WAVE) all_small = false;
-        }
-        if (!all_small && total >= prev_total) {
-            int64_t c0 = 0;
-#pragma unroll
-            for (int t = 0; t < K; ++t) c0 += cl[t];
-            return tracked_search<kLast, K, Acc, kDeep>(ops, m, R64, base, l, h, c0, p, sh);
-        }
-        prev_total = total;
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
-            const bool valid = lane < mt[t];
-            const int s = valid ? sample_pos(l[t], w[t], lane) : l[t];
-            v[t] = Acc::kNone;
-            cb[t] = s - base[t];
-            ca[t] = s + 1 - base[t];
-            if (t < k) {
-                if (valid) v[t] = Acc::load(ops, t, m, s + sh[t]);
-                if (!kLast) {
-                    cb[t] = valid ? cost_at<kDeep>(ops, t, m, s) - base[t] : 0;
-                    ca[t] = valid ? cost_at<kDeep>(ops, t, m, s + 1) - base[t] : 0;
-                }
+    int below_l = l, below_h = h;              // (kDepth 2) pos_1 of l and h
+    int base = cost_from(l, below_l), cl = base, ch = cost_from(h, below_h);
+    int row_from = l;
+    int W = g.sum(h - l);
+    float share = (float)R * __builtin_amdgcn_rcpf((float)total);      // of the windows' cost that lies before the boundary
+    bool even = false;
+    for (int round = 0;; ++round) {
+        const int w = h - l, n = w < g.size ? w : g.size;
+        const bool small = __ballot(w > g.size && g.i < g.size) == 0ull;
+        const bool valid = g.i < n;
+        int s = g.i;
+        if (!small) {
+            const bool wide = w > g.size && valid;
+            if (wide) s = aimed_sample(g.i, g.size, w, share * (float)w, even);
+            if (__ballot(wide && g.i > 0 && s < lane_left(s)) != 0ull) {      // (rounding: samples have to ascend)
+                if (wide) s = aimed_sample(g.i, g.size, w, 0.0f, true);
             }
         }
-
-        // Bounds of the cost of every sampled coordinate, from the rank lo_t[u] of the sample
-        // among the samples of every other operand u.  Inside one operand the
-        // samples ascend with the lane and so do both bounds, so the samples whose
-        // upper bound is within the query are a prefix of the lanes and those whose
-        // lower bound exceeds it a suffix: one ballot each finds the largest / smallest
-        // such sample, no reduction over the wavefront.
-        CoordT vminus = -1, vplus = Acc::kNone;
-        // Until the windows are small one operand's samples are bounded per round, those of the widest window:
-        // they are the ones that narrow the total, and K - 1 rank searches take a third of the instructions
-        // of K (K - 1) (three operands; the chain of them is what a boundary takes).  Its neighbours' windows shrink
-        // to what overlaps.
-        auto bounds_of_widest = [&]() {
-            int wide = 0, w_wide = w[0];
-#pragma unroll
-            for (int u = 1; u < K; ++u)
-                if (w[u] > w_wide) { wide = u; w_wide = w[u]; }
-            CoordT vp = v[0];
-            int cp = cb[0];
-#pragma unroll
-            for (int u = 1; u < K; ++u)
-                if (u == wide) { vp = v[u]; cp = cb[u]; }
-            int glo = cp, ghi = cp;
-#pragma unroll
-            for (int u = 0; u < K; ++u) {
-                if (u == wide || mt[u] == 0) {         // (uniform)
-                    if (u != wide) { glo += cl[u]; ghi += cl[u]; }
-                    continue;
-                }
-                const int c = rank_among<CoordT>(v[u], vp);
-                const int a = __shfl(ca[u], (c - 1) & (NACHO_WAVE - 1), NACHO_WAVE);
-                const int bq = __shfl(cb[u], c & (NACHO_WAVE - 1), NACHO_WAVE);
-                glo += c == 0 ? cl[u] : a;
-                ghi += c == mt[u] ? ch[u] : bq;
+        s = valid ? l + s : h;
+        C v = Acc::kNone;
+        int cb, ca, below_b = 0, below_a = 0;  // cost before and behind the sample
+        if (valid) v = crd.load(s + sh);
+        if (kLast) { cb = s; ca = valid ? s + 1 : s; }
+        else {
+            cb = ca = 0;
+            if (valid) {
+                cb = cost_from(s, below_b);
+                ca = cost_from(s + 1, below_a);
             }
-            const int n_le = __popcll(__ballot(ghi <= R_lo)), n_in = __popcll(__ballot(glo <= R_hi));   // (64 samples)
-            if (n_le > 0) vminus = lane_value(vp, n_le - 1);
-            if (n_in < NACHO_WAVE) vplus = lane_value(vp, n_in);
-        };
-        auto bounds_of = [&](int t, const int (&lo_t)[K]) {
-            int glo = cb[t], ghi = cb[t];           // own operand: the sample's position is exact
-#pragma unroll
-            for (int u = 0; u < K; ++u) {
-                if (u == t) continue;
-                const int c = lo_t[u];              // u's samples below this coordinate
-                // cost before u's sample c - 1 ... before its sample c: what the lanes c - 1 and c hold
-                // (with positions as costs, the last level, these are the samples' positions)
-                const int a = __shfl(ca[u], (c - 1) & (NACHO_WAVE - 1), NACHO_WAVE);
-                const int bq = __shfl(cb[u], c & (NACHO_WAVE - 1), NACHO_WAVE);
-                const int costA = c == 0 ? cl[u] : a;
-                const int costB = c == mt[u] ? ch[u] : bq;
-                glo += costA;
-                ghi += costB;
-            }
-            const bool valid = lane < mt[t];
-            const int n_le = __popcll(__ballot(valid && ghi <= R_lo));   // lanes 0 .. n_le - 1
-            const int n_in = __popcll(__ballot(valid && glo <= R_hi));   // lanes n_in .. mt - 1 are after
-            if (n_le > 0) {
-                const CoordT cand = lane_value(v[t], n_le - 1);
-                vminus = cand > vminus ? cand : vminus;  // largest sample not after the first boundary
-            }
-            if (n_in < mt[t]) {
-                const CoordT cand = lane_value(v[t], n_in);
-                vplus = cand < vplus ? cand : vplus;     // smallest sample after the last boundary
-            }
-        };
-        // rank of every sample of t among the samples of u (lanes past mt[u] hold kNone, which is
-        // smaller than no key: a rank never exceeds mt[u]); one operand at a time, ranks and bounds
-        if (!all_small) bounds_of_widest();
-        else
-#pragma unroll
-            for (int t = 0; t < K; ++t) {
-                int lo_t[K];
-#pragma unroll
-                for (int u = 0; u < K; ++u) lo_t[u] = u == t ? 0 : rank_among<CoordT>(v[u], v[t]);
-                bounds_of(t, lo_t);
-            }
-
-#pragma unroll
-        for (int u = 0; u < K; ++u) {
-            const bool in = lane < mt[u];
-            int nl = l[u], ncl = cl[u], nh = h[u], nch = ch[u];
-            if (vminus >= 0) {
-                const int c = __popcll(__ballot(in && v[u] < vminus));
-                const bool eq = __ballot(in && v[u] == vminus) != 0ull;
-                const int sc = c < mt[u] ? sample_pos(l[u], w[u], c) : h[u];
-                const int sp = c > 0 ? sample_pos(l[u], w[u], c - 1) + 1 : l[u];
-                nl = eq ? sc : sp;
-                if (kLast) ncl = nl - base[u];
-                else {
-                    const int e = lane_value(cb[u], c & (NACHO_WAVE - 1));
-                    const int a = lane_value(ca[u], (c - 1) & (NACHO_WAVE - 1));
-                    ncl = eq ? e : (c == 0 ? cl[u] : a);
-                }
-            }
-            if (vplus != Acc::kNone) {
-                const int c = __popcll(__ballot(in && v[u] < vplus));
-                nh = c == mt[u] ? h[u] : sample_pos(l[u], w[u], c);
-                if (kLast) nch = nh - base[u];
-                else {
-                    const int e = lane_value(cb[u], c & (NACHO_WAVE - 1));
-                    nch = c == mt[u] ? ch[u] : e;
-                }
-            }
-            l[u] = nl; cl[u] = ncl; h[u] = nh; ch[u] = nch;
+            cb = valid ? cb : ch;
+            ca = valid ? ca : ch;
         }
-        if (all_small) {
-            if (vminus < 0) {                           // cannot happen for an interior query
-                int64_t c0 = 0;
+        // bounds of the sample's cost (no branches: the searches in the other groups hide each other's latency)
+        int lo_cost = cb - base, hi_cost = lo_cost;
+        int c[K], b[K];
 #pragma unroll
-                for (int t = 0; t < K; ++t) {
-                    l[t] = W.l[t]; h[t] = W.h[t];
-                    c0 += W.cl[t];
-                }
-                return tracked_search<kLast, K, Acc, kDeep>(ops, m, R64, base, l, h, c0, p, sh);
-            }
-            r.x = vminus;
+        for (int r = 1; r < K; ++r) {
+            b[r] = g.first + r * g.size;       // the first lane of another group
+            b[r] = g.t + r >= g.k ? b[r] - g.k * g.size : b[r];
+            b[r] = r < g.k ? b[r] : g.first;
+            c[r] = rank_in<K>(v, b[r], g.size, v);
+        }
 #pragma unroll
-            for (int t = 0; t < K; ++t) {
-                if (t < k) p[t] = l[t];
-                r.c += cl[t];
+        for (int r = 1; r < K; ++r) {
+            // (the first sample is the window's first entry, the last sample of a full group its last one)
+            const int before = value_from(ca - base, b[r] + (c[r] > 0 ? c[r] - 1 : 0));
+            const int after = value_from(cb - base, b[r] + (c[r] < g.size ? c[r] : g.size - 1));
+            lo_cost += r >= g.k ? 0 : (c[r] == 0 ? after : before);
+            hi_cost += r >= g.k ? 0 : (c[r] == g.size ? before : after);
+        }
+        const C none_below = C(-1), none_above = Acc::kNone;
+        const C vminus = extreme_of_lanes<true, C>(valid && hi_cost <= R ? v : none_below, none_below);
+        const C vplus = extreme_of_lanes<false, C>(valid && lo_cost > R ? v : none_above, none_above);
+        // cut the windows
+        const int c1 = g.count(__ballot(valid && v < vminus));
+        const bool at_it = g.any(__ballot(valid && v == vminus));
+        const int c2 = g.count(__ballot(valid && v < vplus));
+        const int i1 = c1 < g.size ? c1 : g.size - 1, i0 = c1 > 0 ? c1 - 1 : 0, i2 = c2 < g.size ? c2 : g.size - 1;
+        if constexpr (Acc::kPairs) {
+            const int cr = g.count(__ballot(valid && (v >> 32) < (vminus >> 32)));
+            const int to = g.from(s, cr > 0 ? cr - 1 : 0) + 1;
+            row_from = cr > 0 ? to : row_from;
+        }
+        const int s1 = g.from(s, i1), s0 = g.from(s, i0) + 1, s2 = g.from(s, i2);
+        const int l_new = at_it ? s1 : (c1 > 0 ? s0 : l), h_new = c2 == n ? h : s2;
+        int cl_new = l_new, ch_new = h_new;
+        if (!kLast) {
+            const int e1 = g.from(cb, i1), e0 = g.from(ca, i0), e2 = g.from(cb, i2);
+            cl_new = at_it ? e1 : (c1 > 0 ? e0 : cl);
+            ch_new = c2 == n ? ch : e2;
+        }
+        if (kDepth == 2) {
+            const int d1 = g.from(below_b, i1), d0 = g.from(below_a, i0), d2 = g.from(below_b, i2);
+            below_l = at_it ? d1 : (c1 > 0 ? d0 : below_l);
+            below_h = c2 == n ? below_h : d2;
+        }
+        if (small) {
+            found.x = vminus;
+            found.c = g.sum(cl_new - base);
+            found.p = l_new;
+            found.present = at_it;
+            found.row_from = row_from;
+            found.lo = found.hi = found.deep_lo = found.deep_hi = 0;
+            if (!kLast) {
+                const int behind = g.from(ca, i1), below = g.from(below_a, i1);
+                found.lo = kDepth == 2 ? below_l : cl_new;
+                found.hi = at_it ? (kDepth == 2 ? below : behind) : found.lo;
+                found.deep_lo = cl_new;
+                found.deep_hi = at_it ? behind : cl_new;
             }
-            return r;
+            return found;
+        }
+        l = l_new; cl = cl_new;
+        h = h_new > l_new ? h_new : l_new; ch = ch_new;        // (never below l, but for operands that are not sorted)
+        int W_new = g.sum(h - l);
+        const bool slow = even ? W_new > W - (W >> 2) : W_new > (W >> 1);
+        if (slow && even) {
+            // the middle entry of the largest window, looked up in all of them
+            const int wide = extreme_of_lanes<true, int>(g.i < g.size ? h - l : -1, -1);
+            const int owner = __ffsll((long long)__ballot(g.i < g.size && h - l == wide)) - 1;
+            C mid = Acc::kNone;
+            if (h > l) mid = crd.load(l + ((h - l) >> 1) + sh);
+            mid = lane_value(mid, owner);
+            const int a = group_lower_bound<K>(g, l, h, [&](int at) { return crd.load(at + sh) < mid; });
+            int below_at = 0;
+            const int cost = cost_from(a, below_at);
+            if (g.sum(cost - base) <= R) { l = a; cl = cost; below_l = below_at; }
+            else { h = a; ch = cost; below_h = below_at; }
+            W_new = g.sum(h - l);
+        }
+        even = slow && !even;
+        share = (float)(R - g.sum(cl - base)) * __builtin_amdgcn_rcpf((float)(kLast ? W_new : g.sum(ch - cl)));
+        W = W_new;
+        if (round >= kMostRounds) {
+            // (operands that are not sorted, which nothing has to come of but an end: some position of the windows)
+            found.x = vminus > none_below ? vminus : C(0);
+            found.c = R;
+            found.p = l;
+            found.present = false;
+            found.row_from = row_from < l ? row_from : l;
+            found.lo = found.hi = kDepth == 2 ? below_l : cl;
+            found.deep_lo = found.deep_hi = cl;
+            return found;
         }
     }
 }
 
 // Two operands on the last level, where the cost is the number of entries: the boundary of query R is the element
 // of rank R of the two merged segments, so the search is for the split of the first R merged entries (the first
-// operand first on ties) -- i of them from the first operand for the largest i with A[i - 1] <= B[R - i] -- and every
-// lane tries one i per round.  Two loads and a ballot a round; the sampled search spends a few hundred
-// instructions on the ranks and bounds that more operands need (DCSR + DCSR, 8192 boundaries: 36 against 28 us).
+// operand first on ties) -- i of them from the first operand for the largest i with A[i - 1] <= B[R - i].  Two loads and a
+// ballot a round.  Sixteen candidates, placed around the expected split as the samples above are (its first
+// expectation: the operands' shares; later ones from how far apart A and B are at the ends of the range); once the
+// range is a few cache lines every lane has one.  (10M + 10M entries, 8192 boundaries, evenly spaced candidates: 64 a round 46
+// us, 16 24, 8 19 -- with thousands of boundaries in flight the lines are what takes the time, a line a candidate, with few of
+// them the rounds are.  Two DCSR matrices of 20M, 7218 boundaries, both levels: 29.2 us with eight evenly spaced ones, 21.0 like
+// this.)
 // Requires both segments non-empty and 0 <= R < their total length.
-template <int K, class Acc>
-__device__ __forceinline__ LevelResult split_search(const DevOperands &ops, int m, int R, const int *seg_lo,
-                                                    const int *seg_hi, int *p, const int *sh, int fan)
+template <class Acc>
+__device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const Acc &A, const Acc &B, int l, int h, int R, int sh)
 {
-    static_assert(K == 2, "two operands");
-    typedef typename Acc::type CoordT;
+    typedef typename Acc::type C;
     const int lane = lane_id();
-    const int a0 = seg_lo[0], b0 = seg_lo[1], na = seg_hi[0] - a0, nb = seg_hi[1] - b0;
+    const int a0 = lane_value(l, 0), b0 = lane_value(l, NACHO_WAVE / 2);
+    const int na = lane_value(h, 0) - a0, nb = lane_value(h, NACHO_WAVE / 2) - b0;
+    const int a_at0 = a0 + lane_value(sh, 0), b_at0 = b0 + lane_value(sh, NACHO_WAVE / 2);     // where the segments are stored
     int lo = R > nb ? R - nb : 0, hi = R < na ? R : na;
+    float at = (float)R * (float)na * __builtin_amdgcn_rcpf((float)na + (float)nb) - (float)lo;
+    bool even = Acc::kPairs;                           // (rows of unequal length: an expectation is worth nothing)
+    constexpr int kShare = 4, kWays = NACHO_WAVE / kShare;     // lanes that share a candidate read the same words
     while (lo < hi) {
-        // 64 >> fan candidates a round (lanes that share one read the same words), all 64 once they share cache lines
-        const int f = hi - lo > 256 ? fan : 0;
-        const int way = lane >> f, ways = NACHO_WAVE >> f;
-        const int step = (hi - lo + ways - 1) >> (6 - f);
-        int i = lo + (way + 1) * step;
-        i = i < hi ? i : hi;
+        const int w = hi - lo;                         // candidates lo + 1 .. hi
+        int i;
+        if (w <= 256) i = (lane + 1) * ((w + NACHO_WAVE - 1) / NACHO_WAVE);
+        else {
+            i = 1 + aimed_sample(lane / kShare, kWays, w, at, even);
+            if (__ballot(lane > 0 && i < lane_left(i)) != 0ull) i = 1 + aimed_sample(lane / kShare, kWays, w, at, true);
+        }
+        i = lo + (i < w ? i : w);
         const int j = R - i;                           // (i <= R, and i >= R - nb: 0 <= j <= nb)
-        const CoordT av = Acc::load(ops, 0, m, a0 + i - 1 + sh[0]);
-        const CoordT bv = j < nb ? Acc::load(ops, 1, m, b0 + j + sh[1]) : Acc::kNone;
+        const C av = A.load(a_at0 + i - 1);
+        const C bv = j < nb ? B.load(b_at0 + j) : Acc::kNone;
         const int n = __popcll(__ballot(av <= bv));    // a prefix of the lanes
+        const float apart = Acc::apart(av, bv);        // >= 0 for the prefix
+        float f = 0.5f;
+        if (n > 0 && n < NACHO_WAVE) {
+            const float below = __int_as_float(lane_value(__float_as_int(apart), n - 1));
+            f = below * __builtin_amdgcn_rcpf(below - __int_as_float(lane_value(__float_as_int(apart), n)));
+        }
         const int lo_new = lane_value(i, n > 0 ? n - 1 : 0), hi_new = lane_value(i, n < NACHO_WAVE ? n : NACHO_WAVE - 1);
         if (n > 0) lo = lo_new;
         if (n < NACHO_WAVE) hi = hi_new - 1;
+        even = Acc::kPairs || (!even && hi - lo > w >> 3);
+        at = f * (float)(hi - lo);
     }
     const int i = lo, j = R - lo;
     // A[i - 1], A[i], B[j]: lanes 0, 1, 2
-    CoordT v = Acc::kNone;
-    if (lane == 0 && i > 0) v = Acc::load(ops, 0, m, a0 + i - 1 + sh[0]);
-    if (lane == 1 && i < na) v = Acc::load(ops, 0, m, a0 + i + sh[0]);
-    if (lane == 2 && j < nb) v = Acc::load(ops, 1, m, b0 + j + sh[1]);
-    const CoordT a_before = lane_value(v, 0), a_at = lane_value(v, 1), b_at = lane_value(v, 2);
-    const CoordT x = a_at < b_at ? a_at : b_at;
+    C v = Acc::kNone;
+    if (lane == 0 && i > 0) v = A.load(a_at0 + i - 1);
+    if (lane == 1 && i < na) v = A.load(a_at0 + i);
+    if (lane == 2 && j < nb) v = B.load(b_at0 + j);
+    const C a_before = lane_value(v, 0), a_at = lane_value(v, 1), b_at = lane_value(v, 2);
+    const C x = a_at < b_at ? a_at : b_at;
     const int la = i - (i > 0 && a_before == x ? 1 : 0);       // (the coordinate's entry of A may lie before the split)
-    p[0] = a0 + la;
-    p[1] = b0 + j;
-    LevelResult r;
-    r.x = x;
-    r.c = (int64_t)la + j;
-    return r;
+    LevelFound<Acc> found;
+    found.x = x;
+    found.c = la + j;
+    found.p = g.t == 0 ? a0 + la : b0 + j;
+    found.present = false;                             // (the last level: nobody asks)
+    found.lo = found.hi = found.deep_lo = found.deep_hi = 0;
+    found.row_from = l;
+    return found;
 }
 
-// The first position in [0, hi) of operand t's row coordinates (coordinate list) whose row is not before x, for all
-// operands at once: the lanes are split into K groups, one operand each, that narrow their range 64 / K-fold a
-// round.  `hi` and the result: in the lanes of group t for operand t.
-template <int K>
-__device__ inline int row_starts(const DevOperands &ops, int hi, int64_t x)
+// One level of Algorithm 1 for one query, 0 <= R: as group_search, and what is shorter than that.
+template <int K, class Acc, int kDepth>
+__device__ __forceinline__ LevelFound<Acc> search_level(const DevOperands &ops, const Group<K> &g, int m, const Acc &crd,
+                                                        Ints32 pos_1, Ints32 pos_2, int l, int h, int R, int total, int sh)
 {
-    constexpr int G = NACHO_WAVE / (K <= 2 ? 2 : (K <= 4 ? 4 : 8));
-    const int lane = lane_id(), sub = lane & (G - 1), first = lane - sub, t = lane / G;
-    const unsigned long long group = low_bits(first + G) & ~low_bits(first);
-    const int32_t *rows = ops.lvl[t < ops.k ? t : 0][0].crd;
-    int lo = 0;
-    while (__ballot(lo < hi) != 0ull) {
-        // probes lo + (sub + 1) * step - 1: those before x are a prefix of the group
-        const int step = (hi - lo + G - 1) / G;
-        const int at = lo + (sub + 1) * step - 1;
-        const bool before = lo < hi && at < hi && (int64_t)rows[at] < x;
-        const int n = __popcll(__ballot(before) & group);
-        if (lo < hi) {
-            const int lo_new = lo + n * step, at_next = lo + (n + 1) * step - 1;
-            hi = n < G && at_next < hi ? at_next : hi;
-            lo = lo_new < hi ? lo_new : hi;
-        }
-    }
-    return lo;
-}
-
-// One level of Algorithm 1 for one query, starting from windows that bracket the
-// boundary.  `total` = cost of the level's whole segments.  On return p[t] =
-// position of operand t's first entry with coordinate >= x inside its segment.
-template <bool kLast, int K, class Acc = PlainCoords, bool kDeep = false>
-__device__ __forceinline__ LevelResult compressed_level(const DevOperands &ops, int m, int64_t R, int64_t total,
-                                        const int *seg_lo, const int *seg_hi, Windows<K> &W, int *p,
-                                        const int *sh, int fan = 0)
-{
-    const int k = ops.k;
-    LevelResult r;
+    LevelFound<Acc> found;
+    found.row_from = l;
+    found.present = false;
+    found.lo = found.hi = found.deep_lo = found.deep_hi = 0;
     if (R >= total) {
-        // the query reaches past this level's segments: highest coordinate is the extent
-#pragma unroll
-        for (int t = 0; t < K; ++t)
-            if (t < k) p[t] = seg_hi[t];
-        r.x = Acc::extent(ops, m);
-        r.c = total;
-        return r;
+        // the query reaches past this level's segments (no valid operands' does): the extent is the highest coordinate
+        found.x = (typename Acc::type)Acc::extent(ops, m);
+        found.c = total;
+        found.p = h;
+        if (kDepth > 0) found.lo = found.hi = pos_1[h];
+        if (kDepth == 2) found.deep_lo = found.deep_hi = pos_2[found.lo];
+        return found;
     }
-    int nonempty = 0, which = 0;
-#pragma unroll
-    for (int t = 0; t < K; ++t)
-        if (t < k && seg_hi[t] > seg_lo[t]) { ++nonempty; which = t; }
-    if (kLast && nonempty == 1) {
-        // exactly one operand with a non-empty segment: the residual indexes it
-#pragma unroll
-        for (int t = 0; t < K; ++t)
-            if (t < k) p[t] = seg_lo[t];
-        int at = 0;                                    // (no array is indexed by `which`: they stay in registers)
-#pragma unroll
-        for (int t = 0; t < K; ++t)
-            if (t == which) {
-                p[t] = seg_lo[t] + (int)R;
-                at = p[t] + sh[t];
-            }
-        r.x = Acc::load(ops, which, m, at);
-        r.c = R;
-        return r;
-    }
-    if constexpr (kLast && K == 2) {
-        if (nonempty == 2) return split_search<K, Acc>(ops, m, (int)R, seg_lo, seg_hi, p, sh, fan);
-    }
-    if constexpr (K > 4) {
-        // many operands: the sampled search would carry K * K rank searches per round and a
-        // code size no instruction cache holds; the coordinate search with tracked windows
-        // is the faster one there (8 operands of 2.5M entries: 275 us against 394 us)
-        int64_t c0 = 0;
-#pragma unroll
-        for (int t = 0; t < K; ++t) c0 += W.cl[t];
-        return tracked_search<kLast, K, Acc, kDeep>(ops, m, R, W.base, W.l, W.h, c0, p, sh);
-    }
-    return sampled_search<kLast, K, Acc, kDeep>(ops, m, R, W, p, sh);
-}
-
-template <bool kLast, int K>
-__device__ inline int64_t level_total(const DevOperands &ops, int m, const int *seg_lo, const int *seg_hi)
-{
-    int64_t total = 0;
-#pragma unroll
-    for (int t = 0; t < K; ++t)
-        if (t < ops.k) {
-            if (kLast) total += seg_hi[t] - seg_lo[t];
-            else total += ops.lvl[t][m + 1].pos[seg_hi[t]] - ops.lvl[t][m + 1].pos[seg_lo[t]];
+    if constexpr (kDepth == 0) {
+        const unsigned long long filled = __ballot(h > l && g.i == 0);
+        const int operands = __popcll(filled);
+        if (operands <= 1) {
+            // one operand with entries in its segment: the residual indexes it
+            const int owner = filled ? __ffsll((long long)filled) - 1 : 0;
+            found.p = h > l ? l + R : l;               // (R < total: the operand's own entries)
+            typename Acc::type v = Acc::kNone;
+            if (h > l) v = crd.load(found.p + sh);
+            found.x = lane_value(v, owner);
+            found.c = R;
+            return found;
         }
-    return total;
+        if constexpr (K == 2) return split_search<Acc>(g, Acc::of(ops, 0, m), Acc::of(ops, 1, m), l, h, R, sh);
+    }
+    if constexpr (K > 1 || kDepth > 0) found = group_search<K, Acc, kDepth>(g, crd, pos_1, pos_2, l, h, R, total, sh);
+    return found;
 }
 
 // One wavefront searches boundary b (0 <= b <= P) and stores its coordinate, positions and cost.
@@ -562,210 +535,141 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
 #pragma unroll
     for (int t = 0; t < K; ++t) found[t] = 0;
     const int64_t total_scaled = total_unscaled * cost_scale;
-    // Two operands: candidates per round of the split search, 64 >> fan.  Every candidate is a cache line of its own
-    // that no other boundary asks for: with thousands of boundaries in flight the lines are what takes the time (10M
-    // + 10M entries, 8192 boundaries: 46 us with 64 candidates a round, 24 with 16, 19 with 8, 18 with 4), with
-    // few of them the rounds are (16 boundaries: 6.5 / 7.0 / 7.4 / 8.1 us).
-    const int fan = P > 1024 ? 3 : 2;
-    const bool dense0 = ops.lvl[0][0].kind == NACHO_DENSE;
-    constexpr bool pairs = kMode == 1;                              // coordinate lists (COO), d == 2
-    constexpr bool csf3 = kMode == 2;                               // three compressed levels, d == 3
 
     int64_t Q = 0;
     if (queries) Q = queries[b];
     else if (grain > 0) Q = b * grain < total_scaled ? b * grain : total_scaled;
+    else if (total_scaled < 0x7fffffffLL && P < 0x7fffffffLL) Q = equal_query_short((unsigned)b, (unsigned)total_scaled, (unsigned)P);
     else Q = equal_query(b, total_scaled, P);
     if (Q < 0) Q = 0;
-    const int64_t Qu = Q / cost_scale;
+    const int64_t Qu = cost_scale == 1 ? Q : Q / cost_scale;
     const bool interior = b > 0 && b < P && Qu < total_unscaled;
-
-    // level-0 segments and, for a compressed level 0, the windows the search starts from
-    int seg0_lo[K], seg0_hi[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        seg0_lo[t] = seg0_hi[t] = 0;
-        if (t < k) {
-            const DevLevel &L = ops.lvl[t][0];
-            seg0_hi[t] = (L.kind == NACHO_DENSE) ? (int)L.extent : (int)L.count;
-        }
-    }
-    int no_shift[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) no_shift[t] = 0;
-    Windows<K> W0;
-    if (!dense0 && interior) {
-        if (pairs) windows_init<true, K>(ops, 0, seg0_lo, seg0_hi, W0);
-        else if (csf3) windows_init<false, K, true>(ops, 0, seg0_lo, seg0_hi, W0);
-        else if (d == 1) windows_init<true, K>(ops, 0, seg0_lo, seg0_hi, W0);
-        else windows_init<false, K>(ops, 0, seg0_lo, seg0_hi, W0);
-    }
-
-    {
-        int32_t *cb = coord + b * d;
+    int32_t *cb = coord + b * d;
+    if (!interior) {
         int32_t *pb = posn + b * (int64_t)k * d;
-        if (!interior) {
-            const bool end = (b != 0);
-            if (lane == 0) {
-                for (int m = 0; m < d; ++m) cb[m] = 0;
-                if (end) cb[0] = (int32_t)level0_extent(ops);
-                for (int t = 0; t < k; ++t)
-                    for (int m = 0; m < d; ++m) {
-                        const DevLevel &L = ops.lvl[t][m];
-                        int32_t at = 0;
-                        if (end) at = (L.kind == NACHO_DENSE) ? (int32_t)L.extent : (int32_t)L.count;
-                        if (end && ops.dyn_head) at = m == 0 ? (int32_t)level0_extent(ops) : (int32_t)last_count(ops, t);
-                        pb[t * d + m] = at;
-                    }
-                cost[b] = end ? total_scaled : 0;
-            }
-            if (end && d == 1) {
-#pragma unroll
-                for (int t = 0; t < K; ++t)
-                    if (t < k) found[t] = (int)ops.lvl[t][0].count;
-            }
-            return;
+        const bool end = (b != 0);
+        if (lane == 0) {
+            for (int m = 0; m < d; ++m) cb[m] = 0;
+            if (end) cb[0] = (int32_t)level0_extent(ops);
+            for (int t = 0; t < k; ++t)
+                for (int m = 0; m < d; ++m) {
+                    const DevLevel &L = ops.lvl[t][m];
+                    int32_t at = 0;
+                    if (end) at = (L.kind == NACHO_DENSE) ? (int32_t)L.extent : (int32_t)L.count;
+                    if (end && ops.dyn_head) at = m == 0 ? (int32_t)level0_extent(ops) : (int32_t)last_count(ops, t);
+                    pb[t * d + m] = at;
+                }
+            cost[b] = end ? total_scaled : 0;
         }
-        int seg_lo[K], seg_hi[K], p[K];
-        int64_t R = Qu;
-        if (pairs) {
-            // one search over the (row, column) pairs; the row-level position of an operand is
-            // that of its first entry in the boundary's row
-            Windows<K> W = W0;
-            LevelResult r = compressed_level<true, K, PairCoords>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi, W, p,
-                                                                  no_shift, fan);
-            R -= r.c;
-            const int x0 = (int)(r.x >> 32), x1 = (int)(r.x & 0xffffffffLL);
-            constexpr int G = NACHO_WAVE / (K <= 2 ? 2 : (K <= 4 ? 4 : 8));    // lanes of an operand's group
-            const int t_mine = lane / G;
-            int mine = 0;
+        if (end && d == 1) {
 #pragma unroll
             for (int t = 0; t < K; ++t)
-                if (t < k && t_mine == t) mine = p[t];
-            const int row_at = row_starts<K>(ops, mine, x0);
-            if ((lane & (G - 1)) == 0 && t_mine < k) {
-                pb[t_mine * 2 + 0] = row_at;
-                pb[t_mine * 2 + 1] = mine;
-            }
-            if (lane == 0) {
-                cb[0] = x0;
-                cb[1] = x1;
-            }
-        } else if (csf3) {
-            // three compressed levels: Algorithm 1 level by level; a level's cost counts the
-            // non-zeros below its entries (two pos arrays down at level 0, one at level 1)
-            int p0[K], p1[K];
-            Windows<K> W = W0;
-            LevelResult r0 = compressed_level<false, K, PlainCoords, true>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi,
-                                                                           W, p, no_shift);
-            R -= r0.c;
-            int64_t tot1 = 0;
+                if (t < k) found[t] = (int)ops.lvl[t][0].count;
+        }
+        return;
+    }
+
+    // Everything about an operand is in the lanes of its group.
+    const Group<K> g(k);
+    const bool writer = g.i == 0;
+    int32_t *pb = posn + (b * (int64_t)k + g.t) * d;
+    auto ints_of = [&](auto get) -> Ints32 {
+        Ints32 v = as_global(get(0));
 #pragma unroll
-            for (int t = 0; t < K; ++t) {
-                p0[t] = 0;
-                seg_lo[t] = seg_hi[t] = 0;
-                if (t < k) {
-                    p0[t] = p[t];
-                    const int32_t *pos1 = ops.lvl[t][1].pos;
-                    const bool present = p[t] < seg0_hi[t] && (int64_t)ops.lvl[t][0].crd[p[t]] == r0.x;
-                    seg_lo[t] = pos1[p[t]];
-                    seg_hi[t] = present ? pos1[p[t] + 1] : seg_lo[t];
-                    tot1 += ops.lvl[t][2].pos[seg_hi[t]] - ops.lvl[t][2].pos[seg_lo[t]];
-                }
-            }
-            Windows<K> W1;
-            windows_init<false, K>(ops, 1, seg_lo, seg_hi, W1);
-            LevelResult r1 = compressed_level<false, K>(ops, 1, R, tot1, seg_lo, seg_hi, W1, p, no_shift);
-            R -= r1.c;
-            int64_t tot2 = 0;
+        for (int u = 1; u < K; ++u) v = g.t == u ? as_global(get(u)) : v;      // (no branches: one round trip)
+        return v;
+    };
+    auto count_of = [&](int m) -> int {
+        int v = (int)ops.lvl[0][m].count;
 #pragma unroll
-            for (int t = 0; t < K; ++t) {
-                p1[t] = 0;
-                if (t < k) {
-                    p1[t] = p[t];
-                    const int32_t *pos2 = ops.lvl[t][2].pos;
-                    const bool present = p[t] < seg_hi[t] && (int64_t)ops.lvl[t][1].crd[p[t]] == r1.x;
-                    const int lo2 = pos2[p[t]];
-                    seg_hi[t] = present ? pos2[p[t] + 1] : lo2;     // (level-1 bounds are used up)
-                    seg_lo[t] = lo2;
-                    tot2 += seg_hi[t] - seg_lo[t];
-                } else {
-                    seg_lo[t] = seg_hi[t] = 0;
-                }
-            }
-            Windows<K> W2;
-            windows_init<true, K>(ops, 2, seg_lo, seg_hi, W2);
-            LevelResult r2 = compressed_level<true, K>(ops, 2, R, tot2, seg_lo, seg_hi, W2, p, no_shift, fan);
-            R -= r2.c;
-            if (lane == 0) {
-                cb[0] = (int32_t)r0.x;
-                cb[1] = (int32_t)r1.x;
-                cb[2] = (int32_t)r2.x;
+        for (int u = 1; u < K; ++u) v = g.t == u ? (int)ops.lvl[u][m].count : v;
+        return v;
+    };
+    auto plain = [&](int m) { return PlainCoords{ints_of([&](int t) { return ops.lvl[t][m].crd; })}; };
+    auto pos_of = [&](int m) { return ints_of([&](int t) { return ops.lvl[t][m].pos; }); };
+    int R = (int)Qu;
+    const int total = (int)total_unscaled;
+    if constexpr (kMode == 1) {
+        // coordinate lists, d == 2: one search over the (row, column) pairs; the row-level position of an operand is
+        // that of its first entry in the boundary's row
+        const PairCoords pairs = {ints_of([&](int t) { return ops.lvl[t][0].crd; }), ints_of([&](int t) { return ops.lvl[t][1].crd; })};
+        const auto f = search_level<K, PairCoords, 0>(ops, g, 0, pairs, nullptr, nullptr, 0, count_of(0), R, total, 0);
+        R -= f.c;
+        const int x0 = (int)(f.x >> 32), x1 = (int)(f.x & 0xffffffffLL);
+        const int row_at = group_lower_bound<K>(g, f.row_from, f.p, [&](int at) { return pairs.row[at] < x0; });
+        if (writer) {
+            pb[0] = row_at;
+            pb[1] = f.p;
+        }
+        if (lane == 0) {
+            cb[0] = x0;
+            cb[1] = x1;
+        }
+    } else if constexpr (kMode == 2) {
+        // three compressed levels: Algorithm 1 level by level; a level's cost counts the
+        // non-zeros below its entries (two pos arrays down at level 0, one at level 1)
+        const Ints32 pos1 = pos_of(1), pos2 = pos_of(2);
+        const auto f0 = search_level<K, PlainCoords, 2>(ops, g, 0, plain(0), pos1, pos2, 0, count_of(0), R, total, 0);
+        R -= f0.c;
+        const auto f1 = search_level<K, PlainCoords, 1>(ops, g, 1, plain(1), pos2, nullptr, f0.lo, f0.hi, R,
+                                                        g.sum(f0.deep_hi - f0.deep_lo), 0);
+        R -= f1.c;
+        const auto f2 = search_level<K, PlainCoords, 0>(ops, g, 2, plain(2), nullptr, nullptr, f1.lo, f1.hi, R,
+                                                        g.sum(f1.hi - f1.lo), 0);
+        R -= f2.c;
+        if (writer) {
+            pb[0] = f0.p;
+            pb[1] = f1.p;
+            pb[2] = f2.p;
+        }
+        if (lane == 0) {
+            cb[0] = f0.x;
+            cb[1] = f1.x;
+            cb[2] = f2.x;
+        }
+    } else if (d == 1) {
+        const auto f = search_level<K, PlainCoords, 0>(ops, g, 0, plain(0), nullptr, nullptr, 0, count_of(0), R, total, 0);
+        R -= f.c;
 #pragma unroll
-                for (int t = 0; t < K; ++t)
-                    if (t < k) {
-                        pb[t * 3 + 0] = p0[t];
-                        pb[t * 3 + 1] = p1[t];
-                        pb[t * 3 + 2] = p[t];
-                    }
-            }
-        } else if (d == 1) {
-            Windows<K> W = W0;
-            LevelResult r = compressed_level<true, K>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi, W, p, no_shift, fan);
-            R -= r.c;
-#pragma unroll
-            for (int t = 0; t < K; ++t)
-                if (t < k) found[t] = p[t];
-            if (lane == 0) {
-                cb[0] = (int32_t)r.x;
-#pragma unroll
-                for (int t = 0; t < K; ++t)
-                    if (t < k) pb[t] = p[t];
+        for (int t = 0; t < K; ++t)
+            if (t < k) found[t] = lane_value(f.p, t * g.size);
+        if (writer) pb[0] = f.p;
+        if (lane == 0) cb[0] = f.x;
+    } else {
+        const Ints32 pos1 = pos_of(1);
+        int x0, p0, lo, hi, sh = 0;
+        if (ops.lvl[0][0].kind == NACHO_DENSE) {
+            int64_t c = 0;
+            const int64_t row = dense_search<K>(ops, R, c);
+            R -= (int)c;
+            x0 = p0 = (int)row;
+            const bool present = row < ops.lvl[0][0].extent;
+            lo = pos1[p0];
+            hi = present ? pos1[p0 + 1] : lo;
+            if (ops.start[0]) {                        // a remapped operand's row
+                const Ints32 start = ints_of([&](int t) { return ops.start[t]; });
+                if (present) sh = start[p0] - lo;
             }
         } else {
-            LevelResult r0;
-            if (dense0) r0 = dense_search<K>(ops, 0, R, p);
-            else {
-                Windows<K> W = W0;
-                r0 = compressed_level<false, K>(ops, 0, R, total_unscaled, seg0_lo, seg0_hi, W, p, no_shift);
-            }
-            R -= r0.c;
-            int p0[K], sh[K];
-#pragma unroll
-            for (int t = 0; t < K; ++t) {
-                p0[t] = 0;
-                sh[t] = 0;
-                seg_lo[t] = seg_hi[t] = 0;
-                if (t < k) {
-                    p0[t] = p[t];
-                    const DevLevel &L0 = ops.lvl[t][0];
-                    const int32_t *pos1 = ops.lvl[t][1].pos;
-                    bool present;
-                    if (dense0) present = r0.x < L0.extent;
-                    else present = p[t] < seg0_hi[t] && (int64_t)L0.crd[p[t]] == r0.x;
-                    const int lo1 = pos1[p[t]];
-                    seg_lo[t] = lo1;
-                    seg_hi[t] = present ? pos1[p[t] + 1] : lo1;
-                    if (present && ops.start[t]) sh[t] = ops.start[t][p[t]] - lo1;   // remapped row
-                }
-            }
-            Windows<K> W1;
-            windows_init<true, K>(ops, 1, seg_lo, seg_hi, W1);
-            const int64_t tot1 = level_total<true, K>(ops, 1, seg_lo, seg_hi);
-            LevelResult r1 = compressed_level<true, K>(ops, 1, R, tot1, seg_lo, seg_hi, W1, p, sh, fan);
-            R -= r1.c;
-            if (lane == 0) {
-                cb[0] = (int32_t)r0.x;
-                cb[1] = (int32_t)r1.x;
-#pragma unroll
-                for (int t = 0; t < K; ++t)
-                    if (t < k) {
-                        pb[t * 2 + 0] = p0[t];
-                        pb[t * 2 + 1] = p[t];
-                    }
-            }
+            const auto f = search_level<K, PlainCoords, 1>(ops, g, 0, plain(0), pos1, nullptr, 0, count_of(0), R, total, 0);
+            R -= f.c;
+            x0 = f.x;
+            p0 = f.p;
+            lo = f.lo;
+            hi = f.hi;
         }
-        if (lane == 0) cost[b] = (Qu - R) * cost_scale;
+        const auto f = search_level<K, PlainCoords, 0>(ops, g, 1, plain(1), nullptr, nullptr, lo, hi, R, g.sum(hi - lo), sh);
+        R -= f.c;
+        if (writer) {
+            pb[0] = p0;
+            pb[1] = f.p;
+        }
+        if (lane == 0) {
+            cb[0] = x0;
+            cb[1] = f.x;
+        }
     }
+    if (lane == 0) cost[b] = (Qu - R) * cost_scale;
 }
 
 }  // namespace
