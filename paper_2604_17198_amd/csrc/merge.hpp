@@ -1560,6 +1560,7 @@ spadd_kernel(MergeArgs args)
 {
     __shared__ TileOf<FMT, T, KeyT, kSmall> w;
     const WaveStamp stamp = wave_begin();
+    touch_arguments<sizeof(MergeArgs) <= 1408 ? sizeof(MergeArgs) : 1408>();
     const ArgPtr arg_ptr = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
     merge_partition<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch>(arg_ptr, w, args.ops, stamp);
 }
