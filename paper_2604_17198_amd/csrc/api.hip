@@ -152,6 +152,7 @@ struct CarryWs {
     PartsWs parts;
     void *carry_val;
     int32_t *carry_row;
+    int32_t *deal;             // SpMM calls that deal their partitions out
     size_t bytes;
 };
 
@@ -161,13 +162,14 @@ constexpr int64_t kSpmmPass = 256;
 int spmm_pass(int64_t n) { return (int)(n < NACHO_WAVE ? NACHO_WAVE : (n < kSpmmPass ? n : kSpmmPass)); }
 
 // SpMV: one carry value per partition; SpMM: one carry row per partition.
-CarryWs carve_carry(void *ws, int64_t P, int32_t dtype, int width)
+CarryWs carve_carry(void *ws, int64_t P, int32_t dtype, int width, bool dealt = false)
 {
     Carver c(ws);
     CarryWs w;
     w.parts = carve_parts(c, P, 1, 2);
     w.carry_val = c.take<char>((size_t)P * width * dtype_size(dtype));
     w.carry_row = c.take<int32_t>((size_t)P);
+    w.deal = dealt ? c.take<int32_t>((size_t)spmm_deal_words(P)) : nullptr;
     w.bytes = align_up(c.off, 256);
     return w;
 }
@@ -241,9 +243,44 @@ MergeFields fields_of(Format fmt, int32_t dtype, const nacho_tensor *ops, int64_
 int64_t fused_partitions(int32_t op, int32_t dtype, int64_t total_nnz, int64_t P)
 {
     const int64_t cap = op == NACHO_OP_SPMV ? spmv_capacity(dtype)
-                                            : (P == 0 ? spmm_grain(total_nnz, compute_units()) : spmm_capacity());
+                                            : (P == 0 ? spmm_grain(total_nnz, compute_units(), false, 0) : spmm_capacity());
     const int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
     return P > need ? P : need;
+}
+
+// How an SpMM call runs on a workspace of ws_bytes bytes (ws NULL: one of any size).  Large calls sort their partitions by
+// column; a workspace that has no room for that (sized for other columns) serves them unsorted.
+struct SpmmPlan {
+    int64_t Pe, grain;         // grain 0: the caller's P
+    int pass;                  // columns at a time
+    bool dealt;
+    CarryWs w;
+    bool fits;
+};
+SpmmPlan plan_spmm(void *ws, size_t ws_bytes, int32_t dtype, int64_t nnz, int64_t n_cols, int64_t n, int64_t P)
+{
+    SpmmPlan plan;
+    plan.pass = spmm_pass(n);
+    const int64_t row_bytes = n * (int64_t)dtype_size(dtype);
+    plan.dealt = P == 0 && n > 0 && spmm_dealt(nnz, n_cols, row_bytes);
+    if (plan.dealt) {
+        plan.grain = spmm_grain(nnz, compute_units(), true, row_bytes);
+        plan.Pe = ceil_div(nnz, plan.grain);
+        plan.w = carve_carry(ws, plan.Pe, dtype, plan.pass, true);
+        plan.fits = ws_bytes >= plan.w.bytes;
+        if (!ws || plan.fits) return plan;
+        plan.dealt = false;
+    }
+    plan.grain = P == 0 ? spmm_grain(nnz, compute_units(), false, row_bytes) : 0;
+    plan.Pe = fused_partitions(NACHO_OP_SPMM, dtype, nnz, P);
+    plan.w = carve_carry(ws, plan.Pe, dtype, plan.pass);
+    plan.fits = ws_bytes >= plan.w.bytes;
+    if (ws && !plan.fits) {
+        plan.pass = NACHO_WAVE;
+        plan.w = carve_carry(ws, plan.Pe, dtype, plan.pass);
+        plan.fits = ws_bytes >= plan.w.bytes;
+    }
+    return plan;
 }
 
 // The same for the merge kernel of sums and products; `fields` is its key layout for the operands.
@@ -375,7 +412,6 @@ const char *nacho_status_string(int32_t status)
 int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int32_t dtype,
                              int64_t n_dense, int64_t P)
 {
-    (void)n_dense;
     if (P < 0 || (dtype != NACHO_F32 && dtype != NACHO_F64)) return 0;
     DevOperands dev;
     int64_t total = 0;
@@ -386,6 +422,7 @@ int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int
     case NACHO_OP_SPMV:
     case NACHO_OP_SPMM:
         if (k != 1 || fmt != FMT_CSR) return 0;
+        if (op == NACHO_OP_SPMM) return plan_spmm(nullptr, 0, dtype, total, ops[0].lvl[1].extent, n_dense, P).Pe;
         return fused_partitions(op, dtype, total, P);
     case NACHO_OP_SPADD:
     case NACHO_OP_SPMUL:      // (a DCSR product: an upper bound, the count depends on the intersected rows)
@@ -410,8 +447,8 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
     case NACHO_OP_SPMV:
     case NACHO_OP_SPMM: {
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
-        const int64_t Pe = fused_partitions(op, dtype, total, P);
-        *bytes = carve_carry(nullptr, Pe, dtype, op == NACHO_OP_SPMM ? spmm_pass(n_dense) : 1).bytes;
+        if (op == NACHO_OP_SPMM) *bytes = plan_spmm(nullptr, 0, dtype, total, ops[0].lvl[1].extent, n_dense, P).w.bytes;
+        else *bytes = carve_carry(nullptr, fused_partitions(op, dtype, total, P), dtype, 1).bytes;
         return NACHO_OK;
     }
     case NACHO_OP_SPMUL:
@@ -449,12 +486,19 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
     case NACHO_OP_SPMM: {
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
         if (op == NACHO_OP_SPMM && n_dense < 1) return NACHO_ERR_INVALID_ARG;
-        Pe = fused_partitions(op, dtype, total, P);
-        // (the table comes first; the call itself also takes a workspace sized for one pass of 64 columns)
-        CarryWs c = carve_carry(ws, Pe, dtype, op == NACHO_OP_SPMM ? NACHO_WAVE : 1);
-        w = c.parts;
-        need = c.bytes;
-        if (P == 0) g = op == NACHO_OP_SPMV ? (int64_t)spmv_capacity(dtype) : spmm_grain(total, compute_units()) * n_dense;
+        if (op == NACHO_OP_SPMM) {
+            const SpmmPlan plan = plan_spmm(ws, ws_bytes, dtype, total, ops[0].lvl[1].extent, n_dense, P);
+            Pe = plan.Pe;
+            w = plan.w.parts;
+            need = plan.w.bytes;
+            g = plan.grain * n_dense;
+        } else {
+            Pe = fused_partitions(op, dtype, total, P);
+            const CarryWs c = carve_carry(ws, Pe, dtype, 1);
+            w = c.parts;
+            need = c.bytes;
+            if (P == 0) g = (int64_t)spmv_capacity(dtype);
+        }
         break;
     }
     case NACHO_OP_SPMUL:
@@ -679,20 +723,18 @@ int32_t nacho_spmm(const nacho_tensor *A, const void *B, int64_t n, int64_t ldb,
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && !A->val) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMM, dtype, nnz, P);
-    int pass = spmm_pass(n);
-    CarryWs w = carve_carry(ws, Pe, dtype, pass);
-    if (ws && ws_bytes < w.bytes) {
-        pass = NACHO_WAVE;
-        w = carve_carry(ws, Pe, dtype, pass);
-    }
-    if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
+    const SpmmPlan plan = plan_spmm(ws, ws_bytes, dtype, nnz, A->lvl[1].extent, n, P);
+    if (!ws || !plan.fits) return NACHO_ERR_WORKSPACE;
+    const int64_t Pe = plan.Pe, grain = plan.grain;
+    const int pass = plan.pass;
+    const CarryWs &w = plan.w;
+    const size_t elem = dtype_size(dtype);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int64_t n_rows = A->lvl[0].extent;
     profile_begin(s);
     // cost of a stored non-zero = n (broadcast over the dense loop); queries are multiples of n
-    const int64_t grain = P == 0 ? spmm_grain(nnz, compute_units()) : 0;
-    const bool whole = grain > 0 && spmm_whole(Pe, n_rows);
+    const bool whole = grain > 0 && !plan.dealt && spmm_whole(Pe, n_rows);
+    SpmmDeal deal = {nullptr, nullptr};
     if (!whole) {
         ZeroRows zero;                  // rows of C whose row of A is empty
         zero.base = C;
@@ -704,17 +746,20 @@ int32_t nacho_spmm(const nacho_tensor *A, const void *B, int64_t n, int64_t ldb,
             return NACHO_ERR_HIP;
         profile_mark("partition");
     }
+    if (plan.dealt) {
+        if (launch_spmm_deal(w.parts.coord, Pe, A->lvl[1].extent, w.deal, &deal, s) != hipSuccess) return NACHO_ERR_HIP;
+        profile_mark("spmm_deal");
+    }
     // Wide operands go through in passes.  The partitions are the same for every pass (the queries are multiples of n,
     // so no boundary falls inside the dense loop), and so are the carry buffers, which the passes use one after the
     // other on the stream.
-    const size_t elem = dtype_size(dtype);
     for (int64_t j0 = 0; j0 < n; j0 += pass) {
         const int width = (int)(n - j0 < pass ? n - j0 : pass);
         const void *Bj = static_cast<const char *>(B) + (size_t)j0 * elem;
         void *Cj = static_cast<char *>(C) + (size_t)j0 * elem;
         if (launch_spmm_exec(dtype, A->lvl[1].pos, A->lvl[1].crd, A->val, Bj, width, ldb, Cj, ldc, n_rows, nnz,
                              w.parts.coord, w.parts.posn, w.parts.cost, Pe, w.carry_val, w.carry_row, grain, n, whole,
-                             s) != hipSuccess)
+                             deal, (double)A->lvl[1].extent * ldb * elem, s) != hipSuccess)
             return NACHO_ERR_HIP;
         profile_mark("spmm_exec");
         if (launch_spmm_fixup(dtype, Cj, ldc, width, Pe, w.carry_val, w.carry_row, A->lvl[1].pos, w.parts.posn, grain,

@@ -220,6 +220,29 @@ __device__ inline void rows_holding(const int32_t *__restrict__ pos, int n_rows,
     rb = __builtin_amdgcn_readlane(lo, G);
 }
 
+// Which partition the workgroup of partition p executes when partitions inside one row are dealt out by XCD: p lies in the
+// row whose non-zeros are [a, e) (counted from the matrix's first), partitions have `grain` non-zeros.  Workgroups are handed to
+// the 8 XCDs in turn (workgroup w runs on XCD w mod 8), and every XCD has its own L2.  The partitions inside the row are
+// first = ceil(a / grain) .. end - 1 = floor(e / grain) - 1.  Among the workgroups first .. end - 1 those with index = j (mod 8)
+// take, in order, the j-th stretch of these partitions (stretches as long as there are such workgroups): a permutation of
+// first .. end - 1; everything else keeps its index.  XCD j then gathers from one eighth of what the row gathers from
+// (columns are sorted inside a row), and that eighth is the same for every long row.
+__device__ inline int dealt_partition(int p, int a, int e, int grain)
+{
+    const int first = shares_before(a, grain), end = e / grain;
+    if (end - first < 4 || p < first || p >= end) return p;
+    const int j = p & 7;
+    int before = 0, mine = 0;                          // partitions of the stretches before stretch j; first workgroup of j
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) {
+        const int f = first + ((jj - first) & 7);      // first workgroup >= first with index = jj (mod 8)
+        const int cnt = f < end ? (end - f + 7) >> 3 : 0;
+        if (jj < j) before += cnt;
+        if (jj == j) mine = f;
+    }
+    return first + before + ((p - mine) >> 3);
+}
+
 // ---- instrumented build (-DNACHO_INSTRUMENT): what every wavefront did, and when -----------
 // The executing kernels take a log descriptor as their last argument.  In the ordinary build the
 // flag below is false and every use of it folds away; in the instrumented build lane 0 of

@@ -47,14 +47,23 @@ hipError_t launch_spmv_fixup(int dtype, void *y, int64_t P, const void *carry_va
 
 // ---- SpMM ------------------------------------------------------------------
 int spmm_capacity();                                // most non-zeros of a partition
-int spmm_grain(int64_t nnz, int units);             // non-zeros of a fixed-grain partition
+// Whether a fixed-grain call sorts its partitions by column (row_bytes: of a row of B).
+bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes);
+int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes);      // non-zeros of a fixed-grain partition
 // Whether a fixed-grain call goes without a partition kernel (the executing kernel writes the table and the zeros).
 bool spmm_whole(int64_t P, int64_t n_rows);
-// carry_val: n values per partition.  `grain` (non-zeros) > 0: fixed-grain partitions.
+// Workgroup w executes partition sorted[place[w]], or partition w where place[w] < 0.  NULL: workgroup w partition w.
+struct SpmmDeal {
+    int32_t *place, *sorted;
+};
+int64_t spmm_deal_words(int64_t P);                 // 32-bit words it takes
+hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int32_t *words, SpmmDeal *deal, hipStream_t stream);
+// carry_val: n values per partition.  b_bytes: of B.  `grain` (non-zeros) > 0: fixed-grain partitions.
 hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *B, int n, int64_t ldb, void *C, int64_t ldc, int64_t n_rows, int64_t nnz,
                             int32_t *coord, int32_t *posn, int64_t *cost, int64_t P, void *carry_val,
-                            int32_t *carry_row, int64_t grain, int64_t cost_scale, bool whole, hipStream_t stream);
+                            int32_t *carry_row, int64_t grain, int64_t cost_scale, bool whole, const SpmmDeal &deal,
+                            double b_bytes, hipStream_t stream);
 hipError_t launch_spmm_fixup(int dtype, void *C, int64_t ldc, int n, int64_t P, const void *carry_val,
                              const int32_t *carry_row, const int32_t *pos, const int32_t *posn, int64_t grain,
                              hipStream_t stream);

@@ -2,8 +2,9 @@
 // innermost (the broadcast rule of Section 4.2.2 scales the cost of every stored non-zero by n, so the
 // partitions are those of SpMV), one wavefront per partition.
 //
-// What bounds it: large matrices the rows of B (30M non-zeros x 256 bytes: 6.6 TB/s out of the last-level cache and
-// memory), all others how many of those rows are on their way at a time.  So a row of B is not spread over the whole
+// What bounds it: large matrices the rows of B (30M non-zeros x 256 bytes, 7.7 GB past the L2s at 7 TB/s, unless partitions
+// that need the same rows run at the same time on the same XCD: deal_count_kernel below; 1095 to 590 us), all others how many of
+// those rows are on their way at a time.  So a row of B is not spread over the whole
 // wavefront: a lane takes 16 bytes of it, W = 4 to 16 lanes a row, and the 64 / W groups of lanes of a wavefront each
 // walk their own stretch of the partition's non-zeros.  One instruction then asks for up to 16 rows, and the chain of
 // dependent steps is that many times shorter (20,000 non-zeros, n = 4: 80 us with a lane per column and the wavefront
@@ -35,13 +36,14 @@ template <typename T, int V> struct Piece {
 
 // W lanes a row, CPL pieces of V elements a lane.  kWhole: there is no partition kernel; the wavefront searches its
 // rows, stores its part of the partition table and writes the zeros of its empty rows.
+// `deal` (without kWhole): the partition a workgroup executes, see deal_count_kernel.
 template <typename T, int V, int W, int CPL, bool kWhole>
 __global__ void __launch_bounds__(NACHO_WAVE)
 spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd, const T *__restrict__ val,
                  const T *__restrict__ B, int n, int span, int64_t ldb, T *__restrict__ C, int64_t ldc,
                  int32_t *__restrict__ coord, int32_t *__restrict__ posn, int64_t *__restrict__ cost,
                  T *__restrict__ carry_val, int32_t *__restrict__ carry_row, int n_rows, int nnz, int grain,
-                 int64_t cost_scale, WaveLog wlog)
+                 int64_t cost_scale, SpmmDeal deal, bool deal_rows, WaveLog wlog)
 {
     typedef typename Piece<T, V>::type P;
     typedef typename Piece<T, V>::mem PM;
@@ -59,7 +61,12 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     T *s_val = reinterpret_cast<T *>(smem);
     int32_t *s_crd = reinterpret_cast<int32_t *>(smem + kSlots * sizeof(T));
 
-    const int p = blockIdx.x, lane = threadIdx.x, g = lane / W, gl = lane & (W - 1);
+    const int lane = threadIdx.x, g = lane / W, gl = lane & (W - 1);
+    int p = blockIdx.x;
+    if (!kWhole && deal.place) {
+        const int at = deal.place[p];
+        if (at >= 0) p = deal.sorted[at];
+    }
     int r0, r1, n0, n1;
     if (kWhole) {
         const int base = pos[0];
@@ -70,6 +77,16 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         if (p == 0) r0 = 0;
         else if (Qa >= nnz) r0 = n_rows;
         if (Qb >= nnz) r1 = n_rows;
+        if (r0 < n_rows && deal_rows) {
+            const int dealt = dealt_partition(p, pos[r0] - base, pos[r0 + 1] - base, grain);
+            if (dealt != p) {
+                // (a partition inside row r0; it may end with the row)
+                p = dealt;
+                n0 = base + p * grain;
+                n1 = n0 + grain;
+                r1 = r0;
+            }
+        }
     } else {
         r0 = coord[2 * p]; r1 = coord[2 * p + 2];
         n0 = posn[2 * p + 1]; n1 = posn[2 * p + 3];
@@ -255,25 +272,31 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     if (blockIdx.y == 0) wave_end(wlog, p, stamp, (uint32_t)len, (uint32_t)(next_first - r0));
 }
 
-// Carry fix-up: 16 lanes and up to 64 columns per partition, 16 partitions per workgroup.  The carries of a row lie in
+// Carry fix-up: 64 / V lanes per partition, a piece of V columns each, 16 (floats) or 8 partitions per workgroup.  The carries of a row lie in
 // consecutive partitions; the lanes of the first one add the run to the row of C.  A run of more than kShort carries
 // (there is at most one per workgroup: it is longer than the workgroup's partitions) is added by the whole workgroup,
-// every group a sixteenth of it: the largest row of 30M non-zeros has 488, which one wavefront, a row of carries at a
-// time, took 35 us for.  The order of the additions is fixed.
-constexpr int kFixLanes = 16, kFixCols = 4, kFixGroups = 256 / kFixLanes, kShort = 32;
+// every group an equal share of it: the largest row of 30M non-zeros has a thousand, which one wavefront, a row of carries at a
+// time, took 35 us for (half as many).  The order of the additions is fixed.  Bound: the loads in flight, so they are as wide
+// as the lanes' pieces (element by element, 117k partitions of 64 columns: 26.5 us, like this 22.8).
+constexpr int kFixCols = 64, kShort = 32;
 
-template <typename T>
+template <typename T, int V>
 __global__ void __launch_bounds__(256)
 spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restrict__ carry_val,
                   const int32_t *__restrict__ carry_row, const int32_t *__restrict__ pos,
                   const int32_t *__restrict__ posn, int grain)
 {
+    typedef typename Piece<T, V>::type Vec;
+    typedef typename Piece<T, V>::mem Mem;
+    constexpr int kFixLanes = kFixCols / V, kFixGroups = 256 / kFixLanes;
     static_assert(kShort >= kFixGroups, "one long run per workgroup");
-    __shared__ T part[kFixGroups][kFixLanes * kFixCols];
+    __shared__ Vec part[kFixGroups][kFixLanes];
     __shared__ int s_first, s_end, s_row;
     const int g = threadIdx.x / kFixLanes, gl = threadIdx.x & (kFixLanes - 1);
     const int p = blockIdx.x * kFixGroups + g;
-    const int j0 = blockIdx.y * (kFixLanes * kFixCols) + gl;
+    // (n >= V; the last piece of a row moves back where it would stick out: the columns it shares with the one before are
+    // that one's to store)
+    const int j0 = blockIdx.y * (kFixLanes * V) + gl * V, col = j0 < n - V ? j0 : n - V, shared = j0 - col;
     if (threadIdx.x == 0) s_first = -1;
     __syncthreads();
     const int r = p < P ? carry_row[p] : -1;
@@ -293,32 +316,33 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
         }
         e = e < P ? e : P;
     }
-    // carries q, q + step, ... below `to`, eight of them in flight
-    auto sum = [&](int q, int to, int step, T (&x)[kFixCols]) {
+    auto add_to = [&](int row, Vec x) {
+        T *at = C + (int64_t)row * ldc + col;
+        if (shared == 0) *reinterpret_cast<Mem *>(at) += x;
+        else
 #pragma unroll
-        for (int c = 0; c < kFixCols; ++c) x[c] = T(0);
-        for (; q < to; q += 8 * step) {
-            T t[8][kFixCols];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int c = 0; c < kFixCols; ++c) {
-                    t[u][c] = T(0);
-                    if (q + u * step < to && j0 + c * kFixLanes < n)
-                        t[u][c] = carry_val[(int64_t)(q + u * step) * n + j0 + c * kFixLanes];
-                }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int c = 0; c < kFixCols; ++c) x[c] += t[u][c];
-        }
+            for (int c = 1; c < V; ++c)
+                if (c >= shared) at[c] += x[c];
     };
-    T x[kFixCols];
-    if (first && e - p <= kShort) {
-        sum(p, e, 1, x);
+    // carries q, q + step, ... below `to`, sixteen of them in flight
+    auto sum = [&](int q, int to, int step) -> Vec {
+        Vec x = Vec(T(0));
+        constexpr int kFlight = sizeof(Vec) == 16 ? 8 : 16;
+        for (; q < to; q += kFlight * step) {
+            Vec t[kFlight];
 #pragma unroll
-        for (int c = 0; c < kFixCols; ++c)
-            if (j0 + c * kFixLanes < n) C[(int64_t)r * ldc + j0 + c * kFixLanes] += x[c];
+            for (int u = 0; u < kFlight; ++u) {
+                t[u] = Vec(T(0));
+                if (q + u * step < to) t[u] = *reinterpret_cast<const Mem *>(carry_val + (int64_t)(q + u * step) * n + col);
+            }
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) x += t[u];
+        }
+        return x;
+    };
+    const bool mine = j0 < n;
+    if (first && e - p <= kShort) {
+        if (mine) add_to(r, sum(p, e, 1));
     } else if (first && gl == 0) {
         s_first = p;
         s_end = e;
@@ -326,27 +350,137 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
     }
     __syncthreads();
     if (s_first < 0) return;                           // (the whole workgroup)
-    sum(s_first + g, s_end, kFixGroups, x);
-#pragma unroll
-    for (int c = 0; c < kFixCols; ++c) part[g][c * kFixLanes + gl] = x[c];
+    part[g][gl] = mine ? sum(s_first + g, s_end, kFixGroups) : Vec(T(0));
     __syncthreads();
-    if (g < kFixCols && j0 + g * kFixLanes < n) {
-        T y = T(0);
+    if (g == 0 && mine) {
+        Vec y = Vec(T(0));
 #pragma unroll
-        for (int u = 0; u < kFixGroups; ++u) y += part[u][g * kFixLanes + gl];
-        C[(int64_t)s_row * ldc + j0 + g * kFixLanes] += y;
+        for (int u = 0; u < kFixGroups; ++u) y += part[u][gl];
+        add_to(s_row, y);
+    }
+}
+
+// ---- which workgroup executes which partition ----------------------------------
+// The rows of B that the partitions of long rows gather ascend with the partition: a partition inside a row covers a
+// stretch of columns, and so do those of every other long row.  Executed in the order of their columns, partitions that need the same
+// rows of B run at the same time, and dealt out so that an XCD gets one eighth of the columns they find them in its L2.  (A
+// workgroup runs on XCD index mod 8, and workgroups start in the order of their indexes.)  So the partitions that lie
+// inside one row are sorted by their first column, the sorted list is cut into eight stretches, one for the workgroups of
+// every residue, and those workgroups take their stretch in order.  All other partitions stay where they are: they miss the
+// L2 whatever their order, and the memory system and the L2s work at the same time.
+// A counting sort in two kernels: counts per workgroup and bin, then places.  The order inside a bin is left to chance;
+// nothing that is computed hangs on it.
+constexpr int kDealGroups = 32, kDealBins = 512, kDealThreads = 512;
+
+__device__ inline int deal_bin(const int32_t *__restrict__ coord, int p, int shift)
+{
+    // (a partition inside one row: its end lies in the row it starts in)
+    return coord[2 * p] == coord[2 * p + 2] ? coord[2 * p + 1] >> shift : -1;
+}
+
+__global__ void __launch_bounds__(kDealThreads)
+deal_count_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, int32_t *__restrict__ counts)
+{
+    __shared__ int s_count[kDealBins + 8];
+    for (int i = threadIdx.x; i < kDealBins + 8; i += kDealThreads) s_count[i] = 0;
+    __syncthreads();
+    const int first = blockIdx.x * chunk, end = P < first + chunk ? P : first + chunk;
+    for (int p = first + (int)threadIdx.x; p < end; p += kDealThreads) {
+        const int bin = deal_bin(coord, p, shift);
+        if (bin >= 0) {
+            atomicAdd(&s_count[bin], 1);
+            atomicAdd(&s_count[kDealBins + (p & 7)], 1);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kDealBins + 8; i += kDealThreads) counts[blockIdx.x * (kDealBins + 8) + i] = s_count[i];
+}
+
+__global__ void __launch_bounds__(kDealThreads)
+deal_place_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, const int32_t *__restrict__ counts,
+                  SpmmDeal deal)
+{
+    static_assert(kDealThreads == kDealBins, "a thread per bin");
+    __shared__ int s_at[kDealBins + 8], s_wave[kDealThreads / NACHO_WAVE], s_class[8];
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE;
+    // entries of the thread's bin: all, and those of the workgroups before this one; the same of the residues
+    auto tally = [&](int i, int &all, int &before) {
+        all = before = 0;
+        int c[kDealGroups];
+#pragma unroll
+        for (int u = 0; u < kDealGroups; ++u) c[u] = counts[u * (kDealBins + 8) + i];
+#pragma unroll
+        for (int u = 0; u < kDealGroups; ++u) {
+            all += c[u];
+            before += u < (int)blockIdx.x ? c[u] : 0;
+        }
+    };
+    int all, before, class_all = 0, class_before = 0;
+    tally(tid, all, before);
+    if (tid < 8) tally(kDealBins + tid, class_all, class_before);
+    const int incl = wave_inclusive_scan(all);
+    if (lane == NACHO_WAVE - 1) s_wave[wave] = incl;
+    if (tid < 8) s_class[tid] = class_all;
+    __syncthreads();
+    int base = incl - all;
+    for (int u = 0; u < wave; ++u) base += s_wave[u];
+    s_at[tid] = base + before;
+    if (tid < 8) {
+        int start = 0;
+        for (int u = 0; u < tid; ++u) start += s_class[u];
+        s_at[kDealBins + tid] = start + class_before;
+    }
+    __syncthreads();
+    const int first = blockIdx.x * chunk, end = P < first + chunk ? P : first + chunk;
+    for (int p = first + tid; p < end; p += kDealThreads) {
+        const int bin = deal_bin(coord, p, shift);
+        int at = -1;
+        if (bin >= 0) {
+            deal.sorted[atomicAdd(&s_at[bin], 1)] = p;
+            at = atomicAdd(&s_at[kDealBins + (p & 7)], 1);
+        }
+        deal.place[p] = at;
     }
 }
 
 }  // namespace
 
+int64_t spmm_deal_words(int64_t P) { return 2 * P + kDealGroups * (kDealBins + 8); }
+
+hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int32_t *words, SpmmDeal *deal, hipStream_t stream)
+{
+    int shift = 0;
+    while ((n_cols - 1) >> shift >= kDealBins) ++shift;
+    const int chunk = (int)((P + kDealGroups - 1) / kDealGroups);
+    deal->place = words;
+    deal->sorted = words + P;
+    int32_t *counts = words + 2 * P;
+    hipLaunchKernelGGL(deal_count_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, coord, (int)P, chunk, shift, counts);
+    hipLaunchKernelGGL(deal_place_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, coord, (int)P, chunk, shift, counts,
+                       *deal);
+    return hipGetLastError();
+}
+
 int spmm_capacity() { return kGrain; }
 
 // Non-zeros per partition when the caller leaves the partitioning to the library: enough wavefronts for the chip.
-int spmm_grain(int64_t nnz, int units)
+// Calls that sort their partitions take shorter ones, which cover fewer columns, the shorter the wider a row of B is: its
+// gathers are what that saves, the carries what it costs (10M non-zeros in 200k rows, 256, 192, 128 and 64 non-zeros, us: 16
+// floats 105, 111, 125, -; 64 198, 194, 195, 237; 64 doubles 429, 404, 380, 374; 200 doubles 1635, 1532, 1397, 1284).
+int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes)
 {
+    if (dealt) return row_bytes >= 768 ? 64 : (row_bytes >= 384 ? 128 : (row_bytes >= 144 ? 192 : 256));
     const int64_t per = nnz / ((int64_t)units * 16);
     return per >= kGrain ? kGrain : (per < 64 ? 64 : (int)((per + 63) / 64 * 64));
+}
+
+// Whether a call sorts its partitions: a partition kernel and two more in front are 20 us, which pays from about 600 MB of
+// gathers on, at least a cache line each (us, unsorted and sorted: 1M non-zeros, 64 columns of doubles 47 and 52, 200 of floats 89
+// and 77, of doubles 185 and 133; 3M, 16 floats 44 and 44, 64 77 and 69; 10M, 4 138 and 112, 64 297 and 194), while an L2 does
+// not hold B anyway (5M, 4 doubles, 3.2 MB of B: 63 and 65).
+bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes)
+{
+    return (double)nnz * (double)(row_bytes > 128 ? row_bytes : 128) >= 6e8 && (double)n_cols * (double)row_bytes >= 4e6;
 }
 
 // Fixed-grain calls do without a partition kernel: the wavefronts of the executing kernel find their rows in two to
@@ -358,10 +492,12 @@ bool spmm_whole(int64_t P, int64_t n_rows) { return n_rows <= P * 1024; }
 hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *B, int n, int64_t ldb, void *C, int64_t ldc, int64_t n_rows, int64_t nnz,
                             int32_t *coord, int32_t *posn, int64_t *cost, int64_t P, void *carry_val,
-                            int32_t *carry_row, int64_t grain, int64_t cost_scale, bool whole,
-                            hipStream_t stream)
+                            int32_t *carry_row, int64_t grain, int64_t cost_scale, bool whole, const SpmmDeal &deal,
+                            double b_bytes, hipStream_t stream)
 {
     const int V = dtype == NACHO_F64 ? 2 : 4;
+    // (an L2 holds 4 MB; 1.3M non-zeros, 37 columns of doubles, 15 MB of B: 65 to 48 us)
+    const bool deal_rows = b_bytes > 4e6;
     // stretches of up to 64 pieces of V columns, of about equal width
     const int pieces = n < V ? n : (n + V - 1) / V, stretches = (pieces + NACHO_WAVE - 1) / NACHO_WAVE;
     const int per = (pieces + stretches - 1) / stretches;
@@ -369,7 +505,7 @@ hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, c
 #define NACHO_SPMM_LAUNCH(T, VV, W, CPL, WHOLE)                                                                         \
     hipLaunchKernelGGL((spmm_exec_kernel<T, VV, W, CPL, WHOLE>), dim3((unsigned)P, (unsigned)stretches), dim3(NACHO_WAVE), 0,  \
                        stream, pos, crd, (const T *)val, (const T *)B, n, span, ldb, (T *)C, ldc, coord, posn, cost,    \
-                       (T *)carry_val, carry_row, (int)n_rows, (int)nnz, (int)grain, cost_scale, \
+                       (T *)carry_val, carry_row, (int)n_rows, (int)nnz, (int)grain, cost_scale, deal, deal_rows, \
                        nacho_host::wave_log())
 #define NACHO_SPMM_SHAPE(T, VV, W, CPL)                                                                                 \
     do {                                                                                                                \
@@ -399,14 +535,18 @@ hipError_t launch_spmm_fixup(int dtype, void *C, int64_t ldc, int n, int64_t P, 
                              const int32_t *carry_row, const int32_t *pos, const int32_t *posn, int64_t grain,
                              hipStream_t stream)
 {
-    constexpr int cols = kFixLanes * kFixCols;
-    const dim3 grid((unsigned)((P + kFixGroups - 1) / kFixGroups), (unsigned)((n + cols - 1) / cols));
-    if (dtype == NACHO_F64)
-        hipLaunchKernelGGL((spmm_fixup_kernel<double>), grid, dim3(256), 0, stream, (double *)C, ldc,
-                           n, (int)P, (const double *)carry_val, carry_row, pos, posn, (int)grain);
-    else
-        hipLaunchKernelGGL((spmm_fixup_kernel<float>), grid, dim3(256), 0, stream, (float *)C, ldc,
-                           n, (int)P, (const float *)carry_val, carry_row, pos, posn, (int)grain);
+#define NACHO_FIXUP_LAUNCH(T, V)                                                                                        \
+    hipLaunchKernelGGL((spmm_fixup_kernel<T, V>),                                                                       \
+                       dim3((unsigned)((P * (kFixCols / V) + 255) / 256), (unsigned)((n + kFixCols - 1) / kFixCols)),   \
+                       dim3(256), 0, stream, (T *)C, ldc, n, (int)P, (const T *)carry_val, carry_row, pos, posn, (int)grain)
+    if (dtype == NACHO_F64) {
+        if (n >= 2) NACHO_FIXUP_LAUNCH(double, 2);
+        else NACHO_FIXUP_LAUNCH(double, 1);
+    } else {
+        if (n >= 4) NACHO_FIXUP_LAUNCH(float, 4);
+        else NACHO_FIXUP_LAUNCH(float, 1);
+    }
+#undef NACHO_FIXUP_LAUNCH
     return hipGetLastError();
 }
 

@@ -50,17 +50,8 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     __shared__ int32_t spos[RBLK + 1];
 
     const int lane = threadIdx.x;
-    // Which partition this workgroup executes.  Workgroups are handed to the 8
-    // XCDs in turn (workgroup w runs on XCD w mod 8) and every XCD has its own
-    // L2, which x does not fit.  The partitions that lie inside one long row are
-    // therefore dealt out so that XCD j gets the j-th eighth of the row, in
-    // ascending order: its gathers then stay inside one eighth of x (columns
-    // are sorted inside a row), which its L2 holds.  With fixed-grain queries
-    // the partitions inside row r are first = ceil(pos[r] / grain) .. end - 1 =
-    // floor(pos[r+1] / grain) - 1.  Among the workgroups first .. end - 1 those
-    // with index = j (mod 8) take, in order, the j-th stretch of these
-    // partitions (stretches as long as there are such workgroups): a
-    // permutation of first .. end - 1; everything else keeps its index.
+    // Which partition this workgroup executes: those inside one long row are dealt out by XCD, so that the gathers of an XCD
+    // stay inside one eighth of x, which its L2 holds (all of x it does not).
     int p = blockIdx.x;
     // (fused search) the rows and positions of the boundaries p and p + 1
     int r0 = 0, r1 = 0, n0 = 0, n1 = 0;
@@ -79,20 +70,7 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         const int r = kFused ? r0 : coord[2 * p];
         if (r < n_rows) {
             const int base = pos[0];
-            const int first = shares_before(pos[r] - base, grain);
-            const int end = (pos[r + 1] - base) / grain;
-            if (end - first >= 4 && p >= first && p < end) {
-                const int j = p & 7;
-                int before = 0, mine = 0;              // partitions of the stretches before stretch j; first workgroup of j
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                    const int f = first + ((jj - first) & 7);      // first workgroup >= first with index = jj (mod 8)
-                    const int cnt = f < end ? (end - f + 7) >> 3 : 0;
-                    if (jj < j) before += cnt;
-                    if (jj == j) mine = f;
-                }
-                p = first + before + ((p - mine) >> 3);
-            }
+            p = dealt_partition(p, pos[r] - base, pos[r + 1] - base, grain);
         }
     }
     // k = 1, d = 2: coord[b*2 + 0] = row, posn[b*2 + 1] = position in crd/val
