@@ -28,8 +28,8 @@
 //      k - 1 equal keys follow those of the product; every wavefront counts all
 //      bits by itself (two 64-bit words per lane and one scan);
 //   4. prefix sum: publishes the partition's counts and reads the counts of
-//      everything before the partition (two levels, see below).  While that is on
-//      its way every thread asks for the VALUES of its output entries, straight
+//      everything before the partition (two levels, see below).  In front of that
+//      every thread asks for the VALUES of its output entries, straight
 //      from the operands: in the merged order a wavefront's 64 places read one
 //      contiguous stretch per operand, and the values need no place in LDS;
 //   5. compute: every output entry writes coordinate and value at offset + heads
@@ -102,11 +102,13 @@ template <typename KeyT, typename T, bool kSmall> struct Shape {
 //   word:  bit 31 published, bits 14..27 rows, bits 0..13 nnz
 //   total: bit 63 published, bits 31..61 rows, bits 0..30 nnz
 // Workgroups per chunk.  Vectors: a large chunk, so that few totals are read (their workgroups run
-// nearly in step and a total is there early).  Matrices and tensors: a small one; their partitions
+// nearly in step and a total is there early).  Matrices and tensors: a smaller one; their partitions
 // take unequal time, the waiting wavefronts poll the words of their chunk, and hundreds of them on
-// the same 2 KB of words measured a sixth slower than on 256 bytes each.
-constexpr int kChunkVector = 512, kChunkOther = 64;
-constexpr int chunk_size(int fmt) { return fmt == SPADD_VECTOR ? kChunkVector : kChunkOther; }
+// the same 2 KB of words are slower (chunks of 64, 128 and 256, us: two DCSR matrices of 20M 164, 159, 163; two tensors
+// of 8M 116, 114, 115; three CSR matrices of 5M 87.7, 87.9, 92.5).
+// Products: smaller still, their partitions differ most (the product of two DCSR matrices of 20M with chunks of 128 4 % slower).
+constexpr int kChunkVector = 512, kChunkOther = 128, kChunkProduct = 64;
+constexpr int chunk_size(int fmt, bool mul) { return fmt == SPADD_VECTOR ? kChunkVector : (mul ? kChunkProduct : kChunkOther); }
 constexpr int word_loads(int chunk) { return (chunk + NACHO_WAVE - 1) / NACHO_WAVE; }   // words of a chunk a lane reads
 constexpr int kSpinLimit = 1 << 14;   // polls (each a sleep + one round trip to memory: tens of milliseconds in all)
 constexpr unsigned kWordValid = 0x80000000u;
@@ -323,7 +325,7 @@ __device__ inline bool sum_words(const unsigned int *words, int64_t c0, int m, c
 // Second level: the two 31-bit fields of the totals of chunks 0 .. chunk - 1, summed, once published.
 template <int kChunk>
 __device__ inline bool sum_totals(const unsigned long long *totals, const unsigned int *words, int64_t chunk, int lane,
-                                  int &lo31, int &hi31)
+                                  unsigned long long early, int &lo31, int &hi31)
 {
     // A total that its chunk's last workgroup has not published yet (that workgroup first has to get to
     // its own prefix sum) is not waited for: the words of that chunk are summed here -- they may all be
@@ -332,8 +334,8 @@ __device__ inline bool sum_totals(const unsigned long long *totals, const unsign
     const unsigned none[word_loads(kChunk)] = {};
     for (int64_t first = 0; first < chunk; first += NACHO_WAVE) {
         const int64_t j = first + lane;
-        unsigned long long s = kTotalValid;
-        if (j < chunk) s = __hip_atomic_load(&totals[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long s = j < chunk ? (first == 0 ? early : 0ull) : kTotalValid;
+        if (s == 0ull) s = __hip_atomic_load(&totals[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool there = (s & kTotalValid) != 0;
         c_lo += dpp_sum(there ? (int)(s & 0x7fffffffull) : 0);
         c_hi += dpp_sum(there ? (int)((s >> 31) & 0x7fffffffull) : 0);
@@ -394,7 +396,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
     typedef Shape<KeyT, T, kSmall> S;
     constexpr int D = FMT == SPADD_VECTOR ? 1 : (FMT == SPADD_CSF3 ? 3 : 2);
-    constexpr int kChunk = chunk_size(FMT), kWordLoads = word_loads(kChunk);
+    constexpr int kChunk = chunk_size(FMT, kMul), kWordLoads = word_loads(kChunk);
     constexpr bool kCsf = FMT == SPADD_CSF3;   // third-order tensors: three compressed levels
     constexpr bool kCoo = FMT == SPADD_COO;    // coordinate lists: the row of an entry is stored with it
     constexpr bool kWindow = D >= 2 && !kCoo;  // rows (fibres) come from pos arrays
@@ -1147,9 +1149,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
     wave_sync();                               // (a wavefront's places are merged and marked by its own threads)
 
-    // ---- the values, sums: every place asks for its own, straight from the operands -------------
-    // (64 places read one contiguous stretch per operand; the requests travel while the heads are counted and
-    // the counts of the partitions before this one are looked up)
+    // ---- the values: where an entry's is ---------------------------------------------------------
     T val[R], tail = T(0);
     // address of the value of the entry an order word names
     auto value_at = [&](int o) -> T {
@@ -1161,18 +1161,6 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         if constexpr (K <= 2) return moved ? (int)w.order[m] : (mb + m) * KB;
         else return moved ? (int)w.order[mb + m] : (only << 13 | (mb + m));
     };
-    if (!kMul && n > 0) {
-        int o[R];
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int m = place0 + j * NACHO_WAVE + lane;
-            o[j] = order_of(m < n ? m : n - 1);
-            // (past the last place: the order word of an entry of another wavefront may not be there yet)
-            if (m >= n) o[j] = K <= 2 ? of(sb_v, live_t) * KB : (live_t << 13 | of(sb_v, live_t));
-        }
-#pragma unroll
-        for (int j = 0; j < R; ++j) val[j] = value_at(o[j]);
-    }
 
     // ---- 3. assembly: which places are emitted, and how many before every block -----------
     // lane l: block block0 + l of the wavefront's own (and, l = R, the one behind them)
@@ -1253,6 +1241,30 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 __hip_atomic_store(&counts_of2[p], kWordValid | (unsigned)own_slices, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
+    }
+
+    // sums: every place asks for its value, straight from the operands (64 places read one contiguous stretch per operand).
+    // Not before the counts are published: asking takes one to ten microseconds where the memory pipeline is full, and everybody
+    // behind this workgroup waits for them (three vectors, 11M entries: 71.0 to 68.6 us; two DCSR matrices of 20M: 175 to 168).
+    if (!kMul && n > 0) {
+        int o[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int m = place0 + j * NACHO_WAVE + lane;
+            o[j] = order_of(m < n ? m : n - 1);
+            // (past the last place: the order word of an entry of another wavefront may not be there yet)
+            if (m >= n) o[j] = K <= 2 ? of(sb_v, live_t) * KB : (live_t << 13 | of(sb_v, live_t));
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) val[j] = value_at(o[j]);
+    }
+
+    // The counts of the workgroups before this one are asked for behind the values: loads come back in order, so they are
+    // looked at when the values are there however early they were asked for, and a word that was not published yet costs
+    // another round trip (asked for in front of the values, three vectors 68.6 us, like this 61.6; two DCSR matrices 168 and
+    // 162, two tensors 120 and 115).
+    unsigned long long early_total = 0ull;
+    if (wave == 0) {
         const int m = (int)(p - chunk0);
 #pragma unroll
         for (int i = 0; i < kWordLoads; ++i) {
@@ -1261,7 +1273,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if (i * NACHO_WAVE < m && j < m)
                 early[i] = __hip_atomic_load(&counts_of[chunk0 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-    }
+    } else if (wave == 1 && lane < chunk)
+        early_total = __hip_atomic_load(&totals[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // CSR: the rows whose pos this partition writes, and the places before such a row
     int first_row = 0, end_row = 0, pos_at = 0;
@@ -1388,8 +1401,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         int c_nnz = 0, c_rows = 0, c_slices = 0, unused = 0;
         bool ok = true;
         if (chunk > 0) {
-            ok = sum_totals<kChunk>(totals, counts_of, chunk, lane, c_nnz, c_rows);
-            if (kCsf && ok) ok = sum_totals<kChunk>(totals2, counts_of2, chunk, lane, c_slices, unused);
+            ok = sum_totals<kChunk>(totals, counts_of, chunk, lane, early_total, c_nnz, c_rows);
+            if (kCsf && ok) ok = sum_totals<kChunk>(totals2, counts_of2, chunk, lane, 0ull, c_slices, unused);
         }
         if (lane == 0) {
             w.more_nnz = c_nnz;
@@ -1560,7 +1573,8 @@ spadd_kernel(MergeArgs args)
 {
     __shared__ TileOf<FMT, T, KeyT, kSmall> w;
     const WaveStamp stamp = wave_begin();
-    touch_arguments<sizeof(MergeArgs) <= 1408 ? sizeof(MergeArgs) : 1408>();
+    // (not where half of the workgroups find that they have nothing to do)
+    if constexpr (!kMapped) touch_arguments<sizeof(MergeArgs) <= 1408 ? sizeof(MergeArgs) : 1408>();
     const ArgPtr arg_ptr = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
     merge_partition<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch>(arg_ptr, w, args.ops, stamp);
 }
@@ -1570,7 +1584,7 @@ inline int64_t chunks_of(int64_t P, int chunk) { return (P + chunk - 1) / chunk;
 template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch>
 hipError_t launch_k(const MergeLaunch &a)
 {
-    MergeArgs args{a.ops, a.vals, a.P, chunks_of(a.P, chunk_size(FMT)), a.coord, a.posn, a.tile_state, a.out, a.fields,
+    MergeArgs args{a.ops, a.vals, a.P, chunks_of(a.P, chunk_size(FMT, kMul)), a.coord, a.posn, a.tile_state, a.out, a.fields,
                    nacho_host::wave_log(), a.search};
     hipLaunchKernelGGL((spadd_kernel<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch>), dim3((unsigned)a.P), dim3(kThreads), 0,
                        a.s, args);

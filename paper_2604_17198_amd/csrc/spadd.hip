@@ -74,8 +74,8 @@ MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t
 int spadd_capacity(int fmt, int dtype, const MergeFields &f) { (void)fmt; return capacity_of(f.wide != 0, f.small != 0, dtype); }
 
 // 64-bit words of look-up state: one per chunk, then one 32-bit word per workgroup -- twice (third-order
-// tensors count slices in the second set); sized for the smaller chunk, which covers both
-int64_t spadd_state_words(int64_t P) { return 2 * (chunks_of(P, kChunkOther) + (P + 1) / 2); }
+// tensors count slices in the second set); sized for the smallest chunk, which covers all
+int64_t spadd_state_words(int64_t P) { return 2 * (chunks_of(P, kChunkProduct) + (P + 1) / 2); }
 
 hipError_t launch_spadd_vector_search(int dtype, const DevOperands &ops, const SpaddValues &vals, int64_t P,
                                       const SpaddSearch &search, unsigned long long *tile_state, const SpaddOut &out,
