@@ -1262,19 +1262,22 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // The counts of the workgroups before this one are asked for behind the values: loads come back in order, so they are
     // looked at when the values are there however early they were asked for, and a word that was not published yet costs
     // another round trip (asked for in front of the values, three vectors 68.6 us, like this 61.6; two DCSR matrices 168 and
-    // 162, two tensors 120 and 115).
+    // 162, two tensors 120 and 115; the product of two DCSR matrices of 20M, whose values are asked for further down, 174.8 and 165.9).
     unsigned long long early_total = 0ull;
-    if (wave == 0) {
-        const int m = (int)(p - chunk0);
+    auto ask_for_counts = [&]() {
+        if (wave == 0) {
+            const int m = (int)(p - chunk0);
 #pragma unroll
-        for (int i = 0; i < kWordLoads; ++i) {
-            const int j = i * NACHO_WAVE + lane;
-            early[i] = kWordValid;
-            if (i * NACHO_WAVE < m && j < m)
-                early[i] = __hip_atomic_load(&counts_of[chunk0 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    } else if (wave == 1 && lane < chunk)
-        early_total = __hip_atomic_load(&totals[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int i = 0; i < kWordLoads; ++i) {
+                const int j = i * NACHO_WAVE + lane;
+                early[i] = kWordValid;
+                if (i * NACHO_WAVE < m && j < m)
+                    early[i] = __hip_atomic_load(&counts_of[chunk0 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        } else if (wave == 1 && lane < chunk)
+            early_total = __hip_atomic_load(&totals[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if constexpr (!kMul) ask_for_counts();
 
     // CSR: the rows whose pos this partition writes, and the places before such a row
     int first_row = 0, end_row = 0, pos_at = 0;
@@ -1377,6 +1380,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             }
         }
     }
+
+    if constexpr (kMul) ask_for_counts();
 
     // ---- 4. prefix sum, second half: wavefront 0 reads the counts of the workgroups before this one in its
     // chunk, wavefront 1 those of the chunks before
