@@ -426,10 +426,12 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
 // range is a few cache lines every lane has one.  (10M + 10M entries, 8192 boundaries, evenly spaced candidates: 64 a round 46
 // us, 16 24, 8 19 -- with thousands of boundaries in flight the lines are what takes the time, a line a candidate, with few of
 // them the rounds are.  Two DCSR matrices of 20M, 7218 boundaries, both levels: 29.2 us with eight evenly spaced ones, 21.0 like
-// this.)
+// this.)  Coordinate lists' candidates stay evenly spaced, a line each however often the range is cut: eight of them with more
+// than a thousand boundaries in flight (`many`; the product of two lists of 20M, 7172 boundaries: 16 a round 174.1 us, 8 166.0).
 // Requires both segments non-empty and 0 <= R < their total length.
 template <class Acc>
-__device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const Acc &A, const Acc &B, int l, int h, int R, int sh)
+__device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const Acc &A, const Acc &B, int l, int h, int R, int sh,
+                                                        bool many)
 {
     typedef typename Acc::type C;
     const int lane = lane_id();
@@ -439,14 +441,14 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
     int lo = R > nb ? R - nb : 0, hi = R < na ? R : na;
     float at = (float)R * (float)na * __builtin_amdgcn_rcpf((float)na + (float)nb) - (float)lo;
     bool even = Acc::kPairs;                           // (rows of unequal length: an expectation is worth nothing)
-    constexpr int kShare = 4, kWays = NACHO_WAVE / kShare;     // lanes that share a candidate read the same words
+    const int share = Acc::kPairs && many ? 3 : 2;     // log2 of the lanes that share a candidate: they read the same words
     while (lo < hi) {
         const int w = hi - lo;                         // candidates lo + 1 .. hi
         int i;
         if (w <= 256) i = (lane + 1) * ((w + NACHO_WAVE - 1) / NACHO_WAVE);
         else {
-            i = 1 + aimed_sample(lane / kShare, kWays, w, at, even);
-            if (__ballot(lane > 0 && i < lane_left(i)) != 0ull) i = 1 + aimed_sample(lane / kShare, kWays, w, at, true);
+            i = 1 + aimed_sample(lane >> share, NACHO_WAVE >> share, w, at, even);
+            if (__ballot(lane > 0 && i < lane_left(i)) != 0ull) i = 1 + aimed_sample(lane >> share, NACHO_WAVE >> share, w, at, true);
         }
         i = lo + (i < w ? i : w);
         const int j = R - i;                           // (i <= R, and i >= R - nb: 0 <= j <= nb)
@@ -487,7 +489,8 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
 // One level of Algorithm 1 for one query, 0 <= R: as group_search, and what is shorter than that.
 template <int K, class Acc, int kDepth>
 __device__ __forceinline__ LevelFound<Acc> search_level(const DevOperands &ops, const Group<K> &g, int m, const Acc &crd,
-                                                        Ints32 pos_1, Ints32 pos_2, int l, int h, int R, int total, int sh)
+                                                        Ints32 pos_1, Ints32 pos_2, int l, int h, int R, int total, int sh,
+                                                        bool many = false)
 {
     LevelFound<Acc> found;
     found.row_from = l;
@@ -515,7 +518,7 @@ __device__ __forceinline__ LevelFound<Acc> search_level(const DevOperands &ops, 
             found.c = R;
             return found;
         }
-        if constexpr (K == 2) return split_search<Acc>(g, Acc::of(ops, 0, m), Acc::of(ops, 1, m), l, h, R, sh);
+        if constexpr (K == 2) return split_search<Acc>(g, Acc::of(ops, 0, m), Acc::of(ops, 1, m), l, h, R, sh, many);
     }
     if constexpr (K > 1 || kDepth > 0) found = group_search<K, Acc, kDepth>(g, crd, pos_1, pos_2, l, h, R, total, sh);
     return found;
@@ -593,7 +596,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
         // coordinate lists, d == 2: one search over the (row, column) pairs; the row-level position of an operand is
         // that of its first entry in the boundary's row
         const PairCoords pairs = {ints_of([&](int t) { return ops.lvl[t][0].crd; }), ints_of([&](int t) { return ops.lvl[t][1].crd; })};
-        const auto f = search_level<K, PairCoords, 0>(ops, g, 0, pairs, nullptr, nullptr, 0, count_of(0), R, total, 0);
+        const auto f = search_level<K, PairCoords, 0>(ops, g, 0, pairs, nullptr, nullptr, 0, count_of(0), R, total, 0, P > 1024);
         R -= f.c;
         const int x0 = (int)(f.x >> 32), x1 = (int)(f.x & 0xffffffffLL);
         const int row_at = group_lower_bound<K>(g, f.row_from, f.p, [&](int at) { return pairs.row[at] < x0; });
