@@ -52,12 +52,16 @@ bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes);
 int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes);      // non-zeros of a fixed-grain partition
 // Whether a fixed-grain call goes without a partition kernel (the executing kernel writes the table and the zeros).
 bool spmm_whole(int64_t P, int64_t n_rows);
-// Workgroup w executes partition sorted[place[w]], or partition w where place[w] < 0.  NULL: workgroup w partition w.
+// Workgroup w executes partition sorted[place[w]], or partition w where place[w] is -1.  Where all of them are -2, the workgroups
+// w < joined execute partitions w * join .. of the table in one piece.  NULL: workgroup w partition w.
 struct SpmmDeal {
     int32_t *place, *sorted;
+    int join, joined;
 };
 int64_t spmm_deal_words(int64_t P);                 // 32-bit words it takes
-hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int32_t *words, SpmmDeal *deal, hipStream_t stream);
+// row_bytes: of a row of B in one pass.  join: partitions that make up one of an unsorted call (1: they are never joined).
+hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int64_t row_bytes, int join, int32_t *words,
+                            SpmmDeal *deal, hipStream_t stream);
 // carry_val: n values per partition.  b_bytes: of B.  `grain` (non-zeros) > 0: fixed-grain partitions.
 hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *B, int n, int64_t ldb, void *C, int64_t ldc, int64_t n_rows, int64_t nnz,
@@ -66,7 +70,7 @@ hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, c
                             double b_bytes, hipStream_t stream);
 hipError_t launch_spmm_fixup(int dtype, void *C, int64_t ldc, int n, int64_t P, const void *carry_val,
                              const int32_t *carry_row, const int32_t *pos, const int32_t *posn, int64_t grain,
-                             hipStream_t stream);
+                             const SpmmDeal &deal, hipStream_t stream);
 
 // ---- k-way union addition ---------------------------------------------------
 enum { SPADD_VECTOR = 0, SPADD_CSR = 1, SPADD_DCSR = 2, SPADD_COO = 3, SPADD_CSF3 = 4 };

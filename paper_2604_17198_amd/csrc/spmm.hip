@@ -27,6 +27,7 @@ namespace nacho {
 namespace {
 
 constexpr int kGrain = 512;                    // most non-zeros of a partition
+constexpr int kDealAlone = -1, kDealJoined = -2;       // SpmmDeal::place below 0
 
 // V elements of a row of B or C; in memory they are aligned as one element is (16-byte loads and stores need no more).
 template <typename T, int V> struct Piece {
@@ -36,7 +37,7 @@ template <typename T, int V> struct Piece {
 
 // W lanes a row, CPL pieces of V elements a lane.  kWhole: there is no partition kernel; the wavefront searches its
 // rows, stores its part of the partition table and writes the zeros of its empty rows.
-// `deal` (without kWhole): the partition a workgroup executes, see deal_count_kernel.
+// `deal` (without kWhole): what a workgroup executes, see deal_count_kernel.
 template <typename T, int V, int W, int CPL, bool kWhole>
 __global__ void __launch_bounds__(NACHO_WAVE)
 spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd, const T *__restrict__ val,
@@ -62,10 +63,17 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     int32_t *s_crd = reinterpret_cast<int32_t *>(smem + kSlots * sizeof(T));
 
     const int lane = threadIdx.x, g = lane / W, gl = lane & (W - 1);
-    int p = blockIdx.x;
+    int p = blockIdx.x, b0 = p, b1 = p + 1;            // b0, b1: the table's boundaries of what is executed
     if (!kWhole && deal.place) {
         const int at = deal.place[p];
-        if (at >= 0) p = deal.sorted[at];
+        if (at == kDealJoined) {
+            if (p >= deal.joined) return;
+            b0 = p * deal.join;
+            b1 = b0 + deal.join < (int)gridDim.x ? b0 + deal.join : (int)gridDim.x;
+        } else if (at >= 0) {
+            p = b0 = deal.sorted[at];
+            b1 = b0 + 1;
+        }
     }
     int r0, r1, n0, n1;
     if (kWhole) {
@@ -88,8 +96,8 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             }
         }
     } else {
-        r0 = coord[2 * p]; r1 = coord[2 * p + 2];
-        n0 = posn[2 * p + 1]; n1 = posn[2 * p + 3];
+        r0 = coord[2 * b0]; r1 = coord[2 * b1];
+        n0 = posn[2 * b0 + 1]; n1 = posn[2 * b1 + 1];
     }
     const int len = n1 - n0;
     const int S = ((len + NG - 1) / NG + 3) & ~3;      // a group's stretch
@@ -284,7 +292,7 @@ template <typename T, int V>
 __global__ void __launch_bounds__(256)
 spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restrict__ carry_val,
                   const int32_t *__restrict__ carry_row, const int32_t *__restrict__ pos,
-                  const int32_t *__restrict__ posn, int grain)
+                  const int32_t *__restrict__ posn, int grain, SpmmDeal deal)
 {
     typedef typename Piece<T, V>::type Vec;
     typedef typename Piece<T, V>::mem Mem;
@@ -294,6 +302,12 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
     __shared__ int s_first, s_end, s_row;
     const int g = threadIdx.x / kFixLanes, gl = threadIdx.x & (kFixLanes - 1);
     const int p = blockIdx.x * kFixGroups + g;
+    if (deal.join > 1 && deal.place[blockIdx.x * kFixGroups] == kDealJoined) {
+        // (a carry for every `join` partitions; place is the same throughout then)
+        P = deal.joined;
+        grain *= deal.join;
+        if ((int)blockIdx.x * kFixGroups >= P) return;
+    }
     // (n >= V; the last piece of a row moves back where it would stick out: the columns it shares with the one before are
     // that one's to store)
     const int j0 = blockIdx.y * (kFixLanes * V) + gl * V, col = j0 < n - V ? j0 : n - V, shared = j0 - col;
@@ -370,94 +384,127 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
 // L2 whatever their order, and the memory system and the L2s work at the same time.
 // A counting sort in two kernels: counts per workgroup and bin, then places.  The order inside a bin is left to chance;
 // nothing that is computed hangs on it.
-constexpr int kDealGroups = 32, kDealBins = 512, kDealThreads = 512;
+//
+// Partitions of 64 or 128 non-zeros write and add four to eight times the carries of 512, which pays where neighbours share rows of B,
+// sorted or as they are.  Where they do not, a wavefront executes `join` partitions of the table in one piece, as long as an unsorted
+// call's: where fewer than 1/8 of the partitions lie inside a row and the first columns of fewer than half of the neighbours are
+// within 4 MB of B (an L2) of each other.  (6M non-zeros, 200 doubles, us, each partition alone and joined: rows of 30 with columns
+// at random 1639 and 1521, in a band of 4000 columns 836 and 1389; rows by Zipf's law, 30 on average, 860 and 1527.)
+constexpr int kDealGroups = 32, kDealBins = 512, kDealThreads = 1024, kDealWords = kDealBins + 9;
 
-__device__ inline int deal_bin(const int32_t *__restrict__ coord, int p, int shift)
+// Of the lanes with the same residue (mod 8): how many are set in `mask`, and how many of those below this lane.
+__device__ inline int class_count(unsigned long long mask, int residue)
 {
-    // (a partition inside one row: its end lies in the row it starts in)
-    return coord[2 * p] == coord[2 * p + 2] ? coord[2 * p + 1] >> shift : -1;
+    const unsigned mine = 0x01010101u << residue;
+    return __popc((unsigned)mask & mine) + __popc((unsigned)(mask >> 32) & mine);
+}
+__device__ inline int class_rank(unsigned long long mask, int residue)
+{
+    const unsigned mine = 0x01010101u << residue;
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32) & mine, __builtin_amdgcn_mbcnt_lo((unsigned)mask & mine, 0u));
 }
 
+// place[p]: the bin of a partition inside one row, else -1.  counts: of the bins, of the residues, of neighbours near each other.
 __global__ void __launch_bounds__(kDealThreads)
-deal_count_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, int32_t *__restrict__ counts)
+deal_count_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, int near_columns, int32_t *__restrict__ place,
+                  int32_t *__restrict__ counts)
 {
-    __shared__ int s_count[kDealBins + 8];
-    for (int i = threadIdx.x; i < kDealBins + 8; i += kDealThreads) s_count[i] = 0;
+    __shared__ int s_count[kDealWords];
+    if (threadIdx.x < kDealWords) s_count[threadIdx.x] = 0;
     __syncthreads();
+    const int lane = lane_id();
     const int first = blockIdx.x * chunk, end = P < first + chunk ? P : first + chunk;
-    for (int p = first + (int)threadIdx.x; p < end; p += kDealThreads) {
-        const int bin = deal_bin(coord, p, shift);
-        if (bin >= 0) {
-            atomicAdd(&s_count[bin], 1);
-            atomicAdd(&s_count[kDealBins + (p & 7)], 1);
+    for (int p0 = first + (int)threadIdx.x - lane; p0 < end; p0 += kDealThreads) {
+        const int p = p0 + lane;
+        int bin = -1;
+        bool near = false;
+        if (p < end) {
+            const int2 *boundary = reinterpret_cast<const int2 *>(coord) + p;
+            const int2 a = boundary[0], e = boundary[1];       // row and column
+            // (a partition inside one row: its end lies in the row it starts in)
+            if (a.x == e.x) bin = (a.y >> shift) & (kDealBins - 1);
+            near = abs(e.y - a.y) <= near_columns;
+            place[p] = bin;
         }
+        if (bin >= 0) atomicAdd(&s_count[bin], 1);
+        const unsigned long long inside = __ballot(bin >= 0);
+        if (lane < 8 && inside) atomicAdd(&s_count[kDealBins + lane], class_count(inside, lane));       // (p0: a multiple of 64)
+        const unsigned long long close = __ballot(near);
+        if (lane == 8) atomicAdd(&s_count[kDealBins + 8], __popcll(close));
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < kDealBins + 8; i += kDealThreads) counts[blockIdx.x * (kDealBins + 8) + i] = s_count[i];
+    if (threadIdx.x < kDealWords) counts[blockIdx.x * kDealWords + threadIdx.x] = s_count[threadIdx.x];
 }
 
 __global__ void __launch_bounds__(kDealThreads)
-deal_place_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, const int32_t *__restrict__ counts,
-                  SpmmDeal deal)
+deal_place_kernel(int P, int chunk, const int32_t *__restrict__ counts, SpmmDeal deal)
 {
-    static_assert(kDealThreads == kDealBins, "a thread per bin");
-    __shared__ int s_at[kDealBins + 8], s_wave[kDealThreads / NACHO_WAVE], s_class[8];
+    __shared__ int s_at[kDealWords], s_wave[kDealThreads / NACHO_WAVE], s_class[9];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE;
-    // entries of the thread's bin: all, and those of the workgroups before this one; the same of the residues
-    auto tally = [&](int i, int &all, int &before) {
-        all = before = 0;
+    // a thread per count: of all workgroups, and of those before this one
+    int all = 0, before = 0;
+    if (tid < kDealWords) {
         int c[kDealGroups];
 #pragma unroll
-        for (int u = 0; u < kDealGroups; ++u) c[u] = counts[u * (kDealBins + 8) + i];
+        for (int u = 0; u < kDealGroups; ++u) c[u] = counts[u * kDealWords + tid];
 #pragma unroll
         for (int u = 0; u < kDealGroups; ++u) {
             all += c[u];
             before += u < (int)blockIdx.x ? c[u] : 0;
         }
-    };
-    int all, before, class_all = 0, class_before = 0;
-    tally(tid, all, before);
-    if (tid < 8) tally(kDealBins + tid, class_all, class_before);
+    }
     const int incl = wave_inclusive_scan(all);
     if (lane == NACHO_WAVE - 1) s_wave[wave] = incl;
-    if (tid < 8) s_class[tid] = class_all;
+    if (tid >= kDealBins && tid < kDealWords) s_class[tid - kDealBins] = all;
     __syncthreads();
-    int base = incl - all;
-    for (int u = 0; u < wave; ++u) base += s_wave[u];
-    s_at[tid] = base + before;
-    if (tid < 8) {
+    int inside = 0;
+    for (int u = 0; u < 8; ++u) inside += s_class[u];
+    const bool joined = deal.join > 1 && inside < P / 8 && s_class[8] < P / 2;
+    if (tid < kDealBins) {
+        int base = incl - all;
+        for (int u = 0; u < wave; ++u) base += s_wave[u];
+        s_at[tid] = base + before;
+    } else if (tid < kDealBins + 8) {
         int start = 0;
-        for (int u = 0; u < tid; ++u) start += s_class[u];
-        s_at[kDealBins + tid] = start + class_before;
+        for (int u = 0; u < tid - kDealBins; ++u) start += s_class[u];
+        s_at[tid] = start + before;
     }
     __syncthreads();
     const int first = blockIdx.x * chunk, end = P < first + chunk ? P : first + chunk;
-    for (int p = first + tid; p < end; p += kDealThreads) {
-        const int bin = deal_bin(coord, p, shift);
-        int at = -1;
-        if (bin >= 0) {
-            deal.sorted[atomicAdd(&s_at[bin], 1)] = p;
-            at = atomicAdd(&s_at[kDealBins + (p & 7)], 1);
-        }
-        deal.place[p] = at;
+    if (joined) {
+        for (int p = first + tid; p < end; p += kDealThreads) deal.place[p] = kDealJoined;
+        return;
+    }
+    for (int p0 = first + tid - lane; p0 < end; p0 += kDealThreads) {
+        const int p = p0 + lane, residue = lane & 7;           // (p0: a multiple of 64)
+        const int bin = p < end ? deal.place[p] : -1;
+        const unsigned long long mask = __ballot(bin >= 0);
+        int at = 0;
+        if (lane < 8) at = atomicAdd(&s_at[kDealBins + residue], class_count(mask, residue));
+        at = __shfl(at, residue, NACHO_WAVE) + class_rank(mask, residue);
+        if (bin >= 0) deal.sorted[atomicAdd(&s_at[bin], 1)] = p;
+        if (p < end) deal.place[p] = bin >= 0 ? at : kDealAlone;
     }
 }
 
 }  // namespace
 
-int64_t spmm_deal_words(int64_t P) { return 2 * P + kDealGroups * (kDealBins + 8); }
+int64_t spmm_deal_words(int64_t P) { return 2 * P + kDealGroups * kDealWords; }
 
-hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int32_t *words, SpmmDeal *deal, hipStream_t stream)
+hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int64_t row_bytes, int join, int32_t *words,
+                            SpmmDeal *deal, hipStream_t stream)
 {
     int shift = 0;
     while ((n_cols - 1) >> shift >= kDealBins) ++shift;
-    const int chunk = (int)((P + kDealGroups - 1) / kDealGroups);
-    deal->place = words;
-    deal->sorted = words + P;
-    int32_t *counts = words + 2 * P;
-    hipLaunchKernelGGL(deal_count_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, coord, (int)P, chunk, shift, counts);
-    hipLaunchKernelGGL(deal_place_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, coord, (int)P, chunk, shift, counts,
-                       *deal);
+    const int chunk = (int)((P + kDealGroups * NACHO_WAVE - 1) / (kDealGroups * NACHO_WAVE)) * NACHO_WAVE;
+    int32_t *counts = words;
+    deal->place = counts + kDealGroups * kDealWords;
+    deal->sorted = deal->place + P;
+    deal->join = join;
+    deal->joined = (int)((P + join - 1) / join);
+    hipLaunchKernelGGL(deal_count_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, coord, (int)P, chunk, shift,
+                       (int)(4000000 / row_bytes), deal->place, counts);
+    hipLaunchKernelGGL(deal_place_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, (int)P, chunk, counts, *deal);
     return hipGetLastError();
 }
 
@@ -533,12 +580,12 @@ hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, c
 
 hipError_t launch_spmm_fixup(int dtype, void *C, int64_t ldc, int n, int64_t P, const void *carry_val,
                              const int32_t *carry_row, const int32_t *pos, const int32_t *posn, int64_t grain,
-                             hipStream_t stream)
+                             const SpmmDeal &deal, hipStream_t stream)
 {
 #define NACHO_FIXUP_LAUNCH(T, V)                                                                                        \
     hipLaunchKernelGGL((spmm_fixup_kernel<T, V>),                                                                       \
                        dim3((unsigned)((P * (kFixCols / V) + 255) / 256), (unsigned)((n + kFixCols - 1) / kFixCols)),   \
-                       dim3(256), 0, stream, (T *)C, ldc, n, (int)P, (const T *)carry_val, carry_row, pos, posn, (int)grain)
+                       dim3(256), 0, stream, (T *)C, ldc, n, (int)P, (const T *)carry_val, carry_row, pos, posn, (int)grain, deal)
     if (dtype == NACHO_F64) {
         if (n >= 2) NACHO_FIXUP_LAUNCH(double, 2);
         else NACHO_FIXUP_LAUNCH(double, 1);

@@ -88,3 +88,63 @@ def test_rows_dealt_out(n):
     table = oracle.partition([oracle.csr(A["pos"], A["crd"], A["n_rows"], n_cols)], t["P"], queries=queries)
     assert np.array_equal(t["coord"].cpu().numpy().astype(np.int64), table["coord"])
     assert np.array_equal(t["posn"].cpu().numpy().astype(np.int64), table["posn"])
+
+
+def _records(fn, n_records):
+    """The wavefront records of one call through the instrumented library."""
+    nb.select_library(True)
+    try:
+        rec = torch.zeros(n_records * np.dtype(nb.WAVE_RECORD).itemsize, dtype=torch.uint8, device="cuda")
+        nb.instrument(rec)
+        fn()
+        torch.cuda.synchronize()
+        nb.instrument(None)
+    finally:
+        nb.select_library(False)
+    return rec.cpu().numpy().view(np.dtype(nb.WAVE_RECORD))
+
+
+@pytest.mark.parametrize("dtype,n,nnz,grain,join", [(np.float32, 200, 800_003, 64, 4), (np.float64, 97, 1_000_001, 64, 4),
+                                                    (np.float32, 100, 2_200_000, 128, 4), (np.float64, 300, 810_000, 64, 4)])
+@pytest.mark.parametrize("kind", ["random", "band", "long"])
+def test_partitions_joined(kind, dtype, n, nnz, grain, join):
+    """Short rows with columns at random: every wavefront executes `join` partitions of the table in one piece (one long row
+    among them, of more joined partitions than one group of the fix-up adds; empty rows).  In a narrow band, or with long
+    rows: one each.  The table is that of the short partitions."""
+    rng = np.random.default_rng(n)
+    n_cols = 50_000
+    head = [0, 7, grain * join * 40 + 5, 0, 0, grain * join, 1] if kind != "long" else [n_cols // 2] * 16 + [0, 3]
+    left = nnz - sum(head)
+    lens = np.array(head + [30] * (left // 30) + [left % 30, 0], np.int64)
+    A = _matrix(rng, lens, n_cols, dtype)
+    if kind != "long":                                  # the columns of rows of 30: anywhere, or in a band along the diagonal
+        row = np.repeat(np.arange(len(lens)), lens)
+        short = lens[row] <= 30
+        place = rng.integers(0, n_cols, len(row)) if kind == "random" else (row * (n_cols - 2000) // len(lens)
+                                                                            + rng.integers(0, 2000, len(row)))
+        key = np.where(short, row * n_cols + place, row * n_cols + A["crd"])
+        key = np.unique(key)
+        row, A["crd"] = key // n_cols, (key % n_cols).astype(np.int32)
+        A["pos"][1:] = np.cumsum(np.bincount(row, minlength=len(lens)))
+        A["val"] = A["val"][:len(key)]
+    nnz = int(A["pos"][-1])
+    op, code = csr_operand(A), nb.F64 if dtype == np.float64 else nb.F32
+    B = rng.uniform(-1, 1, (n_cols, n)).astype(dtype)
+    ref, sabs = oracle.spmm(A["pos"], A["crd"], A["val"], B)
+    ws = torch.full((nb.workspace_bytes(nb.OP_SPMM, [op], code, n),), 0xff, dtype=torch.uint8, device="cuda")
+    C = torch.full((A["n_rows"], n), float("nan"), dtype=dev(B).dtype, device="cuda")
+    print(f"spmm joined {kind} n={n} nnz={nnz}", flush=True)
+    nb.nacho_spmm(op, dev(B), C, ws=ws)
+    assert tol_ok(C.cpu().numpy(), ref, sabs, TOL[dtype]).all()
+    t = nb.workspace_parts(nb.OP_SPMM, [op], code, ws, n)
+    P = t["P"]
+    assert t["grain"] == grain * n and P == -(-nnz // grain)
+    queries = np.minimum(np.arange(P + 1, dtype=np.int64) * grain, nnz)
+    table = oracle.partition([oracle.csr(A["pos"], A["crd"], A["n_rows"], n_cols)], P, queries=queries)
+    assert np.array_equal(t["coord"].cpu().numpy().astype(np.int64), table["coord"])
+    assert np.array_equal(t["posn"].cpu().numpy().astype(np.int64), table["posn"])
+    items = _records(lambda: nb.nacho_spmm(op, dev(B), C, ws=ws), P)["items"].astype(np.int64)
+    assert tol_ok(C.cpu().numpy(), ref, sabs, TOL[dtype]).all()
+    assert items.sum() == nnz
+    each = grain * (join if kind == "random" else 1)
+    assert np.count_nonzero(items) == -(-nnz // each) and items.max() == each
