@@ -521,13 +521,16 @@ int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes)
     return per >= kGrain ? kGrain : (per < 64 ? 64 : (int)((per + 63) / 64 * 64));
 }
 
-// Whether a call sorts its partitions: a partition kernel and two more in front are 20 us, which pays from about 600 MB of
-// gathers on, at least a cache line each (us, unsorted and sorted: 1M non-zeros, 64 columns of doubles 47 and 52, 200 of floats 89
-// and 77, of doubles 185 and 133; 3M, 16 floats 44 and 44, 64 77 and 69; 10M, 4 138 and 112, 64 297 and 194), while an L2 does
-// not hold B anyway (5M, 4 doubles, 3.2 MB of B: 63 and 65).
+// Whether a call sorts its partitions: the partition kernel and the two of the sort are 14 us (35 with 150k partitions), which pays
+// from about 600 MB of gathers on, at least a cache line each (us, unsorted and sorted, rows by Zipf's law, 30 on average: 400k
+// non-zeros, 200 doubles 71 and 66; 1M, 200 floats 105 and 80; 3M, 64 floats 92 and 72; 5M, 32 floats 76 and 69), while two
+// L2s do not hold B anyway (3M, 64 floats, 200 a row, 4.2 MB of B: 47 and 58; rows of 100, 7.7 MB: 65 and 73; 10M, 16 floats, 80
+// a row, 8.8 MB: 117 and 99); with shorter partitions a little more (1M, 200 doubles, 200 a row, 8.8 MB: 106 and 115; 2M,
+// 128 floats, 80 a row, 14 MB: 94 and 72).
 bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes)
 {
-    return (double)nnz * (double)(row_bytes > 128 ? row_bytes : 128) >= 6e8 && (double)n_cols * (double)row_bytes >= 4e6;
+    return (double)nnz * (double)(row_bytes > 128 ? row_bytes : 128) >= 6e8 &&
+           (double)n_cols * (double)row_bytes >= (row_bytes >= 384 ? 10e6 : 7.8e6);
 }
 
 // Fixed-grain calls do without a partition kernel: the wavefronts of the executing kernel find their rows in two to
