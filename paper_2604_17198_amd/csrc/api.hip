@@ -159,6 +159,7 @@ struct CarryWs {
 // Columns SpMM works on at a time (wider operands: one pass after the other), and with them the width of its carry
 // rows: what one wavefront's lanes hold of a row of floats.  A workspace sized for 64 columns serves any operand.
 constexpr int64_t kSpmmPass = 256;
+constexpr int64_t kSpmmCarries = (int64_t)512 << 20;
 int spmm_pass(int64_t n) { return (int)(n < NACHO_WAVE ? NACHO_WAVE : (n < kSpmmPass ? n : kSpmmPass)); }
 
 // SpMV: one carry value per partition; SpMM: one carry row per partition.
@@ -267,6 +268,11 @@ SpmmPlan plan_spmm(void *ws, size_t ws_bytes, int32_t dtype, int64_t nnz, int64_
     plan.dealt = P == 0 && n > 0 && spmm_dealt(nnz, n_cols, row_bytes);
     if (plan.dealt) {
         plan.grain = spmm_grain(nnz, compute_units(), true, row_bytes);
+        // carries of 512 MB at most, or those of an unsorted call (30M non-zeros, 200 doubles: 731 MB and 4986 us, 365 and 5178; a
+        // bound of 256 MB 5453)
+        while (plan.grain < spmm_capacity() &&
+               ceil_div(nnz, plan.grain) * plan.pass * (int64_t)dtype_size(dtype) > kSpmmCarries)
+            plan.grain += NACHO_WAVE;
         plan.Pe = ceil_div(nnz, plan.grain);
         // (of 192 and 256 non-zeros: nothing gained, 10M, rows of 30, 64 floats 388 and 384 us, 16 floats 181 and 205)
         if (plan.grain <= 128 && unsorted > plan.grain) plan.join = (int)(unsorted / plan.grain);

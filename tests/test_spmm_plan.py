@@ -26,3 +26,21 @@ def _partitions(n_cols, nnz, dtype, n):
 def test_b_that_two_l2s_hold_is_not_sorted_for(dtype, n, n_cols, nnz, short, long):
     assert _partitions(n_cols, nnz, dtype, n) == -(-nnz // short)
     assert _partitions(n_cols - 1, nnz, dtype, n) == -(-nnz // long)
+
+
+def _workspace(n_cols, nnz, dtype, n):
+    size = ctypes.c_size_t(0)
+    assert nb.lib().nacho_workspace_bytes(nb.OP_SPMM, _operand(n_cols, n_cols, nnz), 1, dtype, n, 0, ctypes.byref(size)) == 0
+    return size.value
+
+
+@pytest.mark.parametrize("dtype,n,nnz", [(nb.F32, 64, 100_000_000), (nb.F64, 200, 10_000_000), (nb.F64, 200, 30_000_000),
+                                         (nb.F64, 300, 200_000_000), (nb.F32, 300, 2**31 - 1), (nb.F64, 300, 2**31 - 1)])
+def test_workspace_of_sorted_calls_is_bounded(dtype, n, nnz):
+    """Carries of 512 MiB, or of partitions of 512 non-zeros where those take more; 24 bytes of table, 4 of carry rows and
+    8 of the sort a partition, and what is the same for all calls."""
+    row = min(n, 256) * (8 if dtype == nb.F64 else 4)
+    parts = _partitions(1_000_000, nnz, dtype, n)
+    assert -(-nnz // 512) <= parts <= -(-nnz // 64)
+    assert parts * row <= max(512 << 20, -(-nnz // 512) * row)
+    assert _workspace(1_000_000, nnz, dtype, n) <= parts * (row + 36) + (1 << 20)
