@@ -161,14 +161,21 @@ const char *nacho_status_string(int32_t status);
  * to fit the staging buffer of its wavefront (SpMV, SpMM) or workgroup (SpAdd,
  * SpMul), so the result is >= P.  For a DCSR product it is an upper bound (the
  * count depends on the rows the operands share).  `n_dense`: SpMM's dense
- * extent (0 otherwise).  Returns 0 on bad input. */
+ * extent (0 otherwise).  For SpMM with P = 0 it is the count of a call whose
+ * workspace has the size that nacho_workspace_bytes reports for the same
+ * arguments; with a smaller one (sized for another n_dense) the call may use
+ * fewer, longer partitions, and nacho_workspace_parts answers for the buffer.
+ * Returns 0 on bad input. */
 int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int32_t dtype,
                              int64_t n_dense, int64_t P);
 
 /* Bytes of device workspace `op` needs for these operands (host descriptors;
  * only counts/extents are read).  `P` as passed to the call (0 = automatic),
  * `n_dense` = columns of B for SpMM (0 otherwise).  NACHO_OP_SPADD sizes
- * nacho_spadd_k, NACHO_OP_SPMUL nacho_spmul_k. */
+ * nacho_spadd_k, NACHO_OP_SPMUL nacho_spmul_k.  SpMM keeps a row of up to 256
+ * columns of C per partition; large calls with P = 0 are cut into up to eight
+ * times as many partitions as small ones, as long as these rows take no more
+ * than 512 MiB. */
 int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, int32_t dtype,
                               int64_t n_dense, int64_t P, size_t *bytes);
 
@@ -322,6 +329,9 @@ size_t nacho_static_scratch_bytes(void);
  *   ldc (elements); n >= 1.  The executing kernel covers 256 columns at a time
  *   (64 in a workspace sized for no more): a wider B goes through it in
  *   stretches over the same partitions (A is then read once per stretch).
+ *   Any workspace sized for A, the dtype and P serves, whatever n_dense it was
+ *   sized for: a large call with P = 0 that does not fit its short
+ *   partitions into it runs with longer ones, and slower.
  */
 int32_t nacho_spmm(const nacho_tensor *A, const void *B, int64_t n, int64_t ldb,
                    void *C, int64_t ldc, int32_t dtype, int64_t P,
