@@ -24,7 +24,6 @@ struct PlainCoords {
     static constexpr type kNone = INT32_MAX;            // no coordinate
     Ints32 crd;
     __device__ type load(int at) const { return crd[at]; }
-    __device__ static float apart(type a, type b) { return (float)(b - a); }
     __device__ static PlainCoords of(const DevOperands &ops, int t, int m) { return PlainCoords{as_global(ops.lvl[t][m].crd)}; }
     __device__ static int64_t extent(const DevOperands &ops, int m) { return ops.lvl[0][m].extent; }
 };
@@ -34,11 +33,6 @@ struct PairCoords {
     static constexpr type kNone = INT64_MAX;
     Ints32 row, col;
     __device__ type load(int at) const { return ((long long)row[at] << 32) | (long long)(unsigned)col[at]; }
-    // (in halves: the conversion of 64 bits shifts by an amount of the lane's own)
-    __device__ static float apart(type a, type b)
-    {
-        return (float)(int)((b - a) >> 32) * 4294967296.0f + (float)(unsigned)(b - a);
-    }
     __device__ static PairCoords of(const DevOperands &ops, int t, int)
     {
         return PairCoords{as_global(ops.lvl[t][0].crd), as_global(ops.lvl[t][1].crd)};
@@ -291,8 +285,8 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
         below = pos_1[q];
         return kDepth == 2 ? pos_2[below] : below;
     };
-    int below_l = l, below_h = h;              // (kDepth 2) pos_1 of l and h
-    int base = cost_from(l, below_l), cl = base, ch = cost_from(h, below_h);
+    int below_l = l, unused = 0;               // (kDepth 2) pos_1 of l
+    int base = cost_from(l, below_l), cl = base, ch = cost_from(h, unused);
     int row_from = l;
     int W = g.sum(h - l);
     float share = (float)R * __builtin_amdgcn_rcpf((float)total);      // of the windows' cost that lies before the boundary
@@ -363,9 +357,8 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
             ch_new = c2 == n ? ch : e2;
         }
         if (kDepth == 2) {
-            const int d1 = g.from(below_b, i1), d0 = g.from(below_a, i0), d2 = g.from(below_b, i2);
+            const int d1 = g.from(below_b, i1), d0 = g.from(below_a, i0);
             below_l = at_it ? d1 : (c1 > 0 ? d0 : below_l);
-            below_h = c2 == n ? below_h : d2;
         }
         if (small) {
             found.x = vminus;
@@ -398,7 +391,7 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
             int below_at = 0;
             const int cost = cost_from(a, below_at);
             if (g.sum(cost - base) <= R) { l = a; cl = cost; below_l = below_at; }
-            else { h = a; ch = cost; below_h = below_at; }
+            else { h = a; ch = cost; }
             W_new = g.sum(h - l);
         }
         even = slow && !even;
@@ -440,7 +433,7 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
     const int a_at0 = a0 + lane_value(sh, 0), b_at0 = b0 + lane_value(sh, NACHO_WAVE / 2);     // where the segments are stored
     int lo = R > nb ? R - nb : 0, hi = R < na ? R : na;
     float at = (float)R * (float)na * __builtin_amdgcn_rcpf((float)na + (float)nb) - (float)lo;
-    bool even = Acc::kPairs;                           // (rows of unequal length: an expectation is worth nothing)
+    bool even = Acc::kPairs;                           // (rows of unequal length: an expectation is worth nothing, there is none)
     const int share = Acc::kPairs && many ? 3 : 2;     // log2 of the lanes that share a candidate: they read the same words
     while (lo < hi) {
         const int w = hi - lo;                         // candidates lo + 1 .. hi
@@ -455,17 +448,19 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
         const C av = A.load(a_at0 + i - 1);
         const C bv = j < nb ? B.load(b_at0 + j) : Acc::kNone;
         const int n = __popcll(__ballot(av <= bv));    // a prefix of the lanes
-        const float apart = Acc::apart(av, bv);        // >= 0 for the prefix
-        float f = 0.5f;
-        if (n > 0 && n < NACHO_WAVE) {
-            const float below = __int_as_float(lane_value(__float_as_int(apart), n - 1));
-            f = below * __builtin_amdgcn_rcpf(below - __int_as_float(lane_value(__float_as_int(apart), n)));
-        }
         const int lo_new = lane_value(i, n > 0 ? n - 1 : 0), hi_new = lane_value(i, n < NACHO_WAVE ? n : NACHO_WAVE - 1);
         if (n > 0) lo = lo_new;
         if (n < NACHO_WAVE) hi = hi_new - 1;
-        even = Acc::kPairs || (!even && hi - lo > w >> 3);
-        at = f * (float)(hi - lo);
+        if constexpr (!Acc::kPairs) {
+            const float apart = (float)(bv - av);      // >= 0 for the prefix
+            float f = 0.5f;
+            if (n > 0 && n < NACHO_WAVE) {
+                const float below = __int_as_float(lane_value(__float_as_int(apart), n - 1));
+                f = below * __builtin_amdgcn_rcpf(below - __int_as_float(lane_value(__float_as_int(apart), n)));
+            }
+            even = !even && hi - lo > w >> 3;
+            at = f * (float)(hi - lo);
+        }
     }
     const int i = lo, j = R - lo;
     // A[i - 1], A[i], B[j]: lanes 0, 1, 2
