@@ -27,11 +27,12 @@
 //   3. assembly: the heads are the output entries of the union, the heads that
 //      k - 1 equal keys follow those of the product; every wavefront counts all
 //      bits by itself (two 64-bit words per lane and one scan);
-//   4. prefix sum: publishes the partition's counts and reads the counts of
-//      everything before the partition (two levels, see below).  In front of that
-//      every thread asks for the VALUES of its output entries, straight
-//      from the operands: in the merged order a wavefront's 64 places read one
-//      contiguous stretch per operand, and the values need no place in LDS;
+//   4. prefix sum: publishes the partition's counts, then (sums) every thread asks
+//      for the VALUES of its output entries, straight from the operands: in the
+//      merged order a wavefront's 64 places read one contiguous stretch per
+//      operand, and the values need no place in LDS; products multiply theirs
+//      here.  Behind the values come the counts of everything before the
+//      partition (two levels, see below);
 //   5. compute: every output entry writes coordinate and value at offset + heads
 //      before it -- consecutive lanes write consecutive words.  The hierarchical
 //      arrays (crd0/pos1 of a DCSR result, pos of a CSR result, crd1/pos2 and
@@ -1252,7 +1253,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         for (int j = 0; j < R; ++j) {
             const int m = place0 + j * NACHO_WAVE + lane;
             o[j] = order_of(m < n ? m : n - 1);
-            // (past the last place: the order word of an entry of another wavefront may not be there yet)
+            // (past the last place: the first entry of an operand; with the last place's own entry three vectors take 62.1 us
+            // instead of 61.5, two of 300k entries 11.1 instead of 10.3)
             if (m >= n) o[j] = K <= 2 ? of(sb_v, live_t) * KB : (live_t << 13 | of(sb_v, live_t));
         }
 #pragma unroll
