@@ -457,8 +457,9 @@ def bench_others(steps, warmup, only=None, ceilings=None):
     record("C5", f"C5: CSR (1,000,000 x 1,000,000, {nnz} nnz) x dense 1,000,000 x 64, fp32 SpMM",
            lambda: nb.nacho_spmm(op, B, C, ws=ws), nnz, nbytes,
            table=lambda: nb.workspace_parts(nb.OP_SPMM, [op], nb.F32, ws, 64), main_kernel="spmm_exec", waves=P5,
-           note="compulsory bytes (B and C once); the i -> j -> k order re-reads a 256-byte row of B per stored "
-                f"non-zero: {nnz * 256 / 1e9:.2f} GB through the fabric, which is what bounds this kernel")
+           note="compulsory bytes (B and C once); the i -> j -> k order gathers a 256-byte row of B per stored "
+                f"non-zero, {nnz * 256 / 1e9:.2f} GB: those of long rows come out of the L2s (their partitions are sorted "
+                "by column), the rest goes through the fabric and is what bounds this kernel (traffic)")
     return res
 
 

@@ -3,7 +3,7 @@
 // partitions are those of SpMV), one wavefront per partition.
 //
 // What bounds it: large matrices the rows of B (30M non-zeros x 256 bytes, 7.7 GB past the L2s at 7 TB/s, unless partitions
-// that need the same rows run at the same time on the same XCD: deal_count_kernel below; 1095 to 590 us), all others how many of
+// that need the same rows run at the same time on the same XCD: deal_count_kernel below; 1091 to 578 us), all others how many of
 // those rows are on their way at a time.  So a row of B is not spread over the whole
 // wavefront: a lane takes 16 bytes of it, W = 4 to 16 lanes a row, and the 64 / W groups of lanes of a wavefront each
 // walk their own stretch of the partition's non-zeros.  One instruction then asks for up to 16 rows, and the chain of
@@ -280,12 +280,12 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     if (blockIdx.y == 0) wave_end(wlog, p, stamp, (uint32_t)len, (uint32_t)(next_first - r0));
 }
 
-// Carry fix-up: 64 / V lanes per partition, a piece of V columns each, 16 (floats) or 8 partitions per workgroup.  The carries of a row lie in
-// consecutive partitions; the lanes of the first one add the run to the row of C.  A run of more than kShort carries
+// Carry fix-up: 64 / V lanes per partition, a piece of V columns each: 16 partitions (floats), 8 (doubles) or 4 (fewer columns
+// than a 16-byte piece has) per workgroup.  The carries of a row lie in consecutive partitions; the lanes of the first one add the run to the row of C.  A run of more than kShort carries
 // (there is at most one per workgroup: it is longer than the workgroup's partitions) is added by the whole workgroup,
 // every group an equal share of it: the largest row of 30M non-zeros has a thousand, which one wavefront, a row of carries at a
 // time, took 35 us for (half as many).  The order of the additions is fixed.  Bound: the loads in flight, so they are as wide
-// as the lanes' pieces (element by element, 117k partitions of 64 columns: 26.5 us, like this 22.8).
+// as the lanes' pieces (element by element, 156k partitions of 64 floats 66 us, 62k of 200 doubles 77; like this 28 and 52).
 constexpr int kFixCols = 64, kShort = 32;
 
 template <typename T, int V>
@@ -338,7 +338,7 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
             for (int c = 1; c < V; ++c)
                 if (c >= shared) at[c] += x[c];
     };
-    // carries q, q + step, ... below `to`, sixteen of them in flight
+    // carries q, q + step, ... below `to`, eight 16-byte pieces or sixteen narrower ones in flight
     auto sum = [&](int q, int to, int step) -> Vec {
         Vec x = Vec(T(0));
         constexpr int kFlight = sizeof(Vec) == 16 ? 8 : 16;
@@ -534,8 +534,8 @@ bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes)
 }
 
 // Fixed-grain calls do without a partition kernel: the wavefronts of the executing kernel find their rows in two to
-// four rounds of loads, which hide behind each other, and its place in the stream is saved (100k non-zeros, n = 16:
-// 13.4 to 11.2 us; 1.3M, n = 37: 75 to 72; 30M, n = 64: 1136 to 1125).  The zeros of empty rows are spread over the
+// four rounds of loads, which hide behind each other, and its place in the stream is saved (100k non-zeros, 16 floats:
+// 12.8 to 10.4 us; 2M, 16 floats: 37.7 to 33.7; 30M, 4 floats: 353 to 332).  The zeros of empty rows are spread over the
 // wavefronts; where that would be thousands of rows each, the partition kernel writes them.
 bool spmm_whole(int64_t P, int64_t n_rows) { return n_rows <= P * 1024; }
 
