@@ -105,9 +105,11 @@ template <typename KeyT, typename T, bool kSmall> struct Shape {
 // Workgroups per chunk.  Vectors: a large chunk, so that few totals are read (their workgroups run
 // nearly in step and a total is there early).  Matrices and tensors: a smaller one; their partitions
 // take unequal time, the waiting wavefronts poll the words of their chunk, and hundreds of them on
-// the same 2 KB of words are slower (chunks of 64, 128 and 256, us: two DCSR matrices of 20M 164, 159, 163; two tensors
-// of 8M 116, 114, 115; three CSR matrices of 5M 87.7, 87.9, 92.5).
-// Products: smaller still, their partitions differ most (the product of two DCSR matrices of 20M with chunks of 128 4 % slower).
+// the same 2 KB of words are slower (chunks of 64, 128 and 256, us: two DCSR matrices of 20M 164, 159, 163; two CSR matrices of
+// 10M doubles 118, 113, 114; three tensors of 4M doubles 119, 118, 119; three coordinate lists of 4M doubles 114, 110, 117; four
+// and more operands are 1 % faster with 64, five DCSR matrices of 3M doubles 129, 131, 136).
+// Products: smaller still, their partitions differ most (64 and 128, us: two CSR matrices of 10M 71.7, 75.3; three of 5M 78.6,
+// 81.0; two DCSR matrices of 10M 102.0, 103.2; three coordinate lists of 5M 96.4, 97.5).
 constexpr int kChunkVector = 512, kChunkOther = 128, kChunkProduct = 64;
 constexpr int chunk_size(int fmt, bool mul) { return fmt == SPADD_VECTOR ? kChunkVector : (mul ? kChunkProduct : kChunkOther); }
 constexpr int word_loads(int chunk) { return (chunk + NACHO_WAVE - 1) / NACHO_WAVE; }   // words of a chunk a lane reads

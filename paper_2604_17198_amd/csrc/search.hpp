@@ -420,7 +420,8 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
 // us, 16 24, 8 19 -- with thousands of boundaries in flight the lines are what takes the time, a line a candidate, with few of
 // them the rounds are.  Two DCSR matrices of 20M, 7218 boundaries, both levels: 29.2 us with eight evenly spaced ones, 21.0 like
 // this.)  Coordinate lists' candidates stay evenly spaced, a line each however often the range is cut: eight of them with more
-// than a thousand boundaries in flight (`many`; the product of two lists of 20M, 7172 boundaries: 16 a round 174.1 us, 8 166.0).
+// than a thousand boundaries in flight (`many`), else sixteen (16 and 8 a round, us: sums of two lists, 512 boundaries 27.1 and 27.7,
+// 861 36.1 and 36.1; products, 1375 46.6 and 45.6, 2402 68.9 and 65.7, 4122 106 and 100).
 // Requires both segments non-empty and 0 <= R < their total length.
 template <class Acc>
 __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const Acc &A, const Acc &B, int l, int h, int R, int sh,
