@@ -77,3 +77,41 @@ def test_every_boundary(fmt, kind):
             assert np.array_equal(got["cost"], ref["cost"]), (k, P)
             assert np.array_equal(got["coord"].astype(np.int64), ref["coord"][:, :got["coord"].shape[1]]), (k, P)
             assert np.array_equal(got["posn"].astype(np.int64), ref["posn"]), (k, P)
+
+
+@pytest.mark.parametrize("k", [3, 8])
+@pytest.mark.parametrize("fmt", ["vector", "csr", "dcsr", "coo", "csf3"])
+def test_skewed_operands(fmt, k):
+    """Hundreds of thousands of entries an operand, lengths and densities orders of magnitude apart."""
+    rng = np.random.default_rng([k, len(fmt)])
+    keys = []
+    for t in range(k):
+        n = [300_000, 700, 120_000, 500_000, 9, 250_000, 60_000, 400_000][t]
+        x = rng.random(n) ** (1 + 4 * (t % 3) if t % 2 == 0 else 1 / (1 + 3 * t))
+        if t == 3:
+            x = 0.4 + x / 64                            # all of it in one place
+        keys.append(np.unique((x * (EXTENT - 1)).astype(np.int64)))
+    g, o = _operands(fmt, keys)
+    for P in (1000, 1537):
+        print(f"partition skewed {fmt} k={k} P={P}", flush=True)
+        got, ref = parts_to_numpy(nb.nacho_partition(g, P)), oracle.partition(o, P)
+        assert np.array_equal(got["cost"], ref["cost"])
+        assert np.array_equal(got["coord"].astype(np.int64), ref["coord"][:, :got["coord"].shape[1]])
+        assert np.array_equal(got["posn"].astype(np.int64), ref["posn"])
+
+
+@pytest.mark.parametrize("sizes", [(40_000_000, 3_000_000, 100_000), (20_000_000,) + (1_000_000,) * 7])
+def test_windows_past_single_precision(sizes):
+    """Vectors of more than 2^24 entries, where the places of samples are further apart than floats tell."""
+    extent, g, o = 2**31 - 1, [], []
+    for t, n in enumerate(sizes):
+        i = np.arange(n, dtype=np.int64)
+        x = i + (i * i // n * 40 if t == 0 else np.where(i < n // 3, 0, extent // 5 * (1 + t % 4)))
+        v = x.astype(np.int32)
+        g.append(nb.vector(dev(v), extent))
+        o.append(oracle.vector(v, extent))
+    print(f"partition k={len(sizes)} of {sizes[0]}", flush=True)
+    got, ref = parts_to_numpy(nb.nacho_partition(g, 700)), oracle.partition(o, 700)
+    for name in ("cost", "posn"):
+        assert np.array_equal(got[name].astype(np.int64), ref[name])
+    assert np.array_equal(got["coord"][:, 0].astype(np.int64), ref["coord"][:, 0])
