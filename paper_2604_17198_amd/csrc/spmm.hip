@@ -523,14 +523,16 @@ int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes)
 
 // Whether a call sorts its partitions: the partition kernel and the two of the sort are 14 us (35 with 150k partitions), which pays
 // from about 600 MB of gathers on, at least a cache line each (us, unsorted and sorted, rows by Zipf's law, 30 on average: 400k
-// non-zeros, 200 doubles 71 and 66; 1M, 200 floats 105 and 80; 3M, 64 floats 92 and 72; 5M, 32 floats 76 and 69), while two
-// L2s do not hold B anyway (3M, 64 floats, 200 a row, 4.2 MB of B: 47 and 58; rows of 100, 7.7 MB: 65 and 73; 10M, 16 floats, 80
-// a row, 8.8 MB: 117 and 99); with shorter partitions a little more (1M, 200 doubles, 200 a row, 8.8 MB: 106 and 115; 2M,
-// 128 floats, 80 a row, 14 MB: 94 and 72).
+// non-zeros, 200 doubles 71 and 66; 1M, 200 floats 105 and 80; 3M, 64 floats 92 and 72; 5M, 32 floats 76 and 69), while B is
+// larger than an L2 where its rows are shorter than a line (10M non-zeros, 16 floats, 5 MB of B 117 and 100; 4 doubles: 5M,
+// 3.2 MB 63 and 65), than two L2s for others (Zipf's law, 1.2; B of 7, 9, 11 and 14 MB; 8M, 32 floats 87 and 90, 90 and 92, 93 and
+// 92, 100 and 95; 6M, 64 floats 98 and 104, 110 and 106, 124 and 108, 137 and 113; 2M, 200 floats 118 and 120, 138 and 123, 153
+// and 124, 166 and 126; 1M, 200 doubles 98 and 115, 107 and 116, 117 and 119, 133 and 121).  What this costs matrices of short rows
+// with columns at random, which have nothing to sort: 4 to 8 % of such calls.
 bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes)
 {
     return (double)nnz * (double)(row_bytes > 128 ? row_bytes : 128) >= 6e8 &&
-           (double)n_cols * (double)row_bytes >= (row_bytes >= 384 ? 10e6 : 7.8e6);
+           (double)n_cols * (double)row_bytes >= (row_bytes >= 256 ? 9e6 : (row_bytes >= 128 ? 7.8e6 : 4e6));
 }
 
 // Fixed-grain calls do without a partition kernel: the wavefronts of the executing kernel find their rows in two to

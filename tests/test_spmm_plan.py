@@ -18,12 +18,13 @@ def _partitions(n_cols, nnz, dtype, n):
     return int(nb.lib().nacho_num_partitions(nb.OP_SPMM, _operand(n_cols, n_cols, nnz), 1, dtype, n, 0))
 
 
-# (row of B in bytes; the first number of columns that sorts; non-zeros of a sorted and an unsorted partition)
-@pytest.mark.parametrize("dtype,n,n_cols,nnz,short,long", [(nb.F32, 16, 121_875, 10_000_000, 256, 512),
-                                                           (nb.F32, 64, 30_469, 3_000_000, 192, 512),
-                                                           (nb.F32, 96, 26_042, 2_500_000, 128, 512),
-                                                           (nb.F64, 200, 6_250, 1_000_000, 64, 256)])
-def test_b_that_two_l2s_hold_is_not_sorted_for(dtype, n, n_cols, nnz, short, long):
+# (the first number of columns that sorts; non-zeros of a sorted and of an unsorted partition)
+@pytest.mark.parametrize("dtype,n,n_cols,nnz,short,long", [(nb.F32, 16, 62_500, 10_000_000, 256, 512),
+                                                           (nb.F32, 32, 60_938, 5_000_000, 256, 512),
+                                                           (nb.F32, 64, 35_157, 3_000_000, 192, 512),
+                                                           (nb.F32, 96, 23_438, 2_500_000, 128, 512),
+                                                           (nb.F64, 200, 5_625, 1_000_000, 64, 256)])
+def test_b_that_the_l2s_hold_is_not_sorted_for(dtype, n, n_cols, nnz, short, long):
     assert _partitions(n_cols, nnz, dtype, n) == -(-nnz // short)
     assert _partitions(n_cols - 1, nnz, dtype, n) == -(-nnz // long)
 
