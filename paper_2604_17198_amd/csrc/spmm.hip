@@ -387,9 +387,11 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
 //
 // Partitions of 64 or 128 non-zeros write and add four to eight times the carries of 512, which pays where neighbours share rows of B,
 // sorted or as they are.  Where they do not, a wavefront executes `join` partitions of the table in one piece, as long as an unsorted
-// call's: where fewer than 1/8 of the partitions lie inside a row and the first columns of fewer than half of the neighbours are
-// within 4 MB of B (an L2) of each other.  (6M non-zeros, 200 doubles, us, each partition alone and joined: rows of 30 with columns
-// at random 1639 and 1521, in a band of 4000 columns 836 and 1389; rows by Zipf's law, 30 on average, 860 and 1527.)
+// call's: where fewer than 1/8 of the partitions lie inside a row and cover less than a third of the columns (rows of 100, 6M
+// non-zeros, 200 doubles, columns at random: whatever they cover 1515 us, half 1508, a third 1390; rows of 300: 746, 746, 775),
+// and the first columns of fewer than half of the neighbours are within 4 MB of B (an L2) and an eighth of the columns of each
+// other.  (6M non-zeros, 200 doubles, us, each partition alone and joined: rows of 30 with columns at random 1639 and 1521, in a
+// band of 4000 columns 836 and 1389; rows by Zipf's law, 30 on average, 860 and 1527.)
 constexpr int kDealGroups = 32, kDealBins = 512, kDealThreads = 1024, kDealWords = kDealBins + 9;
 
 // Of the lanes with the same residue (mod 8): how many are set in `mask`, and how many of those below this lane.
@@ -406,8 +408,8 @@ __device__ inline int class_rank(unsigned long long mask, int residue)
 
 // place[p]: the bin of a partition inside one row, else -1.  counts: of the bins, of the residues, of neighbours near each other.
 __global__ void __launch_bounds__(kDealThreads)
-deal_count_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, int near_columns, int32_t *__restrict__ place,
-                  int32_t *__restrict__ counts)
+deal_count_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift, int most_span, int near_columns,
+                  int32_t *__restrict__ place, int32_t *__restrict__ counts)
 {
     __shared__ int s_count[kDealWords];
     if (threadIdx.x < kDealWords) s_count[threadIdx.x] = 0;
@@ -421,8 +423,8 @@ deal_count_kernel(const int32_t *__restrict__ coord, int P, int chunk, int shift
         if (p < end) {
             const int2 *boundary = reinterpret_cast<const int2 *>(coord) + p;
             const int2 a = boundary[0], e = boundary[1];       // row and column
-            // (a partition inside one row: its end lies in the row it starts in)
-            if (a.x == e.x) bin = (a.y >> shift) & (kDealBins - 1);
+            // (a partition inside one row: its end lies in the row it starts in; one that covers more columns is nobody's neighbour)
+            if (a.x == e.x && e.y - a.y <= most_span) bin = (a.y >> shift) & (kDealBins - 1);
             near = abs(e.y - a.y) <= near_columns;
             place[p] = bin;
         }
@@ -497,13 +499,14 @@ hipError_t launch_spmm_deal(const int32_t *coord, int64_t P, int64_t n_cols, int
     int shift = 0;
     while ((n_cols - 1) >> shift >= kDealBins) ++shift;
     const int chunk = (int)((P + kDealGroups * NACHO_WAVE - 1) / (kDealGroups * NACHO_WAVE)) * NACHO_WAVE;
+    const int near_columns = (int)(4000000 / row_bytes < n_cols / 8 ? 4000000 / row_bytes : n_cols / 8);
     int32_t *counts = words;
     deal->place = counts + kDealGroups * kDealWords;
     deal->sorted = deal->place + P;
     deal->join = join;
     deal->joined = (int)((P + join - 1) / join);
     hipLaunchKernelGGL(deal_count_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, coord, (int)P, chunk, shift,
-                       (int)(4000000 / row_bytes), deal->place, counts);
+                       (int)(n_cols / 3), near_columns, deal->place, counts);
     hipLaunchKernelGGL(deal_place_kernel, dim3(kDealGroups), dim3(kDealThreads), 0, stream, (int)P, chunk, counts, *deal);
     return hipGetLastError();
 }
