@@ -106,18 +106,19 @@ def _records(fn, n_records):
 
 @pytest.mark.parametrize("dtype,n,nnz,grain,join", [(np.float32, 200, 800_003, 64, 4), (np.float64, 97, 1_000_001, 64, 4),
                                                     (np.float32, 100, 2_200_000, 128, 4), (np.float64, 300, 810_000, 64, 4)])
-@pytest.mark.parametrize("kind", ["random", "band", "long"])
+@pytest.mark.parametrize("kind", ["random", "wide", "band", "long"])
 def test_partitions_joined(kind, dtype, n, nnz, grain, join):
     """Short rows with columns at random: every wavefront executes `join` partitions of the table in one piece (one long row
-    among them, of more joined partitions than one group of the fix-up adds; empty rows).  In a narrow band, or with long
-    rows: one each.  The table is that of the short partitions."""
+    among them, of more joined partitions than one group of the fix-up adds; empty rows), also where rows hold a partition that
+    covers most of the columns.  In a narrow band, or with long rows: one each.  The table is that of the short partitions."""
     rng = np.random.default_rng(n)
     n_cols = 50_000
     head = [0, 7, grain * join * 40 + 5, 0, 0, grain * join, 1] if kind != "long" else [n_cols // 2] * 16 + [0, 3]
     left = nnz - sum(head)
-    lens = np.array(head + [30] * (left // 30) + [left % 30, 0], np.int64)
+    each = grain * 3 // 2 if kind == "wide" else 30
+    lens = np.array(head + [each] * (left // each) + [left % each, 0], np.int64)
     A = _matrix(rng, lens, n_cols, dtype)
-    if kind != "long":                                  # the columns of rows of 30: anywhere, or in a band along the diagonal
+    if kind in ("random", "band"):                      # the columns of rows of 30: anywhere, or in a band along the diagonal
         row = np.repeat(np.arange(len(lens)), lens)
         short = lens[row] <= 30
         place = rng.integers(0, n_cols, len(row)) if kind == "random" else (row * (n_cols - 2000) // len(lens)
@@ -146,5 +147,5 @@ def test_partitions_joined(kind, dtype, n, nnz, grain, join):
     items = _records(lambda: nb.nacho_spmm(op, dev(B), C, ws=ws), P)["items"].astype(np.int64)
     assert tol_ok(C.cpu().numpy(), ref, sabs, TOL[dtype]).all()
     assert items.sum() == nnz
-    each = grain * (join if kind == "random" else 1)
+    each = grain * (join if kind in ("random", "wide") else 1)
     assert np.count_nonzero(items) == -(-nnz // each) and items.max() == each
