@@ -524,7 +524,7 @@ int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes)
     return per >= kGrain ? kGrain : (per < 64 ? 64 : (int)((per + 63) / 64 * 64));
 }
 
-// Whether a call sorts its partitions: the partition kernel and the two of the sort are 14 us (35 with 150k partitions), which pays
+// Whether a call sorts its partitions: the partition kernel and the two of the sort are 14 us (24 with 150k partitions), which pays
 // from about 600 MB of gathers on, at least a cache line each (us, unsorted and sorted, rows by Zipf's law, 30 on average: 400k
 // non-zeros, 200 doubles 71 and 66; 1M, 200 floats 105 and 80; 3M, 64 floats 92 and 72; 5M, 32 floats 76 and 69), while B is
 // larger than an L2 where its rows are shorter than a line (10M non-zeros, 16 floats, 5 MB of B 117 and 100; 4 doubles: 5M,
