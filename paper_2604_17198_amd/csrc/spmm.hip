@@ -531,7 +531,8 @@ int spmm_grain(int64_t nnz, int units, bool dealt, int64_t row_bytes)
 // 3.2 MB 63 and 65), than two L2s for others (Zipf's law, 1.2; B of 7, 9, 11 and 14 MB; 8M, 32 floats 87 and 90, 90 and 92, 93 and
 // 92, 100 and 95; 6M, 64 floats 98 and 104, 110 and 106, 124 and 108, 137 and 113; 2M, 200 floats 118 and 120, 138 and 123, 153
 // and 124, 166 and 126; 1M, 200 doubles 98 and 115, 107 and 116, 117 and 119, 133 and 121).  What this costs matrices of short rows
-// with columns at random, which have nothing to sort: 4 to 8 % of such calls.
+// with columns at random, which have nothing to sort: 1 to 8 % of such calls, 10 to 15 % of the smallest (1.3M, 64 doubles, rows of
+// 20: 92 and 105).
 bool spmm_dealt(int64_t nnz, int64_t n_cols, int64_t row_bytes)
 {
     return (double)nnz * (double)(row_bytes > 128 ? row_bytes : 128) >= 6e8 &&
