@@ -293,13 +293,19 @@ SpmmPlan plan_spmm(void *ws, size_t ws_bytes, int32_t dtype, int64_t nnz, int64_
     return plan;
 }
 
+constexpr int64_t kNoLimit = 1 << 30;
 // The same for the merge kernel of sums and products; `fields` is its key layout for the operands.
 int64_t merge_partitions(int fmt, int32_t dtype, int32_t k, const MergeFields &fields, int64_t total_nnz, int64_t P,
-                         int64_t most = 1 << 30)
+                         int64_t most = kNoLimit)
 {
     const int64_t cap = std::min<int64_t>(spadd_capacity(fmt, dtype, fields), most) - k;
     int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
-    if (P == 0) need = whole_rounds(need, (int64_t)compute_units() * spadd_resident());
+    // One round of workgroups: as many on every compute unit (1.7M entries, 307 and 512 partitions, us: two vectors 18.3, 17.1; CSR matrices
+    // 21.7, 21.6; tensors 34.3, 30.8; 4M doubles, 881 and 1024, 28.6, 27.4; 33.9, 33.4; 48.2, 46.0).  Not coordinate lists, whose
+    // boundaries take long to find (3M 28.5 and 31.2), nor remapped operands, whose number is found on the device.
+    if (P == 0 && most == kNoLimit && fields.size == MERGE_MIDDLE && fmt != SPADD_COO)
+        need = ceil_div(need, compute_units()) * compute_units();
+    else if (P == 0) need = whole_rounds(need, (int64_t)compute_units() * spadd_resident());
     return P > need ? P : need;
 }
 
@@ -315,7 +321,7 @@ RemapWs carve_remap(void *ws, const nacho_tensor *ops, int k, int32_t dtype, int
     }
     w.P0 = rows_total > 0 ? ceil_div(rows_total, kRemapGrain) : 1;
     // the remapped cost never exceeds the stored non-zeros: enough partitions for any outcome
-    w.fields = merge_fields(SPADD_CSR, dtype, w.Mmax, ops[0].lvl[1].extent, 0, total_nnz, compute_units());
+    w.fields = merge_fields(SPADD_CSR, dtype, w.Mmax, ops[0].lvl[1].extent, 0, total_nnz, compute_units(), true);
     w.Pmax = merge_partitions(SPADD_CSR, dtype, k, w.fields, total_nnz, P, kMappedEntries);
     w.parts0 = carve_parts(c, w.P0, k, 1);
     const int64_t rows_words = remap_state_words(w.P0, k);

@@ -100,13 +100,16 @@ __host__ __device__ inline int64_t whole_rounds(int64_t need, int64_t round)
 
 // How the merge kernel packs the coordinates of a matrix or tensor entry into a key: row field << cb | column; for a
 // tensor the row field is (i - i0) << jb | j.  Rows (slices) count from the partition's first one and a key tells
-// `limit` of them apart.  `wide`: 64-bit keys.  `small`: short partitions, for calls that do not fill the chip.
+// `limit` of them apart.  `wide`: 64-bit keys.  `size`: how many places of the merged order a thread owns (MergeSize).
+enum MergeSize : int { MERGE_LONG, MERGE_SHORT, MERGE_MIDDLE };
 struct MergeFields {
-    int32_t cb, jb, wide, small;
+    int32_t cb, jb, wide, size;
     uint32_t limit;
 };
-// `rows`, `cols`, `depth`: the extents of the levels; `total`: stored entries of all operands; `units`: compute units.
-MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units);
+// `rows`, `cols`, `depth`: the extents of the levels; `total`: stored entries of all operands; `units`: compute units;
+// `mapped`: remapped operands.
+MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units,
+                         bool mapped = false);
 // Entries of all operands one partition (workgroup) may hold.
 int spadd_capacity(int fmt, int dtype, const MergeFields &fields);
 // Workgroups of the merge kernel that run on one compute unit at a time.

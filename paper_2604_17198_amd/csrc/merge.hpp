@@ -72,15 +72,17 @@ constexpr int kWaves = NACHO_MERGE_WAVES;           // wavefronts per workgroup
 constexpr int kThreads = kWaves * NACHO_WAVE;
 constexpr int kMaxRuns = NACHO_MAX_OPERANDS;
 
-// Places of the merged order a thread owns.  Odd: thread i's places start at word
+// Places of the merged order a thread owns.  Odd where it can be: thread i's places start at word
 // i * kIpt of the LDS arrays, and an odd stride spreads the lanes of a wavefront
-// over all banks.  Large calls: chosen so that four workgroups fit a compute unit: its
+// over all banks (ten: two lanes a bank).  Large calls: chosen so that four workgroups fit a compute unit: its
 // LDS (6 bytes per entry with 32-bit keys, 10 with 64-bit ones) and, values of 8 bytes,
-// the registers that hold a thread's values while the prefix sum is looked up.  Small
-// calls, which do not fill the chip anyway: a thread's serial share is what such a call
-// takes, so it is short.
-template <typename KeyT, typename T, bool kSmall> struct Shape {
-    static constexpr int kIpt = kSmall ? 3 : (sizeof(KeyT) == 8 ? 7 : (sizeof(T) == 8 ? 9 : 11));
+// the registers that hold a thread's values while the prefix sum is looked up.  Calls of one
+// round of workgroups: a thread's serial share is what such a call takes, so it is short (merge_fields has
+// the lines).  Remapped operands have at most 4096 entries a partition, which nine places a thread hold: with
+// eleven two of eight wavefronts had nothing to do (the product of two DCSR matrices of 20M 166 to 155.5 us).
+// Twelve for 32-bit values: two DCSR matrices of 20M 157 to 154 us, but three vectors 61.7 to 63.4.
+template <typename KeyT, typename T, int kSize> struct Shape {
+    static constexpr int kIpt = kSize == MERGE_SHORT ? 3 : (sizeof(KeyT) == 8 ? 7 : (kSize == MERGE_MIDDLE ? 9 : (sizeof(T) == 8 ? 10 : 11)));
     static constexpr int kTile = kThreads * kIpt;
     // Entries a partition may hold.  A run occupies up to seven words besides its entries (up to three
     // before it: the copy starts on a 16-byte boundary; its sentinel; the next run's alignment) and the
@@ -216,8 +218,8 @@ struct Tile {
     int32_t gave_up;
 };
 
-template <int FMT, typename T, typename KeyT, bool kSmall>
-using TileOf = Tile<KeyT, Shape<KeyT, T, kSmall>, FMT != SPADD_VECTOR, FMT == SPADD_DCSR || FMT == SPADD_CSF3, FMT == SPADD_CSR,
+template <int FMT, typename T, typename KeyT, int kSize>
+using TileOf = Tile<KeyT, Shape<KeyT, T, kSize>, FMT != SPADD_VECTOR, FMT == SPADD_DCSR || FMT == SPADD_CSF3, FMT == SPADD_CSR,
                     FMT == SPADD_CSF3>;
 
 // One thread's share of the stable merge of the sorted runs X = keys[sx, sx + nx)
@@ -382,8 +384,8 @@ typedef const __attribute__((address_space(4))) MergeArgs *ArgPtr;
 // workgroup search its two boundaries themselves (Algorithm 1, equal-share queries) and store them in
 // the partition table on the way -- the search fused into the executing kernel.
 // A partition whose rows do not fit the row field of its keys is merged by searches (`far` below).
-template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch>
-__device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, KeyT, kSmall> &w, const DevOperands &search_ops,
+template <int FMT, typename T, typename KeyT, int kSize, int K, bool kMul, bool kMapped, bool kSearch>
+__device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, KeyT, kSize> &w, const DevOperands &search_ops,
                                                 const WaveStamp &stamp)
 {
     static_assert(!kSearch || (FMT == SPADD_VECTOR && !kMapped), "the fused search is built for sparse vectors");
@@ -397,7 +399,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         P = arg_ptr->ops.dyn_plan[0];
         if ((int64_t)blockIdx.x >= P || arg_ptr->ops.dyn_plan[3]) return;      // (nor after an abandoned row loop)
     }
-    typedef Shape<KeyT, T, kSmall> S;
+    typedef Shape<KeyT, T, kSize> S;
     constexpr int D = FMT == SPADD_VECTOR ? 1 : (FMT == SPADD_CSF3 ? 3 : 2);
     constexpr int kChunk = chunk_size(FMT, kMul), kWordLoads = word_loads(kChunk);
     constexpr bool kCsf = FMT == SPADD_CSF3;   // third-order tensors: three compressed levels
@@ -693,7 +695,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     }
                 }
                 if (len == 0) continue;
-                constexpr int kMore = !kCsf && !kSmall && K <= 4 ? 8 : 4;      // segments a thread has in flight (registers)
+                constexpr int kMore = !kCsf && kSize != MERGE_SHORT && K <= 4 ? 8 : 4;      // segments a thread has in flight (registers)
                 auto mark_segment = [&](int i, int a, int b, int id) {
                     const int s = a > q ? a : q;
                     if (b <= s || s >= q + len) return;            // nothing of it lies in the partition
@@ -1576,38 +1578,38 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     log_end();
 }
 
-template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch = false>
+template <int FMT, typename T, typename KeyT, int kSize, int K, bool kMul, bool kMapped, bool kSearch = false>
 __global__ void __launch_bounds__(kThreads, kSearch ? 2 : 8)
 spadd_kernel(MergeArgs args)
 {
-    __shared__ TileOf<FMT, T, KeyT, kSmall> w;
+    __shared__ TileOf<FMT, T, KeyT, kSize> w;
     const WaveStamp stamp = wave_begin();
     // (not where half of the workgroups find that they have nothing to do)
     if constexpr (!kMapped) touch_arguments<sizeof(MergeArgs) <= 1408 ? sizeof(MergeArgs) : 1408>();
     const ArgPtr arg_ptr = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    merge_partition<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch>(arg_ptr, w, args.ops, stamp);
+    merge_partition<FMT, T, KeyT, kSize, K, kMul, kMapped, kSearch>(arg_ptr, w, args.ops, stamp);
 }
 
 inline int64_t chunks_of(int64_t P, int chunk) { return (P + chunk - 1) / chunk; }
 
-template <int FMT, typename T, typename KeyT, bool kSmall, int K, bool kMul, bool kMapped, bool kSearch>
+template <int FMT, typename T, typename KeyT, int kSize, int K, bool kMul, bool kMapped, bool kSearch>
 hipError_t launch_k(const MergeLaunch &a)
 {
     MergeArgs args{a.ops, a.vals, a.P, chunks_of(a.P, chunk_size(FMT, kMul)), a.coord, a.posn, a.tile_state, a.out, a.fields,
                    nacho_host::wave_log(), a.search};
-    hipLaunchKernelGGL((spadd_kernel<FMT, T, KeyT, kSmall, K, kMul, kMapped, kSearch>), dim3((unsigned)a.P), dim3(kThreads), 0,
+    hipLaunchKernelGGL((spadd_kernel<FMT, T, KeyT, kSize, K, kMul, kMapped, kSearch>), dim3((unsigned)a.P), dim3(kThreads), 0,
                        a.s, args);
     return hipGetLastError();
 }
 
 // instantiated for up to 2, 3, 4 and 8 operands: the per-entry loops over the runs are unrolled
-template <int FMT, typename T, typename KeyT, bool kSmall, bool kMul, bool kMapped, bool kSearch>
+template <int FMT, typename T, typename KeyT, int kSize, bool kMul, bool kMapped, bool kSearch>
 hipError_t launch_one(const MergeLaunch &a)
 {
-    if (a.ops.k <= 2) return launch_k<FMT, T, KeyT, kSmall, 2, kMul, kMapped, kSearch>(a);
-    if (a.ops.k <= 3) return launch_k<FMT, T, KeyT, kSmall, 3, kMul, kMapped, kSearch>(a);
-    if (a.ops.k <= 4) return launch_k<FMT, T, KeyT, kSmall, 4, kMul, kMapped, kSearch>(a);
-    return launch_k<FMT, T, KeyT, kSmall, 8, kMul, kMapped, kSearch>(a);
+    if (a.ops.k <= 2) return launch_k<FMT, T, KeyT, kSize, 2, kMul, kMapped, kSearch>(a);
+    if (a.ops.k <= 3) return launch_k<FMT, T, KeyT, kSize, 3, kMul, kMapped, kSearch>(a);
+    if (a.ops.k <= 4) return launch_k<FMT, T, KeyT, kSize, 4, kMul, kMapped, kSearch>(a);
+    return launch_k<FMT, T, KeyT, kSize, 8, kMul, kMapped, kSearch>(a);
 }
 
 template <int FMT, bool kMul, bool kMapped = false, bool kSearch = false>
@@ -1615,16 +1617,24 @@ hipError_t launch_types(int dtype, const MergeLaunch &a)
 {
     if constexpr (FMT != SPADD_VECTOR)
         if (a.fields.wide) {
-            if (dtype == NACHO_F64) return launch_one<FMT, double, uint64_t, false, kMul, kMapped, kSearch>(a);
-            return launch_one<FMT, float, uint64_t, false, kMul, kMapped, kSearch>(a);
+            if (dtype == NACHO_F64) return launch_one<FMT, double, uint64_t, MERGE_LONG, kMul, kMapped, kSearch>(a);
+            return launch_one<FMT, float, uint64_t, MERGE_LONG, kMul, kMapped, kSearch>(a);
         }
     if constexpr (!kSearch)
-        if (a.fields.small) {
-            if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, true, kMul, kMapped, kSearch>(a);
-            return launch_one<FMT, float, uint32_t, true, kMul, kMapped, kSearch>(a);
+        if (a.fields.size == MERGE_SHORT) {
+            if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_SHORT, kMul, kMapped, kSearch>(a);
+            return launch_one<FMT, float, uint32_t, MERGE_SHORT, kMul, kMapped, kSearch>(a);
         }
-    if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, false, kMul, kMapped, kSearch>(a);
-    return launch_one<FMT, float, uint32_t, false, kMul, kMapped, kSearch>(a);
+    if constexpr (!kSearch)
+        if (kMapped || a.fields.size == MERGE_MIDDLE) {
+            if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_MIDDLE, kMul, kMapped, kSearch>(a);
+            return launch_one<FMT, float, uint32_t, MERGE_MIDDLE, kMul, kMapped, kSearch>(a);
+        }
+    if constexpr (!kMapped) {
+        if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_LONG, kMul, kMapped, kSearch>(a);
+        return launch_one<FMT, float, uint32_t, MERGE_LONG, kMul, kMapped, kSearch>(a);
+    }
+    return hipErrorInvalidValue;               // (not reached)
 }
 
 }  // namespace

@@ -15,11 +15,12 @@ int bits_of(int64_t extent)                    // bits of the largest coordinate
     return b;
 }
 
-int capacity_of(bool wide, bool small, int dtype)
+int capacity_of(bool wide, int size, int dtype)
 {
-    if (wide) return dtype == NACHO_F64 ? Shape<uint64_t, double, false>::kCapacity : Shape<uint64_t, float, false>::kCapacity;
-    if (small) return dtype == NACHO_F64 ? Shape<uint32_t, double, true>::kCapacity : Shape<uint32_t, float, true>::kCapacity;
-    return dtype == NACHO_F64 ? Shape<uint32_t, double, false>::kCapacity : Shape<uint32_t, float, false>::kCapacity;
+    if (wide) return dtype == NACHO_F64 ? Shape<uint64_t, double, MERGE_LONG>::kCapacity : Shape<uint64_t, float, MERGE_LONG>::kCapacity;
+    if (size == MERGE_SHORT) return dtype == NACHO_F64 ? Shape<uint32_t, double, MERGE_SHORT>::kCapacity : Shape<uint32_t, float, MERGE_SHORT>::kCapacity;
+    if (size == MERGE_MIDDLE) return dtype == NACHO_F64 ? Shape<uint32_t, double, MERGE_MIDDLE>::kCapacity : Shape<uint32_t, float, MERGE_MIDDLE>::kCapacity;
+    return dtype == NACHO_F64 ? Shape<uint32_t, double, MERGE_LONG>::kCapacity : Shape<uint32_t, float, MERGE_LONG>::kCapacity;
 }
 
 }  // namespace
@@ -31,14 +32,34 @@ int spadd_wavefronts() { return kWaves; }
 // The key layout of a call: 32-bit keys when the rows (slices) that an average full partition spans take a
 // quarter of the row field or less, or the field holds any row, else 64-bit keys.  A partition that spans more rows
 // than the field holds is merged by searches (rank_far), for which a key's word has to hold any (slice, fibre) pair.
-MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units)
+MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units, bool mapped)
 {
     MergeFields f;
     f.cb = f.jb = f.wide = 0;
     f.limit = 0;
-    // Short partitions as long as all of them run at once: beyond that a second round of them takes longer
-    // than one round of long ones.
-    f.small = total <= (int64_t)units * spadd_resident() * (capacity_of(false, true, dtype) - NACHO_MAX_OPERANDS) ? 1 : 0;
+    // Short partitions while two of them a compute unit hold a call (vectors; CSR, 16 entries a row and more) or five sixths of a round (the others; CSR
+    // with short rows a whole one), middle ones while one round of workgroups does, else long ones.  A partition takes some 8 us whatever it holds, so few long ones beat many short ones; but a thread's serial share
+    // is what a round takes, so no longer than need be.  Sums of two vectors, CSR matrices, tensors of 32-bit values, us:
+    // 700k entries in all, short 14.2, 16.9, 24.2, middle 13.5, 16.7, 24.9; 1.1M 16.1, 20.3, 27.6 and 14.4, 18.1, 27.9; 1.45M 17.8, 22.7, 30.8
+    // and 15.7, 20.6, 29.0; 3M, long 21.4, 25.8, 39.3, middle 19.9, 24.9, 35.1; products of 700k 1.04 to 1.08 of the time as middle ones, of 900k 0.96
+    // to 1.04; DCSR matrices with three entries a row, two and four operands, 1M 26.7, 40.5 and 27.2, 44.1, 1.4M 33.0, 47.5 and 31.8, 46.2; CSR with four
+    // 1M 22.8, 32.4 and 24.2, 35.4, 1.4M 26.1, 36.7 and 26.3, 37.2.  Past a round of middle ones (4.64M entries) partitions of doubles hold 5040 entries instead of 4536: 5.1M in one round of 1013
+    // and not two, 10 to 14 % less, 10M 0 to 5 %; within the round nine places are 1 to 5 % faster than ten.
+    auto fits = [&](int size, double per_unit) {       // (workgroups on a compute unit)
+        return (double)total <= (double)units * per_unit * (double)(capacity_of(false, size, dtype) - NACHO_MAX_OPERANDS);
+    };
+    const int resident = spadd_resident();
+    double short_ones = 5.0 * resident / 6.0;
+    if (fmt == SPADD_VECTOR || (fmt == SPADD_CSR && total >= 16 * rows)) short_ones = resident / 2;
+    else if (fmt == SPADD_CSR) short_ones = resident;
+    // (remapped operands: the total counts entries that are not coiterated)
+    if (fits(MERGE_SHORT, mapped ? resident : short_ones)) f.size = MERGE_SHORT;
+    else if (mapped) f.size = MERGE_MIDDLE;
+    else if (!fits(MERGE_MIDDLE, resident)) f.size = MERGE_LONG;
+    // two long partitions a compute unit instead of three middle ones (2.6M entries, two and eight operands, us: CSR 23.2 and 23.6, 48.9 and 50.7; DCSR
+    // 27.8 and 28.1, 54.9 and 58.0; but vectors 19.3 and 19.1, 46.4 and 46.7, tensors 35.2 and 33.9, 61.5 and 60.9)
+    else if ((fmt == SPADD_CSR || fmt == SPADD_DCSR) && dtype == NACHO_F32 && !fits(MERGE_MIDDLE, 2) && fits(MERGE_LONG, 2)) f.size = MERGE_LONG;
+    else f.size = MERGE_MIDDLE;
     if (fmt == SPADD_VECTOR) return f;
     const int64_t per = total > 0 ? total : 1;
     if (fmt == SPADD_CSF3) {
@@ -52,12 +73,12 @@ MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t
         const int room = 32 - f.cb < 16 ? 32 - f.cb : 16;
         f.limit = (1u << room) - 1u;           // (room >= 1)
     }
-    int64_t span = (int64_t)((double)rows * capacity_of(false, f.small != 0, dtype) / (double)per) + 2;
+    int64_t span = (int64_t)((double)rows * capacity_of(false, f.size, dtype) / (double)per) + 2;
     if (span > rows) span = rows;
     if (f.limit == 0 || (fmt == SPADD_CSF3 && rows > (int64_t)1 << (32 - f.jb)) ||
         (rows > (int64_t)f.limit && span > (int64_t)(f.limit / 4))) {
         f.wide = 1;
-        f.small = 0;
+        f.size = MERGE_LONG;
         f.limit = 0x80000000u;                 // matrices: any row
         if (fmt != SPADD_CSF3) f.cb = 32;
         else {
@@ -71,7 +92,7 @@ MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t
     return f;
 }
 
-int spadd_capacity(int fmt, int dtype, const MergeFields &f) { (void)fmt; return capacity_of(f.wide != 0, f.small != 0, dtype); }
+int spadd_capacity(int fmt, int dtype, const MergeFields &f) { (void)fmt; return capacity_of(f.wide != 0, f.size, dtype); }
 
 // 64-bit words of look-up state: one per chunk, then one 32-bit word per workgroup -- twice (third-order
 // tensors count slices in the second set); sized for the smallest chunk, which covers all

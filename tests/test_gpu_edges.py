@@ -200,6 +200,27 @@ def test_merge_short_and_long_partitions(k, over):
         add.check_vec(vs, [rng.uniform(-1, 1, n).astype(dtype) for n in sizes], 1 << 22, 0, f"limit+{over}")
 
 
+@pytest.mark.parametrize("per_unit,places", [(2, 3), (4, 9)])
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_merge_between_lengths_of_partitions(per_unit, places, over, dtype):
+    """The lines between short, middle and long partitions, from both sides: the sum and the product are those of the same
+    call in other partitions (vectors: the shared tests hold the oracle's), bit for bit."""
+    total = UNITS * per_unit * (min(places * 504, places * 512 - 64) - 8) + over
+    gen = torch.Generator(device="cuda").manual_seed(total)
+    as_torch = torch.float64 if dtype == np.float64 else torch.float32
+    ops = []
+    for n in (total - total // 3, total // 3):
+        keys = torch.cumsum(torch.randint(1, 3, (n,), device="cuda", generator=gen), 0).to(torch.int32)
+        ops.append(nb.vector(keys, (1 << 30) + 7, torch.rand(n, device="cuda", generator=gen, dtype=as_torch)))
+    print(f"lengths of partitions {total} {dtype.__name__}", flush=True)
+    for call in (nb.nacho_spadd_k, nb.nacho_spmul_k):
+        a, b = (call(ops, nb.SparseOut("vector", 0, total, as_torch, "cuda"), P=P) for P in (0, 2500))
+        n = int(a.counts[1])
+        assert torch.equal(a.counts, b.counts) and int(a.status[0]) == 0 and int(b.status[0]) == 0 and n > 0
+        assert torch.equal(a.crd1[:n], b.crd1[:n]) and torch.equal(a.val[:n], b.val[:n])
+
+
 def _banded(rng, n_rows, n_cols, dense, sparse):
     """Many entries in a band of a few rows and a few in rows far apart: partitions of the latter span more rows than the
     row field of their keys holds."""
