@@ -496,6 +496,29 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         if (D >= 2) row0 = table_coord(p, 0);
     }
+    // Tensors: the coordinates of the first and the last of these slices, the last one's first fibre, the fibres of the boundary's slice.
+    // (asked for here, the round trips lie beside the entries' own; behind the staging one wavefront took all of them,
+    // four in a row per operand, while the others waited: two tensors of 4M entries 68.5 to 65.6 us, three of 2.7M 80 to 78.  Not in short
+    // partitions, which wait for the scalar round trip (300k entries 1 to 5 % longer), nor for more operands than there are registers)
+    constexpr bool kSlicesAhead = kCsf && (kSize == MERGE_LONG ? K <= 4 : (kSize == MERGE_MIDDLE && K <= 3));
+    int first_v = 0, last_v = 0, second_v = 0, fibre_v = 0, fibre_end_v = 0, begin_v = 0;
+    constexpr int kSliceWords = kSlicesAhead ? K : 1;
+    int first_s[kSliceWords], last_s[kSliceWords], second_s[kSliceWords], fibre_s[kSliceWords], fibre_end_s[kSliceWords];
+    if constexpr (kSlicesAhead) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            // (an operand without slices: any words that are there)
+            const bool some = t < k && level_count(t, 0) > 0;
+            const int lo = some ? of(up_lo_v, t) : 0, hi = some ? of(up_hi_v, t) : 0, last = some ? level_count(t, 0) - 1 : 0;
+            const Table crd0 = some ? (Table)(uintptr_t)arg_ptr->ops.lvl[t][0].crd : (Table)(uintptr_t)arg_ptr->coord;
+            const Table pos1 = some ? (Table)(uintptr_t)arg_ptr->ops.lvl[t][1].pos : (Table)(uintptr_t)arg_ptr->coord;
+            first_s[t] = crd0[lo < hi ? lo : hi];
+            last_s[t] = crd0[hi];
+            second_s[t] = pos1[hi];
+            fibre_s[t] = pos1[lo < last ? lo : last];
+            fibre_end_s[t] = pos1[(lo < last ? lo : last) + 1];
+        }
+    }
     // Only an operand that violates its preconditions (unsorted or repeated
     // coordinates) can overflow the staging buffer: such a partition contributes
     // nothing and the call reports INVALID_ARG, but the prefix sum goes on.
@@ -535,8 +558,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
     }
     // (rows of the first 512 segments of every run -- as a rule all of them -- are asked for together with
-    // the entries: one round trip to memory; fibres of a tensor, which are many: of the first 1024)
-    constexpr int kAhead = kCsf && K <= 2 ? 2 : 1;
+    // the entries: one round trip to memory; fibres of a tensor, which are many: of the first 1024 or 1536)
+    constexpr int kAhead = !kCsf ? 1 : (kSize == MERGE_SHORT ? (K <= 2 ? 2 : 1) : (K <= 2 ? 3 : (K <= 4 ? 2 : 1)));
     int seg_a[kWindow ? K : 1][kAhead], seg_b[kWindow ? K : 1][kAhead], seg_id[kWindow ? K : 1][kAhead];
     // segment i of run t: the positions of its entries and its row (CSF: j of the fibre; remapped operands: where
     // its entries are stored)
@@ -556,6 +579,23 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 const int i = of(ilo_v, t) + u * kThreads + tid;
                 if (i < of(ihi_v, t)) load_segment(t, i, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
             }
+    }
+    if constexpr (kSlicesAhead) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            first_v = put(first_v, t, first_s[t]);
+            last_v = put(last_v, t, last_s[t]);
+            second_v = put(second_v, t, second_s[t]);
+            fibre_v = put(fibre_v, t, fibre_s[t]);
+            fibre_end_v = put(fibre_end_v, t, fibre_end_s[t]);
+        }
+        // (one wavefront: where the entries of the boundary's slice start)
+        if (wave == 0) {
+            Ints pos2 = seg_pos[0];
+#pragma unroll
+            for (int t = 1; t < K; ++t) pos2 = lane == t ? seg_pos[t] : pos2;
+            if (ilo_v < ihi_v) begin_v = pos2[fibre_v];
+        }
     }
     // The run of a staged word and the word's place in it; a word that holds no entry stands for the first entry
     // of the partition (valid = false).
@@ -663,11 +703,12 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     if (i_lo < i_hi) {
                         up_lo = of(up_lo_v, t);
                         const int up_hi = of(up_hi_v, t);
-                        const Table crd0 = (Table)(uintptr_t)arg_ptr->ops.lvl[t][0].crd;       // (constant to this kernel)
                         many = up_hi > up_lo + 1;
-                        up_first = crd0[up_lo < up_hi ? up_lo : up_hi];
-                        up_last = crd0[up_hi];
-                        if (up_hi == up_lo + 1) second_at = ((Table)(uintptr_t)arg_ptr->ops.lvl[t][1].pos)[up_hi];
+                        const Table crd0 = (Table)(uintptr_t)arg_ptr->ops.lvl[t][0].crd;       // (constant to this kernel)
+                        up_first = kSlicesAhead ? of(first_v, t) : crd0[up_lo < up_hi ? up_lo : up_hi];
+                        up_last = kSlicesAhead ? of(last_v, t) : crd0[up_hi];
+                        if (up_hi == up_lo + 1)
+                            second_at = kSlicesAhead ? of(second_v, t) : ((Table)(uintptr_t)arg_ptr->ops.lvl[t][1].pos)[up_hi];
                     }
                 }
                 if (t < k) {
@@ -679,10 +720,11 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                         const int i0 = of(up_lo_v, t);
                         if (i_lo < i_hi && i0 < level_count(t, 0) && up_first == row0) {       // (uniform)
                             const Table pos1 = (Table)(uintptr_t)arg_ptr->ops.lvl[t][1].pos;
-                            const int f0 = pos1[i0], f1 = pos1[i0 + 1];
+                            const int f1 = kSlicesAhead ? of(fibre_end_v, t) : pos1[i0 + 1];
+                            const int f0 = kSlicesAhead ? 0 : pos1[i0], begin = kSlicesAhead ? of(begin_v, t) : 0;
                             if (tid == 0) {
                                 if (i < f1 && id0 == table_coord(p, 1) && q > a0) w.cont = 1u;
-                                if (q > seg_pos[t][f0]) w.cont_slice = 1u;
+                                if (q > (kSlicesAhead ? begin : seg_pos[t][f0])) w.cont_slice = 1u;
                             }
                         }
                     } else if (tid == 0 && i < i_hi && (FMT == SPADD_CSR || id0 == row0) && q > a0) w.cont = 1u;

@@ -96,6 +96,27 @@ def test_long_fibres_and_long_slices_span_partitions():
         _check(tens, shape, P, "long")
 
 
+@pytest.mark.parametrize("k", [2, 3, 4])
+@pytest.mark.parametrize("total,dtype", [(1_400_000, np.float32), (1_400_000, np.float64), (5_200_000, np.float32)])
+def test_middle_and_long_partitions(k, total, dtype):
+    """Calls beyond short partitions: slices that span partitions, partitions that span many slices and that end with one, an
+    operand without entries, with entries in the first and the last slice only."""
+    rng = np.random.default_rng(total + k)
+    shape = (3000, 40, 4000)
+    tens = []
+    for t in range(k):
+        n = total // max(1, k - 1) if k > 2 else total // 2
+        if k > 2 and t == k - 1:                             # (the last operand: none, or the two ends)
+            c = np.array([(0, 0, 0), (0, 39, 3999), (2999, 0, 5), (2999, 39, 3999)] if k == 3 else [], np.int64).reshape(-1, 3)
+        else:
+            dense = _coords(rng, (2, 40, 4000), n // 6)      # two long slices, then short ones
+            c = np.concatenate([dense + np.array([700 + t, 0, 0]), _coords(rng, shape, n - n // 6)])
+            c = np.unique(c[:, 0] * 160_000 + c[:, 1] * 4000 + c[:, 2])
+            c = np.stack(np.unravel_index(c, shape), axis=1).astype(np.int64)
+        tens.append(_tensor(c, rng.uniform(-1, 1, c.shape[0]).astype(dtype)))
+    _check(tens, shape, 0, "middle and long")
+
+
 def test_many_partitions_cross_a_chunk_of_the_prefix_look_up():
     """More partitions than one chunk of the two-level prefix holds."""
     rng = np.random.default_rng(23)
