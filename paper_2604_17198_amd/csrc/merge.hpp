@@ -90,7 +90,7 @@ template <typename KeyT, typename T, int kSize> struct Shape {
     static constexpr int kCapacity = kTile - 8 * kMaxRuns > kIpt * (kThreads - kMaxRuns)
                                          ? kIpt * (kThreads - kMaxRuns) : kTile - 8 * kMaxRuns;
     static constexpr int kBlocks = kTile / NACHO_WAVE;     // blocks of 64 places
-    static constexpr int kWords = kTile + 32;              // (a thread past the last place reads on)
+    static constexpr int kWords = kTile + 48;              // (a thread past the last place reads on)
     static_assert(kBlocks <= 2 * NACHO_WAVE, "a lane holds the bits of two blocks");
     static_assert(kTile <= (1 << 13), "the word of an entry fits 13 bits of its order word");
 };
@@ -528,6 +528,11 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     bool far = false;                          // (matrices and tensors) the rows do not fit the keys
     uint32_t logged_items = 0, logged_rows = 0;    // (instrumented build) places / row heads this wavefront walked
 
+    // (sums of matrices and tensors: a workgroup goes before the others of its compute unit until its counts are published -- everybody
+    // behind it waits for the slowest one, nobody for its output: two DCSR matrices of 20M 159.6 to 153.9 us; three vectors, whose
+    // partitions are alike, 57.7 to 60.0, the product of two DCSR matrices 150.5 to 154)
+    constexpr bool kFirst = FMT != SPADD_VECTOR && !kMul;
+    if constexpr (kFirst) __builtin_amdgcn_s_setprio(2);
     // ---- 1. staging -----------------------------------------------------------
     // staged word of the operand's first entry (the copy of a run starts on a 16-byte boundary), words in all
     const int lead_v = kDirect ? (q_v & 3) : 0;
@@ -913,10 +918,10 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     constexpr int KB = (int)sizeof(KeyT);
     const int place0 = wave * (R * NACHO_WAVE);    // a wavefront's places: place0 + j * 64 + lane, j < R
     const int block0 = wave * R;
-    const int two_at = K <= 2 ? of(sb_v, K - 1) * KB : 0;      // two operands: the second one's words start here
-    auto word_of = [&](int o, int &t) -> int {     // the staged word an order word names, and its operand
-        t = K <= 2 ? (K == 2 && o >= two_at ? 1 : 0) : o >> 13;
-        return K <= 2 ? o / KB : o & 0x1fff;
+    const unsigned two_at = K <= 2 ? (unsigned)(of(sb_v, K - 1) * KB) : 0u;    // two operands: the second one's words start here
+    auto word_of = [&](unsigned o, int &t) -> int {    // the staged word an order word names, and its operand
+        t = K <= 2 ? (K == 2 && o >= two_at ? 1 : 0) : (int)(o >> 13);
+        return K <= 2 ? (int)(o / KB) : (int)(o & 0x1fffu);
     };
     auto rank_far = [&]() {
         if constexpr (D >= 2) {
@@ -1198,15 +1203,30 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 
     // ---- the values: where an entry's is ---------------------------------------------------------
     T val[R], tail = T(0);
-    // address of the value of the entry an order word names
-    auto value_at = [&](int o) -> T {
-        int t;
-        const int at = word_of(o, t);
-        return global_ptr<T>(w.sval[t])[at];
+    // the value of the entry an order word names (byte offsets throughout: with two operands and values as long as the
+    // keys the order word is the offset)
+    auto value_at = [&](unsigned o) -> T {
+        const unsigned t8 = K <= 2 ? (K == 2 && o >= two_at ? 8u : 0u) : (o >> 13) * 8u;
+        const unsigned long long base = *reinterpret_cast<const unsigned long long *>(reinterpret_cast<const char *>(w.sval) + t8);
+        const unsigned long long off = K <= 2 ? (unsigned long long)o * sizeof(T) / KB : (unsigned long long)(o & 0x1fffu) * sizeof(T);
+        return *global_ptr<T>(base + off);
     };
-    auto order_of = [&](int m) -> int {
-        if constexpr (K <= 2) return moved ? (int)w.order[m] : (mb + m) * KB;
-        else return moved ? (int)w.order[mb + m] : (only << 13 | (mb + m));
+    auto order_of = [&](int m) -> unsigned {
+        if constexpr (K <= 2) return moved ? (unsigned)w.order[m] : (unsigned)((mb + m) * KB);
+        else return moved ? (unsigned)w.order[mb + m] : (unsigned)(only << 13 | (mb + m));
+    };
+    // the order words of the wavefront's places (past the last place: any words)
+    auto orders = [&](unsigned (&o)[R]) {
+        const int m = place0 + lane;
+        if (moved) {
+            const uint16_t *order = w.order + (K <= 2 ? 0 : mb) + m;
+#pragma unroll
+            for (int j = 0; j < R; ++j) o[j] = order[j * NACHO_WAVE];
+        } else {
+            const unsigned first = K <= 2 ? (unsigned)((mb + m) * KB) : (unsigned)(only << 13 | (mb + m));
+#pragma unroll
+            for (int j = 0; j < R; ++j) o[j] = first + (unsigned)(j * NACHO_WAVE * (K <= 2 ? KB : 1));
+        }
     };
 
     // ---- 3. assembly: which places are emitted, and how many before every block -----------
@@ -1290,27 +1310,35 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
     }
 
+    if constexpr (kFirst) __builtin_amdgcn_s_setprio(0);
     // sums: every place asks for its value, straight from the operands (64 places read one contiguous stretch per operand).
     // Not before the counts are published: asking takes one to ten microseconds where the memory pipeline is full, and everybody
     // behind this workgroup waits for them (three vectors, 11M entries: 71.0 to 68.6 us; two DCSR matrices of 20M: 175 to 168).
+    KeyT key[R];
     if (!kMul && n > 0) {
-        int o[R];
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int m = place0 + j * NACHO_WAVE + lane;
-            o[j] = order_of(m < n ? m : n - 1);
-            // (past the last place: the first entry of an operand; with the last place's own entry three vectors take 62.1 us
+        unsigned o[R];
+        orders(o);
+        if (place0 + R * NACHO_WAVE > n) {         // (uniform: the wavefronts at the end)
+            // past the last place: the first entry of an operand (with the last place's own entry three vectors take 62.1 us
             // instead of 61.5, two of 300k entries 11.1 instead of 10.3)
-            if (m >= n) o[j] = K <= 2 ? of(sb_v, live_t) * KB : (live_t << 13 | of(sb_v, live_t));
+            const unsigned some = K <= 2 ? (unsigned)(of(sb_v, live_t) * KB) : (unsigned)(live_t << 13 | of(sb_v, live_t));
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (place0 + j * NACHO_WAVE + lane >= n) o[j] = some;
         }
 #pragma unroll
         for (int j = 0; j < R; ++j) val[j] = value_at(o[j]);
+        // two operands: the order word is the key's byte offset
+        if constexpr (K <= 2) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) key[j] = *reinterpret_cast<const KeyT *>(kb + o[j]);
+        }
     }
 
-    // The counts of the workgroups before this one are asked for behind the values: loads come back in order, so they are
-    // looked at when the values are there however early they were asked for, and a word that was not published yet costs
-    // another round trip (asked for in front of the values, three vectors 68.6 us, like this 61.6; two DCSR matrices 168 and
-    // 162, two tensors 120 and 115; the product of two DCSR matrices of 20M, whose values are asked for further down, 174.8 and 165.9).
+    // The counts of the workgroups before this one are asked for when the values are there: what decides is whether the words are
+    // published by then, because one that is not costs a sleep and another round trip, and all workgroups poll the same few lines
+    // (asked for together with the values, three vectors 63.8 us, three CSR matrices 89.5, two DCSR matrices of 20M 174; like this
+    // 57.7, 83.3 and 159.6.  All of them looked up in parallel, seven wavefronts on the words of a chunk each, was slower still: 191).
     unsigned long long early_total = 0ull;
     auto ask_for_counts = [&]() {
         if (wave == 0) {
@@ -1325,7 +1353,6 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         } else if (wave == 1 && lane < chunk)
             early_total = __hip_atomic_load(&totals[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    if constexpr (!kMul) ask_for_counts();
 
     // CSR: the rows whose pos this partition writes, and the places before such a row
     int first_row = 0, end_row = 0, pos_at = 0;
@@ -1346,8 +1373,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
 
     // ---- the keys of the output entries, and what else the sums and products need ----------------
-    // (products: the keys after the values, whose requests need the registers)
-    KeyT key[R];
+    // (products: the keys after the values, whose requests need the registers.  Past the last place: any words)
     auto load_keys = [&]() {
         if (K > 2 && __builtin_expect(far, 0)) {
 #pragma unroll
@@ -1355,28 +1381,33 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 const int m = place0 + j * NACHO_WAVE + lane;
                 key[j] = keys[w.order[m < n ? m : n - 1] & 0x1fff];
             }
-            return;
-        }
+        } else if (K <= 2 && moved) {
+            unsigned o[R];
+            orders(o);
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int m = place0 + j * NACHO_WAVE + lane, mm = m < n ? m : n - 1;
-            int at = (mb + mm) * KB;
-            if (K <= 2 && moved) at = w.order[mm];
-            key[j] = *reinterpret_cast<const KeyT *>(kb + at);
+            for (int j = 0; j < R; ++j) {
+                const int m = place0 + j * NACHO_WAVE + lane;
+                key[j] = *reinterpret_cast<const KeyT *>(kb + (m < n ? o[j] : 0u));
+            }
+        } else {
+            const KeyT *first = keys + mb + place0 + lane;
+#pragma unroll
+            for (int j = 0; j < R; ++j) key[j] = first[j * NACHO_WAVE];
         }
     };
     if (n > 0) {
-        if constexpr (!kMul) load_keys();
+        if constexpr (!kMul && K > 2) load_keys();
         if constexpr (kMul) {
             // products: few places are emitted; those ask for the values of all operands
             auto load_value = [&](int m) -> T {
                 if constexpr (kMapped) {
-                    const int o = order_of(m);
-                    const int t = K <= 2 ? (o >= two_at ? 1 : 0) : o >> 13;
-                    const KeyT key = keys[K <= 2 ? o / KB : (far ? o & 0x1fff : mb + m)];
+                    const unsigned o = order_of(m);
+                    int t;
+                    const int s = word_of(o, t);
+                    const KeyT key = keys[K <= 2 || far ? s : mb + m];
                     const int row = row0 + (int)(uint32_t)row_field(key);
                     const int sh = global_ptr<int32_t>(w.srow[t])[row] - global_ptr<int32_t>(w.spos[t])[row];
-                    return global_ptr<T>(w.sval[t])[(K <= 2 ? o / KB : o & 0x1fff) + sh];
+                    return global_ptr<T>(w.sval[t])[s + sh];
                 } else return value_at(order_of(m));
             };
             if (__ballot(e != 0ull && lane < R) != 0ull) {
@@ -1429,7 +1460,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
     }
 
-    if constexpr (kMul) ask_for_counts();
+    ask_for_counts();
 
     // ---- 4. prefix sum, second half: wavefront 0 reads the counts of the workgroups before this one in its
     // chunk, wavefront 1 those of the chunks before
@@ -1563,9 +1594,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         if (kMul && ej == 0ull) continue;      // (uniform)
         const unsigned loc = (unsigned)(at + lanes_below(ej));
-        bool emit = my_bit(ej);
-        if (tight) emit = emit && (int)loc < room;
-        if (emit) {
+        unsigned long long stored = ej;
+        if (__builtin_expect(tight, 0)) stored &= __ballot((int)loc < room);
+        if (my_bit(stored)) {
             store(crd_out, loc, (int32_t)(D == 1 ? (uint32_t)key[j] : (uint32_t)(key[j] & col_mask)));
             if (kCoo) store(row_out, loc, row0 + (int32_t)(uint32_t)row_field(key[j]));
             store(val_out, loc, val[j]);
@@ -1605,7 +1636,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 for (int i = 0; i < 4; ++i) {
                     const int m = place0 + (j0 + i) * NACHO_WAVE + lane;
                     int t;
-                    const int s = word_of((int)w.order[m < n ? m : n - 1], t);
+                    const int s = word_of(w.order[m < n ? m : n - 1], t);
                     col[i] = column_at(t, s, row_field(keys[s]));
                 }
 #pragma unroll
