@@ -237,25 +237,25 @@ __device__ __forceinline__ void merge_share(const char *kb, int sx, int nx, int 
     // one-level operands: the highest c in [lo, hi] such that X[c - 1] comes before Y[d0 - c]
     // (true for every c up to the answer, false beyond it), by binary lifting.
     const int lo = d0 - ny > 0 ? d0 - ny : 0, hi = d0 < nx ? d0 : nx;
-    int pos = lo * KB;
-    const int hib = hi * KB;
-    const int bx = (sx - 1) * KB;              // X[c - 1] lives at bx + c * KB
-    const int by = (sy + d0) * KB;             // Y[d0 - c] at by - c * KB
+    const int bx = (sx - 1) * KB;              // X[c - 1] lives at bx + c * KB: `at` for the c in hand
+    const int by = (sy + d0) * KB + bx;        // Y[d0 - c] at by - at
+    int at = bx + lo * KB;
+    const int most = bx + hi * KB;
     // (four ways a step: half the dependent round trips to LDS)
     for (int step = KB << ((steps - 1) & ~1); step >= KB; step >>= 2) {
         KeyT xv[3], yv[3];
         int cand[3];
 #pragma unroll
         for (int g = 0; g < 3; ++g) {
-            cand[g] = pos + (g + 1) * step;
-            cand[g] = cand[g] < hib ? cand[g] : hib;
-            xv[g] = *reinterpret_cast<const KeyT *>(kb + bx + cand[g]);
-            yv[g] = *reinterpret_cast<const KeyT *>(kb + by - cand[g]);
+            cand[g] = at + (g + 1) * step;
+            cand[g] = cand[g] < most ? cand[g] : most;
+            xv[g] = *reinterpret_cast<const KeyT *>(kb + cand[g]);
+            yv[g] = *reinterpret_cast<const KeyT *>(kb + (by - cand[g]));
         }
 #pragma unroll
-        for (int g = 0; g < 3; ++g) pos = xv[g] <= yv[g] ? cand[g] : pos;
+        for (int g = 0; g < 3; ++g) at = xv[g] <= yv[g] ? cand[g] : at;
     }
-    int xi = sx * KB + pos, yi = by - pos;
+    int xi = at + KB, yi = by - at;
     // the keys in hand and the ones after them: a key is asked for two steps before it is compared
     KeyT xk = *reinterpret_cast<const KeyT *>(kb + xi), yk = *reinterpret_cast<const KeyT *>(kb + yi);
     KeyT xn = *reinterpret_cast<const KeyT *>(kb + xi + KB), yn = *reinterpret_cast<const KeyT *>(kb + yi + KB);
@@ -500,7 +500,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // (asked for here, the round trips lie beside the entries' own; behind the staging one wavefront took all of them,
     // four in a row per operand, while the others waited: two tensors of 4M entries 68.5 to 65.6 us, three of 2.7M 80 to 78.  Not in short
     // partitions, which wait for the scalar round trip (300k entries 1 to 5 % longer), nor for more operands than there are registers)
-    constexpr bool kSlicesAhead = kCsf && (kSize == MERGE_LONG ? K <= 4 : (kSize == MERGE_MIDDLE && K <= 3));
+    constexpr bool kSlicesAhead = kCsf && (kSize == MERGE_LONG ? K <= (kWide ? 3 : 4) : (kSize == MERGE_MIDDLE && K <= 3));
     int first_v = 0, last_v = 0, second_v = 0, fibre_v = 0, fibre_end_v = 0, begin_v = 0;
     constexpr int kSliceWords = kSlicesAhead ? K : 1;
     int first_s[kSliceWords], last_s[kSliceWords], second_s[kSliceWords], fibre_s[kSliceWords], fibre_end_s[kSliceWords];
@@ -682,11 +682,13 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         const unsigned long long x = lane_word(st, j);
         int e = latest;
         if (x) {                           // (uniform) some row starts in the block
+            // how far it lies from the block's last word: the nearest of the start in the upper half, the lower half (32 more; none
+            // stays the largest number) and the one before the block
             const uint32_t lo = (uint32_t)x & upto_lo, hi = (uint32_t)(x >> 32) & upto_hi;
-            const int at = word0 + j * NACHO_WAVE;
-            e = lo ? at + 31 - __builtin_clz(lo) : e;
-            e = hi ? at + 63 - __builtin_clz(hi) : e;
-            latest = at + 63 - __clzll((long long)x);
+            const int end = word0 + j * NACHO_WAVE + NACHO_WAVE - 1;
+            const uint32_t from_hi = hi ? (uint32_t)__builtin_clz(hi) : ~0u, from_lo = (lo ? (uint32_t)__builtin_clz(lo) : ~0u) | 32u;
+            e = end - (int)min(min(from_hi, from_lo), (uint32_t)(end - latest));
+            latest = end - __clzll((long long)x);
         }
         return e;
     };
@@ -823,12 +825,17 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             // the others': a small call waits for its instructions; the product of four CSR matrices of 10k entries 23.9 us with
             // it here, 23.1 there)
         } else if constexpr (!kWide && kWindow && kDirect) {
+            // (all row fields are asked for, then put over the columns: block after block, each waits for a round trip to LDS.
+            // What is written past the last word nobody reads)
+            if (word0 < words) {                                   // (uniform)
+                uint32_t f[R], c[R];
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int s = word0 + j * NACHO_WAVE + lane;
-                if (word0 + j * NACHO_WAVE >= words) break;        // (uniform)
-                const KeyT f = field_at(start_of(j));
-                cols[s] = (uint32_t)((f << cb) | cols[s]);
+                for (int j = 0; j < R; ++j) {
+                    f[j] = (uint32_t)field_at(start_of(j));
+                    c[j] = cols[word0 + j * NACHO_WAVE + lane];
+                }
+#pragma unroll
+                for (int j = 0; j < R; ++j) cols[word0 + j * NACHO_WAVE + lane] = (f[j] << cb) | c[j];
             }
         } else {
             KeyT key[R];
