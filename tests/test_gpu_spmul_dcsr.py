@@ -164,6 +164,26 @@ def test_medium_many_tiles(k):
         check(mats, shape, P, "medium")
 
 
+@pytest.mark.parametrize("k", [2, 3, 5])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [63, 320, 576, 4097, 9300])
+def test_every_entry_or_few_in_all_operands(k, dtype, n):
+    """The values of a product are asked for in batches of places: all places of equal operands (every group of k places
+    is emitted), and few of them, at the sizes where a batch, a wavefront's places and a partition end.  (k factors, one
+    rounding each, are far inside the tolerances.)"""
+    rng = np.random.default_rng(100 * k + n)
+    shape = (97, 5000)
+    whole = random_coords(rng, shape, n)
+    for few in (False, True):
+        mats = []
+        for t in range(k):
+            c = whole
+            if few and t:
+                c = np.unique(np.concatenate([whole[::7], random_coords(rng, shape, n)]), axis=0)
+            mats.append(_mat(c, rng.uniform(0.5, 1.5, len(c)).astype(dtype)))
+        check(mats, shape, 0, f"batches n={n} few={few}")
+
+
 def test_capacity_overflow_is_reported():
     rng = np.random.default_rng(8)
     shape = (300, 200)
