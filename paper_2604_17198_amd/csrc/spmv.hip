@@ -306,8 +306,13 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
     if (writer) y[r] = y_old + (v + (end == NACHO_WAVE - 1 ? tail : T(0)));
 }
 
+// Non-zeros of a partition and row positions staged at a time.  A wavefront's loads, sums and stores are one chain of latencies,
+// so twice as many wavefronts, half as long, are faster wherever there are few (fp32, 1024 non-zeros and 512, us: 27k
+// 9.5, 8.2; 0.65M 16.1, 13.0; 8.8M 46.0, 44.0; 35M 141, 138.6); around 5M, once around the chip either
+// way, 31.0 and 30.5, 6M 34.0 and 34.8, 8M 42.4 and 42.2.  Of 512 and 256 row
+// positions with 1024 non-zeros neither changed a thing; 768 non-zeros lay between.
 constexpr int kGrainF64 = 512, kRowsF64 = 512;
-constexpr int kGrainF32 = 1024, kRowsF32 = 1024;
+constexpr int kGrainF32 = 512, kRowsF32 = 512;
 
 }  // namespace
 
@@ -318,10 +323,13 @@ int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32
 // non-zeros: 9.3 us in all; 1M: 16.8 to 15.4; 5M: 33.2 to 32.4).  Past a thousand partitions only while x fits an L2:
 // partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 309 to 469 us without).  With more
 // rows than the wavefronts can look after in one batch of loads each the partition kernel writes the zeros, a row a
-// thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).
-bool spmv_whole(int64_t P, int64_t n_rows, int64_t x_bytes)
+// thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).  The lines are in partitions of fp64 and in pairs of
+// them of fp32, whose search takes a larger share of a wavefront: with and without the partition kernel 31.6 and 31.0 us for 5M
+// non-zeros, 34.8 and 34.8 for 6M, 42.2 and 43.5 for 8M, with 3.6 MB of x 37.9 and 39.0 for 6M, 45.0 and 47.9 for 8M.
+bool spmv_whole(int dtype, int64_t P, int64_t n_rows, int64_t x_bytes)
 {
-    return n_rows <= (1 << 17) && n_rows <= P * kZeroRows && (P <= 1024 || (P <= 8192 && x_bytes <= (4 << 20)));
+    const int64_t parts = dtype == NACHO_F64 ? P : (P + 1) / 2;
+    return n_rows <= (1 << 17) && n_rows <= parts * kZeroRows && (parts <= 1024 || (parts <= (dtype == NACHO_F64 ? 8192 : 5120) && x_bytes <= (4 << 20)));
 }
 
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
