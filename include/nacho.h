@@ -311,7 +311,7 @@ int32_t nacho_spadd_fused(const nacho_tensor *ops, int32_t k, int32_t dtype, int
  * the library's code object (one copy per GPU, nacho_static_scratch_bytes() bytes,
  * held until the process ends) instead of a caller's workspace.  The call
  * allocates and frees nothing and only enqueues.  A matrix whose partitions do
- * not fit that array (about 36 bytes per partition, i.e. per 512 fp64 / 1024 fp32
+ * not fit that array (about 36 bytes per partition, i.e. per 512
  * non-zeros, or per requested partition when P is given) is refused with
  * NACHO_ERR_TOO_LARGE before anything is launched.  All calls on one GPU share
  * the array: two calls that overlap in time on one GPU (different streams or
