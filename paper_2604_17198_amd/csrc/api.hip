@@ -382,7 +382,7 @@ int32_t spmv_enqueue(const nacho_tensor *A, const DevOperands &dev, int64_t nnz,
 // until the process ends.  In host code the array's name is only a handle for
 // hipGetSymbolAddress; the address on the current device is looked up once per device and
 // that pointer is what the kernels get.
-constexpr size_t kStaticScratchBytes = 8u << 20;
+constexpr size_t kStaticScratchBytes = 16u << 20;     // (fp32 matrices of 268M non-zeros, as when their partitions held 1024)
 constexpr int kMaxDevices = 64;
 }  // namespace
 
