@@ -947,7 +947,10 @@ int32_t nacho_spadd_fused(const nacho_tensor *ops, int32_t k, int32_t dtype, int
     }
     if (!out->counts || !out->status || !out->pos1 || out->cap_nnz < 0) return NACHO_ERR_INVALID_ARG;
     if (out->cap_nnz > 0 && (!out->crd1 || !out->val)) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
+    MergeFields fields = fields_of(fmt, dtype, ops, total);
+    const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields, total, P);
+    // (the kernel for long partitions holds any; three of its workgroups run on a compute unit whatever the operands)
+    if (Pe <= 3 * (int64_t)compute_units()) fields.size = MERGE_LONG;
     SpaddWs w = carve_spadd(ws, Pe, k, dev.d);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     SpaddOut o;
@@ -962,7 +965,7 @@ int32_t nacho_spadd_fused(const nacho_tensor *ops, int32_t k, int32_t dtype, int
     profile_mark("clear_state");
     SpaddSearch search;
     search.coord = w.parts.coord; search.posn = w.parts.posn; search.cost = w.parts.cost; search.total = total;
-    if (launch_spadd_vector_search(dtype, dev, vals, Pe, search, w.tile_state, o, s) != hipSuccess) return NACHO_ERR_HIP;
+    if (launch_spadd_vector_search(dtype, dev, vals, Pe, search, w.tile_state, o, fields, s) != hipSuccess) return NACHO_ERR_HIP;
     profile_mark("spadd_merge_fused");
     return NACHO_OK;
 }

@@ -129,7 +129,7 @@ struct SpaddSearch {
 // The prefix-sum state and the status word must be zero when the kernel starts.
 hipError_t launch_spadd_vector_search(int dtype, const DevOperands &ops, const SpaddValues &vals, int64_t P,
                                       const SpaddSearch &search, unsigned long long *tile_state, const SpaddOut &out,
-                                      hipStream_t s);
+                                      const MergeFields &fields, hipStream_t s);
 // Count, prefix sum and fill in one kernel, one workgroup per partition.  `multiply`: the k-way
 // intersection with products instead of the union with sums (vectors, CSR and coordinate lists; DCSR operands come
 // here remapped, as CSR; no tensors).

@@ -1689,8 +1689,16 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     log_end();
 }
 
+// Four workgroups run on a compute unit if a wavefront takes no more than 64 vector and 80 scalar registers.  The search of a workgroup's
+// own boundaries asks for more of both (67 to 73, 82 to 106): three run, and calls of 769 to 1024 partitions take a second round (four vectors
+// of 4.2M fp32 entries in all: 47.5 us, held to the registers of four 37.4).  Held to them, long partitions of doubles spill from four operands
+// on, and five and more operands move scalars through vector registers (0.3M to 3.3M entries 4 to 7 % slower): these have a
+// kernel for middle partitions beside the one for three workgroups, for calls that three a compute unit do not hold (five vectors of 4.2M 62.4
+// to 48.5 us).
+template <typename T, int K> constexpr bool kSearchOfFour = K <= (sizeof(T) == 8 ? 3 : 4);
+
 template <int FMT, typename T, typename KeyT, int kSize, int K, bool kMul, bool kMapped, bool kSearch = false>
-__global__ void __launch_bounds__(kThreads, kSearch ? 2 : 8)
+__global__ void __launch_bounds__(kThreads, (kSearch && kSize == MERGE_LONG && !kSearchOfFour<T, K> ? 2 : 8))
 spadd_kernel(MergeArgs args)
 {
     __shared__ TileOf<FMT, T, KeyT, kSize> w;
@@ -1708,7 +1716,8 @@ hipError_t launch_k(const MergeLaunch &a)
 {
     MergeArgs args{a.ops, a.vals, a.P, chunks_of(a.P, chunk_size(FMT, kMul)), a.coord, a.posn, a.tile_state, a.out, a.fields,
                    nacho_host::wave_log(), a.search};
-    hipLaunchKernelGGL((spadd_kernel<FMT, T, KeyT, kSize, K, kMul, kMapped, kSearch>), dim3((unsigned)a.P), dim3(kThreads), 0,
+    constexpr int kRun = kSearch && kSearchOfFour<T, K> ? (int)MERGE_LONG : kSize;
+    hipLaunchKernelGGL((spadd_kernel<FMT, T, KeyT, kRun, K, kMul, kMapped, kSearch>), dim3((unsigned)a.P), dim3(kThreads), 0,
                        a.s, args);
     return hipGetLastError();
 }
@@ -1736,11 +1745,10 @@ hipError_t launch_types(int dtype, const MergeLaunch &a)
             if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_SHORT, kMul, kMapped, kSearch>(a);
             return launch_one<FMT, float, uint32_t, MERGE_SHORT, kMul, kMapped, kSearch>(a);
         }
-    if constexpr (!kSearch)
-        if (kMapped || a.fields.size == MERGE_MIDDLE) {
-            if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_MIDDLE, kMul, kMapped, kSearch>(a);
-            return launch_one<FMT, float, uint32_t, MERGE_MIDDLE, kMul, kMapped, kSearch>(a);
-        }
+    if (kMapped || a.fields.size == MERGE_MIDDLE) {
+        if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_MIDDLE, kMul, kMapped, kSearch>(a);
+        return launch_one<FMT, float, uint32_t, MERGE_MIDDLE, kMul, kMapped, kSearch>(a);
+    }
     if constexpr (!kMapped) {
         if (dtype == NACHO_F64) return launch_one<FMT, double, uint32_t, MERGE_LONG, kMul, kMapped, kSearch>(a);
         return launch_one<FMT, float, uint32_t, MERGE_LONG, kMul, kMapped, kSearch>(a);

@@ -100,9 +100,9 @@ int64_t spadd_state_words(int64_t P) { return 2 * (chunks_of(P, kChunkProduct) +
 
 hipError_t launch_spadd_vector_search(int dtype, const DevOperands &ops, const SpaddValues &vals, int64_t P,
                                       const SpaddSearch &search, unsigned long long *tile_state, const SpaddOut &out,
-                                      hipStream_t s)
+                                      const MergeFields &fields, hipStream_t s)
 {
-    const MergeLaunch a{ops, vals, P, search.coord, search.posn, tile_state, out, MergeFields{}, search, s};
+    const MergeLaunch a{ops, vals, P, search.coord, search.posn, tile_state, out, fields, search, s};
     return merge_vector_search(dtype, a);
 }
 

@@ -67,6 +67,27 @@ def test_vectors_random(k, dtype):
             _check(vs, vals, extent, P, f"random{trial}")
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("k", [3, 4, 5, 8])
+def test_three_and_four_workgroups_on_a_compute_unit(k, dtype):
+    """Up to three partitions a compute unit the kernel of long partitions runs, with more of them one held to the
+    registers of four (from four or five operands on a kernel of its own, for middle partitions): both sides of
+    the line, and middle partitions as full as they get."""
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(750 + k)
+
+    def vectors(total):
+        vs = [np.unique(rng.integers(0, 2**30, total // k)).astype(np.int32) for _ in range(k)]
+        vs[-1] = np.unique(np.concatenate([vs[-1][::2], vs[0][:len(vs[-1]) // 2]]))       # (some coordinates in two)
+        return vs, [rng.uniform(-1, 1, len(v)).astype(dtype) for v in vs]
+
+    vs, vals = vectors(units * 12_000)
+    for P in (3 * units, 3 * units + 1):
+        _check(vs, vals, 2**30, P, "line")
+    vs, vals = vectors(units * 4 * 4528)
+    _check(vs, vals, 2**30, 0, "full")
+
+
 def test_all_operands_empty():
     e = np.zeros(0, np.int32)
     _check([e, e], [e.astype(np.float32), e.astype(np.float32)], 100, 0, "empty")
