@@ -528,10 +528,12 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     bool far = false;                          // (matrices and tensors) the rows do not fit the keys
     uint32_t logged_items = 0, logged_rows = 0;    // (instrumented build) places / row heads this wavefront walked
 
-    // (sums of matrices and tensors: a workgroup goes before the others of its compute unit until its counts are published -- everybody
-    // behind it waits for the slowest one, nobody for its output: two DCSR matrices of 20M 159.6 to 153.9 us; three vectors, whose
-    // partitions are alike, 57.7 to 60.0, the product of two DCSR matrices 150.5 to 154)
-    constexpr bool kFirst = FMT != SPADD_VECTOR && !kMul;
+    // (sums of matrices and of two tensors: a workgroup goes before the others of its compute unit until its counts are published --
+    // everybody behind it waits for the slowest one, nobody for its output: two DCSR matrices of 20M 159.6 to 153.9 us, two tensors of
+    // 6.5M entries in all 77.5 to 76.7; three vectors, whose partitions are alike, 57.7 to 60.0, the product of two DCSR matrices 150.5 to 154.
+    // More tensors keep a workgroup before its counts for so long that the others' output waits: three of 12M entries in all 113.2 us without,
+    // 117.0 with it, four 116.8 and 124.7, eight 168.4 and 176.6; of 3.5M, one round, 50.9 and 49.7, 57.6 and 56.9, 73.0 and 72.2)
+    constexpr bool kFirst = FMT != SPADD_VECTOR && !kMul && (!kCsf || K <= 2);
     if constexpr (kFirst) __builtin_amdgcn_s_setprio(2);
     // ---- 1. staging -----------------------------------------------------------
     // staged word of the operand's first entry (the copy of a run starts on a 16-byte boundary), words in all
