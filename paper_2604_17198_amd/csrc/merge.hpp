@@ -497,10 +497,11 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         if (D >= 2) row0 = table_coord(p, 0);
     }
     // Tensors: the coordinates of the first and the last of these slices, the last one's first fibre, the fibres of the boundary's slice.
-    // (asked for here, the round trips lie beside the entries' own; behind the staging one wavefront took all of them,
-    // four in a row per operand, while the others waited: two tensors of 4M entries 68.5 to 65.6 us, three of 2.7M 80 to 78.  Not in short
-    // partitions, which wait for the scalar round trip (300k entries 1 to 5 % longer), nor for more operands than there are registers)
-    constexpr bool kSlicesAhead = kCsf && (kSize == MERGE_LONG ? K <= (kWide ? 3 : 4) : (kSize == MERGE_MIDDLE && K <= 3));
+    // Asked for here, the round trips lie beside the entries' own; behind the staging one wavefront takes all of them, four in a row
+    // per operand, while the others wait.  Only two operands in long partitions with 32-bit keys: elsewhere the entries wait for the scalar round
+    // trip longer than that (two tensors of 16M entries in all 110.6 to 108.6 us, of 16M doubles 127.3 to 125.0, of 6.5M to 8M equal; but three of 5.2M 66.7
+    // and 69.4, two of 2M, one round of middle partitions, 34.9 and 35.6, two of 50k, 64-bit keys, 24.9 and 25.9).
+    constexpr bool kSlicesAhead = kCsf && kSize == MERGE_LONG && !kWide && K <= 2;
     int first_v = 0, last_v = 0, second_v = 0, fibre_v = 0, fibre_end_v = 0, begin_v = 0;
     constexpr int kSliceWords = kSlicesAhead ? K : 1;
     int first_s[kSliceWords], last_s[kSliceWords], second_s[kSliceWords], fibre_s[kSliceWords], fibre_end_s[kSliceWords];
