@@ -303,9 +303,10 @@ int64_t merge_partitions(int fmt, int32_t dtype, int32_t k, const MergeFields &f
     // One round of workgroups: as many on every compute unit (1.7M entries, 307 and 512 partitions, us: two vectors 18.3, 17.1; CSR matrices
     // 21.7, 21.6; tensors 34.3, 30.8; 4M doubles, 881 and 1024, 28.6, 27.4; 33.9, 33.4; 48.2, 46.0).  Not coordinate lists, whose
     // boundaries take long to find (3M 28.5 and 31.2), nor remapped operands, whose number is found on the device.
-    if (P == 0 && most == kNoLimit && fields.size == MERGE_MIDDLE && fmt != SPADD_COO)
+    const int64_t round = (int64_t)compute_units() * spadd_resident();
+    if (P == 0 && most == kNoLimit && fields.size == MERGE_MIDDLE && need <= round && fmt != SPADD_COO)
         need = ceil_div(need, compute_units()) * compute_units();
-    else if (P == 0) need = whole_rounds(need, (int64_t)compute_units() * spadd_resident());
+    else if (P == 0) need = whole_rounds(need, round);
     return P > need ? P : need;
 }
 

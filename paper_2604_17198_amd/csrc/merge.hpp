@@ -1719,7 +1719,7 @@ hipError_t launch_k(const MergeLaunch &a)
 {
     MergeArgs args{a.ops, a.vals, a.P, chunks_of(a.P, chunk_size(FMT, kMul)), a.coord, a.posn, a.tile_state, a.out, a.fields,
                    nacho_host::wave_log(), a.search};
-    constexpr int kRun = kSearch && kSearchOfFour<T, K> ? (int)MERGE_LONG : kSize;
+    constexpr int kRun = kSearch && sizeof(T) == 4 && kSearchOfFour<T, K> ? (int)MERGE_LONG : kSize;    // (floats: that one does as well)
     hipLaunchKernelGGL((spadd_kernel<FMT, T, KeyT, kRun, K, kMul, kMapped, kSearch>), dim3((unsigned)a.P), dim3(kThreads), 0,
                        a.s, args);
     return hipGetLastError();

@@ -55,7 +55,13 @@ MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t
     // (remapped operands: the total counts entries that are not coiterated)
     if (fits(MERGE_SHORT, mapped ? resident : short_ones)) f.size = MERGE_SHORT;
     else if (mapped) f.size = MERGE_MIDDLE;
-    else if (!fits(MERGE_MIDDLE, resident)) f.size = MERGE_LONG;
+    // (doubles of vectors and tensors have ten places a thread only where one round of them holds a call that one of nine does not: 4.7M entries,
+    // vectors of two, three, eight operands 24.2, 36.5, 59.3 us and 27.1, 40.0, 62.4 with nine, tensors 62.9, 73.3, 99.7 and 68.7, 81.6, 116.9; past that
+    // round, 5.3M, 28.7, 42.4, 68.4 and 27.8, 44.4, 64.2, tensors 75.5, 90.0, 127.6 and 73.2, 87.5, 120.8, of 8M 47.0, 58.3, 87.1 and 46.5, 58.4,
+    // 84.4, tensors 85.9, 103.1, 145.7 and 82.9, 98.5, 136.2.  Matrices keep ten: 5.3M CSR 33.4, 46.6, 71.6 and 36.4, 47.7, 72.4, DCSR 39.6, 46.9, 73.7
+    // and 40.6, 51.0, 76.5, lists 47.5, 57.6, 92.4 and 49.9, 63.1, 95.9; of 8M equal within 2 %)
+    else if (!fits(MERGE_MIDDLE, resident))
+        f.size = dtype == NACHO_F64 && (fmt == SPADD_VECTOR || fmt == SPADD_CSF3) && !fits(MERGE_LONG, resident) ? MERGE_MIDDLE : MERGE_LONG;
     // two long partitions a compute unit instead of three middle ones (2.6M entries, two and eight operands, us: CSR 23.2 and 23.6, 48.9 and 50.7; DCSR
     // 27.8 and 28.1, 54.9 and 58.0; but vectors 19.3 and 19.1, 46.4 and 46.7, tensors 35.2 and 33.9, 61.5 and 60.9)
     else if ((fmt == SPADD_CSR || fmt == SPADD_DCSR) && dtype == NACHO_F32 && !fits(MERGE_MIDDLE, 2) && fits(MERGE_LONG, 2)) f.size = MERGE_LONG;

@@ -1,0 +1,65 @@
+"""How sums and products of sparse operands are cut into partitions, from the host descriptors alone (no GPU): the
+entries a partition holds at most tell which kernel a call takes."""
+import ctypes
+
+import pytest
+
+from paper_2604_17198_amd import binding as nb
+
+UNITS = 256                                    # compute units (what the library takes where there is no GPU)
+ROUND = 4 * UNITS                              # workgroups that run at a time
+SHORT, MIDDLE, LONG, WIDE = 1472, 4536, {nb.F32: 5544, nb.F64: 5040}, 3520
+
+DENSE, COMPRESSED, NONUNIQUE, SINGLETON = nb.DENSE, nb.COMPRESSED, nb.NONUNIQUE, nb.SINGLETON
+KINDS = {"vector": (COMPRESSED,), "csr": (DENSE, COMPRESSED), "dcsr": (COMPRESSED, COMPRESSED),
+         "coo": (NONUNIQUE, SINGLETON), "csf3": (COMPRESSED, COMPRESSED, COMPRESSED)}
+# extents that leave the row field of 32-bit keys room
+EXTENTS = {"vector": (1 << 30,), "csr": (4000, 4000), "dcsr": (4000, 4000), "coo": (4000, 4000), "csf3": (60, 60, 60)}
+
+
+def _operands(fmt, counts, extents):
+    ops = (nb._Tensor * len(counts))()
+    for op, n in zip(ops, counts):
+        op.nlevels = len(KINDS[fmt])
+        for m, (kind, extent) in enumerate(zip(KINDS[fmt], extents)):
+            last = m == op.nlevels - 1
+            op.lvl[m].kind, op.lvl[m].extent = kind, extent
+            op.lvl[m].count = 0 if kind == DENSE else (n if last or fmt == "coo" else min(n, extent))
+    return ops
+
+
+def _split(total, k):
+    return [total // k + (t < total % k) for t in range(k)]
+
+
+def partitions(fmt, total, k, dtype, op=nb.OP_SPADD, extents=None, P=0):
+    ops = _operands(fmt, _split(total, k), extents or EXTENTS[fmt])
+    return int(nb.lib().nacho_num_partitions(op, ops, k, dtype, 0, P))
+
+
+def needed(total, entries, k):
+    return -(-total // (entries - k))
+
+
+def whole_rounds(need):
+    up = -(-need // ROUND) * ROUND
+    return up if (up - need) * 12 <= need else need
+
+
+def whole_units(need):
+    return -(-need // UNITS) * UNITS
+
+
+# (the last total that one round of long partitions holds, and the next)
+ONE_ROUND_F64 = ROUND * (LONG[nb.F64] - nb.MAX_OPERANDS)
+
+
+@pytest.mark.parametrize("k", [2, 3, 8])
+@pytest.mark.parametrize("fmt,past", [("vector", MIDDLE), ("csf3", MIDDLE), ("csr", 5040), ("dcsr", 5040), ("coo", 5040)])
+def test_doubles_past_a_round(fmt, past, k):
+    """Ten places a thread as long as one round of such partitions holds the call; past it nine for vectors and tensors."""
+    assert partitions(fmt, ONE_ROUND_F64, k, nb.F64) == whole_rounds(needed(ONE_ROUND_F64, 5040, k))
+    for total in (ONE_ROUND_F64 + 1, 8_000_000, 12_345_679):
+        assert partitions(fmt, total, k, nb.F64) == whole_rounds(needed(total, past, k)), total
+    # floats have eleven
+    assert partitions(fmt, ONE_ROUND_F64 + 1, k, nb.F32) == whole_rounds(needed(ONE_ROUND_F64 + 1, 5544, k))
