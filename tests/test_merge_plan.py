@@ -63,3 +63,23 @@ def test_doubles_past_a_round(fmt, past, k):
         assert partitions(fmt, total, k, nb.F64) == whole_rounds(needed(total, past, k)), total
     # floats have eleven
     assert partitions(fmt, ONE_ROUND_F64 + 1, k, nb.F32) == whole_rounds(needed(ONE_ROUND_F64 + 1, 5544, k))
+
+
+# (the last total that one round of short partitions holds, and that five sixths of one do)
+ONE_ROUND_SHORT = ROUND * (SHORT - nb.MAX_OPERANDS)
+FIVE_SIXTHS = ROUND * 5 * (SHORT - nb.MAX_OPERANDS) // 6
+
+
+@pytest.mark.parametrize("dtype", [nb.F32, nb.F64])
+@pytest.mark.parametrize("k", [2, 3, 8])
+@pytest.mark.parametrize("extents", [(2000, 2000, 2000), (100_000, 40, 4000)])
+def test_tensors_keep_short_keys_while_short_partitions_are_one_round(extents, k, dtype):
+    """Where middle partitions span too many slices for 32-bit keys and short ones do not, short ones up to a whole round;
+    tensors with few slices have middle ones from five sixths of a round on."""
+    for total in (FIVE_SIXTHS, FIVE_SIXTHS + 1, 1_400_000, ONE_ROUND_SHORT):
+        assert partitions("csf3", total, k, dtype, extents=extents) == whole_rounds(needed(total, SHORT, k)), total
+    total = FIVE_SIXTHS + 1
+    assert partitions("csf3", total, k, dtype, extents=(60, 60, 600)) == whole_units(needed(total, MIDDLE, k))
+    # past the round
+    past = partitions("csf3", ONE_ROUND_SHORT + 1, k, dtype, extents=extents)
+    assert past in (needed(ONE_ROUND_SHORT + 1, WIDE, k), whole_units(needed(ONE_ROUND_SHORT + 1, MIDDLE, k)))
