@@ -1411,20 +1411,29 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             // products: few places are emitted; those ask for the values of all operands, as many places at a time as there are
             // registers for beside the products
             constexpr int kBatch = sizeof(T) == 8 ? (R + 1) / 2 : R;
-            // Remapped operands, in stages -- order words, where the rows are stored, values --, each for the whole batch: place
-            // after place, every one waits for two round trips to memory, eighteen in a row with two operands
-            // (two DCSR matrices of 20M: 151.3 to 141.2 us).
+            const unsigned last_row = kMapped ? (unsigned)row_extent() - 1u : 0u;      // (operands that are not sorted can name any)
+            // the staged word of place m, its operand and, remapped operands, the row it lies in
+            auto entry_of = [&](int m, int &t, unsigned &row) -> int {
+                const int s = word_of(order_of(m), t);
+                row = kMapped ? min((unsigned)row0 + (unsigned)row_field(keys[K <= 2 || far ? s : mb + m]), last_row) : 0u;
+                return s;
+            };
+            // Two remapped operands, in stages -- order words, where the rows are stored, values --, each for the whole batch: place
+            // after place, every one waits for two round trips to memory, eighteen in a row (two DCSR matrices of 20M: 151.3 to 141.2 us).
+            // With more operands fewer places are emitted, and asking for the rows of the others costs more than the waits: three, four and five matrices of
+            // 16M entries in all, 20 a row, staged 90.9, 87.1, 92.2 us, like this 88.9, 83.4, 87.2; with nearly all entries common 94.4, 96.1, 105.1
+            // and 89.7, 96.9, 102.0 (doubles; floats of four 75.3 and 79.1 for 8M, of five 87.4 and 88.6, which did take 82.2 and 93.3 before).
+            constexpr bool kStaged = kMapped && K <= 2;
             auto load_values = [&](int g, int j0, T (&to)[R]) {
                 const int m0 = place0 + lane + g;
-                const unsigned last_row = (unsigned)row_extent() - 1u;     // (operands that are not sorted can name any)
                 int at[kBatch], a[kBatch], b[kBatch];      // (the operand above the staged word)
 #pragma unroll
                 for (int i = 0; i < kBatch; ++i) {
                     if (j0 + i >= R) continue;
                     // (every place names an entry and its row: no branches between the loads)
                     int t;
-                    const int m0i = m0 + (j0 + i) * NACHO_WAVE, m = m0i < n ? m0i : n - 1, s = word_of(order_of(m), t);
-                    const unsigned row = min((unsigned)row0 + (unsigned)row_field(keys[K <= 2 || far ? s : mb + m]), last_row);
+                    unsigned row;
+                    const int m = m0 + (j0 + i) * NACHO_WAVE, s = entry_of(m < n ? m : n - 1, t, row);
                     at[i] = t << 16 | s;
                     a[i] = global_ptr<int32_t>(w.srow[t])[row];
                     b[i] = global_ptr<int32_t>(w.spos[t])[row];
@@ -1438,7 +1447,16 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                         to[j0 + i] = global_ptr<T>(w.sval[at[i] >> 16])[(at[i] & 0xffff) + (a[i] - b[i])];
                 }
             };
-            if (kMapped) {
+            auto load_value = [&](int m) -> T {
+                if constexpr (kMapped) {
+                    int t;
+                    unsigned row;
+                    const int s = entry_of(m, t, row);
+                    const int sh = global_ptr<int32_t>(w.srow[t])[row] - global_ptr<int32_t>(w.spos[t])[row];
+                    return global_ptr<T>(w.sval[t])[s + sh];
+                } else return value_at(order_of(m));
+            };
+            if (kStaged) {
                 if (__ballot(e != 0ull && lane < R) != 0ull) {
 #pragma unroll
                     for (int j0 = 0; j0 < R; j0 += kBatch) load_values(0, j0, val);
@@ -1457,7 +1475,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
                 for (int j = 0; j < R; ++j) {
                     val[j] = T(0);
-                    if (my_bit(lane_word(e, j))) val[j] = value_at(order_of(place0 + j * NACHO_WAVE + lane));
+                    if (my_bit(lane_word(e, j))) val[j] = load_value(place0 + j * NACHO_WAVE + lane);
                 }
 #pragma unroll 1
                 for (int g = 1; g < k; ++g) {
@@ -1467,7 +1485,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
                         for (int j = j0; j < j0 + kBatch && j < R; ++j) {
                             more[j - j0] = T(1);
-                            if (my_bit(lane_word(e, j))) more[j - j0] = value_at(order_of(place0 + j * NACHO_WAVE + lane + g));
+                            if (my_bit(lane_word(e, j))) more[j - j0] = load_value(place0 + j * NACHO_WAVE + lane + g);
                         }
 #pragma unroll
                         for (int j = j0; j < j0 + kBatch && j < R; ++j) val[j] *= more[j - j0];
