@@ -276,7 +276,7 @@ int32_t nacho_spmv_rowcost(const nacho_tensor *A, const void *x, void *y, int32_
  * nacho_spmv without a partition pass (a P-free, fused search-in-execute form):
  * there is no partition table; every wavefront of the executing kernel finds its
  * own two boundaries -- Algorithm 1 for one CSR operand with the fixed-grain
- * queries Q_b = min(b * G, nnz), G = one wavefront's capacity, i.e. the row with
+ * queries Q_b = min(b * G, nnz), G non-zeros a wavefront, i.e. the row with
  * pos[r] <= Q_b < pos[r+1] by a 64-ary search over pos -- and y is cleared by a
  * small fill kernel first.  Same partitions, same arithmetic and the same result
  * as nacho_spmv with P = 0; it trades the partition kernel's one pass over pos
@@ -311,8 +311,9 @@ int32_t nacho_spadd_fused(const nacho_tensor *ops, int32_t k, int32_t dtype, int
  * the library's code object (one copy per GPU, nacho_static_scratch_bytes() bytes,
  * held until the process ends) instead of a caller's workspace.  The call
  * allocates and frees nothing and only enqueues.  A matrix whose partitions do
- * not fit that array (about 36 bytes per partition, i.e. per 512
- * non-zeros, or per requested partition when P is given) is refused with
+ * not fit that array (about 36 bytes per partition, i.e. per 512 non-zeros --
+ * per 1024 of a large fp32 matrix with long rows --, or per requested partition
+ * when P is given) is refused with
  * NACHO_ERR_TOO_LARGE before anything is launched.  All calls on one GPU share
  * the array: two calls that overlap in time on one GPU (different streams or
  * threads) race; calls on one stream are ordered and safe.  The first call on a

@@ -241,12 +241,14 @@ MergeFields fields_of(Format fmt, int32_t dtype, const nacho_tensor *ops, int64_
 
 // Partitions a fused call uses: at least P, and enough that one partition's work
 // (ideal share + k - 1 by the tightness bound of Section 3.2.2) fits a wavefront.
-int64_t fused_partitions(int32_t op, int32_t dtype, int64_t total_nnz, int64_t P)
+int64_t fused_partitions(int64_t cap, int64_t total_nnz, int64_t P)
 {
-    const int64_t cap = op == NACHO_OP_SPMV ? spmv_capacity(dtype)
-                                            : (P == 0 ? spmm_grain(total_nnz, compute_units(), false, 0) : spmm_capacity());
     const int64_t need = total_nnz > 0 ? ceil_div(total_nnz, cap) : 1;
     return P > need ? P : need;
+}
+int64_t spmv_partitions(int32_t dtype, int64_t nnz, int64_t n_rows, int64_t P)
+{
+    return fused_partitions(P == 0 ? spmv_grain(dtype, nnz, n_rows) : spmv_capacity(dtype), nnz, P);
 }
 
 // How an SpMM call runs on a workspace of ws_bytes bytes (ws NULL: one of any size).  Large calls sort their partitions by
@@ -282,7 +284,7 @@ SpmmPlan plan_spmm(void *ws, size_t ws_bytes, int32_t dtype, int64_t nnz, int64_
         plan.dealt = false;
     }
     plan.grain = P == 0 ? unsorted : 0;
-    plan.Pe = fused_partitions(NACHO_OP_SPMM, dtype, nnz, P);
+    plan.Pe = fused_partitions(P == 0 ? spmm_grain(nnz, compute_units(), false, 0) : spmm_capacity(), nnz, P);
     plan.w = carve_carry(ws, plan.Pe, dtype, plan.pass);
     plan.fits = ws_bytes >= plan.w.bytes;
     if (ws && !plan.fits) {
@@ -354,8 +356,8 @@ int32_t spmv_enqueue(const nacho_tensor *A, const DevOperands &dev, int64_t nnz,
     // (fixed-grain queries make the partitions inside a row arithmetic in pos, which the executing
     // kernel uses to deal them out; with a row cost the boundaries are no longer multiples of the grain
     // in pos, and the equally spaced queries are used)
-    const int64_t grain = (P == 0 && row_cost == 0) ? spmv_capacity(dtype) : 0;
-    const bool whole = grain > 0 && spmv_whole(dtype, Pe, n_rows, A->lvl[1].extent * (int64_t)dtype_size(dtype));
+    const int64_t grain = (P == 0 && row_cost == 0) ? spmv_grain(dtype, nnz, n_rows) : 0;
+    const bool whole = grain > 0 && spmv_whole(dtype, grain, Pe, n_rows, A->lvl[1].extent * (int64_t)dtype_size(dtype));
     if (!whole) {
         // (the partition kernel also writes the zeros of the rows A stores nothing in)
         ZeroRows zero;
@@ -440,7 +442,7 @@ int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int
     case NACHO_OP_SPMM:
         if (k != 1 || fmt != FMT_CSR) return 0;
         if (op == NACHO_OP_SPMM) return plan_spmm(nullptr, 0, dtype, total, ops[0].lvl[1].extent, n_dense, P).Pe;
-        return fused_partitions(op, dtype, total, P);
+        return spmv_partitions(dtype, total, ops[0].lvl[0].extent, P);
     case NACHO_OP_SPADD:
     case NACHO_OP_SPMUL:      // (a DCSR product: an upper bound, the count depends on the intersected rows)
         if (fmt == FMT_CSF3 && op == NACHO_OP_SPMUL) return 0;
@@ -465,7 +467,8 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
     case NACHO_OP_SPMM: {
         if (k != 1 || fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
         if (op == NACHO_OP_SPMM) *bytes = plan_spmm(nullptr, 0, dtype, total, ops[0].lvl[1].extent, n_dense, P).w.bytes;
-        else *bytes = carve_carry(nullptr, fused_partitions(op, dtype, total, P), dtype, 1).bytes;
+        // (for the shortest partitions: enough for any matrix with as many non-zeros or fewer)
+        else *bytes = carve_carry(nullptr, P == 0 ? fused_partitions(spmv_grain(dtype, 0, 0), total, 0) : spmv_partitions(dtype, total, 0, P), dtype, 1).bytes;
         return NACHO_OK;
     }
     case NACHO_OP_SPMUL:
@@ -510,11 +513,11 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
             need = plan.w.bytes;
             g = plan.grain * n_dense;
         } else {
-            Pe = fused_partitions(op, dtype, total, P);
+            Pe = spmv_partitions(dtype, total, ops[0].lvl[0].extent, P);
             const CarryWs c = carve_carry(ws, Pe, dtype, 1);
             w = c.parts;
             need = c.bytes;
-            if (P == 0) g = (int64_t)spmv_capacity(dtype);
+            if (P == 0) g = spmv_grain(dtype, total, ops[0].lvl[0].extent);
         }
         break;
     }
@@ -604,7 +607,7 @@ int32_t nacho_spmv(const nacho_tensor *A, const void *x, void *y, int32_t dtype,
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && (!A->val || !aligned16(A->val))) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, dtype, nnz, P);
+    const int64_t Pe = spmv_partitions(dtype, nnz, A->lvl[0].extent, P);
     CarryWs w = carve_carry(ws, Pe, dtype, 1);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     return spmv_enqueue(A, dev, nnz, x, y, dtype, P, Pe, w, static_cast<hipStream_t>(hip_stream));
@@ -622,12 +625,12 @@ int32_t nacho_spmv_fused(const nacho_tensor *A, const void *x, void *y, int32_t 
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && (!A->val || !aligned16(A->val))) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, dtype, nnz, 0);
+    const int64_t Pe = spmv_partitions(dtype, nnz, A->lvl[0].extent, 0);
     CarryWs w = carve_carry(ws, Pe, dtype, 1);
     if (!ws || ws_bytes < w.bytes) return NACHO_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const int64_t n_rows = A->lvl[0].extent;
-    const int64_t grain = spmv_capacity(dtype);
+    const int64_t grain = spmv_grain(dtype, nnz, n_rows);
     profile_begin(s);
     if (launch_zero_vector(dtype, y, n_rows, s) != hipSuccess) return NACHO_ERR_HIP;
     profile_mark("zero_y");
@@ -653,7 +656,7 @@ int32_t nacho_spmv_static(const nacho_tensor *A, const void *x, void *y, int32_t
     if (rc != NACHO_OK) return rc;
     if (fmt != FMT_CSR) return NACHO_ERR_UNSUPPORTED;
     if (nnz > 0 && (!A->val || !aligned16(A->val))) return NACHO_ERR_INVALID_ARG;
-    const int64_t Pe = fused_partitions(NACHO_OP_SPMV, dtype, nnz, P);
+    const int64_t Pe = spmv_partitions(dtype, nnz, A->lvl[0].extent, P);
     // sizes first: nothing is touched when the call does not fit the built-in scratch memory
     if (carve_carry(nullptr, Pe, dtype, 1).bytes > kStaticScratchBytes) return NACHO_ERR_TOO_LARGE;
     void *base = nullptr;

@@ -306,30 +306,39 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
     if (writer) y[r] = y_old + (v + (end == NACHO_WAVE - 1 ? tail : T(0)));
 }
 
-// Non-zeros of a partition and row positions staged at a time.  A wavefront's loads, sums and stores are one chain of latencies,
-// so twice as many wavefronts, half as long, are faster wherever there are few (fp32, 1024 non-zeros and 512, us: 27k
-// 9.5, 8.2; 0.65M 16.1, 13.0; 8.8M 46.0, 44.0; 35M 141, 138.6); around 5M, once around the chip either
-// way, 31.0 and 30.5, 6M 34.0 and 34.8, 8M 42.4 and 42.2.  Of 512 and 256 row
-// positions with 1024 non-zeros neither changed a thing; 768 non-zeros lay between.
-constexpr int kGrainF64 = 512, kRowsF64 = 512;
-constexpr int kGrainF32 = 512, kRowsF32 = 512;
+// Non-zeros of a partition (and row positions staged at a time), at most.
+constexpr int kGrainF64 = 512, kGrainF32 = 1024, kShortGrainF32 = 512;
 
 }  // namespace
 
 int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32; }
+
+// Floats, P = 0.  A wavefront's loads, sums and stores are one chain of latencies, so twice as many wavefronts, half as long, are faster
+// where few are in flight and where the chain has many rows to sum (partitions of 1024 and of 512 non-zeros, us: 0.1M, 6, 60, 300
+// a row 13.0, 9.3, 9.2 and 9.9, 8.1, 8.0; 2M, 6, 10, 20 a row 24.9, 23.5, 18.8 and 22.5, 21.3, 17.4; 10M 71.7, 62.7, 54.8 and 68.4, 60.3, 52.9).
+// Rows of many non-zeros are summed at a stretch, and a large call is as long as its loads, of which 5000 wavefronts of 1024 non-zeros
+// hold more in flight than 8192 of 512: 60, 100, 300 a row, 4M 24.6, 23.0, 19.7 and 25.8, 24.5, 21.3, 6M 32.8, 31.3, 27.2 and 34.8, 34.2, 30.8, 50M
+// 196, 189, 180 and 200, 193, 184; but 1M 11.3, 10.9, 10.5 and 10.4, 10.1, 9.7.  The lines lie between: 40 a row 0.97 to 1.03 of the time with 512 (slower at
+// 4M and 5M), 1.5M with 60, 100, 300 a row 1.00, 1.05, 0.96.  Tables of a caller's P and of the row-aware cost have up to 1024 (two non-zeros a row as cost, 5M, 10 a row 39.9 and 46.2).
+int64_t spmv_grain(int dtype, int64_t nnz, int64_t n_rows)
+{
+    if (dtype == NACHO_F64) return kGrainF64;
+    return nnz >= 1'400'000 && nnz >= 48 * n_rows ? kGrainF32 : kShortGrainF32;
+}
 
 // Small calls do without a partition kernel.  Its place in the stream (a launch and 3 us) is a third of what such a
 // call takes, while the wavefronts find their rows in two or three rounds of loads that hit the cache (40,000
 // non-zeros: 9.3 us in all; 1M: 16.8 to 15.4; 5M: 33.2 to 32.4).  Past a thousand partitions only while x fits an L2:
 // partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 309 to 469 us without).  With more
 // rows than the wavefronts can look after in one batch of loads each the partition kernel writes the zeros, a row a
-// thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).  The lines are in partitions of fp64 and in pairs of
-// them of fp32, whose search takes a larger share of a wavefront: with and without the partition kernel 31.6 and 31.0 us for 5M
-// non-zeros, 34.8 and 34.8 for 6M, 42.2 and 43.5 for 8M, with 3.6 MB of x 37.9 and 39.0 for 6M, 45.0 and 47.9 for 8M.
-bool spmv_whole(int dtype, int64_t P, int64_t n_rows, int64_t x_bytes)
+// thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).  The lines are in partitions of fp64 and of long ones of fp32; short
+// ones count half, whose search takes a larger share of a wavefront (with and without the partition kernel 31.6 and 31.0 us for 5M
+// non-zeros, 34.8 and 34.8 for 6M, 42.2 and 43.5 for 8M).
+bool spmv_whole(int dtype, int64_t grain, int64_t P, int64_t n_rows, int64_t x_bytes)
 {
-    const int64_t parts = dtype == NACHO_F64 ? P : (P + 1) / 2;
-    return n_rows <= (1 << 17) && n_rows <= parts * kZeroRows && (parts <= 1024 || (parts <= (dtype == NACHO_F64 ? 8192 : 5120) && x_bytes <= (4 << 20)));
+    const bool halves = dtype == NACHO_F32 && grain < kGrainF32;
+    const int64_t parts = halves ? (P + 1) / 2 : P;
+    return n_rows <= (1 << 17) && n_rows <= parts * kZeroRows && (parts <= 1024 || (parts <= (halves ? 5120 : 8192) && x_bytes <= (4 << 20)));
 }
 
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
@@ -341,15 +350,23 @@ hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, c
     hipLaunchKernelGGL((spmv_exec_kernel<T, G, R, DEALT, FUSED, TABLE>), dim3((unsigned)P), dim3(NACHO_WAVE), 0, stream, \
                        pos, crd, (const T *)val, (const T *)x, (T *)y, (int)nnz, coord, posn, cost, (T *)carry_val,    \
                        carry_row, (int)n_rows, (int)grain, nacho_host::wave_log())
-#define NACHO_SPMV_FORM(T, G, R)                                                                \
+#define NACHO_SPMV_GRAIN(T, G)                                                                  \
+    case SPMV_DEALT: NACHO_SPMV_LAUNCH(T, G, G, true, false, false); break;                     \
+    case SPMV_SEARCH: NACHO_SPMV_LAUNCH(T, G, G, true, true, false); break;                     \
+    case SPMV_WHOLE: NACHO_SPMV_LAUNCH(T, G, G, false, true, true); break;
+#define NACHO_SPMV_FORM(T, G)                                                                   \
     switch (form) {                                                                             \
-    case SPMV_TABLE: NACHO_SPMV_LAUNCH(T, G, R, false, false, false); break;                    \
-    case SPMV_DEALT: NACHO_SPMV_LAUNCH(T, G, R, true, false, false); break;                     \
-    case SPMV_SEARCH: NACHO_SPMV_LAUNCH(T, G, R, true, true, false); break;                     \
-    case SPMV_WHOLE: NACHO_SPMV_LAUNCH(T, G, R, false, true, true); break;                      \
+    case SPMV_TABLE: NACHO_SPMV_LAUNCH(T, G, G, false, false, false); break;                    \
+    NACHO_SPMV_GRAIN(T, G)                                                                      \
     }
-    if (dtype == NACHO_F64) { NACHO_SPMV_FORM(double, kGrainF64, kRowsF64) }
-    else { NACHO_SPMV_FORM(float, kGrainF32, kRowsF32) }
+    if (dtype == NACHO_F64) { NACHO_SPMV_FORM(double, kGrainF64) }
+    else if (grain == kShortGrainF32) {
+        switch (form) {
+        case SPMV_TABLE: return hipErrorInvalidValue;      // (has no grain)
+        NACHO_SPMV_GRAIN(float, kShortGrainF32)
+        }
+    } else { NACHO_SPMV_FORM(float, kGrainF32) }
+#undef NACHO_SPMV_GRAIN
 #undef NACHO_SPMV_FORM
 #undef NACHO_SPMV_LAUNCH
     return hipGetLastError();

@@ -103,8 +103,9 @@ def test_spmm_workspace_for_fewer_columns():
 def test_spmv_row_lengths(dtype):
     """Rows around the four products a lane adds at a time, the 48 from which a wavefront adds them, and the partition."""
     rng = np.random.default_rng(11)
-    grain = 512 if dtype == np.float64 else 1024
-    lens = [1, 2, 3, 4, 5, 7, 8, 9, 0, 46, 47, 48, 49, 50, 63, 64, 65, 0, 0, grain - 1, grain, grain + 1, 3 * grain]
+    lens = [1, 2, 3, 4, 5, 7, 8, 9, 0, 46, 47, 48, 49, 50, 63, 64, 65, 0, 0]
+    for grain in (512,) if dtype == np.float64 else (512, 1024):       # (floats: 1024 for a caller's P)
+        lens += [grain - 1, grain, grain + 1, 3 * grain]
     A = _matrix(rng, lens * 3, 4000, dtype)
     x = rng.uniform(-1, 1, 4000).astype(dtype)
     for P in (0, 5):
@@ -139,6 +140,43 @@ def test_spmv_calls_without_a_partition_kernel(parts, rows, cols):
     ref = oracle.partition([oracle.csr(pos, crd, rows, cols)], t["P"], queries=queries)
     got = {k: v.cpu().numpy() for k, v in t.items() if k in ("coord", "posn", "cost")}
     part._compare(got, ref, "limits")
+
+
+@pytest.mark.parametrize("grain,parts,rows,cols,search", [
+    (512, 2048, 5000, (1 << 20) + 1, False), (512, 2049, 5000, (1 << 20) + 1, True), (512, 2049, 5000, 1 << 20, False),
+    (512, 10240, 120_000, 3000, False), (512, 10241, 120_000, 3000, True), (512, 3, 512, 3000, False), (512, 3, 513, 3000, True),
+    (1024, 1400, 5000, 1 << 20, False), (1024, 1400, 5000, (1 << 20) + 1, True),
+    (1024, 8192, 5000, 3000, False), (1024, 8193, 5000, 3000, True), (1024, 8192, 1 << 17, 3000, False), (1024, 8192, (1 << 17) + 1, 3000, True)])
+def test_spmv_of_floats_without_a_partition_kernel(grain, parts, rows, cols, search):
+    """The same for floats, whose short partitions count half, and whose partitions are long where rows are."""
+    rng = np.random.default_rng(parts + rows + cols)
+    nnz = parts * grain - 100
+    lens = np.zeros(rows, np.int64)
+    some = np.sort(rng.choice(rows, min(rows, 4000), replace=False))
+    lens[some] = nnz // len(some)
+    lens[some[:nnz % len(some)]] += 1
+    pos = np.zeros(rows + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    at = np.arange(nnz) - np.repeat(pos[:-1].astype(np.int64), lens)
+    crd = (at * cols // np.repeat(np.maximum(lens, 1), lens)).astype(np.int32)
+    A = {"n_rows": rows, "n_cols": cols, "pos": pos, "crd": crd, "val": rng.uniform(-1, 1, nnz).astype(np.float32)}
+    x = rng.uniform(-1, 1, cols).astype(np.float32)
+    nb.profile_enable(True)
+    try:
+        spmv._check(A, x, 0, "limits of floats")
+        kernels = [name for name, _ in nb.profile_read()]
+    finally:
+        nb.profile_enable(False)
+    assert ("partition" in kernels) == search
+    op = csr_operand(A)
+    ws = torch.empty(nb.workspace_bytes(nb.OP_SPMV, [op], nb.F32), dtype=torch.uint8, device="cuda")
+    nb.nacho_spmv(op, dev(x), ws=ws)
+    t = nb.workspace_parts(nb.OP_SPMV, [op], nb.F32, ws)
+    assert t["P"] == parts and t["grain"] == grain
+    queries = np.minimum(np.arange(t["P"] + 1, dtype=np.int64) * grain, nnz)
+    ref = oracle.partition([oracle.csr(pos, crd, rows, cols)], t["P"], queries=queries)
+    got = {k: v.cpu().numpy() for k, v in t.items() if k in ("coord", "posn", "cost")}
+    part._compare(got, ref, "limits of floats")
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
