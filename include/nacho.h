@@ -172,10 +172,12 @@ int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int
 /* Bytes of device workspace `op` needs for these operands (host descriptors;
  * only counts/extents are read).  `P` as passed to the call (0 = automatic),
  * `n_dense` = columns of B for SpMM (0 otherwise).  NACHO_OP_SPADD sizes
- * nacho_spadd_k, NACHO_OP_SPMUL nacho_spmul_k.  SpMM keeps a row of up to 256
- * columns of C per partition; large calls with P = 0 are cut into up to eight
- * times as many partitions as small ones, as long as these rows take no more
- * than 512 MiB. */
+ * nacho_spadd_k, NACHO_OP_SPMUL nacho_spmul_k.  What it reports for a sum, for a
+ * product (not of DCSR operands) or for SpMV with P = 0 also serves calls of the
+ * same format, number of operands and value type with fewer entries.  SpMM keeps
+ * a row of up to 256 columns of C per partition; large calls with P = 0 are cut
+ * into up to eight times as many partitions as small ones, as long as these rows
+ * take no more than 512 MiB. */
 int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, int32_t dtype,
                               int64_t n_dense, int64_t P, size_t *bytes);
 

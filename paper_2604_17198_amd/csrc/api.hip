@@ -312,6 +312,19 @@ int64_t merge_partitions(int fmt, int32_t dtype, int32_t k, const MergeFields &f
     return P > need ? P : need;
 }
 
+// Partitions the workspace of a sum or product has room for: as many as any call of these operands' format and number takes that has as many
+// entries or fewer (a round of short partitions, or those of the widest keys), so that a workspace sized for the largest
+// operands of a program serves the others too.
+int64_t merge_room(int fmt, int32_t dtype, int32_t k, int64_t total_nnz, int64_t Pe)
+{
+    MergeFields shortest = {}, widest = {};
+    shortest.size = MERGE_SHORT;
+    widest.wide = 1;
+    const int64_t round = (int64_t)compute_units() * spadd_resident();
+    const int64_t one_round = std::min(round, whole_rounds(ceil_div(total_nnz, spadd_capacity(fmt, dtype, shortest) - k), round));
+    return std::max({Pe, one_round, whole_rounds(ceil_div(total_nnz, spadd_capacity(fmt, dtype, widest) - k), round)});
+}
+
 RemapWs carve_remap(void *ws, const nacho_tensor *ops, int k, int32_t dtype, int64_t total_nnz, int64_t P)
 {
     Carver c(ws);
@@ -480,7 +493,7 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
         /* fall through: the pipeline of the union */
     case NACHO_OP_SPADD: {
         const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
-        *bytes = carve_spadd(nullptr, Pe, k, dev.d).bytes;
+        *bytes = carve_spadd(nullptr, merge_room(spadd_fmt(fmt), dtype, k, total, Pe), k, dev.d).bytes;
         return NACHO_OK;
     }
     default: return NACHO_ERR_UNSUPPORTED;

@@ -83,3 +83,25 @@ def test_tensors_keep_short_keys_while_short_partitions_are_one_round(extents, k
     # past the round
     past = partitions("csf3", ONE_ROUND_SHORT + 1, k, dtype, extents=extents)
     assert past in (needed(ONE_ROUND_SHORT + 1, WIDE, k), whole_units(needed(ONE_ROUND_SHORT + 1, MIDDLE, k)))
+
+
+@pytest.mark.parametrize("dtype", [nb.F32, nb.F64])
+@pytest.mark.parametrize("k", [2, 3, 8])
+@pytest.mark.parametrize("fmt,extents", [(f, e) for f, e in EXTENTS.items()] +
+                         [("dcsr", (800_000, 1_000_000)), ("coo", (400_000, 1_000_000)), ("csr", (400_000, 1_000_000)),
+                          ("csf3", (2000, 2000, 2000)), ("csf3", (100_000, 40, 4000))])
+def test_a_workspace_serves_operands_with_fewer_entries(fmt, extents, k, dtype):
+    """Sized for the largest operands of a program, whatever partitions and keys the others take."""
+    totals = [1, 1000, 700_000, 749_568, 749_569, 1_000_000, FIVE_SIXTHS, FIVE_SIXTHS + 1, ONE_ROUND_SHORT, ONE_ROUND_SHORT + 1, 2_000_000,
+              2_700_000, 3_500_000, 4_200_000, 4_636_672, 4_636_673, 4_700_000, ONE_ROUND_F64, ONE_ROUND_F64 + 1, 5_669_000, 6_000_000,
+              8_000_000, 10_800_000, 12_000_000, 20_000_000, 35_000_000]
+    lib = nb.lib()
+    parts, grain = nb._Parts(), ctypes.c_int64(0)
+    for i, total in enumerate(totals):
+        have = ctypes.c_size_t(0)
+        assert lib.nacho_workspace_bytes(nb.OP_SPADD, _operands(fmt, _split(total, k), extents), k, dtype, 0, 0, ctypes.byref(have)) == 0
+        for fewer in totals[:i + 1]:
+            # (addresses are computed, nothing is read)
+            rc = lib.nacho_workspace_parts(nb.OP_SPADD, _operands(fmt, _split(fewer, k), extents), k, dtype, 0, 0, 1 << 20, have.value,
+                                           ctypes.byref(parts), ctypes.byref(grain), None)
+            assert rc == 0, (total, fewer)
