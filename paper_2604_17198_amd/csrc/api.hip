@@ -233,9 +233,9 @@ int spadd_fmt(Format f)
     return f == FMT_VECTOR ? SPADD_VECTOR : (f == FMT_CSR ? SPADD_CSR : (f == FMT_COO ? SPADD_COO : SPADD_DCSR));
 }
 
-MergeFields fields_of(Format fmt, int32_t dtype, const nacho_tensor *ops, int64_t total_nnz)
+MergeFields fields_of(Format fmt, int32_t dtype, const nacho_tensor *ops, int32_t k, int64_t total_nnz)
 {
-    return merge_fields(spadd_fmt(fmt), dtype, ops[0].lvl[0].extent, ops[0].nlevels > 1 ? ops[0].lvl[1].extent : 0,
+    return merge_fields(spadd_fmt(fmt), dtype, k, ops[0].lvl[0].extent, ops[0].nlevels > 1 ? ops[0].lvl[1].extent : 0,
                         ops[0].nlevels > 2 ? ops[0].lvl[2].extent : 0, total_nnz, compute_units());
 }
 
@@ -337,7 +337,7 @@ RemapWs carve_remap(void *ws, const nacho_tensor *ops, int k, int32_t dtype, int
     }
     w.P0 = rows_total > 0 ? ceil_div(rows_total, kRemapGrain) : 1;
     // the remapped cost never exceeds the stored non-zeros: enough partitions for any outcome
-    w.fields = merge_fields(SPADD_CSR, dtype, w.Mmax, ops[0].lvl[1].extent, 0, total_nnz, compute_units(), true);
+    w.fields = merge_fields(SPADD_CSR, dtype, k, w.Mmax, ops[0].lvl[1].extent, 0, total_nnz, compute_units(), true);
     w.Pmax = merge_partitions(SPADD_CSR, dtype, k, w.fields, total_nnz, P, kMappedEntries);
     w.parts0 = carve_parts(c, w.P0, k, 1);
     const int64_t rows_words = remap_state_words(w.P0, k);
@@ -459,7 +459,7 @@ int64_t nacho_num_partitions(int32_t op, const nacho_tensor *ops, int32_t k, int
     case NACHO_OP_SPADD:
     case NACHO_OP_SPMUL:      // (a DCSR product: an upper bound, the count depends on the intersected rows)
         if (fmt == FMT_CSF3 && op == NACHO_OP_SPMUL) return 0;
-        return merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
+        return merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, k, total), total, P);
     default: return 0;
     }
 }
@@ -492,7 +492,7 @@ int32_t nacho_workspace_bytes(int32_t op, const nacho_tensor *ops, int32_t k, in
         }
         /* fall through: the pipeline of the union */
     case NACHO_OP_SPADD: {
-        const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
+        const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, k, total), total, P);
         *bytes = carve_spadd(nullptr, merge_room(spadd_fmt(fmt), dtype, k, total, Pe), k, dev.d).bytes;
         return NACHO_OK;
     }
@@ -553,7 +553,7 @@ int32_t nacho_workspace_parts(int32_t op, const nacho_tensor *ops, int32_t k, in
         }
         /* fall through */
     case NACHO_OP_SPADD: {
-        Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, total), total, P);
+        Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields_of(fmt, dtype, ops, k, total), total, P);
         SpaddWs c = carve_spadd(ws, Pe, k, dev.d);
         w = c.parts;
         need = c.bytes;
@@ -912,7 +912,7 @@ static int32_t sparse_combine(bool multiply, const nacho_tensor *ops, int32_t k,
     if (fmt == FMT_CSF3 && (!out->pos0 || !out->pos2 || out->cap_fibres < 0 || (out->cap_rows > 0 && !out->crd0) ||
                             (out->cap_fibres > 0 && !out->crd1) || (out->cap_nnz > 0 && !out->crd2)))
         return NACHO_ERR_INVALID_ARG;
-    const MergeFields fields = fields_of(fmt, dtype, ops, total);
+    const MergeFields fields = fields_of(fmt, dtype, ops, k, total);
     const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields, total, P);
     SpaddWs w = carve_spadd(ws, Pe, k, dev.d);
     const bool recursive = multiply && fmt == FMT_DCSR && k > 1;    // (its own workspace layout)
@@ -964,7 +964,7 @@ int32_t nacho_spadd_fused(const nacho_tensor *ops, int32_t k, int32_t dtype, int
     }
     if (!out->counts || !out->status || !out->pos1 || out->cap_nnz < 0) return NACHO_ERR_INVALID_ARG;
     if (out->cap_nnz > 0 && (!out->crd1 || !out->val)) return NACHO_ERR_INVALID_ARG;
-    MergeFields fields = fields_of(fmt, dtype, ops, total);
+    MergeFields fields = fields_of(fmt, dtype, ops, k, total);
     const int64_t Pe = merge_partitions(spadd_fmt(fmt), dtype, k, fields, total, P);
     // (the kernel for long partitions holds any; three of its workgroups run on a compute unit whatever the operands)
     if (Pe <= 3 * (int64_t)compute_units()) fields.size = MERGE_LONG;

@@ -108,9 +108,9 @@ struct MergeFields {
     int32_t cb, jb, wide, size;
     uint32_t limit;
 };
-// `rows`, `cols`, `depth`: the extents of the levels; `total`: stored entries of all operands; `units`: compute units;
+// `k` operands; `rows`, `cols`, `depth`: the extents of the levels; `total`: stored entries of all operands; `units`: compute units;
 // `mapped`: remapped operands.
-MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units,
+MergeFields merge_fields(int fmt, int dtype, int k, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units,
                          bool mapped = false);
 // Entries of all operands one partition (workgroup) may hold.
 int spadd_capacity(int fmt, int dtype, const MergeFields &fields);

@@ -32,26 +32,26 @@ int spadd_wavefronts() { return kWaves; }
 // The key layout of a call: 32-bit keys when the rows (slices) that an average full partition spans take a
 // quarter of the row field or less, or the field holds any row, else 64-bit keys.  A partition that spans more rows
 // than the field holds is merged by searches (rank_far), for which a key's word has to hold any (slice, fibre) pair.
-MergeFields merge_fields(int fmt, int dtype, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units, bool mapped)
+MergeFields merge_fields(int fmt, int dtype, int k, int64_t rows, int64_t cols, int64_t depth, int64_t total, int units, bool mapped)
 {
     MergeFields f;
     f.cb = f.jb = f.wide = 0;
     f.limit = 0;
-    // Short partitions while two of them a compute unit hold a call (vectors; CSR, 16 entries a row and more) or five sixths of a round (the others; CSR
-    // with short rows a whole one), middle ones while one round of workgroups does, else long ones.  A partition takes some 8 us whatever it holds, so few long ones beat many short ones; but a thread's serial share
-    // is what a round takes, so no longer than need be.  Sums of two vectors, CSR matrices, tensors of 32-bit values, us:
-    // 700k entries in all, short 14.2, 16.9, 24.2, middle 13.5, 16.7, 24.9; 1.1M 16.1, 20.3, 27.6 and 14.4, 18.1, 27.9; 1.45M 17.8, 22.7, 30.8
-    // and 15.7, 20.6, 29.0; 3M, long 21.4, 25.8, 39.3, middle 19.9, 24.9, 35.1; products of 700k 1.04 to 1.08 of the time as middle ones, of 900k 0.96
-    // to 1.04; DCSR matrices with three entries a row, two and four operands, 1M 26.7, 40.5 and 27.2, 44.1, 1.4M 33.0, 47.5 and 31.8, 46.2; CSR with four
-    // 1M 22.8, 32.4 and 24.2, 35.4, 1.4M 26.1, 36.7 and 26.3, 37.2.  Past a round of middle ones (4.64M entries) partitions of doubles hold 5040 entries instead of 4536: 5.1M in one round of 1013
-    // and not two, 10 to 14 % less, 10M 0 to 5 %; within the round nine places are 1 to 5 % faster than ten.
+    // Short partitions while two of them a compute unit hold a call (vectors; CSR, 16 entries a row and more), a whole round of them (other CSR; five
+    // and more coordinate lists) or five sixths of one (the others), middle ones while one round of workgroups does, else long ones.  A partition
+    // takes some 8 us whatever it holds, so few long ones beat many short ones; but a thread's serial share is what a round takes, so no longer
+    // than need be.  Sums of two vectors, CSR matrices, tensors of 32-bit values, us: 700k entries in all, short 14.2, 16.9, 24.2, middle 13.5, 16.7,
+    // 24.9; 1.1M 16.1, 20.3, 27.6 and 14.4, 18.1, 27.9; 1.45M 17.8, 22.7, 30.8 and 15.7, 20.6, 29.0; 3M, long 21.4, 25.8, 39.3, middle 19.9, 24.9, 35.1.
+    // DCSR matrices with three entries a row, two and four operands, 1M short 26.7, 40.5, middle 27.2, 44.1; 1.4M 33.0, 47.5 and 31.8, 46.2; CSR with four
+    // 1M 22.8, 32.4 and 24.2, 35.4, 1.4M 26.1, 36.7 and 26.3, 37.2; coordinate lists, four, five, eight operands, 1.4M to 1.5M 39.5, 49.4, 61.5 and 39.4, 51.7,
+    // 64.5.  Products of 700k take 1.04 to 1.08 of the time as middle ones, of 900k 0.96 to 1.04.
     auto fits = [&](int size, double per_unit) {       // (workgroups on a compute unit)
         return (double)total <= (double)units * per_unit * (double)(capacity_of(false, size, dtype) - NACHO_MAX_OPERANDS);
     };
     const int resident = spadd_resident();
     double short_ones = 5.0 * resident / 6.0;
     if (fmt == SPADD_VECTOR || (fmt == SPADD_CSR && total >= 16 * rows)) short_ones = resident / 2;
-    else if (fmt == SPADD_CSR) short_ones = resident;
+    else if (fmt == SPADD_CSR || (fmt == SPADD_COO && k > 4)) short_ones = resident;
     // (remapped operands: the total counts entries that are not coiterated)
     if (fits(MERGE_SHORT, mapped ? resident : short_ones)) f.size = MERGE_SHORT;
     else if (mapped) f.size = MERGE_MIDDLE;

@@ -70,6 +70,57 @@ ONE_ROUND_SHORT = ROUND * (SHORT - nb.MAX_OPERANDS)
 FIVE_SIXTHS = ROUND * 5 * (SHORT - nb.MAX_OPERANDS) // 6
 
 
+def middle(fmt, total, k):
+    """Partitions of a call of one round of middle ones: as many on every compute unit, but for coordinate lists."""
+    need = needed(total, MIDDLE, k)
+    return whole_rounds(need) if fmt == "coo" else whole_units(need)
+
+
+TWO_A_UNIT = ROUND // 2 * (SHORT - nb.MAX_OPERANDS)
+SPARSE_CSR, DENSE_CSR = (1_000_000, 4000), (4000, 4000)
+
+
+@pytest.mark.parametrize("dtype", [nb.F32, nb.F64])
+@pytest.mark.parametrize("fmt,extents,k,last", [
+    ("vector", None, 2, TWO_A_UNIT), ("vector", None, 8, TWO_A_UNIT), ("csr", DENSE_CSR, 2, TWO_A_UNIT), ("csr", DENSE_CSR, 5, TWO_A_UNIT),
+    ("csr", SPARSE_CSR, 2, ONE_ROUND_SHORT), ("csr", SPARSE_CSR, 8, ONE_ROUND_SHORT), ("dcsr", None, 2, FIVE_SIXTHS), ("dcsr", None, 8, FIVE_SIXTHS),
+    ("coo", None, 2, FIVE_SIXTHS), ("coo", None, 4, FIVE_SIXTHS), ("coo", None, 5, ONE_ROUND_SHORT), ("coo", None, 8, ONE_ROUND_SHORT),
+    ("csf3", None, 2, FIVE_SIXTHS), ("csf3", None, 8, FIVE_SIXTHS)])
+def test_short_and_middle_partitions(fmt, extents, k, last, dtype):
+    """The last call with short partitions and the first with middle ones, sums and products (not of tensors)."""
+    for op in (nb.OP_SPADD,) if fmt == "csf3" else (nb.OP_SPADD, nb.OP_SPMUL):
+        assert partitions(fmt, last, k, dtype, op, extents) == whole_rounds(needed(last, SHORT, k))
+        assert partitions(fmt, last + 1, k, dtype, op, extents) == middle(fmt, last + 1, k)
+
+
+@pytest.mark.parametrize("k", [2, 5])
+@pytest.mark.parametrize("dtype", [nb.F32, nb.F64])
+def test_csr_rows_of_16_entries(dtype, k):
+    """Between two short partitions a compute unit and a round of them, the entries a row has in all operands decide."""
+    total = 1_200_000
+    assert partitions("csr", total, k, dtype, extents=(total // 16, 4000)) == middle("csr", total, k)
+    assert partitions("csr", total, k, dtype, extents=(total // 16 + 1, 4000)) == whole_rounds(needed(total, SHORT, k))
+
+
+# (the last total that one round of middle partitions holds; that two middle, that two long ones of floats a compute unit do)
+ONE_ROUND_MIDDLE = ROUND * (MIDDLE - nb.MAX_OPERANDS)
+TWO_MIDDLE, TWO_LONG = ONE_ROUND_MIDDLE // 2, ROUND // 2 * (LONG[nb.F32] - nb.MAX_OPERANDS)
+
+
+@pytest.mark.parametrize("k", [2, 8])
+@pytest.mark.parametrize("dtype", [nb.F32, nb.F64])
+@pytest.mark.parametrize("fmt", list(EXTENTS))
+def test_middle_and_long_partitions(fmt, dtype, k):
+    assert partitions(fmt, ONE_ROUND_MIDDLE, k, dtype) == middle(fmt, ONE_ROUND_MIDDLE, k)
+    total = ONE_ROUND_MIDDLE + 1
+    assert partitions(fmt, total, k, dtype) == whole_rounds(needed(total, LONG[dtype], k))
+    # two long partitions a compute unit instead of three middle ones: floats of CSR and DCSR
+    long = dtype == nb.F32 and fmt in ("csr", "dcsr")
+    for total, between in ((TWO_MIDDLE, False), (TWO_MIDDLE + 1, True), (TWO_LONG, True), (TWO_LONG + 1, False)):
+        expected = whole_rounds(needed(total, LONG[dtype], k)) if long and between else middle(fmt, total, k)
+        assert partitions(fmt, total, k, dtype) == expected, total
+
+
 @pytest.mark.parametrize("dtype", [nb.F32, nb.F64])
 @pytest.mark.parametrize("k", [2, 3, 8])
 @pytest.mark.parametrize("extents", [(2000, 2000, 2000), (100_000, 40, 4000)])
