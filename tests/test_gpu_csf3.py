@@ -96,10 +96,11 @@ def test_long_fibres_and_long_slices_span_partitions():
         _check(tens, shape, P, "long")
 
 
-@pytest.mark.parametrize("k", [2, 3, 4])
-@pytest.mark.parametrize("total,dtype", [(1_400_000, np.float32), (1_400_000, np.float64), (5_200_000, np.float32)])
+@pytest.mark.parametrize("k", [2, 3, 4, 6])
+@pytest.mark.parametrize("total,dtype", [(1_200_000, np.float32), (1_200_000, np.float64), (1_400_000, np.float32), (1_400_000, np.float64),
+                                         (5_200_000, np.float32), (5_300_000, np.float64), (6_000_000, np.float64)])
 def test_middle_and_long_partitions(k, total, dtype):
-    """Calls beyond short partitions: slices that span partitions, partitions that span many slices and that end with one, an
+    """Calls of short partitions, of a round of middle ones, of long ones and, doubles, of middle ones past a round: slices that span partitions, partitions that span many slices and that end with one, an
     operand without entries, with entries in the first and the last slice only."""
     rng = np.random.default_rng(total + k)
     shape = (3000, 40, 4000)

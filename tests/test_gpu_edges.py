@@ -222,13 +222,13 @@ def test_partition_two_vectors():
 
 # ---- merge --------------------------------------------------------------------
 def _short_limit(dtype):
-    """Most entries of a call with short partitions: all of them run at once (1512 places, less 64 words around runs)."""
-    return UNITS * 4 * (min(3 * 504, 3 * 512 - 64) - 8)
+    """Most entries of vectors in short partitions: two a compute unit (1512 places, less 64 words around runs)."""
+    return UNITS * 2 * (min(3 * 504, 3 * 512 - 64) - 8)
 
 
 @pytest.mark.parametrize("k", [2, 3])
 @pytest.mark.parametrize("over", [0, 1])
-def test_merge_short_and_long_partitions(k, over):
+def test_merge_short_and_middle_partitions(k, over):
     rng = np.random.default_rng(31)
     for dtype in DTYPES:
         total = _short_limit(dtype) + over
@@ -259,6 +259,54 @@ def test_merge_between_lengths_of_partitions(per_unit, places, over, dtype):
         assert torch.equal(a.crd1[:n], b.crd1[:n]) and torch.equal(a.val[:n], b.val[:n])
 
 
+def _keys(rng, n, extent):
+    """Exactly n distinct sorted numbers below `extent`, spread over it."""
+    gap = extent // n
+    return np.arange(n) * gap + rng.integers(0, gap, n)
+
+
+SHORT, MIDDLE, LONG_F64 = 3 * 512 - 64 - 8, 9 * 504 - 8, 10 * 504 - 8       # entries of a partition, less one an operand
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("fmt,line", [("vector", 2 * SHORT), ("csr", 2 * SHORT), ("csr few", 4 * SHORT), ("dcsr", 4 * SHORT * 5 / 6),
+                                      ("coo", 4 * SHORT * 5 / 6), ("csf3", 4 * SHORT * 5 / 6)] +
+                         [(f, 4 * MIDDLE) for f in ("vector", "csr", "dcsr", "coo", "csf3")] +
+                         [(f, 4 * LONG_F64) for f in ("vector", "csr", "dcsr", "coo", "csf3")] + [("csr", 2 * MIDDLE), ("dcsr", 2 * MIDDLE)])
+def test_merge_at_the_lines_between_lengths_of_partitions(fmt, line, dtype):
+    """The last call with short, middle or (doubles) long partitions and the first without, every format, two or three
+    operands, against the oracle."""
+    if line == 4 * LONG_F64 and dtype == np.float32:
+        line = 2 * (11 * 504 - 8)                           # (floats: two long ones a compute unit)
+    rng = np.random.default_rng(int(line))
+    for over in (0, 1):
+        total = int(UNITS * line) + over
+        k = 2 + over
+        sizes = [total // k + (t < total % k) for t in range(k)]
+        n_rows = {"csr": 4096, "csr few": 400_000, "dcsr": 60_000, "coo": 60_000}.get(fmt, 0)
+        cells = {"vector": 1 << 30, "csf3": 60 * 256 * 4096}.get(fmt, n_rows << 16)
+        keys = [_keys(rng, n, cells) for n in sizes]
+        keys[1][::5] = keys[0][:len(keys[1][::5])]          # (some coordinates in two operands)
+        keys[1] = np.unique(keys[1])
+        if len(keys[1]) < sizes[1]:
+            keys[1] = np.union1d(keys[1], np.setdiff1d(_keys(rng, 2 * sizes[1], cells), keys[1])[:sizes[1] - len(keys[1])])
+        assert sum(len(x) for x in keys) == total
+        vals = [rng.uniform(-1, 1, len(x)).astype(dtype) for x in keys]
+        tag = f"line {line} {over}"
+        if fmt == "vector":
+            add.check_vec([x.astype(np.int32) for x in keys], vals, 1 << 30, 0, tag)
+        elif fmt == "csf3":
+            shape = (60, 256, 4096)
+            csf3._check([csf3._tensor(np.stack(np.unravel_index(x, shape), 1), v) for x, v in zip(keys, vals)], shape, 0, tag)
+        else:
+            shape = (n_rows, 1 << 16)
+            cs = [np.stack([x >> 16, x & 0xffff], 1) for x in keys]
+            if fmt == "coo":
+                coo._check(nb.nacho_spadd_k, oracle.spadd_coo, cs, vals, shape, 0, tag)
+            else:
+                (add.check_dcsr if fmt == "dcsr" else add.check_csr)(list(zip(cs, vals)), shape, 0, tag)
+
+
 def _banded(rng, n_rows, n_cols, dense, sparse):
     """Many entries in a band of a few rows and a few in rows far apart: partitions of the latter span more rows than the
     row field of their keys holds."""
@@ -268,10 +316,11 @@ def _banded(rng, n_rows, n_cols, dense, sparse):
 
 
 @pytest.mark.parametrize("k,total,dtype", [(2, 1_100_000, np.float32), (3, 1_100_000, np.float64),
-                                           (2, 3_300_000, np.float64), (3, 3_300_000, np.float32)])
+                                           (2, 3_300_000, np.float64), (3, 3_300_000, np.float32),
+                                           (2, 5_600_000, np.float32), (3, 5_600_000, np.float64)])
 def test_merge_in_bands(k, total, dtype):
-    """Rows past the row field (12 bits beside 2^20 columns): the partition is merged by searches; short partitions and
-    long ones."""
+    """Rows past the row field (12 bits beside 2^20 columns): the partition is merged by searches; short partitions,
+    middle and long ones."""
     rng = np.random.default_rng(41)
     shape = (1 << 19, 1 << 20)
     keys = [_banded(rng, *shape, int(total / (k + 0.33)), 9000) for _ in range(k)]
@@ -291,13 +340,14 @@ def test_merge_in_bands(k, total, dtype):
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
-def test_merge_tensors_in_bands(dtype):
-    """Slices past the row field of a tensor's keys (16 bits hold slice and fibre)."""
+@pytest.mark.parametrize("draws", [600_000, 1_500_000, 3_200_000])
+def test_merge_tensors_in_bands(dtype, draws):
+    """Slices past the row field of a tensor's keys (16 bits hold slice and fibre): short, middle and long partitions."""
     rng = np.random.default_rng(51)
     shape = (100_000, 64, 256)
     tens = []
     for _ in range(2):
-        top = rng.integers(0, 400, 1_500_000) * (64 * 256) + rng.integers(0, 64 * 256, 1_500_000)
+        top = rng.integers(0, 400, draws) * (64 * 256) + rng.integers(0, 64 * 256, draws)
         rest = rng.integers(400, shape[0], 4000) * (64 * 256) + rng.integers(0, 64 * 256, 4000)
         lin = np.unique(np.concatenate([top, rest]))
         c = np.stack(np.unravel_index(lin, shape), axis=1)

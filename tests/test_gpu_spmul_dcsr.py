@@ -184,6 +184,31 @@ def test_every_entry_or_few_in_all_operands(k, dtype, n):
         check(mats, shape, 0, f"batches n={n} few={few}")
 
 
+@pytest.mark.parametrize("k", [2, 3, 4, 5])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_every_entry_or_few_in_middle_partitions(k, dtype):
+    """The same in partitions of nine places a thread, which calls of more than 1.5M entries have: rows that only one
+    operand stores make up the number, and are not coiterated."""
+    rng = np.random.default_rng(110 + k)
+    shape = (20_000, 5000)
+    rows = 1_700_000 // (1000 * k)
+    alone = []
+    for t in range(k):
+        r = np.repeat(1000 + t * rows + np.arange(rows), 1000)
+        alone.append(np.stack([r, np.tile(np.arange(0, 5000, 5), rows)], axis=1))
+    for n in (63, 575, 576, 577, 4094, 4095, 4096, 4097, 9300):
+        whole = random_coords(rng, (97, 5000), n)
+        for few in (False, True):
+            mats = []
+            for t in range(k):
+                c = whole
+                if few and t:
+                    c = np.unique(np.concatenate([whole[::7], random_coords(rng, (97, 5000), n)]), axis=0)
+                c = np.concatenate([c, alone[t]])
+                mats.append(_mat(c, rng.uniform(0.5, 1.5, len(c)).astype(dtype)))
+            check(mats, shape, 0, f"middle n={n} few={few}")
+
+
 def test_capacity_overflow_is_reported():
     rng = np.random.default_rng(8)
     shape = (300, 200)
