@@ -100,8 +100,9 @@ def test_long_fibres_and_long_slices_span_partitions():
 @pytest.mark.parametrize("total,dtype", [(1_200_000, np.float32), (1_200_000, np.float64), (1_400_000, np.float32), (1_400_000, np.float64),
                                          (5_200_000, np.float32), (5_300_000, np.float64), (6_000_000, np.float64)])
 def test_middle_and_long_partitions(k, total, dtype):
-    """Calls of short partitions, of a round of middle ones, of long ones and, doubles, of middle ones past a round: slices that span partitions, partitions that span many slices and that end with one, an
-    operand without entries, with entries in the first and the last slice only."""
+    """Calls of short partitions, of a round of middle ones, of long ones and, doubles, of middle ones past a round: slices
+    that span partitions, partitions that span many slices and that end with one, an operand without entries, with entries in
+    the first and the last slice only."""
     rng = np.random.default_rng(total + k)
     shape = (3000, 40, 4000)
     tens = []
