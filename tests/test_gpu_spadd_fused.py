@@ -68,11 +68,11 @@ def test_vectors_random(k, dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("k", [3, 4, 5, 8])
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 8])
 def test_three_and_four_workgroups_on_a_compute_unit(k, dtype):
     """Up to three partitions a compute unit the kernel of long partitions runs, with more of them one held to the
     registers of four (from four or five operands on a kernel of its own, for middle partitions): both sides of
-    the line, and middle partitions as full as they get."""
+    the line, middle partitions as full as they get, and calls past a round, where doubles have middle ones again."""
     units = torch.cuda.get_device_properties(0).multi_processor_count
     rng = np.random.default_rng(750 + k)
 
@@ -84,8 +84,9 @@ def test_three_and_four_workgroups_on_a_compute_unit(k, dtype):
     vs, vals = vectors(units * 12_000)
     for P in (3 * units, 3 * units + 1):
         _check(vs, vals, 2**30, P, "line")
-    vs, vals = vectors(units * 4 * 4528)
-    _check(vs, vals, 2**30, 0, "full")
+    for total, tag in ((units * 4 * 4528, "full"), (units * 4 * 5100, "past a round")):
+        vs, vals = vectors(total)
+        _check(vs, vals, 2**30, 0, tag)
 
 
 def test_all_operands_empty():
