@@ -370,7 +370,7 @@ int32_t spmv_enqueue(const nacho_tensor *A, const DevOperands &dev, int64_t nnz,
     // kernel uses to deal them out; with a row cost the boundaries are no longer multiples of the grain
     // in pos, and the equally spaced queries are used)
     const int64_t grain = (P == 0 && row_cost == 0) ? spmv_grain(dtype, nnz, n_rows) : 0;
-    const bool whole = grain > 0 && spmv_whole(dtype, grain, Pe, n_rows, A->lvl[1].extent * (int64_t)dtype_size(dtype));
+    const bool whole = grain > 0 && spmv_whole(dtype, nnz, grain, Pe, n_rows, A->lvl[1].extent * (int64_t)dtype_size(dtype));
     if (!whole) {
         // (the partition kernel also writes the zeros of the rows A stores nothing in)
         ZeroRows zero;

@@ -196,6 +196,27 @@ __device__ inline int first_row_past(const int32_t *__restrict__ pos, int lo, in
     return lo;
 }
 
+// A search for the number of rows that end at or before q, which is also the row that holds position q: it lies in [lo, hi].
+// A round looks at 64 rows; its load and what follows from it are apart, so that other loads can be asked for between them.
+struct RowWindow {
+    int lo, hi;
+    __device__ int stride() const { return (hi - lo + NACHO_WAVE - 1) / NACHO_WAVE; }
+    // this lane's probe (past the window, or the window empty: some position)
+    __device__ int load(const int32_t *__restrict__ pos, int n_rows) const
+    {
+        const int at = lo + (lane_id() + 1) * stride();
+        return pos[at < n_rows ? at : n_rows];
+    }
+    __device__ void narrow(int probe, int q)
+    {
+        const int step = stride(), at = lo + (lane_id() + 1) * step - 1;
+        const int n = __popcll(__ballot(at < hi && probe <= q));               // (a prefix of the lanes)
+        const int lo_new = lo + n * step, at_next = lo + (n + 1) * step - 1;
+        hi = n < NACHO_WAVE && at_next < hi ? at_next : hi;
+        lo = lo_new < hi ? lo_new : hi;
+    }
+};
+
 // The rows ra, rb with pos[r] <= q < pos[r + 1] for q = qa and qb (n_rows where pos[n_rows] <= q), both at once:
 // half of the wavefront searches each, 32 probes per round.
 __device__ inline void rows_holding(const int32_t *__restrict__ pos, int n_rows, int qa, int qb, int &ra, int &rb)

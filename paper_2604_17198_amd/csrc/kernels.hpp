@@ -38,7 +38,7 @@ int64_t spmv_grain(int dtype, int64_t nnz, int64_t n_rows);
 // SPMV_WHOLE: the same, and the kernel writes the table and the zeros of empty rows itself.
 enum SpmvForm { SPMV_TABLE = 0, SPMV_DEALT = 1, SPMV_SEARCH = 2, SPMV_WHOLE = 3 };
 // Whether a fixed-grain call with P partitions takes the last form.
-bool spmv_whole(int dtype, int64_t grain, int64_t P, int64_t n_rows, int64_t x_bytes);
+bool spmv_whole(int dtype, int64_t nnz, int64_t grain, int64_t P, int64_t n_rows, int64_t x_bytes);
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,
                             const void *x, void *y, int64_t n_rows, int64_t nnz,
                             int32_t *coord, int32_t *posn, int64_t *cost, int64_t P,

@@ -50,39 +50,171 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     __shared__ int32_t spos[RBLK + 1];
 
     const int lane = threadIdx.x;
+    // What bounds a small or middling call is the chain of round trips of one wavefront, so nothing waits that does not have to:
+    // where partitions have a fixed grain their non-zeros are known without their rows, and crd / val travel beside the search for
+    // the rows or the table's row fields, the gathers of x beside its later rounds, the rows' positions beside the gathers (the
+    // search, the row positions and then the non-zeros one after the other 40,000 non-zeros of doubles took 9.9 us, 5M floats of 50 a row
+    // 29.6, 20M of 12 a row 112, like this 8.2, 25.5 and 107).
+    int p = blockIdx.x;
+    int r0 = 0, r1 = 0, n0 = 0, n1 = 0;                // rows and positions of the boundaries p and p + 1
+    auto fixed_range = [&]() {
+        const long long Qa = (long long)p * grain, Qb = Qa + grain;
+        n0 = (int)(Qa < nnz ? Qa : nnz);               // (pos[0] = 0)
+        n1 = (int)(Qb < nnz ? Qb : nnz);
+    };
+    auto ends = [&]() {                                // of the table: by definition
+        if (p == 0) r0 = 0;
+        else if ((long long)p * grain >= nnz) r0 = n_rows;
+        if ((long long)(p + 1) * grain >= nnz) r1 = n_rows;
+    };
+    RowWindow wa, wb;                                  // (kTable) the rows that hold n0 and n1
+    int probe = 0;
+    if (kTable) {
+        wa = wb = RowWindow{0, n_rows};
+        probe = wa.load(pos, n_rows);                  // (the first probes are the same for every boundary)
+        fixed_range();
+    } else if (kFused) {
+        fixed_range();
+        rows_holding(pos, n_rows, n0, n1, r0, r1);
+        ends();
+    }
     // Which partition this workgroup executes: those inside one long row are dealt out by XCD, so that the gathers of an XCD
     // stay inside one eighth of x, which its L2 holds (all of x it does not).
-    int p = blockIdx.x;
-    // (fused search) the rows and positions of the boundaries p and p + 1
-    int r0 = 0, r1 = 0, n0 = 0, n1 = 0;
-    auto boundaries = [&]() {
-        const int base = pos[0];
-        const long long Qa = (long long)p * grain, Qb = Qa + grain;
-        n0 = base + (int)(Qa < nnz ? Qa : nnz);
-        n1 = base + (int)(Qb < nnz ? Qb : nnz);
-        rows_holding(pos, n_rows, n0, n1, r0, r1);
-        if (p == 0) r0 = 0;
-        else if (Qa >= nnz) r0 = n_rows;
-        if (Qb >= nnz) r1 = n_rows;
-    };
-    if (kFused) boundaries();
+    // (k = 1, d = 2: coord[b*2 + 0] = row, posn[b*2 + 1] = position in crd/val)
     if (kDealt) {
         const int r = kFused ? r0 : coord[2 * p];
-        if (r < n_rows) {
-            const int base = pos[0];
-            p = dealt_partition(p, pos[r] - base, pos[r + 1] - base, grain);
+        if (r < n_rows) p = dealt_partition(p, pos[r], pos[r + 1], grain);
+        if (!kFused || p != (int)blockIdx.x) fixed_range();
+        if (kFused && p != (int)blockIdx.x) {
+            rows_holding(pos, n_rows, n0, n1, r0, r1);
+            ends();
         }
     }
-    // k = 1, d = 2: coord[b*2 + 0] = row, posn[b*2 + 1] = position in crd/val
-    if (kFused) {
-        if (p != (int)blockIdx.x) boundaries();
-        if (kTable && lane == 0) {
+    if (!kFused) {
+        r0 = coord[2 * p]; r1 = coord[2 * p + 2];
+        if (!kDealt) { n0 = posn[2 * p + 1]; n1 = posn[2 * p + 3]; }
+    }
+    const int a0 = n0;                                 // prod[i] belongs to position a0 + i
+
+    // Lane l takes positions n0 + l, n0 + 64 + l, ...: consecutive lanes hold
+    // consecutive non-zeros, so inside a dense row the 64 gathers of one
+    // instruction fall into few cache lines of x (columns are sorted).  All
+    // streamed loads are issued before the first gather, all gathers before the
+    // first LDS store, so one wavefront keeps its whole window in flight.
+    // (what lies past the partition's last place is loaded from that place, and nobody's product)
+    constexpr int kIter = G / NACHO_WAVE;
+    const int last = n1 - n0 - 1;                      // (kTable: every partition has non-zeros)
+    int c[kIter];
+    T v[kIter], xv[kIter];
+    if (kTable || last >= 0) {
+#pragma unroll
+        for (int j = 0; j < kIter; ++j) {
+            const int i = j * NACHO_WAVE + lane;
+            c[j] = __builtin_nontemporal_load(crd + n0 + (i < last ? i : last));
+        }
+#pragma unroll
+        for (int j = 0; j < kIter; ++j) {
+            const int i = j * NACHO_WAVE + lane;
+            v[j] = __builtin_nontemporal_load(val + n0 + (i < last ? i : last));
+        }
+        __builtin_amdgcn_sched_barrier(0);             // (left to itself the compiler asks for val behind the gathers)
+    }
+    if (kTable) {
+        wb.narrow(probe, n1);
+        wa.narrow(probe, n0);
+        const int probe_a = wa.load(pos, n_rows), probe_b = wb.load(pos, n_rows);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < kIter; ++j) asm volatile("" : "+v"(c[j]));         // (nor does anything of the gathers' wait before this)
+#pragma unroll
+        for (int j = 0; j < kIter; ++j) xv[j] = x[c[j]];
+        __builtin_amdgcn_sched_barrier(0);
+        wa.narrow(probe_a, n0);
+        wb.narrow(probe_b, n1);
+        while (wa.lo < wa.hi || wb.lo < wb.hi) {
+            const int more_a = wa.load(pos, n_rows), more_b = wb.load(pos, n_rows);
+            wa.narrow(more_a, n0);
+            wb.narrow(more_b, n1);
+        }
+        r0 = wa.lo;
+        r1 = wb.lo;
+        ends();
+    }
+    // the positions of the first row block: one lane a row, the first kAhead * 64 of them through registers, so that neither the
+    // gathers wait for them nor they for the gathers
+    constexpr int kAhead = 4;
+    int staged = r1 - r0 + 1;                          // rows that may overlap or start here, all but the last of which end here
+    staged = staged < n_rows - r0 ? staged : n_rows - r0;
+    staged = staged < RBLK ? staged : RBLK;
+    int row_pos[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        const int i = u * NACHO_WAVE + lane;
+        row_pos[u] = pos[r0 + (i < staged ? i : staged)];
+    }
+    const int pr0 = pos[r0], pr1 = pos[r1];
+    // (kTable) this wavefront's share of the zeros, the first 64 rows of it
+    const int share = kTable ? (n_rows + (int)gridDim.x - 1) / (int)gridDim.x : 0;
+    const int zero0 = (int)blockIdx.x * share + lane, zero1 = min(((int)blockIdx.x + 1) * share, n_rows);
+    int za = 0, zb = 1;
+    if (kTable) {
+        za = pos[zero0 < n_rows ? zero0 : n_rows];
+        zb = pos[zero0 + 1 < n_rows ? zero0 + 1 : n_rows];
+    }
+    if (!kTable && last >= 0) {
+#pragma unroll
+        for (int j = 0; j < kIter; ++j) xv[j] = x[c[j]];
+    }
+    const bool has_head = n0 > pr0;                    // row r0 started in an earlier partition
+    const int next_first = (n1 > pr1) ? r1 + 1 : r1;   // first row that starts after this partition
+    const int nrows = next_first - r0;                 // rows overlapping or starting here
+    int nr = nrows < RBLK ? nrows : RBLK;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        static_assert(kAhead * NACHO_WAVE <= RBLK, "every lane has a word to write");
+        spos[u * NACHO_WAVE + lane] = row_pos[u];      // (what lies past the last row nobody reads)
+    }
+    for (int i0 = kAhead * NACHO_WAVE; i0 <= staged; i0 += kAhead * NACHO_WAVE) {
+        int more[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + u * NACHO_WAVE + lane;
+            more[u] = pos[r0 + (i < staged ? i : staged)];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + u * NACHO_WAVE + lane;
+            spos[i < staged ? i : staged] = more[u];
+        }
+    }
+    if (kTable || last >= 0) {
+#pragma unroll
+        for (int j = 0; j < kIter; ++j) prod[j * NACHO_WAVE + lane] = v[j] * xv[j];
+    }
+    wave_sync();
+    if (kTable) {
+        if (zero0 < zero1 && za == zb) y[zero0] = T(0);
+        if (share > NACHO_WAVE) {                      // (uniform)
+            int a[kZeroRows / NACHO_WAVE - 1], b[kZeroRows / NACHO_WAVE - 1];
+#pragma unroll
+            for (int u = 0; u < kZeroRows / NACHO_WAVE - 1; ++u) {
+                const int z = zero0 + (u + 1) * NACHO_WAVE;
+                a[u] = pos[z < n_rows ? z : n_rows];
+                b[u] = pos[z + 1 < n_rows ? z + 1 : n_rows];
+            }
+#pragma unroll
+            for (int u = 0; u < kZeroRows / NACHO_WAVE - 1; ++u) {
+                const int z = zero0 + (u + 1) * NACHO_WAVE;
+                if (z < zero1 && a[u] == b[u]) y[z] = T(0);
+            }
+        }
+        if (lane == 0) {
             // the partition table: this boundary, and the end
             coord[2 * p] = r0;
-            coord[2 * p + 1] = r0 < n_rows ? (p == 0 ? 0 : crd[n0]) : 0;
+            coord[2 * p + 1] = r0 < n_rows && p > 0 ? c[0] : 0;
             posn[2 * p] = r0;
             posn[2 * p + 1] = p == 0 ? 0 : (r0 < n_rows ? n0 : nnz);
-            cost[p] = n0 - pos[0];
+            cost[p] = n0;
             if (p == (int)gridDim.x - 1) {
                 coord[2 * p + 2] = n_rows;
                 coord[2 * p + 3] = 0;
@@ -91,68 +223,14 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
                 cost[p + 1] = nnz;
             }
         }
-    } else {
-        r0 = coord[2 * p]; r1 = coord[2 * p + 2];
-        n0 = posn[2 * p + 1]; n1 = posn[2 * p + 3];
     }
-    const int pr0 = pos[r0], pr1 = pos[r1];
-    const bool has_head = n0 > pr0;                    // row r0 started in an earlier partition
-    const int next_first = (n1 > pr1) ? r1 + 1 : r1;   // first row that starts after this partition
-    const int nrows = next_first - r0;                 // rows overlapping or starting here
-    const int a0 = n0;                                 // prod[i] belongs to position a0 + i
-    // pos entries of the first row block, requested before the streamed data
-    int nr = nrows < RBLK ? nrows : RBLK;
-    if (nrows > 0)
-        for (int i = lane; i <= nr; i += NACHO_WAVE) spos[i] = pos[r0 + i];
-
-    // Lane l takes positions n0 + l, n0 + 64 + l, ...: consecutive lanes hold
-    // consecutive non-zeros, so inside a dense row the 64 gathers of one
-    // instruction fall into few cache lines of x (columns are sorted).  All
-    // streamed loads are issued before the first gather, all gathers before the
-    // first LDS store, so one wavefront keeps its whole window in flight.
-    // (places are compared, not positions: the last ones may lie past 2^31)
-    constexpr int kIter = G / NACHO_WAVE;
-    const int left = n1 - n0 - lane;
-    int c[kIter];
-    T v[kIter];
-#pragma unroll
-    for (int j = 0; j < kIter; ++j) {
-        c[j] = 0;
-        v[j] = T(0);
-        if (j * NACHO_WAVE < left) {
-            const int idx = n0 + j * NACHO_WAVE + lane;
-            c[j] = __builtin_nontemporal_load(crd + idx);
-            v[j] = __builtin_nontemporal_load(val + idx);
-        }
-    }
-    T xv[kIter];
-#pragma unroll
-    for (int j = 0; j < kIter; ++j) xv[j] = j * NACHO_WAVE < left ? x[c[j]] : T(0);
-    if (kTable) {
-        const int share = (n_rows + (int)gridDim.x - 1) / (int)gridDim.x;
-        const int z = (int)blockIdx.x * share + lane, z_end = min((int)(blockIdx.x + 1) * share, n_rows);
-        int a[kZeroRows / NACHO_WAVE], b[kZeroRows / NACHO_WAVE];
-#pragma unroll
-        for (int u = 0; u < kZeroRows / NACHO_WAVE; ++u) {
-            a[u] = 0;
-            b[u] = 1;
-            if (z + u * NACHO_WAVE < z_end) { a[u] = pos[z + u * NACHO_WAVE]; b[u] = pos[z + u * NACHO_WAVE + 1]; }
-        }
-#pragma unroll
-        for (int u = 0; u < kZeroRows / NACHO_WAVE; ++u)
-            if (a[u] == b[u]) y[z + u * NACHO_WAVE] = T(0);
-    }
-#pragma unroll
-    for (int j = 0; j < kIter; ++j)
-        if (j * NACHO_WAVE < left) prod[j * NACHO_WAVE + lane] = v[j] * xv[j];
-    __syncthreads();
 
     for (int rb = 0; rb < nrows; rb += RBLK) {
         if (rb > 0) {
             nr = nrows - rb < RBLK ? nrows - rb : RBLK;
-            __syncthreads();
+            wave_sync();
             for (int i = lane; i <= nr; i += NACHO_WAVE) spos[i] = pos[r0 + rb + i];
-            __syncthreads();
+            wave_sync();
             // A block of rows without entries: their zeros are written elsewhere (by the partition
             // kernel, or above), so the wavefront steps over them, however many there are.
             const int q = spos[0];
@@ -216,10 +294,15 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
     const int lane = lane_id();
     const int p_first = p - lane;                      // partition of lane 0
     if (p_first >= P) return;                          // whole wavefront leaves together
-    const int r = p < P ? carry_row[p] : -1;
-    T v = r >= 0 ? carry_val[p] : T(0);
+    // (all three asked for at once: a partition without a carry has some words there)
+    const int at = p < P ? p : P - 1;
+    int r = carry_row[at];
+    T v = carry_val[at];
+    const int row_before = carry_row[p_first > 0 ? p_first - 1 : 0];
+    if (p >= P) r = -1;
+    if (r < 0) v = T(0);
     int before = __builtin_amdgcn_update_dpp(0, r, 0x138, 0xf, 0xf, false);    // wave_shr:1
-    if (lane == 0) before = p_first > 0 ? carry_row[p_first - 1] : -1;
+    if (lane == 0) before = p_first > 0 ? row_before : -1;
     const bool head = r >= 0 && r != before;           // first carry of its row
     const bool first_here = r != before || lane == 0;  // first lane of its segment in this wavefront
     const unsigned long long starts = __ballot(first_here);
@@ -314,31 +397,37 @@ constexpr int kGrainF64 = 512, kGrainF32 = 1024, kShortGrainF32 = 512;
 int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32; }
 
 // Floats, P = 0.  A wavefront's loads, sums and stores are one chain of latencies, so twice as many wavefronts, half as long, are faster
-// where few are in flight and where the chain has many rows to sum (partitions of 1024 and of 512 non-zeros, us: 0.1M, 6, 60, 300
-// a row 13.0, 9.3, 9.2 and 9.9, 8.1, 8.0; 2M, 6, 10, 20 a row 24.9, 23.5, 18.8 and 22.5, 21.3, 17.4; 10M 71.7, 62.7, 54.8 and 68.4, 60.3, 52.9).
-// Rows of many non-zeros are summed at a stretch, and a large call is as long as its loads, of which 5000 wavefronts of 1024 non-zeros
-// hold more in flight than 8192 of 512: 60, 100, 300 a row, 4M 24.6, 23.0, 19.7 and 25.8, 24.5, 21.3, 6M 32.8, 31.3, 27.2 and 34.8, 34.2, 30.8, 50M
-// 196, 189, 180 and 200, 193, 184; but 1M 11.3, 10.9, 10.5 and 10.4, 10.1, 9.7.  The lines lie between: 40 a row 0.97 to 1.03 of the time with 512 (slower at
-// 4M and 5M), 1.5M with 60, 100, 300 a row 1.00, 1.05, 0.96.  Tables of a caller's P and of the row-aware cost have up to 1024 (two non-zeros a row as cost, 5M, 10 a row 39.9 and 46.2).
+// where few are in flight and where the chain has many rows to sum (partitions of 1024 and of 512 non-zeros, us: 50,000, 5 a row 11.2 and 8.8;
+// 2M, 5, 10, 20 a row 25.7, 21.0, 16.4 and 22.1, 18.6, 15.7; 10M, 5, 10, 20, 40 a row 78.6, 59.2, 49.5, 45.6 and 72.5, 54.9, 46.2, 43.0).
+// Rows of many non-zeros are summed at a stretch, and 5000 wavefronts of 1024 non-zeros hold more loads in flight than 8192 of 512: 60, 100,
+// 300 a row, 4M 20.9, 19.6, 18.0 and 22.6, 21.7, 19.8, 5M 24.6, 23.5, 21.3 and 26.8, 25.4, 23.0; but 1.5M 12.2, 11.4, 10.5 and 11.9, 11.3, 10.6.  Past
+// one round of wavefronts of either length the short ones draw level (8M 36.2, 34.6, 31.2 and 35.1, 34.4, 32.7, 50M 178, 170, 162 and 173, 163, 157).
+// Tables of a caller's P and of the row-aware cost have up to 1024.
 int64_t spmv_grain(int dtype, int64_t nnz, int64_t n_rows)
 {
     if (dtype == NACHO_F64) return kGrainF64;
     return nnz >= 1'400'000 && nnz >= 48 * n_rows ? kGrainF32 : kShortGrainF32;
 }
 
-// Small calls do without a partition kernel.  Its place in the stream (a launch and 3 us) is a third of what such a
-// call takes, while the wavefronts find their rows in two or three rounds of loads that hit the cache (40,000
-// non-zeros: 9.3 us in all; 1M: 16.8 to 15.4; 5M: 33.2 to 32.4).  Past a thousand partitions only while x fits an L2:
-// partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 309 to 469 us without).  With more
-// rows than the wavefronts can look after in one batch of loads each the partition kernel writes the zeros, a row a
-// thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).  The lines are in partitions of fp64 and of long ones of fp32; short
-// ones count half, whose search takes a larger share of a wavefront (with and without the partition kernel 31.6 and 31.0 us for 5M
-// non-zeros, 34.8 and 34.8 for 6M, 42.2 and 43.5 for 8M).
-bool spmv_whole(int dtype, int64_t grain, int64_t P, int64_t n_rows, int64_t x_bytes)
+// Small calls do without a partition kernel: its place in the stream (a launch and 3 us) is a third of what such a call takes, and the
+// wavefronts' search for their rows travels beside their non-zeros.  More than 1024 partitions only while x fits an L2, more than 4096 only where
+// it leaves most of one: partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 298 to 467 us without).  With and without
+// the partition kernel, us: doubles, x of 2.4 to 3.2 MB, 1.5M 22.7 and 21.2, 2M 26.6 and 25.5, 3M (5860 partitions) 30.0 and 28.7, 4M (7813) 35.9 and 36.5;
+// x of 4.8 MB, 3M 33.1 and 34.4; x of 0.7 and 2 MB, 5M (9766) 34.0, 37.5 and 32.1, 37.5; 8M (15625) 47.9 and 49.3.  Short partitions of floats count
+// half, whose search is a larger share of a wavefront; past 4096 of them the two forms are level while rows are few (20 a row, 2.6M 20.6 and 20.0, 3M 21.7
+// and 21.8, 6M 31.9 and 31.3) and the search loses where they are not (10 a row, 3M 23.6 and 24.1, 5M 31.7 and 34.1).  With more rows than the
+// wavefronts can look after in one batch of loads each the partition kernel writes the zeros, a row a thread (40,000 non-zeros in the first
+// 4096 of 131072 rows: 63 to 17 us).
+bool spmv_whole(int dtype, int64_t nnz, int64_t grain, int64_t P, int64_t n_rows, int64_t x_bytes)
 {
+    if (nnz == 0) return false;                        // (its wavefronts expect non-zeros)
     const bool halves = dtype == NACHO_F32 && grain < kGrainF32;
     const int64_t parts = halves ? (P + 1) / 2 : P;
-    return n_rows <= (1 << 17) && n_rows <= parts * kZeroRows && (parts <= 1024 || (parts <= (halves ? 5120 : 8192) && x_bytes <= (4 << 20)));
+    if (n_rows > parts * kZeroRows) return false;
+    if (parts <= 1024) return true;
+    if (P <= 4096) return x_bytes <= (4 << 20);
+    if (dtype == NACHO_F64) return P <= 10240 && x_bytes <= (5 << 19);
+    return n_rows <= (1 << 17) && parts <= (halves ? 5120 : 8192) && x_bytes <= (4 << 20);
 }
 
 hipError_t launch_spmv_exec(int dtype, const int32_t *pos, const int32_t *crd, const void *val,

@@ -167,3 +167,35 @@ def test_fused_search_in_execute_variant(dtype):
         assert np.all(got[np.diff(A["pos"]) == 0] == 0.0)
         plain = _run(A, x, 0)
         assert np.array_equal(got.view(np.uint8), plain.view(np.uint8)), tag
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n_rows,nnz", [
+    (1, 1), (63, 700), (64, 700), (65, 700), (4095, 1500), (4096, 9000), (4097, 9000), (140_000, 400_000), (262_145, 900_000)])
+def test_rows_found_beside_the_non_zeros(n_rows, nnz, dtype):
+    """Rows around the 64 probes of a search round and its second and third round, more rows than the first batches of
+    row positions hold (short rows, empty ones in between), and a last partition of a few non-zeros; the stored table is
+    Algorithm 1's."""
+    rng = np.random.default_rng(n_rows + nnz)
+    n_cols = 5000
+    lens = np.zeros(n_rows, np.int64)
+    some = np.sort(rng.choice(n_rows, max(1, n_rows - n_rows // 3), replace=False))
+    lens[some] = np.minimum(nnz // len(some) + rng.integers(0, 2, len(some)), n_cols)
+    lens[some[len(some) // 2]] = min(n_cols, max(1, nnz // 4))
+    pos = np.zeros(n_rows + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    total = int(pos[-1])
+    at = np.arange(total) - np.repeat(pos[:-1].astype(np.int64), lens)
+    crd = (at * n_cols // np.repeat(np.maximum(lens, 1), lens)).astype(np.int32)
+    A = {"n_rows": n_rows, "n_cols": n_cols, "pos": pos, "crd": crd, "val": rng.uniform(-1, 1, total).astype(dtype)}
+    x = rng.uniform(-1, 1, n_cols).astype(dtype)
+    for P in (0, 3):
+        _check(A, x, P, "rows")
+    op, code = csr_operand(A), nb.F64 if dtype == np.float64 else nb.F32
+    ws = torch.empty(nb.workspace_bytes(nb.OP_SPMV, [op], code), dtype=torch.uint8, device="cuda")
+    nb.nacho_spmv(op, dev(x), ws=ws)
+    t = nb.workspace_parts(nb.OP_SPMV, [op], code, ws)
+    queries = np.minimum(np.arange(t["P"] + 1, dtype=np.int64) * t["grain"], total)
+    ref = oracle.partition([oracle.csr(pos, crd, n_rows, n_cols)], t["P"], queries=queries)
+    for name in ("coord", "posn", "cost"):
+        assert np.array_equal(t[name].cpu().numpy().reshape(ref[name].shape), ref[name]), name
