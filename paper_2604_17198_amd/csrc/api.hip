@@ -896,7 +896,7 @@ static int32_t sparse_combine(bool multiply, const nacho_tensor *ops, int32_t k,
     if (rc != NACHO_OK) return rc;
     if (fmt == FMT_CSF3 && multiply) return NACHO_ERR_UNSUPPORTED;      // third-order tensors: partition and union
     // (the product of one operand is the operand: the union's pipeline copies it)
-    if (multiply && fmt == FMT_DCSR && k == 1) multiply = false;
+    if (multiply && k == 1) multiply = false;
     SpaddValues vals;
     std::memset(&vals, 0, sizeof(vals));
     for (int t = 0; t < k; ++t) {

@@ -207,6 +207,7 @@ struct Tile {
     int32_t block_before[kCsr ? S::kBlocks : 1];               // ... and how many its wavefront emits before it
     uint32_t wave_counts[kWaves], wave_slices[kWaves];         // emitted | row heads << 16; slice heads
     int32_t wave_before[kWaves];          // CSR: emitted by the wavefronts before
+    uint16_t behind[kWaves][kMaxRuns];    // products: order words of the places behind a wavefront's last one
     unsigned long long sval[kMaxRuns];    // address of the values of run t, biased: [staged word] is the entry's
     unsigned long long scol[kMaxRuns];    // the same for the columns (remapped operands)
     unsigned long long srow[kMaxRuns];    // coordinate lists: the same for the rows; remapped operands: start[t]
@@ -416,7 +417,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid / NACHO_WAVE);
-    const int k = arg_ptr->ops.k;              // <= K
+    // (launch_one.  Products and sums of CSR matrices know it: three CSR matrices of 5M entries in all 39.0 to 38.2 us; sums of vectors of four
+    // doubles and of tensors would spill)
+    const int k = K <= 4 && (kMul || (K > 2 && FMT == SPADD_CSR)) ? K : arg_ptr->ops.k;        // <= K
     const int p = (int)blockIdx.x;             // the partition of this workgroup, p < P
     KeyT *keys = w.keys;
     uint32_t *cols = reinterpret_cast<uint32_t *>(w.keys);                  // staged columns (32-bit keys: the keys)
@@ -1212,7 +1215,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     wave_sync();                               // (a wavefront's places are merged and marked by its own threads)
 
     // ---- the values: where an entry's is ---------------------------------------------------------
-    T val[R], tail = T(0);
+    // Products emit one place in k at most.  (launches for five and more operands: K = 8)
+    constexpr int kLeast = K <= 4 ? K : 5, NP = (R + kLeast - 1) / kLeast;     // (a wavefront's emitted places, in 64s)
+    T val[kMul ? NP : R], tail = T(0);
     // the value of the entry an order word names (byte offsets throughout: with two operands and values as long as the
     // keys the order word is the offset)
     auto value_at = [&](unsigned o) -> T {
@@ -1255,12 +1260,21 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         eq = in & ~e;
         eq_next = ((unsigned long long)(unsigned)lane_after((int)(eq >> 32), 0) << 32) | (unsigned)lane_after((int)(unsigned)eq, 0);
     };
+    // products: the order words of the wavefront's places and of those behind them
+    unsigned product_words[kMul ? R : 1], word_behind = 0u;
+    bool emits = false;                        // (uniform) the wavefront has something to emit
     if constexpr (kMul) {
         lds_barrier();                         // (whether the wavefront's last places are emitted hangs on the next ones)
         load_heads();
 #pragma unroll
         for (int g = 1; g < K; ++g)
             if (g < k) e &= shifted(eq, eq_next, g);
+        if (live < k || lane >= R) e = 0ull;
+        emits = __ballot(e != 0ull) != 0ull;
+        if (emits) {                           // (all operands have entries here, so the order words are in w.order)
+            orders(product_words);
+            word_behind = order_of(place0 + R * NACHO_WAVE + (lane < K ? lane : 0));
+        }
     } else if (!all_heads && lane < R) e = w.heads[block0 + lane] & in;
     if constexpr (kRowHeads) {
         if (lane < R) r = w.row_heads[block0 + lane] & in;
@@ -1324,8 +1338,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // sums: every place asks for its value, straight from the operands (64 places read one contiguous stretch per operand).
     // Not before the counts are published: asking takes one to ten microseconds where the memory pipeline is full, and everybody
     // behind this workgroup waits for them (three vectors, 11M entries: 71.0 to 68.6 us; two DCSR matrices of 20M: 175 to 168).
-    KeyT key[R];
-    if (!kMul && n > 0) {
+    KeyT key[kMul ? NP : R];
+    if constexpr (!kMul) if (n > 0) {
         unsigned o[R];
         orders(o);
         if (place0 + R * NACHO_WAVE > n) {         // (uniform: the wavefronts at the end)
@@ -1371,7 +1385,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             if (t >= k) break;
-            const int at = seg_pos[kWindow ? t : 0][row] - of(q_v, t), len = of(len_v, t);
+            // (products of more operands: the pointer read again, not held from the staging on in scalar registers that move through
+            // vector ones; five CSR matrices of 16M entries in all 104 to 101 us)
+            const int at = (kMul && K > 2 ? pos_of(t, D - 1) : seg_pos[kWindow ? t : 0])[row] - of(q_v, t), len = of(len_v, t);
             m += at < 0 ? 0 : (at < len ? at : len);
         }
         return m;
@@ -1383,21 +1399,13 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     }
 
     // ---- the keys of the output entries, and what else the sums and products need ----------------
-    // (products: the keys after the values, whose requests need the registers.  Past the last place: any words)
+    // (past the last place: any words)
     auto load_keys = [&]() {
-        if (K > 2 && __builtin_expect(far, 0)) {
+        if (__builtin_expect(far, 0)) {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const int m = place0 + j * NACHO_WAVE + lane;
                 key[j] = keys[w.order[m < n ? m : n - 1] & 0x1fff];
-            }
-        } else if (K <= 2 && moved) {
-            unsigned o[R];
-            orders(o);
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int m = place0 + j * NACHO_WAVE + lane;
-                key[j] = *reinterpret_cast<const KeyT *>(kb + (m < n ? o[j] : 0u));
             }
         } else {
             const KeyT *first = keys + mb + place0 + lane;
@@ -1405,95 +1413,104 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             for (int j = 0; j < R; ++j) key[j] = first[j * NACHO_WAVE];
         }
     };
-    if (n > 0) {
-        if constexpr (!kMul && K > 2) load_keys();
-        if constexpr (kMul) {
-            // products: few places are emitted; those ask for the values of all operands, as many places at a time as there are
-            // registers for beside the products
-            constexpr int kBatch = sizeof(T) == 8 ? (R + 1) / 2 : R;
-            const unsigned last_row = kMapped ? (unsigned)row_extent() - 1u : 0u;      // (operands that are not sorted can name any)
-            // the staged word of place m, its operand and, remapped operands, the row it lies in
-            auto entry_of = [&](int m, int &t, unsigned &row) -> int {
-                const int s = word_of(order_of(m), t);
-                row = kMapped ? min((unsigned)row0 + (unsigned)row_field(keys[K <= 2 || far ? s : mb + m]), last_row) : 0u;
-                return s;
-            };
-            // Two remapped operands, in stages -- order words, where the rows are stored, values --, each for the whole batch: place
-            // after place, every one waits for two round trips to memory, eighteen in a row (two DCSR matrices of 20M: 151.3 to 141.2 us).
-            // With more operands fewer places are emitted, and asking for the rows of the others costs more than the waits: three, four and five matrices of
-            // 16M entries in all, 20 a row, staged 90.9, 87.1, 92.2 us, like this 88.9, 83.4, 87.2; with nearly all entries common 94.4, 96.1, 105.1
-            // and 89.7, 96.9, 102.0 (doubles; floats of four 75.3 and 79.1 for 8M, of five 87.4 and 88.6, which did take 82.2 and 93.3 before).
-            constexpr bool kStaged = kMapped && K <= 2;
-            auto load_values = [&](int g, int j0, T (&to)[R]) {
-                const int m0 = place0 + lane + g;
-                int at[kBatch], a[kBatch], b[kBatch];      // (the operand above the staged word)
+    // Products.  Few places are emitted, one in k at most and often one in ten, so the wavefront's emitted ones are moved together
+    // first: the k places of an emitted entry hold the operands' entries in operand order, and behind each other the
+    // order words of all such places are records of k words, one a lane.  What an output entry takes -- rows, addresses, values,
+    // stores -- is then done once per 64 of them and not for every place (two DCSR matrices of 20M, one place in ten emitted: 135.8 to 112.8 us,
+    // 130 to 85 vector instructions a place; two vectors of 8M with nearly all coordinates in both 62.3 to 52.0; two CSR matrices of 2.5M
+    // 28.9 to 27.1).
+    const int emitted = kMul ? of(wave_incl, NACHO_WAVE - 1) & 0xffff : 0;
+    uint16_t *const records = w.order + (K <= 2 ? 0 : mb) + place0;
+    int words_here = 0;                        // words of the records that lie in the wavefront's own places; the rest is in w.behind
+    auto record = [&](int i, int g) -> int {   // the staged word of the g-th operand's entry of output entry i
+        const int at = i * k + g;
+        const unsigned o = *(at < words_here ? records + at : &w.behind[wave][at - words_here]);
+        return K <= 2 ? (int)(o / KB) : (int)(o & 0x1fffu);
+    };
+    if constexpr (kMul) {
+        if (emits) {
+            const unsigned long long before = (unsigned long long)(unsigned)lane_before((int)(e >> 32), 0) << 32 |
+                                              (unsigned)lane_before((int)(unsigned)e, 0);
+            unsigned long long members = e;
 #pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    if (j0 + i >= R) continue;
-                    // (every place names an entry and its row: no branches between the loads)
-                    int t;
-                    unsigned row;
-                    const int m = m0 + (j0 + i) * NACHO_WAVE, s = entry_of(m < n ? m : n - 1, t, row);
-                    at[i] = t << 16 | s;
-                    a[i] = global_ptr<int32_t>(w.srow[t])[row];
-                    b[i] = global_ptr<int32_t>(w.spos[t])[row];
-                }
-                __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0): known to the compiler, which else waits at every branch below
+            for (int g = 1; g < K; ++g)
+                if (g < k) members |= e << g | before >> (64 - g);
+            if (lane >= R) members = 0ull;
+            const int count = __popcll(members), incl = dpp_scan_add(count);
+            words_here = of(incl, NACHO_WAVE - 1);
+            KeyT head_key[K > 2 ? R : 1];
+            if (K > 2 && !far) {
 #pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    if (j0 + i >= R) continue;
-                    to[j0 + i] = T(0);
-                    if (my_bit(lane_word(e, j0 + i)))
-                        to[j0 + i] = global_ptr<T>(w.sval[at[i] >> 16])[(at[i] & 0xffff) + (a[i] - b[i])];
-                }
-            };
-            auto load_value = [&](int m) -> T {
-                if constexpr (kMapped) {
-                    int t;
-                    unsigned row;
-                    const int s = entry_of(m, t, row);
-                    const int sh = global_ptr<int32_t>(w.srow[t])[row] - global_ptr<int32_t>(w.spos[t])[row];
-                    return global_ptr<T>(w.sval[t])[s + sh];
-                } else return value_at(order_of(m));
-            };
-            if (kStaged) {
-                if (__ballot(e != 0ull && lane < R) != 0ull) {
+                for (int j = 0; j < R; ++j) head_key[j] = keys[mb + place0 + j * NACHO_WAVE + lane];
+            }
 #pragma unroll
-                    for (int j0 = 0; j0 < R; j0 += kBatch) load_values(0, j0, val);
-#pragma unroll 1
-                    for (int g = 1; g < k; ++g) {
-#pragma unroll
-                        for (int j0 = 0; j0 < R; j0 += kBatch) {
-                            T more[R];
-                            load_values(g, j0, more);
-#pragma unroll
-                            for (int j = j0; j < j0 + kBatch && j < R; ++j) val[j] *= more[j];
-                        }
-                    }
-                }
-            } else if (__ballot(e != 0ull && lane < R) != 0ull) {
+            for (int j = 0; j < R; ++j) {
+                const unsigned long long mj = lane_word(members, j);
+                if (my_bit(mj)) records[of(incl - count, j) + lanes_below(mj)] = (uint16_t)product_words[j];
+            }
+            if (K > 2 && !far) {               // (more than two operands: the merge moved the keys, and these go where the entries go)
 #pragma unroll
                 for (int j = 0; j < R; ++j) {
-                    val[j] = T(0);
-                    if (my_bit(lane_word(e, j))) val[j] = load_value(place0 + j * NACHO_WAVE + lane);
-                }
-#pragma unroll 1
-                for (int g = 1; g < k; ++g) {
-#pragma unroll
-                    for (int j0 = 0; j0 < R; j0 += kBatch) {
-                        T more[kBatch];
-#pragma unroll
-                        for (int j = j0; j < j0 + kBatch && j < R; ++j) {
-                            more[j - j0] = T(1);
-                            if (my_bit(lane_word(e, j))) more[j - j0] = load_value(place0 + j * NACHO_WAVE + lane + g);
-                        }
-#pragma unroll
-                        for (int j = j0; j < j0 + kBatch && j < R; ++j) val[j] *= more[j - j0];
-                    }
+                    const unsigned long long ej = lane_word(e, j);
+                    if (my_bit(ej)) keys[mb + place0 + (of(wave_incl - block_counts, j) & 0xffff) + lanes_below(ej)] = head_key[j];
                 }
             }
-            if constexpr (!kMapped) load_keys();
-        } else {
+            if (lane < K) w.behind[wave][lane] = (uint16_t)word_behind;
+            wave_sync();
+            // kBatch output entries a lane at a time
+            auto multiply = [&](auto batch_tag) {
+                constexpr int kBatch = decltype(batch_tag)::value, kGroup = K <= 4 ? K : 4;
+                const unsigned last_row = kMapped ? (unsigned)row_extent() - 1u : 0u;      // (operands that are not sorted can name any)
+                // (read from their lanes afresh: the scalar registers are not held from the start for this)
+                int firsts_v = sb_v, starts_v = q_v, lengths_v = len_v;
+                asm volatile("" : "+v"(firsts_v), "+v"(starts_v), "+v"(lengths_v));
+                int entry[kBatch];
+                unsigned row[kBatch];
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    const int x = i * NACHO_WAVE + lane;
+                    entry[i] = x < emitted ? x : emitted - 1;
+                    key[i] = K <= 2 || far ? keys[record(entry[i], 0)] : keys[mb + place0 + entry[i]];
+                    row[i] = kMapped ? min((unsigned)row0 + (unsigned)row_field(key[i]), last_row) : 0u;
+                }
+#pragma unroll
+                for (int g0 = 0; g0 < K; g0 += kGroup) {
+                    int at[kGroup][kBatch];
+                    T v[kGroup][kBatch];
+#pragma unroll
+                    for (int g = g0; g < g0 + kGroup; ++g)
+                        if (g < k) {
+                            const int first = of(firsts_v, g), final = first + of(lengths_v, g) - 1;
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i) {
+                                // (of the operand for sure: repeated coordinates can put another's entry here)
+                                at[g - g0][i] = max(first, min(record(entry[i], g), final)) + (of(starts_v, g) - first);
+                                if constexpr (kMapped)
+                                    at[g - g0][i] += ints(arg_ptr->ops.start[g])[row[i]] - pos_of(g, 1)[row[i]];
+                            }
+                        }
+#pragma unroll
+                    for (int g = g0; g < g0 + kGroup; ++g)
+                        if (g < k) {
+                            const NACHO_GLOBAL T *values = global_ptr<T>((unsigned long long)(uintptr_t)arg_ptr->vals.v[g]);
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i) v[g - g0][i] = values[at[g - g0][i]];
+                        }
+#pragma unroll
+                    for (int g = g0; g < g0 + kGroup; ++g)
+                        if (g < k) {
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i) val[i] = g == 0 ? v[g - g0][i] : val[i] * v[g - g0][i];
+                        }
+                }
+            };
+            if (emitted <= NACHO_WAVE) multiply(std::integral_constant<int, 1>());
+            else multiply(std::integral_constant<int, NP>());
+        }
+    }
+    if constexpr (!kMul) if (n > 0) {
+        if constexpr (K > 2) load_keys();
+        {
             // sums: the equal keys behind a head belong to the lanes after it, in operand order
             load_heads();
             unsigned long long x = e;          // the heads with g equal keys behind them
@@ -1640,9 +1657,31 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     const Out top_crd = kCsf ? out_at(out.crd0, at_slices) : nullptr;
     const Out top_pos = kCsf ? out_at(out.pos1, at_slices) : nullptr;
     int at = wave_before & 0xffff, at_row = wave_before >> 16, at_slice = slices_before;
-    // (remapped operands: no registers for the keys before this)
-    if constexpr (kMapped)
-        if (n > 0) load_keys();
+    if constexpr (kMul) {
+        if (kInstrument) {
+            const int left = n - place0;
+            logged_items += left >= R * NACHO_WAVE ? R * NACHO_WAVE : (left > 0 ? left : 0);
+        }
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            if (j * NACHO_WAVE >= emitted) break;      // (uniform)
+            const int x = j * NACHO_WAVE + lane, loc = at + x;
+            if (x < emitted && (!tight || loc < room)) {
+                store(crd_out, (unsigned)loc, (int32_t)(D == 1 ? (uint32_t)key[j] : (uint32_t)(key[j] & col_mask)));
+                if (kCoo) store(row_out, (unsigned)loc, row0 + (int32_t)(uint32_t)row_field(key[j]));
+                store(val_out, (unsigned)loc, val[j]);
+            }
+        }
+        if constexpr (D >= 2)
+            if (__builtin_expect(far, 0)) {
+                // (uniform, rare) the columns, whose lower bits the keys lack
+#pragma unroll 1
+                for (int x = lane; x < emitted; x += NACHO_WAVE) {
+                    const int s = record(x, 0), col = column_at(0, s, row_field(keys[s]));
+                    if (at + x < room) store(crd_out, (unsigned)(at + x), (int32_t)col);
+                }
+            }
+    } else
 #pragma unroll
     for (int j = 0; j < R; ++j) {
         const unsigned long long ej = lane_word(e, j);
@@ -1651,7 +1690,6 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             logged_items += left >= NACHO_WAVE ? NACHO_WAVE : (left > 0 ? left : 0);
             if (kRowHeads) logged_rows += (uint32_t)__popcll(lane_word(r, j));
         }
-        if (kMul && ej == 0ull) continue;      // (uniform)
         const unsigned loc = (unsigned)(at + lanes_below(ej));
         unsigned long long stored = ej;
         if (__builtin_expect(tight, 0)) stored &= __ballot((int)loc < room);
@@ -1684,7 +1722,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
         at += __popcll(ej);
     }
-    if constexpr (D >= 2)
+    if constexpr (D >= 2 && !kMul)
         if (__builtin_expect(far, 0)) {
             // (uniform, rare) the columns, whose lower bits the keys lack
             at = wave_before & 0xffff;

@@ -117,3 +117,37 @@ def test_csr_hadamard_powerlaw_full_size():
     cfg = workloads.csr_add_config(2)
     mats = [{"pos": m["pos"], "crd": m["crd"], "val": m["val"]} for m in cfg["ops"]]
     check_csr(mats, (cfg["n_rows"], cfg["n_cols"]), 0, "powerlaw 100k")
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 8])
+@pytest.mark.parametrize("common", [1, 95, 96, 97, 704, 2000, 30_000])
+def test_equal_entries_lie_across_wavefronts(k, common):
+    """Coordinates that all operands store, some more of the first operand's before them so that the places of one entry
+    lie on both sides of a wavefront's (192 to 704 places) and of a block's last one, and every second entry
+    missing somewhere; also cut off by the capacity."""
+    rng = np.random.default_rng(k + common)
+    for dtype, lead, every in ((np.float32, 0, 1), (np.float64, 1, 1), (np.float32, k - 1, 1), (np.float64, 2, 2)):
+        base = np.arange(common, dtype=np.int32) * 3 + 1000
+        vs = [np.concatenate([np.arange(lead, dtype=np.int32), base])]
+        vs += [base.copy() for _ in range(k - 2)]
+        vs.append(base[::every].copy())
+        vals = [rng.uniform(0.5, 1.5, len(v)).astype(dtype) for v in vs]
+        extent = int(base[-1]) + 7
+        check_vec(vs, vals, extent, 0, f"across lead={lead} every={every}")
+        n_rows, n_cols = 1 + extent // 50, 50
+        mats = []
+        for v, val in zip(vs, vals):
+            pos, crd = to_csr(np.stack([v // n_cols, v % n_cols], 1).astype(np.int64), n_rows)
+            mats.append({"pos": pos, "crd": crd, "val": val})
+        check_csr(mats, (n_rows, n_cols), 0, f"across lead={lead} every={every}")
+    ref = oracle.spmul_vec(vs, vals)
+    n = ref[0].shape[0]
+    cap = n - n // 3 - 1
+    ops = [nb.vector(dev(i), extent, dev(v)) for i, v in zip(vs, vals)]
+    out = nb.SparseOut("vector", 0, max(cap, 0), dev(vals[0]).dtype, "cuda")
+    out.crd1.fill_(-5)
+    nb.nacho_spmul_k(ops, out)
+    rows, nnz, status = _finish(out)
+    assert status == (-4 if cap < n else 0) and nnz == n
+    got = out.crd1.cpu().numpy()
+    assert np.array_equal(got[:cap], ref[0][:cap]) and (got[cap:] == -5).all()
