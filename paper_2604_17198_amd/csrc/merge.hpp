@@ -173,9 +173,31 @@ __device__ inline unsigned long long lane_word(unsigned long long v, int from)
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), from);
     return ((unsigned long long)hi << 32) | lo;
 }
+// The value of the next lane (the last one: of b's first lane); of lane `from`.
+__device__ inline int next_lane(int a, int b) { return lane_after(a, __builtin_amdgcn_readlane(b, 0)); }
+__device__ inline float next_lane(float a, float b) { return __int_as_float(next_lane(__float_as_int(a), __float_as_int(b))); }
+__device__ inline double next_lane(double a, double b)
+{
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    return __longlong_as_double((long long)next_lane((int)(x >> 32), (int)(y >> 32)) << 32 | (unsigned)next_lane((int)(unsigned)x, (int)(unsigned)y));
+}
+__device__ inline int lane_at(int v, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, v); }
+__device__ inline float lane_at(float v, int from) { return __int_as_float(lane_at(__float_as_int(v), from)); }
+__device__ inline double lane_at(double v, int from)
+{
+    const long long x = __double_as_longlong(v);
+    return __longlong_as_double((long long)lane_at((int)(x >> 32), from) << 32 | (unsigned)lane_at((int)(unsigned)x, from));
+}
 __device__ inline int lanes_below(unsigned long long mask)     // set bits of the mask below this lane
 {
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+// Leading zeros of a word; none set: all ones (the instruction's own answer, for which the compiler would add a comparison and a choice).
+__device__ inline uint32_t leading_zeros(uint32_t v)
+{
+    uint32_t n;
+    asm("v_ffbh_u32 %0, %1" : "=v"(n) : "v"(v));
+    return n;
 }
 // This lane's bit of a mask every lane agrees on.
 __device__ inline bool my_bit(unsigned long long mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
@@ -277,8 +299,9 @@ __device__ __forceinline__ void merge_share(const char *kb, int sx, int nx, int 
         if (j + 2 < IPT) nk = *reinterpret_cast<const KeyT *>(kb + src + 2 * KB);
         emit(j, src, tx, key, prev);
         prev = key;
-        xi += tx ? KB : 0;
-        yi += tx ? 0 : KB;
+        const int next = src + KB;
+        xi = tx ? next : xi;
+        yi = tx ? yi : next;
         xk = tx ? xn : xk;
         yk = tx ? yk : yn;
         xn = tx ? nk : xn;
@@ -572,24 +595,26 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // the entries: one round trip to memory; fibres of a tensor, which are many: of the first 1024 or 1536)
     constexpr int kAhead = !kCsf ? 1 : (kSize == MERGE_SHORT ? (K <= 2 ? 2 : 1) : (K <= 2 ? 3 : (K <= 4 ? 2 : 1)));
     int seg_a[kWindow ? K : 1][kAhead], seg_b[kWindow ? K : 1][kAhead], seg_id[kWindow ? K : 1][kAhead];
-    // segment i of run t: the positions of its entries and its row (CSF: j of the fibre; remapped operands: where
-    // its entries are stored)
+    // segment i of run t, counted from the partition's first: the positions of its entries and its row (CSF: j of the fibre; remapped
+    // operands: where its entries are stored).  (The first one's address is the same in all lanes: the loads take an offset each.)
     auto load_segment = [&](int t, int i, int &a, int &b, int &id) {
         if constexpr (kWindow) {
-            a = seg_pos[t][i];
-            b = seg_pos[t][i + 1];
-            id = FMT == SPADD_CSR && !kMapped ? i : seg_crd[t][i];
+            const Ints pos = seg_pos[t] + of(ilo_v, t), crd = seg_crd[t] + of(ilo_v, t);
+            a = pos[(unsigned)i];
+            b = pos[(unsigned)i + 1u];
+            if constexpr (FMT != SPADD_CSR || kMapped) id = crd[(unsigned)i];
         }
     };
     if constexpr (kWindow) {
 #pragma unroll
-        for (int t = 0; t < K; ++t)
+        for (int t = 0; t < K; ++t) {
+            const int segments = of(ihi_v, t) - of(ilo_v, t);
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
                 seg_a[t][u] = seg_b[t][u] = seg_id[t][u] = 0;
-                const int i = of(ilo_v, t) + u * kThreads + tid;
-                if (i < of(ihi_v, t)) load_segment(t, i, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
+                if (u * kThreads + tid < segments) load_segment(t, u * kThreads + tid, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
             }
+        }
     }
     if constexpr (kSlicesAhead) {
 #pragma unroll
@@ -692,7 +717,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             // stays the largest number) and the one before the block
             const uint32_t lo = (uint32_t)x & upto_lo, hi = (uint32_t)(x >> 32) & upto_hi;
             const int end = word0 + j * NACHO_WAVE + NACHO_WAVE - 1;
-            const uint32_t from_hi = hi ? (uint32_t)__builtin_clz(hi) : ~0u, from_lo = (lo ? (uint32_t)__builtin_clz(lo) : ~0u) | 32u;
+            const uint32_t from_hi = leading_zeros(hi), from_lo = leading_zeros(lo) | 32u;
             e = end - (int)min(min(from_hi, from_lo), (uint32_t)(end - latest));
             latest = end - __clzll((long long)x);
         }
@@ -728,7 +753,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     // Does this partition (the next one) start inside a row, i.e. does some operand hold an
                     // entry of the boundary's row before the boundary?  Then that row's first output entry
                     // belongs to an earlier partition.  The boundary's row is the first (last) segment.
-                    const int i = i_lo + tid, a0 = seg_a[t][0], id0 = seg_id[t][0];
+                    const int a0 = seg_a[t][0], id0 = seg_id[t][0];
                     if constexpr (kCsf) {
                         const int i0 = of(up_lo_v, t);
                         if (i_lo < i_hi && i0 < level_count(t, 0) && up_first == row0) {       // (uniform)
@@ -736,29 +761,30 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                             const int f1 = kSlicesAhead ? of(fibre_end_v, t) : pos1[i0 + 1];
                             const int f0 = kSlicesAhead ? 0 : pos1[i0], begin = kSlicesAhead ? of(begin_v, t) : 0;
                             if (tid == 0) {
-                                if (i < f1 && id0 == table_coord(p, 1) && q > a0) w.cont = 1u;
+                                if (i_lo < f1 && id0 == table_coord(p, 1) && q > a0) w.cont = 1u;
                                 if (q > (kSlicesAhead ? begin : seg_pos[t][f0])) w.cont_slice = 1u;
                             }
                         }
-                    } else if (tid == 0 && i < i_hi && (FMT == SPADD_CSR || id0 == row0) && q > a0) w.cont = 1u;
+                    } else if (tid == 0 && i_lo < i_hi && (FMT == SPADD_CSR || id0 == row0) && q > a0) w.cont = 1u;
                     if (FMT == SPADD_CSR) {
                         const int i_next = of(next_seg_v, t);
                         if (i_next < i_hi) {                       // (uniform)
-                            if (i_next < i_lo + kThreads) { if (i == i_next && q + len > a0) w.cont_next = 1u; }
+                            if (i_next < i_lo + kThreads) { if (tid == i_next - i_lo && q + len > a0) w.cont_next = 1u; }
                             else if (tid == 0 && q + len > seg_pos[t][i_next]) w.cont_next = 1u;
                         }
                     }
                 }
                 if (len == 0) continue;
                 constexpr int kMore = !kCsf && kSize != MERGE_SHORT && K <= 4 ? 8 : 4;      // segments a thread has in flight (registers)
-                auto mark_segment = [&](int i, int a, int b, int id) {
+                auto mark_segment = [&](int r, int a, int b, int id) {       // (segment i_lo + r)
                     const int s = a > q ? a : q;
                     if (b <= s || s >= q + len) return;            // nothing of it lies in the partition
-                    int up = FMT == SPADD_CSR ? i : id;            // row, or slice of the fibre
+                    uint32_t up;                                   // row, or slice of the fibre, counted from row0
                     KeyT field;
                     if constexpr (kCsf) {
-                        up = i < second_at ? up_first : up_last;
+                        up = (uint32_t)((r < second_at - i_lo ? up_first : up_last) - row0);
                         if (many) {                                // (uniform)
+                            const int i = i_lo + r;
                             const Ints pos1 = pos_of(t, 1);
                             int lo = up_lo, hi = of(up_hi_v, t);
                             while (lo < hi) {                      // the last slice that starts at or before fibre i,
@@ -774,31 +800,34 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
                                 for (int g = 0; g < 3; ++g) lo = first[g] <= i ? at[g] : lo;
                             }
-                            up = crd_of(t, 0)[lo];
+                            up = (uint32_t)(crd_of(t, 0)[lo] - row0);
                         }
-                        field = ((KeyT)(uint32_t)(up - row0) << jb) | (KeyT)(uint32_t)id;
-                    } else field = (KeyT)(uint32_t)(up - row0);
-                    const int at = sb + s - q;
+                        field = ((KeyT)up << jb) | (KeyT)(uint32_t)id;
+                    } else {
+                        up = FMT == SPADD_CSR ? (uint32_t)(r + (i_lo - row0)) : (uint32_t)(id - row0);
+                        field = (KeyT)up;
+                    }
+                    const int at = s + (sb - q);
                     mark_start(at, field);
-                    // (remapped operands: how far the row is stored from where it is counted)
-                    if (kMapped) cols[at] = (uint32_t)(id - a);
-                    if ((uint32_t)(up - row0) >= limit) {
+                    // (remapped operands: how far the row is stored from where it is counted; two of them: from its staged words)
+                    if (kMapped) cols[at] = (uint32_t)(id - a + (K <= 2 ? q - sb : 0));
+                    if (up >= limit) {
                         // past the key: the whole field over the column, and a mark that no other field has
                         w.overflow = 1u;
                         if (!kWide || kCsf) w.order[at] = kPastKey;
                         if (!kWide) cols[at] = (uint32_t)field;
-                        else if (kCsf) { cols[at] = (uint32_t)(up - row0); wide_rows[at] = (uint32_t)id; }
+                        else if (kCsf) { cols[at] = up; wide_rows[at] = (uint32_t)id; }
                     }
                 };
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u)
-                    mark_segment(i_lo + u * kThreads + tid, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
-                for (int i = i_lo + tid + kAhead * kThreads; i < i_hi; i += kThreads * kMore) {
+                    mark_segment(u * kThreads + tid, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
+                for (int i = tid + kAhead * kThreads; i < i_hi - i_lo; i += kThreads * kMore) {
                     int a[kMore], b[kMore], id[kMore];
 #pragma unroll
                     for (int u = 0; u < kMore; ++u) {
                         a[u] = b[u] = id[u] = 0;
-                        if (i + u * kThreads < i_hi) load_segment(t, i + u * kThreads, a[u], b[u], id[u]);
+                        if (i + u * kThreads < i_hi - i_lo) load_segment(t, i + u * kThreads, a[u], b[u], id[u]);
                     }
 #pragma unroll
                     for (int u = 0; u < kMore; ++u) mark_segment(i + u * kThreads, a[u], b[u], id[u]);
@@ -863,7 +892,23 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 for (int j = 0; j < R; ++j) e[j] = start_of(j);
 #pragma unroll
                 for (int j = 0; j < R; ++j) key[j] = field_at(e[j]) << cb;
-                if constexpr (kMapped) {
+                if constexpr (kMapped && K <= 2) {
+                    // the words of the columns hold the rows' shifts so far.  A word without an entry asks for some column of its
+                    // operand: its row field alone is past every entry's
+                    const int second = of(sb_v, 1);
+                    const Ints crd0 = crd_of(0, D - 1), crd1 = crd_of(K - 1, D - 1);
+                    const unsigned last0 = (unsigned)arg_ptr->ops.lvl[0][D - 1].count - 1u, last1 = (unsigned)arg_ptr->ops.lvl[K - 1][D - 1].count - 1u;
+                    uint32_t c[R];
+#pragma unroll
+                    for (int j = 0; j < R; ++j) {
+                        const int at = word0 + j * NACHO_WAVE + lane;
+                        const unsigned to = (unsigned)(at + (int)cols[e[j]]);
+                        const Ints crd = at >= second ? crd1 : crd0;
+                        c[j] = (uint32_t)crd[min(to, at >= second ? last1 : last0)];
+                    }
+#pragma unroll
+                    for (int j = 0; j < R; ++j) key[j] |= (KeyT)c[j];
+                } else if constexpr (kMapped) {
                     // the words of the columns hold the rows' shifts so far
                     uint32_t c[R];
 #pragma unroll
@@ -1074,6 +1119,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         if constexpr (kCsf) put_bits(w.slice_heads, sm);
     };
     auto compare = [&](KeyT key, KeyT prev, uint32_t &hm, uint32_t &rm, uint32_t &sm) {
+        // (comparison and addition with carry in inline assembly takes an instruction less a bit, but ties them to places between the others:
+        // two vectors of 10M 77.9 to 80.8 us)
         if constexpr (!kRowHeads) hm += hm + (key != prev ? 1u : 0u);
         else {
             const KeyT diff = key ^ prev;
@@ -1130,6 +1177,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             const bool final_round = 2 * s == NR;
             int t_base = 0, steps = 0;
             int msx = 4, mnx = 0, msy = 4, mny = 0, md0 = -1, mox = 0, moy = 0;
+            const bool carried = s > 1;        // (the entries' order words are in place; before, a staged word names itself)
 #pragma unroll
             for (int g = 0; g < NR; g += 2 * s) {
                 const int nx = rn[g], ny = rn[g + s];
@@ -1141,11 +1189,14 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     if (tid >= t_base && tid < t_base + tg) {
                         msx = rs[g]; mnx = nx; msy = rs[g + s]; mny = ny;
                         md0 = (tid - t_base) * R;
-                        // an entry still at its staged word names itself; a merged one carries its order word
-                        mox = ro[g] < 0 ? 0x10000 : ro[g] << 13;
-                        moy = ro[g + s] < 0 ? 0x10000 : ro[g + s] << 13;
+                        mox = carried ? 0 : ro[g] << 13;
+                        moy = carried ? 0 : ro[g + s] << 13;
                     }
                     t_base += tg;
+                } else if (!carried && live > 1) {
+                    // a run without a partner in the first round: its order words, so that every later round finds them in place
+                    const int first = nx > 0 ? rs[g] : rs[g + s], own = (nx > 0 ? ro[g] : ro[g + s]) << 13;
+                    for (int i = first + tid; i < first + nx + ny; i += kThreads) w.order[i] = (uint16_t)(own | i);
                 }
             }
             if (t_base > 0) {                  // (uniform) some pair has two non-empty sides
@@ -1156,10 +1207,8 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     merge_share<KeyT, R>(kb, msx, mnx, msy, mny, md0, steps,
                                          [&](int j, int src, bool tx, KeyT key, KeyT prev) {
                         mk[j] = key;
-                        const uint32_t own = tx ? mox : moy;
                         const uint32_t at = (uint32_t)src / KB;
-                        const uint32_t carried = w.order[at];
-                        const uint32_t o = own & 0x10000u ? carried : (own | at);
+                        const uint32_t o = carried ? (uint32_t)w.order[at] : ((uint32_t)(tx ? mox : moy) | at);
                         mo[j / 2] = j & 1 ? mo[j / 2] | o << 16 : o;
                         if (final_round) compare(key, prev, hm, rm, sm);
                     });
@@ -1178,11 +1227,11 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 }
                 if (final_round) marked = true;
                 else lds_barrier();
-            }
+            } else if (!carried && live > 1) lds_barrier();        // (the order words just written)
 #pragma unroll
             for (int g = 0; g < NR; g += 2 * s) {
                 if (rn[g] == 0) { rs[g] = rs[g + s]; ro[g] = ro[g + s]; }
-                else if (rn[g + s] > 0) ro[g] = -1;
+                if (live > 1) ro[g] = -1;
                 rn[g] += rn[g + s];
             }
         }
@@ -1528,8 +1577,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                 for (int j = 0; j < R; ++j) {
                     const unsigned long long xj = lane_word(x, j);
                     if (xj == 0ull) continue;  // (uniform)
+                    asm volatile("");          // (a branch it stays: all of them without one need too many registers)
                     const T a = val[j], b = j + 1 < R ? val[j + 1 < R ? j + 1 : j] : tail;
-                    const T from = __shfl(lane < g ? b : a, (lane + g) & (NACHO_WAVE - 1), NACHO_WAVE);
+                    const T from = K <= 2 && sizeof(T) == 4 ? next_lane(a, b) : lane_at(lane < g ? b : a, (lane + g) & (NACHO_WAVE - 1));
                     val[j] = my_bit(xj) ? val[j] + from : val[j];       // (a head is nobody's equal key)
                 }
             }
@@ -1657,6 +1707,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     const Out top_crd = kCsf ? out_at(out.crd0, at_slices) : nullptr;
     const Out top_pos = kCsf ? out_at(out.pos1, at_slices) : nullptr;
     int at = wave_before & 0xffff, at_row = wave_before >> 16, at_slice = slices_before;
+    const bool slices = kCsf && __ballot(lane < R && sl != 0ull) != 0ull;      // (few wavefronts' places start one)
     if constexpr (kMul) {
         if (kInstrument) {
             const int left = n - place0;
@@ -1708,7 +1759,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     store(seg_crd_out, rloc, kCsf ? (int32_t)(uint32_t)(field & ((KeyT(1) << jb) - KeyT(1))) : row0 + (int32_t)(uint32_t)field);
                     store(seg_pos_out, rloc, at_nnz + (int)loc);
                 }
-                if constexpr (kCsf) {
+                if (kCsf && slices) {
                     const unsigned long long sj = lane_word(sl, j);
                     const unsigned sloc = (unsigned)(at_slice + lanes_below(sj));
                     if (my_bit(sj) && (int)sloc < room_slices) {
