@@ -104,9 +104,11 @@ __host__ __device__ inline int64_t whole_rounds(int64_t need, int64_t round)
 // tensor the row field is (i - i0) << jb | j.  Rows (slices) count from the partition's first one and a key tells
 // `limit` of them apart.  `wide`: 64-bit keys.  `size`: how many places of the merged order a thread owns (MergeSize).
 enum MergeSize : int { MERGE_LONG, MERGE_SHORT, MERGE_MIDDLE };
+// `touch`: the lines of the values are asked for beside the merge (kernels that can).
 struct MergeFields {
     int32_t cb, jb, wide, size;
     uint32_t limit;
+    int32_t touch;
 };
 // `k` operands; `rows`, `cols`, `depth`: the extents of the levels; `total`: stored entries of all operands; `units`: compute units;
 // `mapped`: remapped operands.

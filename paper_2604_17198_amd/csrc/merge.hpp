@@ -1096,6 +1096,28 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
         }
     };
 
+    // Sums of two and three coordinate lists and tensors (where merge_fields says so): a word of every line of the values is asked for beside the
+    // merge, so that the lines are on their way from memory before the places ask for them.
+    constexpr bool kTouch = !kMul && (kCoo || kCsf) && K <= 3;
+    int touched[kTouch ? K : 1];
+    if constexpr (kTouch) {
+        const bool touch = arg_ptr->fields.touch != 0;
+        int from = 0;                          // (the threads are shared out over the operands' lines)
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            touched[t] = 0;
+            const int len = touch ? of(len_v, t) : 0;
+            if (len == 0) continue;
+            constexpr int kLine = 128 / (int)sizeof(T);
+            const int q = of(q_v, t), lines = (int)((unsigned)(q + len - 1) / kLine - (unsigned)q / kLine) + 1;
+            int i = tid - from;
+            i += i < 0 ? kThreads : 0;
+            const int at = i * kLine < len ? i * kLine : len - 1;
+            if (i < lines) touched[t] = reinterpret_cast<const NACHO_GLOBAL int *>(global_ptr<T>((unsigned long long)(uintptr_t)arg_ptr->vals.v[t]) + q)[at * (int)(sizeof(T) / 4)];
+            from = (from + lines) & (kThreads - 1);
+        }
+    }
+
     // ---- 2. merge: adjacent runs pairwise, in rounds ------------------------------
     // (all of this is uniform over the workgroup except the thread's own share)
     const char *kb = reinterpret_cast<const char *>(w.keys);
@@ -1388,6 +1410,10 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // Not before the counts are published: asking takes one to ten microseconds where the memory pipeline is full, and everybody
     // behind this workgroup waits for them (three vectors, 11M entries: 71.0 to 68.6 us; two DCSR matrices of 20M: 175 to 168).
     KeyT key[kMul ? NP : R];
+    if constexpr (kTouch) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) asm volatile("" ::"v"(touched[t]));        // (nobody's words, but the loads have to stay)
+    }
     if constexpr (!kMul) if (n > 0) {
         unsigned o[R];
         orders(o);

@@ -568,3 +568,19 @@ def test_the_stream_of_a_call_is_torchs_current_one():
     for stream in (torch.cuda.default_stream(), torch.cuda.Stream(), torch.cuda.Stream()):
         with torch.cuda.stream(stream):
             assert nb._stream() == nb._public_stream() == stream.cuda_stream
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shares", [(0.5, 0.5), (1.0, 0.0), (0.999, 0.001), (0.6, 0.3, 0.1), (0.5, 0.5, 0.0)])
+def test_sums_whose_values_are_asked_for_ahead(shares, dtype):
+    """Two and three tensors and coordinate lists just under and over the entries from which a partition asks for the lines of its
+    values beside its merge: operands of equal length, next to nothing, none at all, and lines that two partitions share."""
+    rng = np.random.default_rng(len(shares))
+    shape = (300, 301, 4001)
+    for total in (3_199_990, 3_200_011):
+        keys = [np.unique(rng.integers(0, shape[0] * shape[1] * shape[2], int(total * s * 1.02) + 2, dtype=np.int64)) for s in shares]
+        keys = [k[:int(round(total * s))] for k, s in zip(keys, shares)]
+        vals = [rng.uniform(-1, 1, len(k)).astype(dtype) for k in keys]
+        csf3._check([csf3._tensor(np.stack(np.unravel_index(k, shape), 1), v) for k, v in zip(keys, vals)], shape, 0, "values ahead")
+        flat = (shape[0] * shape[1], shape[2])
+        coo._check(nb.nacho_spadd_k, oracle.spadd_coo, [np.stack([k // flat[1], k % flat[1]], 1) for k in keys], vals, flat, 0, "values ahead")
