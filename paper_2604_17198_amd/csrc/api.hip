@@ -766,7 +766,7 @@ int32_t nacho_spmm(const nacho_tensor *A, const void *B, int64_t n, int64_t ldb,
     const int64_t n_rows = A->lvl[0].extent;
     profile_begin(s);
     // cost of a stored non-zero = n (broadcast over the dense loop); queries are multiples of n
-    const bool whole = grain > 0 && !plan.dealt && spmm_whole(Pe, n_rows);
+    const bool whole = grain > 0 && !plan.dealt && nnz > 0 && spmm_whole(Pe, n_rows);
     SpmmDeal deal = {};
     if (!whole) {
         ZeroRows zero;                  // rows of C whose row of A is empty

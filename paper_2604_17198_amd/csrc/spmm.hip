@@ -38,7 +38,11 @@ template <typename T, int V> struct Piece {
 // W lanes a row, CPL pieces of V elements a lane.  kWhole: there is no partition kernel; the wavefront searches its
 // rows, stores its part of the partition table and writes the zeros of its empty rows.
 // `deal` (without kWhole): what a workgroup executes, see deal_count_kernel.
-template <typename T, int V, int W, int CPL, bool kWhole>
+// SPMM_SMALL, SPMM_SMALL_DEALT: kWhole for partitions of up to kSmall non-zeros, and those that deal out partitions inside long
+// rows by XCD (of SPMM_WHOLE: `deal_rows`).
+constexpr int kSmall = 128;
+enum SpmmForm { SPMM_TABLE, SPMM_WHOLE, SPMM_SMALL, SPMM_SMALL_DEALT };
+template <typename T, int V, int W, int CPL, int kForm>
 __global__ void __launch_bounds__(NACHO_WAVE)
 spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ crd, const T *__restrict__ val,
                  const T *__restrict__ B, int n, int span, int64_t ldb, T *__restrict__ C, int64_t ldc,
@@ -46,11 +50,12 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
                  T *__restrict__ carry_val, int32_t *__restrict__ carry_row, int n_rows, int nnz, int grain,
                  int64_t cost_scale, SpmmDeal deal, bool deal_rows, WaveLog wlog)
 {
+    constexpr bool kWhole = kForm != SPMM_TABLE, kFew = kForm == SPMM_SMALL || kForm == SPMM_SMALL_DEALT;
     typedef typename Piece<T, V>::type P;
     typedef typename Piece<T, V>::mem PM;
     constexpr int NG = NACHO_WAVE / W;         // groups
     constexpr int kSlots = kGrain + 4 * NG;    // a group's stretch is followed by 4 words (banks of their own for every group)
-    constexpr int kIter = kGrain / NACHO_WAVE;
+    constexpr int kIter = (kFew ? kSmall : kGrain) / NACHO_WAVE;
     // non-zeros a group has in flight: 64 registers of B, 16 at most
     constexpr int kRegs = CPL * V * (int)sizeof(T) / 4;
     constexpr int U = kRegs <= 4 ? 16 : (kRegs <= 8 ? 8 : 4);
@@ -75,58 +80,124 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             b1 = b0 + 1;
         }
     }
-    int r0, r1, n0, n1;
+    int r0, r1, n0, n1, len, S, items, base;           // S: a group's stretch, `items` of it non-zeros, from slot `base` on
+    int32_t c_in[kIter];
+    T v_in[kIter];
+    auto stretch = [&]() {
+        len = n1 - n0;
+        S = ((len + NG - 1) / NG + 3) & ~3;
+        const int left = len - g * S;
+        items = left < 0 ? 0 : (left < S ? left : S);
+        base = g * (S + 4);
+    };
+    auto stream = [&]() {
+        if constexpr (kFew) {
+            // (behind the partition's end its last non-zero again, times zero: no branches between the loads)
+#pragma unroll
+            for (int j = 0; j < kIter; ++j) {
+                const int at = g * S + gl + j * W;
+                c_in[j] = __builtin_nontemporal_load(crd + (n0 + (at < len ? at : len - 1)));
+                v_in[j] = __builtin_nontemporal_load(val + (n0 + (at < len ? at : len - 1)));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kIter; ++j) {
+                const int i = gl + j * W;
+                c_in[j] = 0;
+                v_in[j] = T(0);
+                if (i < items) {
+                    c_in[j] = __builtin_nontemporal_load(crd + (n0 + g * S + i));
+                    v_in[j] = __builtin_nontemporal_load(val + (n0 + g * S + i));
+                }
+            }
+        }
+    };
+    // the ends of the first 64 rows, and (kWhole) of the first 64 of the rows whose zeros are this wavefront's: all rows are shared out evenly
+    bool has_head;                                     // row r0 started in an earlier partition
+    int next_first, row, row_a, row_b, zero_a = 0, zero_b = 0;         // (the first row that starts after this partition)
+    const unsigned share = kWhole ? ((unsigned)n_rows + gridDim.x - 1u) / gridDim.x : 0u;
+    int z0 = 0, z1 = 0;
+    auto rows = [&]() {
+        const int pr0 = pos[r0], pr1 = pos[r1];
+        row = r0 + lane;
+        row_a = row_b = 0;
+        if (kWhole) {
+            z0 = (int)(p * share) < n_rows ? (int)(p * share) : n_rows;
+            z1 = n_rows - z0 < (int)share ? n_rows : z0 + (int)share;
+        }
+        if constexpr (kFew) {                          // (no branches between the loads)
+            row_a = pos[row < n_rows ? row : n_rows];
+            row_b = pos[row + 1 < n_rows ? row + 1 : n_rows];
+            zero_a = pos[z0 + lane < n_rows ? z0 + lane : n_rows];
+            zero_b = pos[z0 + lane + 1 < n_rows ? z0 + lane + 1 : n_rows];
+        }
+        has_head = n0 > pr0;
+        next_first = n1 > pr1 ? r1 + 1 : r1;
+        if constexpr (kFew) {
+            if (row >= next_first) row_a = row_b = 0;
+        } else {
+            if (row < next_first) { row_a = pos[row]; row_b = pos[row + 1]; }
+            if (kWhole && z0 + lane < z1) { zero_a = pos[z0 + lane]; zero_b = pos[z0 + lane + 1]; }
+        }
+    };
     if (kWhole) {
-        const int base = pos[0];
+        // (pos[0] = 0, and every partition has non-zeros)
         const long long Qa = (long long)p * grain, Qb = Qa + grain;
-        n0 = base + (int)(Qa < nnz ? Qa : nnz);
-        n1 = base + (int)(Qb < nnz ? Qb : nnz);
-        rows_holding(pos, n_rows, n0, n1, r0, r1);
-        if (p == 0) r0 = 0;
-        else if (Qa >= nnz) r0 = n_rows;
-        if (Qb >= nnz) r1 = n_rows;
-        if (r0 < n_rows && deal_rows) {
-            const int dealt = dealt_partition(p, pos[r0] - base, pos[r0 + 1] - base, grain);
+        n0 = (int)(Qa < nnz ? Qa : nnz);
+        n1 = (int)(Qb < nnz ? Qb : nnz);
+        auto by_rows = [&]() {
+            if (r0 >= n_rows) return;
+            const int dealt = dealt_partition(p, pos[r0], pos[r0 + 1], grain);
             if (dealt != p) {
                 // (a partition inside row r0; it may end with the row)
                 p = dealt;
-                n0 = base + p * grain;
+                n0 = p * grain;
                 n1 = n0 + grain;
                 r1 = r0;
             }
+        };
+        if constexpr (kFew) {
+            // The call is as long as one wavefront's chain of round trips: 64 probes a round instead of 32, and where the non-zeros are known
+            // without their rows both are asked for at once (20,000 non-zeros, 37 floats 10.0 to 9.1 us, 100,000, 16 doubles 10.6 to 9.5; with millions of non-zeros the
+            // probes' lines cost more than the round: 10M, 4 floats 100 and 114).
+            RowWindow wa{0, n_rows}, wb{0, n_rows};
+            const int probe = wa.load(pos, n_rows);    // (the first probes are the same for both boundaries)
+            if (kForm == SPMM_SMALL) {
+                stretch();
+                stream();
+            }
+            wa.narrow(probe, n0);
+            wb.narrow(probe, n1);
+            while (wa.lo < wa.hi || wb.lo < wb.hi) {
+                const int probe_a = wa.load(pos, n_rows), probe_b = wb.load(pos, n_rows);
+                wa.narrow(probe_a, n0);
+                wb.narrow(probe_b, n1);
+            }
+            r0 = wa.lo;
+            r1 = wb.lo;
+        } else rows_holding(pos, n_rows, n0, n1, r0, r1);
+        if (p == 0) r0 = 0;
+        if (Qb >= nnz) r1 = n_rows;                    // (Qa < nnz)
+        if (kForm == SPMM_SMALL_DEALT || (!kFew && deal_rows)) by_rows();
+        if (kForm != SPMM_SMALL) {
+            stretch();
+            stream();
         }
+        rows();
     } else {
         r0 = coord[2 * b0]; r1 = coord[2 * b1];
         n0 = posn[2 * b0 + 1]; n1 = posn[2 * b1 + 1];
+        stretch();
+        stream();
+        rows();
     }
-    const int len = n1 - n0;
-    const int S = ((len + NG - 1) / NG + 3) & ~3;      // a group's stretch
-    const int left = len - g * S, items = left < 0 ? 0 : (left < S ? left : S);
-    const int base = g * (S + 4);                      // its first slot
-    // everything is asked for before the first wait: the stretch, the ends of the rows
-    int32_t c_in[kIter];
-    T v_in[kIter];
-#pragma unroll
-    for (int j = 0; j < kIter; ++j) {
-        const int i = gl + j * W;
-        c_in[j] = 0;
-        v_in[j] = T(0);
-        if (i < items) {
-            c_in[j] = __builtin_nontemporal_load(crd + (n0 + g * S + i));
-            v_in[j] = __builtin_nontemporal_load(val + (n0 + g * S + i));
-        }
-    }
-    const int pr0 = pos[r0], pr1 = pos[r1];
-    const bool has_head = n0 > pr0;                    // row r0 started in an earlier partition
-    const int next_first = n1 > pr1 ? r1 + 1 : r1;     // first row that starts after this partition
-    int row = r0 + lane, row_a = 0, row_b = 0;
-    if (row < next_first) { row_a = pos[row]; row_b = pos[row + 1]; }
     if (kWhole && lane == 0 && blockIdx.y == 0) {
         coord[2 * p] = r0;
-        coord[2 * p + 1] = r0 < n_rows ? (p == 0 ? 0 : crd[n0]) : 0;
+        coord[2 * p + 1] = r0 < n_rows && p > 0 ? c_in[0] : 0;
         posn[2 * p] = r0;
         posn[2 * p + 1] = p == 0 ? 0 : (r0 < n_rows ? n0 : nnz);
-        cost[p] = (int64_t)(n0 - pos[0]) * cost_scale;
+        cost[p] = (int64_t)n0 * cost_scale;
         if (p == (int)gridDim.x - 1) {
             coord[2 * p + 2] = n_rows;
             coord[2 * p + 3] = 0;
@@ -154,17 +225,15 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         const int i = gl + j * W;
         if (i < S) {
             s_crd[base + i] = c_in[j];
-            s_val[base + i] = v_in[j];
+            s_val[base + i] = i < items ? v_in[j] : T(0);
             s_row[base + i] = -1;
         }
     }
-    __syncthreads();
-    if (kWhole) {
-        // zeros of empty rows: every wavefront looks after an equal share of all rows, 64 of them at a time
-        const int z0 = (int)((int64_t)n_rows * p / gridDim.x), z1 = (int)((int64_t)n_rows * (p + 1) / gridDim.x);
+    unsigned long long empty = kWhole ? __ballot(z0 + lane < z1 && zero_a == zero_b) : 0ull;
+    wave_sync();
+    auto write_zeros = [&]() {
         for (int z = z0; z < z1; z += NACHO_WAVE) {
-            const bool is_empty = z + lane < z1 && pos[z + lane] == pos[z + lane + 1];
-            const unsigned long long empty = __ballot(is_empty);
+            if (z > z0) empty = __ballot(z + lane < z1 && pos[z + lane] == pos[z + lane + 1]);
             if (empty == 0ull) continue;
             for (int i = g; i < NACHO_WAVE; i += NG)
                 if (bit_at(empty, i)) {
@@ -173,7 +242,9 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
                         if (mine[c]) *reinterpret_cast<PM *>(C + (int64_t)(z + i) * ldc + col[c]) = P(T(0));
                 }
         }
-    }
+    };
+    // (a small call's chain goes first; a large one has other wavefronts: at the end 2M non-zeros, 4 floats take 27.7 us, here 26.5)
+    if (kWhole && !kFew) write_zeros();
     const float per_S = 1.0f / (float)S;
     for (;;) {                                         // rows, 64 at a time
         const bool is_row = row < next_first;
@@ -195,7 +266,7 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         row_a = row_b = 0;
         if (row < next_first) { row_a = pos[row]; row_b = pos[row + 1]; }
     }
-    __syncthreads();
+    wave_sync();
 
     P acc[CPL], head[CPL];
 #pragma unroll
@@ -253,11 +324,11 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
 
     // a group's last row goes on in the heads of the groups behind it, up to the first that starts a row of its own
     const unsigned long long started = __ballot(cur >= 0);
-    __syncthreads();
+    wave_sync();
     P *s_head = reinterpret_cast<P *>(smem);
 #pragma unroll
     for (int c = 0; c < CPL; ++c) s_head[c * NACHO_WAVE + lane] = head[c];
-    __syncthreads();
+    wave_sync();
     auto starts = [&](int h) { return bit_at(started, h * W); };
     auto add_heads = [&](P (&x)[CPL]) {
         for (int h = g + 1; h < NG; ++h) {
@@ -277,6 +348,7 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             if (mine[c]) *reinterpret_cast<PM *>(carry_val + (int64_t)p * n + col[c]) = head[c];
     }
     if (lane == 0 && blockIdx.y == 0) carry_row[p] = has_head ? r0 : -1;
+    if (kFew) write_zeros();
     if (blockIdx.y == 0) wave_end(wlog, p, stamp, (uint32_t)len, (uint32_t)(next_first - r0));
 }
 
@@ -554,6 +626,7 @@ hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, c
     const int V = dtype == NACHO_F64 ? 2 : 4;
     // (an L2 holds 4 MB; 1.3M non-zeros, 37 columns of doubles, 15 MB of B: 65 to 48 us)
     const bool deal_rows = b_bytes > 4e6;
+    const int form = !whole ? SPMM_TABLE : (grain > kSmall ? SPMM_WHOLE : (deal_rows ? SPMM_SMALL_DEALT : SPMM_SMALL));
     // stretches of up to 64 pieces of V columns, of about equal width
     const int pieces = n < V ? n : (n + V - 1) / V, stretches = (pieces + NACHO_WAVE - 1) / NACHO_WAVE;
     const int per = (pieces + stretches - 1) / stretches;
@@ -565,8 +638,10 @@ hipError_t launch_spmm_exec(int dtype, const int32_t *pos, const int32_t *crd, c
                        nacho_host::wave_log())
 #define NACHO_SPMM_SHAPE(T, VV, W, CPL)                                                                                 \
     do {                                                                                                                \
-        if (whole) NACHO_SPMM_LAUNCH(T, VV, W, CPL, true);                                                              \
-        else NACHO_SPMM_LAUNCH(T, VV, W, CPL, false);                                                                   \
+        if (form == SPMM_WHOLE) NACHO_SPMM_LAUNCH(T, VV, W, CPL, SPMM_WHOLE);                                           \
+        else if (form == SPMM_SMALL) NACHO_SPMM_LAUNCH(T, VV, W, CPL, SPMM_SMALL);                                      \
+        else if (form == SPMM_SMALL_DEALT) NACHO_SPMM_LAUNCH(T, VV, W, CPL, SPMM_SMALL_DEALT);                          \
+        else NACHO_SPMM_LAUNCH(T, VV, W, CPL, SPMM_TABLE);                                                              \
     } while (0)
     // the fewest lanes that hold a row: more rows in flight per instruction
 #define NACHO_SPMM_TYPE(T, VV)                                                                                          \

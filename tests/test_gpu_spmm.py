@@ -126,3 +126,27 @@ def test_more_than_64_dense_columns(dtype):
     got = Cfull.cpu().numpy()
     assert tol_ok(got[:, :150], ref, sabs, TOL[dtype]).all()
     assert np.isnan(got[:, 150:]).all(), "columns beyond n were written"
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n_rows,nnz,n_cols", [
+    (1, 3, 40), (63, 900, 40), (64, 900, 40), (65, 5000, 4000), (4096, 20_000, 4000), (4097, 20_000, 4000), (60_000, 30_000, 4000),
+    (9000, 262_144, 4000), (9000, 262_145, 4000), (9000, 524_288, 30_000), (9000, 524_289, 30_000)])
+def test_small_calls(n_rows, nnz, n_cols, dtype):
+    """Rows around the 64 probes of a search round and its second and third round, many of them empty, partitions of 64 to 192
+    non-zeros, and B on either side of the 4 MB from which partitions inside long rows are dealt out."""
+    rng = np.random.default_rng(n_rows + nnz)
+    lens = np.zeros(n_rows, np.int64)
+    some = np.sort(rng.choice(n_rows, max(1, n_rows * 2 // 3), replace=False))
+    left = min(nnz, len(some) * n_cols)
+    long_rows = min(n_cols, left // 4)
+    lens[some] = np.minimum((left - long_rows) // len(some), n_cols)
+    lens[some[len(some) // 2]] = max(1, long_rows)
+    pos = np.zeros(n_rows + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    total = int(pos[-1])
+    at = np.arange(total) - np.repeat(pos[:-1].astype(np.int64), lens)
+    crd = (at * n_cols // np.repeat(np.maximum(lens, 1), lens)).astype(np.int32)
+    A = {"n_rows": n_rows, "n_cols": n_cols, "pos": pos, "crd": crd, "val": rng.uniform(-1, 1, total).astype(dtype)}
+    for n in (3, 37):
+        _check(A, rng.uniform(-1, 1, (n_cols, n)).astype(dtype), 0, "small")
