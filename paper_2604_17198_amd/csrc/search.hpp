@@ -92,33 +92,43 @@ template <bool kMax, typename C> __device__ inline C extreme_of_lanes(C v, C non
 }
 
 // Dense level (level 0 of CSR operands): position == coordinate, cost through
-// the next level's pos array.  64-ary search over [0, N].  Returns the row, and its cost in c_low.
+// the next level's pos array.  64-ary search over [0, N].  Returns the row, its cost in c_low, and in first[t], behind[t] where
+// operand t's entries of the row start and end (the rounds have looked at both; behind: not of row N).
 template <int K>
-__device__ __forceinline__ int64_t dense_search(const DevOperands &ops, int64_t R, int64_t &c_low)
+__device__ __forceinline__ int64_t dense_search(const DevOperands &ops, int64_t R, int64_t &c_low, int (&first)[K], int (&behind)[K])
 {
     const int lane = lane_id();
     const int k = ops.k;
     int64_t low = 0, high = level0_extent(ops);
     c_low = 0;
+#pragma unroll
+    for (int t = 0; t < K; ++t) first[t] = behind[t] = 0;      // (pos[0] = 0)
     while (low < high) {
         const int64_t span = high - low;
         const int64_t step = (span + NACHO_WAVE - 1) / NACHO_WAVE;
         int64_t x = low + (int64_t)(lane + 1) * step;
         if (x > high) x = high;
         int64_t c = 0;
+        int at[K];
 #pragma unroll
         for (int t = 0; t < K; ++t) {
-            if (t >= k) break;
-            const int32_t *pos = ops.lvl[t][1].pos;
-            c += (int64_t)(pos[x] - pos[0]);
+            at[t] = 0;
+            if (t < k) at[t] = ops.lvl[t][1].pos[x];
+            c += (int64_t)at[t];
         }
         const unsigned long long ok = __ballot(c <= R);   // a prefix of the lanes (monotone cost)
         const int n = __popcll(ok);
         if (n > 0) {
             low = lane_value((long long)x, n - 1);
             c_low = lane_value((long long)c, n - 1);
+#pragma unroll
+            for (int t = 0; t < K; ++t) first[t] = lane_value(at[t], n - 1);
         }
-        if (n < NACHO_WAVE) high = lane_value((long long)x, n) - 1;
+        if (n < NACHO_WAVE) {
+            high = lane_value((long long)x, n) - 1;
+#pragma unroll
+            for (int t = 0; t < K; ++t) behind[t] = lane_value(at[t], n);
+        }
     }
     return low;
 }
@@ -418,12 +428,15 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
 // operand first on ties) -- i of them from the first operand for the largest i with A[i - 1] <= B[R - i].  Two loads and a
 // ballot a round.  Sixteen candidates, placed around the expected split as the samples above are (its first
 // expectation: the operands' shares; later ones from how far apart A and B are at the ends of the range); once the
-// range is a few cache lines every lane has one.  (10M + 10M entries, 8192 boundaries, evenly spaced candidates: 64 a round 46
-// us, 16 24, 8 19 -- with thousands of boundaries in flight the lines are what takes the time, a line a candidate, with few of
-// them the rounds are.  Two DCSR matrices of 20M, 7218 boundaries, both levels: 29.2 us with eight evenly spaced ones, 21.0 like
-// this.)  Coordinate lists' candidates stay evenly spaced, a line each however often the range is cut: eight of them with more
-// than a thousand boundaries in flight (`many`), else sixteen (16 and 8 a round, us: sums of two lists, 512 boundaries 27.1 and 27.7,
-// 861 36.1 and 36.1; products, 1375 46.6 and 45.6, 2402 68.9 and 65.7, 4122 106 and 100).
+// range is a few cache lines every lane has one, and once there is a lane for every place left the round is the last: what it
+// loads is also what the boundary is made of.  (That asked for by itself, two vectors' sums, us: 30k entries 10.2, so 10.0; 1.2M
+// 14.3, 14.1; 35M 128, 127.  All 64 lanes in every round of calls of up to 512 boundaries gain nothing: 10.0, 14.7.)
+// (10M + 10M entries, 8192 boundaries, evenly spaced candidates: 64 a round 46 us, 16 24, 8 19 -- with thousands of boundaries in
+// flight the lines are what takes the time, a line a candidate, with few of them the rounds are.  Two DCSR matrices of 20M, 7218
+// boundaries, both levels: 29.2 us with eight evenly spaced ones, 21.0 like this.)  Coordinate lists' candidates stay evenly
+// spaced, a line each however often the range is cut: eight of them with more than a thousand boundaries in flight (`many`), else
+// sixteen (16 and 8 a round, us: sums of two lists, 512 boundaries 27.1 and 27.7, 861 36.1 and 36.1; products, 1375 46.6 and 45.6,
+// 2402 68.9 and 65.7, 4122 106 and 100).
 // Requires both segments non-empty and 0 <= R < their total length.
 template <class Acc>
 __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const Acc &A, const Acc &B, int l, int h, int R, int sh,
@@ -438,7 +451,7 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
     float at = (float)R * (float)na * __builtin_amdgcn_rcpf((float)na + (float)nb) - (float)lo;
     bool even = Acc::kPairs;                           // (rows of unequal length: an expectation is worth nothing, there is none)
     const int share = Acc::kPairs && many ? 3 : 2;     // log2 of the lanes that share a candidate: they read the same words
-    while (lo < hi) {
+    while (hi - lo > NACHO_WAVE - 2) {
         const int w = hi - lo;                         // candidates lo + 1 .. hi
         int i;
         if (w <= 256) i = (lane + 1) * ((w + NACHO_WAVE - 1) / NACHO_WAVE);
@@ -465,13 +478,14 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
             at = f * (float)(hi - lo);
         }
     }
-    const int i = lo, j = R - lo;
-    // A[i - 1], A[i], B[j]: lanes 0, 1, 2
-    C v = Acc::kNone;
-    if (lane == 0 && i > 0) v = A.load(a_at0 + i - 1);
-    if (lane == 1 && i < na) v = A.load(a_at0 + i);
-    if (lane == 2 && j < nb) v = B.load(b_at0 + j);
-    const C a_before = lane_value(v, 0), a_at = lane_value(v, 1), b_at = lane_value(v, 2);
+    // The last round: a lane for every place left, lo among them, and one behind; what the boundary is made of is then in the lanes.
+    const int place = lo + lane, left = hi - lo;
+    C av = Acc::kNone, bv = Acc::kNone;
+    if (lane <= left + 1 && place > 0 && place <= na) av = A.load(a_at0 + place - 1);
+    if (lane <= left && R - place < nb) bv = B.load(b_at0 + (R - place));
+    const int n = __popcll(__ballot(lane == 0 || (lane <= left && av <= bv)));         // (a prefix of the lanes)
+    const int i = lo + n - 1, j = R - i;
+    const C a_before = lane_value(av, n - 1), a_at = lane_value(av, n), b_at = lane_value(bv, n - 1);
     const C x = a_at < b_at ? a_at : b_at;
     const int la = i - (i > 0 && a_before == x ? 1 : 0);       // (the coordinate's entry of A may lie before the split)
     LevelFound<Acc> found;
@@ -641,12 +655,19 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
         int x0, p0, lo, hi, sh = 0;
         if (ops.lvl[0][0].kind == NACHO_DENSE) {
             int64_t c = 0;
-            const int64_t row = dense_search<K>(ops, R, c);
+            int first[K], behind[K];
+            const int64_t row = dense_search<K>(ops, R, c, first, behind);
             R -= (int)c;
             x0 = p0 = (int)row;
             const bool present = row < ops.lvl[0][0].extent;
-            lo = pos1[p0];
-            hi = present ? pos1[p0 + 1] : lo;
+            lo = first[0];
+            hi = behind[0];
+#pragma unroll
+            for (int u = 1; u < K; ++u) {
+                lo = g.t == u ? first[u] : lo;
+                hi = g.t == u ? behind[u] : hi;
+            }
+            if (!present) hi = lo;
             if (ops.start[0]) {                        // a remapped operand's row
                 const Ints32 start = ints_of([&](int t) { return ops.start[t]; });
                 if (present) sh = start[p0] - lo;

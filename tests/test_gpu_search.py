@@ -79,6 +79,23 @@ def test_every_boundary(fmt, kind):
             assert np.array_equal(got["posn"].astype(np.int64), ref["posn"]), (k, P)
 
 
+@pytest.mark.parametrize("fmt", ["vector", "csr", "dcsr", "coo", "csf3"])
+def test_two_operands_around_the_lanes(fmt):
+    """Every boundary of two operands as long as a wavefront has lanes, an entry or two fewer or more: all of it in one row
+    (of one fibre), behind an empty row, the operands equal, apart, interleaved."""
+    for n, m in ((1, 1), (61, 61), (62, 61), (62, 63), (63, 200), (64, 64), (126, 65), (1, 300)):
+        for step, shift in ((1, 0), (1, 1), (2, 1), (1, n)):
+            base = 3 << 14
+            keys = [base + step * np.arange(n, dtype=np.int64), base + shift + step * np.arange(m, dtype=np.int64)]
+            g, o = _operands(fmt, keys)
+            P = n + m
+            print(f"partition {fmt} {n} + {m} step {step} shift {shift}", flush=True)
+            got, ref = parts_to_numpy(nb.nacho_partition(g, P)), oracle.partition(o, P)
+            assert np.array_equal(got["cost"], ref["cost"])
+            assert np.array_equal(got["coord"].astype(np.int64), ref["coord"][:, :got["coord"].shape[1]])
+            assert np.array_equal(got["posn"].astype(np.int64), ref["posn"])
+
+
 @pytest.mark.parametrize("k", [3, 8])
 @pytest.mark.parametrize("fmt", ["vector", "csr", "dcsr", "coo", "csf3"])
 def test_skewed_operands(fmt, k):
