@@ -47,27 +47,45 @@ __device__ inline void publish(unsigned long long *state, int64_t p, unsigned lo
     __hip_atomic_store(&state[p], flag | (unsigned)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// By a whole wavefront: the sum of the workgroups before p, whose own sum is `own`; publishes the prefix.
+// By a whole wavefront: the sum of the workgroups before p, whose own sum is `own`; publishes the prefix.  A lane holds
+// kWords words, all in flight at once: with a few hundred workgroups, which all start together and so find no prefix near, one
+// trip to memory in place of one for every 64 of them.
+constexpr int kWords = 4;
 __device__ inline bool look_back(unsigned long long *state, int64_t p, int own, int &before)
 {
     const int lane = lane_id();
     int sum = 0;
-    for (int64_t end = p; end > 0; end -= NACHO_WAVE) {        // words end - 1 - lane
-        const int64_t j = end - 1 - lane;
-        unsigned long long s = 0ull, prefixes = 0ull;
+    bool done = p == 0;
+    for (int64_t end = p; !done; end -= kWords * NACHO_WAVE) {         // words end - 1 - (64 u + lane)
+        unsigned long long s[kWords], prefixes[kWords];
         for (int spins = 0;; ++spins) {
-            if (s == 0ull) s = j < 0 ? kPrefix : __hip_atomic_load(&state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            prefixes = __ballot((s & kPrefix) != 0ull);
-            const unsigned long long missing = __ballot(s == 0ull);
-            // (lanes nearer than the nearest prefix count)
-            const unsigned long long nearer = prefixes ? (prefixes & (0ull - prefixes)) - 1ull : ~0ull;
-            if ((missing & nearer) == 0ull) break;
+#pragma unroll
+            for (int u = 0; u < kWords; ++u) {
+                const int64_t j = end - 1 - (u * NACHO_WAVE + lane);
+                s[u] = __hip_atomic_load(&state[j < 0 ? 0 : j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            bool waits = false, behind = false;        // (behind a prefix nothing counts)
+#pragma unroll
+            for (int u = 0; u < kWords; ++u) {
+                if (end - 1 - (u * NACHO_WAVE + lane) < 0) s[u] = kPrefix;
+                prefixes[u] = __ballot((s[u] & kPrefix) != 0ull);
+                const unsigned long long missing = __ballot(s[u] == 0ull);
+                // (lanes nearer than the nearest prefix count)
+                const unsigned long long nearer = prefixes[u] ? (prefixes[u] & (0ull - prefixes[u])) - 1ull : ~0ull;
+                waits = waits || (!behind && (missing & nearer) != 0ull);
+                behind = behind || prefixes[u] != 0ull;
+            }
+            if (!waits) break;
             if (spins > kSpinLimit) return false;
             __builtin_amdgcn_s_sleep(4);
         }
-        const int nearest = prefixes ? __ffsll((long long)prefixes) - 1 : NACHO_WAVE - 1;
-        sum += __builtin_amdgcn_readlane(wave_inclusive_scan(lane <= nearest ? (int)(unsigned)s : 0), NACHO_WAVE - 1);
-        if (prefixes) break;
+#pragma unroll
+        for (int u = 0; u < kWords; ++u) {
+            const int nearest = prefixes[u] ? __ffsll((long long)prefixes[u]) - 1 : NACHO_WAVE - 1;
+            const int part = wave_inclusive_scan(lane <= nearest ? (int)(unsigned)s[u] : 0);
+            sum += done ? 0 : __builtin_amdgcn_readlane(part, NACHO_WAVE - 1);
+            done = done || prefixes[u] != 0ull;
+        }
     }
     before = sum;
     if (lane == 0) publish(state, p, kPrefix, sum + own);
@@ -102,69 +120,138 @@ struct PlanRule {
 // One workgroup per partition of the level-0 coordinate arrays (at most kRemapGrain + k - 1 coordinates).  Equal
 // coordinates of different operands fall in one partition (Section 6), so every row of operand 0 in the partition
 // looks for itself in the partition's segment of every other operand.
+//
+// A chain of latencies: two trips to memory (the segments' places, then the rows and where their entries start together, all
+// loads of a thread at once), searches in LDS side by side, the look-back.  (Operand by operand and row by row, with the starts
+// asked for once the intersected rows are known and a trip for every 64 workgroups that the sums go back over: two matrices of 100k
+// rows 13.3 us, so 10.7; the whole product of 15k entries each 29.7 us, so 27.8, of 20M each 105.5, so 102.4.)  K: the most
+// operands.
+template <int K>
 __global__ void __launch_bounds__(kScanThreads)
 remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, RemapArrays r,
                   unsigned long long *__restrict__ state, PlanRule rule, int64_t *__restrict__ plan,
                   int32_t *__restrict__ status)
 {
-    constexpr int kMost = kRemapGrain + NACHO_MAX_OPERANDS, kPairs = kMost / 2, kEach = (kPairs + kScanThreads - 1) / kScanThreads;
+    constexpr int kFewest = K == 2 ? 2 : K - 1;                // operands of a call
+    constexpr int kMost = kRemapGrain + K, kPairs = (kRemapGrain + kFewest - 1) / kFewest;     // coordinates, intersected rows of a partition
+    constexpr int kEach = (kPairs + kScanThreads - 1) / kScanThreads, kLoads = (kMost + K + kScanThreads - 1) / kScanThreads;
     static_assert(kMost < (1 << 16), "places in a partition fit 16 bits");
-    __shared__ int s_crd[kMost];
-    __shared__ uint16_t s_q[NACHO_MAX_OPERANDS][kMost];        // place of operand 0's row in the other operands' segments
+    __shared__ int s_crd[kMost], s_pos[kMost + K];             // the rows of all operands; where their entries start (and the last one's end)
+    __shared__ uint16_t s_q[K][kMost];                         // place of operand 0's row in the other operands' segments
     __shared__ uint16_t s_item[kPairs];                        // the intersected rows of the partition
-    __shared__ int s_count[kScanWaves], s_len[NACHO_MAX_OPERANDS][kScanWaves], s_base[NACHO_MAX_OPERANDS + 1];
+    __shared__ int s_count[kScanWaves], s_len[K][kScanWaves], s_base[K + 1];
     __shared__ int s_fail;
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE, k = in.k;
+    touch_arguments<sizeof(RowArrays) + sizeof(RemapArrays) + sizeof(PlanRule) + 40>();
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE, k = K == 2 ? 2 : in.k;
     const int64_t p = blockIdx.x;
 
-    int lo[NACHO_MAX_OPERANDS], off[NACHO_MAX_OPERANDS + 1];
+    int lo[K], off[K + 1];
     off[0] = 0;
     int least = kMost;                                 // coordinates of the operand with the fewest
     bool broken = false;
 #pragma unroll
-    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t) {
-        lo[t] = 0;
-        off[t + 1] = off[t];
-        if (t < k) {
-            lo[t] = posn0[p * k + t];
-            const int len = posn0[(p + 1) * k + t] - lo[t];
-            broken = broken || len < 0 || len > kMost;
-            least = len < least ? len : least;
-            off[t + 1] = off[t] + len;
-        }
+    for (int t = 0; t < K; ++t) lo[t] = posn0[p * k + (t < k ? t : k - 1)];
+#pragma unroll
+    for (int t = 0; t < K; ++t) off[t + 1] = posn0[(p + 1) * k + (t < k ? t : k - 1)];
+#pragma unroll
+    for (int t = 0; t < K; ++t) {
+        const int len = t < k ? off[t + 1] - lo[t] : 0;
+        broken = broken || len < 0 || len > kMost;
+        least = t < k && len < least ? len : least;
+        off[t + 1] = off[t] + len;
     }
     // (only operands that violate their preconditions can have more coordinates in a partition than its share)
-    broken = broken || off[NACHO_MAX_OPERANDS] > kRemapGrain + k - 1;
+    broken = broken || off[K] > kRemapGrain + k - 1;
     if (tid == 0) {
         s_fail = 0;
         if (broken) atomicMin(status, (int32_t)NACHO_ERR_INVALID_ARG);
     }
-    const int n = broken ? 0 : off[1];
-    if (!broken) {
+    const int n = broken ? 0 : off[1], all_rows = off[K];
+    if (!broken && all_rows > 0) {
+        if constexpr (K <= 4) {
+            int x[kLoads], q[kLoads];
 #pragma unroll
-        for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
-            if (t < k)
-                for (int i = tid; i < off[t + 1] - off[t]; i += kScanThreads) s_crd[off[t] + i] = in.crd0[t][lo[t] + i];
+            for (int u = 0; u < kLoads; ++u) {
+                const int place = tid + u * kScanThreads;
+                // (no branches: places past the last one read it again)
+                const int i = place < all_rows ? place : all_rows - 1, j = place < all_rows + k ? place : all_rows + k - 1;
+                const int32_t *crd = in.crd0[0], *pos = in.pos1[0];
+                int at = lo[0] + i, from = lo[0] + j;
+#pragma unroll
+                for (int t = 1; t < K; ++t) {
+                    crd = i >= off[t] ? in.crd0[t] : crd;
+                    at = i >= off[t] ? lo[t] + i - off[t] : at;
+                    pos = j >= off[t] + t ? in.pos1[t] : pos;
+                    from = j >= off[t] + t ? lo[t] + j - (off[t] + t) : from;
+                }
+                x[u] = crd[at];
+                q[u] = pos[from];
+            }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const int place = tid + u * kScanThreads;
+                if (place < all_rows) s_crd[place] = x[u];
+                if (place < all_rows + k) s_pos[place] = q[u];
+            }
+        } else {
+            // (many operands, short segments: a place of each at a time)
+            int longest = 0;
+#pragma unroll
+            for (int t = 0; t < K; ++t) longest = off[t + 1] - off[t] > longest ? off[t + 1] - off[t] : longest;
+            for (int i = tid; i - tid <= longest; i += kScanThreads) {
+                int x[K], q[K];
+#pragma unroll
+                for (int t = 0; t < K; ++t) {
+                    const int len = off[t + 1] - off[t], u = t < k ? t : k - 1;
+                    x[t] = in.crd0[u][len > 0 ? lo[t] + (i < len ? i : len - 1) : 0];
+                    q[t] = in.pos1[u][lo[t] + (i < len ? i : len)];
+                }
+#pragma unroll
+                for (int t = 0; t < K; ++t) {
+                    const int len = off[t + 1] - off[t];
+                    if (i < len) s_crd[off[t] + i] = x[t];
+                    if (i <= len && t < k) s_pos[off[t] + t + i] = q[t];
+                }
+            }
+        }
     }
     __syncthreads();
-    // consecutive rows of operand 0 per thread
+    // consecutive rows of operand 0 per thread; the searches of a row in all operands, or of two rows in one, go side by side
     const int each = (n + kScanThreads - 1) / kScanThreads, first = tid * each;
-    unsigned found = 0u;
-    for (int j = 0; j < each && first + j < n; ++j) {
-        const int x = s_crd[first + j];
-        bool all = true;
+    constexpr int kRows = K == 2 ? 2 : 1;
+    int longest = 0;
 #pragma unroll
-        for (int t = 1; t < NACHO_MAX_OPERANDS; ++t)
-            if (t < k && all) {
-                int a = off[t], z = off[t + 1];
-                while (a < z) {
-                    const int mid = (a + z) >> 1;
-                    if (s_crd[mid] < x) a = mid + 1; else z = mid;
+    for (int t = 1; t < K; ++t) longest = off[t + 1] - off[t] > longest ? off[t + 1] - off[t] : longest;
+    const int widest = longest > 0 ? 1 << (31 - __builtin_clz((unsigned)longest)) : 0;
+    unsigned found = 0u;
+    for (int j = 0; j < each; j += kRows) {
+        int i[kRows], x[kRows], a[kRows][K];
+#pragma unroll
+        for (int g = 0; g < kRows; ++g) {
+            i[g] = first + j + g < n ? first + j + g : n - 1;
+            x[g] = s_crd[i[g]];
+#pragma unroll
+            for (int t = 1; t < K; ++t) a[g][t] = off[t];      // as many of the segment's rows as lie before x
+        }
+        for (int step = widest; step > 0; step >>= 1)
+#pragma unroll
+            for (int t = 1; t < K; ++t)
+#pragma unroll
+                for (int g = 0; g < kRows; ++g) {
+                    const int to = a[g][t] + step, v = s_crd[(to < off[t + 1] ? to : off[t + 1]) - 1];
+                    a[g][t] = to <= off[t + 1] && v < x[g] ? to : a[g][t];
                 }
-                all = a < off[t + 1] && s_crd[a] == x;
-                s_q[t][first + j] = (uint16_t)(a - off[t]);
+#pragma unroll
+        for (int g = 0; g < kRows; ++g) {
+            bool all = j + g < each && first + j + g < n;
+#pragma unroll
+            for (int t = 1; t < K; ++t) {
+                const int v = s_crd[a[g][t]];
+                if (all) s_q[t][i[g]] = (uint16_t)(a[g][t] - off[t]);
+                all = all && (t >= k || (a[g][t] < off[t + 1] && v == x[g]));
             }
-        found |= all ? 1u << j : 0u;
+            found |= all ? 1u << (j + g) : 0u;
+        }
     }
     const int mine = __popc(found), incl = wave_inclusive_scan(mine);
     if (lane == NACHO_WAVE - 1) s_count[wave] = incl;
@@ -186,21 +273,21 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
     for (; found; found &= found - 1u) s_item[at++] = (uint16_t)(first + __ffs(found) - 1);
     __syncthreads();
     // consecutive intersected rows per thread: where their entries start, how many there are
-    int start[NACHO_MAX_OPERANDS][kEach], len[NACHO_MAX_OPERANDS][kEach], before[NACHO_MAX_OPERANDS];
+    int start[K][kEach], len[K][kEach], before[K];
 #pragma unroll
-    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+    for (int t = 0; t < K; ++t)
         if (t < k)
 #pragma unroll
             for (int u = 0; u < kEach; ++u) {
                 start[t][u] = len[t][u] = 0;
                 if (tid * kEach + u < m) {
-                    const int i = s_item[tid * kEach + u], q = lo[t] + (t == 0 ? i : (int)s_q[t][i]);
-                    start[t][u] = in.pos1[t][q];
-                    len[t][u] = in.pos1[t][q + 1] - start[t][u];
+                    const int i = s_item[tid * kEach + u], q = off[t] + t + (t == 0 ? i : (int)s_q[t][i]);
+                    start[t][u] = s_pos[q];
+                    len[t][u] = s_pos[q + 1] - start[t][u];
                 }
             }
 #pragma unroll
-    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+    for (int t = 0; t < K; ++t)
         if (t < k) {
             int sum = 0;
 #pragma unroll
@@ -246,7 +333,7 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
     for (int u = 0; u < kEach; ++u)
         if (tid * kEach + u < m) r.rows[row0 + tid * kEach + u] = s_crd[s_item[tid * kEach + u]];
 #pragma unroll
-    for (int t = 0; t < NACHO_MAX_OPERANDS; ++t)
+    for (int t = 0; t < K; ++t)
         if (t < k) {
             int x = s_base[1 + t] + before[t];
 #pragma unroll
@@ -280,20 +367,23 @@ remap_rows_kernel(RowArrays in, const int32_t *__restrict__ posn0, int64_t P0, R
 constexpr int kKeepItems = 8, kKeepTile = kScanThreads * kKeepItems;
 
 __global__ void __launch_bounds__(kScanThreads)
-compact_rows_kernel(const int32_t *__restrict__ rows, const int32_t *__restrict__ pos_full, const int32_t *__restrict__ head,
+compact_rows_kernel(const int32_t *__restrict__ rows, const int32_t *__restrict__ pos_full, int most, const int32_t *__restrict__ head,
                     const int64_t *__restrict__ counts_in, const int64_t *__restrict__ plan, SpaddOut out,
                     unsigned long long *__restrict__ state)
 {
     __shared__ int s_count[kScanWaves], s_base, s_fail;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid / NACHO_WAVE;
     const int64_t tile = blockIdx.x;
-    if (plan[3]) return;                               // (the row loop was abandoned)
-    const int M = head[0];                             // (the launch is sized for an upper bound)
-    if (tile > 0 && tile * kKeepTile >= M) return;
     const int first = (int)tile * kKeepTile + tid * kKeepItems;
-    int x[kKeepItems + 1];
+    // (the launch is sized for an upper bound of the rows; the loads do not wait for their number: what lies behind is not looked at)
+    int x[kKeepItems + 1], row[kKeepItems];
 #pragma unroll
-    for (int u = 0; u <= kKeepItems; ++u) x[u] = pos_full[first + u < M ? first + u : M];
+    for (int u = 0; u <= kKeepItems; ++u) x[u] = pos_full[first + u < most ? first + u : most];
+#pragma unroll
+    for (int u = 0; u < kKeepItems; ++u) row[u] = rows[first + u < most ? first + u : most - 1];
+    if (plan[3]) return;                               // (the row loop was abandoned)
+    const int M = head[0];
+    if (tile > 0 && tile * kKeepTile >= M) return;
     unsigned keep = 0u;
 #pragma unroll
     for (int u = 0; u < kKeepItems; ++u) keep |= first + u < M && x[u + 1] > x[u] ? 1u << u : 0u;
@@ -325,7 +415,7 @@ compact_rows_kernel(const int32_t *__restrict__ rows, const int32_t *__restrict_
     for (int u = 0; u < kKeepItems; ++u)
         if (keep >> u & 1u) {
             if (at < out.cap_rows) {
-                out.crd0[at] = rows[first + u];
+                out.crd0[at] = row[u];
                 out.pos1[at] = x[u];
             }
             ++at;
@@ -372,8 +462,8 @@ hipError_t launch_remap_rows(const DevOperands &ops, int64_t P0, const int32_t *
         rows.pos1[t] = t < ops.k ? ops.lvl[t][1].pos : nullptr;
     }
     const PlanRule rule = {capacity, round, P_min, P_max};
-    hipLaunchKernelGGL(remap_rows_kernel, dim3((unsigned)P0), dim3(kScanThreads), 0, s, rows, posn0, P0, r, state, rule,
-                       plan, status);
+    auto kernel = ops.k == 2 ? remap_rows_kernel<2> : (ops.k <= 4 ? remap_rows_kernel<4> : (ops.k <= 6 ? remap_rows_kernel<6> : remap_rows_kernel<8>));
+    hipLaunchKernelGGL(kernel, dim3((unsigned)P0), dim3(kScanThreads), 0, s, rows, posn0, P0, r, state, rule, plan, status);
     return hipGetLastError();
 }
 
@@ -382,7 +472,7 @@ hipError_t launch_compact_rows(const RemapArrays &r, const int32_t *pos_full, co
 {
     // (over the upper bound of the rows; tiles past head[0] leave at once)
     hipLaunchKernelGGL(compact_rows_kernel, dim3((unsigned)compact_state_words(r.stride)), dim3(kScanThreads), 0, s, r.rows,
-                       pos_full, r.head, counts_in, plan, out, state);
+                       pos_full, (int)r.stride, r.head, counts_in, plan, out, state);
     return hipGetLastError();
 }
 

@@ -209,6 +209,30 @@ def test_every_entry_or_few_in_middle_partitions(k, dtype):
             check(mats, shape, 0, f"middle n={n} few={few}")
 
 
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 6, 7, 8])
+def test_row_loop(k):
+    """Rows of 0 to 2 entries: partitions of the row loop with as many intersected rows as there can be, with nearly all rows from
+    one operand, with none in common, one behind the other; more than 256 partitions, so that the sums along them reach back over
+    several words a lane."""
+    rng = np.random.default_rng(k)
+    every = np.arange(1024 * 300 // k + 11)
+    n = 20_000
+    for tag, rows in (("equal", [every] * k),
+                      ("few", [np.arange(n)] + [np.unique(rng.integers(0, n, 9 + 7 * t)) for t in range(1, k)]),
+                      ("apart", [t * n + np.arange(n) for t in range(k)]),
+                      ("all but one row apart", [np.append(t * n + np.arange(n - 1), k * n) for t in range(k)]),
+                      ("comb", [np.arange(0, 4 * n, 1 + t % 3) for t in range(k)]),
+                      ("one", [np.array([n * t % 3 if t else 0]) for t in range(k)])):
+        mats = []
+        for t, r in enumerate(rows):
+            per = rng.integers(0 if tag == "few" else 1, 3, len(r))
+            at = np.repeat(r, per)
+            first = np.concatenate([[True], at[1:] != at[:-1]])
+            coords = np.stack([at, np.where(first, 0, 1 + t % 2)], axis=1)
+            mats.append(_mat(coords, rng.standard_normal(len(at)).astype(np.float32)))
+        check(mats, (int(max(r[-1] for r in rows)) + 1, 3), 0, f"row loop {tag}")
+
+
 def test_capacity_overflow_is_reported():
     rng = np.random.default_rng(8)
     shape = (300, 200)
