@@ -113,7 +113,8 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             }
         }
     };
-    // the ends of the first 64 rows, and (kWhole) of the first 64 of the rows whose zeros are this wavefront's: all rows are shared out evenly
+    // the ends of the first 64 rows, and (kFew) of the first 64 of the rows whose zeros are this wavefront's: all rows are shared out
+    // evenly (a large call is bound by what it has in flight: 40M non-zeros, 4 floats, 200 a row 340 us with them, 330 without)
     bool has_head;                                     // row r0 started in an earlier partition
     int next_first, row, row_a, row_b, zero_a = 0, zero_b = 0;         // (the first row that starts after this partition)
     const unsigned share = kWhole ? ((unsigned)n_rows + gridDim.x - 1u) / gridDim.x : 0u;
@@ -123,7 +124,7 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         row = r0 + lane;
         row_a = row_b = 0;
         if (kWhole) {
-            z0 = (int)(p * share) < n_rows ? (int)(p * share) : n_rows;
+            z0 = p * share < (unsigned)n_rows ? (int)(p * share) : n_rows;     // (unsigned: may lie past 2^31)
             z1 = n_rows - z0 < (int)share ? n_rows : z0 + (int)share;
         }
         if constexpr (kFew) {                          // (no branches between the loads)
@@ -138,7 +139,6 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             if (row >= next_first) row_a = row_b = 0;
         } else {
             if (row < next_first) { row_a = pos[row]; row_b = pos[row + 1]; }
-            if (kWhole && z0 + lane < z1) { zero_a = pos[z0 + lane]; zero_b = pos[z0 + lane + 1]; }
         }
     };
     if (kWhole) {
@@ -229,11 +229,11 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
             s_row[base + i] = -1;
         }
     }
-    unsigned long long empty = kWhole ? __ballot(z0 + lane < z1 && zero_a == zero_b) : 0ull;
+    unsigned long long empty = kFew ? __ballot(z0 + lane < z1 && zero_a == zero_b) : 0ull;
     wave_sync();
     auto write_zeros = [&]() {
         for (int z = z0; z < z1; z += NACHO_WAVE) {
-            if (z > z0) empty = __ballot(z + lane < z1 && pos[z + lane] == pos[z + lane + 1]);
+            if (!kFew || z > z0) empty = __ballot(z + lane < z1 && pos[z + lane] == pos[z + lane + 1]);
             if (empty == 0ull) continue;
             for (int i = g; i < NACHO_WAVE; i += NG)
                 if (bit_at(empty, i)) {
