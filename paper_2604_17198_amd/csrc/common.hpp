@@ -166,6 +166,24 @@ __device__ inline unsigned long long low_bits(int n)
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// The value lane `from` holds (`from` the same in every lane), through a scalar register.
+__device__ inline int lane_value(int x, int from) { return __builtin_amdgcn_readlane(x, from); }
+__device__ inline long long lane_value(long long x, int from)
+{
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(unsigned long long)x, from);
+    const int hi = __builtin_amdgcn_readlane((int)(x >> 32), from);
+    return ((long long)hi << 32) | (long long)lo;
+}
+// The value lane `from` holds, `from` this lane's own choice.
+__device__ inline int value_from(int x, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, x); }
+__device__ inline long long value_from(long long x, int from)
+{
+    const unsigned lo = (unsigned)value_from((int)(unsigned)(unsigned long long)x, from);
+    return ((long long)value_from((int)(x >> 32), from) << 32) | (long long)lo;
+}
+
+__device__ inline int lane_left(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false); }     // wave_shr:1
+
 // Bit `at` (this lane's) of a mask every lane agrees on, without such a shift.  (The compiler would turn the choice
 // between the halves of one word into one; it does not know that these two belong together.)
 __device__ inline bool bit_at(unsigned long long mask, int at)

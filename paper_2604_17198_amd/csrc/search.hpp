@@ -40,24 +40,6 @@ struct PairCoords {
     __device__ static int64_t extent(const DevOperands &ops, int) { return ops.lvl[0][0].extent << 32; }
 };
 
-// The value lane `from` holds (`from` the same in every lane), through a scalar register.
-__device__ inline int lane_value(int x, int from) { return __builtin_amdgcn_readlane(x, from); }
-__device__ inline long long lane_value(long long x, int from)
-{
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(unsigned long long)x, from);
-    const int hi = __builtin_amdgcn_readlane((int)(x >> 32), from);
-    return ((long long)hi << 32) | (long long)lo;
-}
-// The value lane `from` holds, `from` this lane's own choice.
-__device__ inline int value_from(int x, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, x); }
-__device__ inline long long value_from(long long x, int from)
-{
-    const unsigned lo = (unsigned)value_from((int)(unsigned)(unsigned long long)x, from);
-    return ((long long)value_from((int)(x >> 32), from) << 32) | (long long)lo;
-}
-
-__device__ inline int lane_left(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false); }     // wave_shr:1
-
 // Sum, maximum and minimum over the wavefront by DPP moves (in every lane).
 __device__ inline int sum_of_lanes(int v)
 {

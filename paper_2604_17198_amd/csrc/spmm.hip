@@ -353,11 +353,12 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
 }
 
 // Carry fix-up: 64 / V lanes per partition, a piece of V columns each: 16 partitions (floats), 8 (doubles) or 4 (fewer columns
-// than a 16-byte piece has) per workgroup.  The carries of a row lie in consecutive partitions; the lanes of the first one add the run to the row of C.  A run of more than kShort carries
-// (there is at most one per workgroup: it is longer than the workgroup's partitions) is added by the whole workgroup,
-// every group an equal share of it: the largest row of 30M non-zeros has a thousand, which one wavefront, a row of carries at a
-// time, took 35 us for (half as many).  The order of the additions is fixed.  Bound: the loads in flight, so they are as wide
-// as the lanes' pieces (element by element, 156k partitions of 64 floats 66 us, 62k of 200 doubles 77; like this 28 and 52).
+// than a 16-byte piece has) per workgroup.  The carries of a row lie in consecutive partitions; the lanes of the first one add the
+// run to the row of C.  A run of more than kShort carries (there is at most one per workgroup: it is longer than the workgroup's
+// partitions) is added by the whole workgroup, every group an equal share of it: the largest row of 30M non-zeros has a thousand,
+// which one wavefront, a row of carries at a time, took 35 us for (half as many).  The order of the additions is fixed.  Bound: round trips, of which there are two: the rows of
+// the carries and the first of each, then the rows of C.  (Where the run ends was looked up in the matrix, in front of the carries: 156k
+// partitions of 64 floats 26.8 us, so 20.9; calls of 100k non-zeros 9.6, so 9.0.)  Loads are as wide as the lanes' pieces.
 constexpr int kFixCols = 64, kShort = 32;
 
 template <typename T, int V>
@@ -370,46 +371,38 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
     typedef typename Piece<T, V>::mem Mem;
     constexpr int kFixLanes = kFixCols / V, kFixGroups = 256 / kFixLanes;
     static_assert(kShort >= kFixGroups, "one long run per workgroup");
+    static_assert(kFixGroups + kShort < NACHO_WAVE && kShort == 32, "a lane for every carry that is looked at");
     __shared__ Vec part[kFixGroups][kFixLanes];
-    __shared__ int s_first, s_end, s_row;
-    const int g = threadIdx.x / kFixLanes, gl = threadIdx.x & (kFixLanes - 1);
-    const int p = blockIdx.x * kFixGroups + g;
-    if (deal.join > 1 && deal.place[blockIdx.x * kFixGroups] == kDealJoined) {
-        // (a carry for every `join` partitions; place is the same throughout then)
-        P = deal.joined;
-        grain *= deal.join;
-        if ((int)blockIdx.x * kFixGroups >= P) return;
-    }
+    const int g = threadIdx.x / kFixLanes, gl = threadIdx.x & (kFixLanes - 1), lane = lane_id();
+    const int p0 = blockIdx.x * kFixGroups, p = p0 + g;
     // (n >= V; the last piece of a row moves back where it would stick out: the columns it shares with the one before are
     // that one's to store)
     const int j0 = blockIdx.y * (kFixLanes * V) + gl * V, col = j0 < n - V ? j0 : n - V, shared = j0 - col;
-    if (threadIdx.x == 0) s_first = -1;
-    __syncthreads();
-    const int r = p < P ? carry_row[p] : -1;
-    const bool first = r >= 0 && (p == 0 || carry_row[p - 1] != r);
-    int e = p + 1;
-    if (first) {
-        // the run ends with the last partition that starts inside the row
-        const int row_end = pos[r + 1];
-        if (grain > 0) e = shares_before(row_end - pos[0], grain);
-        else {
-            int lo = p + 1, hi = P;                    // the first partition that starts at or behind the row's end
-            while (lo < hi) {
-                const int mid = lo + ((hi - lo) >> 1);
-                if (posn[2 * mid + 1] < row_end) lo = mid + 1; else hi = mid;
-            }
-            e = lo;
-        }
-        e = e < P ? e : P;
+    // In one trip to memory: the rows of the carries, from the one before the workgroup's first on, a lane each (every wavefront for
+    // itself); the first carry of every group's run, if it starts one; whether partitions were joined.  Places past the last
+    // partition read that one.
+    const int seen = p0 - 1 + lane;
+    int row = carry_row[seen < 0 ? 0 : (seen < P ? seen : P - 1)];
+    const Vec own = *reinterpret_cast<const Mem *>(carry_val + (int64_t)(p < P ? p : P - 1) * n + col);
+    const int place = *(deal.join > 1 ? deal.place + p0 : carry_row + p0);
+    if (deal.join > 1 && place == kDealJoined) {
+        // (a carry for every `join` partitions; place is the same throughout then)
+        P = deal.joined;
+        grain *= deal.join;
+        if (p0 >= P) return;
     }
-    auto add_to = [&](int row, Vec x) {
-        T *at = C + (int64_t)row * ldc + col;
-        if (shared == 0) *reinterpret_cast<Mem *>(at) += x;
-        else
-#pragma unroll
-            for (int c = 1; c < V; ++c)
-                if (c >= shared) at[c] += x[c];
+    row = seen >= 0 && seen < P ? row : -1;
+    const int left = lane_left(row);                   // (with all lanes on)
+    const unsigned long long on = __ballot(row >= 0 && row == left && lane > 0);       // goes on with the row before it
+    const unsigned long long starts = __ballot(row >= 0) & ~on;
+    // carries of the row of place `at`, as far as they are looked at; workgroups have groups in places 1 to kFixGroups
+    auto run_from = [&](int at) {
+        const unsigned behind = __builtin_amdgcn_alignbit((unsigned)(on >> 32), (unsigned)on, at + 1);     // kShort of them
+        return behind == ~0u ? kShort + 1 : __ffs(~behind);
     };
+    const unsigned long long longer = __ballot(lane > 0 && lane <= kFixGroups && bit_at(starts, lane) && run_from(lane) > kShort);
+    const int run = run_from(g + 1), r = value_from(row, g + 1);
+    const bool first = bit_at(starts, g + 1);
     // carries q, q + step, ... below `to`, eight 16-byte pieces or sixteen narrower ones in flight
     auto sum = [&](int q, int to, int step) -> Vec {
         Vec x = Vec(T(0));
@@ -427,22 +420,43 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
         return x;
     };
     const bool mine = j0 < n;
-    if (first && e - p <= kShort) {
-        if (mine) add_to(r, sum(p, e, 1));
-    } else if (first && gl == 0) {
-        s_first = p;
-        s_end = e;
-        s_row = r;
+    T *const at = C + (int64_t)r * ldc + col;          // (used by the first of a run)
+    auto put = [&](T *to, Vec x) {
+        if (shared == 0) *reinterpret_cast<Mem *>(to) = x;
+        else
+#pragma unroll
+            for (int c = 1; c < V; ++c)
+                if (c >= shared) to[c] = x[c];
+    };
+    if (first && run <= kShort) {
+        if (mine) {
+            const Vec y = *reinterpret_cast<const Mem *>(at);
+            put(at, y + (own + sum(p + 1, p + run, 1)));
+        }
     }
-    __syncthreads();
-    if (s_first < 0) return;                           // (the whole workgroup)
-    part[g][gl] = mine ? sum(s_first + g, s_end, kFixGroups) : Vec(T(0));
+    if (longer == 0ull) return;                        // (the whole workgroup)
+    // the run ends with the last partition that starts inside the row
+    const int at_long = __ffsll((long long)longer) - 1, first_long = p0 + at_long - 1, row_long = lane_value(row, at_long);
+    const int row_end = pos[row_long + 1];
+    int end_long = P;
+    if (grain > 0) end_long = shares_before(row_end - pos[0], grain);
+    else {
+        int lo = first_long + 1, hi = P;               // the first partition that starts at or behind the row's end
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo) >> 1);
+            if (posn[2 * mid + 1] < row_end) lo = mid + 1; else hi = mid;
+        }
+        end_long = lo;
+    }
+    end_long = end_long < P ? end_long : P;
+    part[g][gl] = mine ? sum(first_long + g, end_long, kFixGroups) : Vec(T(0));
     __syncthreads();
     if (g == 0 && mine) {
         Vec y = Vec(T(0));
 #pragma unroll
         for (int u = 0; u < kFixGroups; ++u) y += part[u][gl];
-        add_to(s_row, y);
+        T *const to = C + (int64_t)row_long * ldc + col;
+        put(to, *reinterpret_cast<const Mem *>(to) + y);
     }
 }
 

@@ -128,6 +128,26 @@ def test_more_than_64_dense_columns(dtype):
     assert np.isnan(got[:, 150:]).all(), "columns beyond n were written"
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 37, 66, 130])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_runs_of_carries(dtype, n):
+    """Partitions have 64 non-zeros here: rows whose carries are 0 to 3, 31 to 34 and 150 partitions' (more than 32 are added by a whole
+    workgroup), that start with a partition, behind its first non-zero and with its last one, one behind the other."""
+    lens = []
+    for shift in (0, 1, 63):
+        for m in (1, 2, 3, 31, 32, 33, 34, 150):
+            lens += [64 * m + shift, 0, 64 - shift if shift else 0]
+    lens = np.array(lens, np.int64)
+    pos = np.zeros(len(lens) + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    rng = np.random.default_rng(n)
+    total, n_cols = int(pos[-1]), 10_000
+    at = np.arange(total) - np.repeat(pos[:-1].astype(np.int64), lens)
+    A = {"n_rows": len(lens), "n_cols": n_cols, "pos": pos, "crd": at.astype(np.int32), "val": rng.uniform(-1, 1, total).astype(dtype)}
+    _check(A, rng.uniform(-1, 1, (n_cols, n)).astype(dtype), 0, "carries")
+    _check(A, rng.uniform(-1, 1, (n_cols, n)).astype(dtype), total // 64 + 5, "carries, partitions of fewer")
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("n_rows,nnz,n_cols", [
     (1, 3, 40), (63, 900, 40), (64, 900, 40), (65, 5000, 4000), (4096, 20_000, 4000), (4097, 20_000, 4000), (60_000, 30_000, 4000),
