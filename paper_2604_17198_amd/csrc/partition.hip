@@ -67,7 +67,7 @@ __device__ inline void zero_row(const ZeroRows &z, int64_t r, int lane_in_row, i
 // One wavefront searches one boundary.
 // kMode: 0 = vectors, CSR, DCSR; 1 = coordinate lists; 2 = three compressed levels (CSF).  The
 // last two are instantiations of their own: the other formats keep their register budget.
-template <int K, int kMode>
+template <int K, int kMode, bool kExact>
 __global__ void __launch_bounds__(256)
 partition_kernel(DevOperands ops, int64_t cost_scale, int64_t P, int64_t grain,
                  const int64_t *__restrict__ queries, int64_t total_unscaled,
@@ -84,7 +84,7 @@ partition_kernel(DevOperands ops, int64_t cost_scale, int64_t P, int64_t grain,
     const int64_t b = (int64_t)blockIdx.x * (256 / NACHO_WAVE) + threadIdx.x / NACHO_WAVE;
     if (b > P) return;                       // whole wavefront leaves together
     int found[K];
-    search_boundary<K, kMode>(ops, cost_scale, P, grain, queries, total_unscaled, coord, posn, cost, b, found);
+    search_boundary<K, kMode, kExact>(ops, cost_scale, P, grain, queries, total_unscaled, coord, posn, cost, b, found);
 }
 
 // ---- one CSR operand: all boundaries in one pass over the rows ---------------
@@ -288,12 +288,13 @@ hipError_t launch_partition(const DevOperands &ops, int64_t cost_scale, int64_t 
     };
     auto launch_mode = [&](auto mode) {
         constexpr int kMode = decltype(mode)::value;
-        if (kMode == 0 && ops.k <= 1) launch(partition_kernel<1, 0>);
-        else if (ops.k <= 2) launch(partition_kernel<2, kMode>);
-        else if (ops.k <= 3) launch(partition_kernel<3, kMode>);
-        else if (ops.k <= 4) launch(partition_kernel<4, kMode>);
-        else if (ops.k <= 6) launch(partition_kernel<6, kMode>);
-        else launch(partition_kernel<8, kMode>);
+        if (kMode == 0 && ops.k <= 1) launch(partition_kernel<1, 0, true>);
+        else if (ops.k < 2) launch(partition_kernel<2, kMode, false>);
+        else if (ops.k == 2) launch(partition_kernel<2, kMode, true>);
+        else if (ops.k == 3) launch(partition_kernel<3, kMode, true>);
+        else if (ops.k == 4) launch(partition_kernel<4, kMode, true>);
+        else if (ops.k <= 6) launch(partition_kernel<6, kMode, false>);
+        else launch(partition_kernel<8, kMode, false>);
     };
     if (ops.d == 3) launch_mode(std::integral_constant<int, 2>());
     else if (ops.lvl[0][0].kind == NACHO_NONUNIQUE) launch_mode(std::integral_constant<int, 1>());
