@@ -266,7 +266,8 @@ template <class Acc> struct LevelFound {
 // case: 2^31 entries in 8 operands take a thousand.)
 constexpr int kMostRounds = 1100;
 
-template <int K, class Acc, int kDepth>
+// kExact: as search_boundary.
+template <int K, class Acc, int kDepth, bool kExact>
 __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const Acc &crd, Ints32 pos_1, Ints32 pos_2, int l,
                                                         int h, int R, int total, int sh)
 {
@@ -332,7 +333,7 @@ __device__ __forceinline__ LevelFound<Acc> group_search(const Group<K> &g, const
         const C none_below = C(-1), none_above = Acc::kNone;
         const unsigned long long surely_before = __ballot(valid && hi_cost <= R), surely_behind = __ballot(valid && lo_cost > R);
         C vminus = none_below, vplus = none_above;
-        if constexpr (K <= 4) {
+        if constexpr (kExact) {
             // (the bounds ascend with the samples: the last lane of a group, the first one; by a reduction over all lanes two DCSR
             // matrices of 15k entries each 12.9 us, like this 12.6, of 20M 152.2 and 150.5)
 #pragma unroll
@@ -497,7 +498,7 @@ __device__ __forceinline__ LevelFound<Acc> split_search(const Group<2> &g, const
 }
 
 // One level of Algorithm 1 for one query, 0 <= R: as group_search, and what is shorter than that.
-template <int K, class Acc, int kDepth>
+template <int K, class Acc, int kDepth, bool kExact>
 __device__ __forceinline__ LevelFound<Acc> search_level(const DevOperands &ops, const Group<K> &g, int m, const Acc &crd,
                                                         Ints32 pos_1, Ints32 pos_2, int l, int h, int R, int total, int sh,
                                                         bool many = false)
@@ -530,14 +531,15 @@ __device__ __forceinline__ LevelFound<Acc> search_level(const DevOperands &ops, 
         }
         if constexpr (K == 2) return split_search<Acc>(g, Acc::of(ops, 0, m), Acc::of(ops, 1, m), l, h, R, sh, many);
     }
-    if constexpr (K > 1 || kDepth > 0) found = group_search<K, Acc, kDepth>(g, crd, pos_1, pos_2, l, h, R, total, sh);
+    if constexpr (K > 1 || kDepth > 0) found = group_search<K, Acc, kDepth, kExact>(g, crd, pos_1, pos_2, l, h, R, total, sh);
     return found;
 }
 
 // One wavefront searches boundary b (0 <= b <= P) and stores its coordinate, positions and cost.
 // kMode: 0 = vectors, CSR, DCSR; 1 = coordinate lists; 2 = three compressed levels (CSF).
 // found[t] (operands of one level only): operand t's position of the boundary, in every lane.
-// kExact: of exactly K operands, else of at most K.
+// kExact: of exactly K operands, else of at most K.  (A merge kernel that searches its own boundaries is not: it has no registers to
+// spare for the masks.)
 template <int K, int kMode, bool kExact = false>
 __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scale, int64_t P, int64_t grain,
                                                 const int64_t *__restrict__ queries, int64_t total_unscaled,
@@ -607,7 +609,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
         // coordinate lists, d == 2: one search over the (row, column) pairs; the row-level position of an operand is
         // that of its first entry in the boundary's row
         const PairCoords pairs = {ints_of([&](int t) { return ops.lvl[t][0].crd; }), ints_of([&](int t) { return ops.lvl[t][1].crd; })};
-        const auto f = search_level<K, PairCoords, 0>(ops, g, 0, pairs, nullptr, nullptr, 0, count_of(0), R, total, 0, P > 1024);
+        const auto f = search_level<K, PairCoords, 0, kExact>(ops, g, 0, pairs, nullptr, nullptr, 0, count_of(0), R, total, 0, P > 1024);
         R -= f.c;
         const int x0 = (int)(f.x >> 32), x1 = (int)(f.x & 0xffffffffLL);
         const int row_at = group_lower_bound<K>(g, f.row_from, f.p, [&](int at) { return pairs.row[at] < x0; });
@@ -623,12 +625,12 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
         // three compressed levels: Algorithm 1 level by level; a level's cost counts the
         // non-zeros below its entries (two pos arrays down at level 0, one at level 1)
         const Ints32 pos1 = pos_of(1), pos2 = pos_of(2);
-        const auto f0 = search_level<K, PlainCoords, 2>(ops, g, 0, plain(0), pos1, pos2, 0, count_of(0), R, total, 0);
+        const auto f0 = search_level<K, PlainCoords, 2, kExact>(ops, g, 0, plain(0), pos1, pos2, 0, count_of(0), R, total, 0);
         R -= f0.c;
-        const auto f1 = search_level<K, PlainCoords, 1>(ops, g, 1, plain(1), pos2, nullptr, f0.lo, f0.hi, R,
+        const auto f1 = search_level<K, PlainCoords, 1, kExact>(ops, g, 1, plain(1), pos2, nullptr, f0.lo, f0.hi, R,
                                                         g.sum(f0.deep_hi - f0.deep_lo), 0);
         R -= f1.c;
-        const auto f2 = search_level<K, PlainCoords, 0>(ops, g, 2, plain(2), nullptr, nullptr, f1.lo, f1.hi, R,
+        const auto f2 = search_level<K, PlainCoords, 0, kExact>(ops, g, 2, plain(2), nullptr, nullptr, f1.lo, f1.hi, R,
                                                         g.sum(f1.hi - f1.lo), 0);
         R -= f2.c;
         if (writer) {
@@ -642,7 +644,7 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
             cb[2] = f2.x;
         }
     } else if (d == 1) {
-        const auto f = search_level<K, PlainCoords, 0>(ops, g, 0, plain(0), nullptr, nullptr, 0, count_of(0), R, total, 0);
+        const auto f = search_level<K, PlainCoords, 0, kExact>(ops, g, 0, plain(0), nullptr, nullptr, 0, count_of(0), R, total, 0);
         R -= f.c;
 #pragma unroll
         for (int t = 0; t < K; ++t)
@@ -672,14 +674,14 @@ __device__ inline void search_boundary(const DevOperands &ops, int64_t cost_scal
                 if (present) sh = start[p0] - lo;
             }
         } else {
-            const auto f = search_level<K, PlainCoords, 1>(ops, g, 0, plain(0), pos1, nullptr, 0, count_of(0), R, total, 0);
+            const auto f = search_level<K, PlainCoords, 1, kExact>(ops, g, 0, plain(0), pos1, nullptr, 0, count_of(0), R, total, 0);
             R -= f.c;
             x0 = f.x;
             p0 = f.p;
             lo = f.lo;
             hi = f.hi;
         }
-        const auto f = search_level<K, PlainCoords, 0>(ops, g, 1, plain(1), nullptr, nullptr, lo, hi, R, g.sum(hi - lo), sh);
+        const auto f = search_level<K, PlainCoords, 0, kExact>(ops, g, 1, plain(1), nullptr, nullptr, lo, hi, R, g.sum(hi - lo), sh);
         R -= f.c;
         if (writer) {
             pb[0] = p0;
