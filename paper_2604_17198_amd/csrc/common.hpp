@@ -74,6 +74,14 @@ __host__ __device__ inline int shares_before(int at, int grain)
     return (int)(((unsigned)at + (unsigned)grain - 1u) / (unsigned)grain);
 }
 
+// Rows that the partition between the boundary rows r0 <= r1 may overlap or start, r1 among them where it is one (n_rows is not), at
+// most `most` of them.  (The least before the one that is added: a partition may span all of 2^31 - 1 rows.)
+__host__ __device__ inline int rows_spanned(int r0, int r1, int n_rows, int most)
+{
+    const int rows = r1 - r0 < n_rows - r0 ? r1 - r0 + 1 : n_rows - r0;
+    return rows < most ? rows : most;
+}
+
 // Asks for the first kBytes of the kernel's arguments at once.  They lie in memory that no cache holds at a kernel's
 // start; left to the places where they are used, every line of them is a round trip of its own.
 template <int kBytes> __device__ inline void touch_arguments()

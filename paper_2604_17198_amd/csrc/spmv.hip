@@ -143,9 +143,7 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     // the positions of the first row block: one lane a row, the first kAhead * 64 of them through registers, so that neither the
     // gathers wait for them nor they for the gathers
     constexpr int kAhead = 4;
-    int staged = r1 - r0 + 1;                          // rows that may overlap or start here, all but the last of which end here
-    staged = staged < n_rows - r0 ? staged : n_rows - r0;
-    staged = staged < RBLK ? staged : RBLK;
+    const int staged = rows_spanned(r0, r1, n_rows, RBLK);     // (all but the last of which end here)
     int row_pos[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
