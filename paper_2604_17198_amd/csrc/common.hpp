@@ -82,6 +82,28 @@ __host__ __device__ inline int rows_spanned(int r0, int r1, int n_rows, int most
     return rows < most ? rows : most;
 }
 
+// The row that a lane looks at in one round of a search of the rows [lo, hi), lo < hi: 64 evenly spaced ones, the last row for sure.
+// (Unsigned here and below: a place behind the range may lie past 2^31.)
+__host__ __device__ inline int row_probe(int lo, int hi, int lane)
+{
+    const unsigned step = ((unsigned)(hi - lo) + NACHO_WAVE - 1) / NACHO_WAVE, t = (unsigned)lo + (unsigned)lane * step;
+    return lane == NACHO_WAVE - 1 || t > (unsigned)hi - 1u ? hi - 1 : (int)t;
+}
+
+// One round of a search for a number of rows in [lo, hi] by kLanes lanes: lane i looks at the last of the rows it stands for, which is
+// in the range if it lies below hi; n lanes, the first ones, found theirs too small.
+template <int kLanes> struct RowRound {
+    unsigned lo, hi, step;
+    __host__ __device__ RowRound(int lo_, int hi_) : lo((unsigned)lo_), hi((unsigned)hi_), step((hi - lo + kLanes - 1) / kLanes) {}
+    __host__ __device__ unsigned at(int i) const { return lo + (unsigned)(i + 1) * step - 1u; }
+    __host__ __device__ void narrow(int n, int &lo_, int &hi_) const
+    {
+        const unsigned to = lo + (unsigned)n * step;
+        hi_ = (int)(n < kLanes && at(n) < hi ? at(n) : hi);
+        lo_ = to < (unsigned)hi_ ? (int)to : hi_;
+    }
+};
+
 // Asks for the first kBytes of the kernel's arguments at once.  They lie in memory that no cache holds at a kernel's
 // start; left to the places where they are used, every line of them is a round trip of its own.
 template <int kBytes> __device__ inline void touch_arguments()
@@ -208,10 +230,7 @@ __device__ inline int first_row_past(const int32_t *__restrict__ pos, int lo, in
 {
     const int lane = lane_id();
     while (hi - lo > 1) {
-        const int span = hi - lo;
-        const int step = (span + NACHO_WAVE - 1) / NACHO_WAVE;
-        int t = lo + lane * step;
-        if (lane == NACHO_WAVE - 1 || t > hi - 1) t = hi - 1;
+        const int t = row_probe(lo, hi, lane);
         const unsigned long long past = __ballot(pos[t + 1] > q);    // a suffix of the lanes, never empty
         const int L = __ffsll((long long)past) - 1;
         const int t_hit = __shfl(t, L, NACHO_WAVE);
@@ -223,7 +242,8 @@ __device__ inline int first_row_past(const int32_t *__restrict__ pos, int lo, in
 }
 
 // A search for the number of rows that end at or before q, which is also the row that holds position q: it lies in [lo, hi].
-// A round looks at 64 rows; its load and what follows from it are apart, so that other loads can be asked for between them.
+// A round looks at 64 rows; its load and what follows from it are apart, so that other loads can be asked for between them.  (Rows: a
+// few million at most, spmv_whole and spmm_whole with partitions of up to 128 non-zeros; sums with a lane's offset stay below 2^31.)
 struct RowWindow {
     int lo, hi;
     __device__ int stride() const { return (hi - lo + NACHO_WAVE - 1) / NACHO_WAVE; }
@@ -253,15 +273,11 @@ __device__ inline void rows_holding(const int32_t *__restrict__ pos, int n_rows,
     const unsigned long long half = lane < G ? 0xffffffffull : 0xffffffff00000000ull;
     int lo = 0, hi = n_rows;                           // the number of rows that end at or before q
     while (__ballot(lo < hi) != 0ull) {
-        const int step = (hi - lo + G - 1) / G;
-        const int at = lo + (sub + 1) * step - 1;
-        const bool before = lo < hi && at < hi && pos[at + 1] <= q;        // (a prefix of the half)
+        const RowRound<G> round(lo, hi);
+        const unsigned at = round.at(sub);
+        const bool before = lo < hi && at < round.hi && pos[at + 1u] <= q;     // (a prefix of the half)
         const int n = __popcll(__ballot(before) & half);
-        if (lo < hi) {
-            const int lo_new = lo + n * step, at_next = lo + (n + 1) * step - 1;
-            hi = n < G && at_next < hi ? at_next : hi;
-            lo = lo_new < hi ? lo_new : hi;
-        }
+        if (lo < hi) round.narrow(n, lo, hi);
     }
     ra = __builtin_amdgcn_readlane(lo, 0);
     rb = __builtin_amdgcn_readlane(lo, G);

@@ -223,18 +223,19 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         }
     }
 
-    for (int rb = 0; rb < nrows; rb += RBLK) {
+    // (unsigned: the block behind the last one may start past 2^31)
+    for (unsigned rb = 0; rb < (unsigned)nrows; rb += RBLK) {
         if (rb > 0) {
-            nr = nrows - rb < RBLK ? nrows - rb : RBLK;
+            nr = nrows - (int)rb < RBLK ? nrows - (int)rb : RBLK;
             wave_sync();
-            for (int i = lane; i <= nr; i += NACHO_WAVE) spos[i] = pos[r0 + rb + i];
+            for (int i = lane; i <= nr; i += NACHO_WAVE) spos[i] = pos[r0 + (int)rb + i];
             wave_sync();
             // A block of rows without entries: their zeros are written elsewhere (by the partition
             // kernel, or above), so the wavefront steps over them, however many there are.
             const int q = spos[0];
             if (q == spos[nr]) {
                 if (q >= n1) break;                     // every product of the partition is summed
-                rb = first_row_past(pos, r0 + rb + nr, r0 + nrows, q) - r0 - RBLK;
+                rb = (unsigned)(first_row_past(pos, r0 + (int)rb + nr, r0 + nrows, q) - r0) - RBLK;
                 continue;
             }
         }
@@ -268,7 +269,7 @@ spmv_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
                 if (lane == L) sum = s;
             }
             if (valid) {
-                const int r = r0 + rb + rr;
+                const int r = r0 + (int)rb + rr;
                 if (has_head && r == r0) carry_val[p] = sum;
                 else y[r] = sum;
             }

@@ -13,7 +13,10 @@ ROWS = 2**31 - 1
 COLS = 4000
 DTYPES = [np.float32, np.float64]
 # where the stored rows lie and how many non-zeros they have: one partition that spans all rows, and a few
-FIRST = {"one partition": {0: 5, 3: 60, 4: 1, 700: 200}, "several": {0: 900, 1: 1, 2: 47, 3: 3000, 5000: 48}}
+WHERE = {"first, one partition": {0: 5, 3: 60, 4: 1, 700: 200}, "first, several": {0: 900, 1: 1, 2: 47, 3: 3000, 5000: 48},
+         "last, one partition": {ROWS - 701: 5, ROWS - 513: 60, ROWS - 64: 1, ROWS - 1: 200},
+         "the last": {ROWS - 1: 3000}, "last, several": {ROWS - 2000: 900, ROWS - 63: 48, ROWS - 2: 3, ROWS - 1: 700},
+         "both ends": {2: 47, 2**30: 900, ROWS - 1030: 1, ROWS - 600: 2500, ROWS - 512: 3, ROWS - 1: 30}}
 
 
 def _tall(lens, dtype):
@@ -40,13 +43,14 @@ def _expect(got, rows, want, tag):
 
 def _spmv_forms():
     return {"P=0": lambda op, x, y: nb.nacho_spmv(op, x, y), "P=3": lambda op, x, y: nb.nacho_spmv(op, x, y, P=3),
-            "static": lambda op, x, y: nb.nacho_spmv_static(op, x, y)}
+            "static": lambda op, x, y: nb.nacho_spmv_static(op, x, y),
+            "fused": lambda op, x, y: nb.nacho_spmv_fused(op, x, y)}
 
 
 @pytest.mark.parametrize("dtype", DTYPES)
-@pytest.mark.parametrize("where", list(FIRST))
-def test_spmv_of_the_first_rows(where, dtype):
-    op, of_row, rows, crd, val = _tall(FIRST[where], dtype)
+@pytest.mark.parametrize("where", list(WHERE))
+def test_spmv(where, dtype):
+    op, of_row, rows, crd, val = _tall(WHERE[where], dtype)
     x = np.random.default_rng(9).integers(1, 9, COLS).astype(dtype)
     want = np.zeros(len(rows), dtype)
     np.add.at(want, of_row, val * x[crd])

@@ -66,3 +66,70 @@ static void check()
                     expect("rows", rows_spanned(r0, r1, (int)n, %d), std::min({Wide(r1) - r0 + 1, n - r0, Wide(%d)}));
 }
 """ % (", ".join(f"Wide({n})" for n in EXTENTS), most, most))
+
+
+SEARCH = r"""
+struct Rows {                                  // ascending stored rows, one non-zero each
+    std::vector<Wide> stored;
+    Wide n;
+    Wide pos(Wide r) const
+    {
+        expect("a position of the matrix", r >= 0 && r <= n, 1);
+        return std::lower_bound(stored.begin(), stored.end(), r) - stored.begin();
+    }
+};
+template <class Body> static void matrices(Body body)
+{
+    for (Wide n : {EXTENTS})
+        for (int from : edges(n))
+            for (Wide step : {Wide(1), Wide(70), n / 5 + 1}) {
+                Rows rows{{}, n};
+                for (Wide r = from; r < n && rows.stored.size() < 9; r += step) rows.stored.push_back(r);
+                body(rows);
+            }
+}
+// the rows that end at or before q, by rounds of kLanes lanes
+template <int kLanes> static Wide rows_before(const Rows &rows, Wide q)
+{
+    int lo = 0, hi = (int)rows.n, rounds = 0;
+    while (lo < hi && ++rounds < 40) {
+        const RowRound<kLanes> round(lo, hi);
+        int n = 0;
+        for (int i = 0; i < kLanes; ++i) n += round.at(i) < round.hi && rows.pos(Wide(round.at(i)) + 1) <= q;
+        round.narrow(n, lo, hi);
+    }
+    return lo;
+}
+static void check()
+{
+    matrices([](const Rows &rows) {
+        const Wide nnz = (Wide)rows.stored.size();
+        for (Wide q = 0; q <= nnz; ++q) {
+            const Wide want = q < nnz ? rows.stored[(size_t)q] : rows.n;
+            expect("32 lanes", rows_before<32>(rows, q), want);
+            expect("64 lanes", rows_before<64>(rows, q), want);
+        }
+        // first_row_past from any row up to the one that holds q
+        for (Wide q = 0; q < nnz; ++q)
+            for (int first : edges(rows.n)) {
+                if (rows.pos(first) > q) continue;
+                int lo = first, hi = (int)rows.n, rounds = 0;
+                while (hi - lo > 1 && ++rounds < 40) {
+                    int L = 0;
+                    while (L < 64 && rows.pos(Wide(row_probe(lo, hi, L)) + 1) <= q) ++L;
+                    expect("a lane past it", L < 64, 1);
+                    if (L == 64) break;
+                    const int hit = row_probe(lo, hi, L), before = row_probe(lo, hi, L > 0 ? L - 1 : 0);
+                    if (L > 0) lo = before + 1;
+                    hi = hit + 1;
+                }
+                expect("first row past", lo, std::max<Wide>(first, rows.stored[(size_t)q]));
+            }
+    });
+}
+"""
+
+
+def test_rounds_of_the_searches_for_rows(tmp_path):
+    """All rows of the largest matrix, and the last few of them."""
+    _run(tmp_path, SEARCH.replace("EXTENTS", ", ".join(f"Wide({n})" for n in EXTENTS)))
