@@ -116,25 +116,28 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     // the ends of the first 64 rows, and (kFew) of the first 64 of the rows whose zeros are this wavefront's: all rows are shared out
     // evenly (a large call is bound by what it has in flight: 40M non-zeros, 4 floats, 200 a row 340 us with them, 330 without)
     bool has_head;                                     // row r0 started in an earlier partition
-    int next_first, row, row_a, row_b, zero_a = 0, zero_b = 0;         // (the first row that starts after this partition)
+    // (the first row that starts after this partition; unsigned: a lane's row may lie past 2^31)
+    unsigned next_first, row;
+    int row_a, row_b, zero_a = 0, zero_b = 0;
     const unsigned share = kWhole ? ((unsigned)n_rows + gridDim.x - 1u) / gridDim.x : 0u;
     int z0 = 0, z1 = 0;
     auto rows = [&]() {
         const int pr0 = pos[r0], pr1 = pos[r1];
-        row = r0 + lane;
+        row = (unsigned)r0 + (unsigned)lane;
         row_a = row_b = 0;
         if (kWhole) {
             z0 = p * share < (unsigned)n_rows ? (int)(p * share) : n_rows;     // (unsigned: may lie past 2^31)
             z1 = n_rows - z0 < (int)share ? n_rows : z0 + (int)share;
         }
         if constexpr (kFew) {                          // (no branches between the loads)
-            row_a = pos[row < n_rows ? row : n_rows];
-            row_b = pos[row + 1 < n_rows ? row + 1 : n_rows];
+            const unsigned end = (unsigned)n_rows;
+            row_a = pos[row < end ? row : end];
+            row_b = pos[row + 1 < end ? row + 1 : end];
             zero_a = pos[z0 + lane < n_rows ? z0 + lane : n_rows];
             zero_b = pos[z0 + lane + 1 < n_rows ? z0 + lane + 1 : n_rows];
         }
         has_head = n0 > pr0;
-        next_first = n1 > pr1 ? r1 + 1 : r1;
+        next_first = (unsigned)r1 + (n1 > pr1 ? 1u : 0u);
         if constexpr (kFew) {
             if (row >= next_first) row_a = row_b = 0;
         } else {
@@ -232,8 +235,8 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
     unsigned long long empty = kFew ? __ballot(z0 + lane < z1 && zero_a == zero_b) : 0ull;
     wave_sync();
     auto write_zeros = [&]() {
-        for (int z = z0; z < z1; z += NACHO_WAVE) {
-            if (!kFew || z > z0) empty = __ballot(z + lane < z1 && pos[z + lane] == pos[z + lane + 1]);
+        for (unsigned z = (unsigned)z0; z < (unsigned)z1; z += NACHO_WAVE) {
+            if (!kFew || z > (unsigned)z0) empty = __ballot(z + lane < (unsigned)z1 && pos[z + lane] == pos[z + lane + 1]);
             if (empty == 0ull) continue;
             for (int i = g; i < NACHO_WAVE; i += NG)
                 if (bit_at(empty, i)) {
@@ -251,16 +254,16 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         if (is_row && row_b > row_a && row_a >= n0) {
             const int i = row_a - n0;                  // (< len: the row starts in this partition)
             const int at = (int)(((float)i + 0.5f) * per_S);       // i / S
-            s_row[i + 4 * at] = row;
+            s_row[i + 4 * at] = (int)row;
         }
-        const int next = __builtin_amdgcn_readfirstlane(row) + NACHO_WAVE;
+        const unsigned next = (unsigned)__builtin_amdgcn_readfirstlane((int)row) + NACHO_WAVE;
         if (next >= next_first) break;
-        int from = next;
+        unsigned from = next;
         if (__ballot(row_b > row_a) == 0ull) {
             // 64 rows without an entry: however many there are, stepped over
             const int q = __builtin_amdgcn_readfirstlane(row_b);
             if (q >= n1) break;
-            from = first_row_past(pos, next, next_first, q);
+            from = (unsigned)first_row_past(pos, (int)next, (int)next_first, q);
         }
         row = from + lane;
         row_a = row_b = 0;

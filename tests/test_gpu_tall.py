@@ -60,3 +60,19 @@ def test_spmv(where, dtype):
         y.fill_(float("nan"))
         call(op, dev(x), y)
         _expect(y, rows, want, tag)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("where", list(WHERE))
+def test_spmm(where, dtype):
+    op, of_row, rows, crd, val = _tall(WHERE[where], dtype)
+    for n in (1, 2):
+        B = np.random.default_rng(9).integers(1, 9, (COLS, n)).astype(dtype)
+        want = np.zeros((len(rows), n), dtype)
+        np.add.at(want, of_row, val[:, None] * B[crd])
+        for P in (0, 3):
+            print(f"tall spmm {where} {np.dtype(dtype).name} n={n} P={P}", flush=True)
+            C = torch.full((ROWS, n), float("nan"), dtype=dev(B).dtype, device="cuda")
+            nb.nacho_spmm(op, dev(B), C, P=P)
+            _expect(C, rows, want, (n, P))
+            del C
