@@ -74,11 +74,14 @@ __host__ __device__ inline int shares_before(int at, int grain)
     return (int)(((unsigned)at + (unsigned)grain - 1u) / (unsigned)grain);
 }
 
+// The row behind a boundary's row; the boundary may lie behind all rows already, of which there may be 2^31 - 1.
+__host__ __device__ inline int row_behind(int row, int n_rows) { return row < n_rows ? row + 1 : n_rows; }
+
 // Rows that the partition between the boundary rows r0 <= r1 may overlap or start, r1 among them where it is one (n_rows is not), at
-// most `most` of them.  (The least before the one that is added: a partition may span all of 2^31 - 1 rows.)
+// most `most` of them.
 __host__ __device__ inline int rows_spanned(int r0, int r1, int n_rows, int most)
 {
-    const int rows = r1 - r0 < n_rows - r0 ? r1 - r0 + 1 : n_rows - r0;
+    const int rows = row_behind(r1, n_rows) - r0;
     return rows < most ? rows : most;
 }
 

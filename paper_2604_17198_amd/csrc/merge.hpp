@@ -511,7 +511,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             if constexpr (kWindow) {
                 const int most = level_count(t, D - 2), next = table_pos(p + 1, t, D - 2);
                 ilo_v = put(ilo_v, t, table_pos(p, t, D - 2));
-                ihi_v = put(ihi_v, t, next + 1 < most ? next + 1 : most);
+                ihi_v = put(ihi_v, t, row_behind(next, most));
                 if (FMT == SPADD_CSR) next_seg_v = put(next_seg_v, t, next);
                 if constexpr (kCsf) {
                     const int last = level_count(t, 0) - 1, up = table_pos(p + 1, t, 0);
@@ -769,7 +769,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     if (FMT == SPADD_CSR) {
                         const int i_next = of(next_seg_v, t);
                         if (i_next < i_hi) {                       // (uniform)
-                            if (i_next < i_lo + kThreads) { if (tid == i_next - i_lo && q + len > a0) w.cont_next = 1u; }
+                            if (i_next - i_lo < kThreads) { if (tid == i_next - i_lo && q + len > a0) w.cont_next = 1u; }
                             else if (tid == 0 && q + len > seg_pos[t][i_next]) w.cont_next = 1u;
                         }
                     }
@@ -822,15 +822,17 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
                 for (int u = 0; u < kAhead; ++u)
                     mark_segment(u * kThreads + tid, seg_a[t][u], seg_b[t][u], seg_id[t][u]);
-                for (int i = tid + kAhead * kThreads; i < i_hi - i_lo; i += kThreads * kMore) {
+                // (unsigned, as rows below: a segment behind the last one may lie past 2^31)
+                const unsigned segments = (unsigned)(i_hi > i_lo ? i_hi - i_lo : 0);
+                for (unsigned i = (unsigned)(tid + kAhead * kThreads); i < segments; i += kThreads * kMore) {
                     int a[kMore], b[kMore], id[kMore];
 #pragma unroll
                     for (int u = 0; u < kMore; ++u) {
                         a[u] = b[u] = id[u] = 0;
-                        if (i + u * kThreads < i_hi - i_lo) load_segment(t, i + u * kThreads, a[u], b[u], id[u]);
+                        if (i + u * kThreads < segments) load_segment(t, (int)(i + u * kThreads), a[u], b[u], id[u]);
                     }
 #pragma unroll
-                    for (int u = 0; u < kMore; ++u) mark_segment(i + u * kThreads, a[u], b[u], id[u]);
+                    for (int u = 0; u < kMore; ++u) mark_segment((int)(i + u * kThreads), a[u], b[u], id[u]);
                 }
             }
             // the sentinel of a run: a row start whose row field is all ones, as its column is
@@ -1470,7 +1472,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     if (FMT == SPADD_CSR) {
         first_row = row0 + (w.cont ? 1 : 0);
         end_row = table_coord(p + 1, 0) + (int)w.cont_next;
-        if (first_row + tid < end_row) pos_at = places_before(first_row + tid);
+        if ((unsigned)first_row + (unsigned)tid < (unsigned)end_row) pos_at = places_before(first_row + tid);
     }
 
     // ---- the keys of the output entries, and what else the sums and products need ----------------
@@ -1710,8 +1712,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     if (FMT == SPADD_CSR) {
         // pos of every row that starts inside this partition: the output entries before its first place
         NACHO_GLOBAL int32_t *pos_out = global_out(out.pos1);
-        for (int row = first_row + tid; row < end_row; row += kThreads) {
-            const int m = row == first_row + tid ? pos_at : places_before(row);
+        const unsigned mine = (unsigned)first_row + (unsigned)tid;
+        for (unsigned row = mine; row < (unsigned)end_row; row += kThreads) {
+            const int m = row == mine ? pos_at : places_before((int)row);
             const int b = m / NACHO_WAVE;
             int before = own_nnz;
             if (b < NB) before = w.wave_before[b / R] + w.block_before[b] +

@@ -76,3 +76,58 @@ def test_spmm(where, dtype):
             nb.nacho_spmm(op, dev(B), C, P=P)
             _expect(C, rows, want, (n, P))
             del C
+
+
+def _rows_of(pos):
+    """The row of every entry, from a pos array on the GPU (as it has so many rows, in stretches)."""
+    found = []
+    for r in range(0, ROWS, 1 << 28):
+        part = pos[r:min(r + (1 << 28), ROWS) + 1]
+        lens = part[1:] - part[:-1]
+        at = torch.nonzero(lens)[:, 0]
+        found.append(torch.repeat_interleave(at + r, lens[at].long()))
+    return torch.cat(found)
+
+
+def _csr_of(keys, val):
+    """A matrix of ROWS rows from its entries (row * COLS + column, ascending), on the GPU."""
+    rows = keys // COLS
+    pos = torch.empty(ROWS + 1, dtype=torch.int32, device="cuda")
+    for r in range(0, ROWS + 1, 1 << 27):
+        part = torch.arange(r, min(r + (1 << 27), ROWS + 1), device="cuda")
+        pos[r:r + len(part)] = torch.searchsorted(rows, part, out_int32=True)
+    return nb.csr(pos, (keys % COLS).to(torch.int32), ROWS, COLS, val)
+
+
+# spread: entries of every operand all over the rows (none: one partition that spans all of them); end: in the last rows
+@pytest.mark.parametrize("name,operands,spread,end", [("spadd", 2, 3_000_000, 500_000), ("spmul", 2, 3_000_000, 500_000),
+                                                      ("spadd", 4, 1_500_000, 40_000), ("spmul", 4, 1_500_000, 40_000),
+                                                      ("spadd", 2, 0, 400)])
+def test_sums_and_products(name, operands, spread, end):
+    """Operands that share half of their entries; partitions start and end in the last rows."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(spread + operands)
+    some = lambda lo, hi, n: torch.randint(lo, hi, (n,), dtype=torch.int64, device="cuda", generator=gen)
+    entries = lambda first, n: some(first, ROWS, n) * COLS + some(0, COLS, n)
+    common = torch.cat([entries(0, spread // 2), entries(ROWS - 700, end // 2)])
+    ops, keys, vals = [], [], []
+    for t in range(operands):
+        keys.append(torch.unique(torch.cat([common, entries(0, spread // 2), entries(ROWS - 70, end // 2)])))
+        vals.append(some(1, 9, len(keys[t])).to(torch.float32))
+        ops.append(_csr_of(keys[t], vals[t]))
+    every, place, times = torch.unique(torch.cat(keys), return_inverse=True, return_counts=True)
+    if name == "spadd":
+        want = torch.zeros(len(every), dtype=torch.float32, device="cuda").index_add_(0, place, torch.cat(vals))
+    else:
+        want = torch.ones(len(every), dtype=torch.float32, device="cuda")
+        for k, v in zip(keys, vals):
+            want[torch.searchsorted(every, k)] *= v
+        every, want = every[times == operands], want[times == operands]
+    print(f"tall {name} {operands} operands, {len(every)} entries", flush=True)
+    out = nb.SparseOut("csr", 0, len(every), torch.float32, "cuda", n_rows=ROWS)
+    (nb.nacho_spadd_k if name == "spadd" else nb.nacho_spmul_k)(ops, out)
+    torch.cuda.synchronize()
+    assert int(out.status[0]) == 0 and out.counts[:2].tolist() == [ROWS, len(every)]
+    assert int(out.pos1[0]) == 0 and int(out.pos1[ROWS]) == len(every)
+    assert torch.equal(_rows_of(out.pos1), every // COLS)
+    assert torch.equal(out.crd1[:len(every)].long(), every % COLS) and torch.equal(out.val[:len(every)], want)

@@ -61,9 +61,11 @@ static void check()
 {
     for (Wide n : {%s})
         for (int r0 : edges(n))
-            for (int r1 : edges(n))
+            for (int r1 : edges(n)) {
+                expect("row behind", row_behind(r1, (int)n), std::min(Wide(r1) + 1, n));
                 if (r0 <= r1)
                     expect("rows", rows_spanned(r0, r1, (int)n, %d), std::min({Wide(r1) - r0 + 1, n - r0, Wide(%d)}));
+            }
 }
 """ % (", ".join(f"Wide({n})" for n in EXTENTS), most, most))
 
