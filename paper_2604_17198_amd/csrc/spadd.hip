@@ -67,13 +67,16 @@ MergeFields merge_fields(int fmt, int dtype, int k, int64_t rows, int64_t cols, 
     else if ((fmt == SPADD_CSR || fmt == SPADD_DCSR) && dtype == NACHO_F32 && !fits(MERGE_MIDDLE, 2) && fits(MERGE_LONG, 2)) f.size = MERGE_LONG;
     else f.size = MERGE_MIDDLE;
     if (fmt == SPADD_VECTOR) return f;
-    // Values asked for ahead: coordinate lists and tensors past a few million entries, whose values come from memory itself and whose partitions ask for
-    // little else beside their merge.  us without and with it: two lists of floats, 5M, 6M, 8M, 20M 37.0, 42.0, 57.3, 120.7 and 34.4, 37.1, 54.2, 117.9;
-    // of doubles, 3.5M, 4.5M, 6M, 20M 30.1, 40.1, 55.4, 144.9 and 29.6, 35.0, 51.2, 144.3; three of doubles, 5M, 12M, 35M 0.91, 0.98 and 1.02 of the time;
-    // two tensors of floats, 2.5M, 4.5M, 6M, 35M 0.99, 0.95, 0.96, 0.97, of doubles, 1.5M, 4.5M, 12M 1.04, 0.93, 1.00; three 1.01, 0.95, 1.02.  Not five
-    // (1.01), products, which ask for few, or other formats (two vectors of doubles, 5M 1.10, two CSR matrices, 20M 1.07: their values' lines
-    // leave the L2s again before the places ask for them).
-    if (fmt == SPADD_COO) f.touch = (k == 2 || (k == 3 && total <= 14'000'000)) && f.size != MERGE_SHORT;
+    // Values asked for ahead: coordinate lists past what short partitions hold (some 1.25M entries, whatever the keys) and tensors past a few
+    // million, whose values come from memory itself and whose partitions ask for little else beside their merge.  us without and with it, the
+    // same operands again and operands that no cache holds: two lists of floats, 1.6M 22.2, 22.2 and 26.2, 25.8, 2.5M 25.9, 25.2 and 29.7, 29.1,
+    // 4.5M 33.0, 33.1 and 40.1, 37.4; of doubles 23.6, 23.7 and 27.7, 27.4, 27.4, 27.3 and 32.5, 31.7, 35.5, 35.1 and 45.2, 41.5; three of
+    // doubles 37.5, 37.6 and 39.3, 39.1, 39.4, 39.3 and 45.6, 43.7, 49.2, 49.2 and 57.7, 54.6 (of floats the same but for 3 %).  The same operands
+    // again, two lists of floats, 5M, 6M, 8M, 20M 37.0, 42.0, 57.3, 120.7 and 34.4, 37.1, 54.2, 117.9; of doubles, 6M, 20M 55.4, 144.9 and 51.2, 144.3;
+    // three of doubles, 5M, 12M, 35M 0.91, 0.98 and 1.02 of the time; two tensors of floats, 2.5M, 4.5M, 6M, 35M 0.99, 0.95, 0.96, 0.97, of
+    // doubles, 1.5M, 4.5M, 12M 1.04, 0.93, 1.00; three 1.01, 0.95, 1.02.  Not five (1.01), products, which ask for few, or other formats (two
+    // vectors of doubles, 5M 1.10, two CSR matrices, 20M 1.07: their values' lines leave the L2s again before the places ask for them).
+    if (fmt == SPADD_COO) f.touch = !fits(MERGE_SHORT, short_ones) && (k == 2 || (k == 3 && total <= 14'000'000));
     else if (fmt == SPADD_CSF3 && total >= 3'200'000)
         f.touch = dtype == NACHO_F32 ? k == 2 : (k <= 3 && fits(MERGE_LONG, resident));
     const int64_t per = total > 0 ? total : 1;

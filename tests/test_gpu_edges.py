@@ -584,3 +584,19 @@ def test_sums_whose_values_are_asked_for_ahead(shares, dtype):
         csf3._check([csf3._tensor(np.stack(np.unravel_index(k, shape), 1), v) for k, v in zip(keys, vals)], shape, 0, "values ahead")
         flat = (shape[0] * shape[1], shape[2])
         coo._check(nb.nacho_spadd_k, oracle.spadd_coo, [np.stack([k // flat[1], k % flat[1]], 1) for k in keys], vals, flat, 0, "values ahead")
+
+
+@pytest.mark.parametrize("dtype,shares,total", [(d, s, t) for d in DTYPES for s in [(0.5, 0.5), (1.0, 0.0), (0.6, 0.3, 0.1), (0.3, 0.3, 0.3, 0.1)]
+                                                for t in (1_249_280, 1_249_281)] +
+                         [(np.float32, (0.4, 0.35, 0.25), t) for t in (14_000_000, 14_000_001)])
+def test_lists_whose_values_are_asked_for_ahead(shares, total, dtype):
+    """Two and three coordinate lists on both sides of the entries from which a partition asks for the lines of its values beside its
+    merge, three lists on both sides of those up to which it does, and four, which never do."""
+    rng = np.random.default_rng(len(shares))
+    shape = (90_000, 40_001)
+    counts = [int(total * s) for s in shares[:-1]]
+    counts.append(total - sum(counts))
+    keys = [np.sort(rng.permutation(np.unique(rng.integers(0, shape[0] * shape[1], n + n // 10 + 2, dtype=np.int64)))[:n]) for n in counts]
+    assert sum(len(k) for k in keys) == total
+    coo._check(nb.nacho_spadd_k, oracle.spadd_coo, [np.stack([k // shape[1], k % shape[1]], 1) for k in keys],
+               [rng.uniform(-1, 1, len(k)).astype(dtype) for k in keys], shape, 0, "lists ahead")
