@@ -396,11 +396,12 @@ constexpr int kGrainF64 = 512, kGrainF32 = 1024, kShortGrainF32 = 512;
 int spmv_capacity(int dtype) { return dtype == NACHO_F64 ? kGrainF64 : kGrainF32; }
 
 // Floats, P = 0.  A wavefront's loads, sums and stores are one chain of latencies, so twice as many wavefronts, half as long, are faster
-// where few are in flight and where the chain has many rows to sum (partitions of 1024 and of 512 non-zeros, us: 50,000, 5 a row 11.2 and 8.8;
-// 2M, 5, 10, 20 a row 25.7, 21.0, 16.4 and 22.1, 18.6, 15.7; 10M, 5, 10, 20, 40 a row 78.6, 59.2, 49.5, 45.6 and 72.5, 54.9, 46.2, 43.0).
-// Rows of many non-zeros are summed at a stretch, and 5000 wavefronts of 1024 non-zeros hold more loads in flight than 8192 of 512: 60, 100,
-// 300 a row, 4M 20.9, 19.6, 18.0 and 22.6, 21.7, 19.8, 5M 24.6, 23.5, 21.3 and 26.8, 25.4, 23.0; but 1.5M 12.2, 11.4, 10.5 and 11.9, 11.3, 10.6.  Past
-// one round of wavefronts of either length the short ones draw level (8M 36.2, 34.6, 31.2 and 35.1, 34.4, 32.7, 50M 178, 170, 162 and 173, 163, 157).
+// where few are in flight and where the chain has many rows to sum (partitions of 1024 and of 512 non-zeros, us: 50,000, 5 a row 11.2
+// and 8.8; 2M, 5, 10, 20 a row 25.7, 21.0, 16.4 and 22.1, 18.6, 15.7; 10M, 5, 10, 20, 40 a row 78.6, 59.2, 49.5, 45.6 and 72.5, 54.9,
+// 46.2, 43.0).  Rows of many non-zeros are summed at a stretch, and 5000 wavefronts of 1024 non-zeros hold more loads in flight than 8192
+// of 512: 60, 100, 300 a row, 4M 20.9, 19.6, 18.0 and 22.6, 21.7, 19.8, 5M 24.6, 23.5, 21.3 and 26.8, 25.4, 23.0; 1.5M 12.2, 11.4, 10.5
+// and 11.9, 11.3, 10.6.  Past one round of wavefronts of either length that is over, and long ones, which such calls still take, lose
+// 3 to 4 % where rows are not very long: 8M 36.2, 34.6, 31.2 and 35.1, 34.4, 32.7, 50M 178, 170, 162 and 173, 163, 157.
 // Tables of a caller's P and of the row-aware cost have up to 1024.
 int64_t spmv_grain(int dtype, int64_t nnz, int64_t n_rows)
 {
@@ -409,14 +410,18 @@ int64_t spmv_grain(int dtype, int64_t nnz, int64_t n_rows)
 }
 
 // Small calls do without a partition kernel: its place in the stream (a launch and 3 us) is a third of what such a call takes, and the
-// wavefronts' search for their rows travels beside their non-zeros.  More than 1024 partitions only while x fits an L2, more than 4096 only where
-// it leaves most of one: partitions inside long rows are not dealt out by XCD in this form (50M non-zeros: 298 to 467 us without).  With and without
-// the partition kernel, us: doubles, x of 2.4 to 3.2 MB, 1.5M 22.7 and 21.2, 2M 26.6 and 25.5, 3M (5860 partitions) 30.0 and 28.7, 4M (7813) 35.9 and 36.5;
-// x of 4.8 MB, 3M 33.1 and 34.4; x of 0.7 and 2 MB, 5M (9766) 34.0, 37.5 and 32.1, 37.5; 8M (15625) 47.9 and 49.3.  Short partitions of floats count
-// half, whose search is a larger share of a wavefront; past 4096 of them the two forms are level while rows are few (20 a row, 2.6M 20.6 and 20.0, 3M 21.7
-// and 21.8, 6M 31.9 and 31.3) and the search loses where they are not (10 a row, 3M 23.6 and 24.1, 5M 31.7 and 34.1).  With more rows than the
-// wavefronts can look after in one batch of loads each the partition kernel writes the zeros, a row a thread (40,000 non-zeros in the first
-// 4096 of 131072 rows: 63 to 17 us).
+// wavefronts' search for their rows travels beside their non-zeros.  Short partitions of floats count half, whose search is a larger
+// share of a wavefront.  Up to 1024 partitions, counted so, with any x; past them partitions inside long rows would have to be dealt out
+// by XCD, which this form does not do, unless x fits an L2 of 4 MiB (50M non-zeros: 298 to 467 us without).  With and without the partition
+// kernel, us:
+//   Up to 4096 partitions, whatever their length, x of 4 MiB: doubles, x of 2.4 to 3.2 MB, 1.5M 22.7 and 21.2, 2M 26.6 and 25.5.
+//   Past 4096 doubles with x of 2.5 MiB, which leaves L2 for the rest, up to 10240 partitions: x of 0.7 and 2 MB, 5M (9766) 34.0, 37.5 and
+//   32.1, 37.5; 8M (15625) 47.9 and 49.3; x of 2.4 to 3.2 MB, 3M (5860) 30.0 and 28.7, 4M (7813) 35.9 and 36.5; of 4.8 MB, 3M 33.1 and 34.4.
+//   Past 4096 floats with x of 4 MiB and 131,072 rows up to 10240 short or 8192 long ones: level while rows are few (short ones, 20 a row,
+//   2.6M 20.6 and 20.0, 3M 21.7 and 21.8, 6M 31.9 and 31.3), and the search loses where they are not (10 a row, 3M 23.6 and 24.1, 5M 31.7
+//   and 34.1).
+// With more than 256 rows a partition (counted as above), which the wavefronts could not look after in one batch of loads each, the
+// partition kernel writes the zeros, a row a thread (40,000 non-zeros in the first 4096 of 131072 rows: 63 to 17 us).
 bool spmv_whole(int dtype, int64_t nnz, int64_t grain, int64_t P, int64_t n_rows, int64_t x_bytes)
 {
     if (nnz == 0) return false;                        // (its wavefronts expect non-zeros)

@@ -50,3 +50,36 @@ def test_sums_that_ask_for_their_values_ahead(ask):
                       (_ahead("SPADD_CSF3", dtype, k, long + 1, 60, 60), int(k == 2 and dtype == nb.F32))]
             cases += [(_ahead(f"SPADD_{fmt}", dtype, k, 10_000_000), 0) for fmt in ("VECTOR", "CSR", "DCSR")]
     assert ask([e for e, _ in cases]) == [want for _, want in cases]
+
+
+def _whole(dtype, nnz, n_rows, x_bytes):
+    grain = f"spmv_grain({dtype}, {nnz}, {n_rows})"
+    return f"spmv_whole({dtype}, {nnz}, {grain}, ({nnz} + {grain} - 1) / {grain}, {n_rows}, {x_bytes}LL)"
+
+
+MB4, ANY = 4 << 20, 1 << 33
+
+
+def test_spmv_without_a_partition_kernel(ask):
+    """Up to 1024 partitions (short ones of floats count half) whatever x, up to 4096 of either kind while x fits an L2 (4 MiB); past
+    them doubles up to 10240 with 2.5 MiB of x, floats up to 8192 long or 10240 short ones with 4 MiB and 131,072 rows.  256 rows a partition
+    (two short ones) at most."""
+    F, D = nb.F32, nb.F64
+    cases = [
+        ((D, 0, 100, 8), 0), ((D, 1, 256, 8), 1), ((D, 1, 257, 8), 0), ((D, 513, 512, 8), 1), ((D, 513, 513, 8), 0),
+        ((F, 513, 256, 8), 1), ((F, 513, 257, 8), 0), ((F, 1025, 512, 8), 1), ((F, 1025, 513, 8), 0),
+        # doubles: 1024, 4096, 10240 partitions of 512
+        ((D, 1024 * 512, 9, ANY), 1), ((D, 1024 * 512 + 1, 9, MB4), 1), ((D, 1024 * 512 + 1, 9, MB4 + 8), 0),
+        ((D, 4096 * 512, 9, MB4), 1), ((D, 4096 * 512, 9, MB4 + 8), 0), ((D, 4096 * 512, 4096 * 256, MB4), 1),
+        ((D, 4096 * 512 + 1, 9, 5 << 19), 1), ((D, 4096 * 512 + 1, 9, (5 << 19) + 8), 0),
+        ((D, 10240 * 512, 9, 5 << 19), 1), ((D, 10240 * 512 + 1, 9, 8), 0), ((D, 10240 * 512, 10240 * 256, 8), 1),
+        # floats, short partitions (fewer than 48 a row): 2048, 4096, 10240 of 512
+        ((F, 2048 * 512, 100_000, ANY), 1), ((F, 2048 * 512 + 1, 100_000, MB4), 1), ((F, 2048 * 512 + 1, 100_000, MB4 + 4), 0),
+        ((F, 4096 * 512, 131_073, MB4), 1), ((F, 4096 * 512 + 1, 131_073, 4), 0), ((F, 4096 * 512 + 1, 131_072, MB4), 1),
+        ((F, 4096 * 512 + 1, 131_072, MB4 + 4), 0), ((F, 10240 * 512, 131_072, MB4), 1), ((F, 10240 * 512 + 1, 131_072, MB4), 0),
+        # floats, long ones (1.4M non-zeros and 48 a row): 4096, 8192 of 1024
+        ((F, 1_400_000, 9, MB4), 1), ((F, 1_400_000, 9, MB4 + 4), 0), ((F, 4096 * 1024, 80_000, MB4), 1),
+        ((F, 4096 * 1024 + 1, 80_000, MB4 + 4), 0), ((F, 8192 * 1024, 131_072, MB4), 1), ((F, 8192 * 1024, 131_073, MB4), 0),
+        ((F, 8192 * 1024 + 1, 131_072, 4), 0),
+    ]
+    assert ask([_whole(*c) for c, _ in cases]) == [want for _, want in cases]

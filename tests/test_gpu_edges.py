@@ -600,3 +600,39 @@ def test_lists_whose_values_are_asked_for_ahead(shares, total, dtype):
     assert sum(len(k) for k in keys) == total
     coo._check(nb.nacho_spadd_k, oracle.spadd_coo, [np.stack([k // shape[1], k % shape[1]], 1) for k in keys],
                [rng.uniform(-1, 1, len(k)).astype(dtype) for k in keys], shape, 0, "lists ahead")
+
+
+# (non-zeros and rows on either side of the calls that do without a partition kernel, and the columns on either side of those)
+WHOLE_LINES = [(np.float64, 524_289, 50_000, 524_288), (np.float64, 2_097_152, 200_000, 524_288),
+               (np.float64, 2_097_153, 200_000, 327_680), (np.float64, 5_242_880, 400_000, 327_680),
+               (np.float64, 5_242_881, 400_000, 327_680),
+               (np.float32, 1_048_577, 100_000, 1_048_576), (np.float32, 2_097_152, 131_073, 1_048_576),
+               (np.float32, 2_097_153, 131_072, 1_048_576), (np.float32, 2_097_153, 131_073, 1_048_576),
+               (np.float32, 5_242_880, 131_072, 1_048_576), (np.float32, 5_242_881, 131_072, 1_048_576),
+               (np.float32, 1_400_000, 20_000, 1_048_576), (np.float32, 4_194_305, 60_000, 1_048_576),
+               (np.float32, 8_388_608, 131_072, 1_048_576), (np.float32, 8_388_609, 131_072, 1_048_576)]
+
+
+@pytest.mark.parametrize("dtype,nnz,n_rows,n_cols", WHOLE_LINES)
+def test_spmv_with_and_without_a_partition_kernel(dtype, nnz, n_rows, n_cols):
+    """The same matrix with a column more, whose x is past what a call without a partition kernel may have: the same bits, and the
+    oracle's values.  Rows of all lengths, empty ones, one that spans many partitions."""
+    rng = np.random.default_rng(nnz % 1009)
+    stored = np.union1d(np.flatnonzero(rng.random(n_rows) < 0.8), [n_rows // 3, n_rows - 1])
+    lens = np.zeros(n_rows, np.int64)
+    lens[stored] = rng.integers(0, max(1, nnz // (2 * n_rows)) + 1, len(stored))
+    lens[n_rows // 3] = min(n_cols, nnz // 5)
+    more, rest = divmod(nnz - int(lens.sum()), len(stored))
+    lens[stored] += more
+    lens[stored[:rest]] += 1
+    lens = np.minimum(lens, n_cols)
+    lens[-1] += nnz - int(lens.sum())
+    pos = np.zeros(n_rows + 1, np.int32)
+    pos[1:] = np.cumsum(lens)
+    at = np.arange(nnz) - np.repeat(pos[:-1].astype(np.int64), lens)
+    crd = (at * n_cols // np.repeat(np.maximum(lens, 1), lens)).astype(np.int32)
+    A = {"n_rows": n_rows, "n_cols": n_cols, "pos": pos, "crd": crd, "val": rng.uniform(-1, 1, nnz).astype(dtype)}
+    x = rng.uniform(-1, 1, n_cols).astype(dtype)
+    y = spmv._check(A, x, 0, "without")
+    wider = spmv._check(dict(A, n_cols=n_cols + 1), np.append(x, dtype(1)), 0, "with")
+    assert np.array_equal(y.view(np.uint8), wider.view(np.uint8))
