@@ -230,9 +230,9 @@ struct Tile {
     uint32_t wave_counts[kWaves], wave_slices[kWaves];         // emitted | row heads << 16; slice heads
     int32_t wave_before[kWaves];          // CSR: emitted by the wavefronts before
     uint16_t behind[kWaves][kMaxRuns];    // products: order words of the places behind a wavefront's last one
-    unsigned long long sval[kMaxRuns];    // address of the values of run t, biased: [staged word] is the entry's
-    unsigned long long scol[kMaxRuns];    // the same for the columns (remapped operands)
-    unsigned long long srow[kMaxRuns];    // coordinate lists: the same for the rows; remapped operands: start[t]
+    unsigned long long sval[kMaxRuns];    // sums: address of the values of run t, biased: [staged word] is the entry's
+    unsigned long long scol[kMaxRuns];    // remapped operands: the same for the columns
+    unsigned long long srow[kMaxRuns];    // remapped operands: start[t]
     unsigned long long spos[kMaxRuns];    // remapped operands: pos of run t
     uint32_t cont, cont_next, cont_slice; // does the partition (the next one) start inside a row / slice
     uint32_t overflow;                    // the rows do not fit the key's row field
@@ -683,7 +683,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             const int64_t bias = of(q_v, t) - of(sb_v, t);
-            val_v = put2(val_v, t, arg_ptr->vals.v[t], bias * (int64_t)sizeof(T));
+            if constexpr (!kMul) val_v = put2(val_v, t, arg_ptr->vals.v[t], bias * (int64_t)sizeof(T));
             if (kMapped) {
                 col_v = put2(col_v, t, arg_ptr->ops.lvl[t][1].crd, bias * 4);
                 row_v = put2(row_v, t, arg_ptr->ops.start[t], 0);
@@ -691,7 +691,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
             }
         }
         if (lane < K) {
-            w.sval[lane] = val_v;
+            if constexpr (!kMul) w.sval[lane] = val_v;
             if (kMapped) w.srow[lane] = row_v;
             if (kMapped) { w.scol[lane] = col_v; w.spos[lane] = pos_v; }
             // (the copies leave the word behind a run's last entry alone: its sentinel)
