@@ -442,7 +442,7 @@ spmm_fixup_kernel(T *__restrict__ C, int64_t ldc, int n, int P, const T *__restr
     const int at_long = __ffsll((long long)longer) - 1, first_long = p0 + at_long - 1, row_long = lane_value(row, at_long);
     const int row_end = pos[row_long + 1];
     int end_long = P;
-    if (grain > 0) end_long = shares_before(row_end - pos[0], grain);
+    if (grain > 0) end_long = shares_before(row_end, grain);           // (pos[0] = 0)
     else {
         int lo = first_long + 1, hi = P;               // the first partition that starts at or behind the row's end
         while (lo < hi) {

@@ -334,8 +334,7 @@ spmv_fixup_kernel(T *__restrict__ y, int P, const T *__restrict__ carry_val,
         // so the rest of the run is known without looking: independent loads, eight or
         // (long runs: a row of a million non-zeros has 2000 carries) 32 chunks of 64 in
         // flight, added in a fixed order
-        const int base = pos[0];
-        int last = shares_before(pos[r_last + 1] - base, grain) - 1;
+        int last = shares_before(pos[r_last + 1], grain) - 1;          // (pos[0] = 0)
         if (last > P - 1) last = P - 1;
         T acc[8];
 #pragma unroll
