@@ -176,11 +176,6 @@ __device__ inline unsigned long long lane_word(unsigned long long v, int from)
 // The value of the next lane (the last one: of b's first lane); of lane `from`.
 __device__ inline int next_lane(int a, int b) { return lane_after(a, __builtin_amdgcn_readlane(b, 0)); }
 __device__ inline float next_lane(float a, float b) { return __int_as_float(next_lane(__float_as_int(a), __float_as_int(b))); }
-__device__ inline double next_lane(double a, double b)
-{
-    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
-    return __longlong_as_double((long long)next_lane((int)(x >> 32), (int)(y >> 32)) << 32 | (unsigned)next_lane((int)(unsigned)x, (int)(unsigned)y));
-}
 __device__ inline int lane_at(int v, int from) { return __builtin_amdgcn_ds_bpermute(from << 2, v); }
 __device__ inline float lane_at(float v, int from) { return __int_as_float(lane_at(__float_as_int(v), from)); }
 __device__ inline double lane_at(double v, int from)
@@ -1607,7 +1602,9 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
                     if (xj == 0ull) continue;  // (uniform)
                     asm volatile("");          // (a branch it stays: all of them without one need too many registers)
                     const T a = val[j], b = j + 1 < R ? val[j + 1 < R ? j + 1 : j] : tail;
-                    const T from = K <= 2 && sizeof(T) == 4 ? next_lane(a, b) : lane_at(lane < g ? b : a, (lane + g) & (NACHO_WAVE - 1));
+                    T from;
+                    if constexpr (K <= 2 && sizeof(T) == 4) from = next_lane(a, b);
+                    else from = lane_at(lane < g ? b : a, (lane + g) & (NACHO_WAVE - 1));
                     val[j] = my_bit(xj) ? val[j] + from : val[j];       // (a head is nobody's equal key)
                 }
             }
