@@ -46,9 +46,10 @@ check_compressed_kernel(const int32_t *__restrict__ pos, const int32_t *__restri
         const int src = __ffsll((long long)todo) - 1;
         todo &= todo - 1;
         const int lo = __shfl(a, src, NACHO_WAVE), hi = __shfl(b, src, NACHO_WAVE);
-        for (int q = lo + lane; q < hi; q += NACHO_WAVE) {
+        // (unsigned: the step behind the last position may lie past 2^31)
+        for (unsigned q = (unsigned)lo + (unsigned)lane; q < (unsigned)hi; q += NACHO_WAVE) {
             const int c = crd[q];
-            if (c < 0 || (int64_t)c >= extent || (q > lo && crd[q - 1] >= c)) rep.bad(t, m, q);
+            if (c < 0 || (int64_t)c >= extent || (q > (unsigned)lo && crd[q - 1] >= c)) rep.bad(t, m, (int64_t)q);
         }
     }
 }

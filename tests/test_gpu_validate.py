@@ -78,3 +78,16 @@ def test_planted_violations_are_flagged(name, which, how):
     status, info = nb.nacho_validate([make(arrs)])
     assert status == -1, (name, how)
     assert info[0] == 0 and info[1] >= 0 and info[2] >= 0
+
+
+def test_positions_up_to_the_last_one():
+    """2^31 - 1 stored coordinates, the most an operand has; a violation at the last of them."""
+    rows, cols = 2048, 1 << 20
+    nnz = rows * cols - 1
+    pos = torch.arange(rows + 1, dtype=torch.int64, device="cuda").mul_(cols).clamp_(max=nnz).to(torch.int32)
+    crd = torch.arange(cols, dtype=torch.int32, device="cuda").repeat(rows)[:nnz]
+    op = nb.csr(pos, crd, rows, cols)
+    print("validate: positions to the last one", flush=True)
+    assert nb.nacho_validate([op]) == (0, (-1, -1, -1))
+    crd[-1] = cols
+    assert nb.nacho_validate([op]) == (-1, (0, 1, nnz - 1))
