@@ -442,7 +442,7 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     KeyT *keys = w.keys;
     uint32_t *cols = reinterpret_cast<uint32_t *>(w.keys);                  // staged columns (32-bit keys: the keys)
     uint32_t *wide_rows = reinterpret_cast<uint32_t *>(w.keys) + S::kWords; // 64-bit keys: row fields of the row starts
-    const int cb = arg_ptr->fields.cb, jb = arg_ptr->fields.jb;
+    const int cb = arg_ptr->fields.cb, jb = arg_ptr->fields.jb, ahead = arg_ptr->fields.touch;
     const KeyT col_mask = (KeyT(1) << cb) - KeyT(1);
     const KeyT slice_mask = (KeyT(1) << (cb + jb)) - KeyT(1);
     typedef const NACHO_GLOBAL int32_t *Ints;
@@ -1098,20 +1098,23 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     constexpr bool kTouch = !kMul && (kCoo || kCsf) && K <= 3;
     int touched[kTouch ? K : 1];
     if constexpr (kTouch) {
-        const bool touch = arg_ptr->fields.touch != 0;
-        int from = 0;                          // (the threads are shared out over the operands' lines)
 #pragma unroll
-        for (int t = 0; t < K; ++t) {
-            touched[t] = 0;
-            const int len = touch ? of(len_v, t) : 0;
-            if (len == 0) continue;
-            constexpr int kLine = 128 / (int)sizeof(T);
-            const int q = of(q_v, t), lines = (int)((unsigned)(q + len - 1) / kLine - (unsigned)q / kLine) + 1;
-            int i = tid - from;
-            i += i < 0 ? kThreads : 0;
-            const int at = i * kLine < len ? i * kLine : len - 1;
-            if (i < lines) touched[t] = reinterpret_cast<const NACHO_GLOBAL int *>(global_ptr<T>((unsigned long long)(uintptr_t)arg_ptr->vals.v[t]) + q)[at * (int)(sizeof(T) / 4)];
-            from = (from + lines) & (kThreads - 1);
+        for (int t = 0; t < K; ++t) touched[t] = 0;
+        if (ahead) {                           // (uniform)
+            int from = 0;                      // (the threads are shared out over the operands' lines)
+#pragma unroll
+            for (int t = 0; t < K; ++t) {
+                const int len = of(len_v, t);
+                if (len == 0) continue;
+                constexpr int kLine = 128 / (int)sizeof(T);
+                const int q = of(q_v, t), lines = (int)((unsigned)(q + len - 1) / kLine - (unsigned)q / kLine) + 1;
+                int i = tid - from;
+                i += i < 0 ? kThreads : 0;
+                const int at = i * kLine < len ? i * kLine : len - 1;
+                const auto values = global_ptr<T>((unsigned long long)(uintptr_t)arg_ptr->vals.v[t]) + q;
+                if (i < lines) touched[t] = reinterpret_cast<const NACHO_GLOBAL int *>(values)[at * (int)(sizeof(T) / 4)];
+                from = (from + lines) & (kThreads - 1);
+            }
         }
     }
 
@@ -1407,10 +1410,11 @@ __device__ __forceinline__ void merge_partition(ArgPtr arg_ptr, TileOf<FMT, T, K
     // Not before the counts are published: asking takes one to ten microseconds where the memory pipeline is full, and everybody
     // behind this workgroup waits for them (three vectors, 11M entries: 71.0 to 68.6 us; two DCSR matrices of 20M: 175 to 168).
     KeyT key[kMul ? NP : R];
-    if constexpr (kTouch) {
+    if constexpr (kTouch)
+        if (ahead) {                           // (uniform; a call that asks for nothing does not wait here either)
 #pragma unroll
-        for (int t = 0; t < K; ++t) asm volatile("" ::"v"(touched[t]));        // (nobody's words, but the loads have to stay)
-    }
+            for (int t = 0; t < K; ++t) asm volatile("" ::"v"(touched[t]));    // (nobody's words, but the loads have to stay)
+        }
     if constexpr (!kMul) if (n > 0) {
         unsigned o[R];
         orders(o);
