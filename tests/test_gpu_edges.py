@@ -636,3 +636,33 @@ def test_spmv_with_and_without_a_partition_kernel(dtype, nnz, n_rows, n_cols):
     y = spmv._check(A, x, 0, "without")
     wider = spmv._check(dict(A, n_cols=n_cols + 1), np.append(x, dtype(1)), 0, "with")
     assert np.array_equal(y.view(np.uint8), wider.view(np.uint8))
+
+
+# entries of the operands: the last one has no partner in the merge's first round (five: the fifth), or the one before it has none because
+# an operand is empty; a full short partition (1472 entries, less one an operand) and shares of more
+LONE = [(734, 734, 1), (1, 1, 1467), (1, 734, 734), (700, 0, 769), (0, 1, 1468), (5, 0, 0, 1463), (3, 700, 0, 765),
+        (366, 366, 366, 368, 1), (1, 1, 1, 1, 1463), (500, 0, 0, 0, 967), (300, 0, 400, 0, 767), (200, 200, 200, 200, 200, 200, 265)]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("scale", [1, 2047, 5000])         # one short partition; middle ones; long ones (of doubles: middle again)
+def test_runs_without_a_partner(scale, dtype):
+    """Sums and products of three to seven operands, vectors and coordinate lists (one short partition of these with 64-bit keys too);
+    operands share entries."""
+    rng = np.random.default_rng(scale)
+    for counts in LONE if scale == 1 else LONE[:2] + LONE[7:9]:
+        total = scale * sum(counts)
+        extent = 4 * total
+        pool = rng.permutation(extent).astype(np.int32)
+        vs = [np.sort(pool[:scale * n] if t % 2 == 0 else pool[scale * n // 2:scale * n // 2 + scale * n]) for t, n in enumerate(counts)]
+        vals = [rng.uniform(-1, 1, len(v)).astype(dtype) for v in vs]
+        add.check_vec(vs, vals, extent, 0, "lone run")
+        mul.check_vec(vs, vals, extent, 0, "lone run")
+        far = (2**31 - 1) // extent
+        layouts = [((extent // 1000 + 1, 1000), lambda v: [v // 1000, v % 1000])]
+        if scale == 1:
+            layouts.append(((2**31 - 1, 2**31 - 1), lambda v: [v * far, v % 1000 * far]))
+        for shape, place in layouts:
+            lists = [np.stack(place(v.astype(np.int64)), 1) for v in vs]
+            for fn, ref in ((nb.nacho_spadd_k, oracle.spadd_coo), (nb.nacho_spmul_k, oracle.spmul_coo)):
+                coo._check(fn, ref, lists, vals, shape, 0, "lone run")
