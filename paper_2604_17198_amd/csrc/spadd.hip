@@ -97,9 +97,9 @@ MergeFields merge_fields(int fmt, int dtype, int k, int64_t rows, int64_t cols, 
         return f.limit == 0 || (fmt == SPADD_CSF3 && rows > (int64_t)1 << (32 - f.jb)) ||
                (rows > (int64_t)f.limit && span > (int64_t)(f.limit / 4));
     };
-    // Tensors whose middle partitions would need 64-bit keys stay with short ones of 32-bit keys as long as those are one round (two, three, five of 1.3M
-    // entries in all, 2000 x 2000 x 2000, us: 31.3, 37.5, 48.0 and 33.7, 42.3, 52.9 with 64-bit keys).  Matrices do not (DCSR, coordinate lists of 1.4M, 400,000 rows, 1M
-    // columns, short against 64-bit keys: 31.7 and 29.9, 24.9 and 21.6).
+    // Tensors whose middle partitions would need 64-bit keys stay with short ones of 32-bit keys as long as those are one round (two, three,
+    // five of 1.3M entries in all, 2000 x 2000 x 2000, us: 31.3, 37.5, 48.0 and 33.7, 42.3, 52.9 with 64-bit keys).  Matrices do not (DCSR,
+    // coordinate lists of 1.4M, 400,000 rows, 1M columns, short against 64-bit keys: 31.7 and 29.9, 24.9 and 21.6).
     if (fmt == SPADD_CSF3 && f.size == MERGE_MIDDLE && fits(MERGE_SHORT, resident) && needs_wide(MERGE_MIDDLE) && !needs_wide(MERGE_SHORT))
         f.size = MERGE_SHORT;
     if (needs_wide(f.size)) {

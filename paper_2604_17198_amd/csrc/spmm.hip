@@ -162,8 +162,8 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
         };
         if constexpr (kFew) {
             // The call is as long as one wavefront's chain of round trips: 64 probes a round instead of 32, and where the non-zeros are known
-            // without their rows both are asked for at once (20,000 non-zeros, 37 floats 10.0 to 9.1 us, 100,000, 16 doubles 10.6 to 9.5; with millions of non-zeros the
-            // probes' lines cost more than the round: 10M, 4 floats 100 and 114).
+            // without their rows both are asked for at once (20,000 non-zeros, 37 floats 10.0 to 9.1 us, 100,000, 16 doubles 10.6 to 9.5; with
+            // millions of non-zeros the probes' lines cost more than the round: 10M, 4 floats 100 and 114).
             RowWindow wa{0, n_rows}, wb{0, n_rows};
             const int probe = wa.load(pos, n_rows);    // (the first probes are the same for both boundaries)
             if (kForm == SPMM_SMALL) {
@@ -359,9 +359,10 @@ spmm_exec_kernel(const int32_t *__restrict__ pos, const int32_t *__restrict__ cr
 // than a 16-byte piece has) per workgroup.  The carries of a row lie in consecutive partitions; the lanes of the first one add the
 // run to the row of C.  A run of more than kShort carries (there is at most one per workgroup: it is longer than the workgroup's
 // partitions) is added by the whole workgroup, every group an equal share of it: the largest row of 30M non-zeros has a thousand,
-// which one wavefront, a row of carries at a time, took 35 us for (half as many).  The order of the additions is fixed.  Bound: round trips, of which there are two: the rows of
-// the carries and the first of each, then the rows of C.  (Where the run ends was looked up in the matrix, in front of the carries: 156k
-// partitions of 64 floats 26.8 us, so 20.9; calls of 100k non-zeros 9.6, so 9.0.)  Loads are as wide as the lanes' pieces.
+// which one wavefront, a row of carries at a time, took 35 us for (half as many).  The order of the additions is fixed.
+// What bounds it: round trips, of which there are two: the rows of the carries and the first of each, then the rows of C.  (Where the
+// run ends was looked up in the matrix, in front of the carries: 156k partitions of 64 floats 26.8 us, so 20.9; calls of 100k
+// non-zeros 9.6, so 9.0.)  Loads are as wide as the lanes' pieces.
 constexpr int kFixCols = 64, kShort = 32;
 
 template <typename T, int V>

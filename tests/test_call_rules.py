@@ -19,10 +19,12 @@ def ask(tmp_path_factory):
 
     def values(expressions):
         source, program = where / "rules.hip", where / "rules"
-        lines = "".join(f'std::printf("%lld\\n", (long long)({e}));' for e in expressions)
-        source.write_text('#include <cstdio>\n#include "common.hpp"\n#include "kernels.hpp"\nusing namespace nacho;\nint main() {' + lines + "}\n")
-        subprocess.run([build._hipcc(), "-O0", "-std=c++17", "--offload-host-only", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
-                        str(source), "-L", build.PKG, "-l:libnacho.so", f"-Wl,-rpath,{build.PKG}", "-o", str(program)], check=True, capture_output=True, text=True)
+        lines = "\n".join(f'    std::printf("%lld\\n", (long long)({e}));' for e in expressions)
+        source.write_text('#include <cstdio>\n#include "common.hpp"\n#include "kernels.hpp"\nusing namespace nacho;\n'
+                          f"int main()\n{{\n{lines}\n}}\n")
+        subprocess.run([build._hipcc(), "-O0", "-std=c++17", "--offload-host-only", "-I", os.path.join(build.ROOT, "include"),
+                        "-I", build.CSRC, str(source), "-L", build.PKG, "-l:libnacho.so", f"-Wl,-rpath,{build.PKG}",
+                        "-o", str(program)], check=True, capture_output=True, text=True)
         out = subprocess.run([str(program)], check=True, capture_output=True, text=True, timeout=60).stdout
         return [int(v) for v in out.split()]
 
